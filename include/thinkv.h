@@ -109,10 +109,7 @@ typedef struct {
  *                   position ever written into the page (-1 = none).  Sliding-window attention
  *                   skips pages whose bound lies before the window without reading slot_pos.
  *   n_live          [max_seqs][n_layers] live tokens
- *   work_counters   [n_layers][max_seqs][n_kv_heads][4] scratch of thinkv_decode_attention: per
- *                   (layer, query index, kv-head) the heads of three work queues (one per type)
- *                   and a spare word; zero between calls (init zeroes them, every call leaves
- *                   them zero), so two decode calls on one (view, layer) must not overlap
+ *   work_counters   [n_layers][max_seqs][n_kv_heads][4] reserved; zero (init zeroes them, no call writes them)
  *   append_counters [max_seqs] scratch of thinkv_append_quantized (arrival counts of the
  *                   workgroups of a sequence); zero between calls
  *   dev_status      [max_seqs * n_layers + 1] THINKV_ST_* flags

@@ -61,13 +61,12 @@ static int check_view(const thinkv_view* v) {
   return THINKV_OK;
 }
 
-// Work-item sizes.  The fast kernel's items are single waves; the
-// plain kernel's are workgroups of four waves, three to a compute unit (the fast kernel: two or three waves a SIMD, by head_dim).  An item pays a fixed
-// price (query set-up, three type switches, its partial row), so it is given at least a few page
+// Work-item sizes of the window kernel (items are single waves), of the plain kernel (workgroups of four waves, three to a
+// compute unit) and, with fast = true and no window, the row count the workspace of a full-attention call is sized for.  An
+// item pays a fixed price (query set-up, three type switches, its partial row), so it is given at least a few page
 // pairs.  Where the launch has few (query, kv-head) pairs, the items of the longest sequence fill
 // the machine exactly once; where it has many, an item per so many pages, about sixteen rounds of
-// them if every sequence were as long as the host's bound: on full-attention layers the items of
-// a head share its queues, so late items simply find less to do.
+// them if every sequence were as long as the host's bound.
 // A sliding-window layer is another matter: only the pages that hold one of the last W positions
 // are worked on, the rest of the page list is merely scanned (a few bytes a page), so the fixed
 // price of an item dominates: an item scans at least 64 pages per wave.
@@ -89,7 +88,7 @@ struct ItemSizing {
 
 static ItemSizing size_items(const thinkv_config& c, int B, int max_ctx_pages, int window, bool fast) {
   const int64_t heads = (int64_t)B * c.n_kv_heads;
-  const int64_t resident = fast ? (int64_t)compute_units() * 4 * decode_waves_per_simd(c.head_dim) : (int64_t)compute_units() * 3;
+  const int64_t resident = fast ? (int64_t)compute_units() * 4 * (c.head_dim == 64 ? 3 : 2) : (int64_t)compute_units() * 3;
   const int least = window > 0 ? (fast ? 64 : 256) : (fast ? 16 : 32);   // fewest pages worth an item
   int64_t cap = ((int64_t)max_ctx_pages + least - 1) / least;
   if (cap < 1) cap = 1;
@@ -122,6 +121,39 @@ static int64_t rows_bound(const thinkv_config& c, int B, int max_ctx_pages) {
       if (z.n_rows > most) most = z.n_rows;
     }
   return most;
+}
+
+// Full-attention layers of the fast kernel: an item is a workgroup of W waves.  Where there are at most as many heads as
+// compute units, a workgroup is a compute unit's worth of waves (fewer on short contexts: a wave is worth at least a
+// chunk of pages), and a head has as many as fill the machine once.  Where there are more, workgroups of four, several to a
+// compute unit, so that one's start and end are covered by the others', and an item per so many pages: about sixteen
+// rounds of them if every sequence were as long as the host's bound, but no fewer than 64 pages a wave.
+static ItemSizing size_stream(const thinkv_config& c, int B, int max_ctx_pages, int* waves) {
+  const int64_t heads = (int64_t)B * c.n_kv_heads;
+  const int64_t full = 4 * decode_waves_per_simd(c.head_dim, c.format == THINKV_FMT_FP), resident = (int64_t)compute_units() * full;
+  const int64_t pages = max_ctx_pages > 0 ? max_ctx_pages : 1;
+  const int64_t most = (pages + 7) / 8;
+  int64_t W, per_head, cap;
+  if (heads <= compute_units()) {
+    W = most < full ? most : full;
+    per_head = resident / (heads * W);
+    cap = (pages + 16 * W - 1) / (16 * W);
+  } else {
+    W = most < 4 ? most : 4;
+    per_head = (16 * resident + heads * W - 1) / (heads * W);
+    cap = (pages + 64 * W - 1) / (64 * W);
+  }
+  if (per_head > cap) per_head = cap;
+  const int64_t room = rows_bound(c, B, max_ctx_pages) / heads;   // what the workspace is sized for (at least 1)
+  if (per_head > room) per_head = room;
+  if (per_head > kMaxRowsPerHead) per_head = kMaxRowsPerHead;
+  if (per_head < 1) per_head = 1;
+  *waves = (int)W;
+  ItemSizing z;
+  z.per_head = (int)per_head;
+  z.n_rows = (int)(per_head * heads);
+  z.ppi = (int)((pages + per_head - 1) / per_head);
+  return z;
 }
 
 static size_t partial_bytes_of(const thinkv_config& c, int64_t rows) {
@@ -158,7 +190,9 @@ static int decode_common(const thinkv_view* view, int32_t layer, const void* q, 
   a.window = window;
   a.q_dtype = q_dtype;
   a.out_dtype = out_dtype;
-  const ItemSizing z = size_items(view->cfg, B, max_ctx_pages, window, fast);
+  a.waves = 0;
+  const ItemSizing z = fast && window == 0 ? size_stream(view->cfg, B, max_ctx_pages, &a.waves) : size_items(view->cfg, B, max_ctx_pages, window, fast);
+  if (z.n_rows > rows_bound(view->cfg, B, max_ctx_pages)) return THINKV_E_WORKSPACE;   // cannot happen: a launch never has more rows than the workspace
   a.n_rows = z.n_rows;
   a.per_head = z.per_head;
   a.ppi = z.ppi;
@@ -370,7 +404,7 @@ int thinkv_probe_stream_pages(const thinkv_view* view, int32_t layer, const int3
   if (B == 0) return THINKV_OK;
   if (!seq_ids || !checksum) return THINKV_E_INVALID_ARG;
   // four waves to a workgroup, as many workgroups as fill the machine at the occupancy of the attention kernel
-  int64_t per_head = (int64_t)compute_units() * decode_waves_per_simd(view->cfg.head_dim) / ((int64_t)B * view->cfg.n_kv_heads);
+  int64_t per_head = (int64_t)compute_units() * (view->cfg.head_dim == 64 ? 3 : 2) / ((int64_t)B * view->cfg.n_kv_heads);
   if (per_head < 1) per_head = 1;
   return launch_probe_stream(*view, layer, seq_ids, B, (int)per_head, checksum, (hipStream_t)stream);
 }

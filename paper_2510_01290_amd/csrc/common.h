@@ -26,8 +26,8 @@ struct BlockGeom {
 // fmt THINKV_FMT_FP: the code regions are the same; a meta region is one E4M3 scale byte per (slot, group
 // of 16 channels), byte group16 * 16 + slot, and there is none for the 8-bit type (per-tensor scale).
 constexpr int kGroupFp = 16;
-__host__ __device__ inline BlockGeom block_geom(int bits, int D, int fmt = THINKV_FMT_INT) {
-  BlockGeom g;
+__host__ __device__ constexpr BlockGeom block_geom(int bits, int D, int fmt = THINKV_FMT_INT) {
+  BlockGeom g{};
   g.chunk_bytes = (D / kGroup) * bits;
   g.codes_bytes = 64 * g.chunk_bytes;
   g.meta_bytes = fmt == THINKV_FMT_FP ? (bits == 8 ? 0 : kPage * (D / kGroupFp)) : kPage * (D / kGroup) * 4;

@@ -7,23 +7,19 @@
 //
 // How many items a head gets is decided on the device from its page count, identically by every
 // kernel of a call: an item per `ppi` pages, at most `per_head` (both chosen by the host); the items
-// of a head that is short do not exist (their waves leave at once).  On full-attention layers the
-// fast kernel's items do not own pages: the items of a head draw page pairs from shared queues, so
-// an item is a worker and its count a share of the machine.  Elsewhere item j of n takes the same
-// fraction [j/n, (j+1)/n) of each of the three per-type lists.
+// of a head that is short do not exist (their waves leave at once).  Item j of n takes the same fraction
+// [j/n, (j+1)/n) of each of the three per-type lists.
 #pragma once
 #include "common.h"
 
-// waves per SIMD the fast kernel is built for (its register budget: 256 registers a lane at head_dim 128, where a
-// pair of 8-bit pages alone takes 48 and two pairs are held; half the tiles and half the page bytes at head_dim 64
-// leave room for a third wave); the host sizes launches with the same numbers
-#ifndef TKV_WAVES_128
-#define TKV_WAVES_128 2
-#endif
-#ifndef TKV_WAVES_64
-#define TKV_WAVES_64 3
-#endif
-__host__ __device__ constexpr int decode_waves_per_simd(int head_dim) { return head_dim == 64 ? TKV_WAVES_64 : TKV_WAVES_128; }
+// Waves per SIMD the fast kernel of full-attention layers is built for, and the LDS ring of a wave: together they take
+// 144 KB of the compute unit's 160.  More waves hide more of each other's latency, a deeper ring keeps more bytes in
+// flight; where the line lies is measured: integer formats at head_dim 128 (18 KB: two pairs of 8-bit, three of 4-bit,
+// six of 2-bit pages) 16 x 8k tokens 43 us at two waves, 64 at three; head_dim 64 (12 KB: two, four, eight pairs)
+// 287 us at three, 328 at four for 128 x 4k..32k tokens; the paper's formats at 128, whose registers fit a third wave and
+// whose arithmetic needs it, 132 at three and 137 at two.  The host sizes launches with the same numbers.
+__host__ __device__ constexpr int decode_waves_per_simd(int head_dim, bool fp) { return (head_dim == 64 ? 3 : 2) + (fp ? 1 : 0); }
+__host__ __device__ constexpr int stream_ring_bytes(int head_dim, bool fp) { return 147456 / (4 * decode_waves_per_simd(head_dim, fp)); }
 
 namespace thinkv {
 
@@ -36,7 +32,7 @@ struct DecodeArgs {
   float* partial;       // [n_rows][G][D + 4]
   int32_t* alloc;       // [B * n_kv_heads][2]: first row and number of rows of each head, written by its item 0
   int layer, B, window, q_dtype, out_dtype;
-  int n_rows;           // items (grid extent of the fast kernel, in waves), = per_head * B * n_kv_heads
+  int n_rows;           // items, = per_head * B * n_kv_heads
   int per_head;         // the most items a head can have
   int ppi;              // pages per item
   float scale_log2e;    // softmax_scale * log2(e)
@@ -45,6 +41,7 @@ struct DecodeArgs {
   int64_t stat_stride;  // floats per (query, kv-head): 16 * max_ctx_pages
   float* sparsity;      // [B]
   int direct;           // 1: every head has a single item and the attention kernel writes out / lse itself
+  int waves;            // full-attention layers of the fast kernel: waves of an item's workgroup
 };
 
 constexpr int kMaxRowsPerHead = 1024;
@@ -55,12 +52,15 @@ struct ItemLoc {
   int row0;     // the head's first partial row
 };
 
+// a value that is the same in all lanes but was read by a vector load, as a scalar: what is computed from it stays scalar
+__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+
 __device__ inline int seq_pages(const thinkv_view& v, int layer, int seq, int* np) {
   const thinkv_config& c = v.cfg;
   int tot = 0;
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    np[k] = (seq >= 0 && seq < c.max_seqs) ? v.n_pages[npages_index(c, seq, layer, k)] : 0;
+    np[k] = (seq >= 0 && seq < c.max_seqs) ? uniform(v.n_pages[npages_index(c, seq, layer, k)]) : 0;
     tot += np[k];
   }
   return tot;
@@ -73,14 +73,14 @@ __device__ inline ItemLoc locate_item(const thinkv_view& v, const DecodeArgs& a,
   const thinkv_config& c = v.cfg;
   const int H = c.n_kv_heads, heads = H * a.B;
   ItemLoc it;
-  it.j = id / heads;
-  int rest = id % heads - it.j % heads;
+  it.j = uniform(id / heads);   // (divisions are vector arithmetic)
+  int rest = id - it.j * heads - uniform(it.j % heads);
   if (rest < 0) rest += heads;
-  it.hkv = rest % H;
-  it.b = rest / H;
+  it.b = uniform(rest / H);
+  it.hkv = rest - it.b * H;
   int np[3];
-  const int tot = seq_pages(v, a.layer, a.seq_ids[it.b], np);
-  int n = (int)(((int64_t)tot + a.ppi - 1) / a.ppi);
+  const int tot = seq_pages(v, a.layer, uniform(a.seq_ids[it.b]), np);
+  int n = uniform((int)(((int64_t)tot + a.ppi - 1) / a.ppi));
   n = n < 1 ? 1 : (n > a.per_head ? a.per_head : n);
   it.n = n;
   it.row0 = rest * a.per_head;

@@ -49,7 +49,8 @@ template <int D, int BITS, int NSET>
 struct PageRegsFp {
   static constexpr int CW = (D / 32) * BITS / 4;
   uint32_t kw[CW], vw[CW];
-  uint32_t km[NSET], vm[NSET];   // the E4M3 scale bytes of (the slice's group, the lane's four slots); unused at 8 bits
+  uint8_t ks[NSET];    // the E4M3 scale byte of (the slice's group, the lane's token); unused at 8 bits
+  uint32_t vm[NSET];   // the E4M3 scale bytes of (the slice's group, the lane's four slots); unused at 8 bits
 };
 template <int D, int BITS, int NSET>
 struct PairRegsFp {
@@ -72,50 +73,44 @@ __device__ __forceinline__ void scales_to_halves(uint32_t bytes, uint32_t& lo, u
 // STAT: besides attending, leave the group-pooled score of every visited slot for the attention-sparsity statistic
 // (as the integer-format runner does).
 template <int D, int BITS, int GP, bool STAT>
-struct ClassRunnerFp : PairWalk<ClassRunnerFp<D, BITS, GP, STAT>, PairRegsFp<D, BITS, ColsFp<D, GP>::NSET>> {
+struct ClassRunnerFp {
   using CL = ColsFp<D, GP>;
-  static constexpr int NG32 = D / 32, NM = D / 16, CS = CL::CS, NSET = CL::NSET;
-  static constexpr bool kHalfPipe = false;
-  static constexpr int kLift = 14;   // 2^14 * 448 * 2^-8 < 65504: the lifted second operand of the value products cannot overflow
+  static constexpr int kD = D, kBlockBytes = block_geom(BITS, D, THINKV_FMT_FP).block_bytes;
+  static constexpr bool kStat = STAT, kFp = true;
+  static constexpr int NG32 = D / 32, NM = D / 16, CS = CL::CS, NSET = CL::NSET, NS = GP / 4;
+  static constexpr int kLift = 14;
+  static constexpr float kSlack = 1.0f;   // 2^(14 + 1) * 448 * 2^-8 < 65504: the lifted second operand of the value products cannot overflow
   using F = FldFp<BITS>;
   using Pair = PairRegsFp<D, BITS, NSET>;
-  using Walk = PairWalk<ClassRunnerFp<D, BITS, GP, STAT>, Pair>;
-  using Walk::v;
-  using Walk::a;
-  using Walk::cls;
-  using Walk::hkv;
-  using Walk::lane;
-  WaveState<D, NSET>& st;
-  int qd, n;
-  int meta_off[NSET];   // byte offset, inside a meta region, of the lane's four scale bytes per column set
-  H8 bq[NG32];          // B operands of the score MFMAs: q over the half of the 32 channels that is the slice's group, zeros elsewhere
-  float kappa;          // MFMA score units -> log2 domain
+  const int lane;
+  WaveState<D, GP, NSET>& st;
+  Softmax<D, GP, NSET, STAT> sm;
+  int k_off[NSET], v_off[NSET];   // byte offset, inside a meta region, of the lane's scale byte (K) and of its four scale bytes (V) per column set
+  H8 bq[NG32];          // A operands of the score MFMAs: q over the half of the 32 channels that is the slice's group, zeros elsewhere
   float tile_out;       // tiles -> absolute units / 2^24 when the type is left
   float neg1;
-  float* stat;          // STAT: pooled scores of this type's page list, 16 per page
-  int stat_room;        // STAT: pages of this list the buffer has room for
-  bool head_ok;         // this lane's column belongs to a query head of the group
 
-  __device__ __forceinline__ ClassRunnerFp(WaveState<D, NSET>& st_, const thinkv_view& v_, const DecodeArgs& a_, int cls_, const int32_t* tab_,
-                                           int p0_, int p1_, int hkv_, int G, const QRegsFp<NSET>& qr, int qpos_, float* stat_, int stat_room_)
-      : Walk(v_, a_, cls_, hkv_, qpos_, tab_, p0_, p1_), st(st_), stat(stat_), stat_room(stat_room_) {
-    qd = lane >> 4;
-    n = lane & 15;
+  __device__ __forceinline__ ClassRunnerFp(WaveState<D, GP, NSET>& st_, const thinkv_config& c, const DecodeArgs& a, int G, const QRegsFp<NSET>& qr, float* stat_,
+                                           int stat_room_)
+      : lane(threadIdx.x & 63), st(st_), sm(st_, threadIdx.x & 63, G, stat_, stat_room_) {
+    const int qd = lane >> 4, n = lane & 15;
     const int gl = n / GP;
-    head_ok = n % GP < G;
     const int glc = gl < CS ? gl : CS - 1;
+    const int gk = GP == 4 ? qd : qd >> 1, gkc = gk < CS ? gk : CS - 1;   // slice of the rows of this lane's quad
     neg1 = -1.0f;
     asm volatile("" : "+v"(neg1));
-    const thinkv_config& c = v.cfg;
     if constexpr (BITS == 8) {
-      kappa = 256.0f * c.fp8_scale[0] * a.scale_log2e;
+      sm.kappa = 256.0f * c.fp8_scale[0] * a.scale_log2e;
       tile_out = c.fp8_scale[1] * (1.0f / (float)(1 << 16)) * (1.0f / (float)(1 << kLift));
     } else {
-      kappa = 4194304.0f * a.scale_log2e;                                   // 2^14 (codes) * 2^8 (scales)
+      sm.kappa = 4194304.0f * a.scale_log2e;                                // 2^14 (codes) * 2^8 (scales)
       tile_out = 0.25f * (1.0f / (float)(1 << kLift));                      // 2^(14 + 8 - 24 - lift)
     }
 #pragma unroll
-    for (int s = 0; s < NSET; ++s) meta_off[s] = (s * CS + glc) * kPage + 4 * qd;
+    for (int s = 0; s < NSET; ++s) {
+      k_off[s] = (s * CS + gkc) * kPage + n;
+      v_off[s] = (s * CS + glc) * kPage + 4 * qd;
+    }
 #pragma unroll
     for (int g = 0; g < NG32; ++g) {
       const int set = (2 * g) / CS;
@@ -124,53 +119,48 @@ struct ClassRunnerFp : PairWalk<ClassRunnerFp<D, BITS, GP, STAT>, PairRegsFp<D, 
       for (int w = 0; w < 4; ++w) bq[g].u[w] = on ? qr.q[set].u[w] : 0u;
     }
     // enter the type: the denominator and the tiles take the lift, the tiles the units of the type
-    st.l *= (float)(1 << kLift);
+    sm.scale_sums((float)(1 << kLift));
     const float in = 1.0f / tile_out;
 #pragma unroll
     for (int mb = 0; mb < NM; ++mb) st.o[mb] *= in;
   }
   __device__ __forceinline__ void leave() {
-    st.l *= 1.0f / (float)(1 << kLift);
+    sm.scale_sums(1.0f / (float)(1 << kLift));
 #pragma unroll
     for (int mb = 0; mb < NM; ++mb) st.o[mb] *= tile_out;
   }
 
-  __device__ __forceinline__ void issue_loads(Pair& r, const PairIds& id) const {
-    constexpr int CW = PageRegsFp<D, BITS, NSET>::CW;
-    const int H = v.cfg.n_kv_heads;
+  template <class P>
+  __device__ __forceinline__ void load_k(Pair& r, P blk_a, P blk_b) const {
+    keys_of(r.a, blk_a);
+    keys_of(r.b, blk_b);
+  }
+  template <class P>
+  __device__ __forceinline__ void load_v(Pair& r, P blk_a, P blk_b) const {
+    values_of(r.a, blk_a);
+    values_of(r.b, blk_b);
+  }
+  using Page = PageRegsFp<D, BITS, NSET>;
+  template <class P>
+  __device__ __forceinline__ void keys_of(Page& x, P blk) const {
     const BlockGeom g = block_geom(BITS, D, THINKV_FMT_FP);
-    const uint8_t* blk[2] = {v.arena[cls] + ((int64_t)id.pid_a * H + hkv) * g.block_bytes, v.arena[cls] + ((int64_t)id.pid_b * H + hkv) * g.block_bytes};
+    load_chunk<Page::CW>(x.kw, blk + g.k_codes, lane);
+    if constexpr (BITS != 8) {
 #pragma unroll
-    for (int pg = 0; pg < 2; ++pg) {
-      PageRegsFp<D, BITS, NSET>& x = pg ? r.b : r.a;
-      const uint32_t* kc = (const uint32_t*)(blk[pg] + g.k_codes) + lane * CW;
-      const uint32_t* vc = (const uint32_t*)(blk[pg] + g.v_codes) + lane * CW;
-      if constexpr (CW == 1) {
-        x.kw[0] = kc[0];
-        x.vw[0] = vc[0];
-      } else if constexpr (CW == 2) {
-        const uint2 p = ld8<true>(kc), q = ld8<true>(vc);
-        x.kw[0] = p.x; x.kw[1] = p.y;
-        x.vw[0] = q.x; x.vw[1] = q.y;
-      } else {
+      for (int s = 0; s < NSET; ++s) x.ks[s] = ld_piece<uint8_t>(blk + g.k_meta + k_off[s]);
+    }
+  }
+  template <class P>
+  __device__ __forceinline__ void values_of(Page& x, P blk) const {
+    const BlockGeom g = block_geom(BITS, D, THINKV_FMT_FP);
+    load_chunk<Page::CW>(x.vw, blk + g.v_codes, lane);
+    if constexpr (BITS != 8) {
 #pragma unroll
-        for (int i = 0; i < CW; i += 4) {
-          const uint4 p = ld16<true>(kc + i), q = ld16<true>(vc + i);
-          x.kw[i] = p.x; x.kw[i + 1] = p.y; x.kw[i + 2] = p.z; x.kw[i + 3] = p.w;
-          x.vw[i] = q.x; x.vw[i + 1] = q.y; x.vw[i + 2] = q.z; x.vw[i + 3] = q.w;
-        }
-      }
-      if constexpr (BITS != 8) {
-#pragma unroll
-        for (int s = 0; s < NSET; ++s) {
-          x.km[s] = *(const uint32_t*)(blk[pg] + g.k_meta + meta_off[s]);
-          x.vm[s] = *(const uint32_t*)(blk[pg] + g.v_meta + meta_off[s]);
-        }
-      }
+      for (int s = 0; s < NSET; ++s) x.vm[s] = ld_piece<uint32_t>(blk + g.v_meta + v_off[s]);
     }
   }
 
-  // scores of one page for this lane's four tokens, in MFMA units (times kappa = log2 domain)
+  // scores of one page for this lane's token and heads, in MFMA units (times kappa = log2 domain)
   __device__ __forceinline__ void page_scores(const PageRegsFp<D, BITS, NSET>& r, float* s) const {
     const float4v zero = {0.f, 0.f, 0.f, 0.f};
     float4v c[NSET];
@@ -181,7 +171,7 @@ struct ClassRunnerFp : PairWalk<ClassRunnerFp<D, BITS, GP, STAT>, PairRegsFp<D, 
       H8 ka;
 #pragma unroll
       for (int vv = 0; vv < 4; ++vv) ka.u[vv] = F::get(r.kw, 4 * g + vv);
-      c[set] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ka.h, bq[g].h, first ? zero : c[set], 0, 0, 0);
+      c[set] = __builtin_amdgcn_mfma_f32_16x16x32_f16(bq[g].h, ka.h, first ? zero : c[set], 0, 0, 0);
     }
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -190,70 +180,25 @@ struct ClassRunnerFp : PairWalk<ClassRunnerFp<D, BITS, GP, STAT>, PairRegsFp<D, 
 #pragma unroll
         for (int R = 0; R < 4; ++R) acc[R] = set == 0 ? c[set][R] : acc[R] + c[set][R];
       } else {
-        uint32_t lo, hi;
-        scales_to_halves(r.km[set], lo, hi);
-        acc[0] = fmaf(half_lo(lo), c[set][0], acc[0]);
-        acc[1] = fmaf(half_hi(lo), c[set][1], acc[1]);
-        acc[2] = fmaf(half_lo(hi), c[set][2], acc[2]);
-        acc[3] = fmaf(half_hi(hi), c[set][3], acc[3]);
+        const float sc = (float)__builtin_bit_cast(_Float16, (uint16_t)(r.ks[set] << 7));   // the scale times 2^-8
+#pragma unroll
+        for (int R = 0; R < 4; ++R) acc[R] = fmaf(sc, c[set][R], acc[R]);
       }
     }
-#pragma unroll
-    for (int R = 0; R < 4; ++R) {
-      float t = add_row_ror<8>(acc[R]);
-      if constexpr (GP == 4) t = add_row_ror<4>(t);
-      s[R] = t;
-    }
+    add_groups<GP>(acc, s);
   }
 
-  __device__ __forceinline__ void compute(const Pair& r, const PairIds& id) {
-    const uint32_t live_a = id.live_a, live_b = id.live_b;
-    float sa[4], sb[4];
+  float sa[NS], sb[NS];   // scores of the pair at hand
+  __device__ __forceinline__ void scores(const Pair& r, const PairIds& id) {
     page_scores(r.a, sa);
     page_scores(r.b, sb);
-    if ((live_a & live_b) != 0xFFFFu) {   // dead slots: score -inf, hence p = 0 (their stale codes and scales are finite)
-      const uint32_t la = (live_a >> (4 * qd)) & 0xFu, lb = (live_b >> (4 * qd)) & 0xFu;
-#pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4) {
-        sa[r4] = ((la >> r4) & 1u) ? sa[r4] : -INFINITY;
-        sb[r4] = ((lb >> r4) & 1u) ? sb[r4] : -INFINITY;
-      }
-    }
-    if constexpr (STAT) {
-      // pooled scores: maximum over the heads of the group, i.e. over the GP lanes of a slice (all slices hold the
-      // same totals); the lanes of column 0 store their four slots of each page
-      auto pooled = [&](const float* sc, int idx) {
-        float u[4];
-#pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) {
-          u[r4] = head_ok ? sc[r4] * kappa : -INFINITY;
-          u[r4] = max_dpp<0x4E>(max_dpp<0xB1>(u[r4]));
-          if constexpr (GP == 8) u[r4] = max_dpp<0x124>(u[r4]);
-        }
-        if (n == 0 && idx >= 0 && idx < stat_room) *(float4*)(stat + (int64_t)idx * kPage + 4 * qd) = make_float4(u[0], u[1], u[2], u[3]);
-      };
-      pooled(sa, id.idx_a);
-      pooled(sb, id.idx_b);
-    }
-    const float mx = fmaxf(fmaxf(fmaxf(sa[0], sa[1]), fmaxf(sa[2], sa[3])), fmaxf(fmaxf(sb[0], sb[1]), fmaxf(sb[2], sb[3]))) * kappa;
-    if (__any(mx > st.m)) {
-      const float m_new = fmaxf(st.m, col_max(mx));
-      const float m_sub = m_new == -INFINITY ? 0.f : m_new;
-      const float corr = __builtin_amdgcn_exp2f(st.m - m_sub);
-#pragma unroll
-      for (int mb = 0; mb < NM; ++mb) st.o[mb] *= corr;
-      st.l *= corr;
-      st.m = m_new;
-      st.m_sub = m_sub;
-    }
-    float pa[4], pb[4];
-    const float mref = st.m_sub - (float)kLift;
-#pragma unroll
-    for (int r4 = 0; r4 < 4; ++r4) {
-      pa[r4] = __builtin_amdgcn_exp2f(fmaf(sa[r4], kappa, -mref));
-      pb[r4] = __builtin_amdgcn_exp2f(fmaf(sb[r4], kappa, -mref));
-    }
-    st.l += ((pa[0] + pa[1]) + (pa[2] + pa[3])) + ((pb[0] + pb[1]) + (pb[2] + pb[3]));
+    sm.mask(sa, sb, id);
+    sm.reference(sa, sb, kSlack);
+  }
+  __device__ __forceinline__ void values(const Pair& r) {
+    float ea[NS], eb[NS], pa[4], pb[4];
+    sm.weights(sa, sb, (float)kLift, ea, eb, pa, pb);
+    sm.add(ea, eb);
     // values, per column set: B = two-term split of p * s_V, A = V codes
     H8 hi, lo;
 #pragma unroll

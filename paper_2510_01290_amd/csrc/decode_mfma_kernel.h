@@ -11,42 +11,43 @@
 // c * 2^(position-24); the power of two is folded into the query (for K) or into the output
 // scale (for V).  A quantisation group is 32 channels = the K extent of one MFMA.
 //
-// Column plan.  The 16 MFMA columns are cut into CS slices of GP columns (GP = 4 or 8 >= the
-// number G of query heads that share the kv-head); slice gl carries the G heads *for
-// quantisation group gl* (of the column set being worked on: D/32 groups = NSET sets of CS).
-// Scores: the query of group g is placed in slice g's columns only (zeros elsewhere) and the
-// MFMAs of the CS groups of a set accumulate into ONE 16x16 tile, tokens x (group, head).
-// Lane (column n, row quad qd) then applies, to its four tokens, the scale and zero-point of
-// ITS group -- lane-local binary32 arithmetic on values the lane loaded itself, no broadcast
-// -- and two DPP row rotations add the slices, leaving the complete score of head n % GP in
-// every slice.  That register layout is already the B-operand layout of the PV product.
-// Values: p * s_V(t, g) is likewise lane-local (each slice multiplies by its own group's
+// Column plan.  The 16 rows / columns of a tile that belong to queries are cut into CS slices of GP
+// (GP = 4 or 8 >= the number G of query heads that share the kv-head); slice gl carries the G heads *for
+// quantisation group gl* (of the set being worked on: D/32 groups = NSET sets of CS).
+// Scores: A = the query (row = (slice, head); the query of group g is placed in slice g's rows only, zeros
+// elsewhere), B = the K codes (column = token), so the MFMAs of the CS groups of a set accumulate into ONE
+// 16x16 tile, (group, head) x tokens.  Lane (token n, row quad qd) then applies the scale and zero-point of
+// ITS token and group -- lane-local binary32 arithmetic on values the lane loaded itself, no broadcast -- and
+// the groups are added by half-wave and row exchanges that leave each lane with the scores of GP/4 heads of
+// its token and nothing twice: the softmax runs on 16 tokens x G heads per page, spread over the wave.
+// (The other orientation, A = codes, leaves every slice of columns with the complete scores of four tokens:
+// the exponentials, which the vector unit issues at a quarter of its rate, and everything around them were
+// then done CS times over: 292 vector and matrix instructions per page pair, 221 now.)
+// The weights go back to the layout of the value product (four tokens per lane, column = (slice, head)) by one
+// v_mfma_f32_16x16x4_f32 per page and four heads with a 0/1 matrix: products with one and zero, so exact.
+// Values: p * s_V(t, g) is lane-local (each slice multiplies by its own group's
 // scale), is split once into two binary16 terms (22 significant bits), and the same B operand
 // pair serves the PV MFMAs of every group of the set: the tile of a 16-channel block is only
 // read back in the slice of its group.  The zero-point part of the output and the softmax
 // denominator are lane-local binary32 sums.
 //
-// One wave per work item of a (query, kv-head); the pages of every thought type are walked type
-// by type, so the bit width is a compile-time constant of each inner loop; every item leaves one
-// partial (acc, m, l) per query head, which the merge kernel folds.
-//
-// Work distribution.  On sliding-window layers an item owns a fixed share of each type's page
-// list.  On full-attention layers the items of one (query, kv-head) draw chunks of page pairs
-// from three shared counters (one per type) until the lists are empty: compute units do not
-// all see the same bandwidth, and a fixed split would leave the fast ones idle for the last
-// fifth of the launch.  Which item adds a pair to its partial does not matter: the merge kernel
-// sums the partials of a head whatever they hold.  A wave keeps the loads of its next pair in
-// flight while it works on the current one, and learns the ids of its next chunk by scalar loads,
-// outside the vector-memory queue.
+// Full-attention layers (decode_stream_kernel).  A work item is a workgroup of several waves on one (query, kv-head); the
+// waves draw chunks of page pairs from a ticket counter in LDS, so a wave that sees less bandwidth takes fewer, and
+// fold their partials in LDS: one partial row per item, or the result itself where a head has one item.  What bounds
+// the launch is the bytes in flight: a pair of pages held in registers while the one before is worked on leaves
+// 11 MB in flight on the chip, little more than latency times bandwidth, so every hiccup of a wave shows.  So the
+// pages go from memory to LDS directly (global_load_lds, no registers), several pairs ahead: each wave owns a ring
+// (its slots are sized by the type being walked), reads a pair into registers when it has landed, asks for the pair
+// that will take the slot, and computes.  The waits are vmcnt counts by hand: the compiler knows
+// nothing of these loads (they are inline asm without an output), a wait for an older load of its own only waits longer.
+// Measured against pairs prefetched into registers (one wave per item, tickets by global atomics, one pair in flight):
+// 256 x 1k..64k tokens 1,049 -> 832 us, 16 x 8k 51.6 -> 43.3, 32 x ~2k of scrambled slots 75 -> 48, head_dim 64
+// 128 x 4k..32k 313 -> 287.  Three waves a SIMD with rings of 12 KB (one pair of 8-bit pages) lose to two with 18 KB:
+// 16 x 8k 64 us, 256 x 1k..64k 1,046 us.
+// Sliding-window layers (decode_window_kernel): one wave per item, an item owns a fixed share of each type's page list.
 #pragma once
 #include "decode_common.h"
 
-#ifndef TKV_HALF
-#define TKV_HALF 0
-#endif
-#ifndef TKV_CHUNK
-#define TKV_CHUNK 4
-#endif
 
 namespace thinkv {
 
@@ -60,13 +61,6 @@ union H8 {
   half8 h;
   uint32_t u[4];
 };
-
-// x + (x of the lane DIST places further round this lane's row of 16)
-template <int DIST>
-__device__ __forceinline__ float add_row_ror(float x) {
-  const int y = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x120 + DIST, 0xf, 0xf, true);
-  return x + __builtin_bit_cast(float, y);
-}
 
 // max(x, x of another lane), the other lane chosen by a DPP control word: 0xB1 / 0x4E swap
 // neighbours / pairs inside a quad of lanes, 0x120 + d rotates the row of 16 by d
@@ -128,65 +122,116 @@ struct Cols {
   static constexpr int NSET = NG / CS;
 };
 
-// What one lane holds of one page: its K and V chunks and, per column set, the scales and
-// zero-points of (its slice's group, its four slots) for K and for V.
+// What one lane holds of one page: its K and V chunks and, per column set, the scale and zero-point of its
+// token and its slice's group for K, and those of its four slots and its slice's group for V.
 template <int D, int BITS, int NSET>
 struct PageRegs {
   static constexpr int CW = (D / 32) * BITS / 4;  // chunk dwords
   uint32_t kw[CW], vw[CW];
-  uint4 km[NSET], vm[NSET];   // (scale 0|1, scale 2|3, zero-point 0|1, zero-point 2|3)
+  uint16_t ks[NSET], kz[NSET];
+  uint4 vm[NSET];   // (scale 0|1, scale 2|3, zero-point 0|1, zero-point 2|3)
 };
 
-#ifndef TKV_NT
-#define TKV_NT 7   // bit 0: 2-bit pages, bit 1: 4-bit pages, bit 2: 8-bit pages read with non-temporal loads
-#endif
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-template <bool NT> __device__ __forceinline__ uint4 ld16(const void* p) {
-  if constexpr (NT) { const u32x4 w = __builtin_nontemporal_load((const u32x4*)p); return make_uint4(w.x, w.y, w.z, w.w); }
-  else return *(const uint4*)p;
-}
-template <bool NT> __device__ __forceinline__ uint2 ld8(const void* p) {
-  if constexpr (NT) { const u32x2 w = __builtin_nontemporal_load((const u32x2*)p); return make_uint2(w.x, w.y); }
-  else return *(const uint2*)p;
-}
+typedef __attribute__((address_space(3))) const uint8_t* LdsPtr;
+// pieces of a block in memory (read once: not worth a line of L2) or of its copy in LDS
+template <class T> __device__ __forceinline__ T ld_piece(const uint8_t* p) { return __builtin_nontemporal_load((const T*)p); }
+template <class T> __device__ __forceinline__ T ld_piece(LdsPtr p) { return *(__attribute__((address_space(3))) const T*)p; }
 
-// the K half (codes, scales, zero-points) or the V half of one page's block into the lane's registers
-template <int D, int BITS, int NSET, bool VHALF>
-__device__ __forceinline__ void load_half(PageRegs<D, BITS, NSET>& r, const uint8_t* blk, int lane, const int* meta_off) {
-  constexpr int CW = PageRegs<D, BITS, NSET>::CW;
-  constexpr bool NT = ((TKV_NT >> (BITS == 2 ? 0 : (BITS == 4 ? 1 : 2))) & 1) != 0;
-  const BlockGeom g = block_geom(BITS, D);
-  const uint32_t* src = (const uint32_t*)(blk + (VHALF ? g.v_codes : g.k_codes)) + lane * CW;
-  uint32_t* w = VHALF ? r.vw : r.kw;
+// chunk `lane` of a code region into the lane's registers
+template <int CW, class P>
+__device__ __forceinline__ void load_chunk(uint32_t* w, P region, int lane) {
+  P src = region + lane * CW * 4;
   if constexpr (CW == 1) {
-    w[0] = src[0];
+    w[0] = ld_piece<uint32_t>(src);
   } else if constexpr (CW == 2) {
-    const uint2 a = ld8<NT>(src);
+    const u32x2 a = ld_piece<u32x2>(src);
     w[0] = a.x; w[1] = a.y;
   } else {
 #pragma unroll
     for (int i = 0; i < CW; i += 4) {
-      const uint4 a = ld16<NT>(src + i);
+      const u32x4 a = ld_piece<u32x4>(src + 4 * i);
       w[i] = a.x; w[i + 1] = a.y; w[i + 2] = a.z; w[i + 3] = a.w;
     }
   }
-  uint4* m = VHALF ? r.vm : r.km;
-#pragma unroll
-  for (int s = 0; s < NSET; ++s) m[s] = ld16<NT>(blk + (VHALF ? g.v_meta : g.k_meta) + meta_off[s]);
 }
 
-template <int D, int NSET>
+// the K half (codes, scale, zero-point) or the V half of one page's block into the lane's registers
+template <int D, int BITS, int NSET, class P>
+__device__ __forceinline__ void load_keys(PageRegs<D, BITS, NSET>& r, P blk, int lane, const int* k_off) {
+  const BlockGeom g = block_geom(BITS, D);
+  load_chunk<PageRegs<D, BITS, NSET>::CW>(r.kw, blk + g.k_codes, lane);
+#pragma unroll
+  for (int s = 0; s < NSET; ++s) {
+    r.ks[s] = ld_piece<uint16_t>(blk + g.k_meta + k_off[s]);
+    r.kz[s] = ld_piece<uint16_t>(blk + g.k_meta + k_off[s] + 8);
+  }
+}
+template <int D, int BITS, int NSET, class P>
+__device__ __forceinline__ void load_values(PageRegs<D, BITS, NSET>& r, P blk, int lane, const int* v_off) {
+  const BlockGeom g = block_geom(BITS, D);
+  load_chunk<PageRegs<D, BITS, NSET>::CW>(r.vw, blk + g.v_codes, lane);
+#pragma unroll
+  for (int s = 0; s < NSET; ++s) {
+    const u32x4 m = ld_piece<u32x4>(blk + g.v_meta + v_off[s]);
+    r.vm[s] = make_uint4(m.x, m.y, m.z, m.w);
+  }
+}
+
+// Two layouts occur.  Score layout: lane (token n = lane % 16 of the page, row quad qd = lane / 16) holds, for its
+// token, the NS = GP / 4 heads head_of(qd, i).  Column layout (value tiles): lane (column n = (slice, head n % GP), qd).
+template <int D, int GP, int NSET>
 struct WaveState {
-  static constexpr int NM = D / 16;
-  float4v o[NM];    // o[mb][r]: channel 16*mb + 4*qd + r of column n (while a type is walked: in its units, and lifted)
-  float oz[NSET];   // this lane's share of sum_t p_t zp_V(t, group of the lane's slice)
-  float l;          // this lane's share of sum_t p_t
-  float m;          // running maximum (log2 domain) of column n; -inf before the first live token
-  float m_sub;      // what the exponent subtracts: m, or 0 while m is -inf
+  static constexpr int NM = D / 16, NS = GP / 4;
+  float4v o[NM];    // column layout; o[mb][r]: channel 16*mb + 4*qd + r (while a type is walked: in its units, and lifted)
+  float oz[NSET];   // column layout; this lane's share of sum_t p_t zp_V(t, group of the lane's slice)
+  float l[NS];      // score layout; this lane's share of sum_t p_t
+  float m[NS];      // score layout; running maximum (log2 domain) of the head; -inf before the first live token
+  float m_sub[NS];  // what the exponent subtracts: m, or 0 while m is -inf
 };
 
-// maximum over the four lanes that share a column (lane ^ 16, lane ^ 32), on the VALU
+// head of value i of a lane in row quad qd, as add_groups leaves the scores
+template <int GP>
+__device__ __forceinline__ int head_of(int qd, int i) { return GP == 4 ? qd : 4 * (qd & 1) + 2 * (qd >> 1) + i; }
+
+// score layout -> column layout, for values that are the same in all lanes of a row quad
+template <int GP>
+__device__ __forceinline__ float to_column(const float* x, int lane) {
+  const int h = lane & (GP - 1);
+  if constexpr (GP == 4) return __shfl(x[0], 16 * h, 64);
+  const int src = 16 * ((h >> 2) + (h & 2));
+  const float a = __shfl(x[0], src, 64), b = __shfl(x[1], src, 64);
+  return (h & 1) ? b : a;
+}
+
+__device__ __forceinline__ float add_swapped32(float a, float b) {   // lower half: a + a of the upper half; upper half: b likewise
+  auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b), false, false);
+  return __builtin_bit_cast(float, (uint32_t)r[0]) + __builtin_bit_cast(float, (uint32_t)r[1]);
+}
+__device__ __forceinline__ float add_swapped16(float a, float b) {   // even rows: a + a of the odd row next to it; odd rows: b likewise
+  auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b), false, false);
+  return __builtin_bit_cast(float, (uint32_t)r[0]) + __builtin_bit_cast(float, (uint32_t)r[1]);
+}
+// x[r]: row 4 qd + r of the score tile, i.e. GP = 4: (slice qd, head r), GP = 8: (slice qd / 2, head 4 (qd % 2) + r).
+// Adds the slices; each lane keeps the heads head_of(qd, .).
+template <int GP>
+__device__ __forceinline__ void add_groups(const float* x, float* s) {
+  const float y0 = add_swapped32(x[0], x[2]), y1 = add_swapped32(x[1], x[3]);
+  if constexpr (GP == 4) {
+    s[0] = add_swapped16(y0, y1);
+  } else {
+    s[0] = y0;
+    s[1] = y1;
+  }
+}
+
+// maximum over the lanes of a row quad (16 tokens)
+__device__ __forceinline__ float row_max(float x) {
+  return max_dpp<0x128>(max_dpp<0x124>(max_dpp<0x4E>(max_dpp<0xB1>(x))));
+}
+
+// maximum over the four lanes that share a token / column (lane ^ 16, lane ^ 32), on the VALU
 __device__ __forceinline__ float col_max(float x) {
   const uint32_t u = __builtin_bit_cast(uint32_t, x);
   auto r16 = __builtin_amdgcn_permlane16_swap(u, u, false, false);   // rows (0,1) and (2,3) exchanged
@@ -207,240 +252,361 @@ struct PairRegs {
   PageRegs<D, BITS, NSET> a, b;
 };
 
-// Walking the pages of one type: the part that does not depend on what is done with a pair.  Derived
-// supplies  void issue_loads(Pair&, const PairIds&)  and  void compute(const Pair&, const PairIds&).
-template <class Derived, class Pair>
-struct PairWalk {
-  const thinkv_view& v;
-  const DecodeArgs& a;
-  const int cls, hkv, qpos;
-  const int32_t* tab;
-  const int p0, p1;
-  int lane;
-  __device__ __forceinline__ PairWalk(const thinkv_view& v_, const DecodeArgs& a_, int cls_, int hkv_, int qpos_, const int32_t* tab_, int p0_, int p1_)
-      : v(v_), a(a_), cls(cls_), hkv(hkv_), qpos(qpos_), tab(tab_), p0(p0_), p1(p1_), lane(threadIdx.x & 63) {}
-  __device__ __forceinline__ Derived& self() { return *static_cast<Derived*>(this); }
+// ---- direct copies of a block into LDS.  A wave-wide load moves 1 KB (16 bytes a lane) to consecutive LDS bytes from m0
+// on; the instruction's offset counts on both sides.  The last, shorter piece runs with some lanes off.  The compiler does
+// not see the loads inside the asm, so the wait states between a vector instruction that writes an address register
+// (v_readfirstlane) or m0 and the load that reads it are in the asm too: five cover every such pair.
+template <int BYTES>
+struct BlockDma {
+  static constexpr int kFull = BYTES / 1024, kRest = (BYTES % 1024) / 16;   // whole instructions, lanes of the last one
+  static constexpr int kOps = kFull + (kRest ? 1 : 0);
+  static_assert(BYTES % 16 == 0 && kFull <= 4, "block sizes are multiples of 16 bytes, at most 4.5 KB");
+#define TKV_SET "s_mov_b32 m0, %0\n\ts_nop 4\n\t"
+#define TKV_DMA(OFF) "global_load_lds_dwordx4 %1, %2 offset:" #OFF " nt\n\t"
+#define TKV_SOME(OFF) "s_mov_b64 exec, %3\n\t" TKV_DMA(OFF) "s_mov_b64 exec, -1"
+  // lds: LDS byte address, blk: the block in memory (both wave-uniform), voff: 16 * lane; all lanes are on
+  static __device__ __forceinline__ void issue(uint32_t lds, const uint8_t* blk, uint32_t voff) {
+    const uint64_t on = (1ull << kRest) - 1ull;
+    if constexpr (kFull == 0) {
+      asm volatile(TKV_SET TKV_SOME(0)::"s"(lds), "v"(voff), "s"(blk), "s"(on) : "memory");
+    } else if constexpr (kFull == 1) {
+      asm volatile(TKV_SET TKV_DMA(0) TKV_SOME(1024)::"s"(lds), "v"(voff), "s"(blk), "s"(on) : "memory");
+    } else if constexpr (kFull == 2 && kRest != 0) {
+      asm volatile(TKV_SET TKV_DMA(0) TKV_DMA(1024) TKV_SOME(2048)::"s"(lds), "v"(voff), "s"(blk), "s"(on) : "memory");
+    } else if constexpr (kFull == 2) {
+      asm volatile(TKV_SET TKV_DMA(0) TKV_DMA(1024)::"s"(lds), "v"(voff), "s"(blk) : "memory");
+    } else {
+      static_assert(kFull != 3, "no format has such blocks");
+      asm volatile(TKV_SET TKV_DMA(0) TKV_DMA(1024) TKV_DMA(2048) TKV_DMA(3072)::"s"(lds), "v"(voff), "s"(blk) : "memory");
+      if constexpr (kRest != 0)   // beyond the reach of the offset
+        asm volatile(TKV_SET TKV_SOME(0)::"s"(lds + 4096u), "v"(voff), "s"(blk + 4096), "s"(on) : "memory");
+    }
+  }
+#undef TKV_SOME
+#undef TKV_DMA
+#undef TKV_SET
+};
+// a wave-uniform pointer that the compiler cannot prove to be one, into scalar registers
+__device__ __forceinline__ const uint8_t* scalar_ptr(const uint8_t* p) {
+  const uint64_t u = (uint64_t)(uintptr_t)p;
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((int)(uint32_t)u), hi = __builtin_amdgcn_readfirstlane((int)(uint32_t)(u >> 32));
+  return (const uint8_t*)(uintptr_t)((uint64_t)hi << 32 | lo);
+}
+template <int N>
+__device__ __forceinline__ void wait_loads() {   // until at most N of the wave's vector-memory operations are outstanding
+  static_assert(N >= 0 && N < 64, "six bits");
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+__device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
-  // Shared queues: *counter hands out page pairs of the type's page list tab[0 .. n_pages) to every
-  // item of this (query, kv-head), kChunkPairs consecutive pairs per request.  A wave keeps the
-  // chunk it works on, the ids of the next one (requested when the current one was started, so
-  // they have long arrived when they are needed) and one more chunk on order; its pairs thus
-  // form one stream across chunk boundaries, and the loads of pair i + 1 are requested before
-  // pair i is worked on (two register sets, A and B, used in turn): a wave always has a pair in
-  // flight while it computes.  When the stream ends the pair in flight is a repeat (a cache hit)
-  // and is dropped.
-  static constexpr int kChunkPairs = TKV_CHUNK;
-  static_assert(kChunkPairs == 4, "a chunk's page ids are fetched as eight-word vectors");
-  static_assert(kChunkPairs <= 8, "a chunk's page ids are held in sixteen scalars");
-  static constexpr int kChunkPages = 2 * kChunkPairs;
-  typedef const int32_t __attribute__((address_space(4))) * ConstI32;   // read-only for the whole launch: scalar loads
-  struct Stream {
-    ConstI32 tab, msk;
-    uint32_t* counter;
-    int n_pages, n_pairs;
-    int pg0, cnt, pr;             // current chunk: first page, pages, next pair
-    int vpid;                     // lane L: id of page L of the current chunk
-    int vmask;                    // lane L: mask word of that page (live bits in the low half)
-    int s_pid[kChunkPages];       // the next chunk's ids and mask words: scalar loads requested when the
-    int s_msk[kChunkPages];       //   current chunk was started (no traffic in the vector-memory queue)
-    int nj;                       // first pair of the next chunk (>= n_pairs: none)
-    int on_order;                 // lane 0: first pair of the chunk after that (atomic in flight)
-  };
-  // ids and masks of the chunk that starts at pair j -> scalars.  A chunk that lies inside the list is fetched by two
-  // eight-word scalar loads (page lists are only word-aligned: the scalar unit does not ask for more); the last chunk
-  // of a list word by word, entries past the end repeating the last page (never used).
-  typedef int32_t Words8 __attribute__((ext_vector_type(kChunkPages), aligned(4)));
-  typedef const Words8 __attribute__((address_space(4))) * ConstWords8;
-  __device__ __forceinline__ void load_ids(Stream& q, int j) const {
-    const int pg0 = 2 * j;
-    if (pg0 + kChunkPages <= q.n_pages) {
-      const Words8 a = *(ConstWords8)(q.tab + pg0);
-      const Words8 b = *(ConstWords8)(q.msk + pg0);
-#pragma unroll
-      for (int i = 0; i < kChunkPages; ++i) {
-        q.s_pid[i] = __builtin_amdgcn_readfirstlane(a[i]);
-        q.s_msk[i] = __builtin_amdgcn_readfirstlane(b[i]);
+// The page pairs an item works on, as one wave sees them.  The item's share of the three page lists is cut into chunks of
+// kChunkPairs consecutive pairs, type after type; chunk numbers come from the workgroup's ticket counter.  The ids and
+// masks of the pair after the one just taken are on their way by scalar loads (no traffic in the vector-memory queue).
+constexpr int kChunkPairs = 4;
+typedef const int32_t __attribute__((address_space(4))) * ConstI32;   // read-only for the whole launch: scalar loads
+typedef __attribute__((address_space(3))) int32_t* LdsCounter;
+
+struct Stream {
+  ConstI32 tab, msk;           // page list and masks of type 0; those of type k begin k * max_pages later
+  LdsCounter ticket;
+  int max_pages, lane;
+  // the three types in the order they are walked: type, first pair, end page, chunks up to and including it (plain
+  // members: an array indexed by a choice would not stay in scalar registers)
+  int kind0, kind1, kind2, first0, first1, first2, end0, end1, end2, cum0, cum1, cum2;
+  int left, row, end;          // pairs of the current chunk after the next pair; k * max_pages and end page of its type
+  int sec, pg;                 // the next pair: which of the three types (3: there is none), its first page,
+  int more_pages;              // 1 where it has a second one, else 0,
+  int pid_a, pid_b, msk_a, msk_b;   // ids and mask words of its pages (live bits in the low half), as the scalar loads return them
+
+  static __device__ __forceinline__ int pick(int x, int a, int b, int c) { return x == 0 ? a : (x == 1 ? b : c); }
+  // the share [j / n, (j + 1) / n) of a list of np pages: first pair, end page; its chunks
+  static __device__ __forceinline__ int share(int np, int j, int n, int& first, int& end) {
+    const int pairs = (np + 1) >> 1;
+    first = uniform((int)((int64_t)pairs * j / n));   // (divisions are vector arithmetic)
+    const int hi = uniform((int)((int64_t)pairs * (j + 1) / n));
+    end = 2 * hi < np ? 2 * hi : np;
+    return (hi - first + kChunkPairs - 1) / kChunkPairs;
+  }
+  // The next chunk's number, by one lane.  (In asm, with its wait: a branch on the lane would make the compiler restructure
+  // every loop around it and keep their scalars in vector registers.)
+  __device__ __forceinline__ int draw() const {
+    int r;
+    asm volatile("s_mov_b64 exec, 1\n\tds_add_rtn_u32 %0, %1, %2\n\ts_mov_b64 exec, -1\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&v"(r) : "v"((uint32_t)(uintptr_t)ticket), "v"(1) : "memory");
+    return uniform(r);
+  }
+  // moves on by one pair.  (Sums and minima instead of conditions: a condition turned into a number takes a vector
+  // instruction and drags what depends on it out of the scalar registers.)
+  __device__ __forceinline__ void look() {
+    if (left > 0) {
+      --left;
+      pg += 2;
+    } else {
+      const int c = draw();
+      if (c >= cum2) {
+        sec = 3;
+        return;
       }
-      return;
-    }
-#pragma unroll
-    for (int i = 0; i < kChunkPages; ++i) {
-      const int at = pg0 + i < q.n_pages ? pg0 + i : q.n_pages - 1;
-      q.s_pid[i] = __builtin_amdgcn_readfirstlane(q.tab[at]);
-      q.s_msk[i] = __builtin_amdgcn_readfirstlane(q.msk[at]);
-    }
-  }
-  __device__ __forceinline__ void spread_ids(Stream& q) const {
-#pragma unroll
-    for (int i = 0; i < kChunkPages; ++i) {
-      asm("v_writelane_b32 %0, %1, %2" : "+v"(q.vpid) : "s"(__builtin_amdgcn_readfirstlane(q.s_pid[i])), "n"(i));
-      asm("v_writelane_b32 %0, %1, %2" : "+v"(q.vmask) : "s"(__builtin_amdgcn_readfirstlane(q.s_msk[i])), "n"(i));
-    }
-  }
-  // asks for the next chunk
-  __device__ __forceinline__ void order_chunk(Stream& q) const {
-    int r = 0;
-    if (lane == 0) r = (int)atomicAdd(q.counter, (uint32_t)kChunkPairs);
-    q.on_order = r;   // valid in lane 0
-  }
-  __device__ __forceinline__ void set_chunk(Stream& q, int j) const {
-    q.pg0 = 2 * j;
-    q.cnt = q.n_pages - q.pg0 < kChunkPages ? q.n_pages - q.pg0 : kChunkPages;
-    q.pr = 0;
-  }
-  // the next pair of the stream; false (and a repeat of page 0 of the current chunk with no live slot) at its end
-  __device__ __forceinline__ bool next_pair(Stream& q, PairIds& id) const {
-    bool have = true;
-    if (2 * q.pr >= q.cnt) {
-      if (q.nj < q.n_pairs) {
-        spread_ids(q);
-        set_chunk(q, q.nj);
-        q.nj = __builtin_amdgcn_readfirstlane(q.on_order);
-        if (q.nj < q.n_pairs) load_ids(q, q.nj);
-        order_chunk(q);
+      if (c >= cum1) {
+        sec = 2;
+        end = end2;
+        row = kind2 * max_pages;
+        pg = 2 * (first2 + (c - cum1) * kChunkPairs);
+      } else if (c >= cum0) {
+        sec = 1;
+        end = end1;
+        row = kind1 * max_pages;
+        pg = 2 * (first1 + (c - cum0) * kChunkPairs);
       } else {
-        have = false;
+        sec = 0;
+        end = end0;
+        row = kind0 * max_pages;
+        pg = 2 * (first0 + c * kChunkPairs);
       }
+      left = min((end - pg - 1) >> 1, kChunkPairs - 1);
     }
-    const int ia = have ? 2 * q.pr : 0;
-    const bool two = have && 2 * q.pr + 1 < q.cnt;
-    const int ib = two ? 2 * q.pr + 1 : ia;
-    id.pid_a = __builtin_amdgcn_readlane(q.vpid, ia);
-    id.live_a = have ? (uint32_t)__builtin_amdgcn_readlane(q.vmask, ia) & 0xFFFFu : 0u;
-    id.pid_b = __builtin_amdgcn_readlane(q.vpid, ib);
-    id.live_b = two ? (uint32_t)__builtin_amdgcn_readlane(q.vmask, ib) & 0xFFFFu : 0u;
-    id.idx_a = q.pg0 + ia;
-    id.idx_b = two ? q.pg0 + ib : -1;
-    q.pr += have ? 1 : 0;
-    return have;
-  }
-  __device__ __forceinline__ void run_dynamic(int n_pages, uint32_t* counter) {
-    Stream q;
-    q.tab = (ConstI32)(uintptr_t)tab;
-    q.msk = (ConstI32)(uintptr_t)(v.slot_mask + (tab - v.block_table));
-    q.counter = counter;
-    q.n_pages = n_pages;
-    q.n_pairs = (n_pages + 1) >> 1;
-    order_chunk(q);
-    const int j0 = __builtin_amdgcn_readfirstlane(q.on_order);
-    if (j0 >= q.n_pairs) return;
-    order_chunk(q);
-    load_ids(q, j0);
-    q.vpid = 0;
-    q.vmask = 0;
-    spread_ids(q);
-    set_chunk(q, j0);
-    q.nj = __builtin_amdgcn_readfirstlane(q.on_order);
-    if (q.nj < q.n_pairs) load_ids(q, q.nj);
-    order_chunk(q);
-    if constexpr (Derived::kHalfPipe) {
-      // Two register sets, A and B, each a K half and a V half.  A half is asked for again as soon as it has been
-      // worked on: the K half of pair i + 2 goes out right after the scores of pair i, its V half right after the
-      // values of pair i, so one and a half to two pairs are in flight for the registers of two.
-      PairIds id0, id1, id2;
-      Pair ra, rb;
-      next_pair(q, id0);   // the first chunk has at least one page
-      bool have1 = next_pair(q, id1);
-      self().issue_loads(ra, id0);
-      self().issue_loads(rb, id1);
-      float pa[4], pb[4];
-      while (true) {
-        const bool have2 = next_pair(q, id2);
-        const bool on0 = (id0.live_a | id0.live_b) != 0;
-        if (on0) self().scores(ra, id0, pa, pb);
-        self().template issue_half<false>(ra, id2);
-        if (on0) self().values(ra, pa, pb);
-        self().template issue_half<true>(ra, id2);
-        if (!have1) break;
-        const bool have3 = next_pair(q, id0);
-        const bool on1 = (id1.live_a | id1.live_b) != 0;
-        if (on1) self().scores(rb, id1, pa, pb);
-        self().template issue_half<false>(rb, id0);
-        if (on1) self().values(rb, pa, pb);
-        self().template issue_half<true>(rb, id0);
-        if (!have2) break;
-        id1 = id0;
-        id0 = id2;
-        have1 = have3;
-      }
-      return;
-    }
-    PairIds ida, idb;
-    Pair ra, rb;
-    next_pair(q, ida);   // the first chunk has at least one page
-    self().issue_loads(ra, ida);
-    while (true) {
-      const bool more_b = next_pair(q, idb);
-      self().issue_loads(rb, idb);
-      if ((ida.live_a | ida.live_b) != 0) self().compute(ra, ida);
-      if (!more_b) break;
-      const bool more_a = next_pair(q, ida);
-      self().issue_loads(ra, ida);
-      if ((idb.live_a | idb.live_b) != 0) self().compute(rb, idb);
-      if (!more_a) break;
-    }
-  }
-
-  // Static share (sliding-window layers): page ids and live masks of up to 64 pages are fetched
-  // with one vector load each (lane L holds page p0 + base + L).  A page can hold a visible
-  // token only if the largest position ever written into it lies inside the window, so one
-  // word per page (page_pos_max) settles most pages; a lane reads the 16 positions of its page
-  // only when that test passes.  The pages of a run of 64 that still have a visible slot are
-  // paired up, and ids and masks reach the pair code through v_readlane.
-  __device__ __forceinline__ void run() {
-    const int n_pages = p1 - p0;
-    for (int base = 0; base < n_pages; base += 64) {
-      const int cnt = n_pages - base < 64 ? n_pages - base : 64;
-      int vpid = 0;
-      uint32_t vmask = 0;
-      if (lane < cnt) {
-        vpid = tab[p0 + base + lane];
-        vmask = v.slot_mask[(tab - v.block_table) + p0 + base + lane] & 0xFFFFu;
-      }
-      if (a.window > 0) {
-        uint32_t vis = 0;
-        if (vmask != 0 && v.page_pos_max[cls][vpid] > qpos - a.window) {
-          const int4* sp = (const int4*)(v.slot_pos[cls] + (int64_t)vpid * kPage);
-#pragma unroll
-          for (int t4 = 0; t4 < kPage / 4; ++t4) {
-            const int4 pos = sp[t4];
-            const int d0 = qpos - pos.x, d1 = qpos - pos.y, d2 = qpos - pos.z, d3 = qpos - pos.w;
-            vis |= ((d0 >= 0 && d0 < a.window) ? 1u : 0u) << (4 * t4);
-            vis |= ((d1 >= 0 && d1 < a.window) ? 2u : 0u) << (4 * t4);
-            vis |= ((d2 >= 0 && d2 < a.window) ? 4u : 0u) << (4 * t4);
-            vis |= ((d3 >= 0 && d3 < a.window) ? 8u : 0u) << (4 * t4);
-          }
-        }
-        vmask &= vis;
-      }
-      uint64_t todo = __ballot(vmask != 0);
-      while (todo) {
-        const int ia = __builtin_ctzll(todo);
-        todo &= todo - 1;
-        const bool two = todo != 0;
-        const int ib = two ? __builtin_ctzll(todo) : ia;
-        if (two) todo &= todo - 1;
-        PairIds id;
-        id.pid_a = __builtin_amdgcn_readlane(vpid, ia);
-        id.live_a = __builtin_amdgcn_readlane(vmask, ia);
-        id.pid_b = __builtin_amdgcn_readlane(vpid, ib);
-        id.live_b = two ? __builtin_amdgcn_readlane(vmask, ib) : 0u;
-        id.idx_a = p0 + base + ia;
-        id.idx_b = two ? p0 + base + ib : -1;
-        Pair r;
-        self().issue_loads(r, id);
-        self().compute(r, id);
-      }
-    }
+    more_pages = min(end - pg - 1, 1);
+    const ConstI32 t = tab + (row + pg), m = msk + (row + pg);   // (max_pages < 2^24)
+    pid_a = t[0];
+    msk_a = m[0];
+    pid_b = t[more_pages];
+    msk_b = m[more_pages];
   }
 };
 
+// a scalar that a load may still be bringing: waited for here and not before (what is computed from it would otherwise
+// be moved up to the load, and the wait with it)
+__device__ __forceinline__ int arrived(int x) {
+  int y;
+  asm volatile("s_mov_b32 %0, %1" : "=s"(y) : "s"(x));
+  return y;
+}
+
+// All pairs of the x-th type walked that the wave draws, through its ring at LDS address ring.
+template <class Runner>
+__device__ __forceinline__ void stream_type(Runner& run, Stream& q, int x, const thinkv_view& v, int cls, int hkv, uint32_t ring) {
+  using Dma = BlockDma<Runner::kBlockBytes>;
+  constexpr int kPairBytes = 2 * Runner::kBlockBytes, kOps = 2 * Dma::kOps;
+  constexpr int kSlots = stream_ring_bytes(Runner::kD, Runner::kFp) / kPairBytes;
+  static_assert(kSlots >= 1 && kSlots <= 32 && (kSlots - 1) * kOps < 64, "the ring holds a pair, the waits six bits");
+  const int lane = q.lane;
+  const uint32_t voff = 16 * lane;
+  const uint32_t page_bytes = __builtin_amdgcn_readfirstlane(v.cfg.n_kv_heads * Runner::kBlockBytes);
+  const uint8_t* const base = scalar_ptr(v.arena[cls] + (int64_t)hkv * Runner::kBlockBytes);
+  int f_live = 0, f_idx = 0;   // lane s: what slot s holds (live bits of both pages; twice the list position, plus one where there is a second page)
+  // asks for the next live pair of the type in slot, moves on; false: there is none
+  auto issue = [&](int slot) -> bool {
+    while (q.sec == x) {
+      const int msk_a = arrived(q.msk_a), msk_b = arrived(q.msk_b);
+      const bool on = ((msk_a | msk_b) & 0xFFFF) != 0;   // (a missing second page repeats the first one)
+      if (on) {
+        const uint32_t at = uniform(ring + slot * kPairBytes);
+        Dma::issue(at, scalar_ptr(base + (uint64_t)(uint32_t)arrived(q.pid_a) * page_bytes), voff);
+        Dma::issue(at + Runner::kBlockBytes, scalar_ptr(base + (uint64_t)(uint32_t)arrived(q.pid_b) * page_bytes), voff);
+        const bool mine = lane == slot;
+        f_live = mine ? (msk_a & 0xFFFF) | ((msk_b & (0 - q.more_pages)) << 16) : f_live;
+        if constexpr (Runner::kStat) f_idx = mine ? q.pg << 1 | q.more_pages : f_idx;
+      }
+      q.look();
+      if (on) return true;
+    }
+    return false;
+  };
+  int flying = 0;
+#pragma nounroll
+  while (flying < kSlots && issue(flying)) ++flying;
+  int slot = 0;
+#pragma nounroll
+  while (flying > 0) {
+    // the oldest pair has landed when only the others' loads are left (with fewer pairs in flight all are waited for: the
+    // end of the type is near)
+    if (flying == kSlots) wait_loads<(kSlots - 1) * kOps>();
+    else wait_loads<0>();
+    const LdsPtr blk_a = (LdsPtr)(uintptr_t)(ring + slot * kPairBytes), blk_b = blk_a + Runner::kBlockBytes;
+    typename Runner::Pair r;
+    run.load_k(r, blk_a, blk_b);
+    const uint32_t live = (uint32_t)__builtin_amdgcn_readlane(f_live, slot);
+    PairIds cur;
+    cur.live_a = live & 0xFFFFu;
+    cur.live_b = live >> 16;
+    if constexpr (Runner::kStat) {
+      const int idx = __builtin_amdgcn_readlane(f_idx, slot);
+      cur.idx_a = idx >> 1;
+      cur.idx_b = (idx & 1) ? cur.idx_a + 1 : -1;
+    }
+    run.load_v(r, blk_a, blk_b);
+    wait_lds();   // the slot has been read: it can be filled again
+    if (!issue(slot)) --flying;
+    run.scores(r, cur);
+    run.values(r);
+    slot = slot + 1 == kSlots ? 0 : slot + 1;
+  }
+}
+
+// Sliding-window layers, static share [p0, p1) of a type's page list: page ids and live masks of up to 64 pages are fetched
+// with one vector load each (lane L holds page p0 + base + L).  A page can hold a visible
+// token only if the largest position ever written into it lies inside the window, so one
+// word per page (page_pos_max) settles most pages; a lane reads the 16 positions of its page
+// only when that test passes.  The pages of a run of 64 that still have a visible slot are
+// paired up, and ids and masks reach the pair code through v_readlane.
+template <class Runner>
+__device__ __forceinline__ void walk_window(Runner& run, const thinkv_view& v, const DecodeArgs& a, int cls, int hkv, int qpos, const int32_t* tab,
+                                            int p0, int p1) {
+  const int lane = threadIdx.x & 63, H = v.cfg.n_kv_heads;
+  const int n_pages = p1 - p0;
+  for (int base = 0; base < n_pages; base += 64) {
+    const int cnt = n_pages - base < 64 ? n_pages - base : 64;
+    int vpid = 0;
+    uint32_t vmask = 0;
+    if (lane < cnt) {
+      vpid = tab[p0 + base + lane];
+      vmask = v.slot_mask[(tab - v.block_table) + p0 + base + lane] & 0xFFFFu;
+    }
+    uint32_t vis = 0;
+    if (vmask != 0 && v.page_pos_max[cls][vpid] > qpos - a.window) {
+      const int4* sp = (const int4*)(v.slot_pos[cls] + (int64_t)vpid * kPage);
+#pragma unroll
+      for (int t4 = 0; t4 < kPage / 4; ++t4) {
+        const int4 pos = sp[t4];
+        const int d0 = qpos - pos.x, d1 = qpos - pos.y, d2 = qpos - pos.z, d3 = qpos - pos.w;
+        vis |= ((d0 >= 0 && d0 < a.window) ? 1u : 0u) << (4 * t4);
+        vis |= ((d1 >= 0 && d1 < a.window) ? 2u : 0u) << (4 * t4);
+        vis |= ((d2 >= 0 && d2 < a.window) ? 4u : 0u) << (4 * t4);
+        vis |= ((d3 >= 0 && d3 < a.window) ? 8u : 0u) << (4 * t4);
+      }
+    }
+    vmask &= vis;
+    uint64_t todo = __ballot(vmask != 0);
+    while (todo) {
+      const int ia = __builtin_ctzll(todo);
+      todo &= todo - 1;
+      const bool two = todo != 0;
+      const int ib = two ? __builtin_ctzll(todo) : ia;
+      if (two) todo &= todo - 1;
+      PairIds id;
+      id.pid_a = __builtin_amdgcn_readlane(vpid, ia);
+      id.live_a = __builtin_amdgcn_readlane(vmask, ia);
+      id.pid_b = __builtin_amdgcn_readlane(vpid, ib);
+      id.live_b = two ? __builtin_amdgcn_readlane(vmask, ib) : 0u;
+      id.idx_a = p0 + base + ia;
+      id.idx_b = two ? p0 + base + ib : -1;
+      const uint8_t* blk_a = v.arena[cls] + ((int64_t)id.pid_a * H + hkv) * Runner::kBlockBytes;
+      const uint8_t* blk_b = v.arena[cls] + ((int64_t)id.pid_b * H + hkv) * Runner::kBlockBytes;
+      typename Runner::Pair r;
+      run.load_k(r, blk_a, blk_b);
+      run.load_v(r, blk_a, blk_b);
+      run.scores(r, id);
+      run.values(r);
+    }
+  }
+}
+
 // What a lane keeps of the query for the whole item: per column set the eight binary16 values of
-// (its head, its slice's group, channels 8qd .. 8qd+7) and the sum of the group's 32 values.
+// (its head, its slice's group, channels 8qd .. 8qd+7) and, for the four rows of its quad, the sum of the 32 values
+// of (row's head, row's slice's group).
 template <int NSET>
 struct QRegs {
   H8 q[NSET];
-  float sum[NSET];
+  float sum[NSET][4];
+};
+
+// What the two runners (integer formats, the paper's formats) share: the softmax over the scores of a pair.
+template <int D, int GP, int NSET, bool STAT>
+struct Softmax {
+  static constexpr int NM = D / 16, NS = GP / 4;
+  using State = WaveState<D, GP, NSET>;
+  State& st;
+  int lane;
+  float kappa;       // MFMA score units -> log2 domain (with softmax_scale)
+  float sel[NS];     // B operands of the layout change: 1 where the column's head is the row's
+  float* stat;       // STAT: pooled scores of this type's page list, 16 per page
+  int stat_room;     // STAT: pages of this list the buffer has room for (the host's bound on the context)
+  int G;
+  __device__ __forceinline__ Softmax(State& st_, int lane_, int G_, float* stat_, int room) : st(st_), lane(lane_), stat(stat_), stat_room(room), G(G_) {
+#pragma unroll
+    for (int i = 0; i < NS; ++i) sel[i] = head_of<GP>(lane >> 4, i) == (lane & (GP - 1)) ? 1.0f : 0.0f;
+  }
+  // sa, sb: scores of the lane's token in pages a and b (NS heads each), in MFMA units.  Masks them and leaves the pooled scores.
+  __device__ __forceinline__ void mask(float* sa, float* sb, const PairIds& id) {
+    if ((id.live_a & id.live_b) != 0xFFFFu) {
+      // dead slots: score -inf, hence p = 0.  Their scales and zero-points are finite (stale, or zero in a slot
+      // never written: arenas start zero-filled), so they drop out of every sum.
+      const bool la = __builtin_amdgcn_inverse_ballot_w64(id.live_a * 0x0001000100010001ull);
+      const bool lb = __builtin_amdgcn_inverse_ballot_w64(id.live_b * 0x0001000100010001ull);
+#pragma unroll
+      for (int i = 0; i < NS; ++i) {
+        sa[i] = la ? sa[i] : -INFINITY;
+        sb[i] = lb ? sb[i] : -INFINITY;
+      }
+    }
+    if constexpr (STAT) {
+      // pooled scores: maximum over the heads of the group, i.e. over the lane's heads and the four lanes of a token
+      auto pooled = [&](const float* sc, int idx) {
+        float u = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < NS; ++i) u = head_of<GP>(lane >> 4, i) < G ? fmaxf(u, sc[i] * kappa) : u;
+        u = col_max(u);   // the same in the four lanes of a token, which store it to one place
+        if (idx >= 0 && idx < stat_room) stat[(int64_t)idx * kPage + (lane & (kPage - 1))] = u;
+      };
+      pooled(sa, id.idx_a);
+      pooled(sb, id.idx_b);
+    }
+  }
+  // Online softmax: the weights are 2^(score - m) with m a reference that is at most `slack` below the maximum seen.  It
+  // only moves when a score exceeds it by more, to the maximum: with eight heads a new maximum by any amount turns up
+  // in most pairs of a few thousand tokens (and moving m costs as much as a quarter of the pair), one by a factor of 2^slack hardly ever.
+  __device__ __forceinline__ void reference(const float* sa, const float* sb, float slack) {
+    float mx[NS];
+    bool above = false;
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+      mx[i] = fmaxf(sa[i], sb[i]) * kappa;
+      above = above || mx[i] > st.m[i] + slack;
+    }
+    if (__any(above)) {
+      float corr[NS];
+#pragma unroll
+      for (int i = 0; i < NS; ++i) {
+        const float m_new = fmaxf(st.m[i], row_max(mx[i]));
+        st.m_sub[i] = m_new == -INFINITY ? 0.f : m_new;
+        corr[i] = __builtin_amdgcn_exp2f(st.m[i] - st.m_sub[i]);
+        st.l[i] *= corr[i];
+        st.m[i] = m_new;
+      }
+      const float cc = to_column<GP>(corr, lane);
+#pragma unroll
+      for (int mb = 0; mb < NM; ++mb) st.o[mb] *= cc;
+#pragma unroll
+      for (int set = 0; set < NSET; ++set) st.oz[set] *= cc;
+    }
+  }
+  // the weights 2^(score - m + lift): ea, eb of the lane's token (score layout), pa, pb of the lane's four tokens (column layout)
+  __device__ __forceinline__ void weights(const float* sa, const float* sb, float lift, float* ea, float* eb, float* pa, float* pb) const {
+    float4v ta = {0.f, 0.f, 0.f, 0.f}, tb = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+      const float mref = st.m_sub[i] - lift;
+      ea[i] = __builtin_amdgcn_exp2f(fmaf(sa[i], kappa, -mref));
+      eb[i] = __builtin_amdgcn_exp2f(fmaf(sb[i], kappa, -mref));
+      ta = __builtin_amdgcn_mfma_f32_16x16x4f32(ea[i], sel[i], ta, 0, 0, 0);
+      tb = __builtin_amdgcn_mfma_f32_16x16x4f32(eb[i], sel[i], tb, 0, 0, 0);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      pa[r] = ta[r];
+      pb[r] = tb[r];
+    }
+  }
+  __device__ __forceinline__ void add(const float* ea, const float* eb) {
+#pragma unroll
+    for (int i = 0; i < NS; ++i) st.l[i] += ea[i] + eb[i];
+  }
+  __device__ __forceinline__ void scale_sums(float f) {
+#pragma unroll
+    for (int i = 0; i < NS; ++i) st.l[i] *= f;
+#pragma unroll
+    for (int set = 0; set < NSET; ++set) st.oz[set] *= f;
+  }
 };
 
 // The pages of one type, as one wave walks them.
@@ -448,51 +614,41 @@ struct QRegs {
 // the query heads of the group of the scaled score, log2 domain; -inf for a dead or invisible
 // slot) in a[.].stat, for the attention-sparsity statistic.
 template <int D, int BITS, int GP, bool STAT>
-struct ClassRunner : PairWalk<ClassRunner<D, BITS, GP, STAT>, PairRegs<D, BITS, Cols<D, GP>::NSET>> {
+struct ClassRunner {
   using CL = Cols<D, GP>;
-  static constexpr int NG = D / 32, NM = D / 16, CS = CL::CS, NSET = CL::NSET;
+  static constexpr int kD = D, kBlockBytes = block_geom(BITS, D).block_bytes;
+  static constexpr bool kStat = STAT, kFp = false;
+  static constexpr int NG = D / 32, NM = D / 16, CS = CL::CS, NSET = CL::NSET, NS = GP / 4;
   using F = Fld<BITS>;
   using Pair = PairRegs<D, BITS, NSET>;
-  using Walk = PairWalk<ClassRunner<D, BITS, GP, STAT>, Pair>;
-  static constexpr bool kHalfPipe = TKV_HALF != 0;
-  using Walk::v;
-  using Walk::a;
-  using Walk::cls;
-  using Walk::hkv;
-  using Walk::lane;
-  WaveState<D, NSET>& st;
-  int qd, n;
-  int meta_off[NSET];  // byte offset, inside a meta region, of this lane's unit per column set
-  H8 bq[NG];           // B operands of the score MFMAs: q of group g in slice g % CS, zeros elsewhere
-  float qs[NSET];      // 2^(OMIN-24) * sum_{i in group} q_i of this lane's (slice group, head)
-  float kappa;         // 2^(24-OMIN) * softmax_scale * log2(e): MFMA score units -> log2 domain
+  const int lane;
+  WaveState<D, GP, NSET>& st;
+  Softmax<D, GP, NSET, STAT> sm;
+  int k_off[NSET], v_off[NSET];  // byte offset, inside a meta region, of this lane's scale (K) and unit (V) per column set
+  H8 bq[NG];           // A operands of the score MFMAs: q of group g in slice g % CS, zeros elsewhere
+  float qs[NSET][4];   // 2^(OMIN-24) * sum_{i in group} q_i of the four rows of this lane's quad
   float lift;          // the weights of this type's pages are 2^lift times the softmax weights (kLift, or 0 after a scale too large for it)
   float neg1;          // -1, kept opaque so that x - (float)h stays one fused mixed-precision instruction
-  float* stat;         // STAT: pooled scores of this type's page list, 16 per page
-  int stat_room;       // STAT: pages of this list the buffer has room for (the host's bound on the context)
-  bool head_ok;        // this lane's column belongs to a query head of the group
 
   // qr: this lane's query slice per column set (binary16, channels 32g + 8qd + e of its head and slice group) and the
   // group sums, as the kernel read them once per item
-  __device__ __forceinline__ ClassRunner(WaveState<D, NSET>& st_, const thinkv_view& v_, const DecodeArgs& a_, int cls_,
-                                         const int32_t* tab_, int p0_, int p1_, int hkv_, int G, const QRegs<NSET>& qr,
-                                         int qpos_, float* stat_, int stat_room_)
-      : Walk(v_, a_, cls_, hkv_, qpos_, tab_, p0_, p1_), st(st_), stat(stat_), stat_room(stat_room_) {
-    qd = lane >> 4;
-    n = lane & 15;
+  __device__ __forceinline__ ClassRunner(WaveState<D, GP, NSET>& st_, const thinkv_config& c, const DecodeArgs& a, int G, const QRegs<NSET>& qr, float* stat_, int stat_room_)
+      : lane(threadIdx.x & 63), st(st_), sm(st_, threadIdx.x & 63, G, stat_, stat_room_) {
+    const int qd = lane >> 4, n = lane & 15;
     const int gl = n / GP, head = n % GP;
     const bool used = gl < CS && head < G;
-    head_ok = head < G;
     const int glc = gl < CS ? gl : CS - 1;   // unused slices read slice CS-1's unit (finite, multiplied by zeros)
-    kappa = (float)(1 << (24 - F::OMIN)) * a.scale_log2e;
+    const int gk = GP == 4 ? qd : qd >> 1, gkc = gk < CS ? gk : CS - 1;   // slice of the rows of this lane's quad
+    sm.kappa = (float)(1 << (24 - F::OMIN)) * a.scale_log2e;
     enter();
     neg1 = -1.0f;
     asm volatile("" : "+v"(neg1));
 #pragma unroll
     for (int s = 0; s < NSET; ++s) {
-      const int g = s * CS + glc;
-      meta_off[s] = (g * 4 + qd) * 16;
-      qs[s] = used ? qr.sum[s] * (1.0f / (float)(1 << (24 - F::OMIN))) : 0.f;
+      k_off[s] = ((s * CS + gkc) * 4 + (n >> 2)) * 16 + (n & 3) * 2;
+      v_off[s] = ((s * CS + glc) * 4 + qd) * 16;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) qs[s][r] = qr.sum[s][r] * (1.0f / (float)(1 << (24 - F::OMIN)));
     }
     // the query slice is scaled down by the residual power of two the codes of those fields carry (exact:
     // power-of-two scaling of binary16 values), then dealt to the group's operand; the operands of
@@ -521,23 +677,20 @@ struct ClassRunner : PairWalk<ClassRunner<D, BITS, GP, STAT>, PairRegs<D, BITS, 
   // the largest product out of binary16; every pair is checked, and such a pair ends the lift for the rest of
   // the type).
   static constexpr int kLift = BITS == 8 ? 14 : (BITS == 4 ? 10 : 8);
+  static constexpr float kSlack = 3.0f;
   // the tiles are in the units of the type (its codes carry a power of two that depends on the bit width) and
   // lifted while its pages are walked, in absolute units in between
   __device__ static constexpr float tile_unit(int mb) { return (float)(1 << (BITS == 8 ? 0 : F::OMIN + F::rel_of(mb))); }
   __device__ __forceinline__ void enter() {
     const float up = (float)(1 << kLift);
     lift = (float)kLift;
-    st.l *= up;
-#pragma unroll
-    for (int s = 0; s < NSET; ++s) st.oz[s] *= up;
+    sm.scale_sums(up);
 #pragma unroll
     for (int mb = 0; mb < NM; ++mb) st.o[mb] *= up * tile_unit(mb);
   }
   __device__ __forceinline__ void drop_lift() {
     const float down = __builtin_amdgcn_exp2f(-lift);
-    st.l *= down;
-#pragma unroll
-    for (int s = 0; s < NSET; ++s) st.oz[s] *= down;
+    sm.scale_sums(down);
 #pragma unroll
     for (int mb = 0; mb < NM; ++mb) st.o[mb] *= down;
     lift = 0.f;
@@ -548,27 +701,18 @@ struct ClassRunner : PairWalk<ClassRunner<D, BITS, GP, STAT>, PairRegs<D, BITS, 
     for (int mb = 0; mb < NM; ++mb) st.o[mb] *= 1.0f / tile_unit(mb);
   }
 
-  __device__ __forceinline__ void issue_loads(Pair& r, const PairIds& id) const {
-    const int H = v.cfg.n_kv_heads;
-    const BlockGeom geo = block_geom(BITS, D);
-    const uint8_t* blk_a = v.arena[cls] + ((int64_t)id.pid_a * H + hkv) * geo.block_bytes;
-    const uint8_t* blk_b = v.arena[cls] + ((int64_t)id.pid_b * H + hkv) * geo.block_bytes;
-    load_half<D, BITS, NSET, false>(r.a, blk_a, lane, meta_off);
-    load_half<D, BITS, NSET, false>(r.b, blk_b, lane, meta_off);
-    load_half<D, BITS, NSET, true>(r.a, blk_a, lane, meta_off);
-    load_half<D, BITS, NSET, true>(r.b, blk_b, lane, meta_off);
+  template <class P>
+  __device__ __forceinline__ void load_k(Pair& r, P blk_a, P blk_b) const {
+    load_keys<D, BITS, NSET>(r.a, blk_a, lane, k_off);
+    load_keys<D, BITS, NSET>(r.b, blk_b, lane, k_off);
   }
-  template <bool VHALF>
-  __device__ __forceinline__ void issue_half(Pair& r, const PairIds& id) const {
-    const int H = v.cfg.n_kv_heads;
-    const BlockGeom geo = block_geom(BITS, D);
-    const uint8_t* blk_a = v.arena[cls] + ((int64_t)id.pid_a * H + hkv) * geo.block_bytes;
-    const uint8_t* blk_b = v.arena[cls] + ((int64_t)id.pid_b * H + hkv) * geo.block_bytes;
-    load_half<D, BITS, NSET, VHALF>(r.a, blk_a, lane, meta_off);
-    load_half<D, BITS, NSET, VHALF>(r.b, blk_b, lane, meta_off);
+  template <class P>
+  __device__ __forceinline__ void load_v(Pair& r, P blk_a, P blk_b) const {
+    load_values<D, BITS, NSET>(r.a, blk_a, lane, v_off);
+    load_values<D, BITS, NSET>(r.b, blk_b, lane, v_off);
   }
 
-  // scores of one page for this lane's four tokens, in MFMA units (times kappa = log2 domain)
+  // scores of one page for this lane's token and heads, in MFMA units (times kappa = log2 domain)
   __device__ __forceinline__ void page_scores(const PageRegs<D, BITS, NSET>& r, float* s) const {
     const float4v zero = {0.f, 0.f, 0.f, 0.f};
     float4v c[NSET];
@@ -580,128 +724,55 @@ struct ClassRunner : PairWalk<ClassRunner<D, BITS, GP, STAT>, PairRegs<D, BITS, 
         H8 ka;
 #pragma unroll
         for (int vv = 0; vv < 4; ++vv) ka.u[vv] = F::get(r.kw, 4 * g + vv);
-        c[set] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ka.h, bq[g].h, gl == 0 ? zero : c[set], 0, 0, 0);
+        c[set] = __builtin_amdgcn_mfma_f32_16x16x32_f16(bq[g].h, ka.h, gl == 0 ? zero : c[set], 0, 0, 0);
       }
     }
-#define TKV_SCORE(R)                                                                             \
-  {                                                                                              \
-    float acc = 0.f;                                                                             \
-    _Pragma("unroll") for (int set = 0; set < NSET; ++set) {                                     \
-      const float z = fmaf(half_of<R>(r.km[set].z, r.km[set].w), qs[set], 0.0f);                 \
-      const float t = fmaf(half_of<R>(r.km[set].x, r.km[set].y), c[set][R], z);                  \
-      acc = set == 0 ? t : acc + t;                                                              \
-    }                                                                                            \
-    acc = add_row_ror<8>(acc);                                                                   \
-    if constexpr (GP == 4) acc = add_row_ror<4>(acc);                                            \
-    s[R] = acc;                                                                                  \
-  }
-    TKV_SCORE(0) TKV_SCORE(1) TKV_SCORE(2) TKV_SCORE(3)
-#undef TKV_SCORE
-  }
-
-  __device__ __forceinline__ void compute(const Pair& r, const PairIds& id) {
-    float pa[4], pb[4];
-    scores(r, id, pa, pb);
-    values(r, pa, pb);
-  }
-  __device__ __forceinline__ void scores(const Pair& r, const PairIds& id, float* pa, float* pb) {
-    const uint32_t live_a = id.live_a, live_b = id.live_b;
-    float sa[4], sb[4];
-    page_scores(r.a, sa);
-    page_scores(r.b, sb);
-    // ---------------- dead slots: score -inf, hence p = 0.  Their scales and zero-points are finite
-    // (stale, or zero in a slot never written: arenas start zero-filled), so they drop out of every sum.
-    if ((live_a & live_b) != 0xFFFFu) {
-      const uint32_t la = (live_a >> (4 * qd)) & 0xFu, lb = (live_b >> (4 * qd)) & 0xFu;
-#pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4) {
-        sa[r4] = ((la >> r4) & 1u) ? sa[r4] : -INFINITY;
-        sb[r4] = ((lb >> r4) & 1u) ? sb[r4] : -INFINITY;
-      }
-    }
-    if constexpr (STAT) {
-      // pooled scores: maximum over the heads of the group, i.e. over the GP lanes of a slice (all
-      // slices hold the same totals); the lanes of column 0 store their four slots of each page.
-      // One page after the other, so that only four more values are live at a time.
-      auto pooled = [&](const float* sc, int idx) {
-        float u[4];
-#pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) {
-          u[r4] = head_ok ? sc[r4] * kappa : -INFINITY;
-          // a quad of lanes, then (eight heads) the quad four lanes on: the row of 16 holds CS
-          // identical slices, so rotating the row by four reaches the other half of the slice
-          u[r4] = max_dpp<0x4E>(max_dpp<0xB1>(u[r4]));
-          if constexpr (GP == 8) u[r4] = max_dpp<0x124>(u[r4]);
-        }
-        if (n == 0 && idx >= 0 && idx < stat_room) *(float4*)(stat + (int64_t)idx * kPage + 4 * qd) = make_float4(u[0], u[1], u[2], u[3]);
-      };
-      pooled(sa, id.idx_a);
-      pooled(sb, id.idx_b);
-    }
-    // ---------------- online softmax over the 8 scores of this lane; the running maximum only
-    // moves when some lane of the wave sees a score above it
-    const float mx = fmaxf(fmaxf(fmaxf(sa[0], sa[1]), fmaxf(sa[2], sa[3])), fmaxf(fmaxf(sb[0], sb[1]), fmaxf(sb[2], sb[3]))) * kappa;
-    if (__any(mx > st.m)) {
-      const float m_new = fmaxf(st.m, col_max(mx));
-      const float m_sub = m_new == -INFINITY ? 0.f : m_new;
-      const float corr = __builtin_amdgcn_exp2f(st.m - m_sub);
-#pragma unroll
-      for (int mb = 0; mb < NM; ++mb) st.o[mb] *= corr;
-#pragma unroll
-      for (int set = 0; set < NSET; ++set) st.oz[set] *= corr;
-      st.l *= corr;
-      st.m = m_new;
-      st.m_sub = m_sub;
-    }
-    // p = 2^(score - m + lift): the weights are lifted by a power of two (see kLift), and with them
-    // the denominator, the zero-point sums and the value tiles of this type
-    const float mref = st.m_sub - lift;
-#pragma unroll
-    for (int r4 = 0; r4 < 4; ++r4) {
-      pa[r4] = __builtin_amdgcn_exp2f(fmaf(sa[r4], kappa, -mref));
-      pb[r4] = __builtin_amdgcn_exp2f(fmaf(sb[r4], kappa, -mref));
-    }
-    st.l += ((pa[0] + pa[1]) + (pa[2] + pa[3])) + ((pb[0] + pb[1]) + (pb[2] + pb[3]));
-  }
-  // ---------------- values, per column set: B = two-term split of p * s_V, A = V codes
-  __device__ __forceinline__ void values(const Pair& r, float* pa, float* pb) {
-    float xa[NSET][4], xb[NSET][4];
+    float x[4];
 #pragma unroll
     for (int set = 0; set < NSET; ++set) {
+      const float sc = (float)__builtin_bit_cast(_Float16, r.ks[set]), zp = (float)__builtin_bit_cast(_Float16, r.kz[set]);
+#pragma unroll
+      for (int r4 = 0; r4 < 4; ++r4) {
+        const float t = fmaf(sc, c[set][r4], fmaf(zp, qs[set][r4], 0.0f));
+        x[r4] = set == 0 ? t : x[r4] + t;
+      }
+    }
+    add_groups<GP>(x, s);
+  }
+
+  float sa[NS], sb[NS];   // scores of the pair at hand
+  __device__ __forceinline__ void scores(const Pair& r, const PairIds& id) {
+    page_scores(r.a, sa);
+    page_scores(r.b, sb);
+    sm.mask(sa, sb, id);
+    sm.reference(sa, sb, lift != 0.f ? kSlack : 0.f);   // without the lift a weight above one could take the largest scales out of binary16
+  }
+  // ---------------- values, per column set: B = two-term split of p * s_V, A = V codes
+  __device__ __forceinline__ void values(const Pair& r) {
+    float ea[NS], eb[NS], pa[4], pb[4], xa[NSET][4], xb[NSET][4];
+    for (int again = 0;; ++again) {
+      sm.weights(sa, sb, lift, ea, eb, pa, pb);
+      float big = 0.f;
+#pragma unroll
+      for (int set = 0; set < NSET; ++set) {
 #define TKV_X(R)                                                               \
   {                                                                            \
     xa[set][R] = fmaf(half_of<R>(r.a.vm[set].x, r.a.vm[set].y), pa[R], 0.0f);  \
     xb[set][R] = fmaf(half_of<R>(r.b.vm[set].x, r.b.vm[set].y), pb[R], 0.0f);  \
   }
-      TKV_X(0) TKV_X(1) TKV_X(2) TKV_X(3)
+        TKV_X(0) TKV_X(1) TKV_X(2) TKV_X(3)
 #undef TKV_X
-    }
-    if (lift != 0.f) {
-      // would a lifted product leave binary16?  (scales this large are far outside what a cache holds in
-      // practice; then the rest of this type's pages is worked on without the lift)
-      float big = 0.f;
-#pragma unroll
-      for (int set = 0; set < NSET; ++set)
         big = fmaxf(fmaxf(fmaxf(big, fmaxf(xa[set][0], xa[set][1])), fmaxf(fmaxf(xa[set][2], xa[set][3]), fmaxf(xb[set][0], xb[set][1]))),
                     fmaxf(xb[set][2], xb[set][3]));
-      if (__any(big > 6.0e4f)) {
-        const float down = __builtin_amdgcn_exp2f(-lift);
-        drop_lift();   // the denominator already holds this pair's weights: they come down with it
-#pragma unroll
-        for (int set = 0; set < NSET; ++set) {
-#pragma unroll
-          for (int r4 = 0; r4 < 4; ++r4) {
-            xa[set][r4] *= down;
-            xb[set][r4] *= down;
-          }
-        }
-#pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) {
-          pa[r4] *= down;
-          pb[r4] *= down;
-        }
       }
+      if (lift == 0.f || !__any(big > 6.0e4f)) break;
+      // A lifted product would leave binary16.  First the reference moves up to the maximum; scales that are too large
+      // even then are far outside what a cache holds in practice, and the rest of this type's pages is worked on without
+      // the lift.
+      if (again == 0) sm.reference(sa, sb, 0.0f);
+      else drop_lift();
     }
+    sm.add(ea, eb);
 #pragma unroll
     for (int set = 0; set < NSET; ++set) {
       float z = st.oz[set];
@@ -744,15 +815,245 @@ struct ClassRunner : PairWalk<ClassRunner<D, BITS, GP, STAT>, PairRegs<D, BITS, 
 #include "decode_mfma_fp.h"
 namespace thinkv {
 
-// One wave per item; a workgroup is four items that share nothing but the launch (the hardware starts a
-// four-wave workgroup as fast as a one-wave one, and a launch of thousands of single waves takes ten
-// microseconds to get going).  WIN: sliding-window layer (static shares).
+// What both kernels hold of the query: lane (slice gl, head, row quad qd) reads, per column set, the eight values of
+// channels 32g + 8qd .. of its head (g = the set's group of its slice) and rounds them to binary16.
+template <int D, int GP, bool FP>
+struct Query {
+  static constexpr int CS = FP ? ColsFp<D, GP>::CS : Cols<D, GP>::CS, NSET = FP ? ColsFp<D, GP>::NSET : Cols<D, GP>::NSET;
+  QRegs<FP ? 1 : NSET> qr;
+  QRegsFp<FP ? NSET : 1> qf;
+  static __device__ __forceinline__ H8 read8(const DecodeArgs& a, int64_t at) {
+    H8 t;
+    if (a.q_dtype == THINKV_F16) {
+      const uint4 raw = *(const uint4*)((const _Float16*)a.q + at);
+      t.u[0] = raw.x; t.u[1] = raw.y; t.u[2] = raw.z; t.u[3] = raw.w;
+    } else {
+      const uint4 raw = *(const uint4*)((const uint16_t*)a.q + at);
+      const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const uint32_t u = (e & 1) ? (w[e >> 1] & 0xFFFF0000u) : (w[e >> 1] << 16);
+        t.h[e] = (_Float16)__builtin_bit_cast(float, u);
+      }
+    }
+    return t;
+  }
+  // at: first element of the group's heads
+  __device__ __forceinline__ void read(const DecodeArgs& a, int64_t at, int G, int lane) {
+    const int qd = lane >> 4, n = lane & 15, gl = n / GP, head = n % GP;
+    const bool used = gl < CS && head < G;
+    const int glc = gl < CS ? gl : CS - 1;
+    at += (int64_t)(used ? head : 0) * D + 8 * qd;
+#pragma unroll
+    for (int s = 0; s < NSET; ++s) {
+      if constexpr (FP) {
+        // the paper's formats: a slice carries a group of 16 channels; the lane holds the eight values of channels
+        // 32 G + 8 qd .. of its head where those lie in its slice's group (qd / 2 = parity of the group), zeros otherwise
+        const int g16 = s * CS + glc;
+        const bool mine = used && (g16 & 1) == (qd >> 1);
+        const H8 t = read8(a, at + 32 * (g16 >> 1));
+#pragma unroll
+        for (int w4 = 0; w4 < 4; ++w4) qf.q[s].u[w4] = mine ? t.u[w4] : 0u;
+      } else {
+        // ... and the sum of the group's 32 values: the four row quads complete it
+        qr.q[s] = read8(a, at + 32 * (s * CS + glc));
+        float sum = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) sum += (float)qr.q[s].h[e];
+        sum += __shfl_xor(sum, 16, 64);
+        sum += __shfl_xor(sum, 32, 64);
+        sum = used ? sum : 0.f;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) qr.sum[s][r] = __shfl(sum, 4 * qd + r, 64);   // from the lane whose column is the row
+      }
+    }
+  }
+};
+
+// A wave's partial (or, with one item per head, result) from its registers.  The lanes of a row quad (sixteen tokens)
+// each hold a share of the denominators of the quad's heads, the four lanes of a column a share of the zero-point sums;
+// the tile of channel block mb is valid in the slice of its group, where lane (head, qd) holds channels 16 mb + 4 qd .. + 3.
+template <int D, int GP, bool FP>
+struct Partial {
+  static constexpr int NM = D / 16, NS = GP / 4, CS = Query<D, GP, FP>::CS, NSET = Query<D, GP, FP>::NSET;
+  static constexpr int GB = FP ? 1 : 2;   // 16-channel blocks per quantisation group
+  float l, m, zsum[NSET];                 // of the lane's column
+  __device__ __forceinline__ Partial(const WaveState<D, GP, NSET>& st, int lane) {
+    float ls[NS];
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+      ls[i] = st.l[i];
+#pragma unroll
+      for (int d = 8; d >= 1; d >>= 1) ls[i] += __shfl_xor(ls[i], d, 64);
+    }
+    l = to_column<GP>(ls, lane);
+    m = to_column<GP>(st.m, lane);
+#pragma unroll
+    for (int set = 0; set < NSET; ++set) {
+      float z = FP ? 0.f : st.oz[set];   // the paper's formats have no zero-points
+      if constexpr (!FP) {
+        z += __shfl_xor(z, 16, 64);
+        z += __shfl_xor(z, 32, 64);
+      }
+      zsum[set] = z;
+    }
+  }
+  // f(channel, four values) for the lane's share of its head's accumulator (lanes of a used head only)
+  template <class F>
+  __device__ __forceinline__ void each(const WaveState<D, GP, NSET>& st, int lane, F f) const {
+    const int qd = lane >> 4, gl = (lane & 15) / GP;
+#pragma unroll
+    for (int mb = 0; mb < NM; ++mb) {
+      const int g = mb / GB, set = g / CS;
+      if (gl == g % CS)
+        f(16 * mb + 4 * qd, make_float4(st.o[mb][0] * 16777216.f + zsum[set], st.o[mb][1] * 16777216.f + zsum[set],
+                                        st.o[mb][2] * 16777216.f + zsum[set], st.o[mb][3] * 16777216.f + zsum[set]));
+    }
+  }
+};
+
+template <int D, int GP, int NSET>
+__device__ __forceinline__ void clear(WaveState<D, GP, NSET>& st) {
+#pragma unroll
+  for (int mb = 0; mb < D / 16; ++mb) st.o[mb] = float4v{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int set = 0; set < NSET; ++set) st.oz[set] = 0.f;
+#pragma unroll
+  for (int i = 0; i < GP / 4; ++i) {
+    st.l[i] = 0.f;
+    st.m[i] = -INFINITY;
+    st.m_sub[i] = 0.f;
+  }
+}
+
+// STAT: where the pooled scores of type k of (query b, kv-head) begin (they lie in the order of the three page lists), and
+// how many pages of that list there is room for
+__device__ __forceinline__ float* stat_row(const thinkv_config& c, const DecodeArgs& a, int b, int hkv, int k, const int* np, int* room) {
+  const int before = k == 0 ? 0 : (k == 1 ? np[0] : np[0] + np[1]);
+  *room = (int)(a.stat_stride / kPage) - before;
+  return a.stat + ((int64_t)b * c.n_kv_heads + hkv) * a.stat_stride + (int64_t)before * kPage;
+}
+
+// runs CALL with the runner `cr` of the type's bit width
+#define TKV_WITH_RUNNER(BITS_, CALL)                                                                  \
+  {                                                                                                   \
+    if constexpr (FP) {                                                                               \
+      ClassRunnerFp<D, BITS_, GP, STAT> cr(st, c, a, G, query.qf, stat, stat_room);                   \
+      CALL;                                                                                           \
+      cr.leave();                                                                                     \
+    } else {                                                                                          \
+      ClassRunner<D, BITS_, GP, STAT> cr(st, c, a, G, query.qr, stat, stat_room);                     \
+      CALL;                                                                                           \
+      cr.leave();                                                                                     \
+    }                                                                                                 \
+  }
+#define TKV_BY_WIDTH(BITS, CALL)                \
+  if (BITS == 2) TKV_WITH_RUNNER(2, CALL)       \
+  else if (BITS == 4) TKV_WITH_RUNNER(4, CALL)  \
+  else TKV_WITH_RUNNER(8, CALL)
+
+// Full-attention layers: a workgroup of W = blockDim.x / 64 waves per item (see the head of the file).
 // FP: the cache is in the paper's number formats (decode_mfma_fp.h), else in the integer formats.
-template <int D, int GP, bool WIN, bool STAT, bool FP>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(decode_waves_per_simd(D), decode_waves_per_simd(D)))) void decode_mfma_kernel(thinkv_view v, DecodeArgs a) {
-  constexpr int NM = D / 16;
-  constexpr int CS = FP ? ColsFp<D, GP>::CS : Cols<D, GP>::CS, NSET = FP ? ColsFp<D, GP>::NSET : Cols<D, GP>::NSET;
-  constexpr int GB = FP ? 1 : 2;   // 16-channel blocks per quantisation group
+template <int D, int GP, bool STAT, bool FP>
+__global__ __launch_bounds__(256 * decode_waves_per_simd(D, FP)) __attribute__((amdgpu_waves_per_eu(decode_waves_per_simd(D, FP), decode_waves_per_simd(D, FP)))) void decode_stream_kernel(thinkv_view v, DecodeArgs a) {
+  constexpr int kRing = stream_ring_bytes(D, FP), kRow = D + kRowPad;
+  extern __shared__ __attribute__((aligned(16))) uint8_t tkv_lds[];
+  const thinkv_config& c = v.cfg;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, W = blockDim.x >> 6;
+  const ItemLoc it = locate_item(v, a, blockIdx.x);
+  if (it.j >= it.n) return;
+  const int b = it.b, hkv = it.hkv, seq = uniform(a.seq_ids[b]);
+  const int Hq = c.n_q_heads, G = Hq / c.n_kv_heads;
+  int np[3];
+  seq_pages(v, a.layer, seq, np);
+  const bool valid = seq >= 0 && seq < c.max_seqs;
+  Stream q;
+  q.ticket = (LdsCounter)(uintptr_t)(W * kRing);
+  q.lane = lane;
+  q.max_pages = c.max_pages;
+  q.tab = (ConstI32)(uintptr_t)(v.block_table + (valid ? table_base(c, seq, a.layer, 0) : 0));
+  q.msk = (ConstI32)(uintptr_t)(v.slot_mask + (valid ? table_base(c, seq, a.layer, 0) : 0));
+  // Heads start on different types: a pair of 8-bit pages moves three times the bytes of a pair of 2-bit pages for the
+  // same arithmetic, so if all walked the types in the same order the whole chip would swing between bandwidth-bound
+  // and issue-bound phases.  An item takes the same fraction of each list.
+  const int rot = (hkv + b + it.j) % 3;
+  q.kind0 = rot;
+  q.kind1 = rot + 1 < 3 ? rot + 1 : rot - 2;
+  q.kind2 = rot + 2 < 3 ? rot + 2 : rot - 1;
+  q.cum0 = Stream::share(Stream::pick(q.kind0, np[0], np[1], np[2]), it.j, it.n, q.first0, q.end0);
+  q.cum1 = q.cum0 + Stream::share(Stream::pick(q.kind1, np[0], np[1], np[2]), it.j, it.n, q.first1, q.end1);
+  q.cum2 = q.cum1 + Stream::share(Stream::pick(q.kind2, np[0], np[1], np[2]), it.j, it.n, q.first2, q.end2);
+  if (it.j == 0 && threadIdx.x == 0 && !a.direct) {
+    a.alloc[2 * (b * c.n_kv_heads + hkv)] = it.row0;
+    a.alloc[2 * (b * c.n_kv_heads + hkv) + 1] = it.n;
+  }
+  if (threadIdx.x == 0) *q.ticket = 0;
+  q.left = q.row = q.end = q.sec = q.pg = q.more_pages = q.pid_a = q.pid_b = q.msk_a = q.msk_b = 0;
+  Query<D, GP, FP> query;
+  query.read(a, ((int64_t)b * Hq + hkv * G) * D, G, lane);
+  WaveState<D, GP, Query<D, GP, FP>::NSET> st;
+  clear(st);
+  __syncthreads();
+  const uint32_t ring = (uint32_t)(wave * kRing);
+  q.look();
+  while (q.sec < 3) {
+    const int x = q.sec, k = Stream::pick(x, q.kind0, q.kind1, q.kind2);
+    const int bits = c.bits_of_class[k];
+    float* stat = nullptr;
+    int stat_room = 0;
+    if constexpr (STAT) stat = stat_row(c, a, b, hkv, k, np, &stat_room);
+    TKV_BY_WIDTH(bits, stream_type(cr, q, x, v, k, hkv, ring))
+  }
+  // ---- the waves' partials meet in LDS (the rings are done with) and are folded there
+  const Partial<D, GP, FP> part(st, lane);
+  const int head = lane & (GP - 1), qd = lane >> 4;
+  float* const rows = (float*)tkv_lds;   // [wave][G][kRow]
+  __syncthreads();
+  if (head < G) {
+    float* dst = rows + (wave * G + head) * kRow;
+    part.each(st, lane, [&](int ch, float4 x) { *(float4*)(dst + ch) = x; });
+    if (qd == 0 && (lane & 15) < GP) {
+      dst[D] = part.m;
+      dst[D + 1] = part.l;
+    }
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < G * (D / 4); i += blockDim.x) {
+    const int g = i / (D / 4), ch = 4 * (i % (D / 4));
+    float M = -INFINITY;
+    for (int w = 0; w < W; ++w) M = fmaxf(M, rows[(w * G + g) * kRow + D]);
+    float L = 0.f;
+    float4 A = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int w = 0; w < W; ++w) {
+      const float* src = rows + (w * G + g) * kRow;
+      const float f = src[D] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(src[D] - M);
+      const float4 x = *(const float4*)(src + ch);
+      L = fmaf(src[D + 1], f, L);
+      A.x = fmaf(x.x, f, A.x);
+      A.y = fmaf(x.y, f, A.y);
+      A.z = fmaf(x.z, f, A.z);
+      A.w = fmaf(x.w, f, A.w);
+    }
+    if (a.direct) {   // the only item of its head: this is the result
+      const int64_t at = ((int64_t)b * Hq + hkv * G + g) * D + ch;
+      const float o[4] = {A.x, A.y, A.z, A.w};
+#pragma unroll
+      for (int r = 0; r < 4; ++r) store_from_f32(a.out, at + r, a.out_dtype, L > 0.f ? o[r] / L : 0.f);
+      if (a.lse && ch == 0) a.lse[(int64_t)b * Hq + hkv * G + g] = L > 0.f ? (M + log2f(L)) * 0.6931471805599453f : -INFINITY;
+    } else {
+      float* dst = partial_row(a, G, D, it.row0 + it.j, g);
+      *(float4*)(dst + ch) = A;
+      if (ch == 0) {
+        dst[D] = M;
+        dst[D + 1] = L;
+      }
+    }
+  }
+}
+
+// Sliding-window layers: one wave per item; a workgroup is four items that share nothing but the launch.
+template <int D, int GP, bool STAT, bool FP>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 128 ? 2 : 3, D == 128 ? 2 : 3))) void decode_window_kernel(thinkv_view v, DecodeArgs a) {
   const thinkv_config& c = v.cfg;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int item = blockIdx.x * 4 + wave;
@@ -760,200 +1061,72 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(decode_wave
   const ItemLoc it = locate_item(v, a, item);
   if (it.j >= it.n) return;
   const int b = it.b, hkv = it.hkv;
-  const int seq = a.seq_ids[b];
+  const int seq = uniform(a.seq_ids[b]);
   int np[3];
   seq_pages(v, a.layer, seq, np);
-  const int lane = threadIdx.x & 63, qd = lane >> 4, n = lane & 15;
-  const int gl = n / GP, head = n % GP;
+  const int lane = threadIdx.x & 63, qd = lane >> 4, head = lane & (GP - 1);
   const int Hq = c.n_q_heads, G = Hq / c.n_kv_heads;
   if (it.j == 0 && lane == 0 && !a.direct) {
     a.alloc[2 * (b * c.n_kv_heads + hkv)] = it.row0;
     a.alloc[2 * (b * c.n_kv_heads + hkv) + 1] = it.n;
   }
-
-  // ---- the query: lane (slice gl, head, row quad qd) reads, per column set, the eight values of
-  // channels 32g + 8qd .. of its head (g = the set's group of its slice), rounds them to binary16
-  // and adds them up; the four row quads complete the group's sum
-  QRegs<FP ? 1 : NSET> qr;
-  QRegsFp<FP ? NSET : 1> qf;
-  if constexpr (FP) {
-    // the paper's formats: a slice carries a group of 16 channels; the lane holds the eight values of channels
-    // 32 G + 8 qd .. of its head where those lie in its slice's group (qd / 2 = parity of the group), zeros otherwise
-    const bool used = gl < CS && head < G;
-    const int glc = gl < CS ? gl : CS - 1;
-#pragma unroll
-    for (int s = 0; s < NSET; ++s) {
-      const int g16 = s * CS + glc;
-      const bool mine = used && (g16 & 1) == (qd >> 1);
-      const int64_t at = ((int64_t)b * Hq + hkv * G + (used ? head : 0)) * D + 32 * (g16 >> 1) + 8 * qd;
-      H8 t;
-      if (a.q_dtype == THINKV_F16) {
-        const uint4 raw = *(const uint4*)((const _Float16*)a.q + at);
-        t.u[0] = raw.x; t.u[1] = raw.y; t.u[2] = raw.z; t.u[3] = raw.w;
-      } else {
-        const uint4 raw = *(const uint4*)((const uint16_t*)a.q + at);
-        const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const uint32_t u = (e & 1) ? (w[e >> 1] & 0xFFFF0000u) : (w[e >> 1] << 16);
-          t.h[e] = (_Float16)__builtin_bit_cast(float, u);
-        }
-      }
-#pragma unroll
-      for (int w4 = 0; w4 < 4; ++w4) qf.q[s].u[w4] = mine ? t.u[w4] : 0u;
-    }
-  } else {
-    const bool used = gl < CS && head < G;
-    const int glc = gl < CS ? gl : CS - 1;
-#pragma unroll
-    for (int s = 0; s < NSET; ++s) {
-      const int g = s * CS + glc;
-      const int64_t at = ((int64_t)b * Hq + hkv * G + (used ? head : 0)) * D + 32 * g + 8 * qd;
-      float sum = 0.f;
-      if (a.q_dtype == THINKV_F16) {
-        const uint4 raw = *(const uint4*)((const _Float16*)a.q + at);
-        qr.q[s].u[0] = raw.x; qr.q[s].u[1] = raw.y; qr.q[s].u[2] = raw.z; qr.q[s].u[3] = raw.w;
-      } else {
-        const uint4 raw = *(const uint4*)((const uint16_t*)a.q + at);
-        const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const uint32_t u = (e & 1) ? (w[e >> 1] & 0xFFFF0000u) : (w[e >> 1] << 16);
-          qr.q[s].h[e] = (_Float16)__builtin_bit_cast(float, u);
-        }
-      }
-#pragma unroll
-      for (int e = 0; e < 8; ++e) sum += (float)qr.q[s].h[e];
-      sum += __shfl_xor(sum, 16, 64);
-      sum += __shfl_xor(sum, 32, 64);
-      qr.sum[s] = sum;
-    }
-  }
-
-  WaveState<D, NSET> st;
-#pragma unroll
-  for (int mb = 0; mb < NM; ++mb) st.o[mb] = float4v{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int set = 0; set < NSET; ++set) st.oz[set] = 0.f;
-  st.l = 0.f;
-  st.m = -INFINITY;
-  st.m_sub = 0.f;
-  const int qpos = WIN ? a.q_pos[b] : 0;
-
-  // Items start on different types: a pair of 8-bit pages moves three times the bytes of a pair of
-  // 2-bit pages for the same arithmetic, so if every wave walked the types in the same order the
-  // whole chip would swing between bandwidth-bound and issue-bound phases.
-  const int rot = (it.j + hkv + b) % 3;
-  for (int kk = 0; kk < 3; ++kk) {
-    const int k = kk + rot < 3 ? kk + rot : kk + rot - 3;
+  Query<D, GP, FP> query;
+  query.read(a, ((int64_t)b * Hq + hkv * G) * D, G, lane);
+  WaveState<D, GP, Query<D, GP, FP>::NSET> st;
+  clear(st);
+  const int qpos = uniform(a.q_pos[b]);
+  for (int k = 0; k < 3; ++k) {
     const int bits = c.bits_of_class[k];
     const int npk = k == 0 ? np[0] : (k == 1 ? np[1] : np[2]);
-    const int p0 = WIN ? (int)((int64_t)it.j * npk / it.n) : 0, p1 = WIN ? (int)((int64_t)(it.j + 1) * npk / it.n) : npk;
+    const int p0 = uniform((int)((int64_t)it.j * npk / it.n)), p1 = uniform((int)((int64_t)(it.j + 1) * npk / it.n));
     if (p1 > p0) {
       const int32_t* tab = v.block_table + table_base(c, seq, a.layer, k);
-      uint32_t* counter = v.work_counters + (((int64_t)a.layer * c.max_seqs + b) * c.n_kv_heads + hkv) * 4 + k;
-      // STAT: the pooled scores of a (query, kv-head) lie in the order of the three page lists
       float* stat = nullptr;
       int stat_room = 0;
-      if constexpr (STAT) {
-        const int before = k == 0 ? 0 : (k == 1 ? np[0] : np[0] + np[1]);
-        stat = a.stat + ((int64_t)b * c.n_kv_heads + hkv) * a.stat_stride + (int64_t)before * kPage;
-        stat_room = (int)(a.stat_stride / kPage) - before;
-      }
-#define TKV_RUN(B_)                                                                                     \
-  if constexpr (FP) {                                                                                   \
-    ClassRunnerFp<D, B_, GP, STAT> cr(st, v, a, k, tab, p0, p1, hkv, G, qf, qpos, stat, stat_room);      \
-    if constexpr (WIN) cr.run();                                                                        \
-    else cr.run_dynamic(npk, counter);                                                                  \
-    cr.leave();                                                                                         \
-  } else {                                                                                              \
-    ClassRunner<D, B_, GP, STAT> cr(st, v, a, k, tab, p0, p1, hkv, G, qr, qpos, stat, stat_room);        \
-    if constexpr (WIN) cr.run();                                                                        \
-    else cr.run_dynamic(npk, counter);                                                                  \
-    cr.leave();                                                                                         \
-  }
-      if (bits == 2) TKV_RUN(2) else if (bits == 4) TKV_RUN(4) else TKV_RUN(8)
-#undef TKV_RUN
+      if constexpr (STAT) stat = stat_row(c, a, b, hkv, k, np, &stat_room);
+      TKV_BY_WIDTH(bits, walk_window(cr, v, a, k, hkv, qpos, tab, p0, p1))
     }
   }
-
-  // ---- the item's partial row per query head.  The four lanes of a column (row quads) each hold a
-  // share of the denominator and of the zero-point sums; the tile of channel block mb is valid in
-  // the slice of its group, where lane (head, qd) holds channels 16 mb + 4 qd .. + 3.
-  float l = st.l;
-  l += __shfl_xor(l, 16, 64);
-  l += __shfl_xor(l, 32, 64);
-  float zsum[NSET];
+  const Partial<D, GP, FP> part(st, lane);
+  if (head >= G) return;
+  if (a.direct) {   // the only item of its head: this is the result
+    const int64_t o_at = ((int64_t)b * Hq + hkv * G + head) * D;
+    part.each(st, lane, [&](int ch, float4 x) {
+      const float o[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
-  for (int set = 0; set < NSET; ++set) {
-    float z = FP ? 0.f : st.oz[set];   // the paper's formats have no zero-points
-    if constexpr (!FP) {
-      z += __shfl_xor(z, 16, 64);
-      z += __shfl_xor(z, 32, 64);
-    }
-    zsum[set] = z;
-  }
-  if (head < G) {
-    if (a.direct) {   // the only item of its head: this is the result
-      const int64_t o_at = ((int64_t)b * Hq + hkv * G + head) * D;
-#pragma unroll
-      for (int mb = 0; mb < NM; ++mb) {
-        const int g = mb / GB, set = g / CS;
-        if (gl == g % CS) {
-#pragma unroll
-          for (int r = 0; r < 4; ++r)
-            store_from_f32(a.out, o_at + 16 * mb + 4 * qd + r, a.out_dtype, l > 0.f ? (st.o[mb][r] * 16777216.f + zsum[set]) / l : 0.f);
-        }
-      }
-      if (a.lse && qd == 0 && gl == 0) a.lse[(int64_t)b * Hq + hkv * G + head] = l > 0.f ? (st.m + log2f(l)) * 0.6931471805599453f : -INFINITY;
-    } else {
-      float* dst = partial_row(a, G, D, it.row0 + it.j, head);
-#pragma unroll
-      for (int mb = 0; mb < NM; ++mb) {
-        const int g = mb / GB, set = g / CS;
-        if (gl == g % CS) {
-          float4 o4;
-          o4.x = st.o[mb][0] * 16777216.f + zsum[set];
-          o4.y = st.o[mb][1] * 16777216.f + zsum[set];
-          o4.z = st.o[mb][2] * 16777216.f + zsum[set];
-          o4.w = st.o[mb][3] * 16777216.f + zsum[set];
-          *(float4*)(dst + 16 * mb + 4 * qd) = o4;
-        }
-      }
-      if (qd == 0 && gl == 0) {
-        dst[D] = st.m;
-        dst[D + 1] = l;
-      }
+      for (int r = 0; r < 4; ++r) store_from_f32(a.out, o_at + ch + r, a.out_dtype, part.l > 0.f ? o[r] / part.l : 0.f);
+    });
+    if (a.lse && qd == 0 && (lane & 15) < GP) a.lse[(int64_t)b * Hq + hkv * G + head] = part.l > 0.f ? (part.m + log2f(part.l)) * 0.6931471805599453f : -INFINITY;
+  } else {
+    float* dst = partial_row(a, G, D, it.row0 + it.j, head);
+    part.each(st, lane, [&](int ch, float4 x) { *(float4*)(dst + ch) = x; });
+    if (qd == 0 && (lane & 15) < GP) {
+      dst[D] = part.m;
+      dst[D + 1] = part.l;
     }
   }
-  // (direct) the work queues of this head are left empty for the next call: no other item shares them
-  if (a.direct && lane < 4) v.work_counters[(((int64_t)a.layer * c.max_seqs + b) * c.n_kv_heads + hkv) * 4 + lane] = 0u;
 }
 
-template <int D, bool WIN, bool STAT>
-static int launch_dw(const thinkv_view& v, const DecodeArgs& a, hipStream_t st) {
-  const int G = v.cfg.n_q_heads / v.cfg.n_kv_heads;
-  dim3 grid((a.n_rows + 3) / 4), blk(256);
-  if (G > 8) return THINKV_E_SHAPE;
-  if (v.cfg.format == THINKV_FMT_FP) {
-    if (G <= 4)
-      hipLaunchKernelGGL((decode_mfma_kernel<D, 4, WIN, STAT, true>), grid, blk, 0, st, v, a);
-    else
-      hipLaunchKernelGGL((decode_mfma_kernel<D, 8, WIN, STAT, true>), grid, blk, 0, st, v, a);
-  } else if (G <= 4) {
-    hipLaunchKernelGGL((decode_mfma_kernel<D, 4, WIN, STAT, false>), grid, blk, 0, st, v, a);
-  } else {
-    hipLaunchKernelGGL((decode_mfma_kernel<D, 8, WIN, STAT, false>), grid, blk, 0, st, v, a);
-  }
+template <int D, int GP, bool STAT, bool FP>
+static int launch_one(const thinkv_view& v, const DecodeArgs& a, hipStream_t st) {
+  if (a.window > 0)
+    hipLaunchKernelGGL((decode_window_kernel<D, GP, STAT, FP>), dim3((a.n_rows + 3) / 4), dim3(256), 0, st, v, a);
+  else
+    hipLaunchKernelGGL((decode_stream_kernel<D, GP, STAT, FP>), dim3(a.n_rows), dim3(64 * a.waves), a.waves * stream_ring_bytes(D, FP) + 16, st, v, a);
   return hipGetLastError() == hipSuccess ? THINKV_OK : THINKV_E_HIP;
 }
 
-// sliding-window layers take static shares, full-attention layers the shared work queues
 template <bool STAT>
 static int launch_decode_mfma_t(const thinkv_view& v, const DecodeArgs& a, hipStream_t st) {
-  if (v.cfg.head_dim == 128)
-    return a.window > 0 ? launch_dw<128, true, STAT>(v, a, st) : launch_dw<128, false, STAT>(v, a, st);
-  return a.window > 0 ? launch_dw<64, true, STAT>(v, a, st) : launch_dw<64, false, STAT>(v, a, st);
+  const int G = v.cfg.n_q_heads / v.cfg.n_kv_heads;
+  if (G > 8) return THINKV_E_SHAPE;
+  const bool fp = v.cfg.format == THINKV_FMT_FP;
+  if (v.cfg.head_dim == 128) {
+    if (G <= 4) return fp ? launch_one<128, 4, STAT, true>(v, a, st) : launch_one<128, 4, STAT, false>(v, a, st);
+    return fp ? launch_one<128, 8, STAT, true>(v, a, st) : launch_one<128, 8, STAT, false>(v, a, st);
+  }
+  if (G <= 4) return fp ? launch_one<64, 4, STAT, true>(v, a, st) : launch_one<64, 4, STAT, false>(v, a, st);
+  return fp ? launch_one<64, 8, STAT, true>(v, a, st) : launch_one<64, 8, STAT, false>(v, a, st);
 }
 
 }  // namespace thinkv

@@ -1,0 +1,98 @@
+"""Full-attention decode at the edges of its work distribution: items of one and of several workgroups, short lists, a
+ring that wraps, pages with nothing live, batches whose row count is limited by the workspace, and value scales that leave
+the range of the second matrix operand.  The reference is the plain vector-ALU kernel (itself checked against the oracle);
+the workspace has exactly the size the library asks for, with a guard behind it."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2510_01290_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+def _cache(D, G, H, ctx, fmt, bits, seed, v_scale=1.0, dead=0.0):
+    """a cache of len(ctx) sequences, types in runs of 1..60 tokens; a share `dead` of the runs is evicted as a whole"""
+    rng = np.random.default_rng(seed)
+    S, n = len(ctx), int(np.sum(ctx))
+    seq = np.repeat(np.arange(S), ctx).astype(np.int32)
+    pos = np.concatenate([np.arange(c) for c in ctx]).astype(np.int32)
+    runs = np.repeat(np.arange(n), rng.integers(1, 61, n))[:n]
+    cls = rng.integers(0, 3, n).astype(np.uint8)[runs]
+    most = int(max(ctx)) // 16 + 3
+    c = B.Cache(1, G * H, H, D, bits, S, most, [n // 16 + 3 * S + 8] * 3, fmt=fmt, fp8_scale=(0.05, 0.05 * v_scale))
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(seed)
+    k = torch.randn((n, H, D), generator=gen, device="cuda:0").to(torch.bfloat16)
+    v = (torch.randn((n, H, D), generator=gen, device="cuda:0") * v_scale).to(torch.bfloat16)
+    h = torch.empty(n, dtype=torch.int32, device="cuda:0")
+    d = lambda x: torch.from_numpy(np.ascontiguousarray(x)).to("cuda:0")  # noqa: E731
+    B.thinkv_append_quantized(c, 0, k, v, d(seq), d(pos), d(cls), h)
+    gone = (rng.random(n) < dead)[runs]
+    if gone.any():
+        at = d(np.flatnonzero(gone))
+        B.thinkv_evict(c, 0, d(seq)[at], h[at])
+    q = torch.randn((S, G * H, D), generator=gen, device="cuda:0").to(torch.bfloat16)
+    return c, q
+
+
+def _both(c, q, D, bound=None):
+    S, Hq = q.shape[:2]
+    ids = torch.arange(S, dtype=torch.int32, device="cuda:0")
+    pages = int(c.n_pages[:, 0].sum(-1).max()) if bound is None else bound
+    res = []
+    for fn in (B.load().thinkv_decode_attention, B.load().thinkv_decode_attention_valu):
+        need = B.thinkv_decode_workspace_bytes(c.cfg, S, pages)
+        ws = torch.full((need + 4096,), 0x5A, dtype=torch.uint8, device="cuda:0")
+        out = torch.empty((S, Hq, D), dtype=torch.float32, device="cuda:0")
+        lse = torch.empty((S, Hq), dtype=torch.float32, device="cuda:0")
+        rc = fn(B.C.byref(c.view), 0, B._ptr(q), B._ptr(out), B._ptr(lse), B._ptr(ids), None, S, 0, D ** -0.5, B.BF16, B.F32, pages,
+                B._ptr(ws), need, B._stream(None))
+        torch.cuda.synchronize()
+        assert rc == 0
+        assert bool((ws[need:] == 0x5A).all()), "written behind the workspace"
+        res.append((out.double().cpu(), lse.double().cpu()))
+    assert int(c.dev_status.abs().sum()) == 0
+    return res
+
+
+@pytest.mark.parametrize("D,G,H,ctx,fmt,bits,dead", [
+    (128, 4, 1, [9000], 0, (8, 2, 4), 0.0),                    # several items a head, every ring wraps
+    (64, 8, 2, [12000, 1], 0, (8, 4, 2), 0.3),                 # ... and runs of whole pages with nothing live
+    (128, 8, 2, [2000, 33, 16, 17, 15, 1], 0, (2, 2, 2), 0.0),  # list lengths around a page, a pair, a chunk
+    (64, 1, 3, [700, 129, 128, 127, 256, 8], 0, (8, 8, 8), 0.2),
+    (128, 4, 1, [9000], 1, (2, 4, 8), 0.0),
+    (64, 8, 2, [5000, 40, 1], 1, (8, 2, 4), 0.3),
+    (64, 8, 8, [1500] * 127 + [3000], 0, (8, 2, 4), 0.0),      # more heads than compute units: rows limited by the workspace
+    (64, 8, 16, [900] * 70, 1, (4, 4, 4), 0.0),
+    (128, 4, 8, [300] * 40, 0, (8, 2, 4), 0.5),
+], ids=lambda x: str(x)[:24].replace(" ", ""))
+def test_stream_kernel_against_the_plain_kernel(D, G, H, ctx, fmt, bits, dead):
+    print("stream:", D, G, H, len(ctx), max(ctx), fmt, bits, dead, flush=True)
+    c, q = _cache(D, G, H, ctx, fmt, bits, 11 + D + G + len(ctx), dead=dead)
+    (o, l), (ro, rl) = _both(c, q, D)
+    # binary32 sums of at most 12,000 products whose second operand holds 22 bits: about 1e-6 of the largest value
+    assert float((o - ro).abs().max()) <= 1e-4 * max(1.0, float(ro.abs().max()))
+    fin = torch.isfinite(rl)
+    assert torch.equal(torch.isfinite(l), fin) and float((l[fin] - rl[fin]).abs().max()) <= 1e-4
+
+
+@pytest.mark.parametrize("bound", [0, 1, 40, 100000])
+def test_stream_kernel_with_a_wrong_context_bound(bound):
+    """the host's bound sizes the launch only: too small or far too large, every page is attended"""
+    print("stream bound:", bound, flush=True)
+    c, q = _cache(128, 4, 2, [1300, 200, 77], 0, (8, 2, 4), 5)
+    (o, l), (ro, rl) = _both(c, q, 128, bound)
+    assert float((o - ro).abs().max()) <= 1e-4 and float((l - rl).abs().max()) <= 1e-4
+
+
+@pytest.mark.parametrize("D,G,v_scale", [(128, 4, 60.0), (64, 8, 60.0), (128, 8, 3000.0), (64, 4, 8000.0)])
+def test_value_scales_out_of_the_lifted_range(D, G, v_scale):
+    """value ranges of a few hundred (the softmax reference has to move before the lifted product fits) and of tens of
+    thousands (the lift itself is dropped)"""
+    print("stream scales:", D, G, v_scale, flush=True)
+    c, q = _cache(D, G, 2, [3000, 50], 0, (8, 2, 4), 9, v_scale=v_scale)
+    (o, l), (ro, rl) = _both(c, q, D)
+    # without the lift, weights below 2^-24 of the largest are lost: 3,000 of them are 2e-4 of the largest value
+    assert float((o - ro).abs().max()) <= 5e-4 * float(ro.abs().max())
+    assert float((l - rl).abs().max()) <= 1e-4
