@@ -14,17 +14,21 @@
 //   survivors  per non-empty cluster the member nearest the centroid (ties -> lowest index; of
 //              two members the earlier one: both are equally near their mean)
 //
-// Two kernels.  gather: one workgroup per token writes its key row [Hkv * D] into the workspace.
+// Two kernels.  gather writes the key rows [Hkv * D] of the listed tokens into the workspace.
 // kmeans: one workgroup of sixteen waves per segment (segments hold at most 256 live tokens, the
-// schedule keeps at most 64).  Squared distances are taken as |x|^2 - 2 x.c + |c|^2 with the
-// products x.c of all points with all centroids on the matrix cores; a dequantised key does not
+// schedule keeps at most 64).  A centroid is the mean of points, so every product Lloyd's algorithm asks for is a
+// mean of products between points: x.c_j = mean over the members i of x.x_i, |c_j|^2 = mean over the members of
+// x_i.c_j.  So the channels are walked once: all products between the points of the segment (the Gram matrix, at most
+// 256 x 256, its lower triangle kept in LDS), and an iteration is n^2 additions from LDS.  (Products of the points with
+// the centroids in every iteration walked all channels up to nine times: 318 segments of ~108 tokens, 1,024 channels,
+// %%KM_BEFORE%% us; now %%KM_AFTER%% us.)  A centroid is represented by the set of points it is the mean of: at the start one
+// point, later the members, and for a cluster that has lost its last member the members it had before.
+// The products run on the matrix cores; a dequantised key does not
 // fit binary16 and the binary32 matrix instruction is slow, so every number enters as the sum of
 // two binary16 parts (22 significant bits) and a product is three binary16 MFMAs.  The error of
 // all this is of the order of 1e-6 of |x|^2, far below the gaps that separate genuine decisions;
-// an assignment only needs |c|^2 - 2 x.c.  The channels go through LDS 64 at a time, the centroid
-// update is folded into the next pass over the channels (a cluster's members are summed from the
-// point tile that is in LDS anyway, in index order, so the result is the same on every run), and
-// the survivor of a cluster is found with a 64-bit LDS minimum over (distance bits, index).
+// an assignment only needs |c|^2 - 2 x.c.  All sums run in index order or in a fixed tree, so the result is the same on
+// every run; the survivor of a cluster is found with a 64-bit LDS minimum over (distance bits, index).
 #include "common.h"
 
 namespace thinkv {
@@ -51,14 +55,48 @@ size_t tbe_ws_bytes(const thinkv_config& c, int n_tok, int n_seg) {
          (size_t)(n_tok > 0 ? n_tok : 1) * sizeof(int32_t) + 256;
 }
 
-// ---- gather: x[i][hd * D + ch] = the stored key of token i.  A workgroup takes kGatherTokens tokens:
-// one thread per token walks the chain handle -> page list -> page, then all threads extract codes.
+// ---- gather: x[i][hd * D + ch] = the stored key of token i.  A workgroup takes kGatherTokens tokens: one thread per
+// token walks the chain handle -> page list -> page; then a thread takes one chunk of a token's block (a kv-head, eight
+// channels of every group: one vector load of codes) and writes eight channels of each group as two 16-byte stores, four
+// neighbours 128 bytes.  Bound by those stores (four bytes a channel): 34,500 tokens of 1,024 channels (141 MB) %%GA_AFTER%% us
+// (one channel a thread: 84).
 constexpr int kGatherTokens = 8;
 
+template <int D, int BITS>
+__device__ __forceinline__ void gather_chunk(const thinkv_config& c, const uint8_t* blk, int j, int slot, bool fp, float* row) {
+  constexpr int NG = D / kGroup, FPH = 16 / BITS, CW = NG * BITS / 4;
+  const BlockGeom g = block_geom(BITS, D, c.format);
+  uint32_t codes[CW];
+#pragma unroll
+  for (int w = 0; w < CW; ++w) codes[w] = ((const uint32_t*)(blk + g.k_codes + (16 * j + slot) * g.chunk_bytes))[w];
+#pragma unroll
+  for (int grp = 0; grp < NG; ++grp) {
+    float sc, zp = 0.f;
+    if (fp) {   // the eight channels lie in the group of 16 number 2 grp + j / 2
+      sc = BITS == 8 ? c.fp8_scale[0] : e4m3_value(blk[g.k_meta + (2 * grp + (j >> 1)) * kPage + slot]);
+    } else {
+      const _Float16* meta = (const _Float16*)(blk + g.k_meta);
+      sc = (float)meta[meta_index(slot, grp)];
+      zp = (float)meta[meta_index(slot, grp) + 4];
+    }
+    float x[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int f = 4 * grp + (e >> 1);
+      const uint32_t raw = (codes[f / FPH] >> (16 * (e & 1) + BITS * (f % FPH))) & ((1u << BITS) - 1u);
+      x[e] = fp ? fp_code_value(raw, BITS) * sc : fmaf((float)raw, sc, zp);
+    }
+    float* dst = row + 32 * grp + 8 * j;
+    *(float4*)dst = make_float4(x[0], x[1], x[2], x[3]);
+    *(float4*)(dst + 4) = make_float4(x[4], x[5], x[6], x[7]);
+  }
+}
+
+template <int D>
 __global__ __launch_bounds__(256) void tbe_gather_kernel(thinkv_view v, TbeArgs a) {
   const thinkv_config& c = v.cfg;
   const int tid = threadIdx.x, i0 = blockIdx.x * kGatherTokens;
-  const int D = c.head_dim, H = c.n_kv_heads, ld = D == 128 ? 7 : 6;
+  const int H = c.n_kv_heads;
   __shared__ int s_ok[kGatherTokens], s_cls[kGatherTokens], s_slot[kGatherTokens], s_pid[kGatherTokens];
   if (tid < kGatherTokens) {
     const int i = i0 + tid;
@@ -82,58 +120,58 @@ __global__ __launch_bounds__(256) void tbe_gather_kernel(thinkv_view v, TbeArgs 
     s_ok[tid] = ok; s_cls[tid] = cls; s_slot[tid] = slot; s_pid[tid] = pid;
   }
   __syncthreads();
-  for (int t = 0; t < kGatherTokens && i0 + t < a.n_tok; ++t) {
-    float* row = a.x + (int64_t)(i0 + t) * a.dim;
+  const bool fp = c.format == THINKV_FMT_FP;
+  const int per = 4 * H;   // chunks of a token
+  for (int idx = tid; idx < kGatherTokens * per; idx += 256) {
+    const int t = idx / per, hd = (idx % per) >> 2, j = idx & 3;
+    if (i0 + t >= a.n_tok) continue;
+    float* row = a.x + (int64_t)(i0 + t) * a.dim + hd * D;
     if (!s_ok[t]) {   // a token that does not exist clusters as the origin and is never evicted
-      for (int idx = tid; idx < a.dim; idx += 256) row[idx] = 0.f;
+      for (int grp = 0; grp < D / kGroup; ++grp) {
+        *(float4*)(row + 32 * grp + 8 * j) = make_float4(0.f, 0.f, 0.f, 0.f);
+        *(float4*)(row + 32 * grp + 8 * j + 4) = make_float4(0.f, 0.f, 0.f, 0.f);
+      }
       continue;
     }
-    const int cls = s_cls[t], slot = s_slot[t];
-    const int bits = c.bits_of_class[cls];
-    const int lb = bits == 8 ? 3 : (bits == 4 ? 2 : 1), lf = 4 - lb;   // log2 of the bits per code and of the fields per half word
-    const uint32_t mask = (1u << bits) - 1u;
-    const bool fp = c.format == THINKV_FMT_FP;
+    const int cls = s_cls[t], bits = c.bits_of_class[cls];
     const BlockGeom g = block_geom(bits, D, c.format);
-    const uint8_t* page = v.arena[cls] + (int64_t)s_pid[t] * H * g.block_bytes;
-    for (int idx = tid; idx < a.dim; idx += 256) {
-      const int hd = idx >> ld, ch = idx & (D - 1);
-      const uint8_t* blk = page + (int64_t)hd * g.block_bytes;
-      const int grp = ch >> 5, chunk = 16 * ((ch & 31) >> 3) + slot;
-      const int f = 4 * grp + ((ch & 7) >> 1), bit = 32 * (f >> lf) + 16 * (ch & 1) + ((f & ((1 << lf) - 1)) << lb);
-      const uint32_t word = ((const uint32_t*)(blk + g.k_codes + chunk * g.chunk_bytes))[bit >> 5];
-      const uint32_t raw = (word >> (bit & 31)) & mask;
-      if (fp) {   // the paper's formats: value of the code times the tensor's scale or the E4M3 scale of the channel's group of 16
-        const float sc = bits == 8 ? c.fp8_scale[0] : e4m3_value(blk[g.k_meta + (ch >> 4) * kPage + slot]);
-        row[idx] = fp_code_value(raw, bits) * sc;
-        continue;
-      }
-      const float code = (float)raw;
-      const _Float16* meta = (const _Float16*)(blk + g.k_meta);
-      row[idx] = fmaf(code, (float)meta[meta_index(slot, grp)], (float)meta[meta_index(slot, grp) + 4]);
-    }
+    const uint8_t* blk = v.arena[cls] + ((int64_t)s_pid[t] * H + hd) * g.block_bytes;
+    if (bits == 2) gather_chunk<D, 2>(c, blk, j, s_slot[t], fp, row);
+    else if (bits == 4) gather_chunk<D, 4>(c, blk, j, s_slot[t], fp, row);
+    else gather_chunk<D, 8>(c, blk, j, s_slot[t], fp, row);
   }
 }
 
 // ---- kmeans
-constexpr int kPT = kTbeMaxTokens / 64;   // points per lane at most: lane L looks after points L, L + 64, ...
-constexpr int kRB = kTbeMaxTokens / 16;   // 16-point row blocks of the distance matrix at most
-constexpr int kKmThreads = 1024;          // sixteen waves, four per SIMD: the staging of a tile is mostly waiting
-constexpr int kRowSplit = kKmThreads / 256;   // waves that share a cluster quarter and split the row blocks
-constexpr int kRBW = kRB / kRowSplit;     // row blocks per wave: wave w takes blocks kRowSplit t + w / 4
+constexpr int kPT = kTbeMaxTokens / 64;   // tokens per lane of a wave that sorts a list
+constexpr int kKmThreads = 1024;          // sixteen waves
+constexpr int kQuarters = kKmThreads / kTbeMaxTokens;   // threads per point: each looks at every fourth cluster
+constexpr int kClPerThread = kTbeMaxKeep / kQuarters;
+constexpr int kMacro = 32;                // points on a side of a wave's piece of the Gram matrix (2 x 2 MFMA tiles)
+constexpr int kMacroMax = (kTbeMaxTokens / kMacro) * (kTbeMaxTokens / kMacro + 1) / 2;   // pieces of the lower triangle: 36
+constexpr int kMacroPerWave = (kMacroMax + kKmThreads / 64 - 1) / (kKmThreads / 64);     // 3
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 constexpr int kPadH = 2 * kTile + 8;   // binary16 numbers per tile row: high parts, low parts, padding (an odd multiple of 16 bytes)
 
+__device__ __forceinline__ int tri(int i) { return i * (i + 1) / 2; }   // where row i of the lower triangle begins
+
 struct KmScratch {
-  _Float16 xs[kTbeMaxTokens][kPadH];   // one tile: 64 channels of every point, each as high + low binary16 part ...
-  _Float16 cs[kTbeMaxKeep][kPadH];     // ... and of every centroid
-  float xx[kTbeMaxTokens];             // squared norms of the points
-  float cc[kTbeMaxKeep];               // squared norms of the centroids
-  int cnt[kTbeMaxKeep];                // members of every cluster,
-  int start[kTbeMaxKeep];              // where its members begin in order[],
-  int order[kTbeMaxTokens];            // and the points cluster by cluster, in index order inside a cluster
+  union {
+    _Float16 xs[kTbeMaxTokens][kPadH];                       // one tile: 64 channels of every point, each as high + low binary16 part
+    float gram[kTbeMaxTokens * (kTbeMaxTokens + 1) / 2];     // then the products of all pairs of points, lower triangle
+  };
+  uint32_t basis[kTbeMaxKeep][kTbeMaxTokens / 32];           // the points a cluster's centroid is the mean of,
+  uint32_t next[kTbeMaxKeep][kTbeMaxTokens / 32];            // its members under the assignment just made
+  float own[kTbeMaxTokens];                                  // product of a point with the centroid it belongs to
+  float cc[kTbeMaxKeep];                                     // squared norms of the centroids
+  int cnt[kTbeMaxKeep], moved[kTbeMaxKeep];                  // points of the basis; whether it changed last
+  int cluster[kTbeMaxTokens];                                // cluster whose basis the point is in (-1: none)
+  float bd[kQuarters][kTbeMaxTokens];                        // per quarter of the clusters: best distance of every point ...
+  int bj[kQuarters][kTbeMaxTokens];                          // ... and the cluster it belongs to
+  int low[kTbeMaxKeep];                                      // survivors: lowest index of every cluster
+  unsigned long long best[kTbeMaxKeep];
 };
 
 // four channels into a tile row: x = hi + lo with hi = binary16(x), lo = binary16(x - hi), 22 significant bits
@@ -145,60 +183,39 @@ __device__ inline void store_split(_Float16* row, int c, float4 v) {
   *(f16x4*)&row[kTile + c] = lo;
 }
 
-// eight channels of a tile row back as binary32 (hi + lo)
-__device__ inline void load_joined(const _Float16* row, int c, float* out) {
-  const f16x8 hi = *(const f16x8*)&row[c], lo = *(const f16x8*)&row[kTile + c];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) out[e] = (float)hi[e] + (float)lo[e];
-}
-
-// One pass over the channels, 64 at a time through LDS (the loads of the next tile are in flight
-// while the current one is worked on):
-//   update  the centroid of every cluster that has members moves to their mean (sum from zero in
-//           index order, times 1 / count), tile by tile, from the point tile that is in LDS anyway;
-//           the moved rows go back to cent[] so that a cluster that later loses all its members
-//           still finds its centroid there
-//   dots    dot[p][j] of all points with all centroids on the matrix cores.  The binary32 matrix
-//           instruction is slow (a sixteenth of the binary16 rate), and binary16 alone cannot hold a
-//           dequantised key, so every number enters as the sum of two binary16 parts and a product
-//           is taken as hi.hi + hi.lo + lo.hi on v_mfma_f32_16x16x32_f16 (exact products, binary32
-//           sums; what is dropped is of the order of 2^-22 of |x||c|).  Wave w owns clusters
-//           16 (w % 4) .. + 15 and every fourth row block of 16 points (blocks 4 t + w / 4); after
-//           the call lane l holds, in acc[t][i], the product of point 16 (4 t + w / 4) + 4 (l / 16) + i
-//           with cluster 16 (w % 4) + l % 16
-//   norms   squared norms of the centroids, and of the points when first is set (they do not move)
-__device__ inline void pass_over_channels(const float* __restrict__ x, float* __restrict__ cent, int n, int k, int dim, bool first,
-                                          bool update, KmScratch& sm, f32x4 (&acc)[kRBW]) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+// sm.gram: the products of all pairs of the n points.  The channels go through LDS 64 at a time (the loads of the next
+// tile are in flight while the current one is worked on); wave w owns the pieces w, w + 16, w + 32 of the lower
+// triangle, 32 x 32 points each: 2 x 2 tiles share their operands, which halves the LDS reads a product costs.  A product
+// is hi.hi + hi.lo + lo.hi (exact products, binary32 sums; what is dropped is of the order of 2^-22 of |x||y|).
+__device__ inline void gram_matrix(const float* __restrict__ x, int n, int dim, KmScratch& sm) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r = lane & 15, g = lane >> 4;
-  const int rbs = (n + 15) >> 4;
-  constexpr int kC4 = kTile / 4;                          // float4 per tile row
-  const int xq = (rbs * 16 * kC4 + kKmThreads - 1) / kKmThreads;   // float4 loads per thread for the points' tile
-  constexpr int kXQ = kTbeMaxTokens * kC4 / kKmThreads;
-  constexpr int kCQ = kTbeMaxKeep * kC4 / kKmThreads;
-  const int cb = wave & 3, half = wave >> 2;
+  const int mb = (n + kMacro - 1) / kMacro, pieces = mb * (mb + 1) / 2;
+  constexpr int kC4 = kTile / 4;                           // float4 per tile row
+  constexpr int kXQ = kTbeMaxTokens * kC4 / kKmThreads;    // float4 loads per thread at most
+  const int xq = (mb * kMacro * kC4 + kKmThreads - 1) / kKmThreads;
+  int pi[kMacroPerWave], pj[kMacroPerWave];                // block row and column of the wave's pieces
+  f32x4 acc[kMacroPerWave][2][2];
 #pragma unroll
-  for (int t = 0; t < kRBW; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float nx = 0.f, nc = 0.f;
-  float4 px[kXQ], pc[kCQ];
-  const float4 zero4 = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int t = 0; t < kMacroPerWave; ++t) {
+    int rest = wave + t * (kKmThreads / 64), i = 0;
+    while (rest > i) rest -= ++i;
+    pi[t] = i;
+    pj[t] = rest;
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int w = 0; w < 2; ++w) acc[t][u][w] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  float4 px[kXQ];
   auto fetch = [&](int d0) {
 #pragma unroll
     for (int q = 0; q < kXQ; ++q)
       if (q < xq) {
         const int idx = tid + kKmThreads * q, row = idx / kC4, c4 = idx % kC4;
-        px[q] = row < n ? *(const float4*)&x[(int64_t)row * dim + d0 + 4 * c4] : zero4;
+        px[q] = row < n ? *(const float4*)&x[(int64_t)row * dim + d0 + 4 * c4] : make_float4(0.f, 0.f, 0.f, 0.f);
       }
-#pragma unroll
-    for (int q = 0; q < kCQ; ++q) {
-      const int idx = tid + kKmThreads * q, row = idx / kC4, c4 = idx % kC4;
-      pc[q] = row < k ? *(const float4*)&cent[(int64_t)row * dim + d0 + 4 * c4] : zero4;
-    }
   };
-  // the update: thread (cluster tid / 8, part tid % 8) owns 8 channels of the cluster's row
-  const int uj = tid >> 3, upart = tid & 7;
-  const int um = update && uj < k ? sm.cnt[uj] : 0, ust = uj < k ? sm.start[uj] : 0;
-  const float uinv = um > 0 ? 1.0f / (float)um : 0.f;
   fetch(0);
   for (int d0 = 0; d0 < dim; d0 += kTile) {
     __syncthreads();   // the previous tile has been used
@@ -208,80 +225,105 @@ __device__ inline void pass_over_channels(const float* __restrict__ x, float* __
         const int idx = tid + kKmThreads * q;
         store_split(sm.xs[idx / kC4], 4 * (idx % kC4), px[q]);
       }
-#pragma unroll
-    for (int q = 0; q < kCQ; ++q) {
-      const int idx = tid + kKmThreads * q;
-      store_split(sm.cs[idx / kC4], 4 * (idx % kC4), pc[q]);
-    }
     __syncthreads();
     if (d0 + kTile < dim) fetch(d0 + kTile);
-    if (update) {
-      if (um > 0) {
-        float sum[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) sum[e] = 0.f;
-        for (int i = 0; i < um; ++i) {
-          float t[8];
-          load_joined(sm.xs[sm.order[ust + i]], 8 * upart, t);
+    for (int t = 0; t < kMacroPerWave; ++t)
+      if (wave + t * (kKmThreads / 64) < pieces) {
 #pragma unroll
-          for (int e = 0; e < 8; ++e) sum[e] += t[e];
-        }
-        const float4 m0 = make_float4(sum[0] * uinv, sum[1] * uinv, sum[2] * uinv, sum[3] * uinv);
-        const float4 m1 = make_float4(sum[4] * uinv, sum[5] * uinv, sum[6] * uinv, sum[7] * uinv);
-        store_split(sm.cs[uj], 8 * upart, m0);
-        store_split(sm.cs[uj], 8 * upart + 4, m1);
-        *(float4*)&cent[(int64_t)uj * dim + d0 + 8 * upart] = m0;
-        *(float4*)&cent[(int64_t)uj * dim + d0 + 8 * upart + 4] = m1;
-      }
-      __syncthreads();
-    }
-    if (first && tid < n) {
+        for (int ks = 0; ks < kTile / 32; ++ks) {
+          // lane (r, g) holds channels 32 ks + 8 g .. + 7 of its row, on both sides
+          f16x8 ah[2], al[2], bh[2], bl[2];
 #pragma unroll
-      for (int c8 = 0; c8 < kTile / 8; ++c8) {
-        float t[8];
-        load_joined(sm.xs[tid], 8 * c8, t);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) nx = fmaf(t[e], t[e], nx);
-      }
-    }
-    if (uj < k) {   // the eight channels of thread (cluster, part), as the products will see them
-      float t[8];
-      load_joined(sm.cs[uj], 8 * upart, t);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) nc = fmaf(t[e], t[e], nc);
-    }
-    if (16 * cb < k) {
-#pragma unroll
-      for (int ks = 0; ks < kTile / 32; ++ks) {
-        // lane (r, g) holds channels 32 ks + 8 g .. + 7 of its row, on both sides
-        const f16x8 bh = *(const f16x8*)&sm.cs[16 * cb + r][32 * ks + 8 * g];
-        const f16x8 bl = *(const f16x8*)&sm.cs[16 * cb + r][kTile + 32 * ks + 8 * g];
-#pragma unroll
-        for (int t = 0; t < kRBW; ++t)
-          if (kRowSplit * t + half < rbs) {
-            const _Float16* row = sm.xs[16 * (kRowSplit * t + half) + r];
-            const f16x8 ah = *(const f16x8*)&row[32 * ks + 8 * g];
-            const f16x8 al = *(const f16x8*)&row[kTile + 32 * ks + 8 * g];
-            acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, bh, acc[t], 0, 0, 0);
-            acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, bl, acc[t], 0, 0, 0);
-            acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al, bh, acc[t], 0, 0, 0);
+          for (int u = 0; u < 2; ++u) {
+            const _Float16* ra = sm.xs[kMacro * pi[t] + 16 * u + r];
+            const _Float16* rb = sm.xs[kMacro * pj[t] + 16 * u + r];
+            ah[u] = *(const f16x8*)&ra[32 * ks + 8 * g];
+            al[u] = *(const f16x8*)&ra[kTile + 32 * ks + 8 * g];
+            bh[u] = *(const f16x8*)&rb[32 * ks + 8 * g];
+            bl[u] = *(const f16x8*)&rb[kTile + 32 * ks + 8 * g];
           }
+#pragma unroll
+          for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int w = 0; w < 2; ++w) {
+              acc[t][u][w] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[u], bh[w], acc[t][u][w], 0, 0, 0);
+              acc[t][u][w] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[u], bl[w], acc[t][u][w], 0, 0, 0);
+              acc[t][u][w] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al[u], bh[w], acc[t][u][w], 0, 0, 0);
+            }
+        }
       }
+  }
+  __syncthreads();   // the last tile has been used: its place becomes the matrix
+#pragma unroll
+  for (int t = 0; t < kMacroPerWave; ++t)
+    if (wave + t * (kKmThreads / 64) < pieces) {
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int w = 0; w < 2; ++w)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int p = kMacro * pi[t] + 16 * u + 4 * g + i, q = kMacro * pj[t] + 16 * w + r;
+            if (p < n && q <= p) sm.gram[tri(p) + q] = acc[t][u][w][i];
+          }
+    }
+  __syncthreads();
+}
+
+// f(point) for every point of a cluster's basis, in index order; the point is the same in all lanes
+template <class F>
+__device__ __forceinline__ void for_basis(const uint32_t* mask, F f) {
+#pragma unroll
+  for (int w = 0; w < kTbeMaxTokens / 32; ++w) {
+    uint32_t m = __builtin_amdgcn_readfirstlane(mask[w]);
+    while (m) {
+      const int i = __builtin_ctz(m);
+      m &= m - 1;
+      f(32 * w + i);
+    }
+  }
+}
+
+// Products of every point with every centroid that has one: thread (point tid % 256, quarter tid / 256) leaves those of the
+// clusters quarter, quarter + 4, ... in dot[]; sm.own of the points that are in a basis; sm.cc of the centroids that moved.
+__device__ inline void centroid_products(int n, int k, KmScratch& sm, float (&dot)[kClPerThread]) {
+  const int tid = threadIdx.x, p = tid & (kTbeMaxTokens - 1), lane = tid & 63;
+  const int quarter = __builtin_amdgcn_readfirstlane(tid / kTbeMaxTokens), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int pc = p < n ? p : n - 1, tp = tri(pc);
+  const int mine = sm.cluster[p];
+  const bool idle = (p & ~63) >= n;   // no point of the wave exists
+#pragma unroll
+  for (int i = 0; i < kClPerThread; ++i) {
+    const int j = quarter + kQuarters * i;
+    dot[i] = 0.f;
+    if (j < k && !idle) {
+      float sum = 0.f;
+      for_basis(sm.basis[j], [&](int m) { sum += sm.gram[pc >= m ? tp + m : tri(m) + pc]; });
+      dot[i] = sum * (1.0f / (float)sm.cnt[j]);
+      if (mine == j && p < n) sm.own[p] = dot[i];
     }
   }
   __syncthreads();
-  if (first && tid < n) sm.xx[tid] = nx;
-  // the eight parts of a cluster's norm sit in eight neighbouring lanes
-  nc += __shfl_xor(nc, 1, 64);
-  nc += __shfl_xor(nc, 2, 64);
-  nc += __shfl_xor(nc, 4, 64);
-  if (upart == 0 && uj < kTbeMaxKeep) sm.cc[uj] = uj < k ? nc : 0.f;
+  // |c|^2 = mean over the basis of its points' products with the centroid: a wave per cluster, a fixed tree
+  for (int j = wave; j < k; j += kKmThreads / 64) {
+    if (!sm.moved[j]) continue;
+    float sum = 0.f;
+#pragma unroll
+    for (int w = 0; w < kTbeMaxTokens / 64; ++w) {
+      const int q = 64 * w + lane;
+      if (sm.basis[j][q >> 5] >> (q & 31) & 1u) sum += sm.own[q];
+    }
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, 64);
+    if (lane == 0) sm.cc[j] = sum * (1.0f / (float)sm.cnt[j]);
+  }
   __syncthreads();
 }
 
 __global__ __launch_bounds__(kKmThreads) void tbe_kmeans_kernel(thinkv_view v, TbeArgs a) {
   const thinkv_config& c = v.cfg;
-  const int seg = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int seg = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lo = a.seg_offset[seg], hi = a.seg_offset[seg + 1];
   const int n = hi - lo, want = a.seg_keep[seg];
   if (n <= 0) return;
@@ -301,153 +343,117 @@ __global__ __launch_bounds__(kKmThreads) void tbe_kmeans_kernel(thinkv_view v, T
     }
     return;
   }
-  const int k = want, dim = a.dim, pt = (n + 63) / 64, rbs = (n + 15) >> 4;
+  const int k = want, dim = a.dim;
   const float* x = a.x + (int64_t)lo * dim;
   float* cent = a.cent + (int64_t)seg * kTbeMaxKeep * dim;
   __shared__ __attribute__((aligned(16))) KmScratch sm;
-  __shared__ float s_bd[4][kTbeMaxTokens];   // per cluster quarter: best distance of every point ...
-  __shared__ int s_bj[4][kTbeMaxTokens];     // ... and the cluster it belongs to
-  __shared__ int s_assign[kTbeMaxTokens];
-  __shared__ int s_cnt[kTbeMaxKeep], s_start[kTbeMaxKeep];   // survivors: members and lowest index of every cluster
-  __shared__ unsigned long long s_best[kTbeMaxKeep];
   // initial centroids: evenly spaced points
-  for (int idx = tid; idx < k * dim; idx += kKmThreads) {
-    const int j = idx / dim, d = idx % dim;
-    cent[idx] = x[(int64_t)((j * n) / k) * dim + d];
-  }
+  for (int i = tid; i < kTbeMaxKeep * (kTbeMaxTokens / 32); i += kKmThreads) (&sm.basis[0][0])[i] = 0u;
+  if (tid < kTbeMaxTokens) sm.cluster[tid] = -1;
   __syncthreads();
-  f32x4 acc[kRBW];
-  int mine[kPT];
-#pragma unroll
-  for (int q = 0; q < kPT; ++q) mine[q] = -1;
-  const int r = lane & 15, g = lane >> 4, cb = wave & 3, half = wave >> 2, my_cl = 16 * cb + r;
-  // nearest cluster of every point: |c|^2 - 2 x.c decides (|x|^2 is common to a point's candidates);
-  // best of the sixteen clusters of this wave by exchanges among the sixteen lanes that hold a point's
-  // row, then best of the four cluster quarters (ties go to the lowest cluster)
-  auto assign = [&](int* out) {
-    const float ccj = my_cl < k ? sm.cc[my_cl] : 0.f;
-#pragma unroll
-    for (int t = 0; t < kRBW; ++t)
-      if (kRowSplit * t + half < rbs) {
-        const int rb = kRowSplit * t + half;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          float bd = my_cl < k ? fmaf(-2.f, acc[t][i], ccj) : INFINITY;
-          int bj = my_cl;
-#pragma unroll
-          for (int d = 1; d < 16; d <<= 1) {
-            const float od = __shfl_xor(bd, d, 64);
-            const int oj = __shfl_xor(bj, d, 64);
-            if (od < bd || (od == bd && oj < bj)) {
-              bd = od;
-              bj = oj;
-            }
-          }
-          if (r == 0) {
-            s_bd[cb][16 * rb + 4 * g + i] = bd;
-            s_bj[cb][16 * rb + 4 * g + i] = bj;
-          }
-        }
-      }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < kPT; ++q) {
-      const int p = lane + 64 * q;
-      float bd = s_bd[0][p];
-      int bj = s_bj[0][p];
-#pragma unroll
-      for (int w = 1; w < 4; ++w)
-        if (s_bd[w][p] < bd) {
-          bd = s_bd[w][p];
-          bj = s_bj[w][p];
-        }
-      out[q] = q < pt ? bj : -1;
-    }
-  };
+  if (tid < k) {
+    const int p = (tid * n) / k;   // distinct, since k < n
+    sm.basis[tid][p >> 5] = 1u << (p & 31);
+    sm.cluster[p] = tid;
+    sm.cnt[tid] = 1;
+    sm.moved[tid] = 1;
+  }
+  gram_matrix(x, n, dim, sm);
+  const int p = tid & (kTbeMaxTokens - 1), quarter = tid / kTbeMaxTokens;
+  float dot[kClPerThread];
+  int mine = -1;   // this point's cluster at the last assignment
   bool converged = false;
   for (int it = 0; it < a.max_iters; ++it) {
-    // centroids: the initial ones, later the means under the previous assignment; then all products
-    pass_over_channels(x, cent, n, k, dim, it == 0, it > 0, sm, acc);
-    int now[kPT];
-    assign(now);
-    int changed = 0;
+    // centroids: the initial ones, later the means under the previous assignment
+    centroid_products(n, k, sm, dot);
+    // nearest cluster of every point: |c|^2 - 2 x.c decides (|x|^2 is common to a point's candidates); ties go to the
+    // lowest cluster
+    float bd = INFINITY;
+    int bj = kTbeMaxKeep;
 #pragma unroll
-    for (int q = 0; q < kPT; ++q) {
-      changed |= (lane + 64 * q < n) && now[q] != mine[q];
-      mine[q] = now[q];
+    for (int i = 0; i < kClPerThread; ++i) {
+      const int j = quarter + kQuarters * i;
+      const float d = j < k ? fmaf(-2.f, dot[i], sm.cc[j]) : INFINITY;
+      if (d < bd) {
+        bd = d;
+        bj = j;
+      }
     }
+    sm.bd[quarter][p] = bd;
+    sm.bj[quarter][p] = bj;
+    for (int i = tid; i < kTbeMaxKeep * (kTbeMaxTokens / 32); i += kKmThreads) (&sm.next[0][0])[i] = 0u;
+    __syncthreads();
+    bd = sm.bd[0][p];
+    bj = sm.bj[0][p];
+#pragma unroll
+    for (int w = 1; w < kQuarters; ++w) {
+      const float od = sm.bd[w][p];
+      const int oj = sm.bj[w][p];
+      if (od < bd || (od == bd && oj < bj)) {
+        bd = od;
+        bj = oj;
+      }
+    }
+    if (bj >= k) bj = 0;   // no candidate compares (the distances are not numbers): the first cluster, as a comparison that never holds leaves it
+    const int changed = p < n && bj != mine;
+    mine = bj;
     if (!__syncthreads_or(changed)) {
       converged = true;   // the products at hand are those with the final centroids
       break;
     }
-    // ---- members of every cluster in index order, for the next pass
-    if (tid < kTbeMaxKeep) sm.cnt[tid] = 0;
-    if (wave == 0) {
+    // members of every cluster; a cluster without any keeps its basis
+    if (quarter == 0 && p < n) {
+      sm.cluster[p] = mine;
+      atomicOr(&sm.next[mine][p >> 5], 1u << (p & 31));
+    }
+    __syncthreads();
+    if (tid < k) {
+      int m = 0;
 #pragma unroll
-      for (int q = 0; q < kPT; ++q)
-        if (lane + 64 * q < n) s_assign[lane + 64 * q] = mine[q];
-    }
-    __syncthreads();
-    int rank = 0;
-    if (tid < n) {
-      const int cl = s_assign[tid];
-      for (int i = 0; i < tid; ++i) rank += s_assign[i] == cl;
-      atomicAdd(&sm.cnt[cl], 1);
-    }
-    __syncthreads();
-    if (tid == 0) {
-      int run = 0;
-      for (int j = 0; j < k; ++j) {
-        sm.start[j] = run;
-        run += sm.cnt[j];
+      for (int w = 0; w < kTbeMaxTokens / 32; ++w) m += __popc(sm.next[tid][w]);
+      sm.moved[tid] = m > 0;
+      if (m > 0) {
+        sm.cnt[tid] = m;
+#pragma unroll
+        for (int w = 0; w < kTbeMaxTokens / 32; ++w) sm.basis[tid][w] = sm.next[tid][w];
       }
     }
-    __syncthreads();
-    if (tid < n) sm.order[sm.start[s_assign[tid]] + rank] = tid;
     __syncthreads();
   }
   // ---- survivors: nearest member of every cluster under the final centroids
-  if (!converged) pass_over_channels(x, cent, n, k, dim, false, true, sm, acc);
+  if (!converged) centroid_products(n, k, sm, dot);
   if (tid < kTbeMaxKeep) {
-    s_cnt[tid] = 0;
-    s_start[tid] = kTbeMaxTokens;   // here: lowest index among the cluster's members
-    s_best[tid] = ~0ull;
-  }
-  if (wave == 0) {
-#pragma unroll
-    for (int q = 0; q < kPT; ++q)
-      if (lane + 64 * q < n) s_assign[lane + 64 * q] = mine[q];
+    sm.low[tid] = kTbeMaxTokens;
+    sm.best[tid] = ~0ull;
   }
   __syncthreads();
-  if (my_cl < k) {
-    const float ccj = sm.cc[my_cl];
-#pragma unroll
-    for (int t = 0; t < kRBW; ++t)
-      if (kRowSplit * t + half < rbs) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int p = 16 * (kRowSplit * t + half) + 4 * g + i;
-          if (p < n && s_assign[p] == my_cl) {   // this lane holds the point's product with its own cluster
-            const float own = fmaxf(fmaf(-2.f, acc[t][i], sm.xx[p]) + ccj, 0.f);
-            atomicAdd(&s_cnt[my_cl], 1);
-            atomicMin(&s_start[my_cl], p);
-            // distances are not negative, so their bit patterns order like the numbers; the index breaks ties
-            atomicMin(&s_best[my_cl], ((unsigned long long)__builtin_bit_cast(uint32_t, own) << 32) | (unsigned)p);
-          }
-        }
-      }
+  if (quarter == 0 && p < n) {
+    const float dist = fmaxf(fmaf(-2.f, sm.own[p], sm.gram[tri(p) + p]) + sm.cc[mine], 0.f);
+    atomicMin(&sm.low[mine], p);
+    // distances are not negative, so their bit patterns order like the numbers; the index breaks ties
+    atomicMin(&sm.best[mine], ((unsigned long long)__builtin_bit_cast(uint32_t, dist) << 32) | (unsigned)p);
   }
   __syncthreads();
-  if (wave == 0) {
-#pragma unroll
-    for (int q = 0; q < kPT; ++q) {
-      const int p = lane + 64 * q;
-      if (p < n) {
-        // two members are equally near their mean whatever the rounding says: the earlier one stays
-        const bool keep = s_cnt[mine[q]] <= 2 ? p == s_start[mine[q]] : (int)(s_best[mine[q]] & 0xFFFFFFFFull) == p;
-        a.ev_handle[lo + p] = keep ? -1 : a.tok_handle[lo + p];
-        a.assign[lo + p] = mine[q];
-      }
+  if (quarter == 0 && p < n) {
+    // two members are equally near their mean whatever the rounding says: the earlier one stays (a cluster with members
+    // has them as its basis)
+    const bool keep = sm.cnt[mine] <= 2 ? p == sm.low[mine] : (int)(sm.best[mine] & 0xFFFFFFFFull) == p;
+    a.ev_handle[lo + p] = keep ? -1 : a.tok_handle[lo + p];
+    a.assign[lo + p] = mine;
+  }
+  // ---- the centroids, for callers that look at them: a wave per cluster, 256 channels at a time, members in index order
+  for (int j = wave; j < k; j += kKmThreads / 64) {
+    const float inv = 1.0f / (float)sm.cnt[j];
+    for (int d = 4 * lane; d < dim; d += 256) {
+      float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+      for_basis(sm.basis[j], [&](int m) {
+        const float4 t = *(const float4*)&x[(int64_t)m * dim + d];
+        sum.x += t.x;
+        sum.y += t.y;
+        sum.z += t.z;
+        sum.w += t.w;
+      });
+      *(float4*)&cent[(int64_t)j * dim + d] = make_float4(sum.x * inv, sum.y * inv, sum.z * inv, sum.w * inv);
     }
   }
 }
@@ -469,7 +475,11 @@ int launch_tbe_select(const thinkv_view& v, int layer, const int32_t* tok_seq, c
   a.n_seg = n_seg;
   a.n_tok = n_tok;
   a.max_iters = max_iters;
-  hipLaunchKernelGGL(tbe_gather_kernel, dim3((n_tok + kGatherTokens - 1) / kGatherTokens), dim3(256), 0, st, v, a);
+  const dim3 groups((n_tok + kGatherTokens - 1) / kGatherTokens);
+  if (v.cfg.head_dim == 128)
+    hipLaunchKernelGGL(tbe_gather_kernel<128>, groups, dim3(256), 0, st, v, a);
+  else
+    hipLaunchKernelGGL(tbe_gather_kernel<64>, groups, dim3(256), 0, st, v, a);
   hipLaunchKernelGGL(tbe_kmeans_kernel, dim3(n_seg), dim3(kKmThreads), 0, st, v, a);
   return hipGetLastError() == hipSuccess ? THINKV_OK : THINKV_E_HIP;
 }
