@@ -183,8 +183,8 @@ __device__ inline void store_split(_Float16* row, int c, float4 v) {
   *(f16x4*)&row[kTile + c] = lo;
 }
 
-// sm.gram: the products of all pairs of the n points.  The channels go through LDS 64 at a time (the loads of the next
-// tile are in flight while the current one is worked on); wave w owns the pieces w, w + 16, w + 32 of the lower
+// sm.gram: the products of all pairs of the n points.  The channels go through LDS 64 at a time (the loads of the next two
+// tiles are in flight while the current one is worked on); wave w owns the pieces w, w + 16, w + 32 of the lower
 // triangle, 32 x 32 points each: 2 x 2 tiles share their operands, which halves the LDS reads a product costs.  A product
 // is hi.hi + hi.lo + lo.hi (exact products, binary32 sums; what is dropped is of the order of 2^-22 of |x||y|).
 __device__ inline void gram_matrix(const float* __restrict__ x, int n, int dim, KmScratch& sm) {
@@ -207,17 +207,16 @@ __device__ inline void gram_matrix(const float* __restrict__ x, int n, int dim, 
 #pragma unroll
       for (int w = 0; w < 2; ++w) acc[t][u][w] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-  float4 px[kXQ];
-  auto fetch = [&](int d0) {
+  float4 pa[kXQ], pb[kXQ];   // two tiles ahead, used in turn
+  auto fetch = [&](int d0, float4 (&px)[kXQ]) {
 #pragma unroll
     for (int q = 0; q < kXQ; ++q)
       if (q < xq) {
         const int idx = tid + kKmThreads * q, row = idx / kC4, c4 = idx % kC4;
-        px[q] = row < n ? *(const float4*)&x[(int64_t)row * dim + d0 + 4 * c4] : make_float4(0.f, 0.f, 0.f, 0.f);
+        px[q] = row < n && d0 < dim ? *(const float4*)&x[(int64_t)row * dim + d0 + 4 * c4] : make_float4(0.f, 0.f, 0.f, 0.f);
       }
   };
-  fetch(0);
-  for (int d0 = 0; d0 < dim; d0 += kTile) {
+  auto tile = [&](int d0, float4 (&px)[kXQ]) {
     __syncthreads();   // the previous tile has been used
 #pragma unroll
     for (int q = 0; q < kXQ; ++q)
@@ -226,7 +225,7 @@ __device__ inline void gram_matrix(const float* __restrict__ x, int n, int dim, 
         store_split(sm.xs[idx / kC4], 4 * (idx % kC4), px[q]);
       }
     __syncthreads();
-    if (d0 + kTile < dim) fetch(d0 + kTile);
+    fetch(d0 + 2 * kTile, px);
 #pragma unroll
     for (int t = 0; t < kMacroPerWave; ++t)
       if (wave + t * (kKmThreads / 64) < pieces) {
@@ -253,6 +252,12 @@ __device__ inline void gram_matrix(const float* __restrict__ x, int n, int dim, 
             }
         }
       }
+  };
+  fetch(0, pa);
+  fetch(kTile, pb);
+  for (int d0 = 0; d0 < dim; d0 += 2 * kTile) {
+    tile(d0, pa);
+    if (d0 + kTile < dim) tile(d0 + kTile, pb);
   }
   __syncthreads();   // the last tile has been used: its place becomes the matrix
 #pragma unroll
@@ -441,19 +446,29 @@ __global__ __launch_bounds__(kKmThreads) void tbe_kmeans_kernel(thinkv_view v, T
     a.ev_handle[lo + p] = keep ? -1 : a.tok_handle[lo + p];
     a.assign[lo + p] = mine;
   }
-  // ---- the centroids, for callers that look at them: a wave per cluster, 256 channels at a time, members in index order
+  // ---- the centroids, for callers that look at them: a wave per cluster, up to 1,024 channels at a time (four loads a
+  // lane in flight), members in index order
   for (int j = wave; j < k; j += kKmThreads / 64) {
     const float inv = 1.0f / (float)sm.cnt[j];
-    for (int d = 4 * lane; d < dim; d += 256) {
-      float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int d0 = 4 * lane; d0 < dim; d0 += 1024) {
+      float4 sum[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) sum[u] = make_float4(0.f, 0.f, 0.f, 0.f);
       for_basis(sm.basis[j], [&](int m) {
-        const float4 t = *(const float4*)&x[(int64_t)m * dim + d];
-        sum.x += t.x;
-        sum.y += t.y;
-        sum.z += t.z;
-        sum.w += t.w;
+        float4 t[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) t[u] = d0 + 256 * u < dim ? *(const float4*)&x[(int64_t)m * dim + d0 + 256 * u] : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          sum[u].x += t[u].x;
+          sum[u].y += t[u].y;
+          sum[u].z += t[u].z;
+          sum[u].w += t[u].w;
+        }
       });
-      *(float4*)&cent[(int64_t)j * dim + d] = make_float4(sum.x * inv, sum.y * inv, sum.z * inv, sum.w * inv);
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (d0 + 256 * u < dim) *(float4*)&cent[(int64_t)j * dim + d0 + 256 * u] = make_float4(sum[u].x * inv, sum[u].y * inv, sum[u].z * inv, sum[u].w * inv);
     }
   }
 }
