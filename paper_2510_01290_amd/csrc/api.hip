@@ -156,6 +156,31 @@ static ItemSizing size_stream(const thinkv_config& c, int B, int max_ctx_pages, 
   return z;
 }
 
+// Sliding-window layers of the fast kernel: an item is a workgroup of eight waves that scans the page lists for hg kv-heads and
+// attends what is visible with 8 / hg waves a head.  As many heads to a workgroup as leave a workgroup for every compute
+// unit (fewer repeated scans), and, where even one head a workgroup does not, several items to a head: at least 512
+// tokens of the window each.
+static ItemSizing size_window(const thinkv_config& c, int B, int max_ctx_pages, int window, int* heads_per_group) {
+  const int64_t heads = (int64_t)B * c.n_kv_heads, cus = compute_units();
+  int hg = 1;
+  while (hg < kWindowWaves && 2 * hg <= c.n_kv_heads && heads >= 2 * hg * cus) hg *= 2;
+  const int64_t groups = (int64_t)B * ((c.n_kv_heads + hg - 1) / hg);
+  const int64_t pages = max_ctx_pages > 0 ? max_ctx_pages : 1;
+  int64_t per_head = cus / groups;
+  const int64_t cap = ((int64_t)window + 511) / 512, by_pages = (pages + 63) / 64, room = rows_bound(c, B, max_ctx_pages) / heads;
+  if (per_head > cap) per_head = cap;
+  if (per_head > by_pages) per_head = by_pages;
+  if (per_head > room) per_head = room;
+  if (per_head > kMaxRowsPerHead) per_head = kMaxRowsPerHead;
+  if (per_head < 1) per_head = 1;
+  *heads_per_group = hg;
+  ItemSizing z;
+  z.per_head = (int)per_head;
+  z.n_rows = (int)(per_head * heads);
+  z.ppi = (int)((pages + per_head - 1) / per_head);
+  return z;
+}
+
 static size_t partial_bytes_of(const thinkv_config& c, int64_t rows) {
   const int G = c.n_q_heads / c.n_kv_heads;
   return (size_t)rows * G * (c.head_dim + kRowPad) * sizeof(float);
@@ -191,7 +216,8 @@ static int decode_common(const thinkv_view* view, int32_t layer, const void* q, 
   a.q_dtype = q_dtype;
   a.out_dtype = out_dtype;
   a.waves = 0;
-  const ItemSizing z = fast && window == 0 ? size_stream(view->cfg, B, max_ctx_pages, &a.waves) : size_items(view->cfg, B, max_ctx_pages, window, fast);
+  const ItemSizing z = !fast ? size_items(view->cfg, B, max_ctx_pages, window, false)
+                             : (window > 0 ? size_window(view->cfg, B, max_ctx_pages, window, &a.waves) : size_stream(view->cfg, B, max_ctx_pages, &a.waves));
   if (z.n_rows > rows_bound(view->cfg, B, max_ctx_pages)) return THINKV_E_WORKSPACE;   // cannot happen: a launch never has more rows than the workspace
   a.n_rows = z.n_rows;
   a.per_head = z.per_head;

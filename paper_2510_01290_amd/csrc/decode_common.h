@@ -21,6 +21,12 @@
 __host__ __device__ constexpr int decode_waves_per_simd(int head_dim, bool fp) { return (head_dim == 64 ? 3 : 2) + (fp ? 1 : 0); }
 __host__ __device__ constexpr int stream_ring_bytes(int head_dim, bool fp) { return 147456 / (4 * decode_waves_per_simd(head_dim, fp)); }
 
+// Sliding-window layers: waves of a workgroup, pages of each type it scans at a time, its rings and all its LDS (the rings,
+// then per type the ids, masks and list positions of the visible pages, then their counts per wave).
+constexpr int kWindowWaves = 8, kWindowBlock = 64 * kWindowWaves;
+__host__ __device__ constexpr int window_ring_bytes(int head_dim) { return head_dim == 128 ? 14336 : 9216; }
+__host__ __device__ constexpr int window_lds_bytes(int head_dim) { return kWindowWaves * window_ring_bytes(head_dim) + 9 * kWindowBlock * 4 + 3 * kWindowWaves * 4; }
+
 namespace thinkv {
 
 struct DecodeArgs {
@@ -41,7 +47,7 @@ struct DecodeArgs {
   int64_t stat_stride;  // floats per (query, kv-head): 16 * max_ctx_pages
   float* sparsity;      // [B]
   int direct;           // 1: every head has a single item and the attention kernel writes out / lse itself
-  int waves;            // full-attention layers of the fast kernel: waves of an item's workgroup
+  int waves;            // fast kernel: waves of an item's workgroup (full attention), kv-heads of one (sliding window)
 };
 
 constexpr int kMaxRowsPerHead = 1024;

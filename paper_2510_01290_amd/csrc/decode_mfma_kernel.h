@@ -44,7 +44,8 @@
 // 256 x 1k..64k tokens 1,049 -> 832 us, 16 x 8k 51.6 -> 43.3, 32 x ~2k of scrambled slots 75 -> 48, head_dim 64
 // 128 x 4k..32k 313 -> 287.  Three waves a SIMD with rings of 12 KB (one pair of 8-bit pages) lose to two with 18 KB:
 // 16 x 8k 64 us, 256 x 1k..64k 1,046 us.
-// Sliding-window layers (decode_window_kernel): one wave per item, an item owns a fixed share of each type's page list.
+// Sliding-window layers (decode_window_kernel): a workgroup scans the page lists for several kv-heads, then its waves attend
+// the visible pages through the same rings.
 #pragma once
 #include "decode_common.h"
 
@@ -306,6 +307,14 @@ constexpr int kChunkPairs = 4;
 typedef const int32_t __attribute__((address_space(4))) * ConstI32;   // read-only for the whole launch: scalar loads
 typedef __attribute__((address_space(3))) int32_t* LdsCounter;
 
+// a scalar that a load may still be bringing: waited for here and not before (what is computed from it would otherwise
+// be moved up to the load, and the wait with it)
+__device__ __forceinline__ int arrived(int x) {
+  int y;
+  asm volatile("s_mov_b32 %0, %1" : "=s"(y) : "s"(x));
+  return y;
+}
+
 struct Stream {
   ConstI32 tab, msk;           // page list and masks of type 0; those of type k begin k * max_pages later
   LdsCounter ticket;
@@ -372,40 +381,48 @@ struct Stream {
     pid_b = t[more_pages];
     msk_b = m[more_pages];
   }
+  // the pair at hand, if it is one of the x-th type walked (want): its ids and masks are waited for here and not before
+  int want;
+  __device__ __forceinline__ bool next(PairIds& id) const {
+    if (sec != want) return false;
+    id.pid_a = arrived(pid_a);
+    id.pid_b = arrived(pid_b);
+    id.live_a = (uint32_t)arrived(msk_a) & 0xFFFFu;
+    id.live_b = (uint32_t)(arrived(msk_b) & (0 - more_pages)) & 0xFFFFu;
+    id.idx_a = pg;
+    id.idx_b = more_pages ? pg + 1 : -1;
+    return true;
+  }
 };
 
-// a scalar that a load may still be bringing: waited for here and not before (what is computed from it would otherwise
-// be moved up to the load, and the wait with it)
-__device__ __forceinline__ int arrived(int x) {
-  int y;
-  asm volatile("s_mov_b32 %0, %1" : "=s"(y) : "s"(x));
-  return y;
-}
-
-// All pairs of the x-th type walked that the wave draws, through its ring at LDS address ring.
-template <class Runner>
-__device__ __forceinline__ void stream_type(Runner& run, Stream& q, int x, const thinkv_view& v, int cls, int hkv, uint32_t ring) {
+// All pairs that `q` hands out (next(): the pair at hand, false when there is none; look(): move on), through the wave's ring
+// of RING bytes at LDS address `ring`.
+template <int RING, class Runner, class Source>
+__device__ __forceinline__ void stream_pairs(Runner& run, Source& q, const thinkv_view& v, int cls, int hkv, uint32_t ring) {
   using Dma = BlockDma<Runner::kBlockBytes>;
   constexpr int kPairBytes = 2 * Runner::kBlockBytes, kOps = 2 * Dma::kOps;
-  constexpr int kSlots = stream_ring_bytes(Runner::kD, Runner::kFp) / kPairBytes;
+  constexpr int kSlots = RING / kPairBytes;
   static_assert(kSlots >= 1 && kSlots <= 32 && (kSlots - 1) * kOps < 64, "the ring holds a pair, the waits six bits");
-  const int lane = q.lane;
+  const int lane = run.lane;
   const uint32_t voff = 16 * lane;
   const uint32_t page_bytes = __builtin_amdgcn_readfirstlane(v.cfg.n_kv_heads * Runner::kBlockBytes);
   const uint8_t* const base = scalar_ptr(v.arena[cls] + (int64_t)hkv * Runner::kBlockBytes);
-  int f_live = 0, f_idx = 0;   // lane s: what slot s holds (live bits of both pages; twice the list position, plus one where there is a second page)
-  // asks for the next live pair of the type in slot, moves on; false: there is none
+  int f_live = 0, f_ia = 0, f_ib = 0;   // lane s: what slot s holds (live bits of both pages; STAT: their list positions)
+  // asks for the next live pair in slot, moves on; false: there is none
   auto issue = [&](int slot) -> bool {
-    while (q.sec == x) {
-      const int msk_a = arrived(q.msk_a), msk_b = arrived(q.msk_b);
-      const bool on = ((msk_a | msk_b) & 0xFFFF) != 0;   // (a missing second page repeats the first one)
+    PairIds id;
+    while (q.next(id)) {
+      const bool on = (id.live_a | id.live_b) != 0;
       if (on) {
         const uint32_t at = uniform(ring + slot * kPairBytes);
-        Dma::issue(at, scalar_ptr(base + (uint64_t)(uint32_t)arrived(q.pid_a) * page_bytes), voff);
-        Dma::issue(at + Runner::kBlockBytes, scalar_ptr(base + (uint64_t)(uint32_t)arrived(q.pid_b) * page_bytes), voff);
+        Dma::issue(at, scalar_ptr(base + (uint64_t)(uint32_t)id.pid_a * page_bytes), voff);
+        Dma::issue(at + Runner::kBlockBytes, scalar_ptr(base + (uint64_t)(uint32_t)id.pid_b * page_bytes), voff);
         const bool mine = lane == slot;
-        f_live = mine ? (msk_a & 0xFFFF) | ((msk_b & (0 - q.more_pages)) << 16) : f_live;
-        if constexpr (Runner::kStat) f_idx = mine ? q.pg << 1 | q.more_pages : f_idx;
+        f_live = mine ? (int)(id.live_a | id.live_b << 16) : f_live;
+        if constexpr (Runner::kStat) {
+          f_ia = mine ? id.idx_a : f_ia;
+          f_ib = mine ? id.idx_b : f_ib;
+        }
       }
       q.look();
       if (on) return true;
@@ -419,7 +436,7 @@ __device__ __forceinline__ void stream_type(Runner& run, Stream& q, int x, const
 #pragma nounroll
   while (flying > 0) {
     // the oldest pair has landed when only the others' loads are left (with fewer pairs in flight all are waited for: the
-    // end of the type is near)
+    // end is near)
     if (flying == kSlots) wait_loads<(kSlots - 1) * kOps>();
     else wait_loads<0>();
     const LdsPtr blk_a = (LdsPtr)(uintptr_t)(ring + slot * kPairBytes), blk_b = blk_a + Runner::kBlockBytes;
@@ -430,9 +447,8 @@ __device__ __forceinline__ void stream_type(Runner& run, Stream& q, int x, const
     cur.live_a = live & 0xFFFFu;
     cur.live_b = live >> 16;
     if constexpr (Runner::kStat) {
-      const int idx = __builtin_amdgcn_readlane(f_idx, slot);
-      cur.idx_a = idx >> 1;
-      cur.idx_b = (idx & 1) ? cur.idx_a + 1 : -1;
+      cur.idx_a = __builtin_amdgcn_readlane(f_ia, slot);
+      cur.idx_b = __builtin_amdgcn_readlane(f_ib, slot);
     }
     run.load_v(r, blk_a, blk_b);
     wait_lds();   // the slot has been read: it can be filled again
@@ -443,63 +459,26 @@ __device__ __forceinline__ void stream_type(Runner& run, Stream& q, int x, const
   }
 }
 
-// Sliding-window layers, static share [p0, p1) of a type's page list: page ids and live masks of up to 64 pages are fetched
-// with one vector load each (lane L holds page p0 + base + L).  A page can hold a visible
-// token only if the largest position ever written into it lies inside the window, so one
-// word per page (page_pos_max) settles most pages; a lane reads the 16 positions of its page
-// only when that test passes.  The pages of a run of 64 that still have a visible slot are
-// paired up, and ids and masks reach the pair code through v_readlane.
-template <class Runner>
-__device__ __forceinline__ void walk_window(Runner& run, const thinkv_view& v, const DecodeArgs& a, int cls, int hkv, int qpos, const int32_t* tab,
-                                            int p0, int p1) {
-  const int lane = threadIdx.x & 63, H = v.cfg.n_kv_heads;
-  const int n_pages = p1 - p0;
-  for (int base = 0; base < n_pages; base += 64) {
-    const int cnt = n_pages - base < 64 ? n_pages - base : 64;
-    int vpid = 0;
-    uint32_t vmask = 0;
-    if (lane < cnt) {
-      vpid = tab[p0 + base + lane];
-      vmask = v.slot_mask[(tab - v.block_table) + p0 + base + lane] & 0xFFFFu;
-    }
-    uint32_t vis = 0;
-    if (vmask != 0 && v.page_pos_max[cls][vpid] > qpos - a.window) {
-      const int4* sp = (const int4*)(v.slot_pos[cls] + (int64_t)vpid * kPage);
-#pragma unroll
-      for (int t4 = 0; t4 < kPage / 4; ++t4) {
-        const int4 pos = sp[t4];
-        const int d0 = qpos - pos.x, d1 = qpos - pos.y, d2 = qpos - pos.z, d3 = qpos - pos.w;
-        vis |= ((d0 >= 0 && d0 < a.window) ? 1u : 0u) << (4 * t4);
-        vis |= ((d1 >= 0 && d1 < a.window) ? 2u : 0u) << (4 * t4);
-        vis |= ((d2 >= 0 && d2 < a.window) ? 4u : 0u) << (4 * t4);
-        vis |= ((d3 >= 0 && d3 < a.window) ? 8u : 0u) << (4 * t4);
-      }
-    }
-    vmask &= vis;
-    uint64_t todo = __ballot(vmask != 0);
-    while (todo) {
-      const int ia = __builtin_ctzll(todo);
-      todo &= todo - 1;
-      const bool two = todo != 0;
-      const int ib = two ? __builtin_ctzll(todo) : ia;
-      if (two) todo &= todo - 1;
-      PairIds id;
-      id.pid_a = __builtin_amdgcn_readlane(vpid, ia);
-      id.live_a = __builtin_amdgcn_readlane(vmask, ia);
-      id.pid_b = __builtin_amdgcn_readlane(vpid, ib);
-      id.live_b = two ? __builtin_amdgcn_readlane(vmask, ib) : 0u;
-      id.idx_a = p0 + base + ia;
-      id.idx_b = two ? p0 + base + ib : -1;
-      const uint8_t* blk_a = v.arena[cls] + ((int64_t)id.pid_a * H + hkv) * Runner::kBlockBytes;
-      const uint8_t* blk_b = v.arena[cls] + ((int64_t)id.pid_b * H + hkv) * Runner::kBlockBytes;
-      typename Runner::Pair r;
-      run.load_k(r, blk_a, blk_b);
-      run.load_v(r, blk_a, blk_b);
-      run.scores(r, id);
-      run.values(r);
-    }
+// Sliding-window layers: the pages of one type with a visible slot, as the workgroup's scan left them in LDS; a wave takes
+// pairs i, i + step, ...
+struct VisiblePages {
+  typedef __attribute__((address_space(3))) const int32_t* Words;
+  Words pid, msk, idx;
+  int n, i, step;
+  __device__ __forceinline__ bool next(PairIds& id) const {
+    if (2 * i >= n) return false;
+    const int a = 2 * i, b = min(a + 1, n - 1);
+    const int two = b - a;
+    id.pid_a = uniform(pid[a]);
+    id.pid_b = uniform(pid[b]);
+    id.live_a = (uint32_t)uniform(msk[a]);
+    id.live_b = (uint32_t)(uniform(msk[b]) & (0 - two));
+    id.idx_a = uniform(idx[a]);
+    id.idx_b = two ? uniform(idx[b]) : -1;
+    return true;
   }
-}
+  __device__ __forceinline__ void look() { i += step; }
+};
 
 // What a lane keeps of the query for the whole item: per column set the eight binary16 values of
 // (its head, its slice's group, channels 8qd .. 8qd+7) and, for the four rows of its quad, the sum of the 32 values
@@ -952,6 +931,40 @@ __device__ __forceinline__ float* stat_row(const thinkv_config& c, const DecodeA
   else if (BITS == 4) TKV_WITH_RUNNER(4, CALL)  \
   else TKV_WITH_RUNNER(8, CALL)
 
+// Four channels of the sum of W partials of query head g of (query b, kv-head), `stride` floats apart in LDS: the result where
+// the head has one item, else the item's partial row.
+template <int D>
+__device__ __forceinline__ void fold_rows(const DecodeArgs& a, const float* rows, int stride, int W, int b, int hkv, int g, int ch, int Hq, int G, int row) {
+  float M = -INFINITY;
+  for (int w = 0; w < W; ++w) M = fmaxf(M, rows[w * stride + D]);
+  float L = 0.f;
+  float4 A = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int w = 0; w < W; ++w) {
+    const float* src = rows + w * stride;
+    const float f = src[D] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(src[D] - M);
+    const float4 x = *(const float4*)(src + ch);
+    L = fmaf(src[D + 1], f, L);
+    A.x = fmaf(x.x, f, A.x);
+    A.y = fmaf(x.y, f, A.y);
+    A.z = fmaf(x.z, f, A.z);
+    A.w = fmaf(x.w, f, A.w);
+  }
+  if (a.direct) {
+    const int64_t at = ((int64_t)b * Hq + hkv * G + g) * D + ch;
+    const float o[4] = {A.x, A.y, A.z, A.w};
+#pragma unroll
+    for (int r = 0; r < 4; ++r) store_from_f32(a.out, at + r, a.out_dtype, L > 0.f ? o[r] / L : 0.f);
+    if (a.lse && ch == 0) a.lse[(int64_t)b * Hq + hkv * G + g] = L > 0.f ? (M + log2f(L)) * 0.6931471805599453f : -INFINITY;
+  } else {
+    float* dst = partial_row(a, G, D, row, g);
+    *(float4*)(dst + ch) = A;
+    if (ch == 0) {
+      dst[D] = M;
+      dst[D + 1] = L;
+    }
+  }
+}
+
 // Full-attention layers: a workgroup of W = blockDim.x / 64 waves per item (see the head of the file).
 // FP: the cache is in the paper's number formats (decode_mfma_fp.h), else in the integer formats.
 template <int D, int GP, bool STAT, bool FP>
@@ -1002,7 +1015,8 @@ __global__ __launch_bounds__(256 * decode_waves_per_simd(D, FP)) __attribute__((
     float* stat = nullptr;
     int stat_room = 0;
     if constexpr (STAT) stat = stat_row(c, a, b, hkv, k, np, &stat_room);
-    TKV_BY_WIDTH(bits, stream_type(cr, q, x, v, k, hkv, ring))
+    q.want = x;
+    TKV_BY_WIDTH(bits, stream_pairs<kRing>(cr, q, v, k, hkv, ring))
   }
   // ---- the waves' partials meet in LDS (the rings are done with) and are folded there
   const Partial<D, GP, FP> part(st, lane);
@@ -1020,99 +1034,160 @@ __global__ __launch_bounds__(256 * decode_waves_per_simd(D, FP)) __attribute__((
   __syncthreads();
   for (int i = threadIdx.x; i < G * (D / 4); i += blockDim.x) {
     const int g = i / (D / 4), ch = 4 * (i % (D / 4));
-    float M = -INFINITY;
-    for (int w = 0; w < W; ++w) M = fmaxf(M, rows[(w * G + g) * kRow + D]);
-    float L = 0.f;
-    float4 A = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int w = 0; w < W; ++w) {
-      const float* src = rows + (w * G + g) * kRow;
-      const float f = src[D] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(src[D] - M);
-      const float4 x = *(const float4*)(src + ch);
-      L = fmaf(src[D + 1], f, L);
-      A.x = fmaf(x.x, f, A.x);
-      A.y = fmaf(x.y, f, A.y);
-      A.z = fmaf(x.z, f, A.z);
-      A.w = fmaf(x.w, f, A.w);
-    }
-    if (a.direct) {   // the only item of its head: this is the result
-      const int64_t at = ((int64_t)b * Hq + hkv * G + g) * D + ch;
-      const float o[4] = {A.x, A.y, A.z, A.w};
-#pragma unroll
-      for (int r = 0; r < 4; ++r) store_from_f32(a.out, at + r, a.out_dtype, L > 0.f ? o[r] / L : 0.f);
-      if (a.lse && ch == 0) a.lse[(int64_t)b * Hq + hkv * G + g] = L > 0.f ? (M + log2f(L)) * 0.6931471805599453f : -INFINITY;
-    } else {
-      float* dst = partial_row(a, G, D, it.row0 + it.j, g);
-      *(float4*)(dst + ch) = A;
-      if (ch == 0) {
-        dst[D] = M;
-        dst[D + 1] = L;
-      }
-    }
+    fold_rows<D>(a, rows + g * kRow, G * kRow, W, b, hkv, g, ch, Hq, G, it.row0 + it.j);
   }
 }
 
-// Sliding-window layers: one wave per item; a workgroup is four items that share nothing but the launch.
+// Sliding-window layers.  Little is visible (a window of 128 tokens: some twenty pages of a list of a thousand), so the
+// scan of the page lists is most of the work: mask and id, page_pos_max, and where that reaches into the window the
+// sixteen positions, three dependent loads.  A workgroup of eight waves scans for `hg` kv-heads at once, a page of
+// each type per thread with the three chains side by side, leaves the visible pages in LDS in list order, and its waves then
+// attend them, 8 / hg waves to a head; partials are folded in LDS, so a head with one item is finished here.
+// (One wave per head and third of the lists, each scanning for itself 64 pages at a time: 128 x 4k..32k tokens, window 128,
+// 64 heads, head_dim 64: 52 us; now 29, most of it the arithmetic of pages with one or two visible slots each.)
 template <int D, int GP, bool STAT, bool FP>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 128 ? 2 : 3, D == 128 ? 2 : 3))) void decode_window_kernel(thinkv_view v, DecodeArgs a) {
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void decode_window_kernel(thinkv_view v, DecodeArgs a) {
+  constexpr int kRing = window_ring_bytes(D), kRow = D + kRowPad;
+  extern __shared__ __attribute__((aligned(16))) uint8_t tkv_lds[];
   const thinkv_config& c = v.cfg;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int item = blockIdx.x * 4 + wave;
-  if (item >= a.n_rows) return;
-  const ItemLoc it = locate_item(v, a, item);
-  if (it.j >= it.n) return;
-  const int b = it.b, hkv = it.hkv;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int H = c.n_kv_heads, Hq = c.n_q_heads, G = Hq / H, hg = a.waves, wph = kWindowWaves / hg;
+  const int groups = (H + hg - 1) / hg;
+  // item id -> query, group of heads, item j of n (item-major)
+  const int per = groups * a.B, j = uniform((int)blockIdx.x / per), rest = (int)blockIdx.x - j * per;
+  const int b = uniform(rest / groups), h0 = (rest - b * groups) * hg;
   const int seq = uniform(a.seq_ids[b]);
   int np[3];
-  seq_pages(v, a.layer, seq, np);
-  const int lane = threadIdx.x & 63, qd = lane >> 4, head = lane & (GP - 1);
-  const int Hq = c.n_q_heads, G = Hq / c.n_kv_heads;
-  if (it.j == 0 && lane == 0 && !a.direct) {
-    a.alloc[2 * (b * c.n_kv_heads + hkv)] = it.row0;
-    a.alloc[2 * (b * c.n_kv_heads + hkv) + 1] = it.n;
+  const int tot = seq_pages(v, a.layer, seq, np);
+  int n = uniform((int)(((int64_t)tot + a.ppi - 1) / a.ppi));
+  n = n < 1 ? 1 : (n > a.per_head ? a.per_head : n);
+  if (j >= n) return;
+  const int hw = uniform(wave / wph), hkv = min(h0 + hw, H - 1);   // this wave's head (waves beyond the last head idle)
+  if (j == 0 && !a.direct && tid < hg && h0 + tid < H) {
+    a.alloc[2 * (b * H + h0 + tid)] = (b * H + h0 + tid) * a.per_head;
+    a.alloc[2 * (b * H + h0 + tid) + 1] = n;
   }
+  int32_t* const lists = (int32_t*)(tkv_lds + kWindowWaves * kRing);   // [type][id, mask, list position][kWindowBlock]
+  int32_t* const counts = lists + 9 * kWindowBlock;                    // [type][wave]
   Query<D, GP, FP> query;
   query.read(a, ((int64_t)b * Hq + hkv * G) * D, G, lane);
   WaveState<D, GP, Query<D, GP, FP>::NSET> st;
   clear(st);
   const int qpos = uniform(a.q_pos[b]);
-  for (int k = 0; k < 3; ++k) {
-    const int bits = c.bits_of_class[k];
-    const int npk = k == 0 ? np[0] : (k == 1 ? np[1] : np[2]);
-    const int p0 = uniform((int)((int64_t)it.j * npk / it.n)), p1 = uniform((int)((int64_t)(it.j + 1) * npk / it.n));
-    if (p1 > p0) {
-      const int32_t* tab = v.block_table + table_base(c, seq, a.layer, k);
-      float* stat = nullptr;
-      int stat_room = 0;
-      if constexpr (STAT) stat = stat_row(c, a, b, hkv, k, np, &stat_room);
-      TKV_BY_WIDTH(bits, walk_window(cr, v, a, k, hkv, qpos, tab, p0, p1))
+  const bool valid = seq >= 0 && seq < c.max_seqs;
+  // the item's share of each list
+  const int s0 = uniform((int)((int64_t)j * np[0] / n)), e0 = uniform((int)((int64_t)(j + 1) * np[0] / n));
+  const int s1 = uniform((int)((int64_t)j * np[1] / n)), e1 = uniform((int)((int64_t)(j + 1) * np[1] / n));
+  const int s2 = uniform((int)((int64_t)j * np[2] / n)), e2 = uniform((int)((int64_t)(j + 1) * np[2] / n));
+  const int most = max(e0 - s0, max(e1 - s1, e2 - s2));
+  for (int base = 0; base < most; base += kWindowBlock) {
+    int pg[3], pid[3];
+    uint32_t vis[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      pg[k] = (k == 0 ? s0 : (k == 1 ? s1 : s2)) + base + tid;
+      const bool in = valid && pg[k] < (k == 0 ? e0 : (k == 1 ? e1 : e2));
+      pid[k] = 0;
+      vis[k] = 0;
+      if (in) {
+        const int64_t at = table_base(c, seq, a.layer, k) + pg[k];
+        pid[k] = v.block_table[at];
+        vis[k] = v.slot_mask[at] & 0xFFFFu;
+      }
     }
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      if (vis[k] != 0 && v.page_pos_max[k][pid[k]] <= qpos - a.window) vis[k] = 0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      if (vis[k] != 0) {
+        const int4* sp = (const int4*)(v.slot_pos[k] + (int64_t)pid[k] * kPage);
+        uint32_t m = 0;
+#pragma unroll
+        for (int t4 = 0; t4 < kPage / 4; ++t4) {
+          const int4 pos = sp[t4];
+          const int d0 = qpos - pos.x, d1 = qpos - pos.y, d2 = qpos - pos.z, d3 = qpos - pos.w;
+          m |= ((d0 >= 0 && d0 < a.window) ? 1u : 0u) << (4 * t4);
+          m |= ((d1 >= 0 && d1 < a.window) ? 2u : 0u) << (4 * t4);
+          m |= ((d2 >= 0 && d2 < a.window) ? 4u : 0u) << (4 * t4);
+          m |= ((d3 >= 0 && d3 < a.window) ? 8u : 0u) << (4 * t4);
+        }
+        vis[k] &= m;
+      }
+    // the visible pages in list order
+    uint64_t seen[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      seen[k] = __ballot(vis[k] != 0);
+      if (lane == 0) counts[k * kWindowWaves + wave] = __popcll(seen[k]);
+    }
+    __syncthreads();
+    int total[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      int before = 0;
+      total[k] = 0;
+#pragma unroll
+      for (int w = 0; w < kWindowWaves; ++w) {
+        const int x = uniform(counts[k * kWindowWaves + w]);
+        before += w < wave ? x : 0;
+        total[k] += x;
+      }
+      if (vis[k] != 0) {
+        const int at = before + __popcll(seen[k] & ((1ull << lane) - 1ull));
+        lists[(3 * k + 0) * kWindowBlock + at] = pid[k];
+        lists[(3 * k + 1) * kWindowBlock + at] = (int32_t)vis[k];
+        lists[(3 * k + 2) * kWindowBlock + at] = pg[k];
+      }
+    }
+    __syncthreads();
+    if (h0 + hw < H) {
+#pragma unroll 1
+      for (int k = 0; k < 3; ++k) {
+        VisiblePages q;
+        q.n = k == 0 ? total[0] : (k == 1 ? total[1] : total[2]);
+        if (q.n == 0) continue;
+        const uint32_t at = (uint32_t)(kWindowWaves * kRing + 3 * k * kWindowBlock * 4);
+        q.pid = (VisiblePages::Words)(uintptr_t)at;
+        q.msk = (VisiblePages::Words)(uintptr_t)(at + kWindowBlock * 4);
+        q.idx = (VisiblePages::Words)(uintptr_t)(at + kWindowBlock * 8);
+        q.i = wave - hw * wph;
+        q.step = wph;
+        const int bits = c.bits_of_class[k];
+        float* stat = nullptr;
+        int stat_room = 0;
+        if constexpr (STAT) stat = stat_row(c, a, b, hkv, k, np, &stat_room);
+        TKV_BY_WIDTH(bits, stream_pairs<kRing>(cr, q, v, k, hkv, (uint32_t)(wave * kRing)))
+      }
+    }
+    __syncthreads();   // the lists have been used
   }
   const Partial<D, GP, FP> part(st, lane);
-  if (head >= G) return;
-  if (a.direct) {   // the only item of its head: this is the result
-    const int64_t o_at = ((int64_t)b * Hq + hkv * G + head) * D;
-    part.each(st, lane, [&](int ch, float4 x) {
-      const float o[4] = {x.x, x.y, x.z, x.w};
-#pragma unroll
-      for (int r = 0; r < 4; ++r) store_from_f32(a.out, o_at + ch + r, a.out_dtype, part.l > 0.f ? o[r] / part.l : 0.f);
-    });
-    if (a.lse && qd == 0 && (lane & 15) < GP) a.lse[(int64_t)b * Hq + hkv * G + head] = part.l > 0.f ? (part.m + log2f(part.l)) * 0.6931471805599453f : -INFINITY;
-  } else {
-    float* dst = partial_row(a, G, D, it.row0 + it.j, head);
+  const int head = lane & (GP - 1), qd = lane >> 4;
+  float* const rows = (float*)tkv_lds;   // [wave][G][kRow]
+  if (head < G) {
+    float* dst = rows + (wave * G + head) * kRow;
     part.each(st, lane, [&](int ch, float4 x) { *(float4*)(dst + ch) = x; });
     if (qd == 0 && (lane & 15) < GP) {
       dst[D] = part.m;
       dst[D + 1] = part.l;
     }
   }
+  __syncthreads();
+  for (int i = tid; i < hg * G * (D / 4); i += 64 * kWindowWaves) {
+    const int hd = i / (G * (D / 4)), g = i / (D / 4) % G, ch = 4 * (i % (D / 4));
+    if (h0 + hd < H) fold_rows<D>(a, rows + (hd * wph * G + g) * kRow, G * kRow, wph, b, h0 + hd, g, ch, Hq, G, (b * H + h0 + hd) * a.per_head + j);
+  }
 }
 
 template <int D, int GP, bool STAT, bool FP>
 static int launch_one(const thinkv_view& v, const DecodeArgs& a, hipStream_t st) {
-  if (a.window > 0)
-    hipLaunchKernelGGL((decode_window_kernel<D, GP, STAT, FP>), dim3((a.n_rows + 3) / 4), dim3(256), 0, st, v, a);
-  else
+  if (a.window > 0) {
+    const int groups = (v.cfg.n_kv_heads + a.waves - 1) / a.waves;
+    hipLaunchKernelGGL((decode_window_kernel<D, GP, STAT, FP>), dim3(a.per_head * groups * a.B), dim3(64 * kWindowWaves), window_lds_bytes(D), st, v, a);
+  } else {
     hipLaunchKernelGGL((decode_stream_kernel<D, GP, STAT, FP>), dim3(a.n_rows), dim3(64 * a.waves), a.waves * stream_ring_bytes(D, FP) + 16, st, v, a);
+  }
   return hipGetLastError() == hipSuccess ? THINKV_OK : THINKV_E_HIP;
 }
 

@@ -21,7 +21,7 @@
 // x_i.c_j.  So the channels are walked once: all products between the points of the segment (the Gram matrix, at most
 // 256 x 256, its lower triangle kept in LDS), and an iteration is n^2 additions from LDS.  (Products of the points with
 // the centroids in every iteration walked all channels up to nine times: 318 segments of ~108 tokens, 1,024 channels,
-// %%KM_BEFORE%% us; now %%KM_AFTER%% us.)  A centroid is represented by the set of points it is the mean of: at the start one
+// 1,050 us; now 150 us.)  A centroid is represented by the set of points it is the mean of: at the start one
 // point, later the members, and for a cluster that has lost its last member the members it had before.
 // The products run on the matrix cores; a dequantised key does not
 // fit binary16 and the binary32 matrix instruction is slow, so every number enters as the sum of
@@ -58,7 +58,7 @@ size_t tbe_ws_bytes(const thinkv_config& c, int n_tok, int n_seg) {
 // ---- gather: x[i][hd * D + ch] = the stored key of token i.  A workgroup takes kGatherTokens tokens: one thread per
 // token walks the chain handle -> page list -> page; then a thread takes one chunk of a token's block (a kv-head, eight
 // channels of every group: one vector load of codes) and writes eight channels of each group as two 16-byte stores, four
-// neighbours 128 bytes.  Bound by those stores (four bytes a channel): 34,500 tokens of 1,024 channels (141 MB) %%GA_AFTER%% us
+// neighbours 128 bytes.  Bound by those stores (four bytes a channel): 34,500 tokens of 1,024 channels (141 MB) 44 us
 // (one channel a thread: 84).
 constexpr int kGatherTokens = 8;
 

@@ -1,4 +1,4 @@
-"""Full-attention decode at the edges of its work distribution: items of one and of several workgroups, short lists, a
+"""Decode attention at the edges of its work distribution: items of one and of several workgroups, short lists, a
 ring that wraps, pages with nothing live, batches whose row count is limited by the workspace, and value scales that leave
 the range of the second matrix operand.  The reference is the plain vector-ALU kernel (itself checked against the oracle);
 the workspace has exactly the size the library asks for, with a guard behind it."""
@@ -36,17 +36,18 @@ def _cache(D, G, H, ctx, fmt, bits, seed, v_scale=1.0, dead=0.0):
     return c, q
 
 
-def _both(c, q, D, bound=None):
+def _both(c, q, D, bound=None, window=0, q_pos=None):
     S, Hq = q.shape[:2]
     ids = torch.arange(S, dtype=torch.int32, device="cuda:0")
     pages = int(c.n_pages[:, 0].sum(-1).max()) if bound is None else bound
+    qp = None if q_pos is None else torch.tensor(q_pos, dtype=torch.int32, device="cuda:0")
     res = []
     for fn in (B.load().thinkv_decode_attention, B.load().thinkv_decode_attention_valu):
         need = B.thinkv_decode_workspace_bytes(c.cfg, S, pages)
         ws = torch.full((need + 4096,), 0x5A, dtype=torch.uint8, device="cuda:0")
         out = torch.empty((S, Hq, D), dtype=torch.float32, device="cuda:0")
         lse = torch.empty((S, Hq), dtype=torch.float32, device="cuda:0")
-        rc = fn(B.C.byref(c.view), 0, B._ptr(q), B._ptr(out), B._ptr(lse), B._ptr(ids), None, S, 0, D ** -0.5, B.BF16, B.F32, pages,
+        rc = fn(B.C.byref(c.view), 0, B._ptr(q), B._ptr(out), B._ptr(lse), B._ptr(ids), B._ptr(qp), S, window, D ** -0.5, B.BF16, B.F32, pages,
                 B._ptr(ws), need, B._stream(None))
         torch.cuda.synchronize()
         assert rc == 0
@@ -96,3 +97,19 @@ def test_value_scales_out_of_the_lifted_range(D, G, v_scale):
     # without the lift, weights below 2^-24 of the largest are lost: 3,000 of them are 2e-4 of the largest value
     assert float((o - ro).abs().max()) <= 5e-4 * float(ro.abs().max())
     assert float((l - rl).abs().max()) <= 1e-4
+
+
+@pytest.mark.parametrize("D,G,H,ctx,fmt,window,dead", [
+    (64, 8, 8, [3000] * 70, 0, 128, 0.3),            # several heads to a workgroup
+    (128, 4, 5, [9000, 40, 1, 700], 0, 1024, 0.2),   # one head to a workgroup, several items a head; heads no power of two
+    (128, 8, 3, [26000], 0, 30000, 0.0),             # lists longer than one scan, everything visible
+    (64, 2, 16, [500] * 64, 1, 100, 0.0),
+    (128, 4, 8, [17, 16, 300], 1, 1, 0.0),
+], ids=lambda x: str(x)[:24].replace(" ", ""))
+def test_window_kernel_against_the_plain_kernel(D, G, H, ctx, fmt, window, dead):
+    print("window:", D, G, H, len(ctx), max(ctx), fmt, window, dead, flush=True)
+    c, q = _cache(D, G, H, ctx, fmt, (8, 2, 4), 21 + D + G + len(ctx), dead=dead)
+    (o, l), (ro, rl) = _both(c, q, D, window=window, q_pos=[x - 1 for x in ctx])
+    assert float((o - ro).abs().max()) <= 1e-4 * max(1.0, float(ro.abs().max()))
+    fin = torch.isfinite(rl)
+    assert torch.equal(torch.isfinite(l), fin) and float((l[fin] - rl[fin]).abs().max()) <= 1e-4
