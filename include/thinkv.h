@@ -110,8 +110,7 @@ typedef struct {
  *                   skips pages whose bound lies before the window without reading slot_pos.
  *   n_live          [max_seqs][n_layers] live tokens
  *   work_counters   [n_layers][max_seqs][n_kv_heads][4] reserved; zero (init zeroes them, no call writes them)
- *   append_counters [max_seqs] scratch of thinkv_append_quantized (arrival counts of the
- *                   workgroups of a sequence); zero between calls
+ *   append_counters [max_seqs] reserved; zero (init zeroes them, no call writes them)
  *   dev_status      [max_seqs * n_layers + 1] THINKV_ST_* flags
  *
  * Byte layout of one page: n_kv_heads blocks of thinkv_block_bytes(); a block is

@@ -9,103 +9,146 @@
 //     k < R + tail     slot filled + (k - R) of the last page                  (tail = 16 - filled)
 //     otherwise        slot (k-R-tail) % 16 of the (k-R-tail)/16-th new page
 // and new pages are granted to sequences in ascending sequence id, which is token order.
-// Three steps in two kernels, both on the caller's stream:
-//   plan   (block per sequence)  token ranks per type, prefix popcounts of the reclaimable bits,
-//                                pages needed
-//   place  (block per token)     slot lookup, quantisation, packing, slot_pos, handle
-//   commit (block per sequence)  masks, fill counts, page lists, counters
-// The commit of a sequence changes tables that the place blocks of the sequence's tokens read
-// (masks, fill counts, page list), and reads nothing that they write.  So it needs no kernel of
-// its own, only to come after those reads: every place block, once its slot is settled, bumps
-// an arrival counter of its sequence (view->append_counters), and the block that completes the
-// count commits the sequence before it goes on to quantise its own token.  Reads-before-writes
-// is all that has to hold, so no fence is involved (a release fence costs an L2 write-back here).
-// A call of more than 64 tokens (a prefill, a refill: hundreds of blocks would bump one sequence's
-// counter) keeps a commit kernel of its own and places its tokens sixteen to a block (see
-// append_place_bulk_kernel).
+// Two kernels on the caller's stream:
+//   plan   (block per sequence)  everything that concerns the sequence alone: token ranks per type, a place for every
+//                                token, the masks, fill counts and the live count that follow from places in
+//                                existing pages, and the new pages wanted
+//   place  (block per token and share of its kv-heads, or per 32 tokens)  quantisation, packing, slot_pos,
+//                                handle.  Which page a new one is depends on the sequences before: it is worked out
+//                                here, and the token that takes the page's first slot enters it into the tables.
+// The place blocks read what the plan left in the workspace and the pools as the plan found them, never the tables
+// they write, so nothing has to wait inside the kernel.  Small calls are bound by the two launches and chains of dependent loads, so
+// the plan asks for everything that it can name at once and leaves a place ready for every token.  (With the tables left to
+// the place kernel, which searched them for every token's slot, and to the last block of a sequence to arrive, or with
+// a grant and a commit kernel behind more than 64 tokens: 16 tokens of 16 sequences of 32k, plan + place 20 us, now
+// 14; 256 tokens of 256 sequences, a call, 34.6 us, now 17.2.)
 // The grant of new pages (exclusive sum of the needs of the sequences before s, against what the
-// pool held when the call began) is a sum over at most max_seqs small numbers: every block that
-// wants it works it out for itself rather than waiting for a kernel of its own.  A decode step
+// pool held when the call began) is a sum over at most max_seqs small numbers: whoever wants it works it out for
+// itself rather than waiting for a kernel of its own.  A decode step
 // appends one token per sequence, so the call is a chain of short dependent launches and one
 // launch less is a good part of its time.
 #include "common.h"
 #include "formats_dev.h"
+
+#include <type_traits>
 
 namespace thinkv {
 
 struct SeqPlan {
   int lo, hi;        // token range of the sequence inside the call
   int n[3];          // tokens per type
-  int R[3];          // reclaimable slots per type before the call
-  int tail[3];       // never-used slots in the last page
+  int old[3];        // reclaimable and never-used slots of the type's pages before the call: the first n tokens take them
   int np_old[3];
-  int need[3];       // new pages wanted (already limited by the page-list capacity)
-  int grant[3];      // new pages granted
-  int base[3];       // offset of the first granted page in pop order
-  int pad;
 };
-static_assert(sizeof(SeqPlan) == 24 * 4, "SeqPlan layout");
+static_assert(sizeof(SeqPlan) == 11 * 4, "SeqPlan layout");
 
-constexpr int kBulkFrom = 64;   // calls of more tokens take the bulk kernels
+constexpr int kBulkFrom = 64;   // calls of more tokens take the bulk place kernel
+
+// a token's place: state << 28 | index in the type's page list << 4 | slot
+constexpr uint32_t kNoPlace = 0, kOldPage = 1, kNewPage = 2;
 
 struct AppendWs {
   SeqPlan* plan;     // [max_seqs]
+  int* need;         // [3][max_seqs] new pages wanted (already limited by the page-list capacity)
   int* avail_old;    // [4]
-  int* tok_rank;     // [n_tok]
-  int* pre;          // [max_seqs][3][max_pages]
+  uint32_t* place;   // [n_tok]
 };
 
 __host__ __device__ inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
+// What a caller is asked for is more than carve() takes: it has room for a count per page of every list, which an earlier
+// layout kept, and callers hold workspaces of that size.
 size_t append_ws_bytes(const thinkv_config& c, int n_tok) {
-  return align256((size_t)c.max_seqs * sizeof(SeqPlan)) + 256 + align256((size_t)(n_tok > 0 ? n_tok : 1) * 4) +
+  return align256((size_t)c.max_seqs * 96) + 256 + align256((size_t)(n_tok > 0 ? n_tok : 1) * 4) +
          align256((size_t)c.max_seqs * 3 * c.max_pages * 4);
 }
 
 static AppendWs carve(const thinkv_config& c, int n_tok, void* ws) {
+  static_assert(sizeof(SeqPlan) + 3 * sizeof(int) <= 96, "append_ws_bytes");
   char* p = (char*)ws;
   AppendWs w;
   w.plan = (SeqPlan*)p;
-  p += align256((size_t)c.max_seqs * sizeof(SeqPlan));
+  w.need = (int*)(w.plan + c.max_seqs);
+  p += align256((size_t)c.max_seqs * (sizeof(SeqPlan) + 3 * sizeof(int)));
   w.avail_old = (int*)p;
   p += 256;
-  w.tok_rank = (int*)p;
-  p += align256((size_t)(n_tok > 0 ? n_tok : 1) * 4);
-  w.pre = (int*)p;
+  w.place = (uint32_t*)p;
   return w;
 }
 
-// Sum over a 256-thread block (every thread gets it).
-__device__ inline int block_sum(int v, int* lds /*[5]*/) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = v;
-  __syncthreads();
-  return lds[0] + lds[1] + lds[2] + lds[3];
+// three counts of at most 2^21 - 1 in one word
+typedef unsigned long long Packed3;
+__device__ __forceinline__ Packed3 pack3(int a, int b, int c) { return (Packed3)a | (Packed3)b << 21 | (Packed3)c << 42; }
+__device__ __forceinline__ int part3(Packed3 x, int k) { return (int)(x >> (21 * k)) & 0x1FFFFF; }
+
+template <int CTRL, int ROWS>
+__device__ __forceinline__ Packed3 scan_step(Packed3 x) {
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xF, false);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(x >> 32), CTRL, ROWS, 0xF, false);
+  return x + ((Packed3)hi << 32 | lo);
 }
 
-// exclusive scan of one int per thread over a 256-thread block; returns the block total
-__device__ inline int block_excl_scan(int v, int* excl, int* lds /*[5]*/) {
+// inclusive scan over a wave: by 1, 2, 4, 8 lanes inside rows of sixteen, then the rows' sums onwards
+__device__ __forceinline__ Packed3 wave_scan(Packed3 x) {
+  x = scan_step<0x111, 0xF>(x);
+  x = scan_step<0x112, 0xF>(x);
+  x = scan_step<0x114, 0xF>(x);
+  x = scan_step<0x118, 0xF>(x);
+  x = scan_step<0x142, 0xA>(x);
+  return scan_step<0x143, 0xC>(x);
+}
+
+// exclusive scans of N words per thread over a 256-thread block, and the block's totals
+template <int N>
+__device__ inline void block_excl_scan(const Packed3 (&v)[N], Packed3 (&excl)[N], Packed3 (&tot)[N], Packed3 (*lds)[4]) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int inc = v;
+  Packed3 inc[N];
 #pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    int o = __shfl_up(inc, d, 64);
-    if (lane >= d) inc += o;
-  }
+  for (int i = 0; i < N; ++i) inc[i] = wave_scan(v[i]);
   __syncthreads();
-  if (lane == 63) lds[wave] = inc;
-  __syncthreads();
-  int off = 0, tot = 0;
+  if (lane == 63)
 #pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    int t = lds[w];
-    if (w < wave) off += t;
-    tot += t;
+    for (int i = 0; i < N; ++i) lds[i][wave] = inc[i];
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    Packed3 off = 0;
+    tot[i] = 0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const Packed3 t = lds[i][w];
+      if (w < wave) off += t;
+      tot[i] += t;
+    }
+    excl[i] = off + inc[i] - v[i];
   }
-  *excl = off + inc - v;
-  return tot;
+}
+
+// Where the tokens of sequences below s end (bound 0) or those of sequences up to s (bound 1), by a wave: tok_seq does not
+// decrease, so 256 probes at a time cut what is left into pieces, and the number of probes that lie before the bound
+// says which piece has it.  (One thread halving the range takes fifteen dependent loads a bound for 35,000 tokens.)
+__device__ inline int token_bound(const int32_t* __restrict__ tok_seq, int n_tok, int s, int bound) {
+  int lo = 0, len = n_tok;   // the bound lies in [lo, lo + len]
+  while (len > 0) {
+    const int piece = (len + 255) / 256;
+    int id[4], before = 0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) id[u] = tok_seq[lo + min((4 * (int)(threadIdx.x & 63) + u + 1) * piece, len) - 1];   // a piece's last element
+#pragma unroll
+    for (int u = 0; u < 4; ++u) before += __popcll(__ballot((4 * (int)(threadIdx.x & 63) + u) * piece < len && id[u] < s + bound));
+    const int skip = min(before * piece, len);   // whole pieces before the bound
+    lo += skip;
+    len = skip >= len ? 0 : min(piece, len - skip) - 1;   // the next piece's last element does not lie before it
+  }
+  return lo;
+}
+
+constexpr int kKeep = 4;        // pages of a type a thread keeps the masks of (1,024 pages a list); longer lists are read again
+constexpr int kWindow = 4096;   // tokens ranked at a time
+
+__device__ __forceinline__ uint32_t page_mask(const uint32_t* msk, const uint32_t (&kept)[kKeep], int pi, int q0) {
+  const int u = pi - q0;
+  return u == 0 ? kept[0] : (u == 1 ? kept[1] : (u == 2 ? kept[2] : (u == 3 ? kept[3] : msk[pi])));
 }
 
 __global__ __launch_bounds__(256) void append_plan_kernel(thinkv_view v, int layer, const int32_t* __restrict__ tok_seq,
@@ -113,7 +156,8 @@ __global__ __launch_bounds__(256) void append_plan_kernel(thinkv_view v, int lay
                                                           const int32_t* __restrict__ ev_seq, const int32_t* __restrict__ ev_handle,
                                                           int n_ev) {
   __shared__ int s_rng[2];
-  __shared__ int s_scan[5];
+  __shared__ Packed3 s_scan[4][4];
+  __shared__ uint16_t s_tok[kWindow];
   const thinkv_config& c = v.cfg;
   const int s = blockIdx.x, tid = threadIdx.x;
   // Evictions that come with the call (thinkv_evict_append): an eviction touches the tables of its
@@ -128,130 +172,392 @@ __global__ __launch_bounds__(256) void append_plan_kernel(thinkv_view v, int lay
     __threadfence_block();
     __syncthreads();
   }
-  if (n_tok <= kBulkFrom) {
-    // small call (decode-style): every thread looks at a few tokens and the two that see the
-    // sequence's first and last token publish the range
-    if (tid == 0) s_rng[0] = s_rng[1] = 0;
-    __syncthreads();
-    for (int i = tid; i < n_tok; i += 256) {
-      if (tok_seq[i] != s) continue;
-      if (i == 0 || tok_seq[i - 1] != s) s_rng[0] = i;
-      if (i == n_tok - 1 || tok_seq[i + 1] != s) s_rng[1] = i + 1;
+  if (s == 0 && tid < 3) ws.avail_old[tid] = v.free_top[tid];   // the pools as the call finds them
+  // the sequence's tokens, by two waves, while the page counts are on their way
+  int np_of[3], last_of[3], fill_of[3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) np_of[k] = v.n_pages[npages_index(c, s, layer, k)];
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  if (wave < 2) {
+    if (n_tok <= kBulkFrom) {   // (a probe a token: one round)
+      const uint64_t mine = __ballot(lane < n_tok && tok_seq[lane < n_tok ? lane : 0] == s);
+      if (tid == 0) s_rng[0] = mine ? __builtin_ctzll(mine) : 0;
+      if (tid == 64) s_rng[1] = mine ? 64 - __builtin_clzll(mine) : 0;
+    } else {
+      const int at = token_bound(tok_seq, n_tok, s, wave);
+      if (lane == 0) s_rng[wave] = at;
     }
-  } else if (tid == 0) {
-    int lo = 0, hi = n_tok;  // lower_bound(s)
-    while (lo < hi) {
-      int mid = (lo + hi) >> 1;
-      if (tok_seq[mid] < s) lo = mid + 1; else hi = mid;
-    }
-    int lo2 = lo, hi2 = n_tok;  // upper_bound(s)
-    while (lo2 < hi2) {
-      int mid = (lo2 + hi2) >> 1;
-      if (tok_seq[mid] <= s) lo2 = mid + 1; else hi2 = mid;
-    }
-    s_rng[0] = lo;
-    s_rng[1] = lo2;
-  }
-  __syncthreads();
-  // page counts and never-used slots in the last page of every type: three lanes walk the three
-  // dependent load chains (page count -> last page id -> fill count) side by side
-  __shared__ int s_np[3], s_tail[3];
-  if (tid < 3) {
-    const int npk = v.n_pages[npages_index(c, s, layer, tid)];
-    s_np[tid] = npk;
-    s_tail[tid] = npk > 0 ? kPage - (int)v.page_filled[tid][v.block_table[table_base(c, s, layer, tid) + npk - 1]] : 0;
   }
   __syncthreads();
   const int lo = s_rng[0], hi = s_rng[1];
   SeqPlan pl;
   pl.lo = lo;
   pl.hi = hi;
-  pl.pad = 0;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) pl.n[k] = pl.old[k] = pl.np_old[k] = 0;
+  if (lo >= hi) {
+    if (tid == 0) ws.plan[s] = pl;
+    if (tid < 3) ws.need[tid * c.max_seqs + s] = 0;
+    return;
+  }
+  // ---- reclaimable slots: every thread takes a contiguous run of pages of every type.  (Loads without branches around them:
+  // all are under way at once, with those of the last pages' fill counts and of the tokens' types.)
+  int q0[3], q1[3], first[3], have[3], R[3];
+  uint32_t kept[3][kKeep];
+#pragma unroll
   for (int k = 0; k < 3; ++k) {
-    pl.n[k] = pl.R[k] = pl.tail[k] = pl.need[k] = pl.grant[k] = pl.base[k] = 0;
-    pl.np_old[k] = 0;
+    const int64_t row = table_base(c, s, layer, k);
+    const int np = np_of[k], per = (np + 255) / 256;
+    last_of[k] = v.block_table[row + max(np - 1, 0)];
+    q0[k] = min(tid * per, np);
+    q1[k] = min(q0[k] + per, np);
+#pragma unroll
+    for (int u = 0; u < kKeep; ++u) kept[k][u] = v.slot_mask[row + min(q0[k] + u, c.max_pages - 1)];
   }
-  if (lo < hi) {
-    // rank of every token among the call's tokens of its type: the three types' 0/1 flags are
-    // scanned together, ten bits each (a chunk holds at most 256 tokens)
-    int running[3] = {0, 0, 0};
-    for (int b0 = lo; b0 < hi; b0 += 256) {
-      const int i = b0 + tid;
-      const int cl = i < hi ? (int)tok_class[i] : 3;
-      const int flag = cl < 3 ? 1 << (10 * cl) : 0;
-      int ex;
-      const int tot = block_excl_scan(flag, &ex, s_scan);
-      if (cl < 3) ws.tok_rank[i] = running[cl] + ((ex >> (10 * cl)) & 1023);
-      for (int k = 0; k < 3; ++k) running[k] += (tot >> (10 * k)) & 1023;
-    }
-    // exclusive prefix of the reclaimable-slot counts over each page list: every thread takes a
-    // contiguous run of pages of every type (all masks are requested before the first scan), so
-    // one block scan per type suffices
-    int mine[3], q0[3], q1[3];
-    for (int k = 0; k < 3; ++k) {
-      const uint32_t* msk = v.slot_mask + table_base(c, s, layer, k);
-      const int np = s_np[k], per = (np + 255) / 256;
-      q0[k] = tid * per;
-      q1[k] = q0[k] + per < np ? q0[k] + per : np;
-      mine[k] = 0;
-      for (int pi = q0[k]; pi < q1[k]; ++pi) mine[k] += __popc(msk[pi] >> 16);
-    }
-    for (int k = 0; k < 3; ++k) {
-      const uint32_t* msk = v.slot_mask + table_base(c, s, layer, k);
-      int* pre = ws.pre + ((int64_t)s * 3 + k) * c.max_pages;
-      const int np = s_np[k];
-      int ex;
-      const int runR = block_excl_scan(mine[k], &ex, s_scan);
-      for (int pi = q0[k]; pi < q1[k]; ++pi) {
-        pre[pi] = ex;
-        ex += __popc(msk[pi] >> 16);
+  // ---- tokens, a window at a time: every token's rank among the call's tokens of its type.  A token behind the reclaimable
+  // slots knows its place from its rank; the others are listed by rank and get it from the thread that has the slot's page.
+  int n[3] = {0, 0, 0};
+  auto window = [&](auto per_thread, int w0) {
+    constexpr int U = decltype(per_thread)::value;
+    const int t0 = w0 + tid * U;
+    int cl[U], mine[3] = {0, 0, 0}, rank[3], cnt[3];
+#pragma unroll
+    for (int u = 0; u < U; ++u) cl[u] = (int)tok_class[min(t0 + u, hi - 1)];
+    if (w0 == lo) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        fill_of[k] = np_of[k] > 0 ? (int)v.page_filled[k][last_of[k]] : kPage;
+        have[k] = 0;
+#pragma unroll
+        for (int u = 0; u < kKeep; ++u) {
+          kept[k][u] = q0[k] + u < q1[k] ? kept[k][u] : 0u;
+          have[k] += __popc(kept[k][u] >> 16);
+        }
+        for (int pi = q0[k] + kKeep; pi < q1[k]; ++pi) have[k] += __popc(v.slot_mask[table_base(c, s, layer, k) + pi] >> 16);
       }
-      const int tail = s_tail[k];
-      int need = running[k] - runR - tail;
-      need = need > 0 ? (need + kPage - 1) / kPage : 0;
-      const int room = c.max_pages - np;
-      need = need < room ? need : room;
-      pl.n[k] = running[k];
-      pl.R[k] = runR;
-      pl.tail[k] = tail;
-      pl.np_old[k] = np;
-      pl.need[k] = need;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      cl[u] = t0 + u < hi ? cl[u] : 3;
+#pragma unroll
+      for (int k = 0; k < 3; ++k) mine[k] += cl[u] == k;
+    }
+    // the window's tokens of each type together, the reclaimable slots apart (there may be more than a packed word holds)
+    const Packed3 x[4] = {pack3(mine[0], mine[1], mine[2]), (Packed3)have[0], (Packed3)have[1], (Packed3)have[2]};
+    Packed3 ex[4], tot[4];
+    block_excl_scan(x, ex, tot, s_scan);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      rank[k] = part3(ex[0], k);
+      cnt[k] = part3(tot[0], k);
+      first[k] = (int)ex[k + 1];
+      R[k] = (int)tot[k + 1];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      uint32_t at = kNoPlace << 28;
+      bool listed = false;
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        if (cl[u] != k) continue;
+        const int r = n[k] + rank[k], kk = r - R[k] - (kPage - fill_of[k]);
+        if (r < R[k]) {
+          s_tok[(k > 0 ? cnt[0] : 0) + (k > 1 ? cnt[1] : 0) + rank[k]] = (uint16_t)(tid * U + u);
+          listed = true;
+        } else if (kk < 0) {
+          at = kOldPage << 28 | (uint32_t)(np_of[k] - 1) << 4 | (uint32_t)(kk + kPage);
+        } else {
+          const int pi = np_of[k] + (kk >> 4);   // never granted beyond the page list
+          at = kNewPage << 28 | (uint32_t)(pi < c.max_pages ? pi : c.max_pages) << 4 | (uint32_t)(kk & 15);
+        }
+        ++rank[k];
+      }
+      if (t0 + u < hi && !listed) ws.place[t0 + u] = at;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const int off = (k > 0 ? cnt[0] : 0) + (k > 1 ? cnt[1] : 0) - n[k];
+      const int r0 = max(first[k], n[k]), r1 = min(first[k] + have[k], n[k] + cnt[k]);   // the window's ranks on this thread's pages
+      int r = first[k];
+      for (int pi = q0[k]; r0 < r1 && pi < q1[k] && r < r1; ++pi) {
+        uint32_t e = page_mask(v.slot_mask + table_base(c, s, layer, k), kept[k], pi, q0[k]) >> 16;
+        for (; e && r < r1; e &= e - 1, ++r)
+          if (r >= r0) ws.place[w0 + s_tok[off + r]] = kOldPage << 28 | (uint32_t)pi << 4 | (uint32_t)(__ffs(e) - 1);
+      }
+    }
+    __syncthreads();   // (the list is rewritten)
+#pragma unroll
+    for (int k = 0; k < 3; ++k) n[k] += cnt[k];
+  };
+  if (hi - lo <= 256) window(std::integral_constant<int, 1>(), lo);
+  else
+    for (int w0 = lo; w0 < hi; w0 += kWindow) window(std::integral_constant<int, kWindow / 256>(), w0);
+  // ---- what follows for the pages the sequence has: the first n of the reclaimable, then of the never-used slots are live
+  int placed = 0;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const int np = np_of[k], fill = fill_of[k], old = R[k] + kPage - fill;
+    int need = n[k] > old ? (n[k] - old + kPage - 1) / kPage : 0;
+    need = min(need, c.max_pages - np);
+    pl.n[k] = n[k];
+    pl.old[k] = old;
+    pl.np_old[k] = np;
+    if (tid == 0) ws.need[k * c.max_seqs + s] = need;
+    placed += min(n[k], old);
+    uint32_t* const msk = v.slot_mask + table_base(c, s, layer, k);
+    const int add = n[k] > R[k] ? min(n[k] - R[k], kPage - fill) : 0;   // never-used slots of the last page that are taken
+    int left = n[k] - first[k];   // slots to take from this thread's pages
+    for (int pi = q0[k]; pi < q1[k]; ++pi) {
+      const bool tail = add > 0 && pi == np - 1;
+      if (left <= 0 && add == 0) break;
+      uint32_t m = page_mask(msk, kept[k], pi, q0[k]);
+      const uint32_t before = m;
+      for (uint32_t e = m >> 16; e && left > 0; e &= e - 1, --left) {
+        const uint32_t bit = e & (0u - e);
+        m = (m | bit) & ~(bit << 16);
+      }
+      if (tail) {
+        m |= ((1u << add) - 1u) << fill;
+        v.page_filled[k][last_of[k]] = (uint8_t)(fill + add);
+      }
+      if (m != before) msk[pi] = m;
     }
   }
-  if (tid == 0) ws.plan[s] = pl;
-  if (s == 0 && tid < 3) ws.avail_old[tid] = v.free_top[tid];   // the pools as the call finds them
+  if (tid == 0) {
+    ws.plan[s] = pl;
+    if (placed) v.n_live[sl_index(c, s, layer)] += placed;
+  }
 }
 
-// New pages of type k granted to sequence s: base = pages wanted by the sequences before s
-// (pop order), grant = what the pool (avail pages when the call began) still covers of s's own
-// need.  Called by every thread of the block.
-__device__ inline void grant_of(const AppendWs& ws, int s, int k, int* base, int* grant, int* lds /*[5]*/) {
+// New pages of type k granted to sequence s: base = pages wanted by the sequences before s (pop order), grant = what the pool
+// (avail pages when the call began) still covers of s's own need.  Called by LPT neighbouring lanes together.
+template <int LPT>
+__device__ inline void grant_of(const AppendWs& ws, int n_seqs, int s, int k, int* base, int* grant) {
   const int avail = ws.avail_old[k];
+  const int* const need = ws.need + k * n_seqs;
   int before = 0;
-  for (int t = threadIdx.x; t < s; t += 256) before += ws.plan[t].need[k];
-  before = block_sum(before, lds);
-  const int need = ws.plan[s].need[k];
+  for (int t = threadIdx.x & (LPT - 1); t < s; t += LPT) before += need[t];
+#pragma unroll
+  for (int d = LPT / 2; d >= 1; d >>= 1) before += __shfl_xor(before, d, 64);
   const int left = avail - before;
   *base = before < avail ? before : avail;
-  *grant = left < 0 ? 0 : (left < need ? left : need);
+  *grant = left < 0 ? 0 : (left < need[s] ? left : need[s]);
 }
 
-__device__ void update_pools(const thinkv_view& v, const AppendWs& ws, int* s_scan);
-__device__ void commit_sequence(const thinkv_view& v, int layer, const AppendWs& ws, int s, int* s_scan);
+// One token's place, by LPT neighbouring lanes: type, page, slot, page list index; ok = 0 if it gets none; cnt = tokens that the
+// call puts into the page, if it is a new one.  enter: these lanes also record it (slot_pos, handle) and, for a token in a new
+// page, enter the page into the tables: the token in the page's first slot writes the page's row, the first token of
+// the type that wants a new page the counts.  BULK: the positions of a new page's tokens are left to who writes the page.
+struct Place {
+  int ok, cls, pid, slot, pi, cnt;
+};
+template <int LPT, bool BULK>
+__device__ inline Place settle(const thinkv_view& v, int layer, const AppendWs& ws, const int32_t* __restrict__ tok_seq, const int32_t* __restrict__ tok_pos,
+                               const uint8_t* __restrict__ tok_class, int32_t* __restrict__ tok_handle, int i, bool enter) {
+  const thinkv_config& c = v.cfg;
+  const int lane = threadIdx.x & (LPT - 1);
+  const int s = tok_seq[i];
+  const int cls = tok_class[i];
+  const uint32_t at = ws.place[i];
+  const int pos = tok_pos[i];
+  Place p = {0, cls > 2 ? 0 : cls, 0, 0, 0, 0};
+  if (s < 0 || s >= c.max_seqs) {
+    if (enter && lane == 0) atomicOr(&v.dev_status[c.max_seqs * c.n_layers], THINKV_ST_BAD_SEQ);
+  } else {
+    const SeqPlan& pl = ws.plan[s];
+    if (cls > 2) {
+      if (enter && lane == 0) atomicOr(&v.dev_status[sl_index(c, s, layer)], THINKV_ST_BAD_CLASS);
+    } else if (i >= pl.lo && i < pl.hi) {   // (outside: the sequence ids of the call decrease somewhere)
+      const uint32_t state = at >> 28;
+      p.slot = at & 15;
+      p.pi = (at >> 4) & 0xFFFFFF;
+      const int npi = p.pi - pl.np_old[cls];
+      if (state == kOldPage && npi < 0) {
+        p.ok = 1;
+        p.pid = v.block_table[table_base(c, s, layer, cls) + p.pi];
+      } else if (state == kNewPage && npi >= 0) {
+        int base, grant;
+        grant_of<LPT>(ws, c.max_seqs, s, cls, &base, &grant);
+        const int n_new = pl.n[cls] - pl.old[cls];
+        if (npi < grant) {
+          p.ok = 1;
+          p.pid = v.free_stack[cls][ws.avail_old[cls] - 1 - (base + npi)];
+        }
+        p.cnt = n_new - kPage * npi < kPage ? n_new - kPage * npi : kPage;
+        if (enter && p.slot == 0) {
+          if (p.ok) {
+            if (lane == 0) {
+              const int64_t row = table_base(c, s, layer, cls) + p.pi;
+              v.block_table[row] = p.pid;
+              v.slot_mask[row] = (1u << p.cnt) - 1u;
+              v.page_filled[cls][p.pid] = (uint8_t)p.cnt;
+            }
+            if (!BULK)
+              for (int sl = p.cnt + lane; sl < kPage; sl += LPT) v.slot_pos[cls][(int64_t)p.pid * kPage + sl] = -1;
+          }
+          if (npi == 0 && lane == 0) {
+            if (grant > 0) {
+              v.n_pages[npages_index(c, s, layer, cls)] = pl.np_old[cls] + grant;
+              atomicAdd(&v.n_live[sl_index(c, s, layer)], n_new < kPage * grant ? n_new : kPage * grant);
+            }
+            if (n_new > kPage * grant) atomicOr(&v.dev_status[sl_index(c, s, layer)], THINKV_ST_NOPAGES);
+          }
+        }
+      }
+    }
+  }
+  if (enter && lane == 0) {
+    if (p.ok && !(BULK && p.cnt > 0)) {
+      v.slot_pos[p.cls][(int64_t)p.pid * kPage + p.slot] = pos;
+      atomicMax(&v.page_pos_max[p.cls][p.pid], pos);
+    }
+    if (tok_handle) tok_handle[i] = p.ok ? THINKV_HANDLE(p.cls, p.pi, p.slot) : -1;
+  }
+  return p;
+}
+
+// The pools after the call: what all sequences together were granted is gone.  (One wave; nothing in the call reads free_top
+// after the plan kernel's snapshot.)
+__device__ inline void update_pools(const thinkv_view& v, const AppendWs& ws) {
+  const int lane = threadIdx.x & 63;
+  for (int k = 0; k < 3; ++k) {
+    int want = 0;
+    for (int t = lane; t < v.cfg.max_seqs; t += 64) want += ws.need[k * v.cfg.max_seqs + t];
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) want += __shfl_xor(want, d, 64);
+    const int avail = ws.avail_old[k];
+    if (lane == 0) v.free_top[k] = avail - (want < avail ? want : avail);
+  }
+}
+
+// Codes of a group in the integer formats: code = clamp(rint((x - zp) / s), 0, qmax) with IEEE's quotient, s = (max - min) / qmax
+// rounded up to binary16.  Both divisors have few significant bits, eleven and at most eight: the quotient of a binary32 number by such
+// a number is never within 2^-12 of a unit in the last place of the middle between two neighbouring numbers, so a
+// reciprocal good to a unit in the last place, one product and one residual correction (exact: its terms have a dozen bits
+// in common) give the correctly rounded quotient: three instructions in place of the eleven of a division.  That
+// needs finite numbers.  Otherwise the division's result is one of two for the whole group, and numbers in place of zp,
+// s and 1 / s make the same three instructions give it: code 0 if the scale is 0 or not finite (or the zero-point is not a number or
+// +inf), and the highest code if the zero-point is -inf.  A value that is not a number gets code 0.
+struct GroupCode {
+  float sf, zf, r;
+  uint32_t meta;   // scale | zero-point << 16
+};
+__device__ __forceinline__ GroupCode group_code(float mn, float mx, float qmax, float inv_qmax) {
+  const _Float16 zp = (_Float16)(mn + 0.0f);
+  const float range = mx - mn, s0 = range * inv_qmax;
+  const float s32 = range < INFINITY ? fmaf(fmaf(-qmax, s0, range), inv_qmax, s0) : range;
+  const _Float16 near = (_Float16)s32;
+  const uint16_t sc = (uint16_t)(__builtin_bit_cast(uint16_t, near) + ((float)near < s32 ? 1 : 0));
+  GroupCode g;
+  g.sf = (float)__builtin_bit_cast(_Float16, sc);
+  g.zf = (float)zp;
+  g.r = __builtin_amdgcn_rcpf(g.sf);
+  g.meta = (uint32_t)sc | (uint32_t)__builtin_bit_cast(uint16_t, zp) << 16;
+  const bool scale = g.sf > 0.0f && g.sf < INFINITY;
+  if (!(scale && fabsf(g.zf) < INFINITY)) {
+    const bool top = scale && g.zf == -INFINITY;
+    g.zf = top ? g.zf : 0.0f;
+    g.sf = top ? -1.0f : 0.0f;
+    g.r = top ? 1.0f : 0.0f;
+  }
+  return g;
+}
+// (The middle of three with a NaN is the smaller of the other two.  With a finite scale differences stay below 2^25, but for an
+// infinity whose group's maximum a signalling NaN has swallowed: the first clamp keeps it out of the correction.)
+__device__ __forceinline__ float group_quotient(const GroupCode& g, float x, float qmax) {
+  const float d = __builtin_amdgcn_fmed3f(x - g.zf, -0x1p60f, 0x1p60f);
+  const float q0 = d * g.r;
+  const float q = fmaf(fmaf(-g.sf, q0, d), g.r, q0);
+  return __builtin_amdgcn_fmed3f(rintf(q), 0.0f, qmax);
+}
+
+template <int CTRL>
+__device__ __forceinline__ float dpp(float x) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xF, 0xF, true));
+}
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E;   // lane ^ 1 and lane ^ 2 of a quad
+
+// A row piece: eight channels of a group of 32, whose four pieces are held by four neighbouring lanes.  Returns the codes, one a
+// byte.
+__device__ __forceinline__ uint2 piece_codes(const float (&x)[8], float qmax, float inv_qmax, uint32_t* meta) {
+  float mn = x[0], mx = x[0];
+#pragma unroll
+  for (int e = 1; e < 8; ++e) {
+    mn = fminf(mn, x[e]);
+    mx = fmaxf(mx, x[e]);
+  }
+  mn = fminf(mn, dpp<kDppXor1>(mn));
+  mx = fmaxf(mx, dpp<kDppXor1>(mx));
+  mn = fminf(mn, dpp<kDppXor2>(mn));
+  mx = fmaxf(mx, dpp<kDppXor2>(mx));
+  const GroupCode g = group_code(mn, mx, qmax, inv_qmax);
+  *meta = g.meta;
+  uint2 w = {0u, 0u};
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    w.x = __builtin_amdgcn_cvt_pk_u8_f32(group_quotient(g, x[e], qmax), e, w.x);
+    w.y = __builtin_amdgcn_cvt_pk_u8_f32(group_quotient(g, x[4 + e], qmax), e, w.y);
+  }
+  return w;
+}
+
+// The same in the paper's formats: the eight channels lie in one group of 16, which two neighbouring lanes share; ratios to the
+// scale in binary64, as the formats are defined.  whole_scale: the tensor-wide scale of the 8-bit format.
+__device__ __forceinline__ uint2 piece_codes_fp(const float (&x)[8], int bits, double whole_scale, uint32_t* meta) {
+  double sd = whole_scale;
+  if (bits != 8) {
+    float amax = fabsf(x[0]);
+#pragma unroll
+    for (int e = 1; e < 8; ++e) amax = fmaxf(amax, fabsf(x[e]));
+    amax = fmaxf(amax, dpp<kDppXor1>(amax));
+    *meta = e4m3_code_up((double)amax / (bits == 4 ? 6.0 : 1.0));
+    sd = (double)e4m3_value(*meta);
+  }
+  uint32_t code[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const double r = sd > 0.0 ? (double)x[e] / sd : 0.0;
+    code[e] = bits == 8 ? e4m3_encode(r) : (bits == 4 ? e2m1_encode(r) : ternary_encode(r));
+  }
+  uint2 w = {0u, 0u};
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    w.x |= code[e] << (8 * e);
+    w.y |= code[4 + e] << (8 * e);
+  }
+  return w;
+}
+
+// K codes of piece j of group grp: channel 32 grp + 8 j + e is field 4 grp + e / 2, half e % 2, of the chunk.
+__device__ __forceinline__ void put_k(uint8_t* chunk, int bits, int grp, uint2 w) {
+  if (bits == 8) {          // fields 4 grp .. + 3 are words 2 grp and 2 grp + 1
+    *(uint2*)(chunk + 8 * grp) = uint2{__builtin_amdgcn_perm(0u, w.x, 0x03010200u), __builtin_amdgcn_perm(0u, w.y, 0x03010200u)};
+    return;
+  }
+  const uint32_t even = __builtin_amdgcn_perm(w.y, w.x, 0x05010400u), odd = __builtin_amdgcn_perm(w.y, w.x, 0x07030602u);   // codes 0 4 1 5, 2 6 3 7
+  if (bits == 4) {          // word grp
+    *(uint32_t*)(chunk + 4 * grp) = even | odd << 4;
+  } else {                  // a quarter of each half of word grp / 2
+    const uint32_t two = even | odd << 2, four = two | two >> 4;
+    chunk[4 * (grp >> 1) + (grp & 1)] = (uint8_t)four;
+    chunk[4 * (grp >> 1) + 2 + (grp & 1)] = (uint8_t)(four >> 16);
+  }
+}
 
 // ---------------------------------------------------------------------------------------------
 // place: one block per (token, share of the kv-heads); every block of a token derives the same
-// slot, block 0 records it.
+// place, block 0 records it.
 template <int D>
 __global__ __launch_bounds__(256) void append_place_kernel(thinkv_view v, int layer, const void* __restrict__ k_new,
                                                            const void* __restrict__ v_new, const int32_t* __restrict__ tok_seq,
                                                            const int32_t* __restrict__ tok_pos, const uint8_t* __restrict__ tok_class,
                                                            int32_t* __restrict__ tok_handle, int n_tok, int in_dtype, AppendWs ws,
-                                                           int heads_per_block, int commit_here) {
+                                                           int heads_per_block) {
   constexpr int NG = D / kGroup;        // groups per row
   constexpr int NM = D / 16;            // 16-channel blocks per row
   constexpr int HP = 256 / (2 * D);     // heads handled per pass
-  __shared__ int s_place[7];            // type, page id, slot, ok, index in the page list, arrivals wanted, last to arrive
+  __shared__ int s_place[4];            // type, page id, slot, ok
   __shared__ uint8_t s_codes[HP][2][D];
   __shared__ uint32_t s_meta[HP][2][NG];
   __shared__ uint8_t s_scale8[HP][2][D / kGroupFp];   // THINKV_FMT_FP: the E4M3 scale codes of the row's groups of 16
@@ -264,99 +570,14 @@ __global__ __launch_bounds__(256) void append_place_kernel(thinkv_view v, int la
   const int h_end = (int)(blockIdx.y + 1) * heads_per_block < c.n_kv_heads ? (int)(blockIdx.y + 1) * heads_per_block : c.n_kv_heads;
   float x_first = 0.f;
   if (h_first < h_end) x_first = load_as_f32(kind ? v_new : k_new, ((int64_t)i * c.n_kv_heads + h_first) * D + ch, in_dtype);
-  // slot selection.  Thread 0 settles every case that is a closed form; the page of the k-th
-  // reclaimable slot (k < R) is found by all threads, each testing a stride of the page list.
-  __shared__ int s_find[4];   // 1 = search wanted / 2 = grant wanted, sequence, type, rank
-  __shared__ int s_scan[5];
-  if (tid == 0) {
-    int ok = 0, cls = 0, pid = 0, slot = 0, pi = 0, find = 0, k = 0, target = 0;
-    const int s = tok_seq[i];
-    if (s < 0 || s >= c.max_seqs) {
-      atomicOr(&v.dev_status[c.max_seqs * c.n_layers], THINKV_ST_BAD_SEQ);
-    } else {
-      cls = tok_class[i];
-      const SeqPlan& pl = ws.plan[s];
-      // every block of every token inside the sequence's range reports to the sequence
-      if (i >= pl.lo && i < pl.hi) target = (pl.hi - pl.lo) * (int)gridDim.y;
-      if (cls > 2) {
-        atomicOr(&v.dev_status[sl_index(c, s, layer)], THINKV_ST_BAD_CLASS);
-      } else if (i >= pl.lo && i < pl.hi) {
-        k = ws.tok_rank[i];
-        const int32_t* tab = v.block_table + table_base(c, s, layer, cls);
-        const int R = pl.R[cls], tail = pl.tail[cls], np = pl.np_old[cls];
-        if (k < R) {
-          find = 1;
-        } else if (k < R + tail) {
-          pi = np - 1;
-          pid = tab[pi];
-          slot = (int)v.page_filled[cls][pid] + (k - R);
-          ok = 1;
-        } else {
-          find = 2;   // a new page: which one depends on the grant, worked out by the whole block
-        }
-      }
-    }
-    s_find[0] = find; s_find[1] = s; s_find[2] = cls; s_find[3] = k;
-    s_place[0] = cls; s_place[1] = pid; s_place[2] = slot; s_place[3] = ok; s_place[4] = pi; s_place[5] = target;
-  }
-  __syncthreads();
-  if (s_find[0] == 1) {
-    const int s = s_find[1], cls = s_find[2], k = s_find[3];
-    const int np = ws.plan[s].np_old[cls];
-    const int64_t tb = table_base(c, s, layer, cls);
-    const int* pre = ws.pre + ((int64_t)s * 3 + cls) * c.max_pages;
-    for (int pi = tid; pi < np; pi += 256) {
-      uint32_t e = v.slot_mask[tb + pi] >> 16;
-      const int first = pre[pi];
-      if (k >= first && k < first + (int)__popc(e)) {   // exactly one page of the list
-        for (int j = k - first; j > 0; --j) e &= e - 1;
-        s_place[1] = v.block_table[tb + pi];
-        s_place[2] = __ffs(e) - 1;
-        s_place[3] = 1;
-        s_place[4] = pi;
-      }
-    }
-    __syncthreads();
-  }
-  if (s_find[0] == 2) {
-    const int s = s_find[1], cls = s_find[2], k = s_find[3];
-    int base, grant;
-    grant_of(ws, s, cls, &base, &grant, s_scan);
+  if (tid < 64) {
+    const Place p = settle<64, false>(v, layer, ws, tok_seq, tok_pos, tok_class, tok_handle, i, blockIdx.y == 0);
     if (tid == 0) {
-      const SeqPlan& pl = ws.plan[s];
-      const int kk = k - pl.R[cls] - pl.tail[cls], npi = kk >> 4;
-      if (npi < grant) {
-        s_place[1] = v.free_stack[cls][ws.avail_old[cls] - 1 - (base + npi)];
-        s_place[2] = kk & 15;
-        s_place[3] = 1;
-        s_place[4] = pl.np_old[cls] + npi;
-      }
+      s_place[0] = p.cls; s_place[1] = p.pid; s_place[2] = p.slot; s_place[3] = p.ok;
     }
-    __syncthreads();
+  } else if (tid < 128 && blockIdx.x == 0 && blockIdx.y == 0) {
+    update_pools(v, ws);
   }
-  if (tid == 0 && blockIdx.y == 0) {
-    const int cls = s_place[0], pid = s_place[1], slot = s_place[2], ok = s_place[3], pi = s_place[4];
-    if (ok) {
-      v.slot_pos[cls][(int64_t)pid * kPage + slot] = tok_pos[i];
-      atomicMax(&v.page_pos_max[cls][pid], tok_pos[i]);
-    }
-    if (tok_handle) tok_handle[i] = ok ? THINKV_HANDLE(cls, pi, slot) : -1;
-  }
-  __syncthreads();
-  // Everything this block reads of the sequence's tables has been read.  Report; the block that
-  // completes the sequence's count commits it (and puts the counter back to zero).
-  if (tid == 0) {
-    const int target = s_place[5], s = s_find[1];
-    int last = 0;
-    if (target > 0 && commit_here) {
-      last = atomicAdd(&v.append_counters[s], 1u) == (uint32_t)target - 1u;
-      if (last) v.append_counters[s] = 0u;
-    }
-    s_place[6] = last;
-  }
-  __syncthreads();
-  if (s_place[6]) commit_sequence(v, layer, ws, s_find[1], s_scan);
-  if (commit_here && blockIdx.x == 0 && blockIdx.y == 0) update_pools(v, ws, s_scan);
   __syncthreads();
   if (!s_place[3]) return;
   const int cls = s_place[0], pid = s_place[1], t = s_place[2];
@@ -396,22 +617,11 @@ __global__ __launch_bounds__(256) void append_place_kernel(thinkv_view v, int la
         mn = fminf(mn, __shfl_xor(mn, d, 64));
         mx = fmaxf(mx, __shfl_xor(mx, d, 64));
       }
-      const _Float16 zp = (_Float16)(mn + 0.0f);
-      const float s32 = (mx - mn) / qmax;
-      _Float16 sc = (_Float16)s32;
-      if ((float)sc < s32) {
-        uint16_t u = __builtin_bit_cast(uint16_t, sc);
-        sc = __builtin_bit_cast(_Float16, (uint16_t)(u + 1));
-      }
-      const float sf = (float)sc, zf = (float)zp;
-      float code = 0.0f;
-      if (sf > 0.0f) {
-        code = rintf((x - zf) / sf);
-        code = fminf(fmaxf(code, 0.0f), qmax);
-      }
+      const GroupCode gc = group_code(mn, mx, qmax, 1.0f / qmax);
+      const float code = group_quotient(gc, x, qmax);
       s_codes[hs][kind][ch] = (uint8_t)(int)code;
       if ((ch & 31) == 0)
-        s_meta[hs][kind][ch >> 5] = (uint32_t)__builtin_bit_cast(uint16_t, sc) | ((uint32_t)__builtin_bit_cast(uint16_t, zp) << 16);
+        s_meta[hs][kind][ch >> 5] = gc.meta;
       }
     }
     __syncthreads();
@@ -463,406 +673,242 @@ __global__ __launch_bounds__(256) void append_place_kernel(thinkv_view v, int la
   }
 }
 
-// The pools after the call: what all sequences together were granted is gone.  (One block;
-// nothing in the call reads free_top after the plan kernel's snapshot.)
-__device__ void update_pools(const thinkv_view& v, const AppendWs& ws, int* s_scan /*[5]*/) {
-  const int tid = threadIdx.x;
-  for (int k = 0; k < 3; ++k) {
-    int want = 0;
-    for (int t = tid; t < v.cfg.max_seqs; t += 256) want += ws.plan[t].need[k];
-    want = block_sum(want, s_scan);
-    const int avail = ws.avail_old[k];
-    if (tid == 0) v.free_top[k] = avail - (want < avail ? want : avail);
-  }
-}
-
-// One block: masks, fill counts, page lists and counters of sequence s, once every place block
-// of the sequence has settled its slot.
-__device__ void commit_sequence(const thinkv_view& v, int layer, const AppendWs& ws, int s, int* s_scan /*[5]*/) {
-  const thinkv_config& c = v.cfg;
-  const int tid = threadIdx.x;
-  const SeqPlan pl = ws.plan[s];
-  if (pl.lo >= pl.hi) return;
-  int placed_all = 0, short_any = 0;
-  for (int k = 0; k < 3; ++k) {
-    const int n = pl.n[k], R = pl.R[k], tail = pl.tail[k], np = pl.np_old[k];
-    if (n == 0) continue;
-    int base = 0, grant = 0;
-    if (pl.need[k] > 0) grant_of(ws, s, k, &base, &grant, s_scan);
-    int32_t* tab = v.block_table + table_base(c, s, layer, k);
-    uint32_t* msk = v.slot_mask + table_base(c, s, layer, k);
-    const int* pre = ws.pre + ((int64_t)s * 3 + k) * c.max_pages;
-    for (int pi = tid; pi < np; pi += 256) {
-      uint32_t m = msk[pi];
-      uint32_t e = m >> 16;
-      int take = n - pre[pi];
-      const int have = __popc(e);
-      take = take < 0 ? 0 : (take > have ? have : take);
-      uint32_t bits = 0;
-      for (int j = 0; j < take; ++j) {
-        uint32_t b = e & (0u - e);
-        bits |= b;
-        e ^= b;
-      }
-      m = (m | bits) & ~(bits << 16);
-      if (pi == np - 1 && tail > 0 && n > R) {
-        const int add = (n - R) < tail ? (n - R) : tail;
-        const int pid = tab[pi];
-        const int f = v.page_filled[k][pid];
-        m |= ((1u << add) - 1u) << f;
-        v.page_filled[k][pid] = (uint8_t)(f + add);
-      }
-      msk[pi] = m;
-    }
-    for (int i = tid; i < grant; i += 256) {
-      const int pid = v.free_stack[k][ws.avail_old[k] - 1 - (base + i)];
-      int cnt = n - R - tail - kPage * i;
-      cnt = cnt > kPage ? kPage : cnt;
-      tab[np + i] = pid;
-      v.page_filled[k][pid] = (uint8_t)cnt;
-      msk[np + i] = (1u << cnt) - 1u;
-      for (int sl = cnt; sl < kPage; ++sl) v.slot_pos[k][(int64_t)pid * kPage + sl] = -1;
-    }
-    const int cap = R + tail + kPage * grant;
-    placed_all += n < cap ? n : cap;
-    if (n > cap) short_any = 1;
-    if (tid == 0) v.n_pages[npages_index(c, s, layer, k)] = np + grant;
-  }
-  if (tid == 0) {
-    v.n_live[sl_index(c, s, layer)] += placed_all;
-    if (short_any) atomicOr(&v.dev_status[sl_index(c, s, layer)], THINKV_ST_NOPAGES);
-  }
-}
-
 // ---------------------------------------------------------------------------------------------
-// Bulk calls (prefill-style: thousands of tokens).  One block per token pays the slot selection and
-// eight short load-quantise-store passes for every token; here a block takes sixteen consecutive
-// tokens of the call: sixteen threads settle their slots side by side, then every pass quantises
-// one (kv-head, K or V) row of all sixteen tokens, eight channels per thread (one 16-byte load).
-// K codes go straight from registers to the page: the eight channels of a thread are the fields
-// of one 8-channel piece of a group, which the layout keeps together (8, 4 or 2 x 1 bytes).  V
-// codes are transposed through LDS (a V chunk holds channels 16 apart).  The grants of new pages
-// are worked out once, by a small kernel between plan and place.
-__global__ __launch_bounds__(256) void append_grant_kernel(thinkv_view v, AppendWs ws) {
-  __shared__ int s_scan[5];
-  const int S = v.cfg.max_seqs, tid = threadIdx.x;
-  for (int k = 0; k < 3; ++k) {
-    const int avail = ws.avail_old[k];
-    int run = 0;
-    for (int s0 = 0; s0 < S; s0 += 256) {
-      const int s = s0 + tid;
-      const int need = s < S ? ws.plan[s].need[k] : 0;
-      int ex;
-      const int tot = block_excl_scan(need, &ex, s_scan);
-      if (s < S) {
-        const int before = run + ex, left = avail - before;
-        ws.plan[s].base[k] = before < avail ? before : avail;
-        ws.plan[s].grant[k] = left < 0 ? 0 : (left < need ? left : need);
-      }
-      run += tot;
-    }
-  }
-}
-
+// Bulk calls (prefill-style: thousands of tokens).  A block takes 32 consecutive tokens of the call and settles their
+// places side by side, eight lanes a token.  The unit of work behind that is the K or the V rows of sixteen tokens and one
+// kv-head, by one wave: eight channels a lane (one 16-byte load), codes in registers, V codes transposed through LDS (a V
+// chunk holds channels 16 apart).
+// New pages are written whole: the token in a new page's first slot brings the page to its block, the others are the next
+// fifteen of its type, and the unit's part of the page (0.3 to 2.3 KB) is put together in LDS and stored in 16-byte words.
+// Tokens that take slots of existing pages are stored field by field.
+// What bounds it: reading the rows, 256 bytes at a time; quantising and storing take a tenth of its time when left out.
+// 37,000 tokens of 16 prompts, 8 kv-heads of 128, bf16 (151 MB in, 50 MB out): 96.5 us with a block of sixteen tokens
+// storing 2 to 8 bytes at a time into pages that four blocks shared, 67 with whole pages, 60 with nontemporal loads of
+// neighbouring heads side by side.  Rows requested a unit ahead gained nothing (64 against 60), nor did K and V in one unit (more
+// registers, fewer waves).
 constexpr int kBulkTokens = 16;   // tokens per block of the bulk place kernel
 
-template <int D, bool F32>
+// A new page: its first token in the call, type, number, tokens the call puts into it, the end of the sequence's tokens.
+struct NewPage {
+  int first, cls, pid, cnt, end;
+};
+
+// LDS of a wave: the K or V part of a block (codes, scales), and the V codes of sixteen rows, one a byte
+template <int D>
+struct UnitLds {
+  uint4 codes[(D == 128 ? 2048 : 1024) / 16];
+  uint4 meta[(D == 128 ? 256 : 128) / 16];
+  uint32_t v[kPage][D / 4];
+};
+
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+template <int IN>
+__device__ __forceinline__ void widen(const uint4* raw, float (&x)[8]) {
+  const uint4 r0 = raw[0], r1 = raw[IN == THINKV_F32 ? 1 : 0];
+  const uint32_t w[8] = {r0.x, r0.y, r0.z, r0.w, r1.x, r1.y, r1.z, r1.w};
+  if (IN == THINKV_F32) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = __builtin_bit_cast(float, w[e]);
+  } else if (IN == THINKV_F16) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = (float)__builtin_bit_cast(_Float16, (uint16_t)(w[e >> 1] >> (16 * (e & 1))));
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = __builtin_bit_cast(float, e & 1 ? w[e >> 1] & 0xFFFF0000u : w[e >> 1] << 16);
+  }
+}
+
+// Sixteen bytes that are read once (nontemporal: they leave the caches to the pages).
+__device__ __forceinline__ uint4 load_once(const void* p) {
+  typedef uint32_t Word4 __attribute__((ext_vector_type(4)));
+  const Word4 w = __builtin_nontemporal_load((const Word4*)p);
+  return uint4{w.x, w.y, w.z, w.w};
+}
+
+// What a row of a unit is: its token, and the page and slot it goes to.
+struct Row {
+  int tok, cls, pid, slot;
+};
+
+// The K (kind 0) or V (kind 1) rows of sixteen tokens and kv-head h, by a wave.  WHOLE: the rows are the slots of one new page, of
+// which the first cnt are taken.  Otherwise row r goes to its own page if bit r of rows is set.
+template <int D, int IN, bool FP, bool WHOLE, typename RowOf>
+__device__ __forceinline__ void place_unit(const thinkv_view& v, const void* __restrict__ src, int kind, int h, RowOf row_of, uint32_t rows, UnitLds<D>& lds) {
+  constexpr int NM = D / 16, TPR = D / 8, RP = 64 / TPR, NP = kPage / RP, kW = IN == THINKV_F32 ? 2 : 1;
+  const thinkv_config& c = v.cfg;
+  const int lane = threadIdx.x & 63, H = c.n_kv_heads;
+  const int piece = lane % TPR, grp = piece >> 2, j = piece & 3;
+  uint4 raw[NP][kW];
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    const int r = RP * p + lane / TPR;
+    const int i = row_of(rows >> r & 1 ? r : __builtin_ctz(rows)).tok;   // (rows that are not there are quantised and not stored)
+    const int64_t at = ((int64_t)i * H + h) * D + 8 * piece;
+#pragma unroll
+    for (int w = 0; w < kW; ++w)
+      raw[p][w] = load_once(IN == THINKV_F32 ? (const void*)((const float*)src + at + 4 * w) : (const void*)((const uint16_t*)src + at));
+  }
+  // WHOLE: the page's two parts
+  uint4 *page_codes = nullptr, *page_meta = nullptr;
+  int n_codes = 0, n_meta = 0;
+  if (WHOLE) {
+    const Row row = row_of(0);
+    const BlockGeom g = block_geom(c.bits_of_class[row.cls], D, c.format);
+    uint8_t* const blk = v.arena[row.cls] + ((int64_t)row.pid * H + h) * g.block_bytes;
+    page_codes = (uint4*)(blk + (kind ? g.v_codes : g.k_codes));
+    page_meta = (uint4*)(blk + (kind ? g.v_meta : g.k_meta));
+    n_codes = 4 * g.chunk_bytes;                                    // 64 chunks
+    n_meta = (g.block_bytes - 2 * 64 * g.chunk_bytes) / 2 / 16;
+    if (rows != 0xFFFFu) {   // a page that stays partly empty keeps what its other slots hold
+      for (int w = lane; w < n_codes; w += 64) lds.codes[w] = page_codes[w];
+      for (int w = lane; w < n_meta; w += 64) lds.meta[w] = page_meta[w];
+    }
+    wave_lds_order();
+  }
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    const int r = RP * p + lane / TPR;
+    const Row row = row_of(r);
+    const int bits = c.bits_of_class[row.cls];
+    const float qmax = (float)((1 << bits) - 1);
+    float x[8];
+    widen<IN>(raw[p], x);
+    uint32_t meta = 0;
+    const uint2 w = FP ? piece_codes_fp(x, bits, (double)c.fp8_scale[kind], &meta) : piece_codes(x, qmax, 1.0f / qmax, &meta);
+    if (rows >> r & 1) {
+      const BlockGeom g = block_geom(bits, D, c.format);
+      uint8_t* const blk = WHOLE ? nullptr : v.arena[row.cls] + ((int64_t)row.pid * H + h) * g.block_bytes;
+      if (!kind) put_k((WHOLE ? (uint8_t*)lds.codes : blk + g.k_codes) + (16 * j + row.slot) * g.chunk_bytes, bits, grp, w);
+      else *(uint2*)&lds.v[r][2 * piece] = w;
+      uint8_t* const m = WHOLE ? (uint8_t*)lds.meta : blk + (kind ? g.v_meta : g.k_meta);
+      if (FP) {
+        if (bits != 8 && (j & 1) == 0) m[(2 * grp + (j >> 1)) * kPage + row.slot] = (uint8_t)meta;
+      } else if (j == 0) {
+        ((uint16_t*)m)[meta_index(row.slot, grp)] = (uint16_t)meta;
+        ((uint16_t*)m)[meta_index(row.slot, grp) + 4] = (uint16_t)(meta >> 16);
+      }
+    }
+  }
+  wave_lds_order();
+  // V: chunk 16 (slot / 4) + m holds channels m, m + 16, ... of four slots.  A lane takes four m of one row: the codes of
+  // its channels mb are whole halves of consecutive words (one byte when a row has fewer fields than a half).
+  if (kind && (rows >> (lane >> 2) & 1)) {
+    const Row row = row_of(lane >> 2);
+    const int mq = lane & 3, bits = c.bits_of_class[row.cls];
+    const BlockGeom g = block_geom(bits, D, c.format);
+    uint32_t d[NM];
+#pragma unroll
+    for (int mb = 0; mb < NM; ++mb) d[mb] = lds.v[lane >> 2][4 * mb + mq];
+    uint8_t* const at = (WHOLE ? (uint8_t*)lds.codes : v.arena[row.cls] + ((int64_t)row.pid * H + h) * g.block_bytes + g.v_codes) +
+                        (16 * (row.slot >> 2) + 4 * mq) * g.chunk_bytes + 2 * (row.slot & 1);
+    const int u = (row.slot >> 1) & 1;
+    auto halves = [&](uint32_t a, uint32_t b, int off) {   // bytes of a below bytes of b, one half for each of the four chunks
+      const uint32_t h01 = __builtin_amdgcn_perm(b, a, 0x05010400u), h23 = __builtin_amdgcn_perm(b, a, 0x07030602u);
+      *(uint16_t*)(at + off) = (uint16_t)h01;
+      *(uint16_t*)(at + off + g.chunk_bytes) = (uint16_t)(h01 >> 16);
+      *(uint16_t*)(at + off + 2 * g.chunk_bytes) = (uint16_t)h23;
+      *(uint16_t*)(at + off + 3 * g.chunk_bytes) = (uint16_t)(h23 >> 16);
+    };
+    if (bits == 8) {
+#pragma unroll
+      for (int w = 0; w < NM / 2; ++w) halves(d[2 * w], d[2 * w + 1], 4 * (u * (NM / 2) + w));
+    } else if (bits == 4) {
+#pragma unroll
+      for (int w = 0; w < NM / 4; ++w) halves(d[4 * w] | d[4 * w + 1] << 4, d[4 * w + 2] | d[4 * w + 3] << 4, 4 * (u * (NM / 4) + w));
+    } else {
+      const uint32_t a = d[0] | d[1] << 2 | d[2] << 4 | d[3] << 6;
+      if constexpr (NM == 8) {
+        halves(a, d[4] | d[5] << 2 | d[6] << 4 | d[7] << 6, 4 * u);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) at[u + e * g.chunk_bytes] = (uint8_t)(a >> (8 * e));
+      }
+    }
+  }
+  wave_lds_order();
+  if (WHOLE) {
+    for (int w = lane; w < n_codes; w += 64) page_codes[w] = lds.codes[w];
+    for (int w = lane; w < n_meta; w += 64) page_meta[w] = lds.meta[w];
+    wave_lds_order();   // (the next unit's first stores come behind these loads)
+  }
+}
+
+template <int D, int IN, bool FP>
 __global__ __launch_bounds__(256) void append_place_bulk_kernel(thinkv_view v, int layer, const void* __restrict__ k_new,
                                                                 const void* __restrict__ v_new, const int32_t* __restrict__ tok_seq,
                                                                 const int32_t* __restrict__ tok_pos,
                                                                 const uint8_t* __restrict__ tok_class, int32_t* __restrict__ tok_handle,
-                                                                int n_tok, int in_dtype, AppendWs ws, int heads_per_block) {
-  constexpr int NM = D / 16;            // 16-channel blocks per row
-  constexpr int TPR = D / 8;            // threads per row
-  constexpr int RPP = 256 / TPR;        // rows per pass: 16 (one (head, K or V) of all tokens) or 32 (one head, K and V)
-  __shared__ int s_cls[kBulkTokens], s_pid[kBulkTokens], s_slot[kBulkTokens], s_ok[kBulkTokens], s_pi[kBulkTokens];
-  __shared__ int s_find[kBulkTokens], s_seq[kBulkTokens], s_rank[kBulkTokens];
-  __shared__ __attribute__((aligned(8))) uint8_t s_codes[2][kBulkTokens][D];
+                                                                int n_tok, AppendWs ws, int heads_per_block) {
+  __shared__ int s_cls[kBulkTokens], s_pid[kBulkTokens], s_slot[kBulkTokens];
+  __shared__ NewPage s_new[kBulkTokens];
+  __shared__ int s_tok[kBulkTokens][kPage];   // the tokens of the new pages
+  __shared__ int s_n_new;
+  __shared__ uint32_t s_old;                  // bit t: token t of the block goes to an existing page
+  __shared__ UnitLds<D> s_unit[4];
   const thinkv_config& c = v.cfg;
   const int tid = threadIdx.x, i0 = blockIdx.x * kBulkTokens;
-  // this block's share of the kv-heads; the first input rows are requested before the slots are settled
+  // this block's share of the kv-heads
   const int H = c.n_kv_heads;
   const int h_lo = blockIdx.y * heads_per_block, h_hi = h_lo + heads_per_block < H ? h_lo + heads_per_block : H;
-  const int rsub = tid / TPR, cpiece = tid % TPR;          // row inside the pass, 8-channel piece of the row
-  const int grp = cpiece >> 2, j = cpiece & 3;             // group of the piece, piece inside the group
-  const int n_pass = (2 * (h_hi - h_lo) * kBulkTokens) / RPP;
-  // row of this thread in pass p: always the same token (a pass holds whole runs of sixteen rows);
-  // head and K or V change from pass to pass
-  const int t = rsub % kBulkTokens;
-  auto row_of = [&](int p, int* h, int* kind) {
-    const int hk = (p * RPP + rsub) / kBulkTokens;
-    *h = h_lo + (hk >> 1);
-    *kind = hk & 1;
-  };
-  // the eight input values of this thread in pass p (16-bit inputs: one 16-byte word, binary32: two)
-  const int64_t row_at = (int64_t)(i0 + t) * H * D + 8 * cpiece;
-  constexpr int kW = F32 ? 2 : 1;
-  struct Raw {
-    uint4 w[kW];
-  };
-  auto fetch = [&](int p, Raw* r) {
-    int h, kind;
-    row_of(p, &h, &kind);
-    if (p >= n_pass || i0 + t >= n_tok) return;   // (a token without a slot is loaded too: its slot is not known yet at the first call)
-    const int64_t at = row_at + h * D;
-    const void* src = kind ? v_new : k_new;
-    if (F32) {
-      r->w[0] = *(const uint4*)((const float*)src + at);
-      r->w[kW - 1] = *(const uint4*)((const float*)src + at + 4);
-    } else {
-      r->w[0] = *(const uint4*)((const uint16_t*)src + at);
-    }
-  };
-  // four passes are requested ahead: a pass is short, and one pass is not enough to cover a load
-  constexpr int kAhead = 4;
-  Raw cur[kAhead], nxt[kAhead];
-#pragma unroll
-  for (int q = 0; q < kAhead; ++q) {
-#pragma unroll
-    for (int i = 0; i < kW; ++i) cur[q].w[i] = nxt[q].w[i] = uint4{0u, 0u, 0u, 0u};
-    fetch(q, &cur[q]);
-  }
-  // ---- slots: every case that is a closed form is settled by the token's own thread
-  if (tid < kBulkTokens) {
-    const int i = i0 + tid;
-    int ok = 0, cls = 0, pid = 0, slot = 0, pi = 0, find = 0, k = 0, s = -1;
-    if (i < n_tok) {
-      s = tok_seq[i];
-      if (s < 0 || s >= c.max_seqs) {
-        atomicOr(&v.dev_status[c.max_seqs * c.n_layers], THINKV_ST_BAD_SEQ);
-      } else {
-        cls = tok_class[i];
-        const SeqPlan& pl = ws.plan[s];
-        if (cls > 2) {
-          atomicOr(&v.dev_status[sl_index(c, s, layer)], THINKV_ST_BAD_CLASS);
-        } else if (i >= pl.lo && i < pl.hi) {
-          k = ws.tok_rank[i];
-          const int32_t* tab = v.block_table + table_base(c, s, layer, cls);
-          const int R = pl.R[cls], tail = pl.tail[cls], np = pl.np_old[cls];
-          if (k < R) {
-            find = 1;   // the k-th reclaimable slot: searched by the whole block below
-          } else if (k < R + tail) {
-            pi = np - 1;
-            pid = tab[pi];
-            slot = (int)v.page_filled[cls][pid] + (k - R);
-            ok = 1;
-          } else {
-            const int kk = k - R - tail, npi = kk >> 4;
-            if (npi < pl.grant[cls]) {
-              pid = v.free_stack[cls][ws.avail_old[cls] - 1 - (pl.base[cls] + npi)];
-              slot = kk & 15;
-              pi = np + npi;
-              ok = 1;
-            }
-          }
-        }
-      }
-    }
-    s_cls[tid] = cls; s_pid[tid] = pid; s_slot[tid] = slot; s_ok[tid] = ok; s_pi[tid] = pi;
-    s_find[tid] = find; s_seq[tid] = s; s_rank[tid] = k;
-  }
+  // ---- places
+  if (tid == 0) s_n_new = s_old = 0;
   __syncthreads();
-  for (int t = 0; t < kBulkTokens; ++t) {
-    if (s_find[t] != 1) continue;   // the same for all threads
-    const int s = s_seq[t], cls = s_cls[t], k = s_rank[t];
-    const int np = ws.plan[s].np_old[cls];
-    const int64_t tb = table_base(c, s, layer, cls);
-    const int* pre = ws.pre + ((int64_t)s * 3 + cls) * c.max_pages;
-    for (int pi = tid; pi < np; pi += 256) {
-      uint32_t e = v.slot_mask[tb + pi] >> 16;
-      const int first = pre[pi];
-      if (k >= first && k < first + (int)__popc(e)) {   // exactly one page of the list
-        for (int j = k - first; j > 0; --j) e &= e - 1;
-        s_pid[t] = v.block_table[tb + pi];
-        s_slot[t] = __ffs(e) - 1;
-        s_ok[t] = 1;
-        s_pi[t] = pi;
-      }
+  {
+    constexpr int LPT = 256 / kBulkTokens;
+    const int u = tid / LPT;
+    Place p = {0, 0, 0, 0, 0, 0};
+    if (i0 + u < n_tok) p = settle<LPT, true>(v, layer, ws, tok_seq, tok_pos, tok_class, tok_handle, i0 + u, blockIdx.y == 0);
+    if (tid % LPT == 0) {
+      s_cls[u] = p.cls; s_pid[u] = p.pid; s_slot[u] = p.slot;
+      if (p.ok && p.cnt == 0) atomicOr(&s_old, 1u << u);
+      if (p.ok && p.cnt > 0 && p.slot == 0) s_new[atomicAdd(&s_n_new, 1)] = NewPage{i0 + u, p.cls, p.pid, p.cnt, ws.plan[tok_seq[i0 + u]].hi};
+    }
+  }
+  if (blockIdx.x == 0 && blockIdx.y == 0 && tid < 64) update_pools(v, ws);
+  __syncthreads();
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int n_new = __builtin_amdgcn_readfirstlane(s_n_new), hn = h_hi - h_lo;
+  const uint32_t old = __builtin_amdgcn_readfirstlane(s_old);
+  for (int q = wave; q < n_new; q += 4) {   // the new pages' tokens: the next of the type, from the first on
+    const NewPage np = s_new[q];
+    int found = 0;
+    for (int i = np.first; i < np.end && found < np.cnt; i += 64) {
+      const bool is = i + lane < np.end && tok_class[i + lane] == np.cls;
+      const uint64_t all = __ballot(is);
+      const int at = found + __popcll(all & ((1ull << lane) - 1ull));
+      if (is && at < np.cnt) s_tok[q][at] = i + lane;
+      found += __popcll(all);
+    }
+    found = min(found, np.cnt);   // (fewer only if the sequence ids of the call decrease somewhere)
+    if (lane == 0) s_new[q].cnt = found;
+    wave_lds_order();
+    if (blockIdx.y == 0) {
+      int pos = lane < found ? tok_pos[s_tok[q][lane]] : -1;
+      if (lane < kPage) v.slot_pos[np.cls][(int64_t)np.pid * kPage + lane] = pos;
+#pragma unroll
+      for (int d = 8; d >= 1; d >>= 1) pos = max(pos, __shfl_xor(pos, d, 64));
+      if (lane == 0) atomicMax(&v.page_pos_max[np.cls][np.pid], pos);
     }
   }
   __syncthreads();
-  if (tid < kBulkTokens && i0 + tid < n_tok && blockIdx.y == 0) {
-    const int i = i0 + tid, cls = s_cls[tid], pid = s_pid[tid], slot = s_slot[tid], ok = s_ok[tid];
-    if (ok) {
-      v.slot_pos[cls][(int64_t)pid * kPage + slot] = tok_pos[i];
-      atomicMax(&v.page_pos_max[cls][pid], tok_pos[i]);
-    }
-    if (tok_handle) tok_handle[i] = ok ? THINKV_HANDLE(cls, s_pi[tid], slot) : -1;
+  for (int w = wave; w < 2 * n_new * hn; w += 4) {
+    const int q = w / (2 * hn), kind = w / hn & 1, h = h_lo + w % hn;   // neighbours in memory side by side
+    const int cls = __builtin_amdgcn_readfirstlane(s_new[q].cls), pid = __builtin_amdgcn_readfirstlane(s_new[q].pid);
+    const int cnt = __builtin_amdgcn_readfirstlane(s_new[q].cnt);
+    place_unit<D, IN, FP, true>(v, kind ? v_new : k_new, kind, h, [&](int r) { return Row{s_tok[q][r], cls, pid, r}; }, (1u << cnt) - 1u, s_unit[wave]);
   }
-  // ---- quantise and store
-  // what does not change from pass to pass: this thread's token as a quantiser thread ...
-  const bool ok = s_ok[t] != 0;
-  const int slot = s_slot[t];
-  const int bits = c.bits_of_class[s_cls[t]];
-  const bool fp = c.format == THINKV_FMT_FP;
-  const BlockGeom gm = block_geom(bits, D, c.format);
-  uint8_t* const page = v.arena[s_cls[t]] + (int64_t)s_pid[t] * H * gm.block_bytes;
-  const float qmax = (float)((1 << bits) - 1);
-  // ... and its (token, chunk) as a thread that packs V codes
-  const int tv = tid >> 4, m = tid & 15;
-  const bool v_ok = s_ok[tv] != 0;
-  const int bv = c.bits_of_class[s_cls[tv]], slv = s_slot[tv];
-  const BlockGeom gv = block_geom(bv, D, c.format);
-  uint8_t* const v_chunk = v.arena[s_cls[tv]] + (int64_t)s_pid[tv] * H * gv.block_bytes + gv.v_codes +
-                           (16 * (slv >> 2) + m) * gv.chunk_bytes + 2 * (slv & 1);
-  const int v_u = (slv >> 1) & 1;
-  auto pass = [&](int p, const Raw& raw) {
-    int h, kind;
-    row_of(p, &h, &kind);
-    const bool has_v = RPP > kBulkTokens || (p & 1);       // some rows of this pass are V rows (the same for all threads)
-    const int buf = (RPP > kBulkTokens ? p : p >> 1) & 1;
-    uint8_t* blk = page + h * gm.block_bytes;
-    if (ok) {
-      float x[8];
-      const uint4 r0 = raw.w[0], r1 = raw.w[kW - 1];
-      const uint32_t w[8] = {r0.x, r0.y, r0.z, r0.w, r1.x, r1.y, r1.z, r1.w};
-      if (F32) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) x[e] = __builtin_bit_cast(float, w[e]);
-      } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const uint16_t u = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
-          x[e] = in_dtype == THINKV_F16 ? (float)__builtin_bit_cast(_Float16, u) : __builtin_bit_cast(float, (uint32_t)u << 16);
-        }
-      }
-      uint32_t code[8];
-      if (fp) {
-        // the paper's formats: the eight channels of a thread lie in one group of 16 (number 2 grp + j / 2), which two
-        // neighbour threads share; ratios to the scale in binary64, as the formats are defined
-        double sd = (double)c.fp8_scale[kind];
-        if (bits != 8) {
-          float amax = fabsf(x[0]);
-#pragma unroll
-          for (int e = 1; e < 8; ++e) amax = fmaxf(amax, fabsf(x[e]));
-          amax = fmaxf(amax, __shfl_xor(amax, 1, 64));
-          const uint32_t sc8 = e4m3_code_up((double)amax / (bits == 4 ? 6.0 : 1.0));
-          sd = (double)e4m3_value(sc8);
-          if ((j & 1) == 0) (blk + (kind ? gm.v_meta : gm.k_meta))[(2 * grp + (j >> 1)) * kPage + slot] = (uint8_t)sc8;
-        }
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const double r = sd > 0.0 ? (double)x[e] / sd : 0.0;
-          code[e] = bits == 8 ? e4m3_encode(r) : (bits == 4 ? e2m1_encode(r) : ternary_encode(r));
-        }
-      } else {
-      float mn = x[0], mx = x[0];
-#pragma unroll
-      for (int e = 1; e < 8; ++e) {
-        mn = fminf(mn, x[e]);
-        mx = fmaxf(mx, x[e]);
-      }
-#pragma unroll
-      for (int d = 1; d <= 2; d <<= 1) {   // the four threads of a group are neighbours
-        mn = fminf(mn, __shfl_xor(mn, d, 64));
-        mx = fmaxf(mx, __shfl_xor(mx, d, 64));
-      }
-      const _Float16 zp = (_Float16)(mn + 0.0f);
-      const float s32 = (mx - mn) / qmax;
-      _Float16 sc = (_Float16)s32;
-      if ((float)sc < s32) {
-        uint16_t u = __builtin_bit_cast(uint16_t, sc);
-        sc = __builtin_bit_cast(_Float16, (uint16_t)(u + 1));
-      }
-      const float sf = (float)sc, zf = (float)zp;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        float q = 0.0f;
-        if (sf > 0.0f) {
-          q = rintf((x[e] - zf) / sf);
-          q = fminf(fmaxf(q, 0.0f), qmax);
-        }
-        code[e] = (uint32_t)(int)q;
-      }
-      if (j == 0) {
-        uint16_t* meta = (uint16_t*)(blk + (kind ? gm.v_meta : gm.k_meta));
-        meta[meta_index(slot, grp)] = __builtin_bit_cast(uint16_t, sc);
-        meta[meta_index(slot, grp) + 4] = __builtin_bit_cast(uint16_t, zp);
-      }
-      }
-      if (!kind) {
-        // K: channel 32 grp + 8 j + e is field 4 grp + e / 2, half e % 2, of chunk 16 j + slot
-        uint8_t* chunk = blk + gm.k_codes + (16 * j + slot) * gm.chunk_bytes;
-        if (bits == 8) {          // fields 4 grp .. + 3 are words 2 grp and 2 grp + 1
-          uint32_t w0 = 0, w1 = 0;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            w0 |= code[e] << (16 * (e & 1) + 8 * (e >> 1));
-            w1 |= code[4 + e] << (16 * (e & 1) + 8 * (e >> 1));
-          }
-          *(uint2*)(chunk + 8 * grp) = uint2{w0, w1};
-        } else if (bits == 4) {   // word grp
-          uint32_t w0 = 0;
-#pragma unroll
-          for (int e = 0; e < 8; ++e) w0 |= code[e] << (16 * (e & 1) + 4 * (e >> 1));
-          *(uint32_t*)(chunk + 4 * grp) = w0;
-        } else {                  // a quarter of each half of word grp / 2
-          uint32_t lo = 0, hi = 0;
-#pragma unroll
-          for (int e = 0; e < 8; e += 2) {
-            lo |= code[e] << e;
-            hi |= code[e + 1] << e;
-          }
-          chunk[4 * (grp >> 1) + (grp & 1)] = (uint8_t)lo;
-          chunk[4 * (grp >> 1) + 2 + (grp & 1)] = (uint8_t)hi;
-        }
-      } else {
-        uint32_t w0 = 0, w1 = 0;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          w0 |= code[e] << (8 * e);
-          w1 |= code[4 + e] << (8 * e);
-        }
-        *(uint2*)&s_codes[buf][t][8 * cpiece] = uint2{w0, w1};
-      }
+  if (old)
+    for (int w = wave; w < kBulkTokens / kPage * 2 * hn; w += 4) {
+      const int t0 = w / (2 * hn) * kPage, kind = w & 1;
+      const uint32_t rows = old >> t0 & 0xFFFFu;
+      if (rows)
+        place_unit<D, IN, FP, false>(v, kind ? v_new : k_new, kind, h_lo + (w >> 1) % hn,
+                                     [&](int r) { return Row{i0 + t0 + r, s_cls[t0 + r], s_pid[t0 + r], s_slot[t0 + r]}; }, rows, s_unit[wave]);
     }
-    if (has_v) {
-      __syncthreads();
-      // V: chunk 16 (slot / 4) + m holds channels m, m + 16, ... of four slots.  Thread (token, m)
-      // packs the token's NM codes of the chunk: field u NM + mb of half hh (u, hh from the slot), i.e.
-      // whole 16-bit halves of consecutive words, or one byte when a row has fewer fields than a half.
-      const int hv = h_lo + (RPP > kBulkTokens ? p : p >> 1);   // the head whose V rows were just staged
-      if (v_ok) {
-        uint32_t cd[NM];
-#pragma unroll
-        for (int mb = 0; mb < NM; ++mb) cd[mb] = s_codes[buf][tv][16 * mb + m];
-        uint8_t* chunk = v_chunk + hv * gv.block_bytes;        // already at the half word of the slot
-        if (bv == 8) {
-#pragma unroll
-          for (int w = 0; w < NM / 2; ++w) *(uint16_t*)(chunk + 4 * (v_u * (NM / 2) + w)) = (uint16_t)(cd[2 * w] | cd[2 * w + 1] << 8);
-        } else if (bv == 4) {
-#pragma unroll
-          for (int w = 0; w < NM / 4; ++w)
-            *(uint16_t*)(chunk + 4 * (v_u * (NM / 4) + w)) =
-                (uint16_t)(cd[4 * w] | cd[4 * w + 1] << 4 | cd[4 * w + 2] << 8 | cd[4 * w + 3] << 12);
-        } else {
-          uint32_t val = 0;
-#pragma unroll
-          for (int mb = 0; mb < NM; ++mb) val |= cd[mb] << (2 * mb);
-          if (NM == 8)
-            *(uint16_t*)(chunk + 4 * v_u) = (uint16_t)val;
-          else
-            chunk[v_u] = (uint8_t)val;
-        }
-      }
-    }
-  };
-  for (int p0 = 0; p0 < n_pass; p0 += kAhead) {
-#pragma unroll
-    for (int q = 0; q < kAhead; ++q) fetch(p0 + kAhead + q, &nxt[q]);
-#pragma unroll
-    for (int q = 0; q < kAhead; ++q)
-      if (p0 + q < n_pass) pass(p0 + q, cur[q]);
-#pragma unroll
-    for (int q = 0; q < kAhead; ++q) cur[q] = nxt[q];
-  }
-}
-
-// bulk calls: one block per sequence after the place kernel
-__global__ __launch_bounds__(256) void append_commit_kernel(thinkv_view v, int layer, AppendWs ws) {
-  __shared__ int s_scan[5];
-  if (blockIdx.x == 0) update_pools(v, ws, s_scan);
-  commit_sequence(v, layer, ws, blockIdx.x, s_scan);
 }
 
 int launch_append(const thinkv_view& v, int layer, const void* k_new, const void* v_new, const int32_t* tok_seq,
@@ -871,40 +917,46 @@ int launch_append(const thinkv_view& v, int layer, const void* k_new, const void
   AppendWs ws = carve(v.cfg, n_tok, workspace);
   const int S = v.cfg.max_seqs;
   hipLaunchKernelGGL(append_plan_kernel, dim3(S), dim3(256), 0, st, v, layer, tok_seq, tok_class, n_tok, ws, ev_seq, ev_handle, n_ev);
-  const int commit_here = n_tok <= kBulkFrom;   // else thousands of blocks would bump one sequence's counter
+  const bool small = n_tok <= kBulkFrom;
   const bool aligned = (((uintptr_t)k_new | (uintptr_t)v_new) & 15) == 0;
-  if (!commit_here && aligned) {
-    hipLaunchKernelGGL(append_grant_kernel, dim3(1), dim3(256), 0, st, v, ws);
+  if (!small && aligned) {
     // enough blocks to fill the chip: a mid-sized call spreads the kv-heads of its token groups over blocks
     const int H = v.cfg.n_kv_heads, groups = (n_tok + kBulkTokens - 1) / kBulkTokens;
+    // (every block of a group settles its places again, so a large call gives each as many heads as it has waves: one head
+    // each took 124 us where four took 94, and eight 97: too few blocks to even out)
     int hpb = (int)(((int64_t)H * groups + 4095) / 4096);
+    if (hpb > 2) hpb = 4;
     hpb = hpb < 1 ? 1 : (hpb > H ? H : hpb);
     const dim3 grid(groups, (H + hpb - 1) / hpb);
-    const bool f32 = in_dtype == THINKV_F32;
-#define THINKV_BULK(DD, FF)                                                                                                   \
-  hipLaunchKernelGGL((append_place_bulk_kernel<DD, FF>), grid, dim3(256), 0, st, v, layer, k_new, v_new, tok_seq, tok_pos, \
-                     tok_class, tok_handle, n_tok, in_dtype, ws, hpb)
+    const bool fp = v.cfg.format == THINKV_FMT_FP;
+#define THINKV_BULK(DD, II, FF)                                                                                                   \
+  hipLaunchKernelGGL((append_place_bulk_kernel<DD, II, FF>), grid, dim3(256), 0, st, v, layer, k_new, v_new, tok_seq, tok_pos, \
+                     tok_class, tok_handle, n_tok, ws, hpb)
+#define THINKV_BULK_IN(DD, FF)                                         \
+  if (in_dtype == THINKV_F32) THINKV_BULK(DD, THINKV_F32, FF);         \
+  else if (in_dtype == THINKV_F16) THINKV_BULK(DD, THINKV_F16, FF);    \
+  else THINKV_BULK(DD, THINKV_BF16, FF)
     if (v.cfg.head_dim == 128) {
-      if (f32) THINKV_BULK(128, true); else THINKV_BULK(128, false);
+      if (fp) { THINKV_BULK_IN(128, true); } else { THINKV_BULK_IN(128, false); }
     } else {
-      if (f32) THINKV_BULK(64, true); else THINKV_BULK(64, false);
+      if (fp) { THINKV_BULK_IN(64, true); } else { THINKV_BULK_IN(64, false); }
     }
+#undef THINKV_BULK_IN
 #undef THINKV_BULK
   } else {
     // A decode-style call (few tokens) spreads the kv-heads of a token over several workgroups so
     // that their load-quantise-store chains run side by side; a bulk call whose rows are not
     // 16-byte aligned keeps one workgroup per token.
     const int H = v.cfg.n_kv_heads, hp = v.cfg.head_dim == 128 ? 1 : 2;
-    const int hpb = commit_here ? hp : ((H + hp - 1) / hp) * hp;
+    const int hpb = small ? hp : ((H + hp - 1) / hp) * hp;
     const dim3 grid(n_tok, (H + hpb - 1) / hpb);
     if (v.cfg.head_dim == 128)
       hipLaunchKernelGGL(append_place_kernel<128>, grid, dim3(256), 0, st, v, layer, k_new, v_new, tok_seq, tok_pos,
-                         tok_class, tok_handle, n_tok, in_dtype, ws, hpb, commit_here);
+                         tok_class, tok_handle, n_tok, in_dtype, ws, hpb);
     else
       hipLaunchKernelGGL(append_place_kernel<64>, grid, dim3(256), 0, st, v, layer, k_new, v_new, tok_seq, tok_pos,
-                         tok_class, tok_handle, n_tok, in_dtype, ws, hpb, commit_here);
+                         tok_class, tok_handle, n_tok, in_dtype, ws, hpb);
   }
-  if (!commit_here) hipLaunchKernelGGL(append_commit_kernel, dim3(S), dim3(256), 0, st, v, layer, ws);
   return hipGetLastError() == hipSuccess ? THINKV_OK : THINKV_E_HIP;
 }
 

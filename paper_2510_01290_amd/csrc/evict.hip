@@ -17,6 +17,10 @@ __global__ __launch_bounds__(256) void evict_kernel(thinkv_view v, int layer, co
   evict_one(v, layer, s, ev_handle[i]);
 }
 
+// Tables, counters and arenas as an empty cache has them.  The arenas are zero-filled, in 16-byte stores (page sizes are
+// multiples of 16 bytes): a page can hold slots that were never written; attention reads them and discards them by their
+// live bit, which is only safe if their scales and zero-points are finite numbers.  (One launch instead of one for the
+// tables and one an arena, each of which starts on an idle chip: 60 MB of arenas in 14 us instead of 26.)
 __global__ __launch_bounds__(256) void init_kernel(thinkv_view v) {
   const thinkv_config& c = v.cfg;
   const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -42,6 +46,11 @@ __global__ __launch_bounds__(256) void init_kernel(thinkv_view v) {
   for (int64_t i = tid; i < nsl + 1; i += stride) v.dev_status[i] = 0;
   for (int64_t i = tid; i < c.max_seqs; i += stride) v.append_counters[i] = 0;
   for (int64_t i = tid; i < nsl * c.n_kv_heads * 4; i += stride) v.work_counters[i] = 0;
+  for (int k = 0; k < 3; ++k) {
+    const int64_t n16 = v.arena_pages[k] * (int64_t)c.n_kv_heads * block_geom(c.bits_of_class[k], c.head_dim, c.format).block_bytes / 16;
+    uint4* const p = (uint4*)v.arena[k];
+    for (int64_t i = tid; i < n16; i += stride) p[i] = uint4{0u, 0u, 0u, 0u};
+  }
 }
 
 int launch_evict(const thinkv_view& v, int layer, const int32_t* ev_seq, const int32_t* ev_handle, int n_ev, hipStream_t st) {
@@ -50,20 +59,8 @@ int launch_evict(const thinkv_view& v, int layer, const int32_t* ev_seq, const i
   return hipGetLastError() == hipSuccess ? THINKV_OK : THINKV_E_HIP;
 }
 
-// Zero-fill of an arena in 16-byte stores (page sizes are multiples of 16 bytes).  A page can
-// hold slots that were never written; attention reads them and discards them by their live
-// bit, which is only safe if their scales and zero-points are finite numbers.
-__global__ __launch_bounds__(256) void arena_clear_kernel(uint4* p, int64_t n16) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n16; i += stride) p[i] = uint4{0u, 0u, 0u, 0u};
-}
-
 int launch_init(const thinkv_view& v, hipStream_t st) {
-  hipLaunchKernelGGL(init_kernel, dim3(1024), dim3(256), 0, st, v);
-  for (int k = 0; k < 3; ++k) {
-    const int64_t n16 = v.arena_pages[k] * (int64_t)v.cfg.n_kv_heads * block_geom(v.cfg.bits_of_class[k], v.cfg.head_dim, v.cfg.format).block_bytes / 16;
-    if (n16 > 0) hipLaunchKernelGGL(arena_clear_kernel, dim3(2048), dim3(256), 0, st, (uint4*)v.arena[k], n16);
-  }
+  hipLaunchKernelGGL(init_kernel, dim3(2048), dim3(256), 0, st, v);
   return hipGetLastError() == hipSuccess ? THINKV_OK : THINKV_E_HIP;
 }
 

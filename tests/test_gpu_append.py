@@ -1,0 +1,70 @@
+"""Appends at the edges of their plan and of the bulk place kernel: calls around the size from which they are placed in bulk, one
+to five thousand tokens a sequence (one and several ranking windows), page lists longer than the masks a thread keeps, reclaimable
+slots taken across windows, new pages that stay partly empty, groups whose zero-point or scale leaves binary16's range.
+Tables and bytes equal the oracle's."""
+import numpy as np
+import pytest
+import torch
+
+import parity
+from paper_2510_01290_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("D,dtype,fmt,calls,classes", [
+    (64, torch.bfloat16, "int", [[1, 63], [0, 65]], 3),                    # 64 tokens: small; 65: bulk
+    (128, torch.float16, "int", [[256, 257, 1], [4096, 15, 4097]], 3),     # a window and one token more
+    (128, torch.bfloat16, "fp", [[33, 200], [170, 16]], 3),
+    (64, torch.float32, "fp", [[90, 31], [16, 64]], 2),
+    (64, torch.bfloat16, "int", [[17000, 5], [6000, 700]], 1),             # lists of more than 1,024 pages
+])
+def test_bulk_plan_and_new_pages(D, dtype, fmt, calls, classes):
+    print(f"[gpu] append D={D} {dtype} {fmt} {calls}", flush=True)
+    H = 1 if calls[0][0] > 4096 else 3
+    S = len(calls[0])
+    rng = np.random.default_rng(D + S + classes)
+    geom = synth.Geometry(1, 2 * H, H, D, "f16", (8, 4, 2), fmt=fmt) if fmt == "fp" else synth.Geometry(1, 2 * H, H, D, "f16", (8, 4, 2))
+    cls = [[rng.integers(0, classes, n).astype(np.uint8) for n in call] for call in calls]
+    wl = synth.Workload("append-edges", geom, 0, S, [np.concatenate([c[s] for c in cls]) for s in range(S)], [])
+    gc, ob = parity.make_gpu_cache(wl), parity.make_oracle(wl)
+    gb = parity.GpuBackend(gc)
+    base = np.zeros(S, np.int32)
+    for ci, call in enumerate(calls):
+        n = sum(call)
+        ts = np.repeat(np.arange(S, dtype=np.int32), call)
+        tp = np.concatenate([base[s] + np.arange(call[s]) for s in range(S)]).astype(np.int32)
+        gen = torch.Generator().manual_seed(ci)
+        k, v = [(torch.randn((n, H, D), generator=gen) * 3).to(dtype) for _ in range(2)]
+        hg = gb.append(0, k.cuda(), v.cuda(), ts, tp, np.concatenate(cls[ci]))
+        ho = ob.append(0, k, v, ts, tp, np.concatenate(cls[ci]))
+        assert np.array_equal(hg, ho), ci
+        parity.compare_bookkeeping_full(ob.cache, gc)
+        base += np.asarray(call, np.int32)
+        pick = rng.random(n) < 0.4
+        gb.evict(0, ts[pick], hg[pick])
+        ob.evict(0, ts[pick], ho[pick])
+    parity.compare_bookkeeping_full(ob.cache, gc)
+    parity.compare_sequences(ob.cache, gc, [(s, s, 0) for s in range(S)], check_bytes=True)
+
+
+@pytest.mark.parametrize("n_tok", [40, 100])
+def test_groups_out_of_binary16_range(n_tok):
+    """zero-points that overflow to -inf and +inf next to a finite scale, ranges whose scale overflows, equal values, tiny ranges: both
+    kernels give what the division gives"""
+    print(f"[gpu] groups out of range, {n_tok} tokens", flush=True)
+    geom = synth.Geometry(1, 2, 1, 64, "f16", (8, 4, 2))
+    cls = (np.arange(n_tok) % 3).astype(np.uint8)
+    wl = synth.Workload("append-range", geom, 0, 1, [cls], [])
+    gc, ob = parity.make_gpu_cache(wl), parity.make_oracle(wl)
+    rng = np.random.default_rng(5)
+    lo = np.array([-7e4, 7e4, -3e38, 2.5, -1e-7, 0.0, -65504.0, 1e-40, 65519.0, -65520.0], np.float32)
+    span = np.array([100.0, 90.0, 6e37, 0.0, 2e-7, 1e-39, 131008.0, 1e-41, 1.0, 3.0], np.float32)
+    pick = rng.integers(0, len(lo), (2, n_tok, 1, 2, 1))
+    x = (lo[pick] + span[pick] * rng.random((2, n_tok, 1, 2, 32), dtype=np.float32)).astype(np.float32).reshape(2, n_tok, 1, 64)
+    k, v = torch.from_numpy(x[0].copy()), torch.from_numpy(x[1].copy())
+    ts, tp = np.zeros(n_tok, np.int32), np.arange(n_tok, dtype=np.int32)
+    hg = parity.GpuBackend(gc).append(0, k.cuda(), v.cuda(), ts, tp, cls)
+    assert np.array_equal(hg, ob.append(0, k, v, ts, tp, cls))
+    parity.compare_bookkeeping_full(ob.cache, gc)
+    parity.compare_sequences(ob.cache, gc, [(0, 0, 0)], check_bytes=True)
