@@ -5,10 +5,12 @@
 // the row's maximum, and the fractions of negligible entries are averaged over the groups).
 //
 // The scores are those the attention kernel computes anyway, so the statistic rides on a decode
-// call: the STAT instantiation of the attention kernel stores the pooled score of every slot it
-// visits (16 floats per page, log2 domain), after a fill kernel has set the buffer to -inf (dead
-// and invisible slots, pages skipped because nothing in them is live), and two small kernels take
-// the maximum of each (query, kv-head) row, count, and average over the kv-heads.  w_j < 0.01 max w  <=>  pooled_j <
+// call: the STAT instantiation of the attention kernel stores the pooled score of every slot of the pages it
+// visits (16 floats per page, log2 domain, -inf for dead and invisible slots), and two small kernels take
+// the maximum of each (query, kv-head) row, count, and average over the kv-heads.  Full attention visits the pages with
+// a live slot, which the counts tell by the masks; a sliding window visits what it reaches, so there a fill kernel sets the
+// buffer to -inf first.  (16 queries over 8k to 32k tokens: 131.4 us with the
+// fill and rows read twice, 127 so.)  w_j < 0.01 max w  <=>  pooled_j <
 // max pooled - log2(100) in the log2 domain, so no softmax is ever formed.
 #include "decode_mfma_kernel.h"
 
@@ -22,7 +24,10 @@ __global__ __launch_bounds__(256) void stat_fill_kernel(float4* p, int64_t n4) {
 
 // One workgroup per (query, kv-head): the row maximum, then the counts of visible and of
 // negligible entries; the row's fraction negligible / visible (0 where nothing is visible) goes
-// to frac[b][kv-head].  Rows are read 16 bytes a lane; the second pass finds them in L2.
+// to frac[b][kv-head].  Rows are read 16 bytes a lane, once up to 32,768 entries.  MASKS: entries of pages without a live
+// slot were not written and count as -inf.
+constexpr int kKept = 8;
+template <bool MASKS>
 __global__ __launch_bounds__(1024) void stat_count_kernel(thinkv_view v, DecodeArgs a, float* frac) {
   const thinkv_config& c = v.cfg;
   const int hkv = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -30,17 +35,36 @@ __global__ __launch_bounds__(1024) void stat_count_kernel(thinkv_view v, DecodeA
   __shared__ int s_cnt[2][16];
   const int seq = a.seq_ids[b];
   int64_t n = 0;
-  if (seq >= 0 && seq < c.max_seqs)
-    for (int k = 0; k < 3; ++k) n += v.n_pages[npages_index(c, seq, a.layer, k)];
+  int end0 = 0, end1 = 0;   // where the pages of the first two types end
+  if (seq >= 0 && seq < c.max_seqs) {
+    end0 = v.n_pages[npages_index(c, seq, a.layer, 0)];
+    end1 = end0 + v.n_pages[npages_index(c, seq, a.layer, 1)];
+    n = (int64_t)end1 + v.n_pages[npages_index(c, seq, a.layer, 2)];
+  }
   n *= kPage;
   if (n > a.stat_stride) n = a.stat_stride;   // the host's bound on the context was too small: count what was kept
   const float4* row = (const float4*)(a.stat + ((int64_t)b * c.n_kv_heads + hkv) * a.stat_stride);
   const int n4 = (int)(n / 4);                // whole pages: a multiple of four
+  const uint32_t* const masks = n4 > 0 ? v.slot_mask + table_base(c, seq, a.layer, 0) : nullptr;
+  auto entry = [&](int i) {
+    float4 x = row[i];
+    if (MASKS && n4 > 0) {
+      const int p = i >> 2;   // the types' page lists lie max_pages apart
+      const uint32_t m = masks[p < end0 ? p : (p < end1 ? p - end0 + c.max_pages : p - end1 + 2 * (int64_t)c.max_pages)];
+      if ((m & 0xFFFFu) == 0) x = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+    }
+    return x;
+  };
+  // the first 32,768 entries stay in registers between the passes, all their loads under way at once
+  float4 kept[kKept];
+#pragma unroll
+  for (int u = 0; u < kKept; ++u) kept[u] = entry(min(tid + 1024 * u, max(n4 - 1, 0)));
   float m = -INFINITY;
-  for (int i = tid; i < n4; i += 1024) {
-    const float4 x = row[i];
-    m = fmaxf(fmaxf(m, fmaxf(x.x, x.y)), fmaxf(x.z, x.w));
-  }
+  auto highest = [&](float4 x) { m = fmaxf(fmaxf(m, fmaxf(x.x, x.y)), fmaxf(x.z, x.w)); };
+#pragma unroll
+  for (int u = 0; u < kKept; ++u)
+    if (tid + 1024 * u < n4) highest(kept[u]);
+  for (int i = tid + 1024 * kKept; i < n4; i += 1024) highest(entry(i));
   for (int d = 32; d >= 1; d >>= 1) m = fmaxf(m, __shfl_xor(m, d, 64));
   if (lane == 0) s_max[wave] = m;
   __syncthreads();
@@ -48,12 +72,15 @@ __global__ __launch_bounds__(1024) void stat_count_kernel(thinkv_view v, DecodeA
   for (int w = 1; w < 16; ++w) m = fmaxf(m, s_max[w]);
   const float cut = m - 6.643856189774724f;   // log2(100)
   int vis = 0, neg = 0;
-  for (int i = tid; i < n4; i += 1024) {
-    const float4 x = row[i];
+  auto count = [&](float4 x) {
     vis += (x.x > -INFINITY) + (x.y > -INFINITY) + (x.z > -INFINITY) + (x.w > -INFINITY);
     neg += (x.x > -INFINITY && x.x < cut) + (x.y > -INFINITY && x.y < cut) + (x.z > -INFINITY && x.z < cut) +
            (x.w > -INFINITY && x.w < cut);
-  }
+  };
+#pragma unroll
+  for (int u = 0; u < kKept; ++u)
+    if (tid + 1024 * u < n4) count(kept[u]);
+  for (int i = tid + 1024 * kKept; i < n4; i += 1024) count(entry(i));
   for (int d = 32; d >= 1; d >>= 1) {
     vis += __shfl_xor(vis, d, 64);
     neg += __shfl_xor(neg, d, 64);
@@ -83,6 +110,7 @@ __global__ __launch_bounds__(256) void stat_mean_kernel(const float* frac, float
 }
 
 int launch_stat_fill(const thinkv_view& v, const DecodeArgs& a, hipStream_t st) {
+  if (a.window <= 0) return THINKV_OK;   // the counts go by the masks
   const int64_t n4 = (int64_t)a.B * v.cfg.n_kv_heads * a.stat_stride / 4;
   int64_t blocks = (n4 + 255) / 256;
   if (blocks > 4096) blocks = 4096;
@@ -95,7 +123,8 @@ int launch_decode_mfma_stat(const thinkv_view& v, const DecodeArgs& a, hipStream
 int launch_stat_count(const thinkv_view& v, const DecodeArgs& a, hipStream_t st) {
   // the per-row fractions live behind the pooled scores
   float* frac = a.stat + (int64_t)a.B * v.cfg.n_kv_heads * a.stat_stride;
-  hipLaunchKernelGGL(stat_count_kernel, dim3(v.cfg.n_kv_heads, a.B), dim3(1024), 0, st, v, a, frac);
+  if (a.window > 0) hipLaunchKernelGGL(stat_count_kernel<false>, dim3(v.cfg.n_kv_heads, a.B), dim3(1024), 0, st, v, a, frac);
+  else hipLaunchKernelGGL(stat_count_kernel<true>, dim3(v.cfg.n_kv_heads, a.B), dim3(1024), 0, st, v, a, frac);
   hipLaunchKernelGGL(stat_mean_kernel, dim3((a.B + 255) / 256), dim3(256), 0, st, frac, a.sparsity, a.B, v.cfg.n_kv_heads);
   return hipGetLastError() == hipSuccess ? THINKV_OK : THINKV_E_HIP;
 }

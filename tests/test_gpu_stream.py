@@ -113,3 +113,29 @@ def test_window_kernel_against_the_plain_kernel(D, G, H, ctx, fmt, window, dead)
     assert float((o - ro).abs().max()) <= 1e-4 * max(1.0, float(ro.abs().max()))
     fin = torch.isfinite(rl)
     assert torch.equal(torch.isfinite(l), fin) and float((l[fin] - rl[fin]).abs().max()) <= 1e-4
+
+
+@pytest.mark.parametrize("D,G,ctx,fmt,dead,bound", [
+    (128, 4, [3000, 17, 1], 0, 0.6, None), (64, 8, [5000, 300], 0, 0.6, 100), (128, 2, [900], 1, 0.6, None), (64, 4, [200, 40], 0, 1.0, None)])
+def test_sparsity_of_pages_with_nothing_live(D, G, ctx, fmt, dead, bound):
+    """full attention counts by the masks: what the workspace held before does not matter, and a window over everything (which
+    clears the scores first) gives the same"""
+    print("sparsity with dead pages:", D, G, ctx, fmt, dead, bound, flush=True)
+    c, q = _cache(D, G, 3, ctx, fmt, (8, 2, 4), 5 + D, dead=dead)
+    S, Hq = q.shape[:2]
+    ids = torch.arange(S, dtype=torch.int32, device="cuda:0")
+    qp = torch.full((S,), 1 << 20, dtype=torch.int32, device="cuda:0")
+    pages = int(c.n_pages[:, 0].sum(-1).max()) if bound is None else bound
+    need = B.load().thinkv_decode_sparsity_workspace_bytes(B.C.byref(c.cfg), S, pages)
+    got = []
+    for junk, window in ((float("nan"), 0), (3e38, 0), (0.0, 1 << 21)):
+        ws = torch.full((need // 4,), junk, dtype=torch.float32, device="cuda:0")
+        out, sp = torch.empty((S, Hq, D), dtype=torch.float32, device="cuda:0"), torch.empty(S, dtype=torch.float32, device="cuda:0")
+        rc = B.load().thinkv_decode_attention_sparsity(B.C.byref(c.view), 0, B._ptr(q), B._ptr(out), B._ptr(None), B._ptr(sp), B._ptr(ids), B._ptr(qp), S,
+                                                       window, D ** -0.5, B.BF16, B.F32, pages, B._ptr(ws), need, B._stream(None))
+        torch.cuda.synchronize()
+        assert rc == 0
+        got.append(sp.cpu())
+    assert torch.equal(got[0], got[1])
+    # the two attention kernels round scores alike up to the order of a few additions: one entry in a thousand may change sides
+    assert float((got[0] - got[2]).abs().max()) <= 1e-3
