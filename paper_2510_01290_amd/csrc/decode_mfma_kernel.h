@@ -22,7 +22,7 @@
 // its token and nothing twice: the softmax runs on 16 tokens x G heads per page, spread over the wave.
 // (The other orientation, A = codes, leaves every slice of columns with the complete scores of four tokens:
 // the exponentials, which the vector unit issues at a quarter of its rate, and everything around them were
-// then done CS times over: 292 vector and matrix instructions per page pair, 221 now.)
+// then done CS times over: 292 vector-ALU instructions per page pair and wave, 238 now.)
 // The weights go back to the layout of the value product (four tokens per lane, column = (slice, head)) by one
 // v_mfma_f32_16x16x4_f32 per page and four heads with a 0/1 matrix: products with one and zero, so exact.
 // Values: p * s_V(t, g) is lane-local (each slice multiplies by its own group's
