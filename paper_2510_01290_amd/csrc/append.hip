@@ -13,7 +13,7 @@
 //   plan   (block per sequence)  everything that concerns the sequence alone: token ranks per type, a place for every
 //                                token, the masks, fill counts and the live count that follow from places in
 //                                existing pages, and the new pages wanted
-//   place  (block per token and share of its kv-heads, or per 32 tokens)  quantisation, packing, slot_pos,
+//   place  (block per token and share of its kv-heads, or per sixteen tokens)  quantisation, packing, slot_pos,
 //                                handle.  Which page a new one is depends on the sequences before: it is worked out
 //                                here, and the token that takes the page's first slot enters it into the tables.
 // The place blocks read what the plan left in the workspace and the pools as the plan found them, never the tables
@@ -674,8 +674,8 @@ __global__ __launch_bounds__(256) void append_place_kernel(thinkv_view v, int la
 }
 
 // ---------------------------------------------------------------------------------------------
-// Bulk calls (prefill-style: thousands of tokens).  A block takes 32 consecutive tokens of the call and settles their
-// places side by side, eight lanes a token.  The unit of work behind that is the K or the V rows of sixteen tokens and one
+// Bulk calls (prefill-style: thousands of tokens).  A block takes sixteen consecutive tokens of the call and settles their
+// places side by side, sixteen lanes a token.  The unit of work behind that is the K or the V rows of sixteen tokens and one
 // kv-head, by one wave: eight channels a lane (one 16-byte load), codes in registers, V codes transposed through LDS (a V
 // chunk holds channels 16 apart).
 // New pages are written whole: the token in a new page's first slot brings the page to its block, the others are the next
