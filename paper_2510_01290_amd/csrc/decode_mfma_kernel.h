@@ -24,7 +24,8 @@
 // the exponentials, which the vector unit issues at a quarter of its rate, and everything around them were
 // then done CS times over: 292 vector-ALU instructions per page pair and wave, 238 now.)
 // The weights go back to the layout of the value product (four tokens per lane, column = (slice, head)) by one
-// v_mfma_f32_16x16x4_f32 per page and four heads with a 0/1 matrix: products with one and zero, so exact.
+// v_mfma_f32_16x16x4_f32 per page and four heads with a 0/1 matrix: products with one and zero, so exact for numbers (a
+// weight that is not one, from a query head that is not finite, must not reach the sum: it would spoil the other heads).
 // Values: p * s_V(t, g) is lane-local (each slice multiplies by its own group's
 // scale), is split once into two binary16 terms (22 significant bits), and the same B operand
 // pair serves the PV MFMAs of every group of the set: the tile of a 16-channel block is only
@@ -567,8 +568,10 @@ struct Softmax {
       const float mref = st.m_sub[i] - lift;
       ea[i] = __builtin_amdgcn_exp2f(fmaf(sa[i], kappa, -mref));
       eb[i] = __builtin_amdgcn_exp2f(fmaf(sb[i], kappa, -mref));
-      ta = __builtin_amdgcn_mfma_f32_16x16x4f32(ea[i], sel[i], ta, 0, 0, 0);
-      tb = __builtin_amdgcn_mfma_f32_16x16x4f32(eb[i], sel[i], tb, 0, 0, 0);
+      // (the product adds four heads, and 0 times what is not a number is not one: such a weight goes in as 0, and spoils
+      // its own head through the denominator, which adds ea and eb as they are.  Weights are never infinite.)
+      ta = __builtin_amdgcn_mfma_f32_16x16x4f32(fmaxf(ea[i], 0.f), sel[i], ta, 0, 0, 0);
+      tb = __builtin_amdgcn_mfma_f32_16x16x4f32(fmaxf(eb[i], 0.f), sel[i], tb, 0, 0, 0);
     }
 #pragma unroll
     for (int r = 0; r < 4; ++r) {

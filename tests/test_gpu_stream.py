@@ -139,3 +139,23 @@ def test_sparsity_of_pages_with_nothing_live(D, G, ctx, fmt, dead, bound):
     assert torch.equal(got[0], got[1])
     # the two attention kernels round scores alike up to the order of a few additions: one entry in a thousand may change sides
     assert float((got[0] - got[2]).abs().max()) <= 1e-3
+
+
+@pytest.mark.parametrize("D,G,fmt,window", [(128, 4, 0, 0), (128, 8, 0, 0), (64, 8, 0, 0), (64, 3, 1, 0), (128, 8, 1, 0),
+                                            (128, 4, 0, 200), (64, 8, 1, 200)])
+def test_a_query_head_that_is_not_finite_stays_alone(D, G, fmt, window):
+    """one head of a group holds a NaN, an infinity, or a bf16 number above binary16's range: the heads that share its kv-head
+    get what the plain kernel gives them, and the head itself the result of a denominator that is not a number"""
+    print("stream, one head not finite:", D, G, fmt, window, flush=True)
+    ctx = [900, 700, 300]
+    c, q = _cache(D, G, 2, ctx, fmt, (8, 2, 4), 31 + D + G, dead=0.1)
+    bad = torch.zeros((len(ctx), 2 * G), dtype=torch.bool)
+    for s, x in enumerate((float("nan"), float("inf"), 1e5)):
+        head = (s + 1) % G
+        q[s, head, 5 + s] = x
+        bad[s, head] = True
+    (o, l), (ro, rl) = _both(c, q, D, window=window, q_pos=[x - 1 for x in ctx])
+    assert bool(torch.isfinite(ro[~bad]).all()) and bool(torch.isfinite(rl[~bad]).all())
+    assert float((o - ro)[~bad].abs().max()) <= 1e-4 * max(1.0, float(ro[~bad].abs().max()))
+    assert float((l - rl)[~bad].abs().max()) <= 1e-4
+    assert bool((o[bad] == 0).all()) and bool((l[bad] == -float("inf")).all())
