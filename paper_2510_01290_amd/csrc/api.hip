@@ -123,33 +123,39 @@ static int64_t rows_bound(const thinkv_config& c, int B, int max_ctx_pages) {
   return most;
 }
 
-// Full-attention layers of the fast kernel: an item is a workgroup of W waves.  Where there are at most as many heads as
-// compute units, a workgroup is a compute unit's worth of waves (fewer on short contexts: a wave is worth at least a
-// chunk of pages), and a head has as many as fill the machine once.  Where there are more, workgroups of four, several to a
-// compute unit, so that one's start and end are covered by the others', and an item per so many pages: about sixteen
-// rounds of them if every sequence were as long as the host's bound, but no fewer than 64 pages a wave.
-static ItemSizing size_stream(const thinkv_config& c, int B, int max_ctx_pages, int* waves) {
-  const int64_t heads = (int64_t)B * c.n_kv_heads;
-  const int64_t full = 4 * decode_waves_per_simd(c.head_dim, c.format == THINKV_FMT_FP), resident = (int64_t)compute_units() * full;
+// Full-attention layers of the fast kernel: workgroups of *waves waves.
+// Dealt (*grid > 0, deal_item): a workgroup per compute unit, of all the waves it holds, and every item at once; the device sizes
+// them by what the sequences hold.  Up to two heads a compute unit; with more, one item a head fills the machine.
+// A head to a workgroup, which writes the result itself, where an item would be worth less than the
+// merge launch: contexts of up to 16 pages a wave, 24 if every other compute unit has a head, and 80 with about as many
+// heads as compute units.
+// More heads: workgroups of four, several to a compute unit, so that one's start and end are covered by the others', and an
+// item per so many pages: about sixteen rounds of them if every sequence were as long as the host's bound, but no
+// fewer than 64 pages a wave.
+static ItemSizing size_stream(const thinkv_config& c, int B, int max_ctx_pages, int* waves, int* grid) {
+  const int64_t heads = (int64_t)B * c.n_kv_heads, cus = compute_units();
+  const int64_t full = 4 * decode_waves_per_simd(c.head_dim, c.format == THINKV_FMT_FP);
   const int64_t pages = max_ctx_pages > 0 ? max_ctx_pages : 1;
-  const int64_t most = (pages + 7) / 8;
-  int64_t W, per_head, cap;
-  if (heads <= compute_units()) {
-    W = most < full ? most : full;
-    per_head = resident / (heads * W);
-    cap = (pages + 16 * W - 1) / (16 * W);
-  } else {
-    W = most < 4 ? most : 4;
-    per_head = (16 * resident + heads * W - 1) / (heads * W);
-    cap = (pages + 64 * W - 1) / (64 * W);
+  const int64_t most = (pages + 7) / 8, bound = rows_bound(c, B, max_ctx_pages);   // rows: what the workspace is sized for
+  const bool few = heads <= cus;
+  const bool single = few ? pages <= (10 * heads >= 9 * cus ? 80 : (2 * heads > cus ? 24 : 16)) * full : pages <= 256;
+  ItemSizing z;
+  *grid = 0;
+  if (heads <= 2 * cus && B <= kDealSeqs && !single) {
+    const int64_t wanted = heads * ((pages + kDealPages * full - 1) / (kDealPages * full));
+    *waves = (int)full;
+    *grid = (int)(wanted < cus ? wanted : cus);
+    z.n_rows = (int)(*grid * full < bound ? *grid * full : bound);
+    z.per_head = z.ppi = 1;   // (not used)
+    return z;
   }
+  const int64_t W = few ? (most < full ? most : full) : (most < 4 ? most : 4);
+  int64_t per_head = few ? 1 : (16 * cus * full + heads * W - 1) / (heads * W);
+  const int64_t cap = (pages + 64 * W - 1) / (64 * W), room = bound / heads;   // (room is at least 1)
   if (per_head > cap) per_head = cap;
-  const int64_t room = rows_bound(c, B, max_ctx_pages) / heads;   // what the workspace is sized for (at least 1)
   if (per_head > room) per_head = room;
   if (per_head > kMaxRowsPerHead) per_head = kMaxRowsPerHead;
-  if (per_head < 1) per_head = 1;
   *waves = (int)W;
-  ItemSizing z;
   z.per_head = (int)per_head;
   z.n_rows = (int)(per_head * heads);
   z.ppi = (int)((pages + per_head - 1) / per_head);
@@ -215,9 +221,9 @@ static int decode_common(const thinkv_view* view, int32_t layer, const void* q, 
   a.window = window;
   a.q_dtype = q_dtype;
   a.out_dtype = out_dtype;
-  a.waves = 0;
+  a.waves = a.grid = 0;
   const ItemSizing z = !fast ? size_items(view->cfg, B, max_ctx_pages, window, false)
-                             : (window > 0 ? size_window(view->cfg, B, max_ctx_pages, window, &a.waves) : size_stream(view->cfg, B, max_ctx_pages, &a.waves));
+                             : (window > 0 ? size_window(view->cfg, B, max_ctx_pages, window, &a.waves) : size_stream(view->cfg, B, max_ctx_pages, &a.waves, &a.grid));
   if (z.n_rows > rows_bound(view->cfg, B, max_ctx_pages)) return THINKV_E_WORKSPACE;   // cannot happen: a launch never has more rows than the workspace
   a.n_rows = z.n_rows;
   a.per_head = z.per_head;
@@ -228,7 +234,7 @@ static int decode_common(const thinkv_view* view, int32_t layer, const void* q, 
   a.stat = nullptr;
   a.stat_stride = 0;
   a.sparsity = sparsity;
-  a.direct = fast && !sparsity && a.per_head == 1;   // short contexts or huge batches: one item per head, no merge launch
+  a.direct = fast && !sparsity && !a.grid && a.per_head == 1;   // short contexts or huge batches: one item per head, no merge launch
   hipStream_t st = (hipStream_t)stream;
   if (sparsity) {
     // pooled scores behind the partials (whose size is a multiple of 16 bytes)

@@ -5,10 +5,10 @@
 // the unnormalised weighted value sum, the running maximum of the scaled scores in the log2
 // domain, and the sum of 2^(score - m).  The merge kernel folds the rows of a head.
 //
-// How many items a head gets is decided on the device from its page count, identically by every
-// kernel of a call: an item per `ppi` pages, at most `per_head` (both chosen by the host); the items
-// of a head that is short do not exist (their waves leave at once).  Item j of n takes the same fraction
-// [j/n, (j+1)/n) of each of the three per-type lists.
+// How many items a head gets is decided on the device from page counts, identically by every workgroup of a launch.  Either
+// (locate_item) from its own: an item per `ppi` pages, at most `per_head` (both chosen by the host); the items
+// of a head that is short do not exist (their waves leave at once).  Or (deal_item) from those of the whole batch, so that the
+// items fill the machine once.  Item j of n takes the same fraction [j/n, (j+1)/n) of each of the three per-type lists.
 #pragma once
 #include "common.h"
 
@@ -26,6 +26,9 @@ __host__ __device__ constexpr int stream_ring_bytes(int head_dim, bool fp) { ret
 constexpr int kWindowWaves = 8, kWindowBlock = 64 * kWindowWaves;
 __host__ __device__ constexpr int window_ring_bytes(int head_dim) { return head_dim == 128 ? 14336 : 9216; }
 __host__ __device__ constexpr int window_lds_bytes(int head_dim) { return kWindowWaves * window_ring_bytes(head_dim) + 9 * kWindowBlock * 4 + 3 * kWindowWaves * 4; }
+
+// Items dealt over a batch (deal_item): fewest pages a wave is worth, one chunk of its ticket counter.
+constexpr int kDealPages = 8;
 
 namespace thinkv {
 
@@ -47,7 +50,8 @@ struct DecodeArgs {
   int64_t stat_stride;  // floats per (query, kv-head): 16 * max_ctx_pages
   float* sparsity;      // [B]
   int direct;           // 1: every head has a single item and the attention kernel writes out / lse itself
-  int waves;            // fast kernel: waves of an item's workgroup (full attention), kv-heads of one (sliding window)
+  int waves;            // fast kernel: waves of a workgroup (full attention), kv-heads of one (sliding window)
+  int grid;             // full attention, items dealt by the batch's page counts: workgroups; 0: locate_item
 };
 
 constexpr int kMaxRowsPerHead = 1024;
@@ -91,6 +95,119 @@ __device__ inline ItemLoc locate_item(const thinkv_view& v, const DecodeArgs& a,
   it.n = n;
   it.row0 = rest * a.per_head;
   return it;
+}
+
+// inclusive scan over a wave (x not negative): by 1, 2, 4, 8 lanes inside rows of sixteen, then the rows' results onwards
+template <class T, class Op>
+__device__ __forceinline__ T wave_scan(T x, Op op) {
+#define TKV_STEP(CTRL, ROWS) x = op(x, __builtin_bit_cast(T, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, ROWS, 0xF, false)))
+  TKV_STEP(0x111, 0xF); TKV_STEP(0x112, 0xF); TKV_STEP(0x114, 0xF); TKV_STEP(0x118, 0xF); TKV_STEP(0x142, 0xA); TKV_STEP(0x143, 0xC);
+#undef TKV_STEP
+  return x;
+}
+template <class T>
+__device__ __forceinline__ T last_lane(T x) { return __builtin_bit_cast(T, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), 63)); }
+
+// Items in proportion to the pages of the batch's sequences (a.grid > 0; at most kDealSeqs queries): a.grid workgroups of kFull
+// waves, a compute unit's worth each, and every item at once.  A workgroup works on `sub` items side by side, each by
+// kFull / sub of its waves.  With sub = 1 a batch of 17 x 8 heads leaves 120 of 256 compute units idle, and so do the short
+// sequences of a batch of uneven lengths; smaller shares pack better, but each pays for a query, a row and a last
+// chunk of its own.  So: the first sub whose workgroups have at most 8 % more pages than they would with everything
+// spread evenly, or else the best one, with as many items for the longest sequence as let all items fit and, for the
+// others, an item per as many pages.  Every wave works this out for itself, a sequence per lane (under a microsecond, most of
+// it loads that it needs in any case).  Measured against items of equal size by the host's bound alone, 8 kv-heads of 128,
+// us: 17 x 32k tokens 181, now 139; 20 x 6.5k..65k 333, now 119; 28 x 3.2k..32k 171, now 101; 16 x 8k (two items a head either way) 42, now 43.
+constexpr int kDealSeqs = 256;
+struct Deal {
+  int items;      // all of them
+  int wph;        // waves of an item
+  ItemLoc it;     // this wave's item (n = 0: none)
+  int np[3];      // its sequence's pages by type
+};
+template <int kFull>
+__device__ inline Deal deal_item(const thinkv_view& v, const DecodeArgs& a, int wg, int wave) {
+  constexpr int kU = kDealSeqs / 64;
+  const thinkv_config& c = v.cfg;
+  const int H = c.n_kv_heads, lane = threadIdx.x & 63;
+  auto add = [](auto x, auto y) { return x + y; };
+  int p[kU][3], tot[kU], most = 0;   // pages of sequences lane, lane + 64, ...
+  float all = 0.f;
+#pragma unroll
+  for (int u = 0; u < kU; ++u) {
+    p[u][0] = p[u][1] = p[u][2] = 0;
+    if (64 * u < a.B) {
+      const int seq = a.seq_ids[min(64 * u + lane, a.B - 1)];
+      if (64 * u + lane < a.B && seq >= 0 && seq < c.max_seqs) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) p[u][k] = v.n_pages[npages_index(c, seq, a.layer, k)];
+      }
+    }
+    tot[u] = p[u][0] + p[u][1] + p[u][2];
+    most = max(most, tot[u]);
+    all += (float)tot[u];
+  }
+  most = last_lane(wave_scan(most, [](int x, int y) { return max(x, y); }));
+  all = last_lane(wave_scan(all, add)) * (float)H;
+  // the items of every sequence where the longest has n; their sum
+  int mine[kU];
+  auto spread = [&](int n) {
+    const float per_page = (float)n / (float)max(most, 1);
+    int sum = 0;
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      mine[u] = 64 * u + lane < a.B ? min(max((int)ceilf((float)tot[u] * per_page), 1), n) : 0;
+      sum += mine[u];
+    }
+    return last_lane(wave_scan(sum, add));
+  };
+  int sub = 1, best_sub = kFull, best_n = 1;
+  float best = INFINITY;
+  while (true) {
+    const int slots = min(a.grid * sub, a.n_rows);
+    if (slots >= a.B * H) {   // (holds for the last sub)
+      const int least = kDealPages * (kFull / sub), cap = max(min((most + least - 1) / least, kMaxRowsPerHead), 1);
+      int n = max(min((int)(1.0001f * (float)slots * (float)most / fmaxf(all, 1.f)), cap), 1);
+      int sum = spread(n);
+      for (; n > 1 && sum * H > slots; sum = spread(n)) n = max(min(n - 1, (int)((float)n * (float)slots / (float)(sum * H))), 1);
+      const float busiest = (float)most * (float)sub / (float)n;
+      if (busiest < 0.95f * best) {
+        best = busiest;
+        best_sub = sub;
+        best_n = n;
+      }
+      // (n == cap: nothing to gain by smaller shares)
+      if (best * (float)a.grid <= (sub == 1 && sum == n * a.B ? 1.3f : 1.08f) * all || n == cap) break;
+    }
+    if (sub == kFull) break;
+    sub = kFull % (2 * sub) == 0 ? 2 * sub : kFull;
+  }
+  sub = uniform(best_sub);
+  const int sum = spread(uniform(best_n));
+  Deal d;
+  d.items = sum * H;
+  d.wph = uniform(kFull / sub);
+  d.it = ItemLoc{0, 0, 0, 0, 0};
+  d.np[0] = d.np[1] = d.np[2] = 0;
+  const int id = uniform(wave / d.wph) * a.grid + wg;   // neighbouring items on different compute units
+  if (id >= d.items) return d;
+  int before = 0;
+#pragma unroll
+  for (int u = 0; u < kU; ++u) {
+    const int upto = before + wave_scan(mine[u], add), all_u = last_lane(upto);
+    if (d.it.n == 0 && id < all_u * H) {
+      const int at = __popcll(__ballot(upto * H <= id));   // (lanes without a sequence hold the same sum as the last one with)
+      d.it.b = 64 * u + at;
+      d.it.n = __builtin_amdgcn_readlane(mine[u], at);
+      const int first = (__builtin_amdgcn_readlane(upto, at) - d.it.n) * H;
+      d.it.j = uniform((id - first) / H);
+      d.it.hkv = id - first - d.it.j * H;
+      d.it.row0 = first + d.it.hkv * d.it.n;
+#pragma unroll
+      for (int k = 0; k < 3; ++k) d.np[k] = __builtin_amdgcn_readlane(p[u][k], at);
+    }
+    before = all_u;
+  }
+  return d;
 }
 
 constexpr int kRowPad = 4;   // a partial row: acc[D], m, l, two unused words (rows stay 16-byte aligned)

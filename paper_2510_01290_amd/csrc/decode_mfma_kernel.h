@@ -305,6 +305,8 @@ __device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)"
 // kChunkPairs consecutive pairs, type after type; chunk numbers come from the workgroup's ticket counter.  The ids and
 // masks of the pair after the one just taken are on their way by scalar loads (no traffic in the vector-memory queue).
 constexpr int kChunkPairs = 4;
+static_assert(2 * kChunkPairs == kDealPages, "a wave is worth a chunk");
+constexpr int kTicketBytes = 64;   // a counter for each of up to sixteen items, behind the rings
 typedef const int32_t __attribute__((address_space(4))) * ConstI32;   // read-only for the whole launch: scalar loads
 typedef __attribute__((address_space(3))) int32_t* LdsCounter;
 
@@ -968,23 +970,36 @@ __device__ __forceinline__ void fold_rows(const DecodeArgs& a, const float* rows
   }
 }
 
-// Full-attention layers: a workgroup of W = blockDim.x / 64 waves per item (see the head of the file).
+// Full-attention layers: a workgroup of W = blockDim.x / 64 waves, on one item or on several side by side (see the head of the
+// file).
 // FP: the cache is in the paper's number formats (decode_mfma_fp.h), else in the integer formats.
 template <int D, int GP, bool STAT, bool FP>
 __global__ __launch_bounds__(256 * decode_waves_per_simd(D, FP)) __attribute__((amdgpu_waves_per_eu(decode_waves_per_simd(D, FP), decode_waves_per_simd(D, FP)))) void decode_stream_kernel(thinkv_view v, DecodeArgs a) {
-  constexpr int kRing = stream_ring_bytes(D, FP), kRow = D + kRowPad;
+  constexpr int kRing = stream_ring_bytes(D, FP), kRow = D + kRowPad, kFull = 4 * decode_waves_per_simd(D, FP);
   extern __shared__ __attribute__((aligned(16))) uint8_t tkv_lds[];
   const thinkv_config& c = v.cfg;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, W = blockDim.x >> 6;
-  const ItemLoc it = locate_item(v, a, blockIdx.x);
-  if (it.j >= it.n) return;
-  const int b = it.b, hkv = it.hkv, seq = uniform(a.seq_ids[b]);
+  // this wave's item, and the waves it shares it with: `wph` from wave0 on
+  ItemLoc it;
+  int np[3], wph = W;
+  if (a.grid) {
+    const Deal d = deal_item<kFull>(v, a, blockIdx.x, wave);
+    if ((int)blockIdx.x >= d.items) return;   // (then no wave has one)
+    it = d.it;
+    wph = d.wph;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) np[k] = d.np[k];
+  } else {
+    it = locate_item(v, a, blockIdx.x);
+    if (it.j >= it.n) return;
+    seq_pages(v, a.layer, uniform(a.seq_ids[it.b]), np);
+  }
+  const int group = uniform(wave / wph), wave0 = group * wph;
+  const int b = it.b, hkv = it.hkv, seq = uniform(a.seq_ids[b]), share_n = it.n > 0 ? it.n : 1;
   const int Hq = c.n_q_heads, G = Hq / c.n_kv_heads;
-  int np[3];
-  seq_pages(v, a.layer, seq, np);
   const bool valid = seq >= 0 && seq < c.max_seqs;
   Stream q;
-  q.ticket = (LdsCounter)(uintptr_t)(W * kRing);
+  q.ticket = (LdsCounter)(uintptr_t)(W * kRing + 4 * group);
   q.lane = lane;
   q.max_pages = c.max_pages;
   q.tab = (ConstI32)(uintptr_t)(v.block_table + (valid ? table_base(c, seq, a.layer, 0) : 0));
@@ -996,14 +1011,16 @@ __global__ __launch_bounds__(256 * decode_waves_per_simd(D, FP)) __attribute__((
   q.kind0 = rot;
   q.kind1 = rot + 1 < 3 ? rot + 1 : rot - 2;
   q.kind2 = rot + 2 < 3 ? rot + 2 : rot - 1;
-  q.cum0 = Stream::share(Stream::pick(q.kind0, np[0], np[1], np[2]), it.j, it.n, q.first0, q.end0);
-  q.cum1 = q.cum0 + Stream::share(Stream::pick(q.kind1, np[0], np[1], np[2]), it.j, it.n, q.first1, q.end1);
-  q.cum2 = q.cum1 + Stream::share(Stream::pick(q.kind2, np[0], np[1], np[2]), it.j, it.n, q.first2, q.end2);
-  if (it.j == 0 && threadIdx.x == 0 && !a.direct) {
-    a.alloc[2 * (b * c.n_kv_heads + hkv)] = it.row0;
-    a.alloc[2 * (b * c.n_kv_heads + hkv) + 1] = it.n;
+  q.cum0 = Stream::share(Stream::pick(q.kind0, np[0], np[1], np[2]), it.j, share_n, q.first0, q.end0);
+  q.cum1 = q.cum0 + Stream::share(Stream::pick(q.kind1, np[0], np[1], np[2]), it.j, share_n, q.first1, q.end1);
+  q.cum2 = q.cum1 + Stream::share(Stream::pick(q.kind2, np[0], np[1], np[2]), it.j, share_n, q.first2, q.end2);
+  if (wave == wave0 && lane == 0) {
+    *q.ticket = 0;
+    if (it.n > 0 && it.j == 0 && !a.direct) {
+      a.alloc[2 * (b * c.n_kv_heads + hkv)] = it.row0;
+      a.alloc[2 * (b * c.n_kv_heads + hkv) + 1] = it.n;
+    }
   }
-  if (threadIdx.x == 0) *q.ticket = 0;
   q.left = q.row = q.end = q.sec = q.pg = q.more_pages = q.pid_a = q.pid_b = q.msk_a = q.msk_b = 0;
   Query<D, GP, FP> query;
   query.read(a, ((int64_t)b * Hq + hkv * G) * D, G, lane);
@@ -1035,9 +1052,10 @@ __global__ __launch_bounds__(256 * decode_waves_per_simd(D, FP)) __attribute__((
     }
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < G * (D / 4); i += blockDim.x) {
+  if (it.n == 0) return;
+  for (int i = threadIdx.x - 64 * wave0; i < G * (D / 4); i += 64 * wph) {
     const int g = i / (D / 4), ch = 4 * (i % (D / 4));
-    fold_rows<D>(a, rows + g * kRow, G * kRow, W, b, hkv, g, ch, Hq, G, it.row0 + it.j);
+    fold_rows<D>(a, rows + (wave0 * G + g) * kRow, G * kRow, wph, b, hkv, g, ch, Hq, G, it.row0 + it.j);
   }
 }
 
@@ -1189,7 +1207,7 @@ static int launch_one(const thinkv_view& v, const DecodeArgs& a, hipStream_t st)
     const int groups = (v.cfg.n_kv_heads + a.waves - 1) / a.waves;
     hipLaunchKernelGGL((decode_window_kernel<D, GP, STAT, FP>), dim3(a.per_head * groups * a.B), dim3(64 * kWindowWaves), window_lds_bytes(D), st, v, a);
   } else {
-    hipLaunchKernelGGL((decode_stream_kernel<D, GP, STAT, FP>), dim3(a.n_rows), dim3(64 * a.waves), a.waves * stream_ring_bytes(D, FP) + 16, st, v, a);
+    hipLaunchKernelGGL((decode_stream_kernel<D, GP, STAT, FP>), dim3(a.grid ? a.grid : a.n_rows), dim3(64 * a.waves), a.waves * stream_ring_bytes(D, FP) + kTicketBytes, st, v, a);
   }
   return hipGetLastError() == hipSuccess ? THINKV_OK : THINKV_E_HIP;
 }

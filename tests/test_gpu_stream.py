@@ -36,9 +36,17 @@ def _cache(D, G, H, ctx, fmt, bits, seed, v_scale=1.0, dead=0.0):
     return c, q
 
 
-def _both(c, q, D, bound=None, window=0, q_pos=None):
+def _items(c, ws, need, S):
+    """how many items every (query, kv-head) got and where its partial rows begin, as the call left them in its workspace"""
+    H = c.cfg.n_kv_heads
+    at = need - 256 - 8 * S * H
+    alloc = ws[at:at + 8 * S * H].view(torch.int32).view(S, H, 2).cpu()
+    return alloc[..., 1], alloc[..., 0]
+
+
+def _both(c, q, D, bound=None, window=0, q_pos=None, ids=None, items=None):
     S, Hq = q.shape[:2]
-    ids = torch.arange(S, dtype=torch.int32, device="cuda:0")
+    ids = torch.arange(S, dtype=torch.int32, device="cuda:0") if ids is None else torch.tensor(ids, dtype=torch.int32, device="cuda:0")
     pages = int(c.n_pages[:, 0].sum(-1).max()) if bound is None else bound
     qp = None if q_pos is None else torch.tensor(q_pos, dtype=torch.int32, device="cuda:0")
     res = []
@@ -52,6 +60,8 @@ def _both(c, q, D, bound=None, window=0, q_pos=None):
         torch.cuda.synchronize()
         assert rc == 0
         assert bool((ws[need:] == 0x5A).all()), "written behind the workspace"
+        if items is not None and not res:
+            items.extend(_items(c, ws, need, S))
         res.append((out.double().cpu(), lse.double().cpu()))
     assert int(c.dev_status.abs().sum()) == 0
     return res
@@ -159,3 +169,36 @@ def test_a_query_head_that_is_not_finite_stays_alone(D, G, fmt, window):
     assert float((o - ro)[~bad].abs().max()) <= 1e-4 * max(1.0, float(ro[~bad].abs().max()))
     assert float((l - rl)[~bad].abs().max()) <= 1e-4
     assert bool((o[bad] == 0).all()) and bool((l[bad] == -float("inf")).all())
+
+
+@pytest.mark.parametrize("D,G,H,ctx,fmt,ids,bound", [
+    (128, 4, 8, [6500] * 17, 0, None, None),                               # 136 heads: neither one nor two to a compute unit
+    (64, 8, 3, [9000, 30, 0, 1, 4000, 700] * 9, 0, None, None),            # uneven lengths, an empty sequence
+    (64, 2, 1, [40] * 180 + [9000] * 4 + [4100] * 20, 1, None, None),      # more sequences than lanes of a wave
+    (128, 8, 8, [6000] * 20 + [300] * 20, 1, None, None),                  # more heads than compute units
+    (128, 1, 2, [20000, 100], 0, [0, 1, 0, -1, 7, 1], None),               # a sequence asked for twice, and two that do not exist
+    (128, 4, 4, [9000, 2500, 800], 0, None, 300),                          # the host's bound is too low for the first
+    (128, 4, 4, [2500, 800, 90], 0, None, 40000),                          # ... and far too high
+], ids=lambda x: str(x)[:24].replace(" ", ""))
+def test_items_dealt_over_a_batch(D, G, H, ctx, fmt, ids, bound):
+    """every (query, kv-head) gets at least one item and rows of its own, the longer sequences more; results as the plain kernel's"""
+    print("stream, dealt:", D, G, H, len(ctx), max(ctx), fmt, ids, bound, flush=True)
+    c, q = _cache(D, G, H, ctx, fmt, (8, 2, 4), 41 + D + G + len(ctx))
+    seqs = list(range(len(ctx))) if ids is None else ids   # (a call takes as many queries as the cache has sequences)
+    for k in range(0, len(seqs), len(ctx)):
+        part = seqs[k:k + len(ctx)]
+        items = []
+        (o, l), (ro, rl) = _both(c, q[:len(part)], D, bound, ids=part, items=items)
+        n, row0 = items
+        pages = c.n_pages[:, 0].sum(-1).cpu()
+        mine = torch.tensor([int(pages[s]) if 0 <= s < len(ctx) else 0 for s in part])
+        assert bool(((n >= 1) & (n <= 1024) & (row0 >= 0) & (row0 < 1 << 16)).all()) and (int(n.max()) > 1 or int(mine.max()) < 100)
+        assert bool((n == n[:, :1]).all())                                  # the heads of a sequence share alike
+        order = torch.argsort(mine)
+        assert bool((n[order, 0].diff() >= 0).all())
+        rows = torch.cat([torch.arange(int(r), int(r) + int(m)) for r, m in zip(row0.flatten(), n.flatten())])
+        assert len(rows.unique()) == len(rows)
+        for b in range(len(part)):
+            fin = torch.isfinite(rl[b])
+            assert torch.equal(torch.isfinite(l[b]), fin) and (not fin.any() or float((l[b][fin] - rl[b][fin]).abs().max()) <= 1e-4)
+            assert float((o[b] - ro[b]).abs().max()) <= 2e-5 * max(float(ro[b].abs().max()), 1e-3)
