@@ -125,23 +125,25 @@ static int64_t rows_bound(const thinkv_config& c, int B, int max_ctx_pages) {
 
 // Full-attention layers of the fast kernel: workgroups of *waves waves.
 // Dealt (*grid > 0, deal_item): a workgroup per compute unit, of all the waves it holds, and every item at once; the device sizes
-// them by what the sequences hold.  Up to two heads a compute unit; with more, one item a head fills the machine.
+// them by what the sequences hold.  Up to two heads a compute unit, three at head_dim 64; with more, one item a head fills the
+// machine, and the short sequences leave it early (96 x 8 heads of 4k..32k tokens, head_dim 128: 350 us dealt, 337 by the
+// rule below; head_dim 64, of 16k each: 229 and 246).
 // A head to a workgroup, which writes the result itself, where an item would be worth less than the
-// merge launch: contexts of up to 16 pages a wave, 24 if every other compute unit has a head, and 80 with about as many
-// heads as compute units.
+// merge launch: contexts of up to 16 pages a wave, 24 if every other compute unit has a head, 80 with about as many
+// heads as compute units; 256 pages with more heads, and 512 with more than two a compute unit.
 // More heads: workgroups of four, several to a compute unit, so that one's start and end are covered by the others', and an
 // item per so many pages: about sixteen rounds of them if every sequence were as long as the host's bound, but no
-// fewer than 64 pages a wave.
+// fewer than 128 pages a wave (64 pages: head_dim 64, 64 heads, 96 x 4k tokens 76 us, now 65; 128 x 16k 326, now 307).
 static ItemSizing size_stream(const thinkv_config& c, int B, int max_ctx_pages, int* waves, int* grid) {
   const int64_t heads = (int64_t)B * c.n_kv_heads, cus = compute_units();
   const int64_t full = 4 * decode_waves_per_simd(c.head_dim, c.format == THINKV_FMT_FP);
   const int64_t pages = max_ctx_pages > 0 ? max_ctx_pages : 1;
   const int64_t most = (pages + 7) / 8, bound = rows_bound(c, B, max_ctx_pages);   // rows: what the workspace is sized for
   const bool few = heads <= cus;
-  const bool single = few ? pages <= (10 * heads >= 9 * cus ? 80 : (2 * heads > cus ? 24 : 16)) * full : pages <= 256;
+  const bool single = few ? pages <= (10 * heads >= 9 * cus ? 80 : (2 * heads > cus ? 24 : 16)) * full : pages <= (heads <= 2 * cus ? 256 : 512);
   ItemSizing z;
   *grid = 0;
-  if (heads <= 2 * cus && B <= kDealSeqs && !single) {
+  if (heads <= (c.head_dim == 64 ? 3 : 2) * cus && B <= kDealSeqs && !single) {
     const int64_t wanted = heads * ((pages + kDealPages * full - 1) / (kDealPages * full));
     *waves = (int)full;
     *grid = (int)(wanted < cus ? wanted : cus);
@@ -151,7 +153,7 @@ static ItemSizing size_stream(const thinkv_config& c, int B, int max_ctx_pages, 
   }
   const int64_t W = few ? (most < full ? most : full) : (most < 4 ? most : 4);
   int64_t per_head = few ? 1 : (16 * cus * full + heads * W - 1) / (heads * W);
-  const int64_t cap = (pages + 64 * W - 1) / (64 * W), room = bound / heads;   // (room is at least 1)
+  const int64_t cap = few ? 1 : (pages + 128 * W - 1) / (128 * W), room = bound / heads;   // (room is at least 1)
   if (per_head > cap) per_head = cap;
   if (per_head > room) per_head = room;
   if (per_head > kMaxRowsPerHead) per_head = kMaxRowsPerHead;

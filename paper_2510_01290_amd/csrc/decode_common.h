@@ -21,6 +21,9 @@
 __host__ __device__ constexpr int decode_waves_per_simd(int head_dim, bool fp) { return (head_dim == 64 ? 3 : 2) + (fp ? 1 : 0); }
 __host__ __device__ constexpr int stream_ring_bytes(int head_dim, bool fp) { return 147456 / (4 * decode_waves_per_simd(head_dim, fp)); }
 
+// LDS of a wave through which the softmax weights of a pair change layout (0: by a matrix product; see Softmax::weights)
+__host__ __device__ constexpr int exchange_bytes(int head_dim, int heads, bool fp) { return head_dim == 64 && heads == 8 && !fp ? 2 * 16 * heads * 4 : 0; }
+
 // Sliding-window layers: waves of a workgroup, pages of each type it scans at a time, its rings and all its LDS (the rings,
 // then per type the ids, masks and list positions of the visible pages, then their counts per wave).
 constexpr int kWindowWaves = 8, kWindowBlock = 64 * kWindowWaves;

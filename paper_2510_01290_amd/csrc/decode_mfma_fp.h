@@ -84,15 +84,15 @@ struct ClassRunnerFp {
   using Pair = PairRegsFp<D, BITS, NSET>;
   const int lane;
   WaveState<D, GP, NSET>& st;
-  Softmax<D, GP, NSET, STAT> sm;
+  Softmax<D, GP, NSET, STAT, false> sm;
   int k_off[NSET], v_off[NSET];   // byte offset, inside a meta region, of the lane's scale byte (K) and of its four scale bytes (V) per column set
   H8 bq[NG32];          // A operands of the score MFMAs: q over the half of the 32 channels that is the slice's group, zeros elsewhere
   float tile_out;       // tiles -> absolute units / 2^24 when the type is left
   float neg1;
 
   __device__ __forceinline__ ClassRunnerFp(WaveState<D, GP, NSET>& st_, const thinkv_config& c, const DecodeArgs& a, int G, const QRegsFp<NSET>& qr, float* stat_,
-                                           int stat_room_)
-      : lane(threadIdx.x & 63), st(st_), sm(st_, threadIdx.x & 63, G, stat_, stat_room_) {
+                                           int stat_room_, uint32_t xch)
+      : lane(threadIdx.x & 63), st(st_), sm(st_, threadIdx.x & 63, G, stat_, stat_room_, xch) {
     const int qd = lane >> 4, n = lane & 15;
     const int gl = n / GP;
     const int glc = gl < CS ? gl : CS - 1;
@@ -119,12 +119,14 @@ struct ClassRunnerFp {
       for (int w = 0; w < 4; ++w) bq[g].u[w] = on ? qr.q[set].u[w] : 0u;
     }
     // enter the type: the denominator and the tiles take the lift, the tiles the units of the type
+    sm.enter((float)kLift, kSlack);
     sm.scale_sums((float)(1 << kLift));
     const float in = 1.0f / tile_out;
 #pragma unroll
     for (int mb = 0; mb < NM; ++mb) st.o[mb] *= in;
   }
   __device__ __forceinline__ void leave() {
+    sm.leave();
     sm.scale_sums(1.0f / (float)(1 << kLift));
 #pragma unroll
     for (int mb = 0; mb < NM; ++mb) st.o[mb] *= tile_out;
@@ -193,11 +195,11 @@ struct ClassRunnerFp {
     page_scores(r.a, sa);
     page_scores(r.b, sb);
     sm.mask(sa, sb, id);
-    sm.reference(sa, sb, kSlack);
+    sm.reference(sa, sb, false);
   }
   __device__ __forceinline__ void values(const Pair& r) {
     float ea[NS], eb[NS], pa[4], pb[4];
-    sm.weights(sa, sb, (float)kLift, ea, eb, pa, pb);
+    sm.weights(sa, sb, ea, eb, pa, pb);
     sm.add(ea, eb);
     // values, per column set: B = two-term split of p * s_V, A = V codes
     H8 hi, lo;

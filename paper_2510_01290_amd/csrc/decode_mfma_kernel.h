@@ -25,7 +25,8 @@
 // then done CS times over: 292 vector-ALU instructions per page pair and wave, 238 now.)
 // The weights go back to the layout of the value product (four tokens per lane, column = (slice, head)) by one
 // v_mfma_f32_16x16x4_f32 per page and four heads with a 0/1 matrix: products with one and zero, so exact for numbers (a
-// weight that is not one, from a query head that is not finite, must not reach the sum: it would spoil the other heads).
+// weight that is not one, from a query head that is not finite, must not reach the sum: it would spoil the other heads); at
+// head_dim 64 with more than four heads through LDS.
 // Values: p * s_V(t, g) is lane-local (each slice multiplies by its own group's
 // scale), is split once into two binary16 terms (22 significant bits), and the same B operand
 // pair serves the PV MFMAs of every group of the set: the tile of a 16-channel block is only
@@ -70,6 +71,19 @@ template <int CTRL>
 __device__ __forceinline__ float max_dpp(float x) {
   const int y = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true);
   return fmaxf(x, __builtin_bit_cast(float, y));
+}
+
+// The largest of numbers, in one instruction; a NaN loses.  (fmaxf is up to three: it makes sure of quiet NaNs first.  Not for
+// what a matrix or a transcendental instruction has just written: the compiler knows of no wait states for asm.)
+__device__ __forceinline__ float largest(float a, float b) {
+  float x;
+  asm("v_max_f32 %0, %1, %2" : "=v"(x) : "v"(a), "v"(b));
+  return x;
+}
+__device__ __forceinline__ float largest(float a, float b, float c) {
+  float x;
+  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(x) : "v"(a), "v"(b), "v"(c));
+  return x;
 }
 
 __device__ __forceinline__ uint32_t pack_rne(float a, float b) {
@@ -189,8 +203,7 @@ struct WaveState {
   float4v o[NM];    // column layout; o[mb][r]: channel 16*mb + 4*qd + r (while a type is walked: in its units, and lifted)
   float oz[NSET];   // column layout; this lane's share of sum_t p_t zp_V(t, group of the lane's slice)
   float l[NS];      // score layout; this lane's share of sum_t p_t
-  float m[NS];      // score layout; running maximum (log2 domain) of the head; -inf before the first live token
-  float m_sub[NS];  // what the exponent subtracts: m, or 0 while m is -inf
+  float m[NS];      // score layout; between types: the reference of the head's weights (log2 domain, a whole number); -inf before the first live token
 };
 
 // head of value i of a lane in row quad qd, as add_groups leaves the scores
@@ -313,9 +326,8 @@ typedef __attribute__((address_space(3))) int32_t* LdsCounter;
 // a scalar that a load may still be bringing: waited for here and not before (what is computed from it would otherwise
 // be moved up to the load, and the wait with it)
 __device__ __forceinline__ int arrived(int x) {
-  int y;
-  asm volatile("s_mov_b32 %0, %1" : "=s"(y) : "s"(x));
-  return y;
+  asm volatile("" : "+s"(x));
+  return x;
 }
 
 struct Stream {
@@ -347,6 +359,7 @@ struct Stream {
                  : "=&v"(r) : "v"((uint32_t)(uintptr_t)ticket), "v"(1) : "memory");
     return uniform(r);
   }
+  static __device__ __forceinline__ int at(ConstI32 list, uint32_t bytes) { return *(ConstI32)((const char __attribute__((address_space(4)))*)list + bytes); }
   // moves on by one pair.  (Sums and minima instead of conditions: a condition turned into a number takes a vector
   // instruction and drags what depends on it out of the scalar registers.)
   __device__ __forceinline__ void look() {
@@ -378,11 +391,11 @@ struct Stream {
       left = min((end - pg - 1) >> 1, kChunkPairs - 1);
     }
     more_pages = min(end - pg - 1, 1);
-    const ConstI32 t = tab + (row + pg), m = msk + (row + pg);   // (max_pages < 2^24)
-    pid_a = t[0];
-    msk_a = m[0];
-    pid_b = t[more_pages];
-    msk_b = m[more_pages];
+    const uint32_t a = 4u * (uint32_t)(row + pg), b = a + 4u * (uint32_t)more_pages;   // (bytes: 3 max_pages < 2^26)
+    pid_a = at(tab, a);
+    msk_a = at(msk, a);
+    pid_b = at(tab, b);
+    msk_b = at(msk, b);
   }
   // the pair at hand, if it is one of the x-th type walked (want): its ids and masks are waited for here and not before
   int want;
@@ -492,21 +505,58 @@ struct QRegs {
   float sum[NSET][4];
 };
 
+typedef __attribute__((address_space(3))) float* LdsFloats;
+typedef __attribute__((address_space(3))) float4v* LdsFloat4;
+
 // What the two runners (integer formats, the paper's formats) share: the softmax over the scores of a pair.
-template <int D, int GP, int NSET, bool STAT>
+// LDS: the weights of a pair change layout through LDS (exchange_bytes).
+template <int D, int GP, int NSET, bool STAT, bool LDS>
 struct Softmax {
   static constexpr int NM = D / 16, NS = GP / 4;
   using State = WaveState<D, GP, NSET>;
   State& st;
   int lane;
   float kappa;       // MFMA score units -> log2 domain (with softmax_scale)
+  float lift, slack; // weights are 2^(score - m + lift); the reference m is at most slack below the largest score
+  // While a type is walked, per head: m - lift (0 - lift before the first live token), and the score, in MFMA units, above which m
+  // moves (-inf before the first live token).  m and lift are whole numbers, so that all of this is exact.
+  float mref[NS], top[NS];
   float sel[NS];     // B operands of the layout change: 1 where the column's head is the row's
   float* stat;       // STAT: pooled scores of this type's page list, 16 per page
   int stat_room;     // STAT: pages of this list the buffer has room for (the host's bound on the context)
   int G;
-  __device__ __forceinline__ Softmax(State& st_, int lane_, int G_, float* stat_, int room) : st(st_), lane(lane_), stat(stat_), stat_room(room), G(G_) {
+  LdsFloats put, get;   // LDS: where this lane leaves its weights, and finds those of its column and tokens
+  __device__ __forceinline__ Softmax(State& st_, int lane_, int G_, float* stat_, int room, uint32_t xch) : st(st_), lane(lane_), stat(stat_), stat_room(room), G(G_) {
+    if constexpr (LDS) {
+      static_assert(GP == 8, "rows of sixteen tokens, four of a lane's first head, then four of its second");
+      const int h = lane & (GP - 1), row = 4 * (h & 1) + (h >> 2) + (h & 2);   // (head_of: head h is value h & 1 of row quad (h >> 2) + (h & 2))
+      put = (LdsFloats)(uintptr_t)(xch + 4 * lane);
+      get = (LdsFloats)(uintptr_t)(xch + 64 * row + 16 * (lane >> 4));
+    }
 #pragma unroll
     for (int i = 0; i < NS; ++i) sel[i] = head_of<GP>(lane >> 4, i) == (lane & (GP - 1)) ? 1.0f : 0.0f;
+  }
+  __device__ __forceinline__ void enter(float lift_, float slack_) {
+    lift = lift_;
+    slack = slack_;
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+      mref[i] = (st.m[i] == -INFINITY ? 0.f : st.m[i]) - lift;
+      top[i] = (st.m[i] + slack) / kappa;
+    }
+  }
+  // the weights from here on without the lift
+  __device__ __forceinline__ void drop_lift() {
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+      mref[i] += lift;
+      top[i] -= slack / kappa;
+    }
+    lift = slack = 0.f;
+  }
+  __device__ __forceinline__ void leave() {
+#pragma unroll
+    for (int i = 0; i < NS; ++i) st.m[i] = top[i] == -INFINITY ? -INFINITY : mref[i] + lift;
   }
   // sa, sb: scores of the lane's token in pages a and b (NS heads each), in MFMA units.  Masks them and leaves the pooled scores.
   __device__ __forceinline__ void mask(float* sa, float* sb, const PairIds& id) {
@@ -535,25 +585,28 @@ struct Softmax {
     }
   }
   // Online softmax: the weights are 2^(score - m) with m a reference that is at most `slack` below the maximum seen.  It
-  // only moves when a score exceeds it by more, to the maximum: with eight heads a new maximum by any amount turns up
+  // only moves when a score exceeds it by more, to the next whole number above the maximum: with eight heads a new maximum by any amount turns up
   // in most pairs of a few thousand tokens (and moving m costs as much as a quarter of the pair), one by a factor of 2^slack hardly ever.
-  __device__ __forceinline__ void reference(const float* sa, const float* sb, float slack) {
+  // now: it moves if any score is above it.
+  __device__ __forceinline__ void reference(const float* sa, const float* sb, bool now) {
     float mx[NS];
     bool above = false;
 #pragma unroll
     for (int i = 0; i < NS; ++i) {
-      mx[i] = fmaxf(sa[i], sb[i]) * kappa;
-      above = above || mx[i] > st.m[i] + slack;
+      mx[i] = largest(sa[i], sb[i]);
+      above = above || mx[i] > (now ? top[i] - slack / kappa : top[i]);
     }
     if (__any(above)) {
       float corr[NS];
 #pragma unroll
       for (int i = 0; i < NS; ++i) {
-        const float m_new = fmaxf(st.m[i], row_max(mx[i]));
-        st.m_sub[i] = m_new == -INFINITY ? 0.f : m_new;
-        corr[i] = __builtin_amdgcn_exp2f(st.m[i] - st.m_sub[i]);
+        const bool seen = top[i] > -INFINITY;
+        const float m_old = mref[i] + lift, m_new = fmaxf(seen ? m_old : -INFINITY, ceilf(row_max(mx[i]) * kappa));
+        const float m_sub = m_new == -INFINITY ? 0.f : m_new;
+        corr[i] = seen ? __builtin_amdgcn_exp2f(m_old - m_sub) : 0.f;
         st.l[i] *= corr[i];
-        st.m[i] = m_new;
+        mref[i] = m_sub - lift;
+        top[i] = (m_new + slack) / kappa;
       }
       const float cc = to_column<GP>(corr, lane);
 #pragma unroll
@@ -562,18 +615,30 @@ struct Softmax {
       for (int set = 0; set < NSET; ++set) st.oz[set] *= cc;
     }
   }
-  // the weights 2^(score - m + lift): ea, eb of the lane's token (score layout), pa, pb of the lane's four tokens (column layout)
-  __device__ __forceinline__ void weights(const float* sa, const float* sb, float lift, float* ea, float* eb, float* pa, float* pb) const {
+  // the weights 2^(score - m + lift): ea, eb of the lane's token (score layout), pa, pb of the lane's four tokens (column layout).
+  // The layout change by a matrix product takes 32 cycles of the matrix core for four heads and a page, the one through
+  // LDS two short stores and one read for eight: at head_dim 64 with more than four heads, where a pair has few bytes and the compute
+  // units' clock and not the memory is what a long launch waits for, 64 x 16k tokens 156 -> 141 us, 128 x 4k..32k 287 -> 267; at
+  // head_dim 128, and with up to four heads, no difference.
+  __device__ __forceinline__ void weights(const float* sa, const float* sb, float* ea, float* eb, float* pa, float* pb) const {
     float4v ta = {0.f, 0.f, 0.f, 0.f}, tb = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int i = 0; i < NS; ++i) {
-      const float mref = st.m_sub[i] - lift;
-      ea[i] = __builtin_amdgcn_exp2f(fmaf(sa[i], kappa, -mref));
-      eb[i] = __builtin_amdgcn_exp2f(fmaf(sb[i], kappa, -mref));
-      // (the product adds four heads, and 0 times what is not a number is not one: such a weight goes in as 0, and spoils
-      // its own head through the denominator, which adds ea and eb as they are.  Weights are never infinite.)
-      ta = __builtin_amdgcn_mfma_f32_16x16x4f32(fmaxf(ea[i], 0.f), sel[i], ta, 0, 0, 0);
-      tb = __builtin_amdgcn_mfma_f32_16x16x4f32(fmaxf(eb[i], 0.f), sel[i], tb, 0, 0, 0);
+      ea[i] = __builtin_amdgcn_exp2f(fmaf(sa[i], kappa, -mref[i]));
+      eb[i] = __builtin_amdgcn_exp2f(fmaf(sb[i], kappa, -mref[i]));
+      if constexpr (LDS) {
+        put[64 * i] = ea[i];
+        put[64 * (NS + i)] = eb[i];
+      } else {
+        // (the product adds four heads, and 0 times what is not a number is not one: such a weight goes in as 0, and spoils
+        // its own head through the denominator, which adds ea and eb as they are.  Weights are never infinite.)
+        ta = __builtin_amdgcn_mfma_f32_16x16x4f32(__builtin_amdgcn_fmed3f(ea[i], 0.f, INFINITY), sel[i], ta, 0, 0, 0);
+        tb = __builtin_amdgcn_mfma_f32_16x16x4f32(__builtin_amdgcn_fmed3f(eb[i], 0.f, INFINITY), sel[i], tb, 0, 0, 0);
+      }
+    }
+    if constexpr (LDS) {   // (a wave's LDS operations happen in order)
+      ta = *(LdsFloat4)get;
+      tb = *(LdsFloat4)(get + 64 * NS);
     }
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -607,17 +672,17 @@ struct ClassRunner {
   using Pair = PairRegs<D, BITS, NSET>;
   const int lane;
   WaveState<D, GP, NSET>& st;
-  Softmax<D, GP, NSET, STAT> sm;
+  Softmax<D, GP, NSET, STAT, exchange_bytes(D, GP, false) != 0> sm;
   int k_off[NSET], v_off[NSET];  // byte offset, inside a meta region, of this lane's scale (K) and unit (V) per column set
   H8 bq[NG];           // A operands of the score MFMAs: q of group g in slice g % CS, zeros elsewhere
   float qs[NSET][4];   // 2^(OMIN-24) * sum_{i in group} q_i of the four rows of this lane's quad
-  float lift;          // the weights of this type's pages are 2^lift times the softmax weights (kLift, or 0 after a scale too large for it)
+  int lifted;          // the weights of this type's pages are 2^kLift times the softmax weights (0 after a scale too large for it)
   float neg1;          // -1, kept opaque so that x - (float)h stays one fused mixed-precision instruction
 
   // qr: this lane's query slice per column set (binary16, channels 32g + 8qd + e of its head and slice group) and the
   // group sums, as the kernel read them once per item
-  __device__ __forceinline__ ClassRunner(WaveState<D, GP, NSET>& st_, const thinkv_config& c, const DecodeArgs& a, int G, const QRegs<NSET>& qr, float* stat_, int stat_room_)
-      : lane(threadIdx.x & 63), st(st_), sm(st_, threadIdx.x & 63, G, stat_, stat_room_) {
+  __device__ __forceinline__ ClassRunner(WaveState<D, GP, NSET>& st_, const thinkv_config& c, const DecodeArgs& a, int G, const QRegs<NSET>& qr, float* stat_, int stat_room_, uint32_t xch)
+      : lane(threadIdx.x & 63), st(st_), sm(st_, threadIdx.x & 63, G, stat_, stat_room_, xch) {
     const int qd = lane >> 4, n = lane & 15;
     const int gl = n / GP, head = n % GP;
     const bool used = gl < CS && head < G;
@@ -667,20 +732,23 @@ struct ClassRunner {
   __device__ static constexpr float tile_unit(int mb) { return (float)(1 << (BITS == 8 ? 0 : F::OMIN + F::rel_of(mb))); }
   __device__ __forceinline__ void enter() {
     const float up = (float)(1 << kLift);
-    lift = (float)kLift;
+    lifted = 1;
+    sm.enter((float)kLift, kSlack);
     sm.scale_sums(up);
 #pragma unroll
     for (int mb = 0; mb < NM; ++mb) st.o[mb] *= up * tile_unit(mb);
   }
   __device__ __forceinline__ void drop_lift() {
-    const float down = __builtin_amdgcn_exp2f(-lift);
+    const float down = 1.0f / (float)(1 << kLift);
     sm.scale_sums(down);
 #pragma unroll
     for (int mb = 0; mb < NM; ++mb) st.o[mb] *= down;
-    lift = 0.f;
+    lifted = 0;
+    sm.drop_lift();
   }
   __device__ __forceinline__ void leave() {
-    drop_lift();
+    if (lifted) drop_lift();
+    sm.leave();
 #pragma unroll
     for (int mb = 0; mb < NM; ++mb) st.o[mb] *= 1.0f / tile_unit(mb);
   }
@@ -729,13 +797,13 @@ struct ClassRunner {
     page_scores(r.a, sa);
     page_scores(r.b, sb);
     sm.mask(sa, sb, id);
-    sm.reference(sa, sb, lift != 0.f ? kSlack : 0.f);   // without the lift a weight above one could take the largest scales out of binary16
+    sm.reference(sa, sb, false);   // (without the lift there is no slack: a weight above one could take the largest scales out of binary16)
   }
   // ---------------- values, per column set: B = two-term split of p * s_V, A = V codes
   __device__ __forceinline__ void values(const Pair& r) {
     float ea[NS], eb[NS], pa[4], pb[4], xa[NSET][4], xb[NSET][4];
     for (int again = 0;; ++again) {
-      sm.weights(sa, sb, lift, ea, eb, pa, pb);
+      sm.weights(sa, sb, ea, eb, pa, pb);
       float big = 0.f;
 #pragma unroll
       for (int set = 0; set < NSET; ++set) {
@@ -746,14 +814,13 @@ struct ClassRunner {
   }
         TKV_X(0) TKV_X(1) TKV_X(2) TKV_X(3)
 #undef TKV_X
-        big = fmaxf(fmaxf(fmaxf(big, fmaxf(xa[set][0], xa[set][1])), fmaxf(fmaxf(xa[set][2], xa[set][3]), fmaxf(xb[set][0], xb[set][1]))),
-                    fmaxf(xb[set][2], xb[set][3]));
+        big = largest(largest(xa[set][0], xa[set][1], xa[set][2]), largest(xa[set][3], xb[set][0], xb[set][1]), largest(xb[set][2], xb[set][3], big));
       }
-      if (lift == 0.f || !__any(big > 6.0e4f)) break;
+      if (!lifted || !__any(big > 6.0e4f)) break;
       // A lifted product would leave binary16.  First the reference moves up to the maximum; scales that are too large
       // even then are far outside what a cache holds in practice, and the rest of this type's pages is worked on without
       // the lift.
-      if (again == 0) sm.reference(sa, sb, 0.0f);
+      if (again == 0) sm.reference(sa, sb, true);
       else drop_lift();
     }
     sm.add(ea, eb);
@@ -906,7 +973,6 @@ __device__ __forceinline__ void clear(WaveState<D, GP, NSET>& st) {
   for (int i = 0; i < GP / 4; ++i) {
     st.l[i] = 0.f;
     st.m[i] = -INFINITY;
-    st.m_sub[i] = 0.f;
   }
 }
 
@@ -922,11 +988,11 @@ __device__ __forceinline__ float* stat_row(const thinkv_config& c, const DecodeA
 #define TKV_WITH_RUNNER(BITS_, CALL)                                                                  \
   {                                                                                                   \
     if constexpr (FP) {                                                                               \
-      ClassRunnerFp<D, BITS_, GP, STAT> cr(st, c, a, G, query.qf, stat, stat_room);                   \
+      ClassRunnerFp<D, BITS_, GP, STAT> cr(st, c, a, G, query.qf, stat, stat_room, xch);                   \
       CALL;                                                                                           \
       cr.leave();                                                                                     \
     } else {                                                                                          \
-      ClassRunner<D, BITS_, GP, STAT> cr(st, c, a, G, query.qr, stat, stat_room);                     \
+      ClassRunner<D, BITS_, GP, STAT> cr(st, c, a, G, query.qr, stat, stat_room, xch);                     \
       CALL;                                                                                           \
       cr.leave();                                                                                     \
     }                                                                                                 \
@@ -1027,7 +1093,7 @@ __global__ __launch_bounds__(256 * decode_waves_per_simd(D, FP)) __attribute__((
   WaveState<D, GP, Query<D, GP, FP>::NSET> st;
   clear(st);
   __syncthreads();
-  const uint32_t ring = (uint32_t)(wave * kRing);
+  const uint32_t ring = (uint32_t)(wave * kRing), xch = (uint32_t)(W * kRing + kTicketBytes + exchange_bytes(D, GP, FP) * wave);
   q.look();
   while (q.sec < 3) {
     const int x = q.sec, k = Stream::pick(x, q.kind0, q.kind1, q.kind2);
@@ -1088,6 +1154,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     a.alloc[2 * (b * H + h0 + tid)] = (b * H + h0 + tid) * a.per_head;
     a.alloc[2 * (b * H + h0 + tid) + 1] = n;
   }
+  const uint32_t xch = (uint32_t)(window_lds_bytes(D) + exchange_bytes(D, GP, FP) * wave);
   int32_t* const lists = (int32_t*)(tkv_lds + kWindowWaves * kRing);   // [type][id, mask, list position][kWindowBlock]
   int32_t* const counts = lists + 9 * kWindowBlock;                    // [type][wave]
   Query<D, GP, FP> query;
@@ -1205,9 +1272,9 @@ template <int D, int GP, bool STAT, bool FP>
 static int launch_one(const thinkv_view& v, const DecodeArgs& a, hipStream_t st) {
   if (a.window > 0) {
     const int groups = (v.cfg.n_kv_heads + a.waves - 1) / a.waves;
-    hipLaunchKernelGGL((decode_window_kernel<D, GP, STAT, FP>), dim3(a.per_head * groups * a.B), dim3(64 * kWindowWaves), window_lds_bytes(D), st, v, a);
+    hipLaunchKernelGGL((decode_window_kernel<D, GP, STAT, FP>), dim3(a.per_head * groups * a.B), dim3(64 * kWindowWaves), window_lds_bytes(D) + kWindowWaves * exchange_bytes(D, GP, FP), st, v, a);
   } else {
-    hipLaunchKernelGGL((decode_stream_kernel<D, GP, STAT, FP>), dim3(a.grid ? a.grid : a.n_rows), dim3(64 * a.waves), a.waves * stream_ring_bytes(D, FP) + kTicketBytes, st, v, a);
+    hipLaunchKernelGGL((decode_stream_kernel<D, GP, STAT, FP>), dim3(a.grid ? a.grid : a.n_rows), dim3(64 * a.waves), a.waves * (stream_ring_bytes(D, FP) + exchange_bytes(D, GP, FP)) + kTicketBytes, st, v, a);
   }
   return hipGetLastError() == hipSuccess ? THINKV_OK : THINKV_E_HIP;
 }
