@@ -22,7 +22,9 @@ __host__ __device__ constexpr int decode_waves_per_simd(int head_dim, bool fp) {
 __host__ __device__ constexpr int stream_ring_bytes(int head_dim, bool fp) { return 147456 / (4 * decode_waves_per_simd(head_dim, fp)); }
 
 // LDS of a wave through which the softmax weights of a pair change layout (0: by a matrix product; see Softmax::weights)
-__host__ __device__ constexpr int exchange_bytes(int head_dim, int heads, bool fp) { return head_dim == 64 && heads == 8 && !fp ? 2 * 16 * heads * 4 : 0; }
+__host__ __device__ constexpr int exchange_bytes(int head_dim, int heads, bool fp) {
+  return (fp ? head_dim == 128 : head_dim == 64 && heads == 8) ? 2 * 16 * heads * 4 : 0;
+}
 
 // Sliding-window layers: waves of a workgroup, pages of each type it scans at a time, its rings and all its LDS (the rings,
 // then per type the ids, masks and list positions of the visible pages, then their counts per wave).
@@ -127,6 +129,8 @@ struct Deal {
   ItemLoc it;     // this wave's item (n = 0: none)
   int np[3];      // its sequence's pages by type
 };
+// x / y of numbers below 2^20 (the compiler's integer division takes thirty instructions)
+__device__ __forceinline__ int whole(int x, int y) { return uniform((int)(((float)x + 0.5f) * __builtin_amdgcn_rcpf((float)y))); }
 template <int kFull>
 __device__ inline Deal deal_item(const thinkv_view& v, const DecodeArgs& a, int wg, int wave) {
   constexpr int kU = kDealSeqs / 64;
@@ -163,15 +167,14 @@ __device__ inline Deal deal_item(const thinkv_view& v, const DecodeArgs& a, int 
     }
     return last_lane(wave_scan(sum, add));
   };
-  int sub = 1, best_sub = kFull, best_n = 1;
+  int sub = 1, best_sub = kFull, best_n = 1, n = 0, sum = 0;
   float best = INFINITY;
   while (true) {
     const int slots = min(a.grid * sub, a.n_rows);
     if (slots >= a.B * H) {   // (holds for the last sub)
-      const int least = kDealPages * (kFull / sub), cap = max(min((most + least - 1) / least, kMaxRowsPerHead), 1);
-      int n = max(min((int)(1.0001f * (float)slots * (float)most / fmaxf(all, 1.f)), cap), 1);
-      int sum = spread(n);
-      for (; n > 1 && sum * H > slots; sum = spread(n)) n = max(min(n - 1, (int)((float)n * (float)slots / (float)(sum * H))), 1);
+      const int least = kDealPages * whole(kFull, sub), cap = max(min((most + least - 1) / least, kMaxRowsPerHead), 1);
+      n = max(min((int)(1.0001f * (float)slots * (float)most / fmaxf(all, 1.f)), cap), 1);
+      for (sum = spread(n); n > 1 && sum * H > slots; sum = spread(n)) n = max(min(n - 1, (int)((float)n * (float)slots / (float)(sum * H))), 1);
       const float busiest = (float)most * (float)sub / (float)n;
       if (busiest < 0.95f * best) {
         best = busiest;
@@ -185,13 +188,13 @@ __device__ inline Deal deal_item(const thinkv_view& v, const DecodeArgs& a, int 
     sub = kFull % (2 * sub) == 0 ? 2 * sub : kFull;
   }
   sub = uniform(best_sub);
-  const int sum = spread(uniform(best_n));
+  if (n != best_n) sum = spread(uniform(best_n));
   Deal d;
   d.items = sum * H;
-  d.wph = uniform(kFull / sub);
+  d.wph = whole(kFull, sub);
   d.it = ItemLoc{0, 0, 0, 0, 0};
   d.np[0] = d.np[1] = d.np[2] = 0;
-  const int id = uniform(wave / d.wph) * a.grid + wg;   // neighbouring items on different compute units
+  const int id = whole(wave, d.wph) * a.grid + wg;   // neighbouring items on different compute units
   if (id >= d.items) return d;
   int before = 0;
 #pragma unroll
@@ -202,7 +205,7 @@ __device__ inline Deal deal_item(const thinkv_view& v, const DecodeArgs& a, int 
       d.it.b = 64 * u + at;
       d.it.n = __builtin_amdgcn_readlane(mine[u], at);
       const int first = (__builtin_amdgcn_readlane(upto, at) - d.it.n) * H;
-      d.it.j = uniform((id - first) / H);
+      d.it.j = whole(id - first, H);
       d.it.hkv = id - first - d.it.j * H;
       d.it.row0 = first + d.it.hkv * d.it.n;
 #pragma unroll

@@ -84,7 +84,7 @@ struct ClassRunnerFp {
   using Pair = PairRegsFp<D, BITS, NSET>;
   const int lane;
   WaveState<D, GP, NSET>& st;
-  Softmax<D, GP, NSET, STAT, false> sm;
+  Softmax<D, GP, NSET, STAT, exchange_bytes(D, GP, true) != 0> sm;
   int k_off[NSET], v_off[NSET];   // byte offset, inside a meta region, of the lane's scale byte (K) and of its four scale bytes (V) per column set
   H8 bq[NG32];          // A operands of the score MFMAs: q over the half of the 32 channels that is the slice's group, zeros elsewhere
   float tile_out;       // tiles -> absolute units / 2^24 when the type is left

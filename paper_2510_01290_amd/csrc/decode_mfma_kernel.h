@@ -25,8 +25,8 @@
 // then done CS times over: 292 vector-ALU instructions per page pair and wave, 238 now.)
 // The weights go back to the layout of the value product (four tokens per lane, column = (slice, head)) by one
 // v_mfma_f32_16x16x4_f32 per page and four heads with a 0/1 matrix: products with one and zero, so exact for numbers (a
-// weight that is not one, from a query head that is not finite, must not reach the sum: it would spoil the other heads); at
-// head_dim 64 with more than four heads through LDS.
+// weight that is not one, from a query head that is not finite, must not reach the sum: it would spoil the other heads); or, by
+// geometry and format, through LDS (Softmax::weights).
 // Values: p * s_V(t, g) is lane-local (each slice multiplies by its own group's
 // scale), is split once into two binary16 terms (22 significant bits), and the same B operand
 // pair serves the PV MFMAs of every group of the set: the tile of a 16-channel block is only
@@ -528,8 +528,8 @@ struct Softmax {
   LdsFloats put, get;   // LDS: where this lane leaves its weights, and finds those of its column and tokens
   __device__ __forceinline__ Softmax(State& st_, int lane_, int G_, float* stat_, int room, uint32_t xch) : st(st_), lane(lane_), stat(stat_), stat_room(room), G(G_) {
     if constexpr (LDS) {
-      static_assert(GP == 8, "rows of sixteen tokens, four of a lane's first head, then four of its second");
-      const int h = lane & (GP - 1), row = 4 * (h & 1) + (h >> 2) + (h & 2);   // (head_of: head h is value h & 1 of row quad (h >> 2) + (h & 2))
+      // rows of sixteen tokens: four of the row quads' first heads, then (GP = 8) four of their second
+      const int h = lane & (GP - 1), row = GP == 4 ? h : 4 * (h & 1) + (h >> 2) + (h & 2);   // (head_of)
       put = (LdsFloats)(uintptr_t)(xch + 4 * lane);
       get = (LdsFloats)(uintptr_t)(xch + 64 * row + 16 * (lane >> 4));
     }
@@ -617,9 +617,10 @@ struct Softmax {
   }
   // the weights 2^(score - m + lift): ea, eb of the lane's token (score layout), pa, pb of the lane's four tokens (column layout).
   // The layout change by a matrix product takes 32 cycles of the matrix core for four heads and a page, the one through
-  // LDS two short stores and one read for eight: at head_dim 64 with more than four heads, where a pair has few bytes and the compute
-  // units' clock and not the memory is what a long launch waits for, 64 x 16k tokens 156 -> 141 us, 128 x 4k..32k 287 -> 267; at
-  // head_dim 128, and with up to four heads, no difference.
+  // LDS two short stores and one read for eight.  It is used where instructions and not the memory bound the launch: at head_dim
+  // 64 with more than four heads, 64 x 16k tokens 156 -> 141 us, 128 x 4k..32k 287 -> 267; the paper's formats at head_dim 128, 8 x 8k
+  // 35.6 -> 33.7, 16 x 16k of 4-bit types 74.9 -> 72.0, long contexts alike.  The integer formats at 128, and head_dim 64 with up
+  // to four heads: no difference.  (The paper's formats at 64 leave no room for it in LDS.)
   __device__ __forceinline__ void weights(const float* sa, const float* sb, float* ea, float* eb, float* pa, float* pb) const {
     float4v ta = {0.f, 0.f, 0.f, 0.f}, tb = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -1060,7 +1061,7 @@ __global__ __launch_bounds__(256 * decode_waves_per_simd(D, FP)) __attribute__((
     if (it.j >= it.n) return;
     seq_pages(v, a.layer, uniform(a.seq_ids[it.b]), np);
   }
-  const int group = uniform(wave / wph), wave0 = group * wph;
+  const int group = whole(wave, wph), wave0 = group * wph;
   const int b = it.b, hkv = it.hkv, seq = uniform(a.seq_ids[b]), share_n = it.n > 0 ? it.n : 1;
   const int Hq = c.n_q_heads, G = Hq / c.n_kv_heads;
   const bool valid = seq >= 0 && seq < c.max_seqs;
