@@ -112,14 +112,28 @@ def test_value_scales_out_of_the_lifted_range(D, G, v_scale):
 @pytest.mark.parametrize("D,G,H,ctx,fmt,window,dead", [
     (64, 8, 8, [3000] * 70, 0, 128, 0.3),            # several heads to a workgroup
     (128, 4, 5, [9000, 40, 1, 700], 0, 1024, 0.2),   # one head to a workgroup, several items a head; heads no power of two
-    (128, 8, 3, [26000], 0, 30000, 0.0),             # lists longer than one scan, everything visible
+    (128, 8, 3, [26000], 0, 30000, 0.0),             # everything visible, many items
+    (128, 4, 2, [29000], 0, 400, 0.2),               # lists longer than one scan by one item
+    (64, 4, 1, [30000, 500], 1, 900, 0.0),           # a wide window by several items
     (64, 2, 16, [500] * 64, 1, 100, 0.0),
     (128, 4, 8, [17, 16, 300], 1, 1, 0.0),
 ], ids=lambda x: str(x)[:24].replace(" ", ""))
 def test_window_kernel_against_the_plain_kernel(D, G, H, ctx, fmt, window, dead):
     print("window:", D, G, H, len(ctx), max(ctx), fmt, window, dead, flush=True)
     c, q = _cache(D, G, H, ctx, fmt, (8, 2, 4), 21 + D + G + len(ctx), dead=dead)
-    (o, l), (ro, rl) = _both(c, q, D, window=window, q_pos=[x - 1 for x in ctx])
+    items = []
+    q_pos = [x - 1 for x in ctx]
+    pages = c.block_table[0, 0, 0].long()
+    if window == 400:     # a query in the middle: its window reaches over the 512th page of a list
+        q_pos = [int(c.slot_pos[0][pages[512]].min()) + 150]
+    (o, l), (ro, rl) = _both(c, q, D, window=window, q_pos=q_pos, items=items)
+    if window == 900:     # a long scan and a wide window, by several workgroups a head
+        assert int(items[0][0, 0]) >= 8
+    if window == 400:     # one workgroup a head, which writes the result itself; it scans 512 pages at a time and finds some in two passes
+        assert int(items[0][0, 0]) == 0x5A5A5A5A
+        seen = c.slot_pos[0][pages[:int(c.n_pages[0, 0, 0])]]
+        seen = ((seen <= q_pos[0]) & (seen > q_pos[0] - window)).any(-1)
+        assert bool(seen[:512].any()) and bool(seen[512:].any())
     assert float((o - ro).abs().max()) <= 1e-4 * max(1.0, float(ro.abs().max()))
     fin = torch.isfinite(rl)
     assert torch.equal(torch.isfinite(l), fin) and float((l[fin] - rl[fin]).abs().max()) <= 1e-4
