@@ -46,6 +46,10 @@ constexpr int kBulkFrom = 64;   // calls of more tokens take the bulk place kern
 
 // a token's place: state << 28 | index in the type's page list << 4 | slot
 constexpr uint32_t kNoPlace = 0, kOldPage = 1, kNewPage = 2;
+// In a bulk call one wave writes a new page whole if the call brings it at least so many tokens; fewer are stored by themselves, like
+// those of existing pages (256 sequences, a new page each, us, by page and by token: one token 36 and 16, four 23.5 and 16.4, eight 19 and
+// 17.8, twelve 20 and 19.8, sixteen 20.5 and 23.5).
+constexpr int kWholeFrom = 8;
 
 struct AppendWs {
   SeqPlan* plan;     // [max_seqs]
@@ -348,9 +352,9 @@ __device__ inline void grant_of(const AppendWs& ws, int n_seqs, int s, int k, in
 // One token's place, by LPT neighbouring lanes: type, page, slot, page list index; ok = 0 if it gets none; cnt = tokens that the
 // call puts into the page, if it is a new one.  enter: these lanes also record it (slot_pos, handle) and, for a token in a new
 // page, enter the page into the tables: the token in the page's first slot writes the page's row, the first token of
-// the type that wants a new page the counts.  BULK: the positions of a new page's tokens are left to who writes the page.
+// the type that wants a new page the counts.  BULK: the positions of the tokens of a page that is written whole are left to who writes it.
 struct Place {
-  int ok, cls, pid, slot, pi, cnt;
+  int ok, cls, pid, slot, pi, cnt, whole;   // whole: the page is written as one
 };
 template <int LPT, bool BULK>
 __device__ inline Place settle(const thinkv_view& v, int layer, const AppendWs& ws, const int32_t* __restrict__ tok_seq, const int32_t* __restrict__ tok_pos,
@@ -361,7 +365,7 @@ __device__ inline Place settle(const thinkv_view& v, int layer, const AppendWs& 
   const int cls = tok_class[i];
   const uint32_t at = ws.place[i];
   const int pos = tok_pos[i];
-  Place p = {0, cls > 2 ? 0 : cls, 0, 0, 0, 0};
+  Place p = {0, cls > 2 ? 0 : cls, 0, 0, 0, 0, 0};
   if (s < 0 || s >= c.max_seqs) {
     if (enter && lane == 0) atomicOr(&v.dev_status[c.max_seqs * c.n_layers], THINKV_ST_BAD_SEQ);
   } else {
@@ -385,6 +389,7 @@ __device__ inline Place settle(const thinkv_view& v, int layer, const AppendWs& 
           p.pid = v.free_stack[cls][ws.avail_old[cls] - 1 - (base + npi)];
         }
         p.cnt = n_new - kPage * npi < kPage ? n_new - kPage * npi : kPage;
+        p.whole = BULK && p.cnt >= kWholeFrom;
         if (enter && p.slot == 0) {
           if (p.ok) {
             if (lane == 0) {
@@ -393,7 +398,7 @@ __device__ inline Place settle(const thinkv_view& v, int layer, const AppendWs& 
               v.slot_mask[row] = (1u << p.cnt) - 1u;
               v.page_filled[cls][p.pid] = (uint8_t)p.cnt;
             }
-            if (!BULK)
+            if (!p.whole)
               for (int sl = p.cnt + lane; sl < kPage; sl += LPT) v.slot_pos[cls][(int64_t)p.pid * kPage + sl] = -1;
           }
           if (npi == 0 && lane == 0) {
@@ -408,7 +413,7 @@ __device__ inline Place settle(const thinkv_view& v, int layer, const AppendWs& 
     }
   }
   if (enter && lane == 0) {
-    if (p.ok && !(BULK && p.cnt > 0)) {
+    if (p.ok && !p.whole) {
       v.slot_pos[p.cls][(int64_t)p.pid * kPage + p.slot] = pos;
       atomicMax(&v.page_pos_max[p.cls][p.pid], pos);
     }
@@ -860,12 +865,12 @@ __global__ __launch_bounds__(256) void append_place_bulk_kernel(thinkv_view v, i
   {
     constexpr int LPT = 256 / kBulkTokens;
     const int u = tid / LPT;
-    Place p = {0, 0, 0, 0, 0, 0};
+    Place p = {0, 0, 0, 0, 0, 0, 0};
     if (i0 + u < n_tok) p = settle<LPT, true>(v, layer, ws, tok_seq, tok_pos, tok_class, tok_handle, i0 + u, blockIdx.y == 0);
     if (tid % LPT == 0) {
       s_cls[u] = p.cls; s_pid[u] = p.pid; s_slot[u] = p.slot;
-      if (p.ok && p.cnt == 0) atomicOr(&s_old, 1u << u);
-      if (p.ok && p.cnt > 0 && p.slot == 0) s_new[atomicAdd(&s_n_new, 1)] = NewPage{i0 + u, p.cls, p.pid, p.cnt, ws.plan[tok_seq[i0 + u]].hi};
+      if (p.ok && !p.whole) atomicOr(&s_old, 1u << u);
+      if (p.ok && p.whole && p.slot == 0) s_new[atomicAdd(&s_n_new, 1)] = NewPage{i0 + u, p.cls, p.pid, p.cnt, ws.plan[tok_seq[i0 + u]].hi};
     }
   }
   if (blockIdx.x == 0 && blockIdx.y == 0 && tid < 64) update_pools(v, ws);

@@ -68,3 +68,35 @@ def test_groups_out_of_binary16_range(n_tok):
     assert np.array_equal(hg, ob.append(0, k, v, ts, tp, cls))
     parity.compare_bookkeeping_full(ob.cache, gc)
     parity.compare_sequences(ob.cache, gc, [(0, 0, 0)], check_bytes=True)
+
+
+@pytest.mark.parametrize("D,dtype,fmt,S,lens,share", [
+    (64, torch.bfloat16, "int", 2, [9000, 300], 0.004),      # a type whose sixteen tokens lie thousands apart, over several windows
+    (128, torch.float16, "fp", 3, [5000, 17, 4097], 0.02),   # ... around the distance up to which a page is written whole
+    (64, torch.float32, "int", 700, [1] * 699 + [5], 0.3),   # new pages with a token or two, of more sequences than a round of sums
+    (64, torch.bfloat16, "int", 90, [3, 4, 5] * 30, 0.0),    # ... around the number from which a page is written whole
+], ids=lambda x: str(x)[:20].replace(" ", ""))
+def test_new_pages_of_scattered_and_few_tokens(D, dtype, fmt, S, lens, share):
+    print(f"[gpu] append, scattered: D={D} {dtype} {fmt} S={S} {max(lens)} {share}", flush=True)
+    H = 2
+    rng = np.random.default_rng(D + S)
+    geom = synth.Geometry(1, 2 * H, H, D, "f16", (8, 4, 2), fmt=fmt) if fmt == "fp" else synth.Geometry(1, 2 * H, H, D, "f16", (8, 4, 2))
+
+    def types(n):   # mostly type 2, a share of type 0, type 1 in runs
+        t = np.where(rng.random(n) < share, 0, 2).astype(np.uint8)
+        t[n // 3:n // 3 + n // 7] = 1
+        return t
+
+    cls = [types(n) for n in lens]
+    wl = synth.Workload("append-scattered", geom, 0, S, cls, [])
+    gc, ob = parity.make_gpu_cache(wl), parity.make_oracle(wl)
+    gb = parity.GpuBackend(gc)
+    ts = np.repeat(np.arange(S, dtype=np.int32), lens)
+    tp = np.concatenate([np.arange(n) for n in lens]).astype(np.int32)
+    tc = np.concatenate(cls)
+    gen = torch.Generator().manual_seed(S)
+    k, v = (torch.randn((len(ts), H, D), generator=gen).to(dtype) for _ in range(2))
+    hg = gb.append(0, k.cuda(), v.cuda(), ts, tp, tc)
+    assert np.array_equal(hg, ob.append(0, k, v, ts, tp, tc))
+    parity.compare_bookkeeping_full(ob.cache, gc)
+    parity.compare_sequences(ob.cache, gc, [(s, s, 0) for s in range(S)], check_bytes=True)
