@@ -341,7 +341,13 @@ __device__ inline void grant_of(const AppendWs& ws, int n_seqs, int s, int k, in
   const int avail = ws.avail_old[k];
   const int* const need = ws.need + k * n_seqs;
   int before = 0;
-  for (int t = threadIdx.x & (LPT - 1); t < s; t += LPT) before += need[t];
+  for (int t = threadIdx.x & (LPT - 1); t < s; t += 8 * LPT) {   // eight loads at once
+    int x[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) x[u] = need[min(t + u * LPT, s)];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) before += t + u * LPT < s ? x[u] : 0;
+  }
 #pragma unroll
   for (int d = LPT / 2; d >= 1; d >>= 1) before += __shfl_xor(before, d, 64);
   const int left = avail - before;
@@ -428,7 +434,13 @@ __device__ inline void update_pools(const thinkv_view& v, const AppendWs& ws) {
   const int lane = threadIdx.x & 63;
   for (int k = 0; k < 3; ++k) {
     int want = 0;
-    for (int t = lane; t < v.cfg.max_seqs; t += 64) want += ws.need[k * v.cfg.max_seqs + t];
+    for (int t = lane; t < v.cfg.max_seqs; t += 512) {
+      int x[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) x[u] = ws.need[k * v.cfg.max_seqs + min(t + 64 * u, v.cfg.max_seqs - 1)];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) want += t + 64 * u < v.cfg.max_seqs ? x[u] : 0;
+    }
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) want += __shfl_xor(want, d, 64);
     const int avail = ws.avail_old[k];
