@@ -129,10 +129,10 @@ static int64_t rows_bound(const thinkv_config& c, int B, int max_ctx_pages) {
 // machine, and the short sequences leave it early (96 x 8 heads of 4k..32k tokens, head_dim 128: 350 us dealt, 337 by the
 // rule below; head_dim 64, of 16k each: 229 and 246).
 // A head to a workgroup, which writes the result itself, where an item would be worth less than the merge launch: contexts of up
-// to 96 pages, 352 if every other compute unit has a head, 640 with about as many heads as compute units (half as much
+// to 96 pages, 352 if every other compute unit has a head, 1,280 with about as many heads as compute units (half as much
 // again at head_dim 64, where a page is half the work), 256 with more heads and 512 with more than two a compute unit.
 // Measured on both sides, 8 kv-heads of 128, us: 8 x 1k tokens (66 pages) 16.9 so and 17.9 dealt, 8 x 2k 20.9 and 18.4, in the
-// paper's formats 29.6 and 23.5; 24 x 3k (200 pages) 29.5 and 32.7, 17 x 8k 56 and 49; 32 x 8k 65.9 and 69.8; head_dim 64, 16 x 2 heads
+// paper's formats 29.6 and 23.5; 24 x 3k (200 pages) 29.5 and 32.7, 17 x 8k 56 and 49; 32 x 8k 65.9 and 69.8, 32 x 16k 132 and 138 (but 32 x 3.2k..32k 166 and 114); head_dim 64, 16 x 2 heads
 // of 1.5k 16.8 and 20.1.
 // More heads: workgroups of four, several to a compute unit, so that one's start and end are covered by the others', and an
 // item per so many pages: about sixteen rounds of them if every sequence were as long as the host's bound, but no
@@ -143,7 +143,7 @@ static ItemSizing size_stream(const thinkv_config& c, int B, int max_ctx_pages, 
   const int64_t pages = max_ctx_pages > 0 ? max_ctx_pages : 1;
   const int64_t most = (pages + 7) / 8, bound = rows_bound(c, B, max_ctx_pages);   // rows: what the workspace is sized for
   const bool few = heads <= cus;
-  const bool single = few ? pages <= (10 * heads >= 9 * cus ? 640 : (2 * heads > cus ? 352 : 96)) * (c.head_dim == 64 ? 3 : 2) / 2 : pages <= (heads <= 2 * cus ? 256 : 512);
+  const bool single = few ? pages <= (10 * heads >= 9 * cus ? 1280 : (2 * heads > cus ? 352 : 96)) * (c.head_dim == 64 ? 3 : 2) / 2 : pages <= (heads <= 2 * cus ? 256 : 512);
   ItemSizing z;
   *grid = 0;
   if (heads <= (c.head_dim == 64 ? 3 : 2) * cus && B <= kDealSeqs && !single) {
