@@ -279,28 +279,32 @@ struct BlockDma {
 #define TKV_SET "s_mov_b32 m0, %0\n\ts_nop 4\n\t"
 #define TKV_DMA(OFF) "global_load_lds_dwordx4 %1, %2 offset:" #OFF " nt\n\t"
 #define TKV_SOME(OFF) "s_mov_b64 exec, %3\n\t" TKV_DMA(OFF) "s_mov_b64 exec, -1"
-  // lds: LDS byte address, blk: the block in memory (both wave-uniform), voff: 16 * lane; all lanes are on
+  // lds: LDS byte address, blk: the block in memory (both wave-uniform), voff: 16 * lane.  All lanes are on, before and after:
+  // kernels of these files branch on scalars around everything that gets here.
   static __device__ __forceinline__ void issue(uint32_t lds, const uint8_t* blk, uint32_t voff) {
     const uint64_t on = (1ull << kRest) - 1ull;
     if constexpr (kFull == 0) {
-      asm volatile(TKV_SET TKV_SOME(0)::"s"(lds), "v"(voff), "s"(blk), "s"(on) : "memory");
+      asm volatile(TKV_SET TKV_SOME(0)::"s"(lds), "v"(voff), "s"(blk), "s"(on) : "m0", "memory");
     } else if constexpr (kFull == 1) {
-      asm volatile(TKV_SET TKV_DMA(0) TKV_SOME(1024)::"s"(lds), "v"(voff), "s"(blk), "s"(on) : "memory");
+      asm volatile(TKV_SET TKV_DMA(0) TKV_SOME(1024)::"s"(lds), "v"(voff), "s"(blk), "s"(on) : "m0", "memory");
     } else if constexpr (kFull == 2 && kRest != 0) {
-      asm volatile(TKV_SET TKV_DMA(0) TKV_DMA(1024) TKV_SOME(2048)::"s"(lds), "v"(voff), "s"(blk), "s"(on) : "memory");
+      asm volatile(TKV_SET TKV_DMA(0) TKV_DMA(1024) TKV_SOME(2048)::"s"(lds), "v"(voff), "s"(blk), "s"(on) : "m0", "memory");
     } else if constexpr (kFull == 2) {
-      asm volatile(TKV_SET TKV_DMA(0) TKV_DMA(1024)::"s"(lds), "v"(voff), "s"(blk) : "memory");
+      asm volatile(TKV_SET TKV_DMA(0) TKV_DMA(1024)::"s"(lds), "v"(voff), "s"(blk) : "m0", "memory");
     } else {
       static_assert(kFull != 3, "no format has such blocks");
-      asm volatile(TKV_SET TKV_DMA(0) TKV_DMA(1024) TKV_DMA(2048) TKV_DMA(3072)::"s"(lds), "v"(voff), "s"(blk) : "memory");
+      asm volatile(TKV_SET TKV_DMA(0) TKV_DMA(1024) TKV_DMA(2048) TKV_DMA(3072)::"s"(lds), "v"(voff), "s"(blk) : "m0", "memory");
       if constexpr (kRest != 0)   // beyond the reach of the offset
-        asm volatile(TKV_SET TKV_SOME(0)::"s"(lds + 4096u), "v"(voff), "s"(blk + 4096), "s"(on) : "memory");
+        asm volatile(TKV_SET TKV_SOME(0)::"s"(lds + 4096u), "v"(voff), "s"(blk + 4096), "s"(on) : "m0", "memory");
     }
   }
 #undef TKV_SOME
 #undef TKV_DMA
 #undef TKV_SET
 };
+// LDS byte address of the dynamic LDS: what is written below by hand (rings, tickets, lists) and what goes through the array's name
+// count from one place
+__device__ __forceinline__ uint32_t lds_address(void* lds) { return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds; }
 // a wave-uniform pointer that the compiler cannot prove to be one, into scalar registers
 __device__ __forceinline__ const uint8_t* scalar_ptr(const uint8_t* p) {
   const uint64_t u = (uint64_t)(uintptr_t)p;
@@ -1066,7 +1070,8 @@ __global__ __launch_bounds__(256 * decode_waves_per_simd(D, FP)) __attribute__((
   const int Hq = c.n_q_heads, G = Hq / c.n_kv_heads;
   const bool valid = seq >= 0 && seq < c.max_seqs;
   Stream q;
-  q.ticket = (LdsCounter)(uintptr_t)(W * kRing + 4 * group);
+  const uint32_t base = lds_address(tkv_lds);
+  q.ticket = (LdsCounter)(uintptr_t)(base + W * kRing + 4 * group);
   q.lane = lane;
   q.max_pages = c.max_pages;
   q.tab = (ConstI32)(uintptr_t)(v.block_table + (valid ? table_base(c, seq, a.layer, 0) : 0));
@@ -1094,7 +1099,7 @@ __global__ __launch_bounds__(256 * decode_waves_per_simd(D, FP)) __attribute__((
   WaveState<D, GP, Query<D, GP, FP>::NSET> st;
   clear(st);
   __syncthreads();
-  const uint32_t ring = (uint32_t)(wave * kRing), xch = (uint32_t)(W * kRing + kTicketBytes + exchange_bytes(D, GP, FP) * wave);
+  const uint32_t ring = base + wave * kRing, xch = base + W * kRing + kTicketBytes + exchange_bytes(D, GP, FP) * wave;
   q.look();
   while (q.sec < 3) {
     const int x = q.sec, k = Stream::pick(x, q.kind0, q.kind1, q.kind2);
@@ -1155,7 +1160,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     a.alloc[2 * (b * H + h0 + tid)] = (b * H + h0 + tid) * a.per_head;
     a.alloc[2 * (b * H + h0 + tid) + 1] = n;
   }
-  const uint32_t xch = (uint32_t)(window_lds_bytes(D) + exchange_bytes(D, GP, FP) * wave);
+  const uint32_t lds = lds_address(tkv_lds), xch = lds + window_lds_bytes(D) + exchange_bytes(D, GP, FP) * wave;
   int32_t* const lists = (int32_t*)(tkv_lds + kWindowWaves * kRing);   // [type][id, mask, list position][kWindowBlock]
   int32_t* const counts = lists + 9 * kWindowBlock;                    // [type][wave]
   Query<D, GP, FP> query;
@@ -1236,7 +1241,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         VisiblePages q;
         q.n = k == 0 ? total[0] : (k == 1 ? total[1] : total[2]);
         if (q.n == 0) continue;
-        const uint32_t at = (uint32_t)(kWindowWaves * kRing + 3 * k * kWindowBlock * 4);
+        const uint32_t at = lds + kWindowWaves * kRing + 3 * k * kWindowBlock * 4;
         q.pid = (VisiblePages::Words)(uintptr_t)at;
         q.msk = (VisiblePages::Words)(uintptr_t)(at + kWindowBlock * 4);
         q.idx = (VisiblePages::Words)(uintptr_t)(at + kWindowBlock * 8);
@@ -1246,7 +1251,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         float* stat = nullptr;
         int stat_room = 0;
         if constexpr (STAT) stat = stat_row(c, a, b, hkv, k, np, &stat_room);
-        TKV_BY_WIDTH(bits, stream_pairs<kRing>(cr, q, v, k, hkv, (uint32_t)(wave * kRing)))
+        TKV_BY_WIDTH(bits, stream_pairs<kRing>(cr, q, v, k, hkv, lds + wave * kRing))
       }
     }
     __syncthreads();   // the lists have been used
