@@ -67,6 +67,18 @@ def _both(c, q, D, bound=None, window=0, q_pos=None, ids=None, items=None):
     return res
 
 
+def _close(o, l, ro, rl):
+    """Every sequence's outputs to 2e-5 of its own largest one: products whose second operand holds 22 bits are 2e-7 off, and with 11
+    bits, one term of the pair lost, 2e-4.  Below that stands what the sums themselves lose: codes and zero-points are summed
+    apart, about 4 each for values of N(0, 1), with a rounding of 2^-25 of that for each of some hundred additions a wave and item,
+    1.2e-7 * sqrt(100) = 1.2e-6; the largest output of 56,000 tokens is 0.027, so that a lost term would still be seen (6e-6)."""
+    for b in range(len(o)):
+        fin = torch.isfinite(rl[b])
+        assert torch.equal(torch.isfinite(l[b]), fin) and (not fin.any() or float((l[b][fin] - rl[b][fin]).abs().max()) <= 2e-5 * max(1.0, float(rl[b][fin].abs().max())))
+        far, top = float((o[b] - ro[b]).abs().max()), float(ro[b].abs().max())
+        assert far <= max(2e-5 * top, 1.2e-6), (b, far, top)
+
+
 @pytest.mark.parametrize("D,G,H,ctx,fmt,bits,dead", [
     (128, 4, 1, [9000], 0, (8, 2, 4), 0.0),                    # several items a head, every ring wraps
     (64, 8, 2, [12000, 1], 0, (8, 4, 2), 0.3),                 # ... and runs of whole pages with nothing live
@@ -74,18 +86,20 @@ def _both(c, q, D, bound=None, window=0, q_pos=None, ids=None, items=None):
     (64, 1, 3, [700, 129, 128, 127, 256, 8], 0, (8, 8, 8), 0.2),
     (128, 4, 1, [9000], 1, (2, 4, 8), 0.0),
     (64, 8, 2, [5000, 40, 1], 1, (8, 2, 4), 0.3),
-    (64, 8, 8, [1500] * 127 + [3000], 0, (8, 2, 4), 0.0),      # more heads than compute units: rows limited by the workspace
-    (64, 8, 16, [900] * 70, 1, (4, 4, 4), 0.0),
+    (64, 8, 8, [700] * 127 + [56000], 0, (8, 2, 4), 0.0),      # more heads than are dealt: six items for the longest, as the workspace allows
+    (64, 8, 16, [900] * 69 + [30000], 1, (4, 4, 4), 0.0),      # ... in the paper's formats
+    (128, 4, 8, [300] * 66 + [20000], 0, (8, 2, 4), 0.1),
+    (64, 8, 8, [1500] * 128, 0, (8, 2, 4), 0.0),               # ... of one item each
     (128, 4, 8, [300] * 40, 0, (8, 2, 4), 0.5),
 ], ids=lambda x: str(x)[:24].replace(" ", ""))
 def test_stream_kernel_against_the_plain_kernel(D, G, H, ctx, fmt, bits, dead):
     print("stream:", D, G, H, len(ctx), max(ctx), fmt, bits, dead, flush=True)
     c, q = _cache(D, G, H, ctx, fmt, bits, 11 + D + G + len(ctx), dead=dead)
-    (o, l), (ro, rl) = _both(c, q, D)
-    # binary32 sums of at most 12,000 products whose second operand holds 22 bits: about 1e-6 of the largest value
-    assert float((o - ro).abs().max()) <= 1e-4 * max(1.0, float(ro.abs().max()))
-    fin = torch.isfinite(rl)
-    assert torch.equal(torch.isfinite(l), fin) and float((l[fin] - rl[fin]).abs().max()) <= 1e-4
+    items = []
+    (o, l), (ro, rl) = _both(c, q, D, items=items)
+    if max(ctx) >= 20000:
+        assert int(items[0][-1, 0]) == {56000: 6, 30000: 4, 20000: 3}[max(ctx)] and int(items[0][0, 0]) == 1
+    _close(o, l, ro, rl)
 
 
 @pytest.mark.parametrize("bound", [0, 1, 40, 100000])
@@ -94,7 +108,7 @@ def test_stream_kernel_with_a_wrong_context_bound(bound):
     print("stream bound:", bound, flush=True)
     c, q = _cache(128, 4, 2, [1300, 200, 77], 0, (8, 2, 4), 5)
     (o, l), (ro, rl) = _both(c, q, 128, bound)
-    assert float((o - ro).abs().max()) <= 1e-4 and float((l - rl).abs().max()) <= 1e-4
+    _close(o, l, ro, rl)
 
 
 @pytest.mark.parametrize("D,G,v_scale", [(128, 4, 60.0), (64, 8, 60.0), (128, 8, 3000.0), (64, 4, 8000.0)])
@@ -134,9 +148,7 @@ def test_window_kernel_against_the_plain_kernel(D, G, H, ctx, fmt, window, dead)
         seen = c.slot_pos[0][pages[:int(c.n_pages[0, 0, 0])]]
         seen = ((seen <= q_pos[0]) & (seen > q_pos[0] - window)).any(-1)
         assert bool(seen[:512].any()) and bool(seen[512:].any())
-    assert float((o - ro).abs().max()) <= 1e-4 * max(1.0, float(ro.abs().max()))
-    fin = torch.isfinite(rl)
-    assert torch.equal(torch.isfinite(l), fin) and float((l[fin] - rl[fin]).abs().max()) <= 1e-4
+    _close(o, l, ro, rl)
 
 
 @pytest.mark.parametrize("D,G,ctx,fmt,dead,bound", [
@@ -212,7 +224,4 @@ def test_items_dealt_over_a_batch(D, G, H, ctx, fmt, ids, bound):
         assert bool((n[order, 0].diff() >= 0).all())
         rows = torch.cat([torch.arange(int(r), int(r) + int(m)) for r, m in zip(row0.flatten(), n.flatten())])
         assert len(rows.unique()) == len(rows)
-        for b in range(len(part)):
-            fin = torch.isfinite(rl[b])
-            assert torch.equal(torch.isfinite(l[b]), fin) and (not fin.any() or float((l[b][fin] - rl[b][fin]).abs().max()) <= 1e-4)
-            assert float((o[b] - ro[b]).abs().max()) <= 2e-5 * max(float(ro[b].abs().max()), 1e-3)
+        _close(o, l, ro, rl)
