@@ -48,8 +48,10 @@ constexpr int kBulkFrom = 64;   // calls of more tokens take the bulk place kern
 constexpr uint32_t kNoPlace = 0, kOldPage = 1, kNewPage = 2;
 // In a bulk call one wave writes a new page whole if the call brings it at least so many tokens; fewer are stored by themselves, like
 // those of existing pages (256 sequences, a new page each, us, by page and by token: one token 36 and 16, four 23.5 and 16.4, eight 19 and
-// 17.8, twelve 20 and 19.8, sixteen 20.5 and 23.5).
-constexpr int kWholeFrom = 8;
+// 17.8, twelve 20 and 19.8, sixteen 20.5 and 23.5).  A sequence that brings many tokens has three such pages at most: they are
+// written whole too, rather than by a unit of sixteen rows in each block that holds some of their tokens (prompts of 1k to 4k tokens in
+// the paper's formats 157 us, whole 150).
+constexpr int kWholeFrom = 8, kManyTokens = 64;
 
 struct AppendWs {
   SeqPlan* plan;     // [max_seqs]
@@ -395,7 +397,7 @@ __device__ inline Place settle(const thinkv_view& v, int layer, const AppendWs& 
           p.pid = v.free_stack[cls][ws.avail_old[cls] - 1 - (base + npi)];
         }
         p.cnt = n_new - kPage * npi < kPage ? n_new - kPage * npi : kPage;
-        p.whole = BULK && p.cnt >= kWholeFrom;
+        p.whole = BULK && (p.cnt >= kWholeFrom || pl.hi - pl.lo >= kManyTokens);
         if (enter && p.slot == 0) {
           if (p.ok) {
             if (lane == 0) {
@@ -893,21 +895,23 @@ __global__ __launch_bounds__(256) void append_place_bulk_kernel(thinkv_view v, i
   for (int q = wave; q < n_new; q += 4) {   // the new pages' tokens: the next of the type, from the first on
     const NewPage np = s_new[q];
     int found = 0;
-    // (eight loads at once: the sixteen tokens of a rare type may lie far apart.  32,768 tokens, a second type every 4,000: 164 us
-    // with one load at a time, now 123; every 1,000 122 and 112; types in runs of 64 to 192 tokens 115 either way)
-    for (int i = np.first; i < np.end && found < np.cnt; i += 512) {
+    auto take = [&](int i, int cl) {   // tokens i + lane, of types cl
+      const int t = i + lane;
+      const bool is = t < np.end && cl == np.cls;
+      const uint64_t all = __ballot(is);
+      const int at = found + __popcll(all & ((1ull << lane) - 1ull));
+      if (is && at < np.cnt) s_tok[q][at] = t;
+      found += __popcll(all);
+    };
+    take(np.first, tok_class[min(np.first + lane, np.end - 1)]);
+    // (beyond the next 64 tokens eight loads at once: the sixteen tokens of a rare type may lie far apart.  32,768 tokens, a second type
+    // every 4,000: 164 us with one load at a time, now 123; every 1,000 122 and 112; types in runs of 64 to 192 tokens 115 either way)
+    for (int i = np.first + 64; i < np.end && found < np.cnt; i += 512) {
       int cl[8];
 #pragma unroll
       for (int u = 0; u < 8; ++u) cl[u] = tok_class[min(i + 64 * u + lane, np.end - 1)];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int t = i + 64 * u + lane;
-        const bool is = t < np.end && cl[u] == np.cls;
-        const uint64_t all = __ballot(is);
-        const int at = found + __popcll(all & ((1ull << lane) - 1ull));
-        if (is && at < np.cnt) s_tok[q][at] = t;
-        found += __popcll(all);
-      }
+      for (int u = 0; u < 8; ++u) take(i + 64 * u, cl[u]);
     }
     found = min(found, np.cnt);   // (fewer only if the sequence ids of the call decrease somewhere)
     if (lane == 0) s_new[q].cnt = found;
