@@ -3,10 +3,12 @@
 //
 // Same plan as for the integer formats (decode_mfma_kernel.h): the codes go to v_mfma_f32_16x16x32_f16 without being
 // dequantised, the scales are applied to what the matrix cores return.  What differs:
-//   * a code is a sign and a small IEEE-style magnitude.  An IEEE-style format nests in a wider one: the magnitude
-//     bits placed right under a binary16 exponent ARE the code's value times a power of two (2^-14 for E2M1 and the
-//     ternary bit, 2^-8 for E4M3), subnormal codes included; the sign goes to bit 15.  Two shifts and two masks per
-//     operand register instead of the integer formats' one and a half;
+//   * E4M3 and E2M1 codes become binary16 numbers by gfx950's conversions (two codes in neighbouring bytes or nibbles an
+//     instruction; exact, every value is a normal binary16 number); the keys of ternary codes too, spread to nibbles.  The keys come out
+//     in another order of channels, in which the query is kept (QRegsFp); the two slots of a value register come from
+//     different halves of a word and take a byte permutation on top;
+//   * a value's ternary code is a sign and a magnitude bit: the bit placed right under a binary16 exponent IS the code's value
+//     times 2^-14, the sign goes to bit 15;
 //   * there are no zero-points, so the zero-point sums and the group sums of the query are gone;
 //   * a group is 16 channels, half the K extent of the instruction: a slice of columns carries one group of 16, its
 //     second operand is zero over the other half of the 32 channels, and there are twice as many column sets;
@@ -18,22 +20,48 @@
 
 namespace thinkv {
 
+// Codes to operand registers of two binary16 numbers.  Shifts and masks (the magnitude bits under an exponent) took four
+// instructions a register; now one for keys, one and a half (E4M3) or two (E2M1) for values, and three for the keys of ternary codes,
+// which are spread to E2M1's nibbles.
+// 16 x 24k..32k tokens of 2-, 4- and 8-bit types, head_dim 128, four heads: 133.2 us with shifts and masks, 129.0 so; all 4-bit 121
+// and 107, eight heads a group 121 and 112; head_dim 64, 32 x 16k..32k, eight heads 141 and 127; all 8-bit 172 and 170, all 2-bit alike.
 template <int BITS>
 struct FldFp {
   static constexpr int FPH = 16 / BITS;
-  static constexpr int EXP = BITS == 8 ? 8 : 14;   // operand = value of the code * 2^-EXP
-  __device__ static __forceinline__ uint32_t shl(uint32_t x, int s) { return s >= 0 ? (x << s) : (x >> (-s)); }
-  // operand register (two codes: low / high half) for field f of the chunk words w[]
-  __device__ static __forceinline__ uint32_t get(const uint32_t* w, int f) {
-    const int word = f / FPH, pos = f % FPH;
-    const uint32_t x = w[word];
-    if constexpr (BITS == 4) {          // [s e1 e0 m] at bits 4 pos .. 4 pos + 3 of each half
-      return (shl(x, 9 - 4 * pos) & 0x0E000E00u) | ((x << (12 - 4 * pos)) & 0x80008000u);
-    } else if constexpr (BITS == 2) {   // [s m] at bits 2 pos, 2 pos + 1
-      return (shl(x, 10 - 2 * pos) & 0x04000400u) | ((x << (14 - 2 * pos)) & 0x80008000u);
-    } else {                            // [s eeee mmm] in the low (pos 0) or high byte of each half
-      if (pos == 0) return ((x & 0x007F007Fu) << 7) | ((x & 0x00800080u) << 8);
-      return ((x >> 1) & 0x3F803F80u) | (x & 0x80008000u);
+  static constexpr int VEXP = BITS == 2 ? 14 : 0;   // value operand = value of the code * 2^-VEXP
+  static __device__ __forceinline__ uint32_t fp8(uint32_t x, bool upper) {   // bytes 0, 1 or bytes 2, 3
+    return upper ? __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(x, 1.0f, true))
+                 : __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(x, 1.0f, false));
+  }
+  static __device__ __forceinline__ uint32_t fp4(uint32_t x, int byte) {     // the nibbles of a byte
+    return byte == 0   ? __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(x, 1.0f, 0))
+           : byte == 1 ? __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(x, 1.0f, 1))
+           : byte == 2 ? __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(x, 1.0f, 2))
+                       : __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(x, 1.0f, 3));
+  }
+  // two ternary codes [s m] of the lower or upper half of every byte -> two E2M1 codes [s 0 m 0]
+  static __device__ __forceinline__ uint32_t spread(uint32_t x, bool upper) {
+    return upper ? ((x >> 3) & 0x02020202u) | ((x >> 2) & 0x08080808u) | ((x >> 1) & 0x20202020u) | (x & 0x80808080u)
+                 : ((x << 1) & 0x02020202u) | ((x << 2) & 0x08080808u) | ((x << 3) & 0x20202020u) | ((x << 4) & 0x80808080u);
+  }
+  // register i (0..3) of the lane's eight channels of group g of 32: channels (0, 2), (1, 3), (4, 6), (5, 7), the order of QRegsFp::pairs
+  // (a field of the chunk is two neighbouring channels, one in each half of its word; the group's are fields 4 g .. + 3)
+  static __device__ __forceinline__ uint32_t keys(const uint32_t* w, int g, int i) {
+    if constexpr (BITS == 8) return fp8(w[2 * g + (i >> 1)], i & 1);
+    else if constexpr (BITS == 4) return fp4(w[g], (i >> 1) + 2 * (i & 1));
+    else return fp4(spread(w[g >> 1], i >> 1), (g & 1) + 2 * (i & 1));
+  }
+  // field f of a value chunk: two slots (low / high half) of one channel.  (Two neighbouring fields share their first instructions.)
+  static __device__ __forceinline__ uint32_t values(const uint32_t* w, int f) {
+    const uint32_t x = w[f / FPH];
+    const int pos = f % FPH;
+    if constexpr (BITS == 8) {
+      return fp8(__builtin_amdgcn_perm(0u, x, 0x03010200u), pos);
+    } else if constexpr (BITS == 4) {
+      const uint32_t lo = fp4(x, pos >> 1), hi = fp4(x, 2 + (pos >> 1));   // (fields f & ~1, f | 1) of either half
+      return f & 1 ? __builtin_amdgcn_perm(hi, lo, 0x07060302u) : __builtin_amdgcn_perm(hi, lo, 0x05040100u);
+    } else {   // (spread and put together again it would be no less)
+      return ((10 - 2 * pos >= 0 ? x << (10 - 2 * pos & 31) : x >> (2 * pos - 10 & 31)) & 0x04000400u) | ((x << (14 - 2 * pos)) & 0x80008000u);
     }
   }
 };
@@ -58,10 +86,19 @@ struct PairRegsFp {
 };
 
 // per column set the eight binary16 values of (the lane's head, channels 32 G + 8 qd ..) where those channels lie in
-// the group of 16 of the lane's slice; zeros otherwise
+// the group of 16 of the lane's slice; zeros otherwise.  In the order in which FldFp::keys gives the codes.
 template <int NSET>
 struct QRegsFp {
   H8 q[NSET];
+  static __device__ __forceinline__ H8 pairs(const H8& x) {   // channels (0, 1), (2, 3), .. -> (0, 2), (1, 3), ..
+    H8 p;
+#pragma unroll
+    for (int i = 0; i < 4; i += 2) {
+      p.u[i] = __builtin_amdgcn_perm(x.u[i + 1], x.u[i], 0x05040100u);
+      p.u[i + 1] = __builtin_amdgcn_perm(x.u[i + 1], x.u[i], 0x07060302u);
+    }
+    return p;
+  }
 };
 
 // four scale bytes (slots 0..3 of the lane's quad) -> two registers of binary16 pairs, each scale times 2^-8
@@ -100,11 +137,11 @@ struct ClassRunnerFp {
     neg1 = -1.0f;
     asm volatile("" : "+v"(neg1));
     if constexpr (BITS == 8) {
-      sm.kappa = 256.0f * c.fp8_scale[0] * a.scale_log2e;
-      tile_out = c.fp8_scale[1] * (1.0f / (float)(1 << 16)) * (1.0f / (float)(1 << kLift));
+      sm.kappa = c.fp8_scale[0] * a.scale_log2e;
+      tile_out = c.fp8_scale[1] * (1.0f / (float)(1 << 24)) * (1.0f / (float)(1 << kLift));
     } else {
-      sm.kappa = 4194304.0f * a.scale_log2e;                                // 2^14 (codes) * 2^8 (scales)
-      tile_out = 0.25f * (1.0f / (float)(1 << kLift));                      // 2^(14 + 8 - 24 - lift)
+      sm.kappa = 256.0f * a.scale_log2e;                                    // (scales: 2^8)
+      tile_out = (float)(1 << F::VEXP) * (1.0f / (float)(1 << 16)) * (1.0f / (float)(1 << kLift));   // 2^(VEXP + 8 - 24 - lift)
     }
 #pragma unroll
     for (int s = 0; s < NSET; ++s) {
@@ -172,7 +209,7 @@ struct ClassRunnerFp {
       const bool first = (2 * g) % CS == 0;
       H8 ka;
 #pragma unroll
-      for (int vv = 0; vv < 4; ++vv) ka.u[vv] = F::get(r.kw, 4 * g + vv);
+      for (int vv = 0; vv < 4; ++vv) ka.u[vv] = F::keys(r.kw, g, vv);
       c[set] = __builtin_amdgcn_mfma_f32_16x16x32_f16(bq[g].h, ka.h, first ? zero : c[set], 0, 0, 0);
     }
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
@@ -236,10 +273,10 @@ struct ClassRunnerFp {
       for (int mm = 0; mm < CS; ++mm) {
         const int mb = CS * set + mm;   // a 16-channel block is a group
         H8 va;
-        va.u[0] = F::get(r.a.vw, 0 * NM + mb);
-        va.u[1] = F::get(r.a.vw, 1 * NM + mb);
-        va.u[2] = F::get(r.b.vw, 0 * NM + mb);
-        va.u[3] = F::get(r.b.vw, 1 * NM + mb);
+        va.u[0] = F::values(r.a.vw, 0 * NM + mb);
+        va.u[1] = F::values(r.a.vw, 1 * NM + mb);
+        va.u[2] = F::values(r.b.vw, 0 * NM + mb);
+        va.u[3] = F::values(r.b.vw, 1 * NM + mb);
         st.o[mb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(va.h, hi.h, st.o[mb], 0, 0, 0);
         st.o[mb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(va.h, lo.h, st.o[mb], 0, 0, 0);
       }

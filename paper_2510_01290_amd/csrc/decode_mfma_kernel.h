@@ -907,7 +907,7 @@ struct Query {
         // 32 G + 8 qd .. of its head where those lie in its slice's group (qd / 2 = parity of the group), zeros otherwise
         const int g16 = s * CS + glc;
         const bool mine = used && (g16 & 1) == (qd >> 1);
-        const H8 t = read8(a, at + 32 * (g16 >> 1));
+        const H8 t = decltype(qf)::pairs(read8(a, at + 32 * (g16 >> 1)));
 #pragma unroll
         for (int w4 = 0; w4 < 4; ++w4) qf.q[s].u[w4] = mine ? t.u[w4] : 0u;
       } else {

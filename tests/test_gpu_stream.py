@@ -225,3 +225,26 @@ def test_items_dealt_over_a_batch(D, G, H, ctx, fmt, ids, bound):
         rows = torch.cat([torch.arange(int(r), int(r) + int(m)) for r, m in zip(row0.flatten(), n.flatten())])
         assert len(rows.unique()) == len(rows)
         _close(o, l, ro, rl)
+
+
+@pytest.mark.parametrize("D,G,window", [(128, 4, 0), (128, 8, 0), (64, 8, 0), (64, 3, 0), (128, 4, 700)])
+def test_every_code_of_the_papers_formats(D, G, window):
+    """keys and values that take every E4M3 code (subnormal ones included), and groups of many sizes for the other types: each
+    code reaches the matrix cores as the number that it is, in its own channel and slot"""
+    print("stream, every code:", D, G, window, flush=True)
+    H, n, scale = 2, 3 * 16 * 40, 0.0625
+    code = np.arange(127)
+    mag = np.where(code < 8, code * 2.0 ** -9, (1 + code % 8 / 8.0) * 2.0 ** (code // 8 - 7.0)) * scale
+    rng = np.random.default_rng(71 + D + G)
+    at = (np.arange(n * H * D) * 31 + rng.integers(0, 3, n * H * D)) % 127   # (a permutation of the codes, shaken)
+    row = lambda: torch.from_numpy((mag[rng.permutation(at)] * rng.choice([-1.0, 1.0], n * H * D)).reshape(n, H, D)).to("cuda:0").float()  # noqa: E731
+    c = B.Cache(1, G * H, H, D, (8, 4, 2), 1, n // 16 + 3, [n // 16 + 3] * 3, fmt=B.FMT_FP, fp8_scale=(scale, scale))
+    d = lambda x: torch.from_numpy(x).to("cuda:0")  # noqa: E731
+    k, v = row(), row()
+    B.thinkv_append_quantized(c, 0, k, v, d(np.zeros(n, np.int32)), d(np.arange(n, dtype=np.int32)), d((np.arange(n) // 16 % 3).astype(np.uint8)),
+                              torch.empty(n, dtype=torch.int32, device="cuda:0"))
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(D + G)
+    q = (torch.randn((1, G * H, D), generator=gen, device="cuda:0") * 0.05).to(torch.bfloat16)
+    (o, l), (ro, rl) = _both(c, q, D, window=window, q_pos=[n - 1])
+    _close(o, l, ro, rl)
