@@ -61,15 +61,15 @@ static int check_view(const thinkv_view* v) {
   return THINKV_OK;
 }
 
-// Work-item sizes of the window kernel (items are single waves), of the plain kernel (workgroups of four waves, three to a
-// compute unit) and, with fast = true and no window, the row count the workspace of a full-attention call is sized for.  An
-// item pays a fixed price (query set-up, three type switches, its partial row), so it is given at least a few page
+// Item sizes of the plain kernel (fast = false: workgroups of four waves, three to a compute unit), and the row counts that the workspace
+// is sized for (rows_bound: the most over both kernels, with and without a window).  The fast kernel sizes its launches by
+// size_stream and size_window, inside that bound; with fast = true this function only says how many rows a caller has to provide, and
+// what callers provide does not change.
+// An item pays a fixed price (query set-up, type switches, its partial row), so it is given at least a few page
 // pairs.  Where the launch has few (query, kv-head) pairs, the items of the longest sequence fill
-// the machine exactly once; where it has many, an item per so many pages, about sixteen rounds of
-// them if every sequence were as long as the host's bound.
-// A sliding-window layer is another matter: only the pages that hold one of the last W positions
-// are worked on, the rest of the page list is merely scanned (a few bytes a page), so the fixed
-// price of an item dominates: an item scans at least 64 pages per wave.
+// the machine exactly once; where it has many, an item per so many pages, a few rounds of
+// them if every sequence were as long as the host's bound.  With a window most pages are merely scanned (a few bytes a page), so
+// an item takes more of them.
 static int compute_units() {
   static int cached[64];
   int dev = 0;
@@ -209,7 +209,7 @@ static int decode_common(const thinkv_view* view, int32_t layer, const void* q, 
   int rc = check_view(view);
   if (rc) return rc;
   if (B < 0 || layer < 0 || layer >= view->cfg.n_layers || window < 0 || max_ctx_pages < 0) return THINKV_E_INVALID_ARG;
-  if (B > view->cfg.max_seqs) return THINKV_E_INVALID_ARG;   // one row of work counters per query
+  if (B > view->cfg.max_seqs) return THINKV_E_INVALID_ARG;   // at most a query per sequence of the view
   if (!(softmax_scale > 0.0f) || !(softmax_scale < 3.0e38f)) return THINKV_E_INVALID_ARG;   // also rejects NaN
   if (B == 0) return THINKV_OK;
   if (!q || !out || !seq_ids || !workspace || (window > 0 && !q_pos)) return THINKV_E_INVALID_ARG;

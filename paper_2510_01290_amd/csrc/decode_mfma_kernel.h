@@ -1131,13 +1131,15 @@ __global__ __launch_bounds__(256 * decode_waves_per_simd(D, FP)) __attribute__((
   }
 }
 
-// Sliding-window layers.  Little is visible (a window of 128 tokens: some twenty pages of a list of a thousand), so the
-// scan of the page lists is most of the work: mask and id, page_pos_max, and where that reaches into the window the
+// Sliding-window layers.  Little is visible (a window of 128 tokens: some twenty pages of a list of a thousand), so the page
+// lists are scanned: mask and id, page_pos_max, and where that reaches into the window the
 // sixteen positions, three dependent loads.  A workgroup of eight waves scans for `hg` kv-heads at once, a page of
 // each type per thread with the three chains side by side, leaves the visible pages in LDS in list order, and its waves then
 // attend them, 8 / hg waves to a head; partials are folded in LDS, so a head with one item is finished here.
-// (One wave per head and third of the lists, each scanning for itself 64 pages at a time: 128 x 4k..32k tokens, window 128,
-// 64 heads, head_dim 64: 52 us; now 29, most of it the arithmetic of pages with one or two visible slots each.)
+// What bounds it is latency: the scan's chains, then the few page pairs a wave has of each type (with one or two visible slots
+// a page), whose loads little else covers.  128 x 4k..32k tokens, window 128, 64 heads, head_dim 64: the kernel takes 27.6 us, 11.3 with
+// the attending left out; vector ALUs busy 18 %, matrix cores 2 %.  (One wave per head and third of the lists, each scanning for
+// itself 64 pages at a time: 52 us a call, 30 now.)
 template <int D, int GP, bool STAT, bool FP>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void decode_window_kernel(thinkv_view v, DecodeArgs a) {
   constexpr int kRing = window_ring_bytes(D), kRow = D + kRowPad;

@@ -20,8 +20,8 @@
 // mean of products between points: x.c_j = mean over the members i of x.x_i, |c_j|^2 = mean over the members of
 // x_i.c_j.  So the channels are walked once: all products between the points of the segment (the Gram matrix, at most
 // 256 x 256, its lower triangle kept in LDS), and an iteration is n^2 additions from LDS.  (Products of the points with
-// the centroids in every iteration walked all channels up to nine times: 318 segments of ~108 tokens, 1,024 channels,
-// 1,050 us; now 150 us.)  A centroid is represented by the set of points it is the mean of: at the start one
+// the centroids in every iteration walked all channels up to nine times: 314 segments of ~110 tokens, 1,024 channels,
+// 1,050 us; now 177, and the gather 37.)  A centroid is represented by the set of points it is the mean of: at the start one
 // point, later the members, and for a cluster that has lost its last member the members it had before.
 // The products run on the matrix cores; a dequantised key does not
 // fit binary16 and the binary32 matrix instruction is slow, so every number enters as the sum of
