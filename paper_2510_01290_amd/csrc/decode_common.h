@@ -127,7 +127,7 @@ struct Deal {
   int items;      // all of them
   int wph;        // waves of an item
   ItemLoc it;     // this wave's item (n = 0: none)
-  int np[3];      // its sequence's pages by type
+  int seq, np[3]; // its sequence, that one's pages by type
 };
 // x / y of numbers below 2^20 (the compiler's integer division takes thirty instructions)
 __device__ __forceinline__ int whole(int x, int y) { return uniform((int)(((float)x + 0.5f) * __builtin_amdgcn_rcpf((float)y))); }
@@ -137,13 +137,13 @@ __device__ inline Deal deal_item(const thinkv_view& v, const DecodeArgs& a, int 
   const thinkv_config& c = v.cfg;
   const int H = c.n_kv_heads, lane = threadIdx.x & 63;
   auto add = [](auto x, auto y) { return x + y; };
-  int p[kU][3], tot[kU], most = 0;   // pages of sequences lane, lane + 64, ...
+  int ids[kU], p[kU][3], tot[kU], most = 0;   // sequences lane, lane + 64, ..., their pages
   float all = 0.f;
 #pragma unroll
   for (int u = 0; u < kU; ++u) {
-    p[u][0] = p[u][1] = p[u][2] = 0;
+    ids[u] = p[u][0] = p[u][1] = p[u][2] = 0;
     if (64 * u < a.B) {
-      const int seq = a.seq_ids[min(64 * u + lane, a.B - 1)];
+      const int seq = ids[u] = a.seq_ids[min(64 * u + lane, a.B - 1)];
       if (64 * u + lane < a.B && seq >= 0 && seq < c.max_seqs) {
 #pragma unroll
         for (int k = 0; k < 3; ++k) p[u][k] = v.n_pages[npages_index(c, seq, a.layer, k)];
@@ -155,14 +155,17 @@ __device__ inline Deal deal_item(const thinkv_view& v, const DecodeArgs& a, int 
   }
   most = last_lane(wave_scan(most, [](int x, int y) { return max(x, y); }));
   all = last_lane(wave_scan(all, add)) * (float)H;
+  // (quotients by reciprocals: whatever n comes out of them, the sum decides whether it fits; what they are off by must not make
+  // an item more of a whole number)
+  const float per_most = __builtin_amdgcn_rcpf((float)max(most, 1)), per_all = __builtin_amdgcn_rcpf(fmaxf(all, 1.f));
   // the items of every sequence where the longest has n; their sum
   int mine[kU];
   auto spread = [&](int n) {
-    const float per_page = (float)n / (float)max(most, 1);
+    const float per_page = (float)n * per_most;
     int sum = 0;
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
-      mine[u] = 64 * u + lane < a.B ? min(max((int)ceilf((float)tot[u] * per_page), 1), n) : 0;
+      mine[u] = 64 * u + lane < a.B ? min(max((int)ceilf(fmaf((float)tot[u], per_page, -0.002f)), 1), n) : 0;
       sum += mine[u];
     }
     return last_lane(wave_scan(sum, add));
@@ -172,10 +175,10 @@ __device__ inline Deal deal_item(const thinkv_view& v, const DecodeArgs& a, int 
   while (true) {
     const int slots = min(a.grid * sub, a.n_rows);
     if (slots >= a.B * H) {   // (holds for the last sub)
-      const int least = kDealPages * whole(kFull, sub), cap = max(min((most + least - 1) / least, kMaxRowsPerHead), 1);
-      n = max(min((int)(1.0001f * (float)slots * (float)most / fmaxf(all, 1.f)), cap), 1);
-      for (sum = spread(n); n > 1 && sum * H > slots; sum = spread(n)) n = max(min(n - 1, (int)((float)n * (float)slots / (float)(sum * H))), 1);
-      const float busiest = (float)most * (float)sub / (float)n;
+      const int least = kDealPages * whole(kFull, sub), cap = max(min(whole(min(most, 1 << 19) + least - 1, least), kMaxRowsPerHead), 1);
+      n = max(min((int)(1.0001f * (float)slots * (float)most * per_all), cap), 1);
+      for (sum = spread(n); n > 1 && sum * H > slots; sum = spread(n)) n = max(min(n - 1, whole(n * slots, sum * H)), 1);
+      const float busiest = (float)most * (float)sub * __builtin_amdgcn_rcpf((float)n);
       if (busiest < 0.95f * best) {
         best = busiest;
         best_sub = sub;
@@ -193,6 +196,7 @@ __device__ inline Deal deal_item(const thinkv_view& v, const DecodeArgs& a, int 
   d.items = sum * H;
   d.wph = whole(kFull, sub);
   d.it = ItemLoc{0, 0, 0, 0, 0};
+  d.seq = -1;
   d.np[0] = d.np[1] = d.np[2] = 0;
   const int id = whole(wave, d.wph) * a.grid + wg;   // neighbouring items on different compute units
   if (id >= d.items) return d;
@@ -210,6 +214,7 @@ __device__ inline Deal deal_item(const thinkv_view& v, const DecodeArgs& a, int 
       d.it.row0 = first + d.it.hkv * d.it.n;
 #pragma unroll
       for (int k = 0; k < 3; ++k) d.np[k] = __builtin_amdgcn_readlane(p[u][k], at);
+      d.seq = __builtin_amdgcn_readlane(ids[u], at);
     }
     before = all_u;
   }

@@ -1052,21 +1052,23 @@ __global__ __launch_bounds__(256 * decode_waves_per_simd(D, FP)) __attribute__((
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, W = blockDim.x >> 6;
   // this wave's item, and the waves it shares it with: `wph` from wave0 on
   ItemLoc it;
-  int np[3], wph = W;
+  int seq, np[3], wph = W;
   if (a.grid) {
     const Deal d = deal_item<kFull>(v, a, blockIdx.x, wave);
     if ((int)blockIdx.x >= d.items) return;   // (then no wave has one)
     it = d.it;
     wph = d.wph;
+    seq = d.seq;
 #pragma unroll
     for (int k = 0; k < 3; ++k) np[k] = d.np[k];
   } else {
     it = locate_item(v, a, blockIdx.x);
     if (it.j >= it.n) return;
-    seq_pages(v, a.layer, uniform(a.seq_ids[it.b]), np);
+    seq = uniform(a.seq_ids[it.b]);
+    seq_pages(v, a.layer, seq, np);
   }
   const int group = whole(wave, wph), wave0 = group * wph;
-  const int b = it.b, hkv = it.hkv, seq = uniform(a.seq_ids[b]), share_n = it.n > 0 ? it.n : 1;
+  const int b = it.b, hkv = it.hkv, share_n = it.n > 0 ? it.n : 1;
   const int Hq = c.n_q_heads, G = Hq / c.n_kv_heads;
   const bool valid = seq >= 0 && seq < c.max_seqs;
   Stream q;
