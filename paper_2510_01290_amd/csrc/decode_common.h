@@ -16,8 +16,10 @@
 // 144 KB of the compute unit's 160.  More waves hide more of each other's latency, a deeper ring keeps more bytes in
 // flight; where the line lies is measured: integer formats at head_dim 128 (18 KB: two pairs of 8-bit, three of 4-bit,
 // six of 2-bit pages) 16 x 8k tokens 43 us at two waves, 64 at three; head_dim 64 (12 KB: two, four, eight pairs)
-// 287 us at three, 328 at four for 128 x 4k..32k tokens; the paper's formats at 128, whose registers fit a third wave and
-// whose arithmetic needs it, 132 at three and 137 at two.  The host sizes launches with the same numbers.
+// 287 us at three, 328 at four for 128 x 4k..32k tokens; the paper's formats at 128, whose registers fit a third wave:
+// 16 x 32k of ternary codes 110 us at three and 119 at two, eight heads a group 107 and 115; of 8-bit types, and of all three, no
+// difference (171, 130 and 129), in short or odd batches two are better (17 x 16k 89 and 85, 8 x 2k 21.4 and 18.9).  The host
+// sizes launches with the same numbers.
 __host__ __device__ constexpr int decode_waves_per_simd(int head_dim, bool fp) { return (head_dim == 64 ? 3 : 2) + (fp ? 1 : 0); }
 __host__ __device__ constexpr int stream_ring_bytes(int head_dim, bool fp) { return 147456 / (4 * decode_waves_per_simd(head_dim, fp)); }
 
