@@ -29,6 +29,8 @@
 // all this is of the order of 1e-6 of |x|^2, far below the gaps that separate genuine decisions;
 // an assignment only needs |c|^2 - 2 x.c.  All sums run in index order or in a fixed tree, so the result is the same on
 // every run; the survivor of a cluster is found with a 64-bit LDS minimum over (distance bits, index).
+#include <type_traits>
+
 #include "common.h"
 
 namespace thinkv {
@@ -512,16 +514,15 @@ int launch_tbe_select(const thinkv_view& v, int layer, const int32_t* tok_seq, c
 // A live token belongs to the segment whose start is the largest one not above its position
 // (the block table's start-index column, Sec. 5.2).
 //
-// Four kernels.  count (one workgroup per examined sequence): live tokens per segment (every
-// thread takes pages of the sequence's three lists and reads a page's sixteen positions as four
-// vectors; binary search of each live slot's position in the segment starts, held in LDS), then
-// one thread walks the plan and leaves the sequence's cuts in a staging area.  offsets (one
-// workgroup): every sequence's place in the dense output lists; a sequence whose cuts no longer
-// all fit the caller's buffers keeps the leading ones that do (the rest waits for the next call).
-// fill (one workgroup per sequence): list offsets of the sequence's cuts by a prefix sum, then its
-// live tokens are dealt to their lists.  sort (one wave per cut): each list is put in ascending
+// Three kernels.  count (one workgroup per examined sequence): live tokens per segment (a thread takes four slots of a page:
+// one load of positions, a binary search in the segment starts, held in LDS, where a slot leaves the segment of the one
+// before), then the plan, whose cuts wait in a staging area.  fill (one workgroup per sequence): the sequence's place in
+// the dense output lists from the totals of the sequences before it; where the lists are too short for all, the sequences
+// in order keep the leading cuts that still fit (the rest waits for the next call).  Then the list offsets of its cuts by a
+// prefix sum, and its live tokens are dealt to their lists.  sort (one wave per cut): each list is put in ascending
 // position by a rank sort in LDS, so the output does not depend on the order in which threads
-// got there.
+// got there.  32 sequences of 2k to 4k tokens, 314 cuts, us, with sixteen slots of three pages a thread, one thread for the
+// second case and a kernel for the offsets / now: count 39 / 11, offsets 9 / -, fill 32 / 9, sort 19 / 10.
 constexpr int kMaxSegs = THINKV_TBE_MAX_SEGS;
 constexpr int kRetention[5] = {64, 32, 16, 8, 4};
 constexpr int kPlanThreads = 1024;
@@ -540,15 +541,12 @@ struct PlanArgs {
   int32_t* seg_keep;
   int32_t* counts;
   // staging: per examined sequence max_cuts entries of (segment, keep, live tokens); the number of
-  // cuts and of their tokens; the sequence's first cut / first token in the dense lists; per cut of
-  // the dense lists the sequence it belongs to
+  // cuts and of their tokens; per cut of the dense lists the sequence it belongs to
   int32_t* st_seg;
   int32_t* st_keep;
   int32_t* st_cnt;
   int32_t* st_ncuts;
   int32_t* st_total;
-  int32_t* st_seg_base;
-  int32_t* st_tok_base;
   int32_t* st_cut_seq;
   int layer, B, max_segs, budget, max_cuts, cap_seg, cap_tok;
 };
@@ -574,55 +572,51 @@ __device__ inline int segment_of(const int* starts, int n, int pos) {
   return lo - 1;
 }
 
-// calls f(segment, position, handle) for every live token of the sequence; every thread takes pages.
-// The walk is a chain of dependent loads (page count -> live mask and page id -> the page's sixteen
-// positions) and little else, so the chains of the three page lists run side by side.
+// calls f(segment, position, handle) for every live token of the sequence.  A thread takes four slots of a page, a pass two
+// such pieces.  The walk is a chain of dependent loads (page count -> live mask and page id -> four positions) and little
+// else; four slots keep the code behind it short.
 template <typename F>
-__device__ inline void for_live_tokens(const thinkv_view& v, int seq, int layer, const int* s_start, int ns, F f) {
+__device__ __forceinline__ void for_live_tokens(const thinkv_view& v, int seq, int layer, const int* s_start, int ns, F f) {
   const thinkv_config& c = v.cfg;
-  int np[3], most = 0;
+  constexpr int kAhead = 2;
+  int np[3];
 #pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    np[k] = v.n_pages[npages_index(c, seq, layer, k)];
-    most = np[k] > most ? np[k] : most;
-  }
-  for (int pi = threadIdx.x; pi < most; pi += blockDim.x) {
-    uint32_t m[3];
-    int pid[3];
+  for (int k = 0; k < 3; ++k) np[k] = v.n_pages[npages_index(c, seq, layer, k)];
+  const int pieces = 4 * (np[0] + np[1] + np[2]), quarter = threadIdx.x & 3;
+  for (int u0 = threadIdx.x; u0 < pieces; u0 += kAhead * kPlanThreads) {
+    uint32_t m[kAhead];
+    int pid[kAhead], cls[kAhead], pi[kAhead];
+    int4 pos[kAhead];
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      const bool in = pi < np[k];
-      const int64_t at = table_base(c, seq, layer, k) + (in ? pi : 0);
-      m[k] = in ? v.slot_mask[at] & 0xFFFFu : 0u;
-      pid[k] = in ? v.block_table[at] : 0;
+    for (int a = 0; a < kAhead; ++a) {
+      const int u = u0 + a * kPlanThreads;
+      int page = (u < pieces ? u : u0) >> 2;
+      cls[a] = page < np[0] ? 0 : page < np[0] + np[1] ? 1 : 2;
+      pi[a] = page - (cls[a] == 0 ? 0 : cls[a] == 1 ? np[0] : np[0] + np[1]);
+      const int64_t at = table_base(c, seq, layer, cls[a]) + pi[a];
+      m[a] = u < pieces ? v.slot_mask[at] >> (4 * quarter) & 15u : 0u;
+      pid[a] = v.block_table[at];
     }
-    int pos[3][kPage];
 #pragma unroll
-    for (int k = 0; k < 3; ++k)
-      if (m[k]) {
-        const int4* sp = (const int4*)(v.slot_pos[k] + (int64_t)pid[k] * kPage);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int4 w = sp[q];
-          pos[k][4 * q] = w.x; pos[k][4 * q + 1] = w.y; pos[k][4 * q + 2] = w.z; pos[k][4 * q + 3] = w.w;
-        }
+    for (int a = 0; a < kAhead; ++a)
+      if (m[a]) {
+        const int32_t* sp = cls[a] == 0 ? v.slot_pos[0] : cls[a] == 1 ? v.slot_pos[1] : v.slot_pos[2];
+        pos[a] = *(const int4*)(sp + (int64_t)pid[a] * kPage + 4 * quarter);
       }
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      if (!m[k]) continue;
-      // neighbours in a page are mostly neighbours in the sequence: the segment of the slot before is
-      // tried first (two LDS reads), the binary search (eleven dependent ones) only when that fails
+    for (int a = 0; a < kAhead; ++a) {
+      const int at[4] = {pos[a].x, pos[a].y, pos[a].z, pos[a].w};
       int sg = -1, lo_pos = 0, hi_pos = -1;   // [lo_pos, hi_pos): positions of segment sg
 #pragma unroll
-      for (int slot = 0; slot < kPage; ++slot) {
-        if (!(m[k] >> slot & 1)) continue;
-        const int p = pos[k][slot];
+      for (int q = 0; q < 4; ++q) {
+        if (!(m[a] >> q & 1u)) continue;
+        const int p = at[q];
         if (p < lo_pos || p >= hi_pos) {
           sg = segment_of(s_start, ns, p);
           lo_pos = sg >= 0 ? s_start[sg] : 0;
           hi_pos = sg >= 0 ? (sg + 1 < ns ? s_start[sg + 1] : 0x7fffffff) : -1;
         }
-        if (sg >= 0) f(sg, p, THINKV_HANDLE(k, pi, slot));
+        if (sg >= 0) f(sg, p, THINKV_HANDLE(cls[a], pi[a], 4 * quarter + q));
       }
     }
   }
@@ -735,48 +729,68 @@ __global__ __launch_bounds__(kPlanThreads) void tbe_count_plan_kernel(thinkv_vie
       __syncthreads();
     }
   }
-  if (tid != 0) return;
+  if (tid >= 64) return;
   int total = v.n_live[sl_index(c, seq, a.layer)] - s_c1[2];
   int n_cuts = s_c1[0], listed = s_c1[1];
   bool oversize = s_c1[3] != 0;
-  auto cut = [&](int i, int r) {
-    o_seg[n_cuts] = i;
-    o_keep[n_cuts] = r;
-    o_cnt[n_cuts] = s_cnt[i];
-    ++n_cuts;
-    listed += s_cnt[i];
-    total -= s_cnt[i] - r;
-    s_cnt[i] = -r;          // negative: cut in this call, now holding r tokens
-  };
   // Case 2.  A segment that cannot be cut now cannot be cut later in this call either (one cut per
   // segment and call), so "the oldest segment of the least important type that can still shrink",
   // asked again after every cut, is one walk over the types in order of importance and over the
-  // segments of each from the oldest on.
+  // segments of each from the oldest on.  One wave, 64 segments at a time: whether the walk comes as far as a segment follows
+  // from what the segments before it drop.
+  const int lane = tid;
   for (int t = 0; t < 3; ++t)
-    for (int i = 0; i < last && total > a.budget && n_cuts < a.max_cuts; ++i) {
-      if (s_type[i] != t || s_cnt[i] < 0) continue;
-      int r = 0;
-      if (by_count) {
-        // selections that remove nothing follow one another at once (each advances the count)
-        int n = s_lvl[i];
-        while (n < 5 && r == 0) {
-          const int keep = s_cnt[i] < kRetention[n] ? s_cnt[i] : kRetention[n];
-          if (keep < s_cnt[i]) r = keep; else ++n;
+    for (int i0 = 0; i0 < last && total > a.budget && n_cuts < a.max_cuts; i0 += 64) {
+      const int i = i0 + lane, cnt = i < last ? s_cnt[i] : -1;
+      const bool open = cnt >= 0 && s_type[i] == t;
+      int r = 0, n = 0;
+      if (open) {
+        if (by_count) {
+          // selections that remove nothing follow one another at once (each advances the count)
+          n = s_lvl[i];
+          while (n < 5 && r == 0) {
+            const int keep = cnt < kRetention[n] ? cnt : kRetention[n];
+            if (keep < cnt) r = keep; else ++n;
+          }
+        } else {
+          r = next_level(cnt);
         }
-        if (n != s_lvl[i]) {
-          s_lvl[i] = (uint8_t)n;
-          sel[i] = n;
-        }
-      } else {
-        r = next_level(s_cnt[i]);
       }
-      if (!r) continue;
-      if (s_cnt[i] > kTbeMaxTokens) {
-        oversize = true;
-        continue;
+      const bool big = r && cnt > kTbeMaxTokens, can = r && !big;
+      int upto = can ? cnt - r : 0;   // dropped by the segments up to this one, if the walk comes as far
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) {
+        const int o = __shfl_up(upto, d, 64);
+        if (lane >= d) upto += o;
       }
-      cut(i, r);
+      const unsigned long long cans = __ballot(can);
+      const int before = __popcll(cans & ((1ull << lane) - 1));
+      const bool reached = total - (upto - (can ? cnt - r : 0)) > a.budget && n_cuts + before < a.max_cuts;
+      if (open && reached && by_count && n != s_lvl[i]) {
+        s_lvl[i] = (uint8_t)n;
+        sel[i] = n;
+      }
+      const bool take = can && reached;
+      if (take) {
+        const int at = n_cuts + before;
+        o_seg[at] = i;
+        o_keep[at] = r;
+        o_cnt[at] = cnt;
+        s_cnt[i] = -r;          // negative: cut in this call, now holding r tokens
+      }
+      oversize |= __ballot(big && reached) != 0;
+      const unsigned long long taken = __ballot(take);   // the walk ends once, so these are the leading ones of `cans`
+      int in_list = take ? cnt : 0, dropped = take ? cnt - r : 0;
+#pragma unroll
+      for (int d = 32; d >= 1; d >>= 1) {
+        in_list += __shfl_xor(in_list, d, 64);
+        dropped += __shfl_xor(dropped, d, 64);
+      }
+      n_cuts += __popcll(taken);
+      listed += in_list;
+      total -= dropped;
     }
+  if (tid != 0) return;
   a.st_ncuts[b] = n_cuts;
   a.st_total[b] = listed;
   if (oversize) atomicOr(&v.dev_status[c.max_seqs * c.n_layers], THINKV_ST_BAD_SEGMENT);
@@ -803,25 +817,29 @@ __device__ inline int wave_scan4(const int* val, int* ex) {
   return total;
 }
 
-__global__ __launch_bounds__(64) void tbe_offsets_kernel(PlanArgs a) {
-  // one wave: sequences in order (their number is that of a decode batch); a sequence whose cuts all
-  // fit is placed from its two totals, only one that does not is looked at cut by cut
-  const int lane = threadIdx.x;
-  int n_seg = 0, n_tok = 0;
-  for (int b = 0; b < a.B; ++b) {
-    const int nc = a.st_ncuts[b], tot = a.st_total[b];
+struct Place {
+  int seg, tok, cuts;   // first cut and first token of a sequence in the dense lists, and how many of its cuts are made
+};
+
+// Where the lists are too short for all cuts: the sequences up to b in order, by one wave; a sequence whose cuts do not all fit
+// keeps the leading ones that do.  b = B: the ends of the lists.
+__device__ inline Place place_in_order(const PlanArgs& a, int b) {
+  const int lane = threadIdx.x & 63;
+  Place at = {0, 0, 0};
+  for (int i = 0; i <= b && i < a.B; ++i) {
+    const int nc = a.st_ncuts[i], tot = a.st_total[i];
     int kept = nc, kept_tok = tot;
-    if (n_seg + nc > a.cap_seg || (int64_t)n_tok + tot > a.cap_tok) {
+    if (at.seg + nc > a.cap_seg || (int64_t)at.tok + tot > a.cap_tok) {
       // leading cuts that still fit (the lists only grow, so the first that does not fit ends them)
       int val[4], ex[4];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) val[q] = 4 * lane + q < nc ? a.st_cnt[(int64_t)b * a.max_cuts + 4 * lane + q] : 0;
+      for (int q = 0; q < 4; ++q) val[q] = 4 * lane + q < nc ? a.st_cnt[(int64_t)i * a.max_cuts + 4 * lane + q] : 0;
       wave_scan4(val, ex);
       int fits = 0, fits_tok = 0;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const int i = 4 * lane + q;
-        if (i < nc && n_seg + i < a.cap_seg && (int64_t)n_tok + ex[q] + val[q] <= a.cap_tok) {
+        const int j = 4 * lane + q;
+        if (j < nc && at.seg + j < a.cap_seg && (int64_t)at.tok + ex[q] + val[q] <= a.cap_tok) {
           ++fits;
           fits_tok += val[q];
         }
@@ -834,24 +852,51 @@ __global__ __launch_bounds__(64) void tbe_offsets_kernel(PlanArgs a) {
       kept = fits;
       kept_tok = fits_tok;
     }
-    if (lane == 0) {
-      a.st_seg_base[b] = n_seg;
-      a.st_tok_base[b] = n_tok;
-      a.st_ncuts[b] = kept;
+    if (i == b) {
+      at.cuts = kept;
+      return at;
     }
-    n_seg += kept;
-    n_tok += kept_tok;
+    at.seg += kept;
+    at.tok += kept_tok;
   }
-  if (lane == 0) {
-    a.seg_offset[n_seg] = n_tok;
-    a.counts[0] = n_seg;
-    a.counts[1] = n_tok;
-  }
+  return at;
 }
 
 __global__ __launch_bounds__(kPlanThreads) void tbe_fill_kernel(thinkv_view v, PlanArgs a) {
   const int b = blockIdx.x, tid = threadIdx.x;
-  const int n_cuts = a.st_ncuts[b];
+  __shared__ unsigned long long s_sum[4];         // cuts and tokens of all sequences, and of those before this one
+  __shared__ Place s_place;
+  if (tid < 4) s_sum[tid] = 0ull;
+  __syncthreads();
+  for (int i = tid; i < a.B; i += kPlanThreads) {
+    const int nc = a.st_ncuts[i], tot = a.st_total[i];
+    if (nc == 0) continue;
+    atomicAdd(&s_sum[0], (unsigned long long)nc);
+    atomicAdd(&s_sum[1], (unsigned long long)tot);
+    if (i < b) {
+      atomicAdd(&s_sum[2], (unsigned long long)nc);
+      atomicAdd(&s_sum[3], (unsigned long long)tot);
+    }
+  }
+  __syncthreads();
+  if (tid < 64) {
+    const bool fits = s_sum[0] <= (unsigned long long)a.cap_seg && s_sum[1] <= (unsigned long long)a.cap_tok;
+    Place at = {(int)s_sum[2], (int)s_sum[3], b < a.B ? a.st_ncuts[b] : 0}, end = {(int)s_sum[0], (int)s_sum[1], 0};
+    if (!fits) {
+      at = place_in_order(a, b);
+      if (b == 0) end = place_in_order(a, a.B);
+    }
+    if (tid == 0) {
+      s_place = at;
+      if (b == 0) {
+        a.seg_offset[end.seg] = end.tok;
+        a.counts[0] = end.seg;
+        a.counts[1] = end.tok;
+      }
+    }
+  }
+  __syncthreads();
+  const int n_cuts = s_place.cuts;
   if (n_cuts == 0) return;
   __shared__ int s_start[kMaxSegs];
   __shared__ int s_cut[kMaxSegs];                 // cut number of a segment, -1 = not cut
@@ -865,7 +910,7 @@ __global__ __launch_bounds__(kPlanThreads) void tbe_fill_kernel(thinkv_view v, P
     s_start[i] = starts[i];
     s_cut[i] = -1;
   }
-  const int seg_base = a.st_seg_base[b], tok_base = a.st_tok_base[b];
+  const int seg_base = s_place.seg, tok_base = s_place.tok;
   if (tid < 64) {
     int val[4], ex[4];
 #pragma unroll
@@ -901,35 +946,42 @@ __global__ __launch_bounds__(kPlanThreads) void tbe_fill_kernel(thinkv_view v, P
   });
 }
 
-// one wave per cut of the dense lists: ascending position inside the list
+// one wave per cut of the dense lists: ascending position inside the list.  A token's rank is the number of smaller keys (position,
+// then place in the list), four keys of the list compared at a time
 __global__ __launch_bounds__(256) void tbe_sort_kernel(PlanArgs a) {
-  __shared__ int s_pos[4][kTbeMaxTokens];
+  __shared__ __attribute__((aligned(16))) long long s_key[4][kTbeMaxTokens];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int cu = blockIdx.x * 4 + wave;
-  const bool live = cu < a.counts[0];
-  int lo = 0, n = 0, pos[kPT], h[kPT];
-  if (live) {
-    lo = a.seg_offset[cu];
-    n = a.seg_offset[cu + 1] - lo;   // at most kTbeMaxTokens: larger segments are never cut
-#pragma unroll
-    for (int q = 0; q < kPT; ++q)
-      if (lane + 64 * q < n) {
-        pos[q] = a.tok_seq[lo + lane + 64 * q];
-        h[q] = a.tok_handle[lo + lane + 64 * q];
-        s_pos[wave][lane + 64 * q] = pos[q];
-      }
-  }
-  __syncthreads();
-  if (!live) return;
+  if (cu >= a.counts[0]) return;   // the waves do not meet
+  const int lo = a.seg_offset[cu], n = a.seg_offset[cu + 1] - lo;   // at most kTbeMaxTokens: larger segments are never cut
   const int seq = a.st_cut_seq[cu];
-  int rank[kPT];
+  long long key[kPT];
+  int h[kPT], rank[kPT];
 #pragma unroll
-  for (int q = 0; q < kPT; ++q) rank[q] = 0;
-  for (int i = 0; i < n; ++i) {
-    const int other = s_pos[wave][i];
-#pragma unroll
-    for (int q = 0; q < kPT; ++q) rank[q] += other < pos[q] || (other == pos[q] && i < lane + 64 * q);
+  for (int q = 0; q < kPT; ++q) {
+    const int i = lane + 64 * q;
+    rank[q] = 0;
+    key[q] = 0x7FFFFFFFFFFFFFFFll;
+    if (i < n) {
+      key[q] = (long long)a.tok_seq[lo + i] << 8 | i;
+      h[q] = a.tok_handle[lo + i];
+    }
+    s_key[wave][i] = key[q];
   }
+  __builtin_amdgcn_wave_barrier();
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  auto walk = [&](auto rows) {   // points of so many 64
+    for (int i = 0; i < n; i += 4) {
+      const long long o[4] = {s_key[wave][i], s_key[wave][i + 1], s_key[wave][i + 2], s_key[wave][i + 3]};
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int q = 0; q < decltype(rows)::value; ++q) rank[q] += o[e] < key[q];
+    }
+  };
+  if (n <= 64) walk(std::integral_constant<int, 1>{});
+  else if (n <= 128) walk(std::integral_constant<int, 2>{});
+  else walk(std::integral_constant<int, kPT>{});
 #pragma unroll
   for (int q = 0; q < kPT; ++q)
     if (lane + 64 * q < n) {
@@ -962,8 +1014,6 @@ int launch_tbe_plan(const thinkv_view& v, int layer, const int32_t* seq_ids, con
   a.st_cut_seq = w + 3 * (size_t)B * max_cuts;
   a.st_ncuts = w + 4 * (size_t)B * max_cuts;
   a.st_total = a.st_ncuts + B;
-  a.st_seg_base = a.st_total + B;
-  a.st_tok_base = a.st_seg_base + B;
   a.layer = layer;
   a.B = B;
   a.max_segs = max_segs;
@@ -972,8 +1022,7 @@ int launch_tbe_plan(const thinkv_view& v, int layer, const int32_t* seq_ids, con
   a.cap_seg = cap_seg;
   a.cap_tok = cap_tok;
   if (B > 0) hipLaunchKernelGGL(tbe_count_plan_kernel, dim3(B), dim3(kPlanThreads), 0, st, v, a);
-  hipLaunchKernelGGL(tbe_offsets_kernel, dim3(1), dim3(64), 0, st, a);
-  if (B > 0) hipLaunchKernelGGL(tbe_fill_kernel, dim3(B), dim3(kPlanThreads), 0, st, v, a);
+  hipLaunchKernelGGL(tbe_fill_kernel, dim3(B > 0 ? B : 1), dim3(kPlanThreads), 0, st, v, a);
   const int64_t most = (int64_t)B * max_cuts < cap_seg ? (int64_t)B * max_cuts : cap_seg;
   if (most > 0) hipLaunchKernelGGL(tbe_sort_kernel, dim3((unsigned)((most + 3) / 4)), dim3(256), 0, st, a);
   return hipGetLastError() == hipSuccess ? THINKV_OK : THINKV_E_HIP;

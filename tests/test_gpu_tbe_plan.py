@@ -1,0 +1,68 @@
+"""The eviction plan where a sequence has more segments than a wave looks at in one go, where the budget, the limit of cuts or
+the output lists end the walk in the middle, and where pages are more than a workgroup walks in one pass; against the
+oracle's plan, exactly (integers)."""
+import numpy as np
+import pytest
+import torch
+
+import parity
+from paper_2510_01290_amd import synth
+from test_gpu_tbe import _device_plan, _oracle_plan
+
+pytestmark = pytest.mark.gpu
+
+
+def _built(lens, seed):
+    geom = synth.Geometry(1, 2, 2, 64, "f16", (8, 2, 4))
+    rng = np.random.default_rng(seed)
+    S = len(lens)
+    classes = [np.repeat(rng.integers(0, 3, n // 5 + 1), 5)[:n].astype(np.uint8) for n in lens]
+    wl = synth.Workload("tbe-plan-long", geom, seed, S, classes, [], (0,), np.array(lens, np.int32) - 1)
+    pages = max(lens) // 16 + 8
+    gc = parity.make_gpu_cache(wl, arena_pages=(S * pages,) * 3, max_pages=pages)
+    ob = parity.make_oracle(wl, arena_pages=(S * pages,) * 3, max_pages=pages)
+    gb = parity.GpuBackend(gc)
+    for s in range(S):
+        k = synth.kv_rows(seed, 0, s, 0, 0, lens[s], geom, torch.device("cpu"))
+        h = gb.append(0, k.to(gc.device), k.to(gc.device), np.full(lens[s], s), np.arange(lens[s]), classes[s])
+        ob.append(0, k, k, np.full(lens[s], s), np.arange(lens[s]), classes[s])
+        gone = rng.choice(lens[s], size=lens[s] // 6, replace=False)
+        gb.evict(0, np.full(len(gone), s), h[gone])
+        ob.evict(0, np.full(len(gone), s), h[gone])
+    return gc, ob, rng
+
+
+def _segment_table(rng, lens, width, longest):
+    st, ty, ns = np.zeros((len(lens), width), np.int32), np.zeros((len(lens), width), np.uint8), np.zeros(len(lens), np.int32)
+    for s, n in enumerate(lens):
+        cuts = np.cumsum(rng.integers(1, longest + 1, width))
+        cuts = np.concatenate([[0], cuts[cuts < n]])[:width]
+        st[s, :len(cuts)], ns[s] = cuts, len(cuts)
+        ty[s, :len(cuts)] = rng.integers(0, 3, len(cuts))
+    return st, ty, ns
+
+
+@pytest.mark.parametrize("longest,trans,budget,max_cuts,cap_seg,cap_tok", [
+    (14, None, 700, 256, 2048, 1 << 16),          # the budget ends the walk, some hundred segments a type
+    (14, None, 0, 100, 2048, 1 << 16),            # the limit of cuts does
+    (14, [1, 0, 1], 0, 256, 2048, 1 << 16),       # both cases together
+    (14, [1, 1, 1], 10 ** 6, 256, 300, 1 << 16),  # the lists end in the second sequence (segments) ...
+    (14, [1, 1, 1], 10 ** 6, 256, 2048, 2500),    # ... and (tokens)
+    (1, None, 0, 256, 2048, 1 << 16),             # a token a segment: nothing can go
+    (120, [0, 1, 0], 900, 64, 2048, 1 << 16)])    # segments of many pages
+def test_tbe_plan_over_many_segments(longest, trans, budget, max_cuts, cap_seg, cap_tok):
+    print("plan over many segments", longest, trans, budget, max_cuts, cap_seg, cap_tok, flush=True)
+    lens = [3700, 2100, 9000]
+    gc, ob, rng = _built(lens, 51)
+    st, ty, ns = _segment_table(rng, lens, 1400, longest)
+    dev, ora = np.zeros(st.shape, np.int32), np.zeros(st.shape, np.int32)
+    for again in range(2):                        # the second call finds the counts of the first
+        got = _device_plan(gc, 0, [0, 1, 2], st, ty, ns, trans, budget, max_cuts, cap_seg, cap_tok, seg_count=dev)
+        w_seq, w_h, w_off, w_keep = _oracle_plan(ob.cache, 0, [0, 1, 2], st, ty, ns, trans, budget, max_cuts, cap_seg, cap_tok, seg_count=ora)
+        n_seg, n_tok = got["counts"].tolist()
+        assert (n_seg, n_tok) == (len(w_keep), len(w_h)), again
+        assert np.array_equal(got["seg_keep"][:n_seg], w_keep) and np.array_equal(got["seg_offset"][:n_seg + 1], w_off)
+        assert np.array_equal(got["tok_handle"][:n_tok], w_h) and np.array_equal(got["tok_seq"][:n_tok], w_seq)
+        assert np.array_equal(dev, ora)
+    assert int(gc.dev_status.abs().sum().item()) == 0
+
