@@ -14,15 +14,19 @@
 //   survivors  per non-empty cluster the member nearest the centroid (ties -> lowest index; of
 //              two members the earlier one: both are equally near their mean)
 //
-// Two kernels.  gather writes the key rows [Hkv * D] of the listed tokens into the workspace.
-// kmeans: one workgroup of sixteen waves per segment (segments hold at most 256 live tokens, the
-// schedule keeps at most 64).  A centroid is the mean of points, so every product Lloyd's algorithm asks for is a
+// Two kernels.  A centroid is the mean of points, so every product Lloyd's algorithm asks for is a
 // mean of products between points: x.c_j = mean over the members i of x.x_i, |c_j|^2 = mean over the members of
-// x_i.c_j.  So the channels are walked once: all products between the points of the segment (the Gram matrix, at most
-// 256 x 256, its lower triangle kept in LDS), and an iteration is n^2 additions from LDS.  (Products of the points with
-// the centroids in every iteration walked all channels up to nine times: 314 segments of ~110 tokens, 1,024 channels,
-// 1,050 us; now 177, and the gather 37.)  A centroid is represented by the set of points it is the mean of: at the start one
+// x_i.c_j.  So the channels are walked once, for all products between the points of the segment (the Gram matrix, at most
+// 256 x 256, lower triangle), and an iteration is at most n^2 additions from LDS, of the clusters that changed only.
+// A centroid is represented by the set of points it is the mean of: at the start one
 // point, later the members, and for a cluster that has lost its last member the members it had before.
+// gram: the matrix, up to four workgroups a segment, each over some of the heads.  The keys go from the pages to the matrix
+// cores without a stop in memory; the binary32 rows are written on the way.
+// kmeans: a workgroup per segment adds the parts of the matrix and iterates.
+// 314 segments of ~110 tokens, 1,024 channels, us: keys to memory and a workgroup of a whole compute unit per segment (its
+// 139 KB of LDS made that 1.2 rounds of workgroups) 37 + 177; now 72 + 84.  gram is bound by vector instructions (four a
+// number to unpack and split it) and by 141 MB of rows; kmeans by the longest runs (eight iterations of about 6 us, a chain
+// from the list of members to LDS and back) and by the 58 MB of centroids.
 // The products run on the matrix cores; a dequantised key does not
 // fit binary16 and the binary32 matrix instruction is slow, so every number enters as the sum of
 // two binary16 parts (22 significant bits) and a product is three binary16 MFMAs.  The error of
@@ -48,159 +52,220 @@ struct TbeArgs {
   float* x;      // [n_tok][dim]
   float* cent;   // [n_seg][kTbeMaxKeep][dim]
   int32_t* assign;   // [n_tok] cluster of every token at the last assignment (-1: its segment was not clustered)
+  float* gram;       // per segment: the parts of its Gram matrix
+  int64_t gram_room; // numbers from one segment's parts to the next one's
   int layer, n_seg, n_tok, max_iters, dim;
 };
 
-size_t tbe_ws_bytes(const thinkv_config& c, int n_tok, int n_seg) {
-  const size_t dim = (size_t)c.n_kv_heads * c.head_dim;
-  return ((size_t)(n_tok > 0 ? n_tok : 1) * dim + (size_t)(n_seg > 0 ? n_seg : 1) * kTbeMaxKeep * dim) * sizeof(float) +
-         (size_t)(n_tok > 0 ? n_tok : 1) * sizeof(int32_t) + 256;
+constexpr int kGramThreads = 512;         // eight waves, two workgroups a compute unit
+constexpr int kGramWaves = kGramThreads / 64;
+constexpr int kSlices = 4;                // workgroups that share a segment's channels at most: with one, the units that get two segments end last (110 us)
+constexpr int kMacro = 32;                // points on a side of a wave's piece of the Gram matrix (2 x 2 MFMA tiles)
+constexpr int kPiecesPerWave = 3;         // 24 pieces of the lower triangle in one walk: all of 192 points
+constexpr int kMaxGram = kTbeMaxTokens * (kTbeMaxTokens + 1) / 2;
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+constexpr int kPadH = 2 * kTile + 8;   // binary16 numbers per tile row: high parts, low parts, padding (an odd multiple of 16 bytes)
+
+__host__ __device__ __forceinline__ int tri(int i) { return i * (i + 1) / 2; }   // where row i of the lower triangle begins
+
+// The parts of a segment's matrix lie in the place of its centroids, which are written last, or behind everything else
+// where that is too short for the largest segment
+static bool gram_in_centroids(int dim) { return kTbeMaxKeep * dim >= kMaxGram; }
+
+// workgroups that share a segment of n tokens: as many parts as there is room for
+__device__ __forceinline__ int gram_slices(int64_t room, int n, int heads) {
+  int s = (int)(room / tri(n));
+  s = s < kSlices ? s : kSlices;
+  return s < heads ? s : heads;
 }
 
-// ---- gather: x[i][hd * D + ch] = the stored key of token i.  A workgroup takes kGatherTokens tokens: one thread per
-// token walks the chain handle -> page list -> page; then a thread takes one chunk of a token's block (a kv-head, eight
-// channels of every group: one vector load of codes) and writes eight channels of each group as two 16-byte stores, four
-// neighbours 128 bytes.  Bound by those stores (four bytes a channel): 34,500 tokens of 1,024 channels (141 MB) 44 us
-// (one channel a thread: 84).
-constexpr int kGatherTokens = 8;
+size_t tbe_ws_bytes(const thinkv_config& c, int n_tok, int n_seg) {
+  const int dim = c.n_kv_heads * c.head_dim;
+  const size_t toks = n_tok > 0 ? n_tok : 1, segs = n_seg > 0 ? n_seg : 1;
+  return (toks * dim + segs * kTbeMaxKeep * dim + (gram_in_centroids(dim) ? 0 : segs * kMaxGram)) * sizeof(float) +
+         toks * sizeof(int32_t) + 256;
+}
 
-template <int D, int BITS>
-__device__ __forceinline__ void gather_chunk(const thinkv_config& c, const uint8_t* blk, int j, int slot, bool fp, float* row) {
-  constexpr int NG = D / kGroup, FPH = 16 / BITS, CW = NG * BITS / 4;
-  const BlockGeom g = block_geom(BITS, D, c.format);
-  uint32_t codes[CW];
-#pragma unroll
-  for (int w = 0; w < CW; ++w) codes[w] = ((const uint32_t*)(blk + g.k_codes + (16 * j + slot) * g.chunk_bytes))[w];
-#pragma unroll
-  for (int grp = 0; grp < NG; ++grp) {
-    float sc, zp = 0.f;
-    if (fp) {   // the eight channels lie in the group of 16 number 2 grp + j / 2
-      sc = BITS == 8 ? c.fp8_scale[0] : e4m3_value(blk[g.k_meta + (2 * grp + (j >> 1)) * kPage + slot]);
-    } else {
-      const _Float16* meta = (const _Float16*)(blk + g.k_meta);
-      sc = (float)meta[meta_index(slot, grp)];
-      zp = (float)meta[meta_index(slot, grp) + 4];
-    }
-    float x[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int f = 4 * grp + (e >> 1);
-      const uint32_t raw = (codes[f / FPH] >> (16 * (e & 1) + BITS * (f % FPH))) & ((1u << BITS) - 1u);
-      x[e] = fp ? fp_code_value(raw, BITS) * sc : fmaf((float)raw, sc, zp);
-    }
-    float* dst = row + 32 * grp + 8 * j;
-    *(float4*)dst = make_float4(x[0], x[1], x[2], x[3]);
-    *(float4*)(dst + 4) = make_float4(x[4], x[5], x[6], x[7]);
+// ---- a token's keys.  A unit is a chunk of a token's block (a kv-head, eight channels of every group); the four threads of
+// a quad hold the four chunks of one token and head, and each holds the scales of one group for all four.
+struct TokenAt {          // where a token's keys lie
+  const uint8_t* page;    // its page's block of head 0
+  uint32_t slot, bits;    // (width 0: the token does not exist)
+};
+
+__device__ inline TokenAt token_at(const thinkv_view& v, const TbeArgs& a, int i) {
+  const thinkv_config& c = v.cfg;
+  const int s = a.tok_seq[i];
+  const int32_t h = a.tok_handle[i];
+  const uint32_t uh = (uint32_t)h;
+  const int cls = uh >> 28, pi = (uh >> 4) & 0xFFFFFF;
+  TokenAt t = {v.arena[0], uh & 15, 0};
+  if (s < 0 || s >= c.max_seqs) {
+    atomicOr(&v.dev_status[c.max_seqs * c.n_layers], THINKV_ST_BAD_SEQ);
+  } else if (h < 0 || cls > 2 || pi >= v.n_pages[npages_index(c, s, a.layer, cls)]) {
+    atomicOr(&v.dev_status[sl_index(c, s, a.layer)], THINKV_ST_BAD_SLOT);
+  } else {
+    t.bits = cls == 0 ? c.bits_of_class[0] : cls == 1 ? c.bits_of_class[1] : c.bits_of_class[2];
+    t.page = (cls == 0 ? v.arena[0] : cls == 1 ? v.arena[1] : v.arena[2]) +
+             (int64_t)v.block_table[table_base(c, s, a.layer, cls) + pi] * c.n_kv_heads * block_geom(t.bits, c.head_dim, c.format).block_bytes;
   }
+  return t;
 }
 
 template <int D>
-__global__ __launch_bounds__(256) void tbe_gather_kernel(thinkv_view v, TbeArgs a) {
-  const thinkv_config& c = v.cfg;
-  const int tid = threadIdx.x, i0 = blockIdx.x * kGatherTokens;
-  const int H = c.n_kv_heads;
-  __shared__ int s_ok[kGatherTokens], s_cls[kGatherTokens], s_slot[kGatherTokens], s_pid[kGatherTokens];
-  if (tid < kGatherTokens) {
-    const int i = i0 + tid;
-    int ok = 0, cls = 0, slot = 0, pid = 0;
-    if (i < a.n_tok) {
-      const int s = a.tok_seq[i];
-      const int32_t h = a.tok_handle[i];
-      const uint32_t uh = (uint32_t)h;
-      cls = uh >> 28;
-      slot = uh & 15;
-      const int pi = (uh >> 4) & 0xFFFFFF;
-      if (s < 0 || s >= c.max_seqs) {
-        atomicOr(&v.dev_status[c.max_seqs * c.n_layers], THINKV_ST_BAD_SEQ);
-      } else if (h < 0 || cls > 2 || pi >= v.n_pages[npages_index(c, s, a.layer, cls)]) {
-        atomicOr(&v.dev_status[sl_index(c, s, a.layer)], THINKV_ST_BAD_SLOT);
-      } else {
-        pid = v.block_table[table_base(c, s, a.layer, cls) + pi];
-        ok = 1;
-      }
-    }
-    s_ok[tid] = ok; s_cls[tid] = cls; s_slot[tid] = slot; s_pid[tid] = pid;
-  }
-  __syncthreads();
-  const bool fp = c.format == THINKV_FMT_FP;
-  const int per = 4 * H;   // chunks of a token
-  for (int idx = tid; idx < kGatherTokens * per; idx += 256) {
-    const int t = idx / per, hd = (idx % per) >> 2, j = idx & 3;
-    if (i0 + t >= a.n_tok) continue;
-    float* row = a.x + (int64_t)(i0 + t) * a.dim + hd * D;
-    if (!s_ok[t]) {   // a token that does not exist clusters as the origin and is never evicted
-      for (int grp = 0; grp < D / kGroup; ++grp) {
-        *(float4*)(row + 32 * grp + 8 * j) = make_float4(0.f, 0.f, 0.f, 0.f);
-        *(float4*)(row + 32 * grp + 8 * j + 4) = make_float4(0.f, 0.f, 0.f, 0.f);
-      }
-      continue;
-    }
-    const int cls = s_cls[t], bits = c.bits_of_class[cls];
-    const BlockGeom g = block_geom(bits, D, c.format);
-    const uint8_t* blk = v.arena[cls] + ((int64_t)s_pid[t] * H + hd) * g.block_bytes;
-    if (bits == 2) gather_chunk<D, 2>(c, blk, j, s_slot[t], fp, row);
-    else if (bits == 4) gather_chunk<D, 4>(c, blk, j, s_slot[t], fp, row);
-    else gather_chunk<D, 8>(c, blk, j, s_slot[t], fp, row);
-  }
-}
-
-// ---- kmeans
-constexpr int kPT = kTbeMaxTokens / 64;   // tokens per lane of a wave that sorts a list
-constexpr int kKmThreads = 1024;          // sixteen waves
-constexpr int kQuarters = kKmThreads / kTbeMaxTokens;   // threads per point: each looks at every fourth cluster
-constexpr int kClPerThread = kTbeMaxKeep / kQuarters;
-constexpr int kMacro = 32;                // points on a side of a wave's piece of the Gram matrix (2 x 2 MFMA tiles)
-constexpr int kMacroMax = (kTbeMaxTokens / kMacro) * (kTbeMaxTokens / kMacro + 1) / 2;   // pieces of the lower triangle: 36
-constexpr int kMacroPerWave = (kMacroMax + kKmThreads / 64 - 1) / (kKmThreads / 64);     // 3
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
-constexpr int kPadH = 2 * kTile + 8;   // binary16 numbers per tile row: high parts, low parts, padding (an odd multiple of 16 bytes)
-
-__device__ __forceinline__ int tri(int i) { return i * (i + 1) / 2; }   // where row i of the lower triangle begins
-
-struct KmScratch {
-  union {
-    _Float16 xs[kTbeMaxTokens][kPadH];                       // one tile: 64 channels of every point, each as high + low binary16 part
-    float gram[kTbeMaxTokens * (kTbeMaxTokens + 1) / 2];     // then the products of all pairs of points, lower triangle
-  };
-  uint32_t basis[kTbeMaxKeep][kTbeMaxTokens / 32];           // the points a cluster's centroid is the mean of,
-  uint32_t next[kTbeMaxKeep][kTbeMaxTokens / 32];            // its members under the assignment just made
-  float own[kTbeMaxTokens];                                  // product of a point with the centroid it belongs to
-  float cc[kTbeMaxKeep];                                     // squared norms of the centroids
-  int cnt[kTbeMaxKeep], moved[kTbeMaxKeep];                  // points of the basis; whether it changed last
-  int cluster[kTbeMaxTokens];                                // cluster whose basis the point is in (-1: none)
-  float bd[kQuarters][kTbeMaxTokens];                        // per quarter of the clusters: best distance of every point ...
-  int bj[kQuarters][kTbeMaxTokens];                          // ... and the cluster it belongs to
-  int low[kTbeMaxKeep];                                      // survivors: lowest index of every cluster
-  unsigned long long best[kTbeMaxKeep];
+struct RawKeys {
+  uint32_t code[D / 16];   // the codes of the chunk: D / 32 groups of eight
+  uint32_t meta;           // group (lane & 3): scale and zero-point; paper's formats: the scales of its two halves
 };
 
-// four channels into a tile row: x = hi + lo with hi = binary16(x), lo = binary16(x - hi), 22 significant bits
-__device__ inline void store_split(_Float16* row, int c, float4 v) {
-  const f16x4 hi = {(_Float16)v.x, (_Float16)v.y, (_Float16)v.z, (_Float16)v.w};
-  const f16x4 lo = {(_Float16)(v.x - (float)hi[0]), (_Float16)(v.y - (float)hi[1]), (_Float16)(v.z - (float)hi[2]),
-                    (_Float16)(v.w - (float)hi[3])};
-  *(f16x4*)&row[c] = hi;
-  *(f16x4*)&row[kTile + c] = lo;
+// The chunk j of a token and head.  A token that does not exist has codes, scales and zero-points of 0: it clusters as the origin
+template <int D, bool FP>
+__device__ __forceinline__ void load_keys(const TokenAt& t, int hd, int j, RawKeys<D>& r) {
+#pragma unroll
+  for (int w = 0; w < D / 16; ++w) r.code[w] = 0u;
+  r.meta = 0u;
+  const BlockGeom g = block_geom(t.bits, D, FP ? THINKV_FMT_FP : THINKV_FMT_INT);
+  const uint8_t* blk = t.page + (int64_t)hd * g.block_bytes;
+  const uint32_t* chunk = (const uint32_t*)(blk + (16 * j + t.slot) * g.chunk_bytes);
+  auto take = [&](auto words) {
+#pragma unroll
+    for (int w = 0; w < decltype(words)::value; ++w) r.code[w] = chunk[w];
+  };
+  if (t.bits == 2) take(std::integral_constant<int, D / 64>{});
+  if (t.bits == 4) take(std::integral_constant<int, D / 32>{});
+  if (t.bits == 8) take(std::integral_constant<int, D / 16>{});
+  if (j < D / kGroup && t.bits != 0 && !(FP && t.bits == 8)) {
+    if (FP) {
+      const uint8_t* meta = blk + g.k_meta + 2 * j * kPage + t.slot;
+      r.meta = meta[0] | (uint32_t)meta[kPage] << 8;
+    } else {
+      const uint16_t* meta = (const uint16_t*)(blk + g.k_meta) + meta_index(t.slot, j);
+      r.meta = meta[0] | (uint32_t)meta[4] << 16;
+    }
+  }
 }
 
-// sm.gram: the products of all pairs of the n points.  The channels go through LDS 64 at a time (the loads of the next two
-// tiles are in flight while the current one is worked on); wave w owns the pieces w, w + 16, w + 32 of the lower
-// triangle, 32 x 32 points each: 2 x 2 tiles share their operands, which halves the LDS reads a product costs.  A product
-// is hi.hi + hi.lo + lo.hi (exact products, binary32 sums; what is dropped is of the order of 2^-22 of |x||y|).
-__device__ inline void gram_matrix(const float* __restrict__ x, int n, int dim, KmScratch& sm) {
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+
+// The eight channels 32 GRP + 8 j .. + 7, for every width in the same instructions: two words, each with four codes at bits 0,
+// 16, b and 16 + b.  m: the scales of group GRP.  A masked code is a binary16 subnormal, code * 2^-24, which the mixed-precision
+// multiply-add reads as it is; the scale takes the power of two.  In the paper's formats the magnitude bits go under the
+// exponent of a binary16 number and the sign bit to bit 15.
+template <int D, bool FP, int GRP>
+__device__ __forceinline__ void unpack_keys(const thinkv_config& c, const RawKeys<D>& r, uint32_t m, int bits, int j, float (&x)[8]) {
+  const uint32_t two = r.code[GRP / 2] >> (8 * (GRP & 1));
+  const uint32_t word[2] = {bits == 8 ? r.code[2 * GRP] : bits == 4 ? r.code[GRP] : two,
+                            bits == 8 ? r.code[2 * GRP + 1] : bits == 4 ? r.code[GRP] >> 8 : two >> 4};
+  float sc, zp = 0.f;
+  if (FP) {
+    sc = bits == 8 ? c.fp8_scale[0] : e4m3_value(m >> (8 * (j >> 1)) & 0xFFu);
+  } else {
+    sc = (float)__builtin_bit_cast(_Float16, (uint16_t)m) * 16777216.0f;
+    zp = (float)__builtin_bit_cast(_Float16, (uint16_t)(m >> 16));
+  }
+  const uint32_t mask = ((1u << bits) - 1u) * 0x10001u;
+#pragma unroll
+  for (int e = 0; e < 8; e += 2) {
+    const uint32_t two_codes = word[e >> 2] >> (e & 2 ? bits : 0) & mask;
+    if (FP) {
+      const int up = bits == 8 ? 7 : bits == 4 ? 9 : 10;   // a ternary magnitude is 2^-14
+      const uint32_t signs = 0x10001u << (bits - 1);
+      const uint32_t sign = bits == 2 ? two_codes & (two_codes << 1) & signs : two_codes & signs;   // a ternary zero has no sign
+      const f16x2 h = __builtin_bit_cast(f16x2, sign << (16 - bits) | (two_codes & ~signs) << up);
+      const float lift = bits == 8 ? 256.0f : 16384.0f;
+      x[e] = (float)h[0] * lift * sc;
+      x[e + 1] = (float)h[1] * lift * sc;
+    } else {
+      const f16x2 h = __builtin_bit_cast(f16x2, two_codes);
+      x[e] = fmaf((float)h[0], sc, zp);
+      x[e + 1] = fmaf((float)h[1], sc, zp);
+    }
+  }
+}
+
+// the scales of group GRP from the lane of the quad that holds them
+template <int GRP>
+__device__ __forceinline__ uint32_t quad_meta(uint32_t meta) {
+  return (uint32_t)__builtin_amdgcn_mov_dpp((int)meta, 0x55 * GRP, 0xF, 0xF, true);
+}
+
+// f(group) for the groups of a head, the group a compile-time constant
+template <int D, class F>
+__device__ __forceinline__ void for_groups(F f) {
+  f(std::integral_constant<int, 0>{});
+  f(std::integral_constant<int, 1>{});
+  if constexpr (D == 128) {
+    f(std::integral_constant<int, 2>{});
+    f(std::integral_constant<int, 3>{});
+  }
+}
+
+__device__ __forceinline__ void store_row(float* dst, const float (&x)[8]) {
+  *(float4*)dst = make_float4(x[0], x[1], x[2], x[3]);
+  *(float4*)(dst + 4) = make_float4(x[4], x[5], x[6], x[7]);
+}
+
+// the binary32 rows of the tokens [from, to)
+template <int D, bool FP>
+__device__ __forceinline__ void write_rows(const thinkv_view& v, const TbeArgs& a, int from, int to, TokenAt* at) {
+  const int per = 4 * v.cfg.n_kv_heads, count = to - from;
+  __syncthreads();   // the tokens before have been used
+  if ((int)threadIdx.x < count) at[threadIdx.x] = token_at(v, a, from + threadIdx.x);
+  __syncthreads();
+  for (int idx = threadIdx.x; idx < count * per; idx += kGramThreads) {
+    const int i = idx / per, it = idx - i * per, hd = it >> 2, j = it & 3;
+    const int bits = at[i].bits;
+    RawKeys<D> r;
+    load_keys<D, FP>(at[i], hd, j, r);
+    float* row = a.x + (int64_t)(from + i) * a.dim + hd * D + 8 * j;
+    for_groups<D>([&](auto grp) {
+      constexpr int G = decltype(grp)::value;
+      float x[8];
+      unpack_keys<D, FP, G>(v.cfg, r, quad_meta<G>(r.meta), bits, j, x);
+      store_row(row + 32 * G, x);
+    });
+  }
+}
+
+// ---- gram
+struct GramScratch {
+  _Float16 xs[kTbeMaxTokens][kPadH];   // one tile: 64 channels of every point, each as high + low binary16 part
+  TokenAt at[kTbeMaxTokens];
+};
+static_assert(sizeof(GramScratch) <= 81920, "two workgroups share the LDS of a compute unit");
+
+// eight channels into a tile row: x = hi + lo with hi = binary16(x), lo = binary16(x - hi), 22 significant bits
+__device__ __forceinline__ void store_split(_Float16* row, const float (&x)[8]) {
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  union { f16x8 all; f16x2 two[4]; } hi, lo;
+#pragma unroll
+  for (int e = 0; e < 8; e += 2) {
+    const f16x2 h = __builtin_convertvector((f32x2){x[e], x[e + 1]}, f16x2);
+    hi.two[e / 2] = h;
+    lo.two[e / 2] = __builtin_convertvector((f32x2){fmaf((float)h[0], -1.f, x[e]), fmaf((float)h[1], -1.f, x[e + 1])}, f16x2);
+  }
+  *(f16x8*)row = hi.all;
+  *(f16x8*)(row + kTile) = lo.all;
+}
+
+// The products of all pairs of the n points over the heads [h0, h1), in the pieces [first, first + 24) of the lower triangle,
+// into out.  The channels go through LDS 64 at a time (the next head's codes are under way during a head's last products); wave
+// w owns the pieces first + w, + 8, + 16, 32 x 32 points each: 2 x 2 tiles share their operands, which halves the LDS reads a
+// product costs.
+// A product is hi.hi + hi.lo + lo.hi (exact products, binary32 sums; what is dropped is of the order of 2^-22 of |x||y|).
+template <int D, bool FP>
+__device__ __forceinline__ void gram_matrix(const thinkv_view& v, int n, int h0, int h1, int first, GramScratch& sm, float* __restrict__ x, int dim,
+                                            float* __restrict__ out) {
+  const thinkv_config& c = v.cfg;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r = lane & 15, g = lane >> 4;
-  const int mb = (n + kMacro - 1) / kMacro, pieces = mb * (mb + 1) / 2;
-  constexpr int kC4 = kTile / 4;                           // float4 per tile row
-  constexpr int kXQ = kTbeMaxTokens * kC4 / kKmThreads;    // float4 loads per thread at most
-  const int xq = (mb * kMacro * kC4 + kKmThreads - 1) / kKmThreads;
-  int pi[kMacroPerWave], pj[kMacroPerWave];                // block row and column of the wave's pieces
-  f32x4 acc[kMacroPerWave][2][2];
+  const int mb = (n + kMacro - 1) / kMacro, end = mb * (mb + 1) / 2;
+  int pi[kPiecesPerWave], pj[kPiecesPerWave];              // block row and column of the wave's pieces
+  f32x4 acc[kPiecesPerWave][2][2];
 #pragma unroll
-  for (int t = 0; t < kMacroPerWave; ++t) {
-    int rest = wave + t * (kKmThreads / 64), i = 0;
+  for (int t = 0; t < kPiecesPerWave; ++t) {
+    int rest = first + wave + t * kGramWaves, i = 0;
     while (rest > i) rest -= ++i;
     pi[t] = i;
     pj[t] = rest;
@@ -209,28 +274,41 @@ __device__ inline void gram_matrix(const float* __restrict__ x, int n, int dim, 
 #pragma unroll
       for (int w = 0; w < 2; ++w) acc[t][u][w] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-  float4 pa[kXQ], pb[kXQ];   // two tiles ahead, used in turn
-  auto fetch = [&](int d0, float4 (&px)[kXQ]) {
+  RawKeys<D> raw[2];
+  // the places come from LDS every time: held in registers they would be in the way of the products
+  auto fetch = [&](int hd) {
+    if (hd >= h1) return;
 #pragma unroll
-    for (int q = 0; q < kXQ; ++q)
-      if (q < xq) {
-        const int idx = tid + kKmThreads * q, row = idx / kC4, c4 = idx % kC4;
-        px[q] = row < n && d0 < dim ? *(const float4*)&x[(int64_t)row * dim + d0 + 4 * c4] : make_float4(0.f, 0.f, 0.f, 0.f);
-      }
+    for (int q = 0; q < 2; ++q)
+      if (16 * wave + kGramThreads / 4 * q < n) load_keys<D, FP>(sm.at[16 * wave + r + kGramThreads / 4 * q], hd, g, raw[q]);
   };
-  auto tile = [&](int d0, float4 (&px)[kXQ]) {
+  auto tile = [&](int hd, auto half) {
+    constexpr int G0 = 2 * decltype(half)::value;
     __syncthreads();   // the previous tile has been used
+    // a wave takes sixteen tokens, lane (r, g) the chunk g of token r: sixteen lanes write to sixteen rows, whose
+    // starts lie four banks apart
 #pragma unroll
-    for (int q = 0; q < kXQ; ++q)
-      if (q < xq) {
-        const int idx = tid + kKmThreads * q;
-        store_split(sm.xs[idx / kC4], 4 * (idx % kC4), px[q]);
+    for (int q = 0; q < 2; ++q) {
+      const int t = 16 * wave + r + kGramThreads / 4 * q;
+      if (16 * wave + kGramThreads / 4 * q < n) {   // rows that pad the sixteen are zeros
+        const int bits = sm.at[t].bits;
+        float val[8];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const uint32_t m = (uint32_t)__builtin_amdgcn_ds_bpermute(64 * (G0 + u) + 4 * r, (int)raw[q].meta);
+          if (u == 0) unpack_keys<D, FP, G0>(c, raw[q], m, bits, g, val);
+          else unpack_keys<D, FP, G0 + 1>(c, raw[q], m, bits, g, val);
+          store_split(&sm.xs[t][32 * u + 8 * g], val);
+          if (first == 0 && t < n) store_row(&x[(int64_t)t * dim + hd * D + 32 * (G0 + u) + 8 * g], val);
+        }
       }
+    }
+    if (G0 == D / kGroup - 2) fetch(hd + 1);
     __syncthreads();
-    fetch(d0 + 2 * kTile, px);
 #pragma unroll
-    for (int t = 0; t < kMacroPerWave; ++t)
-      if (wave + t * (kKmThreads / 64) < pieces) {
+    for (int t = 0; t < kPiecesPerWave; ++t)
+      if (first + wave + t * kGramWaves < end) {
+        const bool diag = pi[t] == pj[t];
 #pragma unroll
         for (int ks = 0; ks < kTile / 32; ++ks) {
           // lane (r, g) holds channels 32 ks + 8 g .. + 7 of its row, on both sides
@@ -238,33 +316,47 @@ __device__ inline void gram_matrix(const float* __restrict__ x, int n, int dim, 
 #pragma unroll
           for (int u = 0; u < 2; ++u) {
             const _Float16* ra = sm.xs[kMacro * pi[t] + 16 * u + r];
-            const _Float16* rb = sm.xs[kMacro * pj[t] + 16 * u + r];
             ah[u] = *(const f16x8*)&ra[32 * ks + 8 * g];
             al[u] = *(const f16x8*)&ra[kTile + 32 * ks + 8 * g];
-            bh[u] = *(const f16x8*)&rb[32 * ks + 8 * g];
-            bl[u] = *(const f16x8*)&rb[kTile + 32 * ks + 8 * g];
           }
+          if (diag) {
 #pragma unroll
-          for (int u = 0; u < 2; ++u)
-#pragma unroll
-            for (int w = 0; w < 2; ++w) {
-              acc[t][u][w] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[u], bh[w], acc[t][u][w], 0, 0, 0);
-              acc[t][u][w] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[u], bl[w], acc[t][u][w], 0, 0, 0);
-              acc[t][u][w] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al[u], bh[w], acc[t][u][w], 0, 0, 0);
+            for (int u = 0; u < 2; ++u) {
+              bh[u] = ah[u];
+              bl[u] = al[u];
             }
+          } else {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+              const _Float16* rb = sm.xs[kMacro * pj[t] + 16 * u + r];
+              bh[u] = *(const f16x8*)&rb[32 * ks + 8 * g];
+              bl[u] = *(const f16x8*)&rb[kTile + 32 * ks + 8 * g];
+            }
+          }
+          // the four tiles in turn: a product waits for the one before it into the same tile
+#pragma unroll
+          for (int part = 0; part < 3; ++part)
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+              for (int w = 0; w < 2; ++w)
+                acc[t][u][w] = __builtin_amdgcn_mfma_f32_16x16x32_f16(part == 2 ? al[u] : ah[u], part == 1 ? bl[w] : bh[w], acc[t][u][w], 0, 0, 0);
         }
       }
   };
-  fetch(0, pa);
-  fetch(kTile, pb);
-  for (int d0 = 0; d0 < dim; d0 += 2 * kTile) {
-    tile(d0, pa);
-    if (d0 + kTile < dim) tile(d0 + kTile, pb);
+  fetch(h0);
+  // rows that pad the last piece: zero
+  const int full = (n + 15) & ~15;
+  if (full & 16)
+    for (int i = tid; i < 16 * (kPadH / 8); i += kGramThreads)
+      *(f16x8*)&sm.xs[full + i / (kPadH / 8)][8 * (i % (kPadH / 8))] = f16x8{0, 0, 0, 0, 0, 0, 0, 0};
+  for (int hd = h0; hd < h1; ++hd) {
+    tile(hd, std::integral_constant<int, 0>{});
+    if constexpr (D == 128) tile(hd, std::integral_constant<int, 1>{});
   }
-  __syncthreads();   // the last tile has been used: its place becomes the matrix
 #pragma unroll
-  for (int t = 0; t < kMacroPerWave; ++t)
-    if (wave + t * (kKmThreads / 64) < pieces) {
+  for (int t = 0; t < kPiecesPerWave; ++t)
+    if (first + wave + t * kGramWaves < end) {
 #pragma unroll
       for (int u = 0; u < 2; ++u)
 #pragma unroll
@@ -272,205 +364,355 @@ __device__ inline void gram_matrix(const float* __restrict__ x, int n, int dim, 
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             const int p = kMacro * pi[t] + 16 * u + 4 * g + i, q = kMacro * pj[t] + 16 * w + r;
-            if (p < n && q <= p) sm.gram[tri(p) + q] = acc[t][u][w][i];
+            if (p < n && q <= p) out[tri(p) + q] = acc[t][u][w][i];
           }
     }
-  __syncthreads();
 }
 
-// f(point) for every point of a cluster's basis, in index order; the point is the same in all lanes
+// the segments that are clustered
+__device__ __forceinline__ bool seg_ok(const TbeArgs& a, int lo, int hi, int want) {
+  return hi - lo <= kTbeMaxTokens && want <= kTbeMaxKeep && want >= 1 && lo >= 0 && hi <= a.n_tok;
+}
+
+template <int D, bool FP>
+__global__ __launch_bounds__(kGramThreads, 4) void tbe_gram_kernel(thinkv_view v, TbeArgs a) {
+  __shared__ __attribute__((aligned(16))) GramScratch sm;
+  const int seg = blockIdx.x / kSlices, slice = blockIdx.x % kSlices, tid = threadIdx.x;
+  const bool outside = seg == a.n_seg;   // the last workgroups: tokens before the first segment and behind the last
+  const int lo = a.seg_offset[outside ? 0 : seg], hi = a.seg_offset[outside ? seg : seg + 1], n = hi - lo;
+  const int want = outside ? 0 : a.seg_keep[seg], H = v.cfg.n_kv_heads;
+  if (outside || n <= want || !seg_ok(a, lo, hi, want)) {   // not clustered: only the rows
+    int from = outside ? 0 : lo > 0 ? lo : 0, to = outside ? lo : hi;
+    for (int part = 0; part < (outside ? 2 : 1); ++part) {
+      to = to < a.n_tok ? to : a.n_tok;
+      for (from += slice * kTbeMaxTokens; from < to; from += kSlices * kTbeMaxTokens)
+        write_rows<D, FP>(v, a, from, from + kTbeMaxTokens < to ? from + kTbeMaxTokens : to, sm.at);
+      from = hi > 0 ? hi : 0;
+      to = a.n_tok;
+    }
+    return;
+  }
+  const int slices = gram_slices(a.gram_room, n, H);
+  if (slice >= slices) return;
+  if (tid < kTbeMaxTokens) {
+    TokenAt at = {v.arena[0], 0, 0};
+    if (tid < n) at = token_at(v, a, lo + tid);
+    sm.at[tid] = at;
+  }
+  __syncthreads();
+  float* out = a.gram + seg * a.gram_room + (int64_t)slice * tri(n);
+  const int mb = (n + kMacro - 1) / kMacro;
+  for (int first = 0; first < mb * (mb + 1) / 2; first += kPiecesPerWave * kGramWaves)
+    gram_matrix<D, FP>(v, n, H * slice / slices, H * (slice + 1) / slices, first, sm, a.x + (int64_t)lo * a.dim, a.dim, out);
+}
+
+// ---- kmeans
+// Twelve waves, two workgroups a compute unit: LDS holds the matrix of 192 points; the rows of the points 192..255 of a
+// larger segment stay in memory, in the first part of the matrix.
+constexpr int kKmThreads = 768;
+constexpr int kKmWaves = kKmThreads / 64;
+constexpr int kClPerThread = (kTbeMaxKeep + 2) / 3;       // clusters of a thread at most: there are three groups of waves or more
+constexpr int kPT = kTbeMaxTokens / 64;                   // tokens per lane of a wave that sorts a list
+constexpr int kWords = kTbeMaxTokens / 32;
+constexpr int kLdsPoints = 192;
+constexpr int kLdsGram = kLdsPoints * (kLdsPoints + 1) / 2;
+typedef float f32xk __attribute__((ext_vector_type(32)));
+static_assert(kClPerThread <= 32, "");
+
+struct KmScratch {
+  float gram[kLdsGram];                                        // products of all pairs of points, lower triangle
+  uint32_t basis[kTbeMaxKeep][kWords];                         // the points a cluster's centroid is the mean of
+  union {
+    struct {
+      float bd[kKmThreads];                                    // per group of waves: best distance of every point ...
+      uint8_t bj[kKmThreads];                                  // ... and the cluster it belongs to
+    };
+    uint32_t next[kTbeMaxKeep][kWords];                        // members under the assignment just made
+    struct {
+      unsigned long long best[kTbeMaxKeep];                    // survivors: nearest member, and the lowest index, of every cluster
+      int low[kTbeMaxKeep];
+    };
+  };
+  float own[kTbeMaxTokens];                                    // product of a point with the centroid it belongs to
+  float cc[kTbeMaxKeep];                                       // squared norms of the centroids
+  uint32_t span[kTbeMaxKeep];                                  // members in the list: first | count << 16
+  uint32_t list[kTbeMaxTokens / 4];                            // the points, cluster by cluster, in index order, a byte each
+  unsigned long long moved;                                    // clusters whose centroid has just changed
+  int vote[2];                                                 // a point changed its cluster, in iterations of either parity
+};
+static_assert(sizeof(KmScratch) <= 81920, "two workgroups share the LDS of a compute unit");
+
+// f(point) for every point of a cluster's basis, in index order, two at a time (the second -1 where there is none); the
+// points are the same in all lanes
 template <class F>
 __device__ __forceinline__ void for_basis(const uint32_t* mask, F f) {
-#pragma unroll
-  for (int w = 0; w < kTbeMaxTokens / 32; ++w) {
+  int held = -1;
+  for (int w = 0; w < kWords; ++w) {
     uint32_t m = __builtin_amdgcn_readfirstlane(mask[w]);
     while (m) {
-      const int i = __builtin_ctz(m);
+      const int i = 32 * w + __builtin_ctz(m);
       m &= m - 1;
-      f(32 * w + i);
+      if (held < 0) {
+        held = i;
+      } else {
+        f(held, i);
+        held = -1;
+      }
     }
   }
+  if (held >= 0) f(held, -1);
 }
 
-// Products of every point with every centroid that has one: thread (point tid % 256, quarter tid / 256) leaves those of the
-// clusters quarter, quarter + 4, ... in dot[]; sm.own of the points that are in a basis; sm.cc of the centroids that moved.
-__device__ inline void centroid_products(int n, int k, KmScratch& sm, float (&dot)[kClPerThread]) {
-  const int tid = threadIdx.x, p = tid & (kTbeMaxTokens - 1), lane = tid & 63;
-  const int quarter = __builtin_amdgcn_readfirstlane(tid / kTbeMaxTokens), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int pc = p < n ? p : n - 1, tp = tri(pc);
-  const int mine = sm.cluster[p];
-  const bool idle = (p & ~63) >= n;   // no point of the wave exists
-#pragma unroll
-  for (int i = 0; i < kClPerThread; ++i) {
-    const int j = quarter + kQuarters * i;
-    dot[i] = 0.f;
-    if (j < k && !idle) {
-      float sum = 0.f;
-      for_basis(sm.basis[j], [&](int m) { sum += sm.gram[pc >= m ? tp + m : tri(m) + pc]; });
-      dot[i] = sum * (1.0f / (float)sm.cnt[j]);
-      if (mine == j && p < n) sm.own[p] = dot[i];
-    }
-  }
-  __syncthreads();
-  // |c|^2 = mean over the basis of its points' products with the centroid: a wave per cluster, a fixed tree
-  for (int j = wave; j < k; j += kKmThreads / 64) {
-    if (!sm.moved[j]) continue;
-    float sum = 0.f;
-#pragma unroll
-    for (int w = 0; w < kTbeMaxTokens / 64; ++w) {
-      const int q = 64 * w + lane;
-      if (sm.basis[j][q >> 5] >> (q & 31) & 1u) sum += sm.own[q];
-    }
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, 64);
-    if (lane == 0) sm.cc[j] = sum * (1.0f / (float)sm.cnt[j]);
-  }
-  __syncthreads();
-}
-
-__global__ __launch_bounds__(kKmThreads) void tbe_kmeans_kernel(thinkv_view v, TbeArgs a) {
+__global__ __launch_bounds__(kKmThreads) __attribute__((amdgpu_waves_per_eu(6))) void tbe_kmeans_kernel(thinkv_view v, TbeArgs a) {
   const thinkv_config& c = v.cfg;
   const int seg = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lo = a.seg_offset[seg], hi = a.seg_offset[seg + 1];
   const int n = hi - lo, want = a.seg_keep[seg];
   if (n <= 0) return;
-  if (n > kTbeMaxTokens || want > kTbeMaxKeep || want < 1 || lo < 0 || hi > a.n_tok) {
-    // outside what this kernel covers: nothing is evicted, and the caller is told
-    if (tid == 0) atomicOr(&v.dev_status[c.max_seqs * c.n_layers], THINKV_ST_BAD_SEGMENT);
+  const bool ok = seg_ok(a, lo, hi, want);
+  if (!ok || want >= n) {
+    // outside what this kernel covers: nothing is evicted, and the caller is told; or everything survives
+    if (!ok && tid == 0) atomicOr(&v.dev_status[c.max_seqs * c.n_layers], THINKV_ST_BAD_SEGMENT);
     for (int i = tid; i < n && lo >= 0 && lo + i < a.n_tok; i += kKmThreads) {
       a.ev_handle[lo + i] = -1;
       a.assign[lo + i] = -1;
     }
     return;
   }
-  if (want >= n) {
-    for (int i = tid; i < n; i += kKmThreads) {
-      a.ev_handle[lo + i] = -1;
-      a.assign[lo + i] = -1;
-    }
-    return;
-  }
   const int k = want, dim = a.dim;
-  const float* x = a.x + (int64_t)lo * dim;
-  float* cent = a.cent + (int64_t)seg * kTbeMaxKeep * dim;
   __shared__ __attribute__((aligned(16))) KmScratch sm;
-  // initial centroids: evenly spaced points
-  for (int i = tid; i < kTbeMaxKeep * (kTbeMaxTokens / 32); i += kKmThreads) (&sm.basis[0][0])[i] = 0u;
-  if (tid < kTbeMaxTokens) sm.cluster[tid] = -1;
+  // the parts of the matrix meet, in order
+  float* parts = a.gram + seg * a.gram_room;
+  const int slices = gram_slices(a.gram_room, n, c.n_kv_heads);
+  const bool big = n > kLdsPoints;
+  const int all = tri(n);
+  for (int i0 = tid; i0 < all; i0 += 4 * kKmThreads) {   // sixteen loads under way
+    float part[kSlices][4];
+#pragma unroll
+    for (int s = 0; s < kSlices; ++s)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int i = i0 + kKmThreads * q;
+        part[s][q] = s < slices && i < all ? parts[s * all + i] : 0.f;
+      }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int i = i0 + kKmThreads * q;
+      float sum = part[0][q];
+#pragma unroll
+      for (int s = 1; s < kSlices; ++s) sum += part[s][q];
+      if (i < kLdsGram && i < all) sm.gram[i] = sum;
+      else if (i < all) parts[i] = sum;
+    }
+  }
+  // The waves form groups of `pw` that hold all points between them, and a group looks at every `groups`-th cluster
+  const int pw = (n + 63) >> 6, groups = kKmWaves / pw;
+  const int group = wave / pw, p = (wave - group * pw) * 64 + lane;
+  const bool here = p < n;
+  const int pc = here ? p : n - 1, tp = tri(pc);
+  // initial centroids: evenly spaced points, distinct, since k < n
+  for (int i = tid; i < kTbeMaxKeep * kWords; i += kKmThreads) (&sm.basis[0][0])[i] = 0u;
+  if (tid < kTbeMaxKeep) sm.span[tid] = 0u;
+  if (tid < kTbeMaxTokens / 4) sm.list[tid] = 0u;   // every byte is a point's at any time
+  if (tid < 2) sm.vote[tid] = 0;
   __syncthreads();
   if (tid < k) {
-    const int p = (tid * n) / k;   // distinct, since k < n
-    sm.basis[tid][p >> 5] = 1u << (p & 31);
-    sm.cluster[p] = tid;
-    sm.cnt[tid] = 1;
-    sm.moved[tid] = 1;
+    const int q = (tid * n) / k;
+    sm.basis[tid][q >> 5] = 1u << (q & 31);
+    ((uint8_t*)sm.list)[tid] = (uint8_t)q;
+    sm.span[tid] = (uint32_t)tid | 1u << 16;
   }
-  gram_matrix(x, n, dim, sm);
-  const int p = tid & (kTbeMaxTokens - 1), quarter = tid / kTbeMaxTokens;
-  float dot[kClPerThread];
-  int mine = -1;   // this point's cluster at the last assignment
+  if (tid == 0) sm.moved = k == 64 ? ~0ull : (1ull << k) - 1;
+  const int seed = (pc * k + n - 1) / n;             // the only cluster whose first centroid the point can be
+  int mine = seed < k && (seed * n) / k == pc ? seed : -1;   // the cluster whose basis this point is in
+  int last = -1;                                     // this point's cluster at the last assignment
+  __syncthreads();
+  f32xk dot;
+#pragma unroll
+  for (int i = 0; i < kClPerThread; ++i) dot[i] = 0.f;
+  // Products of every point with the centroids that moved: a thread leaves those of the clusters group, group + groups, ...
+  // in dot[]; own of the points that are in a basis, and the squared norms of the centroids
+  auto products = [&]() {
+    const uint32_t list = sm.list[lane], span = sm.span[lane];
+    const uint32_t inv = __builtin_bit_cast(uint32_t, 1.0f / (float)(span >> 16));
+    const uint64_t moved = (uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(sm.moved >> 32)) << 32 | (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)sm.moved);
+    auto place = [&](int q) {   // of the product with the q-th point of the list, the same point in all lanes
+      const int m = (int)((uint32_t)__builtin_amdgcn_readlane(list, q >> 2) >> (8 * (q & 3))) & 255;
+      const int below = tp + m, above = tri(m) + pc;
+      return pc >= m ? below : above;
+    };
+    for (int i = 0, j = group; j < k; ++i, j += groups) {
+      if (!(moved >> j & 1)) continue;
+      const uint32_t sp = __builtin_amdgcn_readlane(span, j);
+      int q = (int)(sp & 0xFFFFu);
+      const int end = q + (int)(sp >> 16);
+      float sum = 0.f;
+      if (!big) {
+        float ahead = sm.gram[place(q)];
+        while (++q < end) {
+          const float a0 = ahead;
+          ahead = sm.gram[place(q)];
+          sum += a0;
+        }
+        sum += ahead;
+      } else {
+        for (; q < end; ++q) {
+          const int at = place(q);
+          sum += at < kLdsGram ? sm.gram[at] : __builtin_nontemporal_load(&parts[at]);
+        }
+      }
+      const float d = sum * __builtin_bit_cast(float, __builtin_amdgcn_readlane(inv, j));
+      dot[i] = d;
+      if (mine == j && here) sm.own[p] = d;
+    }
+    __syncthreads();
+    // |c|^2 = mean over the basis of its points' products with the centroid: eight lanes per cluster, a fixed tree
+    const int j = tid >> 3;
+    if (j < k && (sm.moved >> j & 1)) {
+      const int q0 = (int)(sm.span[j] & 0xFFFFu), cnt = (int)(sm.span[j] >> 16);
+      float sum = 0.f;
+      for (int q = tid & 7; q < cnt; q += 8) sum += sm.own[((const uint8_t*)sm.list)[q0 + q]];
+#pragma unroll
+      for (int d = 4; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, 8);
+      if ((tid & 7) == 0) sm.cc[j] = sum * (1.0f / (float)cnt);
+    }
+    __syncthreads();
+  };
   bool converged = false;
   for (int it = 0; it < a.max_iters; ++it) {
     // centroids: the initial ones, later the means under the previous assignment
-    centroid_products(n, k, sm, dot);
+    products();
     // nearest cluster of every point: |c|^2 - 2 x.c decides (|x|^2 is common to a point's candidates); ties go to the
     // lowest cluster
+    const uint32_t cc = __builtin_bit_cast(uint32_t, sm.cc[lane]);
     float bd = INFINITY;
     int bj = kTbeMaxKeep;
 #pragma unroll
     for (int i = 0; i < kClPerThread; ++i) {
-      const int j = quarter + kQuarters * i;
-      const float d = j < k ? fmaf(-2.f, dot[i], sm.cc[j]) : INFINITY;
-      if (d < bd) {
-        bd = d;
-        bj = j;
+      const int j = group + groups * i;
+      if (j < k) {
+        const float d = fmaf(-2.f, dot[i], __builtin_bit_cast(float, __builtin_amdgcn_readlane(cc, j)));
+        if (d < bd) {
+          bd = d;
+          bj = j;
+        }
       }
     }
-    sm.bd[quarter][p] = bd;
-    sm.bj[quarter][p] = bj;
-    for (int i = tid; i < kTbeMaxKeep * (kTbeMaxTokens / 32); i += kKmThreads) (&sm.next[0][0])[i] = 0u;
+    sm.bd[tid] = bd;
+    sm.bj[tid] = (uint8_t)bj;
     __syncthreads();
-    bd = sm.bd[0][p];
-    bj = sm.bj[0][p];
-#pragma unroll
-    for (int w = 1; w < kQuarters; ++w) {
-      const float od = sm.bd[w][p];
-      const int oj = sm.bj[w][p];
+    bd = sm.bd[p];
+    bj = sm.bj[p];
+    for (int w = 1; w < groups; ++w) {
+      const float od = sm.bd[w * pw * 64 + p];
+      const int oj = sm.bj[w * pw * 64 + p];
       if (od < bd || (od == bd && oj < bj)) {
         bd = od;
         bj = oj;
       }
     }
     if (bj >= k) bj = 0;   // no candidate compares (the distances are not numbers): the first cluster, as a comparison that never holds leaves it
-    const int changed = p < n && bj != mine;
-    mine = bj;
-    if (!__syncthreads_or(changed)) {
+    if (here && bj != last) sm.vote[it & 1] = 1;
+    last = mine = bj;
+    __syncthreads();
+    if (!sm.vote[it & 1]) {
       converged = true;   // the products at hand are those with the final centroids
       break;
     }
+    if (tid == 0) sm.vote[~it & 1] = 0;
     // members of every cluster; a cluster without any keeps its basis
-    if (quarter == 0 && p < n) {
-      sm.cluster[p] = mine;
-      atomicOr(&sm.next[mine][p >> 5], 1u << (p & 31));
+    for (int i = tid; i < kTbeMaxKeep * kWords; i += kKmThreads) (&sm.next[0][0])[i] = 0u;
+    __syncthreads();
+    if (group == 0 && here) atomicOr(&sm.next[mine][p >> 5], 1u << (p & 31));
+    __syncthreads();
+    if (wave == 0) {
+      int m = 0;
+      bool differs = false;
+      uint32_t row[kWords];
+#pragma unroll
+      for (int w = 0; w < kWords; ++w) {
+        row[w] = sm.next[lane][w];
+        m += __popc(row[w]);
+        differs |= row[w] != sm.basis[lane][w];
+      }
+      if (m > 0) {
+#pragma unroll
+        for (int w = 0; w < kWords; ++w) sm.basis[lane][w] = row[w];
+      }
+      int upto = m;
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) {
+        const int o = __shfl_up(upto, d, 64);
+        if (lane >= d) upto += o;
+      }
+      sm.span[lane] = (uint32_t)(upto - m) | (uint32_t)m << 16;
+      const unsigned long long moved = __ballot(m > 0 && differs);
+      if (lane == 0) sm.moved = moved;
     }
     __syncthreads();
-    if (tid < k) {
-      int m = 0;
-#pragma unroll
-      for (int w = 0; w < kTbeMaxTokens / 32; ++w) m += __popc(sm.next[tid][w]);
-      sm.moved[tid] = m > 0;
-      if (m > 0) {
-        sm.cnt[tid] = m;
-#pragma unroll
-        for (int w = 0; w < kTbeMaxTokens / 32; ++w) sm.basis[tid][w] = sm.next[tid][w];
-      }
+    if (group == 0 && here) {
+      int rank = 0;
+      for (int w = 0; w < (p >> 5); ++w) rank += __popc(sm.next[mine][w]);
+      rank += __popc(sm.next[mine][p >> 5] & ((1u << (p & 31)) - 1u));
+      ((uint8_t*)sm.list)[(sm.span[mine] & 0xFFFFu) + rank] = (uint8_t)p;
     }
     __syncthreads();
   }
   // ---- survivors: nearest member of every cluster under the final centroids
-  if (!converged) centroid_products(n, k, sm, dot);
+  if (!converged) products();
   if (tid < kTbeMaxKeep) {
     sm.low[tid] = kTbeMaxTokens;
     sm.best[tid] = ~0ull;
   }
   __syncthreads();
-  if (quarter == 0 && p < n) {
-    const float dist = fmaxf(fmaf(-2.f, sm.own[p], sm.gram[tri(p) + p]) + sm.cc[mine], 0.f);
+  if (group == 0 && here) {
+    const float dist = fmaxf(fmaf(-2.f, sm.own[p], tp + p < kLdsGram ? sm.gram[tp + p] : parts[tp + p]) + sm.cc[mine], 0.f);
     atomicMin(&sm.low[mine], p);
     // distances are not negative, so their bit patterns order like the numbers; the index breaks ties
     atomicMin(&sm.best[mine], ((unsigned long long)__builtin_bit_cast(uint32_t, dist) << 32) | (unsigned)p);
   }
   __syncthreads();
-  if (quarter == 0 && p < n) {
+  if (group == 0 && here) {
     // two members are equally near their mean whatever the rounding says: the earlier one stays (a cluster with members
     // has them as its basis)
-    const bool keep = sm.cnt[mine] <= 2 ? p == sm.low[mine] : (int)(sm.best[mine] & 0xFFFFFFFFull) == p;
+    const bool keep = (sm.span[mine] >> 16) <= 2 ? p == sm.low[mine] : (int)(sm.best[mine] & 0xFFFFFFFFull) == p;
     a.ev_handle[lo + p] = keep ? -1 : a.tok_handle[lo + p];
     a.assign[lo + p] = mine;
   }
-  // ---- the centroids, for callers that look at them: a wave per cluster, up to 1,024 channels at a time (four loads a
-  // lane in flight), members in index order
-  for (int j = wave; j < k; j += kKmThreads / 64) {
-    const float inv = 1.0f / (float)sm.cnt[j];
+  __syncthreads();   // the matrix in memory has been read: the centroids take its place
+  // ---- the centroids, for callers that look at them: a wave per cluster, up to 1,024 channels at a time, two members' rows
+  // (eight loads a lane) in flight, members in index order
+  const float* x = a.x + (int64_t)lo * dim;
+  float* cent = a.cent + (int64_t)seg * kTbeMaxKeep * dim;
+  for (int j = wave; j < k; j += kKmWaves) {
+    int cnt = 0;
+#pragma unroll
+    for (int w = 0; w < kWords; ++w) cnt += __popc(sm.basis[j][w]);
+    const float by = 1.0f / (float)cnt;
     for (int d0 = 4 * lane; d0 < dim; d0 += 1024) {
-      float4 sum[4];
+      f32x4 sum[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) sum[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-      for_basis(sm.basis[j], [&](int m) {
-        float4 t[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) t[u] = d0 + 256 * u < dim ? *(const float4*)&x[(int64_t)m * dim + d0 + 256 * u] : make_float4(0.f, 0.f, 0.f, 0.f);
+      for (int u = 0; u < 4; ++u) sum[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for_basis(sm.basis[j], [&](int m0, int m1) {
+        f32x4 t[2][4];
+        const float* r0 = x + (int64_t)m0 * dim + d0;
+        const float* r1 = x + (int64_t)(m1 < 0 ? m0 : m1) * dim + d0;
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-          sum[u].x += t[u].x;
-          sum[u].y += t[u].y;
-          sum[u].z += t[u].z;
-          sum[u].w += t[u].w;
+          if (d0 + 256 * u >= dim) continue;
+          t[0][u] = *(const f32x4*)(r0 + 256 * u);
+          if (m1 >= 0) t[1][u] = *(const f32x4*)(r1 + 256 * u);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          if (d0 + 256 * u >= dim) continue;
+          sum[u] += t[0][u];
+          if (m1 >= 0) sum[u] += t[1][u];
         }
       });
 #pragma unroll
       for (int u = 0; u < 4; ++u)
-        if (d0 + 256 * u < dim) *(float4*)&cent[(int64_t)j * dim + d0 + 256 * u] = make_float4(sum[u].x * inv, sum[u].y * inv, sum[u].z * inv, sum[u].w * inv);
+        if (d0 + 256 * u < dim) *(f32x4*)&cent[(int64_t)j * dim + d0 + 256 * u] = sum[u] * by;
     }
   }
 }
@@ -488,15 +730,22 @@ int launch_tbe_select(const thinkv_view& v, int layer, const int32_t* tok_seq, c
   a.x = (float*)(((uintptr_t)workspace + 255) & ~(uintptr_t)255);
   a.cent = a.x + (size_t)n_tok * a.dim;
   a.assign = (int32_t*)(a.cent + (size_t)n_seg * kTbeMaxKeep * a.dim);
+  const bool inside = gram_in_centroids(a.dim);
+  a.gram = inside ? a.cent : (float*)(a.assign + n_tok);
+  a.gram_room = inside ? (int64_t)kTbeMaxKeep * a.dim : kMaxGram;
   a.layer = layer;
   a.n_seg = n_seg;
   a.n_tok = n_tok;
   a.max_iters = max_iters;
-  const dim3 groups((n_tok + kGatherTokens - 1) / kGatherTokens);
-  if (v.cfg.head_dim == 128)
-    hipLaunchKernelGGL(tbe_gather_kernel<128>, groups, dim3(256), 0, st, v, a);
-  else
-    hipLaunchKernelGGL(tbe_gather_kernel<64>, groups, dim3(256), 0, st, v, a);
+  const bool fp = v.cfg.format == THINKV_FMT_FP;
+  const dim3 grid((n_seg + 1) * kSlices), block(kGramThreads);
+  if (v.cfg.head_dim == 128) {
+    if (fp) hipLaunchKernelGGL((tbe_gram_kernel<128, true>), grid, block, 0, st, v, a);
+    else hipLaunchKernelGGL((tbe_gram_kernel<128, false>), grid, block, 0, st, v, a);
+  } else {
+    if (fp) hipLaunchKernelGGL((tbe_gram_kernel<64, true>), grid, block, 0, st, v, a);
+    else hipLaunchKernelGGL((tbe_gram_kernel<64, false>), grid, block, 0, st, v, a);
+  }
   hipLaunchKernelGGL(tbe_kmeans_kernel, dim3(n_seg), dim3(kKmThreads), 0, st, v, a);
   return hipGetLastError() == hipSuccess ? THINKV_OK : THINKV_E_HIP;
 }

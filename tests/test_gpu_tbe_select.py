@@ -1,0 +1,79 @@
+"""Survivor choice at the edges of its kernels: one to four workgroups to a segment's products (head counts, segment sizes and
+the room for the parts), rows at tile edges and behind the part of the matrix that LDS holds (192 points), tokens outside every
+segment, both number formats.  Keys, the last Lloyd step and the survivors as in test_gpu_tbe, against the oracle's keys."""
+import numpy as np
+import pytest
+import torch
+
+import parity
+from oracle import tbe as otbe
+from paper_2510_01290_amd import synth
+from test_gpu_tbe import MIN_MARGIN, _check_clustering, _gpu_select
+
+pytestmark = pytest.mark.gpu
+
+SIZES = [2, 15, 16, 17, 33, 64, 65, 127, 129, 191, 192, 193, 224, 225, 256]
+KEEPS = [1, 8, 4, 16, 32, 63, 64, 64, 5, 64, 3, 33, 64, 64, 16]
+
+
+@pytest.mark.parametrize("heads,D,fmt,bits", [(1, 64, "int", (8, 2, 4)), (3, 64, "fp", (2, 4, 8)), (9, 64, "int", (2, 4, 8)),
+                                              (4, 128, "int", (8, 2, 4)), (5, 128, "fp", (2, 4, 8)), (16, 128, "int", (4, 4, 4))])
+def test_select_at_the_edges(heads, D, fmt, bits):
+    print("survivor choice at the edges", heads, D, fmt, bits, flush=True)
+    geom = synth.Geometry(1, heads, heads, D, "f16", bits, fmt)
+    wl = synth.bulk_evict_refill("tbe-edges", geom, 61, 1, np.array([sum(SIZES) + 90]), {synth.E: 0.1}, refill=0)
+    gc = parity.make_gpu_cache(wl)
+    gr = synth.ScriptRunner(wl, parity.GpuBackend(gc)).run()
+    ob = parity.make_oracle(wl)
+    synth.ScriptRunner(wl, ob).run()
+    dead = {(int(s), int(p)) for op in wl.ops if isinstance(op, synth.Evict) for s, p in zip(op.seqs, op.pos)}
+    hs = gr.handle[(0, 0)]
+    live = np.array([int(hs[p]) for p in range(int(wl.q_pos[0]) + 1) if hs[p] != -1 and (0, p) not in dead], np.int32)
+    sizes, keeps = SIZES, KEEPS
+    while sum(sizes) + 12 > len(live):            # the evictions took some: the last segments go
+        sizes, keeps = sizes[1:], keeps[1:]
+    off = (7 + np.concatenate([[0], np.cumsum(sizes)])).astype(np.int32)      # seven tokens before the first segment, five behind
+    th = live[:off[-1] + 5]
+    ts, keep = np.zeros(len(th), np.int32), np.array(keeps, np.int32)
+    got, x, cent, assign = _gpu_select(gc, 0, ts, th, off, keep, inspect=True)
+    stored = otbe.segment_keys(ob.cache, 0, 0, th)
+    assert np.abs(x - stored).max() <= 1e-6 * np.abs(stored).max()            # binary32 rows of every listed token
+    inner = slice(off[0], off[-1])
+    n = _check_clustering(gc, ob, 0, ts, th, off, keep, 8, got, x, cent, assign)
+    assert n == len(keeps)
+    want, margins = otbe.select_evictions(ob.cache, 0, ts[inner], th[inner], off - off[0], keep, 8)
+    clear = 0
+    for sg, (a, b) in enumerate(zip(off[:-1], off[1:])):
+        if margins[sg] > MIN_MARGIN:
+            clear += 1
+            assert np.array_equal(got[a:b], want[a - off[0]:b - off[0]]), (sg, margins[sg])
+    assert clear >= len(keeps) // 2
+    assert (got[:off[0]] == 12345).all() and (got[off[-1]:] == 12345).all()   # tokens of no segment: untouched
+    assert int(gc.dev_status.abs().sum().item()) == 0
+
+
+def test_a_key_that_is_no_number_spoils_its_own_cluster_only():
+    """a token whose scales are infinite: its products are not numbers, it joins the first cluster; the others are clustered as
+    they are without it, but for that cluster"""
+    print("a key that is no number", flush=True)
+    geom = synth.Geometry(1, 2, 2, 64, "f16", (8, 2, 4))
+    wl = synth.bulk_evict_refill("tbe-nan", geom, 62, 1, np.array([200]), {}, refill=0)
+    gc = parity.make_gpu_cache(wl)
+    gr = synth.ScriptRunner(wl, parity.GpuBackend(gc)).run()
+    hs = gr.handle[(0, 0)]
+    th = np.array([int(h) for h in hs[:150]], np.int32)
+    cls, pi, slot = th[70] >> 28, (th[70] >> 4) & 0xFFFFFF, th[70] & 15
+    pid = int(gc.block_table[0, 0, cls, pi].item())
+    block = gc.page_bytes[cls] // 2
+    codes = 64 * 2 * gc.bits_of_class[cls]
+    at = pid * gc.page_bytes[cls] + codes + 2 * ((slot >> 2) * 8 + (slot & 3))   # scale of group 0, head 0
+    assert at < (pid + 1) * gc.page_bytes[cls] and block > codes
+    gc.arena[cls][at:at + 2] = torch.tensor([0x00, 0x7C], dtype=torch.uint8, device=gc.device)
+    off, keep = np.array([0, 150], np.int32), np.array([12], np.int32)
+    got, x, cent, assign = _gpu_select(gc, 0, np.zeros(150, np.int32), th, off, keep, inspect=True)
+    assert not np.isfinite(x[70]).all() and np.isfinite(np.delete(x, 70, 0)).all()
+    assert assign[70] == 0 and 1 <= (got == -1).sum() <= 12
+    for j in np.unique(assign):
+        assert (got[assign == j] == -1).sum() == 1
+    fine = [j for j in range(1, 12) if (assign == j).any()]
+    assert len(fine) >= 6 and np.isfinite(cent[0, fine]).all()
