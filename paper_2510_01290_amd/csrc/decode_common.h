@@ -34,7 +34,7 @@ constexpr int kWindowWaves = 8, kWindowBlock = 64 * kWindowWaves;
 __host__ __device__ constexpr int window_ring_bytes(int head_dim) { return head_dim == 128 ? 14336 : 9216; }
 __host__ __device__ constexpr int window_lds_bytes(int head_dim) { return kWindowWaves * window_ring_bytes(head_dim) + 9 * kWindowBlock * 4 + 3 * kWindowWaves * 4; }
 
-// Items dealt over a batch (deal_item): fewest pages a wave is worth, one chunk of its ticket counter.
+// Items dealt over a batch (deal_item): fewest pages a wave is worth.
 constexpr int kDealPages = 8;
 
 namespace thinkv {
@@ -72,12 +72,35 @@ struct ItemLoc {
 // a value that is the same in all lanes but was read by a vector load, as a scalar: what is computed from it stays scalar
 __device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
 
+// x / y of scalars, 0 <= x < 2^24 and 0 < y < 2^24, exactly: the quotient by the reciprocal is at most two off.  (The compiler's
+// 32-bit division takes thirty instructions and its 64-bit one 130; six of those to find a wave's share of the page lists were
+// 1.7 us of every launch.)
+__device__ __forceinline__ int quotient(int x, int y) {
+  int q = (int)((float)x * __builtin_amdgcn_rcpf((float)y));
+#pragma unroll
+  for (int again = 0; again < 2; ++again) {
+    const int r = x - q * y;
+    q += (r >= y ? 1 : 0) - (r < 0 ? 1 : 0);
+  }
+  return uniform(q);
+}
+// x * j / n for 0 <= x < 2^24, 0 <= j <= n <= kMaxRowsPerHead
+__device__ __forceinline__ int portion(int x, int j, int n) {
+  if (n == 1) return j ? x : 0;
+  const int each = quotient(x, n);
+  return j * each + quotient(j * (x - n * each), n);
+}
+
 __device__ inline int seq_pages(const thinkv_view& v, int layer, int seq, int* np) {
   const thinkv_config& c = v.cfg;
+  const bool valid = seq >= 0 && seq < c.max_seqs;
+  const int32_t* at = v.n_pages + (valid ? npages_index(c, seq, layer, 0) : 0);   // (there is a first sequence)
   int tot = 0;
 #pragma unroll
+  for (int k = 0; k < 3; ++k) np[k] = uniform(at[k]);
+#pragma unroll
   for (int k = 0; k < 3; ++k) {
-    np[k] = (seq >= 0 && seq < c.max_seqs) ? uniform(v.n_pages[npages_index(c, seq, layer, k)]) : 0;
+    np[k] = valid ? np[k] : 0;
     tot += np[k];
   }
   return tot;
@@ -86,21 +109,34 @@ __device__ inline int seq_pages(const thinkv_view& v, int layer, int seq, int* n
 // Item id -> head, item number, item count, first row.  Item-major: ids [j * heads, (j + 1) * heads) are item j of every
 // head (the hardware starts workgroups in id order and a SIMD favours its oldest wave: every head gets workers of every
 // age), shifted by j so that the items of a head land on different XCDs (ids go round the XCDs).
-__device__ inline ItemLoc locate_item(const thinkv_view& v, const DecodeArgs& a, int id) {
-  const thinkv_config& c = v.cfg;
+__device__ inline ItemLoc locate_head(const thinkv_config& c, const DecodeArgs& a, int id) {   // ... without the item count
   const int H = c.n_kv_heads, heads = H * a.B;
   ItemLoc it;
-  it.j = uniform(id / heads);   // (divisions are vector arithmetic)
-  int rest = id - it.j * heads - uniform(it.j % heads);
-  if (rest < 0) rest += heads;
-  it.b = uniform(rest / H);
+  int rest = id;
+  it.j = 0;
+  if (a.per_head > 1) {
+    it.j = uniform(id / heads);
+    rest = id - it.j * heads - uniform(it.j % heads);
+    if (rest < 0) rest += heads;
+  }
+  it.b = heads < (1 << 24) ? quotient(rest, H) : uniform(rest / H);
   it.hkv = rest - it.b * H;
-  int np[3];
-  const int tot = seq_pages(v, a.layer, uniform(a.seq_ids[it.b]), np);
-  int n = uniform((int)(((int64_t)tot + a.ppi - 1) / a.ppi));
-  n = n < 1 ? 1 : (n > a.per_head ? a.per_head : n);
-  it.n = n;
+  it.n = 0;
   it.row0 = rest * a.per_head;
+  return it;
+}
+// the items of a head whose sequence holds `pages`
+__device__ inline void count_items(const DecodeArgs& a, int pages, ItemLoc& it) {
+  it.n = 1;
+  if (a.per_head > 1) {
+    const int n = uniform((int)(((uint32_t)pages + (uint32_t)a.ppi - 1u) / (uint32_t)a.ppi));   // (at most 2^26 pages)
+    it.n = n < 1 ? 1 : (n > a.per_head ? a.per_head : n);
+  }
+}
+__device__ inline ItemLoc locate_item(const thinkv_view& v, const DecodeArgs& a, int id) {
+  ItemLoc it = locate_head(v.cfg, a, id);
+  int np[3];
+  count_items(a, seq_pages(v, a.layer, uniform(a.seq_ids[it.b]), np), it);
   return it;
 }
 
@@ -143,14 +179,19 @@ __device__ inline Deal deal_item(const thinkv_view& v, const DecodeArgs& a, int 
   float all = 0.f;
 #pragma unroll
   for (int u = 0; u < kU; ++u) {
-    ids[u] = p[u][0] = p[u][1] = p[u][2] = 0;
-    if (64 * u < a.B) {
-      const int seq = ids[u] = a.seq_ids[min(64 * u + lane, a.B - 1)];
-      if (64 * u + lane < a.B && seq >= 0 && seq < c.max_seqs) {
+    ids[u] = 0;
+    if (64 * u < a.B) ids[u] = a.seq_ids[min(64 * u + lane, a.B - 1)];
+  }
 #pragma unroll
-        for (int k = 0; k < 3; ++k) p[u][k] = v.n_pages[npages_index(c, seq, a.layer, k)];
-      }
+  for (int u = 0; u < kU; ++u) {
+    p[u][0] = p[u][1] = p[u][2] = 0;
+    if (64 * u < a.B && 64 * u + lane < a.B && ids[u] >= 0 && ids[u] < c.max_seqs) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k) p[u][k] = v.n_pages[npages_index(c, ids[u], a.layer, k)];
     }
+  }
+#pragma unroll
+  for (int u = 0; u < kU; ++u) {
     tot[u] = p[u][0] + p[u][1] + p[u][2];
     most = max(most, tot[u]);
     all += (float)tot[u];

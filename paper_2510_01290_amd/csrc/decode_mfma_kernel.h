@@ -319,10 +319,14 @@ __device__ __forceinline__ void wait_loads() {   // until at most N of the wave'
 __device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
 // The page pairs an item works on, as one wave sees them.  The item's share of the three page lists is cut into chunks of
-// kChunkPairs consecutive pairs, type after type; chunk numbers come from the workgroup's ticket counter.  The ids and
+// 2^shift consecutive pairs, type after type; chunk numbers come from the workgroup's ticket counter.  The ids and
 // masks of the pair after the one just taken are on their way by scalar loads (no traffic in the vector-memory queue).
-constexpr int kChunkPairs = 4;
-static_assert(2 * kChunkPairs == kDealPages, "a wave is worth a chunk");
+// With a whole compute unit's waves to an item at head_dim 128, integer formats, a chunk is one pair: neighbouring waves then
+// read neighbouring pages, and no wave is left
+// with a whole chunk at the end (pairs by fours: 16 x 32k tokens 136.1 us a step, now 133.8, 32 x ~2k of scrambled slots 46.5
+// and 44.9, 16 x 8k 43.1 and 42.5).  Elsewhere a draw a pair costs more than it brings (256 x 1k..64k 837 us by fours, 856 by ones;
+// head_dim 64, 128 x 4k..32k 268 and 272; the paper's formats no difference).
+constexpr int kChunkShift = 2;
 constexpr int kTicketBytes = 64;   // a counter for each of up to sixteen items, behind the rings
 typedef const int32_t __attribute__((address_space(4))) * ConstI32;   // read-only for the whole launch: scalar loads
 typedef __attribute__((address_space(3))) int32_t* LdsCounter;
@@ -341,6 +345,7 @@ struct Stream {
   // the three types in the order they are walked: type, first pair, end page, chunks up to and including it (plain
   // members: an array indexed by a choice would not stay in scalar registers)
   int kind0, kind1, kind2, first0, first1, first2, end0, end1, end2, cum0, cum1, cum2;
+  int shift;                   // a chunk has 2^shift pairs
   int left, row, end;          // pairs of the current chunk after the next pair; k * max_pages and end page of its type
   int sec, pg;                 // the next pair: which of the three types (3: there is none), its first page,
   int more_pages;              // 1 where it has a second one, else 0,
@@ -348,12 +353,12 @@ struct Stream {
 
   static __device__ __forceinline__ int pick(int x, int a, int b, int c) { return x == 0 ? a : (x == 1 ? b : c); }
   // the share [j / n, (j + 1) / n) of a list of np pages: first pair, end page; its chunks
-  static __device__ __forceinline__ int share(int np, int j, int n, int& first, int& end) {
+  __device__ __forceinline__ int share(int np, int j, int n, int& first, int& end) const {
     const int pairs = (np + 1) >> 1;
-    first = uniform((int)((int64_t)pairs * j / n));   // (divisions are vector arithmetic)
-    const int hi = uniform((int)((int64_t)pairs * (j + 1) / n));
+    first = portion(pairs, j, n);
+    const int hi = portion(pairs, j + 1, n);
     end = 2 * hi < np ? 2 * hi : np;
-    return (hi - first + kChunkPairs - 1) / kChunkPairs;
+    return (hi - first + (1 << shift) - 1) >> shift;
   }
   // The next chunk's number, by one lane.  (In asm, with its wait: a branch on the lane would make the compiler restructure
   // every loop around it and keep their scalars in vector registers.)
@@ -380,19 +385,19 @@ struct Stream {
         sec = 2;
         end = end2;
         row = kind2 * max_pages;
-        pg = 2 * (first2 + (c - cum1) * kChunkPairs);
+        pg = 2 * (first2 + ((c - cum1) << shift));
       } else if (c >= cum0) {
         sec = 1;
         end = end1;
         row = kind1 * max_pages;
-        pg = 2 * (first1 + (c - cum0) * kChunkPairs);
+        pg = 2 * (first1 + ((c - cum0) << shift));
       } else {
         sec = 0;
         end = end0;
         row = kind0 * max_pages;
-        pg = 2 * (first0 + c * kChunkPairs);
+        pg = 2 * (first0 + (c << shift));
       }
-      left = min((end - pg - 1) >> 1, kChunkPairs - 1);
+      left = min((end - pg - 1) >> 1, (1 << shift) - 1);
     }
     more_pages = min(end - pg - 1, 1);
     const uint32_t a = 4u * (uint32_t)(row + pg), b = a + 4u * (uint32_t)more_pages;   // (bytes: 3 max_pages < 2^26)
@@ -878,13 +883,12 @@ struct Query {
   static constexpr int CS = FP ? ColsFp<D, GP>::CS : Cols<D, GP>::CS, NSET = FP ? ColsFp<D, GP>::NSET : Cols<D, GP>::NSET;
   QRegs<FP ? 1 : NSET> qr;
   QRegsFp<FP ? NSET : 1> qf;
-  static __device__ __forceinline__ H8 read8(const DecodeArgs& a, int64_t at) {
+  uint4 raw[NSET];
+  static __device__ __forceinline__ H8 halves(int dtype, const uint4& raw) {
     H8 t;
-    if (a.q_dtype == THINKV_F16) {
-      const uint4 raw = *(const uint4*)((const _Float16*)a.q + at);
+    if (dtype == THINKV_F16) {
       t.u[0] = raw.x; t.u[1] = raw.y; t.u[2] = raw.z; t.u[3] = raw.w;
     } else {
-      const uint4 raw = *(const uint4*)((const uint16_t*)a.q + at);
       const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
@@ -894,12 +898,19 @@ struct Query {
     }
     return t;
   }
-  // at: first element of the group's heads
-  __device__ __forceinline__ void read(const DecodeArgs& a, int64_t at, int G, int lane) {
+  // Asks for the elements; at: first element of the group's heads.  They are looked at (finish) when the page lists have been asked
+  // for as well, so that the two wait together.
+  __device__ __forceinline__ void load(const DecodeArgs& a, int64_t at, int G, int lane) {
+    const int qd = lane >> 4, n = lane & 15, gl = n / GP, head = n % GP;
+    const int glc = gl < CS ? gl : CS - 1;
+    at += (int64_t)(gl < CS && head < G ? head : 0) * D + 8 * qd;
+#pragma unroll
+    for (int s = 0; s < NSET; ++s) raw[s] = *(const uint4*)((const uint16_t*)a.q + at + 32 * (FP ? (s * CS + glc) >> 1 : s * CS + glc));
+  }
+  __device__ __forceinline__ void finish(const DecodeArgs& a, int G, int lane) {
     const int qd = lane >> 4, n = lane & 15, gl = n / GP, head = n % GP;
     const bool used = gl < CS && head < G;
     const int glc = gl < CS ? gl : CS - 1;
-    at += (int64_t)(used ? head : 0) * D + 8 * qd;
 #pragma unroll
     for (int s = 0; s < NSET; ++s) {
       if constexpr (FP) {
@@ -907,12 +918,12 @@ struct Query {
         // 32 G + 8 qd .. of its head where those lie in its slice's group (qd / 2 = parity of the group), zeros otherwise
         const int g16 = s * CS + glc;
         const bool mine = used && (g16 & 1) == (qd >> 1);
-        const H8 t = decltype(qf)::pairs(read8(a, at + 32 * (g16 >> 1)));
+        const H8 t = decltype(qf)::pairs(halves(a.q_dtype, raw[s]));
 #pragma unroll
         for (int w4 = 0; w4 < 4; ++w4) qf.q[s].u[w4] = mine ? t.u[w4] : 0u;
       } else {
         // ... and the sum of the group's 32 values: the four row quads complete it
-        qr.q[s] = read8(a, at + 32 * (s * CS + glc));
+        qr.q[s] = halves(a.q_dtype, raw[s]);
         float sum = 0.f;
 #pragma unroll
         for (int e = 0; e < 8; ++e) sum += (float)qr.q[s].h[e];
@@ -1050,6 +1061,8 @@ __global__ __launch_bounds__(256 * decode_waves_per_simd(D, FP)) __attribute__((
   extern __shared__ __attribute__((aligned(16))) uint8_t tkv_lds[];
   const thinkv_config& c = v.cfg;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, W = blockDim.x >> 6;
+  const int Hq = c.n_q_heads, G = Hq / c.n_kv_heads;
+  Query<D, GP, FP> query;
   // this wave's item, and the waves it shares it with: `wph` from wave0 on
   ItemLoc it;
   int seq, np[3], wph = W;
@@ -1059,17 +1072,18 @@ __global__ __launch_bounds__(256 * decode_waves_per_simd(D, FP)) __attribute__((
     it = d.it;
     wph = d.wph;
     seq = d.seq;
+    query.load(a, ((int64_t)it.b * Hq + it.hkv * G) * D, G, lane);
 #pragma unroll
     for (int k = 0; k < 3; ++k) np[k] = d.np[k];
   } else {
-    it = locate_item(v, a, blockIdx.x);
-    if (it.j >= it.n) return;
+    it = locate_head(v.cfg, a, blockIdx.x);
+    query.load(a, ((int64_t)it.b * Hq + it.hkv * G) * D, G, lane);
     seq = uniform(a.seq_ids[it.b]);
-    seq_pages(v, a.layer, seq, np);
+    count_items(a, seq_pages(v, a.layer, seq, np), it);
+    if (it.j >= it.n) return;
   }
   const int group = whole(wave, wph), wave0 = group * wph;
   const int b = it.b, hkv = it.hkv, share_n = it.n > 0 ? it.n : 1;
-  const int Hq = c.n_q_heads, G = Hq / c.n_kv_heads;
   const bool valid = seq >= 0 && seq < c.max_seqs;
   Stream q;
   const uint32_t base = lds_address(tkv_lds);
@@ -1085,9 +1099,10 @@ __global__ __launch_bounds__(256 * decode_waves_per_simd(D, FP)) __attribute__((
   q.kind0 = rot;
   q.kind1 = rot + 1 < 3 ? rot + 1 : rot - 2;
   q.kind2 = rot + 2 < 3 ? rot + 2 : rot - 1;
-  q.cum0 = Stream::share(Stream::pick(q.kind0, np[0], np[1], np[2]), it.j, share_n, q.first0, q.end0);
-  q.cum1 = q.cum0 + Stream::share(Stream::pick(q.kind1, np[0], np[1], np[2]), it.j, share_n, q.first1, q.end1);
-  q.cum2 = q.cum1 + Stream::share(Stream::pick(q.kind2, np[0], np[1], np[2]), it.j, share_n, q.first2, q.end2);
+  q.shift = D == 128 && !FP && W == kFull ? 0 : kChunkShift;
+  q.cum0 = q.share(Stream::pick(q.kind0, np[0], np[1], np[2]), it.j, share_n, q.first0, q.end0);
+  q.cum1 = q.cum0 + q.share(Stream::pick(q.kind1, np[0], np[1], np[2]), it.j, share_n, q.first1, q.end1);
+  q.cum2 = q.cum1 + q.share(Stream::pick(q.kind2, np[0], np[1], np[2]), it.j, share_n, q.first2, q.end2);
   if (wave == wave0 && lane == 0) {
     *q.ticket = 0;
     if (it.n > 0 && it.j == 0 && !a.direct) {
@@ -1096,13 +1111,12 @@ __global__ __launch_bounds__(256 * decode_waves_per_simd(D, FP)) __attribute__((
     }
   }
   q.left = q.row = q.end = q.sec = q.pg = q.more_pages = q.pid_a = q.pid_b = q.msk_a = q.msk_b = 0;
-  Query<D, GP, FP> query;
-  query.read(a, ((int64_t)b * Hq + hkv * G) * D, G, lane);
   WaveState<D, GP, Query<D, GP, FP>::NSET> st;
   clear(st);
   __syncthreads();
   const uint32_t ring = base + wave * kRing, xch = base + W * kRing + kTicketBytes + exchange_bytes(D, GP, FP) * wave;
   q.look();
+  query.finish(a, G, lane);
   while (q.sec < 3) {
     const int x = q.sec, k = Stream::pick(x, q.kind0, q.kind1, q.kind2);
     const int bits = c.bits_of_class[k];
@@ -1149,15 +1163,18 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const thinkv_config& c = v.cfg;
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int H = c.n_kv_heads, Hq = c.n_q_heads, G = Hq / H, hg = a.waves, wph = kWindowWaves / hg;
-  const int groups = (H + hg - 1) / hg;
+  const int groups = quotient(H + hg - 1, hg);
   // item id -> query, group of heads, item j of n (item-major)
-  const int per = groups * a.B, j = uniform((int)blockIdx.x / per), rest = (int)blockIdx.x - j * per;
-  const int b = uniform(rest / groups), h0 = (rest - b * groups) * hg;
+  const int per = groups * a.B, j = a.per_head > 1 ? uniform((int)blockIdx.x / per) : 0, rest = (int)blockIdx.x - j * per;
+  const int b = per < (1 << 24) ? quotient(rest, groups) : uniform(rest / groups), h0 = (rest - b * groups) * hg;
   const int seq = uniform(a.seq_ids[b]);
   int np[3];
   const int tot = seq_pages(v, a.layer, seq, np);
-  int n = uniform((int)(((int64_t)tot + a.ppi - 1) / a.ppi));
-  n = n < 1 ? 1 : (n > a.per_head ? a.per_head : n);
+  int n = 1;
+  if (a.per_head > 1) {
+    n = uniform((int)(((uint32_t)tot + (uint32_t)a.ppi - 1u) / (uint32_t)a.ppi));
+    n = n < 1 ? 1 : (n > a.per_head ? a.per_head : n);
+  }
   if (j >= n) return;
   const int hw = uniform(wave / wph), hkv = min(h0 + hw, H - 1);   // this wave's head (waves beyond the last head idle)
   if (j == 0 && !a.direct && tid < hg && h0 + tid < H) {
@@ -1168,15 +1185,16 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   int32_t* const lists = (int32_t*)(tkv_lds + kWindowWaves * kRing);   // [type][id, mask, list position][kWindowBlock]
   int32_t* const counts = lists + 9 * kWindowBlock;                    // [type][wave]
   Query<D, GP, FP> query;
-  query.read(a, ((int64_t)b * Hq + hkv * G) * D, G, lane);
+  query.load(a, ((int64_t)b * Hq + hkv * G) * D, G, lane);
+  query.finish(a, G, lane);
   WaveState<D, GP, Query<D, GP, FP>::NSET> st;
   clear(st);
   const int qpos = uniform(a.q_pos[b]);
   const bool valid = seq >= 0 && seq < c.max_seqs;
   // the item's share of each list
-  const int s0 = uniform((int)((int64_t)j * np[0] / n)), e0 = uniform((int)((int64_t)(j + 1) * np[0] / n));
-  const int s1 = uniform((int)((int64_t)j * np[1] / n)), e1 = uniform((int)((int64_t)(j + 1) * np[1] / n));
-  const int s2 = uniform((int)((int64_t)j * np[2] / n)), e2 = uniform((int)((int64_t)(j + 1) * np[2] / n));
+  const int s0 = portion(np[0], j, n), e0 = portion(np[0], j + 1, n);
+  const int s1 = portion(np[1], j, n), e1 = portion(np[1], j + 1, n);
+  const int s2 = portion(np[2], j, n), e2 = portion(np[2], j + 1, n);
   const int most = max(e0 - s0, max(e1 - s1, e2 - s2));
   for (int base = 0; base < most; base += kWindowBlock) {
     int pg[3], pid[3];
