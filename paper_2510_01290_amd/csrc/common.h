@@ -74,13 +74,15 @@ __device__ inline int sl_index(const thinkv_config& c, int seq, int layer) { ret
 // Soft eviction of one handle of sequence s (a valid sequence id).  The live bit is cleared with
 // one atomic; only the thread that saw it set goes on to mark the slot reclaimable, so duplicates
 // and dead slots count once.
-__device__ inline void evict_one(const thinkv_view& v, int layer, int s, int32_t h) {
+// np: the page counts of the sequence, where the caller has them.
+__device__ inline void evict_one(const thinkv_view& v, int layer, int s, int32_t h, const int* np = nullptr) {
   const thinkv_config& c = v.cfg;
   if (h == -1) return;   // placeholder: no token
   const uint32_t uh = (uint32_t)h;
   const int cls = uh >> 28, pi = (uh >> 4) & 0xFFFFFF, slot = uh & 15;
   uint32_t* status = &v.dev_status[sl_index(c, s, layer)];
-  if (h < 0 || cls > 2 || pi >= v.n_pages[npages_index(c, s, layer, cls)]) {
+  auto pages = [&]() { return np ? (cls == 0 ? np[0] : (cls == 1 ? np[1] : np[2])) : v.n_pages[npages_index(c, s, layer, cls)]; };
+  if (h < 0 || cls > 2 || pi >= pages()) {
     atomicOr(status, THINKV_ST_BAD_SLOT);
     return;
   }
