@@ -94,12 +94,13 @@ def _check(rc, what):
 
 
 def _ptr(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream(stream):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return C.c_void_p(s.cuda_stream)
+    # the current device's current stream, as torch.cuda.current_stream() finds it, without the Stream object that takes 2.9 us
+    # to make: a decode step of one short sequence is two calls and was bound by the host (26 us a step, now 20)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()) if stream is None else stream.cuda_stream
 
 
 FMT_INT, FMT_FP = 0, 1
