@@ -254,9 +254,7 @@ static int decode_common(const thinkv_view* view, int32_t layer, const void* q, 
     if (rc) return rc;
     rc = launch_decode_mfma_stat(*view, a, st);
     if (rc) return rc;
-    rc = launch_decode_merge(*view, a, st);
-    if (rc) return rc;
-    return launch_stat_count(*view, a, st);
+    return launch_stat_count(*view, a, st);   // and the merge
   }
   rc = fast ? launch_decode_mfma(*view, a, st) : launch_decode_simple(*view, a, st);
   if (rc || a.direct) return rc;

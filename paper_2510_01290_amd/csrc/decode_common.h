@@ -270,4 +270,68 @@ __device__ inline float* partial_row(const DecodeArgs& a, int G, int D, int row,
   return a.partial + ((int64_t)row * G + g) * (D + kRowPad);
 }
 
+// Log-sum-exp merge of the partial rows of query head hq of query b, by D threads (first row and count as item 0 of the head left
+// them); all threads of the workgroup come here together, those of no head (!on) with any head's number.
+// Maxima and weights are found with one
+// row per thread; the weighted sum over rows is unrolled so that several rows are in flight per thread.
+template <int D>
+struct MergeLds {
+  float w[kMaxRowsPerHead];
+  float red[D / 64];
+};
+template <int D>
+__device__ __forceinline__ void merge_head(const thinkv_view& v, const DecodeArgs& a, int b, int hq, int ch, bool on, MergeLds<D>& lds) {
+  const thinkv_config& c = v.cfg;
+  const int Hq = c.n_q_heads, G = Hq / c.n_kv_heads, hkv = hq / G;
+  const int row0 = a.alloc[2 * (b * c.n_kv_heads + hkv)];
+  int ns = a.alloc[2 * (b * c.n_kv_heads + hkv) + 1];
+  ns = ns > kMaxRowsPerHead ? kMaxRowsPerHead : ns;
+  constexpr int RS = D + kRowPad;
+  const float* src = partial_row(a, G, D, row0, hq % G);
+  const int64_t stride = (int64_t)G * RS;   // from one row of this query head to the next
+  // maximum over rows
+  float m_loc = -INFINITY;
+  for (int s = ch; s < ns; s += D) {
+    const float m = src[s * stride + D];
+    lds.w[s] = m;
+    m_loc = fmaxf(m_loc, m);
+  }
+  for (int d = 32; d >= 1; d >>= 1) m_loc = fmaxf(m_loc, __shfl_xor(m_loc, d, 64));
+  if ((ch & 63) == 0) lds.red[ch >> 6] = m_loc;
+  __syncthreads();
+  float M = lds.red[0];
+  for (int w = 1; w < D / 64; ++w) M = fmaxf(M, lds.red[w]);
+  __syncthreads();
+  // weights and denominator
+  float l_loc = 0.f;
+  for (int s = ch; s < ns; s += D) {
+    const float m = lds.w[s];
+    const float f = (m == -INFINITY) ? 0.f : exp2f(m - M);
+    lds.w[s] = f;
+    l_loc = fmaf(src[s * stride + D + 1], f, l_loc);
+  }
+  for (int d = 32; d >= 1; d >>= 1) l_loc += __shfl_xor(l_loc, d, 64);
+  if ((ch & 63) == 0) lds.red[ch >> 6] = l_loc;
+  __syncthreads();
+  float L = lds.red[0];
+  for (int w = 1; w < D / 64; ++w) L += lds.red[w];
+  // weighted sum of the partial rows
+  float A = 0.f;
+  const float* col = src + ch;
+  int s = 0;
+  for (; s + 4 <= ns; s += 4) {
+    const float x0 = col[(s + 0) * stride], x1 = col[(s + 1) * stride];
+    const float x2 = col[(s + 2) * stride], x3 = col[(s + 3) * stride];
+    A = fmaf(x0, lds.w[s], A);
+    A = fmaf(x1, lds.w[s + 1], A);
+    A = fmaf(x2, lds.w[s + 2], A);
+    A = fmaf(x3, lds.w[s + 3], A);
+  }
+  for (; s < ns; ++s) A = fmaf(col[s * stride], lds.w[s], A);
+  if (!on) return;
+  const float o = L > 0.f ? A / L : 0.f;
+  store_from_f32(a.out, ((int64_t)b * Hq + hq) * D + ch, a.out_dtype, o);
+  if (a.lse && ch == 0) a.lse[(int64_t)b * Hq + hq] = L > 0.f ? (M + log2f(L)) * 0.6931471805599453f : -INFINITY;
+}
+
 }  // namespace thinkv

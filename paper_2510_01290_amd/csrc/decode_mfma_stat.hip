@@ -22,17 +22,26 @@ __global__ __launch_bounds__(256) void stat_fill_kernel(float4* p, int64_t n4) {
     p[i] = make_float4(ninf, ninf, ninf, ninf);
 }
 
-// One workgroup per (query, kv-head): the row maximum, then the counts of visible and of
+// The merge of the partial rows and the counts need the attention kernel's results and nothing of each other: one launch.
+// `merges` workgroups of 1,024 threads come first and merge 1,024 / D query heads each; then
+// one workgroup per (query, kv-head): the row maximum, then the counts of visible and of
 // negligible entries; the row's fraction negligible / visible (0 where nothing is visible) goes
 // to frac[b][kv-head].  Rows are read 16 bytes a lane, once up to 32,768 entries.  MASKS: entries of pages without a live
 // slot were not written and count as -inf.
 constexpr int kKept = 8;
-template <bool MASKS>
-__global__ __launch_bounds__(1024) void stat_count_kernel(thinkv_view v, DecodeArgs a, float* frac) {
+template <int D, bool MASKS>
+__global__ __launch_bounds__(1024) void stat_count_kernel(thinkv_view v, DecodeArgs a, float* frac, int merges) {
   const thinkv_config& c = v.cfg;
-  const int hkv = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  __shared__ MergeLds<D> s_merge[1024 / D];
   __shared__ float s_max[16];
   __shared__ int s_cnt[2][16];
+  if ((int)blockIdx.x < merges) {
+    const int per = 1024 / D, head = blockIdx.x * per + tid / D, heads = a.B * c.n_q_heads, hd = head < heads ? head : heads - 1;
+    merge_head<D>(v, a, hd / c.n_q_heads, hd % c.n_q_heads, tid % D, head < heads, s_merge[tid / D]);
+    return;
+  }
+  const int b = ((int)blockIdx.x - merges) / c.n_kv_heads, hkv = (int)blockIdx.x - merges - b * c.n_kv_heads;
   const int seq = a.seq_ids[b];
   int64_t n = 0;
   int end0 = 0, end1 = 0;   // where the pages of the first two types end
@@ -123,8 +132,15 @@ int launch_decode_mfma_stat(const thinkv_view& v, const DecodeArgs& a, hipStream
 int launch_stat_count(const thinkv_view& v, const DecodeArgs& a, hipStream_t st) {
   // the per-row fractions live behind the pooled scores
   float* frac = a.stat + (int64_t)a.B * v.cfg.n_kv_heads * a.stat_stride;
-  if (a.window > 0) hipLaunchKernelGGL(stat_count_kernel<false>, dim3(v.cfg.n_kv_heads, a.B), dim3(1024), 0, st, v, a, frac);
-  else hipLaunchKernelGGL(stat_count_kernel<true>, dim3(v.cfg.n_kv_heads, a.B), dim3(1024), 0, st, v, a, frac);
+  const int D = v.cfg.head_dim, merges = (a.B * v.cfg.n_q_heads + 1024 / D - 1) / (1024 / D);
+  const dim3 grid(merges + v.cfg.n_kv_heads * a.B);
+  if (D == 128) {
+    if (a.window > 0) hipLaunchKernelGGL((stat_count_kernel<128, false>), grid, dim3(1024), 0, st, v, a, frac, merges);
+    else hipLaunchKernelGGL((stat_count_kernel<128, true>), grid, dim3(1024), 0, st, v, a, frac, merges);
+  } else {
+    if (a.window > 0) hipLaunchKernelGGL((stat_count_kernel<64, false>), grid, dim3(1024), 0, st, v, a, frac, merges);
+    else hipLaunchKernelGGL((stat_count_kernel<64, true>), grid, dim3(1024), 0, st, v, a, frac, merges);
+  }
   hipLaunchKernelGGL(stat_mean_kernel, dim3((a.B + 255) / 256), dim3(256), 0, st, frac, a.sparsity, a.B, v.cfg.n_kv_heads);
   return hipGetLastError() == hipSuccess ? THINKV_OK : THINKV_E_HIP;
 }

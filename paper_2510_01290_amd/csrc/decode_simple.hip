@@ -169,64 +169,10 @@ __global__ __launch_bounds__(256) void decode_simple_kernel(thinkv_view v, Decod
   }
 }
 
-// One workgroup of D threads per (query, query head): log-sum-exp merge of the head's partial rows
-// (first row and count as item 0 of the head left them).  Maxima and weights are found with one
-// row per thread; the weighted sum over rows is unrolled so that several rows are in flight per thread.
 template <int D>
 __global__ __launch_bounds__(D) void decode_merge_kernel(thinkv_view v, DecodeArgs a) {
-  const thinkv_config& c = v.cfg;
-  const int hq = blockIdx.x, b = blockIdx.y, ch = threadIdx.x;
-  const int Hq = c.n_q_heads, G = Hq / c.n_kv_heads, hkv = hq / G;
-  __shared__ float s_w[kMaxRowsPerHead];
-  __shared__ float s_red[D / 64];
-  const int row0 = a.alloc[2 * (b * c.n_kv_heads + hkv)];
-  int ns = a.alloc[2 * (b * c.n_kv_heads + hkv) + 1];
-  ns = ns > kMaxRowsPerHead ? kMaxRowsPerHead : ns;
-  constexpr int RS = D + kRowPad;
-  const float* src = partial_row(a, G, D, row0, hq % G);
-  const int64_t stride = (int64_t)G * RS;   // from one row of this query head to the next
-  // maximum over rows
-  float m_loc = -INFINITY;
-  for (int s = ch; s < ns; s += D) {
-    const float m = src[s * stride + D];
-    s_w[s] = m;
-    m_loc = fmaxf(m_loc, m);
-  }
-  for (int d = 32; d >= 1; d >>= 1) m_loc = fmaxf(m_loc, __shfl_xor(m_loc, d, 64));
-  if ((ch & 63) == 0) s_red[ch >> 6] = m_loc;
-  __syncthreads();
-  float M = s_red[0];
-  for (int w = 1; w < D / 64; ++w) M = fmaxf(M, s_red[w]);
-  __syncthreads();
-  // weights and denominator
-  float l_loc = 0.f;
-  for (int s = ch; s < ns; s += D) {
-    const float m = s_w[s];
-    const float f = (m == -INFINITY) ? 0.f : exp2f(m - M);
-    s_w[s] = f;
-    l_loc = fmaf(src[s * stride + D + 1], f, l_loc);
-  }
-  for (int d = 32; d >= 1; d >>= 1) l_loc += __shfl_xor(l_loc, d, 64);
-  if ((ch & 63) == 0) s_red[ch >> 6] = l_loc;
-  __syncthreads();
-  float L = s_red[0];
-  for (int w = 1; w < D / 64; ++w) L += s_red[w];
-  // weighted sum of the partial rows
-  float A = 0.f;
-  const float* col = src + ch;
-  int s = 0;
-  for (; s + 4 <= ns; s += 4) {
-    const float x0 = col[(s + 0) * stride], x1 = col[(s + 1) * stride];
-    const float x2 = col[(s + 2) * stride], x3 = col[(s + 3) * stride];
-    A = fmaf(x0, s_w[s], A);
-    A = fmaf(x1, s_w[s + 1], A);
-    A = fmaf(x2, s_w[s + 2], A);
-    A = fmaf(x3, s_w[s + 3], A);
-  }
-  for (; s < ns; ++s) A = fmaf(col[s * stride], s_w[s], A);
-  const float o = L > 0.f ? A / L : 0.f;
-  store_from_f32(a.out, ((int64_t)b * Hq + hq) * D + ch, a.out_dtype, o);
-  if (a.lse && ch == 0) a.lse[(int64_t)b * Hq + hq] = L > 0.f ? (M + log2f(L)) * 0.6931471805599453f : -INFINITY;
+  __shared__ MergeLds<D> lds;
+  merge_head<D>(v, a, blockIdx.y, blockIdx.x, threadIdx.x, true, lds);
 }
 
 int launch_decode_simple(const thinkv_view& v, const DecodeArgs& a, hipStream_t st) {
