@@ -338,6 +338,8 @@ __device__ __forceinline__ int arrived(int x) {
   return x;
 }
 
+// FINE: the chunk's size is chosen per launch, else it is 2^kChunkShift pairs (a constant: one scalar less in a loop that has few to spare)
+template <bool FINE>
 struct Stream {
   ConstI32 tab, msk;           // page list and masks of type 0; those of type k begin k * max_pages later
   LdsCounter ticket;
@@ -345,7 +347,8 @@ struct Stream {
   // the three types in the order they are walked: type, first pair, end page, chunks up to and including it (plain
   // members: an array indexed by a choice would not stay in scalar registers)
   int kind0, kind1, kind2, first0, first1, first2, end0, end1, end2, cum0, cum1, cum2;
-  int shift;                   // a chunk has 2^shift pairs
+  int fine;
+  __device__ __forceinline__ int shift() const { return FINE ? fine : kChunkShift; }   // a chunk has 2^shift pairs
   int left, row, end;          // pairs of the current chunk after the next pair; k * max_pages and end page of its type
   int sec, pg;                 // the next pair: which of the three types (3: there is none), its first page,
   int more_pages;              // 1 where it has a second one, else 0,
@@ -358,7 +361,7 @@ struct Stream {
     first = portion(pairs, j, n);
     const int hi = portion(pairs, j + 1, n);
     end = 2 * hi < np ? 2 * hi : np;
-    return (hi - first + (1 << shift) - 1) >> shift;
+    return (hi - first + (1 << shift()) - 1) >> shift();
   }
   // The next chunk's number, by one lane.  (In asm, with its wait: a branch on the lane would make the compiler restructure
   // every loop around it and keep their scalars in vector registers.)
@@ -385,19 +388,19 @@ struct Stream {
         sec = 2;
         end = end2;
         row = kind2 * max_pages;
-        pg = 2 * (first2 + ((c - cum1) << shift));
+        pg = 2 * (first2 + ((c - cum1) << shift()));
       } else if (c >= cum0) {
         sec = 1;
         end = end1;
         row = kind1 * max_pages;
-        pg = 2 * (first1 + ((c - cum0) << shift));
+        pg = 2 * (first1 + ((c - cum0) << shift()));
       } else {
         sec = 0;
         end = end0;
         row = kind0 * max_pages;
-        pg = 2 * (first0 + (c << shift));
+        pg = 2 * (first0 + (c << shift()));
       }
-      left = min((end - pg - 1) >> 1, (1 << shift) - 1);
+      left = min((end - pg - 1) >> 1, (1 << shift()) - 1);
     }
     more_pages = min(end - pg - 1, 1);
     const uint32_t a = 4u * (uint32_t)(row + pg), b = a + 4u * (uint32_t)more_pages;   // (bytes: 3 max_pages < 2^26)
@@ -1085,7 +1088,9 @@ __global__ __launch_bounds__(256 * decode_waves_per_simd(D, FP)) __attribute__((
   const int group = whole(wave, wph), wave0 = group * wph;
   const int b = it.b, hkv = it.hkv, share_n = it.n > 0 ? it.n : 1;
   const bool valid = seq >= 0 && seq < c.max_seqs;
-  Stream q;
+  constexpr bool kFine = D == 128 && !FP;
+  using Pairs = Stream<kFine>;
+  Pairs q;
   const uint32_t base = lds_address(tkv_lds);
   q.ticket = (LdsCounter)(uintptr_t)(base + W * kRing + 4 * group);
   q.lane = lane;
@@ -1099,10 +1104,10 @@ __global__ __launch_bounds__(256 * decode_waves_per_simd(D, FP)) __attribute__((
   q.kind0 = rot;
   q.kind1 = rot + 1 < 3 ? rot + 1 : rot - 2;
   q.kind2 = rot + 2 < 3 ? rot + 2 : rot - 1;
-  q.shift = D == 128 && !FP && W == kFull ? 0 : kChunkShift;
-  q.cum0 = q.share(Stream::pick(q.kind0, np[0], np[1], np[2]), it.j, share_n, q.first0, q.end0);
-  q.cum1 = q.cum0 + q.share(Stream::pick(q.kind1, np[0], np[1], np[2]), it.j, share_n, q.first1, q.end1);
-  q.cum2 = q.cum1 + q.share(Stream::pick(q.kind2, np[0], np[1], np[2]), it.j, share_n, q.first2, q.end2);
+  q.fine = kFine && W == kFull ? 0 : kChunkShift;
+  q.cum0 = q.share(Pairs::pick(q.kind0, np[0], np[1], np[2]), it.j, share_n, q.first0, q.end0);
+  q.cum1 = q.cum0 + q.share(Pairs::pick(q.kind1, np[0], np[1], np[2]), it.j, share_n, q.first1, q.end1);
+  q.cum2 = q.cum1 + q.share(Pairs::pick(q.kind2, np[0], np[1], np[2]), it.j, share_n, q.first2, q.end2);
   if (wave == wave0 && lane == 0) {
     *q.ticket = 0;
     if (it.n > 0 && it.j == 0 && !a.direct) {
@@ -1118,7 +1123,7 @@ __global__ __launch_bounds__(256 * decode_waves_per_simd(D, FP)) __attribute__((
   q.look();
   query.finish(a, G, lane);
   while (q.sec < 3) {
-    const int x = q.sec, k = Stream::pick(x, q.kind0, q.kind1, q.kind2);
+    const int x = q.sec, k = Pairs::pick(x, q.kind0, q.kind1, q.kind2);
     const int bits = c.bits_of_class[k];
     float* stat = nullptr;
     int stat_room = 0;
