@@ -627,7 +627,8 @@ __global__ __launch_bounds__(kKmThreads) __attribute__((amdgpu_waves_per_eu(6)))
     __syncthreads();
     if (wave == 0) {
       int m = 0;
-      bool differs = false;
+      // a cluster that gets back the members it lost has the centroid it had, but their products (own) are with others by now
+      bool differs = sm.span[lane] >> 16 == 0;
       uint32_t row[kWords];
 #pragma unroll
       for (int w = 0; w < kWords; ++w) {

@@ -77,3 +77,32 @@ def test_a_key_that_is_no_number_spoils_its_own_cluster_only():
         assert (got[assign == j] == -1).sum() == 1
     fine = [j for j in range(1, 12) if (assign == j).any()]
     assert len(fine) >= 6 and np.isfinite(cent[0, fine]).all()
+
+
+def test_a_cluster_that_gets_its_members_back():
+    """Cluster 1 loses all its members in the second assignment and gets exactly them back in the third: its centroid has not moved,
+    but the distances of its members to it are asked for again.  (Found by a search on the CPU: with the distances to the
+    clusters that they were in meanwhile, token 9 would stay instead of token 1.)  Whole numbers, exact in the 8-bit format."""
+    print("a cluster that gets its members back", flush=True)
+    at = np.array([(70, 44), (66, 22), (0, 22), (60, 61), (63, 20), (60, 63), (181, 7), (2, 27), (62, 40), (123, 3),
+                   (125, 40), (186, 61), (70, 60), (180, 1), (62, 60), (180, 1), (1, 19), (125, 57), (127, 61), (6, 2)])
+    n, k, iters = len(at), 5, 3
+    geom = synth.Geometry(1, 1, 1, 64, "f16", (8, 2, 4))
+    classes = [np.full(n, synth.T, np.uint8)]
+    wl = synth.Workload("tbe-back", geom, 63, 1, classes, [], (0,), np.array([n - 1], np.int32))
+    pages = n // 16 + 4
+    gc = parity.make_gpu_cache(wl, arena_pages=(pages,) * 3, max_pages=pages)
+    ob = parity.make_oracle(wl, arena_pages=(pages,) * 3, max_pages=pages)
+    gb = parity.GpuBackend(gc)
+    rows = torch.zeros((n, 1, 64), dtype=torch.float16)
+    for g in range(2):                            # a group's extremes are the same in every token: its scale is 1
+        rows[:, 0, 32 * g + 1] = 255
+        rows[:, 0, 32 * g + 5] = torch.from_numpy(at[:, g].copy()).to(torch.float16)
+    th = np.asarray(gb.append(0, rows.to(gc.device), rows.to(gc.device), np.zeros(n, np.int64), np.arange(n), classes[0])).astype(np.int32)
+    ob.append(0, rows, rows, np.zeros(n, np.int64), np.arange(n), classes[0])
+    assert np.array_equal(otbe.segment_keys(ob.cache, 0, 0, th)[:, [5, 37]], at)
+    ts, off, keep = np.zeros(n, np.int32), np.array([0, n], np.int32), np.array([k], np.int32)
+    want, margins = otbe.select_evictions(ob.cache, 0, ts, th, off, keep, iters)
+    assert margins[0] > MIN_MARGIN and want[1] == -1 and want[9] != -1
+    got = _gpu_select(gc, 0, ts, th, off, keep, max_iters=iters)
+    assert np.array_equal(got, want)
