@@ -24,7 +24,7 @@
 // cores without a stop in memory; the binary32 rows are written on the way.
 // kmeans: a workgroup per segment adds the parts of the matrix and iterates.
 // 314 segments of ~110 tokens, 1,024 channels, us: keys to memory and a workgroup of a whole compute unit per segment (its
-// 139 KB of LDS made that 1.2 rounds of workgroups) 37 + 177; now 66 + 74.  gram is bound by vector instructions (four a
+// 139 KB of LDS made that 1.2 rounds of workgroups) 37 + 177; now 60 + 74.  gram is bound by vector instructions (four a
 // number to unpack and split it) and by 141 MB of rows; kmeans by chains from the lists of members to LDS and
 // back (20 us around the first assignment, 1.5 to 4 for every further one), the parts (10) and the 54 MB of centroids (20).
 // The products run on the matrix cores; a dequantised key does not
@@ -691,7 +691,8 @@ __global__ __launch_bounds__(kKmThreads) __attribute__((amdgpu_waves_per_eu(6)))
   }
   __syncthreads();   // the matrix in memory has been read: the centroids take its place
   // ---- the centroids, for callers that look at them: a wave per cluster, up to 1,024 channels at a time, two members' rows
-  // (eight loads a lane) in flight, members in index order
+  // (eight loads a lane) in flight, members in index order.  Nothing here reads them again: past the caches, where they made
+  // the next call's gram kernel wait (66 us, now 60)
   const float* x = a.x + (int64_t)lo * dim;
   float* cent = a.cent + (int64_t)seg * kTbeMaxKeep * dim;
   for (int j = wave; j < k; j += kKmWaves) {
@@ -722,7 +723,7 @@ __global__ __launch_bounds__(kKmThreads) __attribute__((amdgpu_waves_per_eu(6)))
       });
 #pragma unroll
       for (int u = 0; u < 4; ++u)
-        if (d0 + 256 * u < dim) *(f32x4*)&cent[(int64_t)j * dim + d0 + 256 * u] = sum[u] * by;
+        if (d0 + 256 * u < dim) __builtin_nontemporal_store(sum[u] * by, (f32x4*)&cent[(int64_t)j * dim + d0 + 256 * u]);
     }
   }
 }
