@@ -152,8 +152,11 @@ typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 // 16, b and 16 + b.  m: the scales of group GRP.  A masked code is a binary16 subnormal, code * 2^-24, which the mixed-precision
 // multiply-add reads as it is; the scale takes the power of two.  In the paper's formats the magnitude bits go under the
 // exponent of a binary16 number and the sign bit to bit 15.
+// A token that does not exist (width 0) has codes, scales and zero-points of 0; it is unpacked as one of the narrowest
+// type, since a shift by a width less one has to be defined.
 template <int D, bool FP, int GRP>
-__device__ __forceinline__ void unpack_keys(const thinkv_config& c, const RawKeys<D>& r, uint32_t m, int bits, int j, float (&x)[8]) {
+__device__ __forceinline__ void unpack_keys(const thinkv_config& c, const RawKeys<D>& r, uint32_t m, int width, int j, float (&x)[8]) {
+  const int bits = width ? width : 2;
   const uint32_t two = r.code[GRP / 2] >> (8 * (GRP & 1));
   const uint32_t word[2] = {bits == 8 ? r.code[2 * GRP] : bits == 4 ? r.code[GRP] : two,
                             bits == 8 ? r.code[2 * GRP + 1] : bits == 4 ? r.code[GRP] >> 8 : two >> 4};
@@ -846,7 +849,7 @@ __device__ __forceinline__ void for_live_tokens(const thinkv_view& v, int seq, i
   for (int u0 = threadIdx.x; u0 < pieces; u0 += kAhead * kPlanThreads) {
     uint32_t m[kAhead];
     int pid[kAhead], cls[kAhead], pi[kAhead];
-    int4 pos[kAhead];
+    int4 pos[kAhead] = {};
 #pragma unroll
     for (int a = 0; a < kAhead; ++a) {
       const int u = u0 + a * kPlanThreads;

@@ -79,6 +79,24 @@ def test_a_key_that_is_no_number_spoils_its_own_cluster_only():
     assert len(fine) >= 6 and np.isfinite(cent[0, fine]).all()
 
 
+@pytest.mark.parametrize("fmt,D", [("int", 64), ("int", 128), ("fp", 64), ("fp", 128)])
+def test_a_token_that_does_not_exist_is_the_origin(fmt, D):
+    """handles that name no page, inside a clustered segment whose size is no multiple of a tile and behind it: rows of zeros, flagged"""
+    print("tokens that do not exist", fmt, D, flush=True)
+    from paper_2510_01290_amd import binding as B
+    geom = synth.Geometry(1, 3, 3, D, "f16", (2, 4, 8), fmt)
+    wl = synth.bulk_evict_refill("tbe-none", geom, 64, 1, np.array([120]), {}, refill=0)
+    gc = parity.make_gpu_cache(wl)
+    gr = synth.ScriptRunner(wl, parity.GpuBackend(gc)).run()
+    th = np.array([int(h) for h in gr.handle[(0, 0)][:75]], np.int32)
+    none = [0, 17, 40, 73]
+    th[none] = 1 << 28 | 4000 << 4
+    got, x, cent, assign = _gpu_select(gc, 0, np.zeros(75, np.int32), th, np.array([0, 70], np.int32), np.array([9], np.int32), inspect=True)
+    assert (x[none] == 0).all() and (np.delete(np.abs(x).sum(1), none) > 0).all()
+    assert len(set(assign[[0, 17, 40]])) == 1 and 1 <= (got[:70] == -1).sum() <= 9
+    assert gc.dev_status.cpu().numpy()[0] & B.ST_BAD_SLOT
+
+
 def test_a_cluster_that_gets_its_members_back():
     """Cluster 1 loses all its members in the second assignment and gets exactly them back in the third: its centroid has not moved,
     but the distances of its members to it are asked for again.  (Found by a search on the CPU: with the distances to the
