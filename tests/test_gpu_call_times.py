@@ -1,0 +1,63 @@
+"""Calls of one kind at two sizes, timed in turn in one process: a path that only one of the two takes must not be slower out of proportion to
+the work.  The bounds lie about halfway (in factors) between what is measured and what the fault that each one names took."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2510_01290_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _put(x, t=torch.int32):
+    return torch.from_numpy(np.ascontiguousarray(x)).to(DEV, t)
+
+
+def _ratio(slow, fast, n=8):
+    """median over five turns of the time of slow() over that of fast()"""
+    times = []
+    for f in (slow, fast):
+        f()
+    for _ in range(5):
+        t = []
+        for f in (slow, fast):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            torch.cuda.synchronize()
+            f()
+            a.record()
+            for _ in range(n):
+                f()
+            b.record()
+            torch.cuda.synchronize()
+            t.append(a.elapsed_time(b) / n)
+        times.append(t[0] / t[1])
+    print("ratio", sorted(times)[2], "of", t[0] * 1000, "to", t[1] * 1000, "us", flush=True)
+    return sorted(times)[2]
+
+
+def _filled(S, n, hkv, D, bits=(4, 4, 4), types=1):
+    """S sequences of n tokens, and the tokens' handles [S, n]"""
+    c = B.Cache(1, hkv, hkv, D, bits, S, n // 16 + 8, (S * (n // 16 + 8),) * 3)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(S + n)
+    rows = torch.randn((S * n, hkv, D), generator=g, device=DEV).half()
+    h = torch.empty(S * n, dtype=torch.int32, device=DEV)
+    cls = np.tile(np.arange(n) // 64 % types, S)
+    B.thinkv_append_quantized(c, 0, rows, rows, _put(np.repeat(np.arange(S), n)), _put(np.tile(np.arange(n), S)), _put(cls, torch.uint8), h)
+    return c, h.cpu().numpy().reshape(S, n)
+
+
+def test_a_plan_into_lists_that_are_too_short():
+    """2,048 sequences, room for a quarter of their cuts: 46 times the call with room for all where every workgroup looked at the
+    sequences before it one after the other, 1.7 times where it looks at 64 at a time"""
+    S, n = 2048, 256
+    c, _ = _filled(S, n, 1, 64)
+    start = np.zeros((S, 4), np.int32)
+    start[:] = np.arange(4) * 64
+    args = (_put(np.arange(S)), _put(start), _put(np.zeros((S, 4)), torch.uint8), _put(np.full(S, 4)), _put(np.ones(S), torch.uint8), 0, 64)
+    z = lambda k: torch.zeros(k, dtype=torch.int32, device=DEV)              # noqa: E731
+    lists = {share: (z(S * n // share), z(S * n // share), z(S * 3 // share + 1), z(S * 3 // share), z(2)) for share in (1, 4)}
+    call = lambda share: B.thinkv_tbe_plan(c, 0, *args, *lists[share], rule=B.TBE_BY_SIZE)   # noqa: E731
+    r = _ratio(lambda: call(4), lambda: call(1))
+    assert lists[4][4][0] == S * 3 // 4 and r < 9.0

@@ -6,6 +6,7 @@ import pytest
 import torch
 
 import parity
+from oracle import tbe as otbe
 from paper_2510_01290_amd import synth
 from test_gpu_tbe import _device_plan, _oracle_plan
 
@@ -66,3 +67,25 @@ def test_tbe_plan_over_many_segments(longest, trans, budget, max_cuts, cap_seg, 
         assert np.array_equal(dev, ora)
     assert int(gc.dev_status.abs().sum().item()) == 0
 
+
+@pytest.mark.parametrize("share_seg,share_tok,max_cuts", [(1.0, 0.9, 256), (0.35, 1.0, 256), (1.0, 0.3, 256), (0.7, 0.02, 256), (0.01, 1.0, 256), (0.5, 0.5, 3), (0.0, 1.0, 8)])
+def test_tbe_plan_of_many_sequences_into_short_lists(share_seg, share_tok, max_cuts):
+    """sequences by the hundred: some fit whole, some in part, some only because an earlier one was passed over; the lists end anywhere"""
+    print("plan into short lists", share_seg, share_tok, max_cuts, flush=True)
+    rng = np.random.default_rng(52)
+    lens = rng.integers(30, 260, 150).tolist()
+    gc, ob, rng = _built(lens, 53)
+    st, ty, ns = _segment_table(rng, lens, 20, 60)
+    order = rng.permutation(150).tolist()
+    trans = (rng.random(150) < 0.8).astype(np.uint8).tolist()
+    full = _oracle_plan(ob.cache, 0, order, st, ty, ns, trans, 60, max_cuts, 1 << 14, 1 << 16, rule=otbe.BY_SIZE)
+    cap_seg, cap_tok = max(1, int(share_seg * len(full[3]))), max(1, int(share_tok * len(full[1])))
+    dev, ora = np.zeros(st.shape, np.int32), np.zeros(st.shape, np.int32)
+    for again in range(2):
+        got = _device_plan(gc, 0, order, st, ty, ns, trans, 60, max_cuts, cap_seg, cap_tok, seg_count=dev)
+        w_seq, w_h, w_off, w_keep = _oracle_plan(ob.cache, 0, order, st, ty, ns, trans, 60, max_cuts, cap_seg, cap_tok, seg_count=ora)
+        n_seg, n_tok = got["counts"].tolist()
+        assert (n_seg, n_tok) == (len(w_keep), len(w_h)), again
+        assert np.array_equal(got["seg_keep"][:n_seg], w_keep) and np.array_equal(got["seg_offset"][:n_seg + 1], w_off)
+        assert np.array_equal(got["tok_handle"][:n_tok], w_h) and np.array_equal(got["tok_seq"][:n_tok], w_seq)
+        assert np.array_equal(dev, ora)
