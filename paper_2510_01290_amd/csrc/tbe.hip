@@ -212,22 +212,25 @@ __device__ __forceinline__ void store_row(float* dst, const float (&x)[8]) {
 // the binary32 rows of the tokens [from, to)
 template <int D, bool FP>
 __device__ __forceinline__ void write_rows(const thinkv_view& v, const TbeArgs& a, int from, int to, TokenAt* at) {
-  const int per = 4 * v.cfg.n_kv_heads, count = to - from;
-  __syncthreads();   // the tokens before have been used
-  if ((int)threadIdx.x < count) at[threadIdx.x] = token_at(v, a, from + threadIdx.x);
-  __syncthreads();
-  for (int idx = threadIdx.x; idx < count * per; idx += kGramThreads) {
-    const int i = idx / per, it = idx - i * per, hd = it >> 2, j = it & 3;
-    const int bits = at[i].bits;
-    RawKeys<D> r;
-    load_keys<D, FP>(at[i], hd, j, r);
-    float* row = a.x + (int64_t)(from + i) * a.dim + hd * D + 8 * j;
-    for_groups<D>([&](auto grp) {
-      constexpr int G = decltype(grp)::value;
-      float x[8];
-      unpack_keys<D, FP, G>(v.cfg, r, quad_meta<G>(r.meta), bits, j, x);
-      store_row(row + 32 * G, x);
-    });
+  const int per = 4 * v.cfg.n_kv_heads;
+  for (; from < to; from += kTbeMaxTokens) {
+    const int count = to - from < kTbeMaxTokens ? to - from : kTbeMaxTokens;
+    __syncthreads();   // the tokens before have been used
+    if ((int)threadIdx.x < count) at[threadIdx.x] = token_at(v, a, from + threadIdx.x);
+    __syncthreads();
+    for (int idx = threadIdx.x; idx < count * per; idx += kGramThreads) {
+      const int i = idx / per, it = idx - i * per, hd = it >> 2, j = it & 3;
+      const int bits = at[i].bits;
+      RawKeys<D> r;
+      load_keys<D, FP>(at[i], hd, j, r);
+      float* row = a.x + (int64_t)(from + i) * a.dim + hd * D + 8 * j;
+      for_groups<D>([&](auto grp) {
+        constexpr int G = decltype(grp)::value;
+        float x[8];
+        unpack_keys<D, FP, G>(v.cfg, r, quad_meta<G>(r.meta), bits, j, x);
+        store_row(row + 32 * G, x);
+      });
+    }
   }
 }
 
@@ -380,19 +383,22 @@ __device__ __forceinline__ bool seg_ok(const TbeArgs& a, int lo, int hi, int wan
 template <int D, bool FP>
 __global__ __launch_bounds__(kGramThreads, 4) void tbe_gram_kernel(thinkv_view v, TbeArgs a) {
   __shared__ __attribute__((aligned(16))) GramScratch sm;
-  const int seg = blockIdx.x / kSlices, slice = blockIdx.x % kSlices, tid = threadIdx.x;
-  const bool outside = seg == a.n_seg;   // the last workgroups: tokens before the first segment and behind the last
-  const int lo = a.seg_offset[outside ? 0 : seg], hi = a.seg_offset[outside ? seg : seg + 1], n = hi - lo;
-  const int want = outside ? 0 : a.seg_keep[seg], H = v.cfg.n_kv_heads;
-  if (outside || n <= want || !seg_ok(a, lo, hi, want)) {   // not clustered: only the rows
-    int from = outside ? 0 : lo > 0 ? lo : 0, to = outside ? lo : hi;
-    for (int part = 0; part < (outside ? 2 : 1); ++part) {
-      to = to < a.n_tok ? to : a.n_tok;
-      for (from += slice * kTbeMaxTokens; from < to; from += kSlices * kTbeMaxTokens)
-        write_rows<D, FP>(v, a, from, from + kTbeMaxTokens < to ? from + kTbeMaxTokens : to, sm.at);
-      from = hi > 0 ? hi : 0;
-      to = a.n_tok;
-    }
+  const int tid = threadIdx.x, outside = (int)blockIdx.x - a.n_seg * kSlices;
+  if (outside >= 0) {   // the last workgroups: tokens before the first segment and behind the last, a share each
+    const int lo = a.seg_offset[0], hi = a.seg_offset[a.n_seg];
+    const int before = lo < 0 ? 0 : (lo < a.n_tok ? lo : a.n_tok), behind = hi < 0 ? 0 : (hi < a.n_tok ? hi : a.n_tok);
+    const int all = before + a.n_tok - behind, part = (all + (int)gridDim.x - a.n_seg * kSlices - 1) / ((int)gridDim.x - a.n_seg * kSlices);
+    const int from = outside * part, to = from + part < all ? from + part : all, skip = behind - before;
+    write_rows<D, FP>(v, a, from, to < before ? to : before, sm.at);
+    write_rows<D, FP>(v, a, (from > before ? from : before) + skip, to + skip, sm.at);
+    return;
+  }
+  const int seg = blockIdx.x / kSlices, slice = blockIdx.x % kSlices;
+  const int lo = a.seg_offset[seg], hi = a.seg_offset[seg + 1], n = hi - lo, want = a.seg_keep[seg], H = v.cfg.n_kv_heads;
+  if (n <= want || !seg_ok(a, lo, hi, want)) {   // not clustered: only the rows, a share for each of the segment's workgroups
+    const int first = lo > 0 ? lo : 0, end = hi < a.n_tok ? hi : a.n_tok, part = (end - first + kSlices - 1) / kSlices;
+    const int from = first + slice * part;
+    write_rows<D, FP>(v, a, from, from + part < end ? from + part : end, sm.at);
     return;
   }
   const int slices = gram_slices(a.gram_room, n, H);
@@ -752,7 +758,10 @@ int launch_tbe_select(const thinkv_view& v, int layer, const int32_t* tok_seq, c
   a.n_tok = n_tok;
   a.max_iters = max_iters;
   const bool fp = v.cfg.format == THINKV_FMT_FP;
-  const dim3 grid((n_seg + 1) * kSlices), block(kGramThreads);
+  // Tokens outside every segment: 64 to a workgroup, 256 workgroups at most (32k such tokens behind 32
+  // segments: by four workgroups 987 us a call, by a kernel of its own for the rows of all tokens 101, now 72).
+  const int outside = (n_tok + 63) / 64;
+  const dim3 grid(n_seg * kSlices + (outside < 256 ? outside : 256)), block(kGramThreads);
   if (v.cfg.head_dim == 128) {
     if (fp) hipLaunchKernelGGL((tbe_gram_kernel<128, true>), grid, block, 0, st, v, a);
     else hipLaunchKernelGGL((tbe_gram_kernel<128, false>), grid, block, 0, st, v, a);
