@@ -14,7 +14,7 @@
 //   survivors  per non-empty cluster the member nearest the centroid (ties -> lowest index; of
 //              two members the earlier one: both are equally near their mean)
 //
-// Two kernels.  A centroid is the mean of points, so every product Lloyd's algorithm asks for is a
+// Three kernels.  A centroid is the mean of points, so every product Lloyd's algorithm asks for is a
 // mean of products between points: x.c_j = mean over the members i of x.x_i, |c_j|^2 = mean over the members of
 // x_i.c_j.  So the channels are walked once, for all products between the points of the segment (the Gram matrix, at most
 // 256 x 256, lower triangle), and an iteration is at most n^2 additions from LDS, of the clusters that changed only.
@@ -22,10 +22,11 @@
 // point, later the members, and for a cluster that has lost its last member the members it had before.
 // gram: the matrix, up to four workgroups a segment, each over some of the heads.  The keys go from the pages to the matrix
 // cores without a stop in memory; the binary32 rows are written on the way.
-// kmeans: a workgroup per segment adds the parts of the matrix and iterates.
+// kmeans: a workgroup per segment adds the parts of the matrix and iterates; up to 192 tokens, two workgroups a compute unit.
+// whole: segments of more tokens (a matrix of up to 132 KB), a workgroup per compute unit that does both.
 // 314 segments of ~110 tokens, 1,024 channels, us: keys to memory and a workgroup of a whole compute unit per segment (its
-// 139 KB of LDS made that 1.2 rounds of workgroups) 37 + 177; now 60 + 74.  gram is bound by vector instructions (four a
-// number to unpack and split it) and by 141 MB of rows; kmeans by chains from the lists of members to LDS and
+// 139 KB of LDS made that 1.2 rounds of workgroups) 37 + 177; now 67 + 74 (and 5 for whole, which finds nothing).  gram is bound by vector
+// instructions (four a number to unpack and split it) and by 141 MB of rows; kmeans by chains from the lists of members to LDS and
 // back (20 us around the first assignment, 1.5 to 4 for every further one), the parts (10) and the 54 MB of centroids (20).
 // The products run on the matrix cores; a dequantised key does not
 // fit binary16 and the binary32 matrix instruction is slow, so every number enters as the sum of
@@ -55,13 +56,15 @@ struct TbeArgs {
   float* gram;       // per segment: the parts of its Gram matrix
   int64_t gram_room; // numbers from one segment's parts to the next one's
   int layer, n_seg, n_tok, max_iters, dim;
+  int wide;          // the products of larger segments are shared too
 };
 
 constexpr int kGramThreads = 512;         // eight waves, two workgroups a compute unit
 constexpr int kGramWaves = kGramThreads / 64;
 constexpr int kSlices = 4;                // workgroups that share a segment's channels at most: with one, the units that get two segments end last (110 us)
 constexpr int kMacro = 32;                // points on a side of a wave's piece of the Gram matrix (2 x 2 MFMA tiles)
-constexpr int kPiecesPerWave = 3;         // 24 pieces of the lower triangle in one walk: all of 192 points
+constexpr int kPiecesPerWave = 3;         // 24 pieces of the lower triangle, all of 192 points, by eight waves; 36, all of 256, by sixteen
+constexpr int kFewPoints = 192;           // points of the largest segment that takes half a compute unit
 constexpr int kMaxGram = kTbeMaxTokens * (kTbeMaxTokens + 1) / 2;
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
@@ -73,9 +76,14 @@ __host__ __device__ __forceinline__ int tri(int i) { return i * (i + 1) / 2; }  
 // where that is too short for the largest segment
 static bool gram_in_centroids(int dim) { return kTbeMaxKeep * dim >= kMaxGram; }
 
-// workgroups that share a segment of n tokens: as many parts as there is room for
-__device__ __forceinline__ int gram_slices(int64_t room, int n, int heads) {
-  int s = (int)(room / tri(n));
+// Workgroups that share the products of a segment of n tokens: as many parts as there is room for, none where tbe_whole_kernel makes the
+// matrix itself.  That takes the larger segments: it walks the channels once, a gram workgroup, whose waves hold the products of 192 points,
+// twice.  But from 4,096 channels on, and with no more segments than have all their gram workgroups under way at once (wide), one
+// workgroup's walk is the longer one.  (200 to 256 tokens, 32 heads of 128, us, shared / not: 1 segment 232 / 345, 8 288 / 387, 64 455 / 501, 300 1,304 /
+// 1,188; 16 heads, 8 segments, by an earlier form of the shared way, 195 / 186, 64 333 / 229.)
+__device__ __forceinline__ int gram_slices(const TbeArgs& a, int n, int heads) {
+  if (n > kFewPoints && !a.wide) return 0;
+  int s = (int)(a.gram_room / tri(n));
   s = s < kSlices ? s : kSlices;
   return s < heads ? s : heads;
 }
@@ -235,11 +243,12 @@ __device__ __forceinline__ void write_rows(const thinkv_view& v, const TbeArgs& 
 }
 
 // ---- gram
+template <int POINTS, int TILES>
 struct GramScratch {
-  _Float16 xs[kTbeMaxTokens][kPadH];   // one tile: 64 channels of every point, each as high + low binary16 part
+  _Float16 xs[TILES][POINTS][kPadH];   // tiles: 64 channels of every point, each as high + low binary16 part
   TokenAt at[kTbeMaxTokens];
 };
-static_assert(sizeof(GramScratch) <= 81920, "two workgroups share the LDS of a compute unit");
+static_assert(sizeof(GramScratch<kTbeMaxTokens, 1>) <= 81920, "two workgroups share the LDS of a compute unit");
 
 // eight channels into a tile row: x = hi + lo with hi = binary16(x), lo = binary16(x - hi), 22 significant bits
 __device__ __forceinline__ void store_split(_Float16* row, const float (&x)[8]) {
@@ -255,14 +264,25 @@ __device__ __forceinline__ void store_split(_Float16* row, const float (&x)[8]) 
   *(f16x8*)(row + kTile) = lo.all;
 }
 
-// The products of all pairs of the n points over the heads [h0, h1), in the pieces [first, first + 24) of the lower triangle,
-// into out.  The channels go through LDS 64 at a time (the next head's codes are under way during a head's last products); wave
-// w owns the pieces first + w, + 8, + 16, 32 x 32 points each: 2 x 2 tiles share their operands, which halves the LDS reads a
-// product costs.
+// the places of a segment's tokens; behind the last one tokens that do not exist
+__device__ __forceinline__ void find_tokens(const thinkv_view& v, const TbeArgs& a, int lo, int n, TokenAt* at) {
+  if (threadIdx.x < kTbeMaxTokens) {
+    TokenAt t = {v.arena[0], 0, 0};
+    if ((int)threadIdx.x < n) t = token_at(v, a, lo + threadIdx.x);
+    at[threadIdx.x] = t;
+  }
+  __syncthreads();
+}
+
+// The products of all pairs of the n points over the heads [h0, h1), in the pieces [first, first + 3 W) of the lower triangle: out(first index,
+// second, product), once done() has been called by all.  The channels go through LDS 64 at a time (the next head's codes are under way during a head's last products); wave
+// w of W owns the pieces first + w, + W, + 2 W, 32 x 32 points each: 2 x 2 tiles share their operands, which halves the LDS reads a
+// product costs.  With two tiles in LDS the next one is unpacked beside the products of this one (a segment of 256 tokens, 2,048 channels, that has
+// a compute unit to itself: 218 us with one, now 182).
 // A product is hi.hi + hi.lo + lo.hi (exact products, binary32 sums; what is dropped is of the order of 2^-22 of |x||y|).
-template <int D, bool FP>
-__device__ __forceinline__ void gram_matrix(const thinkv_view& v, int n, int h0, int h1, int first, GramScratch& sm, float* __restrict__ x, int dim,
-                                            float* __restrict__ out) {
+template <int D, bool FP, int W, int POINTS, int TILES, class Done, class Out>
+__device__ __forceinline__ void gram_matrix(const thinkv_view& v, int n, int h0, int h1, int first, GramScratch<POINTS, TILES>& sm, float* __restrict__ x, int dim, Done done, Out out) {
+  constexpr int kPasses = (POINTS + 16 * W - 1) / (16 * W);   // a wave takes sixteen points at a time
   const thinkv_config& c = v.cfg;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r = lane & 15, g = lane >> 4;
@@ -271,7 +291,7 @@ __device__ __forceinline__ void gram_matrix(const thinkv_view& v, int n, int h0,
   f32x4 acc[kPiecesPerWave][2][2];
 #pragma unroll
   for (int t = 0; t < kPiecesPerWave; ++t) {
-    int rest = first + wave + t * kGramWaves, i = 0;
+    int rest = first + wave + t * W, i = 0;
     while (rest > i) rest -= ++i;
     pi[t] = i;
     pj[t] = rest;
@@ -280,23 +300,22 @@ __device__ __forceinline__ void gram_matrix(const thinkv_view& v, int n, int h0,
 #pragma unroll
       for (int w = 0; w < 2; ++w) acc[t][u][w] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-  RawKeys<D> raw[2];
+  RawKeys<D> raw[kPasses];
   // the places come from LDS every time: held in registers they would be in the way of the products
   auto fetch = [&](int hd) {
     if (hd >= h1) return;
 #pragma unroll
-    for (int q = 0; q < 2; ++q)
-      if (16 * wave + kGramThreads / 4 * q < n) load_keys<D, FP>(sm.at[16 * wave + r + kGramThreads / 4 * q], hd, g, raw[q]);
+    for (int q = 0; q < kPasses; ++q)
+      if (16 * (wave + W * q) < n) load_keys<D, FP>(sm.at[16 * (wave + W * q) + r], hd, g, raw[q]);
   };
-  auto tile = [&](int hd, auto half) {
+  auto store = [&](int hd, auto half, int b) {   // of the last half: and the next head's codes are asked for
     constexpr int G0 = 2 * decltype(half)::value;
-    __syncthreads();   // the previous tile has been used
     // a wave takes sixteen tokens, lane (r, g) the chunk g of token r: sixteen lanes write to sixteen rows, whose
     // starts lie four banks apart
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const int t = 16 * wave + r + kGramThreads / 4 * q;
-      if (16 * wave + kGramThreads / 4 * q < n) {   // rows that pad the sixteen are zeros
+    for (int q = 0; q < kPasses; ++q) {
+      const int t = 16 * (wave + W * q) + r;
+      if (16 * (wave + W * q) < n) {   // rows that pad the sixteen are zeros
         const int bits = sm.at[t].bits;
         float val[8];
 #pragma unroll
@@ -304,16 +323,17 @@ __device__ __forceinline__ void gram_matrix(const thinkv_view& v, int n, int h0,
           const uint32_t m = (uint32_t)__builtin_amdgcn_ds_bpermute(64 * (G0 + u) + 4 * r, (int)raw[q].meta);
           if (u == 0) unpack_keys<D, FP, G0>(c, raw[q], m, bits, g, val);
           else unpack_keys<D, FP, G0 + 1>(c, raw[q], m, bits, g, val);
-          store_split(&sm.xs[t][32 * u + 8 * g], val);
+          store_split(&sm.xs[b][t][32 * u + 8 * g], val);
           if (first == 0 && t < n) store_row(&x[(int64_t)t * dim + hd * D + 32 * (G0 + u) + 8 * g], val);
         }
       }
     }
     if (G0 == D / kGroup - 2) fetch(hd + 1);
-    __syncthreads();
+  };
+  auto products = [&](int b) {
 #pragma unroll
     for (int t = 0; t < kPiecesPerWave; ++t)
-      if (first + wave + t * kGramWaves < end) {
+      if (first + wave + t * W < end) {
         const bool diag = pi[t] == pj[t];
 #pragma unroll
         for (int ks = 0; ks < kTile / 32; ++ks) {
@@ -321,7 +341,7 @@ __device__ __forceinline__ void gram_matrix(const thinkv_view& v, int n, int h0,
           f16x8 ah[2], al[2], bh[2], bl[2];
 #pragma unroll
           for (int u = 0; u < 2; ++u) {
-            const _Float16* ra = sm.xs[kMacro * pi[t] + 16 * u + r];
+            const _Float16* ra = sm.xs[b][kMacro * pi[t] + 16 * u + r];
             ah[u] = *(const f16x8*)&ra[32 * ks + 8 * g];
             al[u] = *(const f16x8*)&ra[kTile + 32 * ks + 8 * g];
           }
@@ -334,7 +354,7 @@ __device__ __forceinline__ void gram_matrix(const thinkv_view& v, int n, int h0,
           } else {
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
-              const _Float16* rb = sm.xs[kMacro * pj[t] + 16 * u + r];
+              const _Float16* rb = sm.xs[b][kMacro * pj[t] + 16 * u + r];
               bh[u] = *(const f16x8*)&rb[32 * ks + 8 * g];
               bl[u] = *(const f16x8*)&rb[kTile + 32 * ks + 8 * g];
             }
@@ -354,15 +374,42 @@ __device__ __forceinline__ void gram_matrix(const thinkv_view& v, int n, int h0,
   // rows that pad the last piece: zero
   const int full = (n + 15) & ~15;
   if (full & 16)
-    for (int i = tid; i < 16 * (kPadH / 8); i += kGramThreads)
-      *(f16x8*)&sm.xs[full + i / (kPadH / 8)][8 * (i % (kPadH / 8))] = f16x8{0, 0, 0, 0, 0, 0, 0, 0};
-  for (int hd = h0; hd < h1; ++hd) {
-    tile(hd, std::integral_constant<int, 0>{});
-    if constexpr (D == 128) tile(hd, std::integral_constant<int, 1>{});
+    for (int b = 0; b < TILES; ++b)
+      for (int i = tid; i < 16 * (kPadH / 8); i += 64 * W)
+        *(f16x8*)&sm.xs[b][full + i / (kPadH / 8)][8 * (i % (kPadH / 8))] = f16x8{0, 0, 0, 0, 0, 0, 0, 0};
+  constexpr std::integral_constant<int, 0> low{};   // halves of a head
+  constexpr std::integral_constant<int, D / 64 - 1> high{};
+  if constexpr (TILES == 1) {
+    auto tile = [&](int hd, auto half) {
+      __syncthreads();   // the previous tile has been used
+      store(hd, half, 0);
+      __syncthreads();
+      products(0);
+    };
+    for (int hd = h0; hd < h1; ++hd) {
+      tile(hd, low);
+      if constexpr (D == 128) tile(hd, high);
+    }
+  } else {
+    store(h0, low, 0);
+    int b = 0;
+    for (int hd = h0; hd < h1; ++hd) {
+      if constexpr (D == 128) {
+        __syncthreads();   // tile b is there, the other one has been used
+        store(hd, high, b ^ 1);
+        products(b);
+        b ^= 1;
+      }
+      __syncthreads();
+      if (hd + 1 < h1) store(hd + 1, low, b ^ 1);
+      products(b);
+      b ^= 1;
+    }
   }
+  done();
 #pragma unroll
   for (int t = 0; t < kPiecesPerWave; ++t)
-    if (first + wave + t * kGramWaves < end) {
+    if (first + wave + t * W < end) {
 #pragma unroll
       for (int u = 0; u < 2; ++u)
 #pragma unroll
@@ -370,7 +417,7 @@ __device__ __forceinline__ void gram_matrix(const thinkv_view& v, int n, int h0,
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             const int p = kMacro * pi[t] + 16 * u + 4 * g + i, q = kMacro * pj[t] + 16 * w + r;
-            if (p < n && q <= p) out[tri(p) + q] = acc[t][u][w][i];
+            if (p < n && q <= p) out(p, q, acc[t][u][w][i]);
           }
     }
 }
@@ -380,9 +427,9 @@ __device__ __forceinline__ bool seg_ok(const TbeArgs& a, int lo, int hi, int wan
   return hi - lo <= kTbeMaxTokens && want <= kTbeMaxKeep && want >= 1 && lo >= 0 && hi <= a.n_tok;
 }
 
-template <int D, bool FP>
+template <int D, bool FP, bool WIDE>
 __global__ __launch_bounds__(kGramThreads, 4) void tbe_gram_kernel(thinkv_view v, TbeArgs a) {
-  __shared__ __attribute__((aligned(16))) GramScratch sm;
+  __shared__ __attribute__((aligned(16))) GramScratch<WIDE ? kTbeMaxTokens : kFewPoints, 1> sm;
   const int tid = threadIdx.x, outside = (int)blockIdx.x - a.n_seg * kSlices;
   if (outside >= 0) {   // the last workgroups: tokens before the first segment and behind the last, a share each
     const int lo = a.seg_offset[0], hi = a.seg_offset[a.n_seg];
@@ -401,40 +448,35 @@ __global__ __launch_bounds__(kGramThreads, 4) void tbe_gram_kernel(thinkv_view v
     write_rows<D, FP>(v, a, from, from + part < end ? from + part : end, sm.at);
     return;
   }
-  const int slices = gram_slices(a.gram_room, n, H);
+  const int slices = gram_slices(a, n, H);
   if (slice >= slices) return;
-  if (tid < kTbeMaxTokens) {
-    TokenAt at = {v.arena[0], 0, 0};
-    if (tid < n) at = token_at(v, a, lo + tid);
-    sm.at[tid] = at;
-  }
-  __syncthreads();
+  find_tokens(v, a, lo, n, sm.at);
   float* out = a.gram + seg * a.gram_room + (int64_t)slice * tri(n);
-  const int mb = (n + kMacro - 1) / kMacro;
-  for (int first = 0; first < mb * (mb + 1) / 2; first += kPiecesPerWave * kGramWaves)
-    gram_matrix<D, FP>(v, n, H * slice / slices, H * (slice + 1) / slices, first, sm, a.x + (int64_t)lo * a.dim, a.dim, out);
+  auto walk = [&](int first) {
+    gram_matrix<D, FP, kGramWaves>(v, n, H * slice / slices, H * (slice + 1) / slices, first, sm, a.x + (int64_t)lo * a.dim, a.dim, [] {},
+                                   [&](int p, int q, float d) { out[tri(p) + q] = d; });
+  };
+  walk(0);
+  if (WIDE && n > kFewPoints) walk(kPiecesPerWave * kGramWaves);
 }
 
 // ---- kmeans
-// Twelve waves, two workgroups a compute unit: LDS holds the matrix of 192 points; the rows of the points 192..255 of a
-// larger segment stay in memory, in the first part of the matrix.
-constexpr int kKmThreads = 768;
-constexpr int kKmWaves = kKmThreads / 64;
-constexpr int kClPerThread = (kTbeMaxKeep + 2) / 3;       // clusters of a thread at most: there are three groups of waves or more
+// W waves; LDS holds the matrix of POINTS points.  Up to kFewPoints: twelve waves, two workgroups a compute unit.  More: sixteen waves, a
+// compute unit to themselves.  (With the products of the points 192..255 in memory instead, 314 segments, us, before the keys went from the pages to the
+// matrix cores / with those in memory / now: 8 heads of 128, 200 to 256 tokens 473 / 534 / 342, 256 tokens 501 / 734 / 353; 8 of 64 337 / 497 / 235; 2 of 128
+// 251 / 384 / 195; 2 of 64 279 / 297 / 185; one segment of 256, 8 of 128, 165 / 268 / 142.)
+constexpr int kKmWaves = 12, kWholeWaves = 16;
 constexpr int kPT = kTbeMaxTokens / 64;                   // tokens per lane of a wave that sorts a list
 constexpr int kWords = kTbeMaxTokens / 32;
-constexpr int kLdsPoints = 192;
-constexpr int kLdsGram = kLdsPoints * (kLdsPoints + 1) / 2;
-typedef float f32xk __attribute__((ext_vector_type(32)));
-static_assert(kClPerThread <= 32, "");
 
+template <int W, int POINTS>
 struct KmScratch {
-  float gram[kLdsGram];                                        // products of all pairs of points, lower triangle
+  float gram[POINTS * (POINTS + 1) / 2];                       // products of all pairs of points, lower triangle
   uint32_t basis[kTbeMaxKeep][kWords];                         // the points a cluster's centroid is the mean of
   union {
     struct {
-      float bd[kKmThreads];                                    // per group of waves: best distance of every point ...
-      uint8_t bj[kKmThreads];                                  // ... and the cluster it belongs to
+      float bd[64 * W];                                        // per group of waves: best distance of every point ...
+      uint8_t bj[64 * W];                                      // ... and the cluster it belongs to
     };
     uint32_t next[kTbeMaxKeep][kWords];                        // members under the assignment just made
     struct {
@@ -449,7 +491,7 @@ struct KmScratch {
   unsigned long long moved;                                    // clusters whose centroid has just changed
   int vote[2];                                                 // a point changed its cluster, in iterations of either parity
 };
-static_assert(sizeof(KmScratch) <= 81920, "two workgroups share the LDS of a compute unit");
+static_assert(sizeof(KmScratch<kKmWaves, kFewPoints>) <= 81920, "two workgroups share the LDS of a compute unit");
 
 // f(point) for every point of a cluster's basis, in index order, two at a time (the second -1 where there is none); the
 // points are the same in all lanes
@@ -472,55 +514,21 @@ __device__ __forceinline__ void for_basis(const uint32_t* mask, F f) {
   if (held >= 0) f(held, -1);
 }
 
-__global__ __launch_bounds__(kKmThreads) __attribute__((amdgpu_waves_per_eu(6))) void tbe_kmeans_kernel(thinkv_view v, TbeArgs a) {
-  const thinkv_config& c = v.cfg;
-  const int seg = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int lo = a.seg_offset[seg], hi = a.seg_offset[seg + 1];
-  const int n = hi - lo, want = a.seg_keep[seg];
-  if (n <= 0) return;
-  const bool ok = seg_ok(a, lo, hi, want);
-  if (!ok || want >= n) {
-    // outside what this kernel covers: nothing is evicted, and the caller is told; or everything survives
-    if (!ok && tid == 0) atomicOr(&v.dev_status[c.max_seqs * c.n_layers], THINKV_ST_BAD_SEGMENT);
-    for (int i = tid; i < n && lo >= 0 && lo + i < a.n_tok; i += kKmThreads) {
-      a.ev_handle[lo + i] = -1;
-      a.assign[lo + i] = -1;
-    }
-    return;
-  }
-  const int k = want, dim = a.dim;
-  __shared__ __attribute__((aligned(16))) KmScratch sm;
-  // the parts of the matrix meet, in order
-  float* parts = a.gram + seg * a.gram_room;
-  const int slices = gram_slices(a.gram_room, n, c.n_kv_heads);
-  const bool big = n > kLdsPoints;
-  const int all = tri(n);
-  for (int i0 = tid; i0 < all; i0 += 4 * kKmThreads) {   // sixteen loads under way
-    float part[kSlices][4];
-#pragma unroll
-    for (int s = 0; s < kSlices; ++s)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int i = i0 + kKmThreads * q;
-        part[s][q] = s < slices && i < all ? parts[s * all + i] : 0.f;
-      }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int i = i0 + kKmThreads * q;
-      float sum = part[0][q];
-#pragma unroll
-      for (int s = 1; s < kSlices; ++s) sum += part[s][q];
-      if (i < kLdsGram && i < all) sm.gram[i] = sum;
-      else if (i < all) parts[i] = sum;
-    }
-  }
-  // The waves form groups of `pw` that hold all points between them, and a group looks at every `groups`-th cluster
-  const int pw = (n + 63) >> 6, groups = kKmWaves / pw;
+// Lloyd's algorithm, the survivors and the centroids of a segment whose matrix is in LDS
+template <int W, int POINTS>
+__device__ __forceinline__ void choose_survivors(const TbeArgs& a, int seg, int lo, int n, int k, KmScratch<W, POINTS>& sm) {
+  constexpr int kThreads = 64 * W, kMinGroups = W / (POINTS / 64), kClPerThread = (kTbeMaxKeep + kMinGroups - 1) / kMinGroups;
+  static_assert(kClPerThread == 16, "");
+  typedef float f32xk __attribute__((ext_vector_type(kClPerThread)));   // a number for each of a thread's clusters
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), dim = a.dim;
+  // The waves form groups of `pw` that hold all points between them, and a group looks at every `groups`-th cluster (waves that
+  // make no whole group: at none)
+  const int pw = (n + 63) >> 6, groups = W / pw;
   const int group = wave / pw, p = (wave - group * pw) * 64 + lane;
   const bool here = p < n;
   const int pc = here ? p : n - 1, tp = tri(pc);
   // initial centroids: evenly spaced points, distinct, since k < n
-  for (int i = tid; i < kTbeMaxKeep * kWords; i += kKmThreads) (&sm.basis[0][0])[i] = 0u;
+  for (int i = tid; i < kTbeMaxKeep * kWords; i += kThreads) (&sm.basis[0][0])[i] = 0u;
   if (tid < kTbeMaxKeep) sm.span[tid] = 0u;
   if (tid < kTbeMaxTokens / 4) sm.list[tid] = 0u;   // every byte is a point's at any time
   if (tid < 2) sm.vote[tid] = 0;
@@ -550,35 +558,28 @@ __global__ __launch_bounds__(kKmThreads) __attribute__((amdgpu_waves_per_eu(6)))
       const int below = tp + m, above = tri(m) + pc;
       return pc >= m ? below : above;
     };
-    for (int i = 0, j = group; j < k; ++i, j += groups) {
+    for (int i = 0, j = group < groups ? group : k; j < k; ++i, j += groups) {
       if (!(moved >> j & 1)) continue;
       const uint32_t sp = __builtin_amdgcn_readlane(span, j);
       int q = (int)(sp & 0xFFFFu);
       const int end = q + (int)(sp >> 16);
       float sum = 0.f;
-      if (!big) {
-        // four at a time, then two, then one: the additions stay in order, the loads do not wait for each other (one ahead of the
-        // other an eviction event of 316 segments took 215.2 us, now 212.2)
-        for (; q + 4 <= end; q += 4) {
-          const float a0 = sm.gram[place(q)], a1 = sm.gram[place(q + 1)], a2 = sm.gram[place(q + 2)], a3 = sm.gram[place(q + 3)];
-          sum += a0;
-          sum += a1;
-          sum += a2;
-          sum += a3;
-        }
-        if (q + 2 <= end) {
-          const float a0 = sm.gram[place(q)], a1 = sm.gram[place(q + 1)];
-          sum += a0;
-          sum += a1;
-          q += 2;
-        }
-        if (q < end) sum += sm.gram[place(q)];
-      } else {
-        for (; q < end; ++q) {
-          const int at = place(q);
-          sum += at < kLdsGram ? sm.gram[at] : __builtin_nontemporal_load(&parts[at]);
-        }
+      // four at a time, then two, then one: the additions stay in order, the loads do not wait for each other (one ahead of the
+      // other an eviction event of 316 segments took 215.2 us, now 212.2)
+      for (; q + 4 <= end; q += 4) {
+        const float a0 = sm.gram[place(q)], a1 = sm.gram[place(q + 1)], a2 = sm.gram[place(q + 2)], a3 = sm.gram[place(q + 3)];
+        sum += a0;
+        sum += a1;
+        sum += a2;
+        sum += a3;
       }
+      if (q + 2 <= end) {
+        const float a0 = sm.gram[place(q)], a1 = sm.gram[place(q + 1)];
+        sum += a0;
+        sum += a1;
+        q += 2;
+      }
+      if (q < end) sum += sm.gram[place(q)];
       const float d = sum * __builtin_bit_cast(float, __builtin_amdgcn_readlane(inv, j));
       dot[i] = d;
       if (mine == j && here) sm.own[p] = d;
@@ -639,7 +640,7 @@ __global__ __launch_bounds__(kKmThreads) __attribute__((amdgpu_waves_per_eu(6)))
     }
     if (tid == 0) sm.vote[~it & 1] = 0;
     // members of every cluster; a cluster without any keeps its basis
-    for (int i = tid; i < kTbeMaxKeep * kWords; i += kKmThreads) (&sm.next[0][0])[i] = 0u;
+    for (int i = tid; i < kTbeMaxKeep * kWords; i += kThreads) (&sm.next[0][0])[i] = 0u;
     __syncthreads();
     if (group == 0 && here) atomicOr(&sm.next[mine][p >> 5], 1u << (p & 31));
     __syncthreads();
@@ -685,7 +686,7 @@ __global__ __launch_bounds__(kKmThreads) __attribute__((amdgpu_waves_per_eu(6)))
   }
   __syncthreads();
   if (group == 0 && here) {
-    const float dist = fmaxf(fmaf(-2.f, sm.own[p], tp + p < kLdsGram ? sm.gram[tp + p] : parts[tp + p]) + sm.cc[mine], 0.f);
+    const float dist = fmaxf(fmaf(-2.f, sm.own[p], sm.gram[tp + p]) + sm.cc[mine], 0.f);
     atomicMin(&sm.low[mine], p);
     // distances are not negative, so their bit patterns order like the numbers; the index breaks ties
     atomicMin(&sm.best[mine], ((unsigned long long)__builtin_bit_cast(uint32_t, dist) << 32) | (unsigned)p);
@@ -698,13 +699,12 @@ __global__ __launch_bounds__(kKmThreads) __attribute__((amdgpu_waves_per_eu(6)))
     a.ev_handle[lo + p] = keep ? -1 : a.tok_handle[lo + p];
     a.assign[lo + p] = mine;
   }
-  __syncthreads();   // the matrix in memory has been read: the centroids take its place
   // ---- the centroids, for callers that look at them: a wave per cluster, up to 1,024 channels at a time, two members' rows
   // (eight loads a lane) in flight, members in index order.  Nothing here reads them again: past the caches, where they made
   // the next call's gram kernel wait (66 us, now 60)
   const float* x = a.x + (int64_t)lo * dim;
   float* cent = a.cent + (int64_t)seg * kTbeMaxKeep * dim;
-  for (int j = wave; j < k; j += kKmWaves) {
+  for (int j = wave; j < k; j += W) {
     int cnt = 0;
 #pragma unroll
     for (int w = 0; w < kWords; ++w) cnt += __popc(sm.basis[j][w]);
@@ -737,6 +737,102 @@ __global__ __launch_bounds__(kKmThreads) __attribute__((amdgpu_waves_per_eu(6)))
   }
 }
 
+// The parts of the matrix meet, in order (they lie where the centroids will: all have been read before those are written)
+template <int THREADS>
+__device__ __forceinline__ void add_parts(const float* parts, int slices, int n, float* gram) {
+  const int all = tri(n);
+  for (int i0 = threadIdx.x; i0 < all; i0 += 4 * THREADS) {   // sixteen loads under way
+    float part[kSlices][4];
+#pragma unroll
+    for (int s = 0; s < kSlices; ++s)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int i = i0 + THREADS * q;
+        part[s][q] = s < slices && i < all ? parts[s * all + i] : 0.f;
+      }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int i = i0 + THREADS * q;
+      float sum = part[0][q];
+#pragma unroll
+      for (int s = 1; s < kSlices; ++s) sum += part[s][q];
+      if (i < all) gram[i] = sum;
+    }
+  }
+}
+
+__global__ __launch_bounds__(64 * kKmWaves) __attribute__((amdgpu_waves_per_eu(6))) void tbe_kmeans_kernel(thinkv_view v, TbeArgs a) {
+  constexpr int kThreads = 64 * kKmWaves;
+  const thinkv_config& c = v.cfg;
+  const int seg = blockIdx.x, tid = threadIdx.x;
+  const int lo = a.seg_offset[seg], hi = a.seg_offset[seg + 1];
+  const int n = hi - lo, want = a.seg_keep[seg];
+  if (n <= 0) return;
+  const bool ok = seg_ok(a, lo, hi, want);
+  if (!ok || want >= n) {
+    // outside what this kernel covers: nothing is evicted, and the caller is told; or everything survives
+    if (!ok && tid == 0) atomicOr(&v.dev_status[c.max_seqs * c.n_layers], THINKV_ST_BAD_SEGMENT);
+    for (int i = tid; i < n && lo >= 0 && lo + i < a.n_tok; i += kThreads) {
+      a.ev_handle[lo + i] = -1;
+      a.assign[lo + i] = -1;
+    }
+    return;
+  }
+  const int slices = gram_slices(a, n, c.n_kv_heads);
+  if (n > kFewPoints || slices == 0) return;
+  __shared__ __attribute__((aligned(16))) KmScratch<kKmWaves, kFewPoints> sm;
+  add_parts<kThreads>(a.gram + seg * a.gram_room, slices, n, sm.gram);
+  choose_survivors(a, seg, lo, n, want, sm);
+}
+
+// The segments that kmeans leaves out: a workgroup of sixteen waves, with the LDS of a whole compute unit, makes the matrix and iterates.
+// Where there are none, the launch is 5 us.  (A segment a lane to find them: the same 5 us, five more registers spilled.)
+template <int D, bool FP>
+__global__ __launch_bounds__(64 * kWholeWaves) void tbe_whole_kernel(thinkv_view v, TbeArgs a) {
+  __shared__ __attribute__((aligned(16))) union {
+    GramScratch<kTbeMaxTokens, 2> tile;
+    KmScratch<kWholeWaves, kTbeMaxTokens> km;
+  } sm;
+  const int H = v.cfg.n_kv_heads;
+  for (int seg = blockIdx.x; seg < a.n_seg; seg += gridDim.x) {
+    const int lo = a.seg_offset[seg], hi = a.seg_offset[seg + 1], n = hi - lo, want = a.seg_keep[seg];
+    if (n <= want || !seg_ok(a, lo, hi, want) || gram_slices(a, n, H) > 0) continue;
+    __syncthreads();   // the segment before is done
+    find_tokens(v, a, lo, n, sm.tile.at);
+    gram_matrix<D, FP, kWholeWaves>(v, n, 0, H, 0, sm.tile, a.x + (int64_t)lo * a.dim, a.dim, [] { __syncthreads(); },   // the matrix takes the tiles' place
+                                    [&](int p, int q, float d) { sm.km.gram[tri(p) + q] = d; });
+    choose_survivors(a, seg, lo, n, want, sm.km);
+  }
+}
+
+// ... or, wide, adds the parts that gram has made of it
+__global__ __launch_bounds__(64 * kWholeWaves) void tbe_wide_kernel(thinkv_view v, TbeArgs a) {
+  __shared__ __attribute__((aligned(16))) KmScratch<kWholeWaves, kTbeMaxTokens> sm;
+  for (int seg = blockIdx.x; seg < a.n_seg; seg += gridDim.x) {
+    const int lo = a.seg_offset[seg], hi = a.seg_offset[seg + 1], n = hi - lo, want = a.seg_keep[seg];
+    if (n <= kFewPoints || !seg_ok(a, lo, hi, want)) continue;   // (nobody keeps so many)
+    __syncthreads();   // the segment before is done
+    add_parts<64 * kWholeWaves>(a.gram + seg * a.gram_room, gram_slices(a, n, v.cfg.n_kv_heads), n, sm.gram);
+    choose_survivors(a, seg, lo, n, want, sm);
+  }
+}
+static_assert(kTbeMaxKeep <= kFewPoints, "tbe_wide_kernel");
+
+template <int D, bool FP>
+static void launch_kernels(const thinkv_view& v, const TbeArgs& a, hipStream_t st) {
+  // Tokens outside every segment: 64 to a workgroup, 256 workgroups at most (32k such tokens behind 32
+  // segments: by four workgroups 987 us a call, by a kernel of its own for the rows of all tokens 101, now 72).
+  const int outside = (a.n_tok + 63) / 64, most = a.n_tok < kTbeMaxTokens ? a.n_tok : kTbeMaxTokens;
+  const dim3 grid(a.n_seg * kSlices + (outside < 256 ? outside : 256));
+  if (a.wide) hipLaunchKernelGGL((tbe_gram_kernel<D, FP, true>), grid, dim3(kGramThreads), 0, st, v, a);
+  else hipLaunchKernelGGL((tbe_gram_kernel<D, FP, false>), grid, dim3(kGramThreads), 0, st, v, a);
+  hipLaunchKernelGGL(tbe_kmeans_kernel, dim3(a.n_seg), dim3(64 * kKmWaves), 0, st, v, a);
+  if (most <= kFewPoints && tri(most) <= a.gram_room) return;   // (no segment can be left out)
+  const dim3 units(a.n_seg < 256 ? a.n_seg : 256), whole(64 * kWholeWaves);   // they go round the segments
+  if (a.wide) hipLaunchKernelGGL(tbe_wide_kernel, units, whole, 0, st, v, a);
+  else hipLaunchKernelGGL((tbe_whole_kernel<D, FP>), units, whole, 0, st, v, a);
+}
+
 int launch_tbe_select(const thinkv_view& v, int layer, const int32_t* tok_seq, const int32_t* tok_handle, const int32_t* seg_offset,
                       const int32_t* seg_keep, int n_seg, int n_tok, int max_iters, int32_t* ev_handle, void* workspace,
                       hipStream_t st) {
@@ -757,19 +853,12 @@ int launch_tbe_select(const thinkv_view& v, int layer, const int32_t* tok_seq, c
   a.n_seg = n_seg;
   a.n_tok = n_tok;
   a.max_iters = max_iters;
+  a.wide = a.dim >= 4096 && n_seg <= 128;   // (512 gram workgroups fill the machine)
   const bool fp = v.cfg.format == THINKV_FMT_FP;
-  // Tokens outside every segment: 64 to a workgroup, 256 workgroups at most (32k such tokens behind 32
-  // segments: by four workgroups 987 us a call, by a kernel of its own for the rows of all tokens 101, now 72).
-  const int outside = (n_tok + 63) / 64;
-  const dim3 grid(n_seg * kSlices + (outside < 256 ? outside : 256)), block(kGramThreads);
-  if (v.cfg.head_dim == 128) {
-    if (fp) hipLaunchKernelGGL((tbe_gram_kernel<128, true>), grid, block, 0, st, v, a);
-    else hipLaunchKernelGGL((tbe_gram_kernel<128, false>), grid, block, 0, st, v, a);
-  } else {
-    if (fp) hipLaunchKernelGGL((tbe_gram_kernel<64, true>), grid, block, 0, st, v, a);
-    else hipLaunchKernelGGL((tbe_gram_kernel<64, false>), grid, block, 0, st, v, a);
-  }
-  hipLaunchKernelGGL(tbe_kmeans_kernel, dim3(n_seg), dim3(kKmThreads), 0, st, v, a);
+  if (v.cfg.head_dim == 128)
+    fp ? launch_kernels<128, true>(v, a, st) : launch_kernels<128, false>(v, a, st);
+  else
+    fp ? launch_kernels<64, true>(v, a, st) : launch_kernels<64, false>(v, a, st);
   return hipGetLastError() == hipSuccess ? THINKV_OK : THINKV_E_HIP;
 }
 
