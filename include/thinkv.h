@@ -288,6 +288,7 @@ int thinkv_decode_attention_valu(const thinkv_view* view, int32_t layer, const v
  *                        float cent[n_seg][THINKV_TBE_MAX_KEEP][n_kv_heads * head_dim], the centroids after the last
  *                        update; int32 assign[n_tok], every token's cluster at the last assignment (-1 where the
  *                        segment was not clustered) -- for callers that want to inspect the clustering
+ *                        -- and that is all it asks for: what the kernels need besides lies in the centroids' place
  * Arithmetic is binary32 (products of 22-bit operands), squared distances taken as |x|^2 - 2 x.c + |c|^2; a decision between
  * two candidates whose distances differ by less than about 1e-5 of the points' mean squared norm
  * may differ from a binary64 evaluation.  Device-side errors: THINKV_ST_BAD_SLOT / BAD_SEQ for a token that

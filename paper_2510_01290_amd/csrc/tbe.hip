@@ -23,7 +23,8 @@
 // gram: the matrix, up to four workgroups a segment, each over some of the heads.  The keys go from the pages to the matrix
 // cores without a stop in memory; the binary32 rows are written on the way.
 // kmeans: a workgroup per segment adds the parts of the matrix and iterates; up to 192 tokens, two workgroups a compute unit.
-// whole: segments of more tokens (a matrix of up to 132 KB), a workgroup per compute unit that does both.
+// whole: segments of more tokens (a matrix of up to 132 KB), a workgroup per compute unit that does both; and, alone, all segments of up to 512
+// channels.
 // 314 segments of ~110 tokens, 1,024 channels, us: keys to memory and a workgroup of a whole compute unit per segment (its
 // 139 KB of LDS made that 1.2 rounds of workgroups) 37 + 177; now 67 + 74 (and 5 for whole, which finds nothing).  gram is bound by vector
 // instructions (four a number to unpack and split it) and by 141 MB of rows; kmeans by chains from the lists of members to LDS and
@@ -53,10 +54,7 @@ struct TbeArgs {
   float* x;      // [n_tok][dim]
   float* cent;   // [n_seg][kTbeMaxKeep][dim]
   int32_t* assign;   // [n_tok] cluster of every token at the last assignment (-1: its segment was not clustered)
-  float* gram;       // per segment: the parts of its Gram matrix
-  int64_t gram_room; // numbers from one segment's parts to the next one's
   int layer, n_seg, n_tok, max_iters, dim;
-  int wide;          // the products of larger segments are shared too
 };
 
 constexpr int kGramThreads = 512;         // eight waves, two workgroups a compute unit
@@ -65,34 +63,33 @@ constexpr int kSlices = 4;                // workgroups that share a segment's c
 constexpr int kMacro = 32;                // points on a side of a wave's piece of the Gram matrix (2 x 2 MFMA tiles)
 constexpr int kPiecesPerWave = 3;         // 24 pieces of the lower triangle, all of 192 points, by eight waves; 36, all of 256, by sixteen
 constexpr int kFewPoints = 192;           // points of the largest segment that takes half a compute unit
-constexpr int kMaxGram = kTbeMaxTokens * (kTbeMaxTokens + 1) / 2;
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 constexpr int kPadH = 2 * kTile + 8;   // binary16 numbers per tile row: high parts, low parts, padding (an odd multiple of 16 bytes)
 
 __host__ __device__ __forceinline__ int tri(int i) { return i * (i + 1) / 2; }   // where row i of the lower triangle begins
 
-// The parts of a segment's matrix lie in the place of its centroids, which are written last, or behind everything else
-// where that is too short for the largest segment
-static bool gram_in_centroids(int dim) { return kTbeMaxKeep * dim >= kMaxGram; }
+// The parts of a segment's matrix lie where its centroids will, which are written last: 64 * dim numbers.
+// narrow: that is less than the largest matrix.  Then no segment is shared, and tbe_whole_kernel is the only launch: a workgroup walks few channels,
+// and three launches and the parts' way through memory cost more (64 to 192 tokens, us, with 131,584 bytes more a segment for the parts / now: 2 heads of
+// 64, 314 segments 119 / 90, 2,000 410 / 384; 5 of 64 138 / 113, 566 / 483; 8 of 64 202 / 169, 725 / 549).
+// wide: the products of segments of more than kFewPoints are shared as well.  A gram workgroup, whose waves hold the products of 192 points, walks
+// the channels twice for them; but from 4,096 channels on, and with no more segments than have all their gram workgroups under
+// way at once (512 of them), tbe_whole_kernel's one walk by one workgroup is the longer one.  (200 to 256 tokens, 32 heads of 128, us, shared / not: 1
+// segment 232 / 345, 8 288 / 387, 64 455 / 501, 300 1,304 / 1,188; 16 heads, 8 segments, by an earlier form of the shared way, 195 / 186, 64 333 / 229.)
+static bool is_narrow(int dim) { return kTbeMaxKeep * dim < tri(kTbeMaxTokens); }
+static bool is_wide(int dim, int n_seg) { return dim >= 4096 && n_seg <= 512 / kSlices; }
 
-// Workgroups that share the products of a segment of n tokens: as many parts as there is room for, none where tbe_whole_kernel makes the
-// matrix itself.  That takes the larger segments: it walks the channels once, a gram workgroup, whose waves hold the products of 192 points,
-// twice.  But from 4,096 channels on, and with no more segments than have all their gram workgroups under way at once (wide), one
-// workgroup's walk is the longer one.  (200 to 256 tokens, 32 heads of 128, us, shared / not: 1 segment 232 / 345, 8 288 / 387, 64 455 / 501, 300 1,304 /
-// 1,188; 16 heads, 8 segments, by an earlier form of the shared way, 195 / 186, 64 333 / 229.)
+__device__ __forceinline__ float* parts_of(const TbeArgs& a, int seg) { return a.cent + (int64_t)seg * kTbeMaxKeep * a.dim; }
+// workgroups that share the products of a segment of n tokens: as many parts as there is room for (one at least)
 __device__ __forceinline__ int gram_slices(const TbeArgs& a, int n, int heads) {
-  if (n > kFewPoints && !a.wide) return 0;
-  int s = (int)(a.gram_room / tri(n));
-  s = s < kSlices ? s : kSlices;
-  return s < heads ? s : heads;
+  const int s = min(kTbeMaxKeep * a.dim / tri(n), kSlices);
+  return min(s, heads);
 }
 
 size_t tbe_ws_bytes(const thinkv_config& c, int n_tok, int n_seg) {
-  const int dim = c.n_kv_heads * c.head_dim;
-  const size_t toks = n_tok > 0 ? n_tok : 1, segs = n_seg > 0 ? n_seg : 1;
-  return (toks * dim + segs * kTbeMaxKeep * dim + (gram_in_centroids(dim) ? 0 : segs * kMaxGram)) * sizeof(float) +
-         toks * sizeof(int32_t) + 256;
+  const size_t dim = (size_t)c.n_kv_heads * c.head_dim, toks = n_tok > 0 ? n_tok : 1, segs = n_seg > 0 ? n_seg : 1;
+  return (toks * dim + segs * kTbeMaxKeep * dim) * sizeof(float) + toks * sizeof(int32_t) + 256;
 }
 
 // ---- a token's keys.  A unit is a chunk of a token's block (a kv-head, eight channels of every group); the four threads of
@@ -218,7 +215,7 @@ __device__ __forceinline__ void store_row(float* dst, const float (&x)[8]) {
 }
 
 // the binary32 rows of the tokens [from, to)
-template <int D, bool FP>
+template <int D, bool FP, int THREADS>
 __device__ __forceinline__ void write_rows(const thinkv_view& v, const TbeArgs& a, int from, int to, TokenAt* at) {
   const int per = 4 * v.cfg.n_kv_heads;
   for (; from < to; from += kTbeMaxTokens) {
@@ -226,7 +223,7 @@ __device__ __forceinline__ void write_rows(const thinkv_view& v, const TbeArgs& 
     __syncthreads();   // the tokens before have been used
     if ((int)threadIdx.x < count) at[threadIdx.x] = token_at(v, a, from + threadIdx.x);
     __syncthreads();
-    for (int idx = threadIdx.x; idx < count * per; idx += kGramThreads) {
+    for (int idx = threadIdx.x; idx < count * per; idx += THREADS) {
       const int i = idx / per, it = idx - i * per, hd = it >> 2, j = it & 3;
       const int bits = at[i].bits;
       RawKeys<D> r;
@@ -240,6 +237,17 @@ __device__ __forceinline__ void write_rows(const thinkv_view& v, const TbeArgs& 
       });
     }
   }
+}
+
+// ... and of share w of W of the tokens before the first segment and behind the last
+template <int D, bool FP, int THREADS>
+__device__ __forceinline__ void write_outside(const thinkv_view& v, const TbeArgs& a, int w, int W, TokenAt* at) {
+  const int lo = a.seg_offset[0], hi = a.seg_offset[a.n_seg];
+  const int before = lo < 0 ? 0 : (lo < a.n_tok ? lo : a.n_tok), behind = hi < 0 ? 0 : (hi < a.n_tok ? hi : a.n_tok);
+  const int all = before + a.n_tok - behind, part = (all + W - 1) / W;
+  const int from = w * part, to = from + part < all ? from + part : all, skip = behind - before;
+  write_rows<D, FP, THREADS>(v, a, from, to < before ? to : before, at);
+  write_rows<D, FP, THREADS>(v, a, (from > before ? from : before) + skip, to + skip, at);
 }
 
 // ---- gram
@@ -430,14 +438,9 @@ __device__ __forceinline__ bool seg_ok(const TbeArgs& a, int lo, int hi, int wan
 template <int D, bool FP, bool WIDE>
 __global__ __launch_bounds__(kGramThreads, 4) void tbe_gram_kernel(thinkv_view v, TbeArgs a) {
   __shared__ __attribute__((aligned(16))) GramScratch<WIDE ? kTbeMaxTokens : kFewPoints, 1> sm;
-  const int tid = threadIdx.x, outside = (int)blockIdx.x - a.n_seg * kSlices;
-  if (outside >= 0) {   // the last workgroups: tokens before the first segment and behind the last, a share each
-    const int lo = a.seg_offset[0], hi = a.seg_offset[a.n_seg];
-    const int before = lo < 0 ? 0 : (lo < a.n_tok ? lo : a.n_tok), behind = hi < 0 ? 0 : (hi < a.n_tok ? hi : a.n_tok);
-    const int all = before + a.n_tok - behind, part = (all + (int)gridDim.x - a.n_seg * kSlices - 1) / ((int)gridDim.x - a.n_seg * kSlices);
-    const int from = outside * part, to = from + part < all ? from + part : all, skip = behind - before;
-    write_rows<D, FP>(v, a, from, to < before ? to : before, sm.at);
-    write_rows<D, FP>(v, a, (from > before ? from : before) + skip, to + skip, sm.at);
+  const int outside = (int)blockIdx.x - a.n_seg * kSlices;
+  if (outside >= 0) {   // the last workgroups
+    write_outside<D, FP, kGramThreads>(v, a, outside, (int)gridDim.x - a.n_seg * kSlices, sm.at);
     return;
   }
   const int seg = blockIdx.x / kSlices, slice = blockIdx.x % kSlices;
@@ -445,13 +448,14 @@ __global__ __launch_bounds__(kGramThreads, 4) void tbe_gram_kernel(thinkv_view v
   if (n <= want || !seg_ok(a, lo, hi, want)) {   // not clustered: only the rows, a share for each of the segment's workgroups
     const int first = lo > 0 ? lo : 0, end = hi < a.n_tok ? hi : a.n_tok, part = (end - first + kSlices - 1) / kSlices;
     const int from = first + slice * part;
-    write_rows<D, FP>(v, a, from, from + part < end ? from + part : end, sm.at);
+    write_rows<D, FP, kGramThreads>(v, a, from, from + part < end ? from + part : end, sm.at);
     return;
   }
+  if (!WIDE && n > kFewPoints) return;   // tbe_whole_kernel's
   const int slices = gram_slices(a, n, H);
   if (slice >= slices) return;
   find_tokens(v, a, lo, n, sm.at);
-  float* out = a.gram + seg * a.gram_room + (int64_t)slice * tri(n);
+  float* out = parts_of(a, seg) + (int64_t)slice * tri(n);
   auto walk = [&](int first) {
     gram_matrix<D, FP, kGramWaves>(v, n, H * slice / slices, H * (slice + 1) / slices, first, sm, a.x + (int64_t)lo * a.dim, a.dim, [] {},
                                    [&](int p, int q, float d) { out[tri(p) + q] = d; });
@@ -737,6 +741,21 @@ __device__ __forceinline__ void choose_survivors(const TbeArgs& a, int seg, int 
   }
 }
 
+// A segment that is not clustered: outside what is covered, then nothing is evicted, and the caller is told; or everything survives
+template <int THREADS>
+__device__ __forceinline__ bool leave_alone(const thinkv_view& v, const TbeArgs& a, int lo, int hi, int want) {
+  const int n = hi - lo;
+  if (n <= 0) return true;
+  const bool ok = seg_ok(a, lo, hi, want);
+  if (ok && want < n) return false;
+  if (!ok && threadIdx.x == 0) atomicOr(&v.dev_status[v.cfg.max_seqs * v.cfg.n_layers], THINKV_ST_BAD_SEGMENT);
+  for (int i = threadIdx.x; i < n && lo >= 0 && lo + i < a.n_tok; i += THREADS) {
+    a.ev_handle[lo + i] = -1;
+    a.assign[lo + i] = -1;
+  }
+  return true;
+}
+
 // The parts of the matrix meet, in order (they lie where the centroids will: all have been read before those are written)
 template <int THREADS>
 __device__ __forceinline__ void add_parts(const float* parts, int slices, int n, float* gram) {
@@ -762,33 +781,20 @@ __device__ __forceinline__ void add_parts(const float* parts, int slices, int n,
 }
 
 __global__ __launch_bounds__(64 * kKmWaves) __attribute__((amdgpu_waves_per_eu(6))) void tbe_kmeans_kernel(thinkv_view v, TbeArgs a) {
-  constexpr int kThreads = 64 * kKmWaves;
-  const thinkv_config& c = v.cfg;
-  const int seg = blockIdx.x, tid = threadIdx.x;
-  const int lo = a.seg_offset[seg], hi = a.seg_offset[seg + 1];
-  const int n = hi - lo, want = a.seg_keep[seg];
-  if (n <= 0) return;
-  const bool ok = seg_ok(a, lo, hi, want);
-  if (!ok || want >= n) {
-    // outside what this kernel covers: nothing is evicted, and the caller is told; or everything survives
-    if (!ok && tid == 0) atomicOr(&v.dev_status[c.max_seqs * c.n_layers], THINKV_ST_BAD_SEGMENT);
-    for (int i = tid; i < n && lo >= 0 && lo + i < a.n_tok; i += kThreads) {
-      a.ev_handle[lo + i] = -1;
-      a.assign[lo + i] = -1;
-    }
-    return;
-  }
-  const int slices = gram_slices(a, n, c.n_kv_heads);
-  if (n > kFewPoints || slices == 0) return;
+  const int seg = blockIdx.x, lo = a.seg_offset[seg], hi = a.seg_offset[seg + 1], n = hi - lo, want = a.seg_keep[seg];
+  if (leave_alone<64 * kKmWaves>(v, a, lo, hi, want)) return;
+  if (n > kFewPoints) return;   // tbe_whole_kernel's, or tbe_wide_kernel's
   __shared__ __attribute__((aligned(16))) KmScratch<kKmWaves, kFewPoints> sm;
-  add_parts<kThreads>(a.gram + seg * a.gram_room, slices, n, sm.gram);
+  add_parts<64 * kKmWaves>(parts_of(a, seg), gram_slices(a, n, v.cfg.n_kv_heads), n, sm.gram);
   choose_survivors(a, seg, lo, n, want, sm);
 }
 
 // The segments that kmeans leaves out: a workgroup of sixteen waves, with the LDS of a whole compute unit, makes the matrix and iterates.
-// Where there are none, the launch is 5 us.  (A segment a lane to find them: the same 5 us, five more registers spilled.)
-template <int D, bool FP>
+// Where there are none, the launch is 5 us.  (A segment a lane to find them: the same 5 us, five more registers spilled.)  NARROW: it is the only
+// kernel, for all segments and for the rows of tokens that are not clustered.
+template <int D, bool FP, bool NARROW>
 __global__ __launch_bounds__(64 * kWholeWaves) void tbe_whole_kernel(thinkv_view v, TbeArgs a) {
+  constexpr int kThreads = 64 * kWholeWaves;
   __shared__ __attribute__((aligned(16))) union {
     GramScratch<kTbeMaxTokens, 2> tile;
     KmScratch<kWholeWaves, kTbeMaxTokens> km;
@@ -796,13 +802,21 @@ __global__ __launch_bounds__(64 * kWholeWaves) void tbe_whole_kernel(thinkv_view
   const int H = v.cfg.n_kv_heads;
   for (int seg = blockIdx.x; seg < a.n_seg; seg += gridDim.x) {
     const int lo = a.seg_offset[seg], hi = a.seg_offset[seg + 1], n = hi - lo, want = a.seg_keep[seg];
-    if (n <= want || !seg_ok(a, lo, hi, want) || gram_slices(a, n, H) > 0) continue;
+    if (NARROW) {
+      if (leave_alone<kThreads>(v, a, lo, hi, want)) {
+        write_rows<D, FP, kThreads>(v, a, lo > 0 ? lo : 0, hi < a.n_tok ? hi : a.n_tok, sm.tile.at);
+        continue;
+      }
+    } else if (n <= kFewPoints || !seg_ok(a, lo, hi, want)) {   // (nobody keeps so many)
+      continue;
+    }
     __syncthreads();   // the segment before is done
     find_tokens(v, a, lo, n, sm.tile.at);
     gram_matrix<D, FP, kWholeWaves>(v, n, 0, H, 0, sm.tile, a.x + (int64_t)lo * a.dim, a.dim, [] { __syncthreads(); },   // the matrix takes the tiles' place
                                     [&](int p, int q, float d) { sm.km.gram[tri(p) + q] = d; });
     choose_survivors(a, seg, lo, n, want, sm.km);
   }
+  if (NARROW) write_outside<D, FP, kThreads>(v, a, blockIdx.x, gridDim.x, sm.tile.at);
 }
 
 // ... or, wide, adds the parts that gram has made of it
@@ -810,27 +824,33 @@ __global__ __launch_bounds__(64 * kWholeWaves) void tbe_wide_kernel(thinkv_view 
   __shared__ __attribute__((aligned(16))) KmScratch<kWholeWaves, kTbeMaxTokens> sm;
   for (int seg = blockIdx.x; seg < a.n_seg; seg += gridDim.x) {
     const int lo = a.seg_offset[seg], hi = a.seg_offset[seg + 1], n = hi - lo, want = a.seg_keep[seg];
-    if (n <= kFewPoints || !seg_ok(a, lo, hi, want)) continue;   // (nobody keeps so many)
+    if (n <= kFewPoints || !seg_ok(a, lo, hi, want)) continue;
     __syncthreads();   // the segment before is done
-    add_parts<64 * kWholeWaves>(a.gram + seg * a.gram_room, gram_slices(a, n, v.cfg.n_kv_heads), n, sm.gram);
+    add_parts<64 * kWholeWaves>(parts_of(a, seg), gram_slices(a, n, v.cfg.n_kv_heads), n, sm.gram);
     choose_survivors(a, seg, lo, n, want, sm);
   }
 }
-static_assert(kTbeMaxKeep <= kFewPoints, "tbe_wide_kernel");
+static_assert(kTbeMaxKeep <= kFewPoints, "a segment that tbe_whole_kernel or tbe_wide_kernel takes is cut");
 
 template <int D, bool FP>
 static void launch_kernels(const thinkv_view& v, const TbeArgs& a, hipStream_t st) {
   // Tokens outside every segment: 64 to a workgroup, 256 workgroups at most (32k such tokens behind 32
   // segments: by four workgroups 987 us a call, by a kernel of its own for the rows of all tokens 101, now 72).
-  const int outside = (a.n_tok + 63) / 64, most = a.n_tok < kTbeMaxTokens ? a.n_tok : kTbeMaxTokens;
-  const dim3 grid(a.n_seg * kSlices + (outside < 256 ? outside : 256));
-  if (a.wide) hipLaunchKernelGGL((tbe_gram_kernel<D, FP, true>), grid, dim3(kGramThreads), 0, st, v, a);
+  const int outside = (a.n_tok + 63) / 64;
+  const int shares = outside < 256 ? outside : 256;
+  const dim3 whole(64 * kWholeWaves);
+  if (is_narrow(a.dim)) {
+    hipLaunchKernelGGL((tbe_whole_kernel<D, FP, true>), dim3(a.n_seg > shares ? a.n_seg : shares), whole, 0, st, v, a);
+    return;
+  }
+  const dim3 grid(a.n_seg * kSlices + shares);
+  if (is_wide(a.dim, a.n_seg)) hipLaunchKernelGGL((tbe_gram_kernel<D, FP, true>), grid, dim3(kGramThreads), 0, st, v, a);
   else hipLaunchKernelGGL((tbe_gram_kernel<D, FP, false>), grid, dim3(kGramThreads), 0, st, v, a);
   hipLaunchKernelGGL(tbe_kmeans_kernel, dim3(a.n_seg), dim3(64 * kKmWaves), 0, st, v, a);
-  if (most <= kFewPoints && tri(most) <= a.gram_room) return;   // (no segment can be left out)
-  const dim3 units(a.n_seg < 256 ? a.n_seg : 256), whole(64 * kWholeWaves);   // they go round the segments
-  if (a.wide) hipLaunchKernelGGL(tbe_wide_kernel, units, whole, 0, st, v, a);
-  else hipLaunchKernelGGL((tbe_whole_kernel<D, FP>), units, whole, 0, st, v, a);
+  if (a.n_tok <= kFewPoints) return;   // (no segment can be larger)
+  const dim3 units(a.n_seg < 256 ? a.n_seg : 256);   // they go round the segments
+  if (is_wide(a.dim, a.n_seg)) hipLaunchKernelGGL(tbe_wide_kernel, units, whole, 0, st, v, a);
+  else hipLaunchKernelGGL((tbe_whole_kernel<D, FP, false>), units, whole, 0, st, v, a);
 }
 
 int launch_tbe_select(const thinkv_view& v, int layer, const int32_t* tok_seq, const int32_t* tok_handle, const int32_t* seg_offset,
@@ -846,14 +866,10 @@ int launch_tbe_select(const thinkv_view& v, int layer, const int32_t* tok_seq, c
   a.x = (float*)(((uintptr_t)workspace + 255) & ~(uintptr_t)255);
   a.cent = a.x + (size_t)n_tok * a.dim;
   a.assign = (int32_t*)(a.cent + (size_t)n_seg * kTbeMaxKeep * a.dim);
-  const bool inside = gram_in_centroids(a.dim);
-  a.gram = inside ? a.cent : (float*)(a.assign + n_tok);
-  a.gram_room = inside ? (int64_t)kTbeMaxKeep * a.dim : kMaxGram;
   a.layer = layer;
   a.n_seg = n_seg;
   a.n_tok = n_tok;
   a.max_iters = max_iters;
-  a.wide = a.dim >= 4096 && n_seg <= 128;   // (512 gram workgroups fill the machine)
   const bool fp = v.cfg.format == THINKV_FMT_FP;
   if (v.cfg.head_dim == 128)
     fp ? launch_kernels<128, true>(v, a, st) : launch_kernels<128, false>(v, a, st);

@@ -42,6 +42,15 @@ def test_layout_queries_match_the_stated_formula(lib):
     assert B.thinkv_decode_workspace_bytes(cfg, 3, 100) >= 3 * 8 * (128 + 2) * 4
 
 
+@pytest.mark.parametrize("heads,D", [(1, 64), (2, 64), (2, 128), (7, 64), (4, 128), (8, 128), (16, 128), (32, 128)])
+def test_survivor_choice_asks_for_what_it_leaves_in_the_workspace(lib, heads, D):
+    """keys, centroids and clusters, and nothing for the kernels' own use: programs hold workspaces of that size"""
+    from paper_2510_01290_amd import binding as B
+    cfg = B.make_config(1, heads, heads, D, (8, 2, 4), 4, 16)
+    for n_tok, n_seg in [(1, 1), (700, 3), (40000, 400)]:
+        assert lib.thinkv_tbe_workspace_bytes(C.byref(cfg), n_tok, n_seg) == 4 * (n_tok * heads * D + n_seg * 64 * heads * D + n_tok) + 256
+
+
 def test_host_side_argument_errors(lib):
     from paper_2510_01290_amd import binding as B
     assert lib.thinkv_init_view(None, None) == 1

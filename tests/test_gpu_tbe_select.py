@@ -1,5 +1,5 @@
-"""Survivor choice at the edges of its kernels: one to four workgroups to a segment's products (head counts, segment sizes and
-the room for the parts), rows at tile edges and behind the part of the matrix that LDS holds (192 points), tokens outside every
+"""Survivor choice at the edges of its kernels: one to four workgroups to a segment's products, or a kernel that does it all (head counts, segment sizes and
+the room for the parts), rows at tile edges, segments larger than half a compute unit holds (192 points), tokens outside every
 segment, both number formats.  Keys, the last Lloyd step and the survivors as in test_gpu_tbe, against the oracle's keys."""
 import numpy as np
 import pytest
@@ -78,6 +78,38 @@ def test_a_key_that_is_no_number_spoils_its_own_cluster_only():
         assert (got[assign == j] == -1).sum() == 1
     fine = [j for j in range(1, 12) if (assign == j).any()]
     assert len(fine) >= 6 and np.isfinite(cent[0, fine]).all()
+
+
+@pytest.mark.parametrize("heads,D", [(1, 64), (2, 64), (1, 128), (7, 64), (8, 64), (9, 64), (8, 128), (32, 128)])
+def test_the_smallest_workspace_is_enough(heads, D):
+    """keys, centroids, clusters and 256 bytes, at an address that is no multiple of 256; what lies around it is left alone"""
+    print("the smallest workspace", heads, D, flush=True)
+    import ctypes as C
+    from paper_2510_01290_amd import binding as B
+    sizes, keeps = [256, 192, 193, 100, 30], [64, 64, 33, 16, 4]
+    n, n_seg = sum(sizes), len(sizes)
+    geom = synth.Geometry(1, heads, heads, D, "f16", (8, 2, 4))
+    wl = synth.bulk_evict_refill("tbe-ws", geom, 66, 1, np.array([n]), {}, refill=0)
+    gc = parity.make_gpu_cache(wl)
+    gr = synth.ScriptRunner(wl, parity.GpuBackend(gc)).run()
+    th = np.array([int(h) for h in gr.handle[(0, 0)][:n]], np.int32)
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    want, x, cent, assign = _gpu_select(gc, 0, np.zeros(n, np.int32), th, off, np.array(keeps, np.int32), inspect=True)
+    size = 4 * (n * heads * D + n_seg * 64 * heads * D + n) + 256
+    buf = torch.full((size + 1024,), 0x5A, dtype=torch.uint8, device=gc.device)
+    assert buf.data_ptr() % 256 == 0
+    args = [torch.from_numpy(a).to(gc.device) for a in (np.zeros(n, np.int32), th, off, np.array(keeps, np.int32))]
+    ev = torch.empty(n, dtype=torch.int32, device=gc.device)
+    call = lambda nb: B.load().thinkv_tbe_select(C.byref(gc.view), 0, *[a.data_ptr() for a in args], n_seg, n, 8, ev.data_ptr(), buf.data_ptr() + 16, nb, None)  # noqa: E731
+    assert call(size - 1) == 4                                       # too small
+    torch.cuda.synchronize()
+    assert (buf == 0x5A).all()
+    assert call(size) == 0
+    torch.cuda.synchronize()
+    assert (buf[:16] == 0x5A).all() and (buf[16 + size:] == 0x5A).all()
+    assert np.array_equal(ev.cpu().numpy(), want)
+    f = buf[256:256 + 4 * (n * heads * D)].view(torch.float32).view(n, -1).cpu().numpy()
+    assert np.array_equal(f.astype(np.float64), x)
 
 
 @pytest.mark.parametrize("before,behind", [(0, 0), (0, 1), (3, 0), (65, 900), (1300, 2), (700, 700)])
