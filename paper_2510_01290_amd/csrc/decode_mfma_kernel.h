@@ -321,11 +321,14 @@ __device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)"
 // The page pairs an item works on, as one wave sees them.  The item's share of the three page lists is cut into chunks of
 // 2^shift consecutive pairs, type after type; chunk numbers come from the workgroup's ticket counter.  The ids and
 // masks of the pair after the one just taken are on their way by scalar loads (no traffic in the vector-memory queue).
-// With a whole compute unit's waves to an item at head_dim 128, integer formats, a chunk is one pair: neighbouring waves then
-// read neighbouring pages, and no wave is left
-// with a whole chunk at the end (pairs by fours: 16 x 32k tokens 136.1 us a step, now 133.8, 32 x ~2k of scrambled slots 46.5
-// and 44.9, 16 x 8k 43.1 and 42.5).  Elsewhere a draw a pair costs more than it brings (256 x 1k..64k 837 us by fours, 856 by ones;
-// head_dim 64, 128 x 4k..32k 268 and 272; the paper's formats no difference).
+// Where an item has all the waves of a compute unit and kFinePages pages or more for each of them (head_dim 128, integer formats), a chunk is
+// one pair: neighbouring waves then read neighbouring pages, and no wave is left with a whole chunk at the end.  Pairs by fours / by ones, us:
+// 33 pages a wave: 16 x 8k tokens 40.1 / 39.5, 24 x 4k 34.9 / 32.8, 32 x ~2k of scrambled slots 46.5 / 44.9.  With fewer pages a wave's loads
+// of its one to four chunks follow each other closer than draws do: 4 pages, 1 x 8k 18.7 / 20.9; 8, 1 x 32k 23.2 / 24.8, 8 x 4k 19.5 / 21.3; 16, 2 x 32k 28.5 / 29.3, 8 x 8k
+// 26.6 / 27.4, 16 x 4k 27.0 / 28.0.  Where waves share out a unit among several items there is nobody to balance with (28 x 3.2k..32k, 40 heads, 88.2 / 90.8), with
+// the statistic the draws' scalars are spilled (16 x 32k, 64 heads, 153 either way, 32 x 16k 150 / 154), and elsewhere a draw a pair costs more than it brings (256 x 1k..64k 837 us
+// by fours, 856 by ones; head_dim 64, 128 x 4k..32k 268 and 272; the paper's formats no difference).
+constexpr int kFinePages = 20;
 constexpr int kChunkShift = 2;
 constexpr int kTicketBytes = 64;   // a counter for each of up to sixteen items, behind the rings
 typedef const int32_t __attribute__((address_space(4))) * ConstI32;   // read-only for the whole launch: scalar loads
@@ -1088,7 +1091,7 @@ __global__ __launch_bounds__(256 * decode_waves_per_simd(D, FP)) __attribute__((
   const int group = whole(wave, wph), wave0 = group * wph;
   const int b = it.b, hkv = it.hkv, share_n = it.n > 0 ? it.n : 1;
   const bool valid = seq >= 0 && seq < c.max_seqs;
-  constexpr bool kFine = D == 128 && !FP;
+  constexpr bool kFine = D == 128 && !FP && !STAT;
   using Pairs = Stream<kFine>;
   Pairs q;
   const uint32_t base = lds_address(tkv_lds);
@@ -1104,7 +1107,7 @@ __global__ __launch_bounds__(256 * decode_waves_per_simd(D, FP)) __attribute__((
   q.kind0 = rot;
   q.kind1 = rot + 1 < 3 ? rot + 1 : rot - 2;
   q.kind2 = rot + 2 < 3 ? rot + 2 : rot - 1;
-  q.fine = kFine && W == kFull ? 0 : kChunkShift;
+  q.fine = kFine && wph == kFull && np[0] + np[1] + np[2] >= kFinePages * kFull * share_n ? 0 : kChunkShift;
   q.cum0 = q.share(Pairs::pick(q.kind0, np[0], np[1], np[2]), it.j, share_n, q.first0, q.end0);
   q.cum1 = q.cum0 + q.share(Pairs::pick(q.kind1, np[0], np[1], np[2]), it.j, share_n, q.first1, q.end1);
   q.cum2 = q.cum1 + q.share(Pairs::pick(q.kind2, np[0], np[1], np[2]), it.j, share_n, q.first2, q.end2);

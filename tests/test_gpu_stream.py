@@ -91,6 +91,8 @@ def _close(o, l, ro, rl):
     (128, 4, 8, [300] * 66 + [20000], 0, (8, 2, 4), 0.1),
     (64, 8, 8, [1500] * 128, 0, (8, 2, 4), 0.0),               # ... of one item each
     (128, 4, 8, [300] * 40, 0, (8, 2, 4), 0.5),
+    (128, 4, 8, [2300 + 25 * i for i in range(24)], 0, (8, 2, 4), 0.1),   # a workgroup a head, 150 to 190 pages: chunks of one pair and of four
+    (128, 5, 8, [700 + 2100 * (i % 5) for i in range(19)], 0, (8, 2, 4), 0.0),   # ... dealt, several items to a workgroup and several to a head
 ], ids=lambda x: str(x)[:24].replace(" ", ""))
 def test_stream_kernel_against_the_plain_kernel(D, G, H, ctx, fmt, bits, dead):
     print("stream:", D, G, H, len(ctx), max(ctx), fmt, bits, dead, flush=True)
