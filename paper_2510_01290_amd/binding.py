@@ -97,10 +97,18 @@ def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
+# The current stream as a plain number, without the Stream object that torch.cuda.current_stream() makes: a decode step of one short sequence is two
+# calls and bound by the host, 25.5 us with two such objects, 21.9 without.  Not part of torch's documented interface: where a
+# version of torch has no such function, the documented way.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream):
-    # the current device's current stream, as torch.cuda.current_stream() finds it, without the Stream object that takes 2.9 us
-    # to make: a decode step of one short sequence is two calls and was bound by the host (26 us a step, now 20)
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()) if stream is None else stream.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 FMT_INT, FMT_FP = 0, 1

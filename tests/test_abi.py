@@ -51,6 +51,26 @@ def test_survivor_choice_asks_for_what_it_leaves_in_the_workspace(lib, heads, D)
         assert lib.thinkv_tbe_workspace_bytes(C.byref(cfg), n_tok, n_seg) == 4 * (n_tok * heads * D + n_seg * 64 * heads * D + n_tok) + 256
 
 
+@pytest.mark.parametrize("raw", [True, False])
+def test_the_current_stream_with_and_without_torchs_raw_query(monkeypatch, raw):
+    import importlib.util
+    import types
+    import torch
+    from paper_2510_01290_amd import binding
+    name = "_cuda_getCurrentRawStream"
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=0x1234))
+    if raw:
+        monkeypatch.setattr(torch._C, name, lambda device: 0x5678 + device, raising=False)
+    else:
+        monkeypatch.delattr(torch._C, name, raising=False)
+    spec = importlib.util.spec_from_file_location("binding_under_test", binding.__file__)
+    b = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(b)
+    assert b._stream(None) == (0x567B if raw else 0x1234)
+    assert b._stream(types.SimpleNamespace(cuda_stream=77)) == 77
+
+
 def test_host_side_argument_errors(lib):
     from paper_2510_01290_amd import binding as B
     assert lib.thinkv_init_view(None, None) == 1
