@@ -28,9 +28,11 @@ __global__ __launch_bounds__(256) void stat_fill_kernel(float4* p, int64_t n4) {
 // negligible entries; the row's fraction negligible / visible (0 where nothing is visible) goes
 // to frac[b][kv-head].  Rows are read 16 bytes a lane, once up to 32,768 entries.  MASKS: entries of pages without a live
 // slot were not written and count as -inf.
+// Two workgroups share a compute unit, so a thread has 64 registers: indices are scalars or 32 bits wide.  (With 66 there was one: 256 x 1k tokens, 8
+// kv-heads of 128, 130.4 us, now 113.7; 256 x 500..5k 206 and 190; two launches without that 117 and 195.)
 constexpr int kKept = 8;
 template <int D, bool MASKS>
-__global__ __launch_bounds__(1024) void stat_count_kernel(thinkv_view v, DecodeArgs a, float* frac, int merges) {
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void stat_count_kernel(thinkv_view v, DecodeArgs a, float* frac, int merges) {
   const thinkv_config& c = v.cfg;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   __shared__ MergeLds<D> s_merge[1024 / D];
@@ -41,14 +43,14 @@ __global__ __launch_bounds__(1024) void stat_count_kernel(thinkv_view v, DecodeA
     merge_head<D>(v, a, hd / c.n_q_heads, hd % c.n_q_heads, tid % D, head < heads, s_merge[tid / D]);
     return;
   }
-  const int b = ((int)blockIdx.x - merges) / c.n_kv_heads, hkv = (int)blockIdx.x - merges - b * c.n_kv_heads;
-  const int seq = a.seq_ids[b];
+  const int b = uniform(((int)blockIdx.x - merges) / c.n_kv_heads), hkv = (int)blockIdx.x - merges - b * c.n_kv_heads;
+  const int seq = uniform(a.seq_ids[b]);
   int64_t n = 0;
   int end0 = 0, end1 = 0;   // where the pages of the first two types end
   if (seq >= 0 && seq < c.max_seqs) {
-    end0 = v.n_pages[npages_index(c, seq, a.layer, 0)];
-    end1 = end0 + v.n_pages[npages_index(c, seq, a.layer, 1)];
-    n = (int64_t)end1 + v.n_pages[npages_index(c, seq, a.layer, 2)];
+    end0 = uniform(v.n_pages[npages_index(c, seq, a.layer, 0)]);
+    end1 = end0 + uniform(v.n_pages[npages_index(c, seq, a.layer, 1)]);
+    n = (int64_t)end1 + uniform(v.n_pages[npages_index(c, seq, a.layer, 2)]);
   }
   n *= kPage;
   if (n > a.stat_stride) n = a.stat_stride;   // the host's bound on the context was too small: count what was kept
@@ -59,7 +61,7 @@ __global__ __launch_bounds__(1024) void stat_count_kernel(thinkv_view v, DecodeA
     float4 x = row[i];
     if (MASKS && n4 > 0) {
       const int p = i >> 2;   // the types' page lists lie max_pages apart
-      const uint32_t m = masks[p < end0 ? p : (p < end1 ? p - end0 + c.max_pages : p - end1 + 2 * (int64_t)c.max_pages)];
+      const uint32_t m = masks[(uint32_t)(p < end0 ? p : (p < end1 ? p - end0 + c.max_pages : p - end1 + 2 * c.max_pages))];   // (max_pages < 2^24)
       if ((m & 0xFFFFu) == 0) x = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
     }
     return x;
