@@ -26,7 +26,7 @@
 // whole: segments of more tokens (a matrix of up to 132 KB), a workgroup per compute unit that does both; and, alone, all segments of up to 512
 // channels.
 // 314 segments of ~110 tokens, 1,024 channels, us: keys to memory and a workgroup of a whole compute unit per segment (its
-// 139 KB of LDS made that 1.2 rounds of workgroups) 37 + 177; now 67 + 74 (and 5 for whole, which finds nothing).  gram is bound by vector
+// 139 KB of LDS made that 1.2 rounds of workgroups) 37 + 177; now 67 + 74 (and 6 for whole, which finds nothing).  gram is bound by vector
 // instructions (four a number to unpack and split it) and by 141 MB of rows; kmeans by chains from the lists of members to LDS and
 // back (20 us around the first assignment, 1.5 to 4 for every further one), the parts (10) and the 54 MB of centroids (20).
 // The products run on the matrix cores; a dequantised key does not
@@ -59,7 +59,9 @@ struct TbeArgs {
 
 constexpr int kGramThreads = 512;         // eight waves, two workgroups a compute unit
 constexpr int kGramWaves = kGramThreads / 64;
-constexpr int kSlices = 4;                // workgroups that share a segment's channels at most: with one, the units that get two segments end last (110 us)
+// Workgroups that share a segment's channels at most.  8 heads of 128, us by two / three / four: 1 segment of 110 tokens 45.6 / 42.3 / 38.6, an eviction event of
+// 314 segments 204 / 202 / 203, 2,000 of 64 to 192 795 / 825 / 877 (by one, 314: the units that get two segments end last, the kernel 110 instead of 67).
+constexpr int kSlices = 4;
 constexpr int kMacro = 32;                // points on a side of a wave's piece of the Gram matrix (2 x 2 MFMA tiles)
 constexpr int kPiecesPerWave = 3;         // 24 pieces of the lower triangle, all of 192 points, by eight waves; 36, all of 256, by sixteen
 constexpr int kFewPoints = 192;           // points of the largest segment that takes half a compute unit
@@ -790,7 +792,7 @@ __global__ __launch_bounds__(64 * kKmWaves) __attribute__((amdgpu_waves_per_eu(6
 }
 
 // The segments that kmeans leaves out: a workgroup of sixteen waves, with the LDS of a whole compute unit, makes the matrix and iterates.
-// Where there are none, the launch is 5 us.  (A segment a lane to find them: the same 5 us, five more registers spilled.)  NARROW: it is the only
+// Where there are none, the launch is 6 us.  (A segment a lane to find them: no less, and five more registers spilled.)  NARROW: it is the only
 // kernel, for all segments and for the rows of tokens that are not clustered.
 template <int D, bool FP, bool NARROW>
 __global__ __launch_bounds__(64 * kWholeWaves) void tbe_whole_kernel(thinkv_view v, TbeArgs a) {
