@@ -112,11 +112,12 @@ def test_the_smallest_workspace_is_enough(heads, D):
     assert np.array_equal(f.astype(np.float64), x)
 
 
+@pytest.mark.parametrize("heads", [3, 9])                             # one kernel that does it all, and three
 @pytest.mark.parametrize("before,behind", [(0, 0), (0, 1), (3, 0), (65, 900), (1300, 2), (700, 700)])
-def test_rows_of_tokens_that_are_not_clustered(before, behind):
+def test_rows_of_tokens_that_are_not_clustered(before, behind, heads):
     """tokens before, behind and in segments that keep all they have or are too large: their rows are written, each once"""
-    print("rows outside", before, behind, flush=True)
-    geom = synth.Geometry(1, 3, 3, 64, "f16", (8, 2, 4))
+    print("rows outside", before, behind, heads, flush=True)
+    geom = synth.Geometry(1, heads, heads, 64, "f16", (8, 2, 4))
     sizes, keeps = [3, 64, 300, 20, 1, 7], [8, 64, 64, 9, 1, 64]
     total = before + sum(sizes) + behind
     wl = synth.bulk_evict_refill("tbe-rows", geom, 65, 1, np.array([total]), {}, refill=0)
@@ -125,7 +126,7 @@ def test_rows_of_tokens_that_are_not_clustered(before, behind):
     synth.ScriptRunner(wl, ob).run()
     th = np.array([int(h) for h in gr.handle[(0, 0)][:total]], np.int32)
     off = (before + np.concatenate([[0], np.cumsum(sizes)])).astype(np.int32)
-    gc.workspace(1 << 22).fill_(0x7F)
+    gc.workspace(1 << 23).fill_(0x7F)
     got, x, _, assign = _gpu_select(gc, 0, np.zeros(total, np.int32), th, off, np.array(keeps, np.int32), inspect=True)
     stored = otbe.segment_keys(ob.cache, 0, 0, th)
     assert np.abs(x - stored).max() <= 1e-6 * np.abs(stored).max()
@@ -135,12 +136,12 @@ def test_rows_of_tokens_that_are_not_clustered(before, behind):
     assert (got[before:off[-1]][~clustered[before:off[-1]]] == -1).all() and (got[clustered] == -1).sum() <= 9
 
 
-@pytest.mark.parametrize("fmt,D", [("int", 64), ("int", 128), ("fp", 64), ("fp", 128)])
-def test_a_token_that_does_not_exist_is_the_origin(fmt, D):
+@pytest.mark.parametrize("fmt,heads,D", [("int", 3, 64), ("int", 5, 128), ("fp", 9, 64), ("fp", 3, 128)])
+def test_a_token_that_does_not_exist_is_the_origin(fmt, heads, D):
     """handles that name no page, inside a clustered segment whose size is no multiple of a tile and behind it: rows of zeros, flagged"""
-    print("tokens that do not exist", fmt, D, flush=True)
+    print("tokens that do not exist", fmt, heads, D, flush=True)
     from paper_2510_01290_amd import binding as B
-    geom = synth.Geometry(1, 3, 3, D, "f16", (2, 4, 8), fmt)
+    geom = synth.Geometry(1, heads, heads, D, "f16", (2, 4, 8), fmt)
     wl = synth.bulk_evict_refill("tbe-none", geom, 64, 1, np.array([120]), {}, refill=0)
     gc = parity.make_gpu_cache(wl)
     gr = synth.ScriptRunner(wl, parity.GpuBackend(gc)).run()
