@@ -167,18 +167,19 @@ static ItemSizing size_stream(const thinkv_config& c, int B, int max_ctx_pages, 
   return z;
 }
 
-// Sliding-window layers of the fast kernel: an item is a workgroup of eight waves that scans the page lists for hg kv-heads and
-// attends what is visible with 8 / hg waves a head.  As many heads to a workgroup as leave a workgroup for every compute
+// Sliding-window layers of the fast kernel: an item is a workgroup of all the waves of a compute unit that scans the page lists for hg kv-heads and
+// attends what is visible with an hg-th of its waves a head.  As many heads to a workgroup as leave a workgroup for every compute
 // unit (fewer repeated scans), and, where even one head a workgroup does not, several items to a head.  How many follows from the
 // two things an item spends its time on.  What is visible: the window's tokens lie in as few pages as hold them, or, where they
 // took freed slots, in a page each, so above 512 tokens an item per 128 of them (2 x 8 heads, 16k tokens, window 1,024, a third
-// of the slots reused: 38.5 us with an item per 512 tokens, 27.7 per 256, 21.9 per 128; all in fresh pages 19.4, 19.3, 20.0).
+// of the slots reused, when whole pages were attended: 38.5 us with an item per 512 tokens, 27.7 per 256, 21.9 per 128; all in fresh pages 19.4,
+// 19.3, 20.0).
 // And the scan: above 6,144 pages an item per 2,048 of them (8 x 8 heads, window 128: 131k tokens 24.1 us with one item, now 17.8,
 // 262k 35.0 and 22.1; below, the merge launch costs what the shorter scan gains).
 static ItemSizing size_window(const thinkv_config& c, int B, int max_ctx_pages, int window, int* heads_per_group) {
   const int64_t heads = (int64_t)B * c.n_kv_heads, cus = compute_units();
   int hg = 1;
-  while (hg < kWindowWaves && 2 * hg <= c.n_kv_heads && heads >= 2 * hg * cus) hg *= 2;
+  while (2 * hg <= window_waves(c.head_dim) && 2 * hg <= c.n_kv_heads && heads >= 2 * hg * cus) hg *= 2;
   const int64_t groups = (int64_t)B * ((c.n_kv_heads + hg - 1) / hg);
   const int64_t pages = max_ctx_pages > 0 ? max_ctx_pages : 1;
   int64_t per_head = cus / groups;

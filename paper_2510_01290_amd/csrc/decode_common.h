@@ -28,11 +28,15 @@ __host__ __device__ constexpr int exchange_bytes(int head_dim, int heads, bool f
   return (fp ? head_dim == 128 : head_dim == 64 && heads == 8) ? 2 * 16 * heads * 4 : 0;
 }
 
-// Sliding-window layers: waves of a workgroup, pages of each type it scans at a time, its rings and all its LDS (the rings,
-// then per type the ids, masks and list positions of the visible pages, then their counts per wave).
-constexpr int kWindowWaves = 8, kWindowBlock = 64 * kWindowWaves;
+// Sliding-window layers: waves of a workgroup (as many as a compute unit holds; a page of each type per thread is scanned at a time), entries
+// of a type's list of what is visible, a wave's ring, and all LDS (rings, the lists' page ids, with the statistic list positions, and their
+// masks, counts per wave).
+constexpr int kWindowList = 1024;
+__host__ __device__ constexpr int window_waves(int head_dim) { return 4 * decode_waves_per_simd(head_dim, false); }
 __host__ __device__ constexpr int window_ring_bytes(int head_dim) { return head_dim == 128 ? 14336 : 9216; }
-__host__ __device__ constexpr int window_lds_bytes(int head_dim) { return kWindowWaves * window_ring_bytes(head_dim) + 9 * kWindowBlock * 4 + 3 * kWindowWaves * 4; }
+__host__ __device__ constexpr int window_lds_bytes(int head_dim, bool stat) {
+  return window_waves(head_dim) * window_ring_bytes(head_dim) + 3 * kWindowList * (stat ? 10 : 6) + 64;
+}
 
 // Items dealt over a batch (deal_item): fewest pages a wave is worth.
 constexpr int kDealPages = 8;

@@ -228,7 +228,8 @@ struct ClassRunnerFp {
   }
 
   float sa[NS], sb[NS];   // scores of the pair at hand
-  __device__ __forceinline__ void scores(const Pair& r, const PairIds& id) {
+  template <class Ids>
+  __device__ __forceinline__ void scores(const Pair& r, const Ids& id) {
     page_scores(r.a, sa);
     page_scores(r.b, sb);
     sm.mask(sa, sb, id);

@@ -47,8 +47,10 @@
 // 128 x 4k..32k 313 -> 287.  Three waves a SIMD with rings of 12 KB (one pair of 8-bit pages) lose to two with 18 KB:
 // 16 x 8k 64 us, 256 x 1k..64k 1,046 us.
 // Sliding-window layers (decode_window_kernel): a workgroup scans the page lists for several kv-heads, then its waves attend
-// the visible pages through the same rings.
+// what is visible through the same rings.
 #pragma once
+#include <type_traits>
+
 #include "decode_common.h"
 
 
@@ -260,6 +262,16 @@ struct PairIds {
   int pid_a, pid_b;
   uint32_t live_a, live_b;
   int idx_a, idx_b;   // positions in the type's page list (idx_b = -1: no second page); used by STAT only
+  // STAT: where the lane's tokens stand in the type's pooled scores (negative: nowhere)
+  __device__ __forceinline__ int place_a(int lane) const { return idx_a * kPage + (lane & (kPage - 1)); }
+  __device__ __forceinline__ int place_b(int lane) const { return idx_b < 0 ? -1 : idx_b * kPage + (lane & (kPage - 1)); }
+};
+// ... of a pair whose "pages" are made of quads of slots (SlotQuads)
+struct QuadIds {
+  uint32_t live_a, live_b;
+  int at_a, at_b;
+  __device__ __forceinline__ int place_a(int) const { return at_a; }
+  __device__ __forceinline__ int place_b(int) const { return at_b; }
 };
 
 template <int D, int BITS, int NSET>
@@ -490,26 +502,141 @@ __device__ __forceinline__ void stream_pairs(Runner& run, Source& q, const think
   }
 }
 
-// Sliding-window layers: the pages of one type with a visible slot, as the workgroup's scan left them in LDS; a wave takes
-// pairs i, i + step, ...
+// Sliding-window layers, the paper's formats: pages of one type with a visible slot, as the workgroup's scan left them in LDS; a wave takes
+// the pairs i, i + step, ... before end.
+typedef __attribute__((address_space(3))) const int32_t* LdsWords;
+typedef __attribute__((address_space(3))) const uint16_t* LdsHalves;
+template <bool STAT>
 struct VisiblePages {
-  typedef __attribute__((address_space(3))) const int32_t* Words;
-  Words pid, msk, idx;
-  int n, i, step;
+  static constexpr int kPair = 2;   // entries of a pair
+  LdsWords pid, idx;
+  LdsHalves msk;
+  int n, i, end, step;
   __device__ __forceinline__ bool next(PairIds& id) const {
-    if (2 * i >= n) return false;
+    if (i >= end) return false;
     const int a = 2 * i, b = min(a + 1, n - 1);
     const int two = b - a;
     id.pid_a = uniform(pid[a]);
     id.pid_b = uniform(pid[b]);
     id.live_a = (uint32_t)uniform(msk[a]);
     id.live_b = (uint32_t)(uniform(msk[b]) & (0 - two));
-    id.idx_a = uniform(idx[a]);
-    id.idx_b = two ? uniform(idx[b]) : -1;
+    if constexpr (STAT) {
+      id.idx_a = uniform(idx[a]);
+      id.idx_b = two ? uniform(idx[b]) : -1;
+    }
     return true;
   }
   __device__ __forceinline__ void look() { i += step; }
 };
+
+// Sliding-window layers, integer formats.  Where slots are reused in place, the window's tokens lie a few to a page, all over the lists, and
+// a page costs the same arithmetic however few of its slots are visible.  So the scan lists quads of slots (4 q .. 4 q + 3 of a page: a
+// lane of the value product holds one) with a visible slot, and a pair's two "pages" are put together in LDS from any eight of them: a
+// block's regions are made of 16-byte units of one quad each, and a direct load to LDS takes an address from every lane.
+template <bool STAT>
+struct SlotQuads {
+  static constexpr int kPair = 8;
+  LdsWords pid, idx;   // page << 2 | quad (a page number has far fewer than thirty bits: pages of 768 bytes and more); list positions
+  LdsHalves msk;       // visible slots of the quad
+  int n, i, end, step;
+};
+
+// Unit u (16 bytes) of a block, u = 64 op + lane: the quad of the "page" it belongs to, and where it lies in the block of the page that the
+// quad comes from: at + quad there << shift.  In one register: quad | shift << 2 | at << 8.
+template <int D, int BITS>
+__device__ __forceinline__ int quad_unit(int u) {
+  constexpr int CB = block_geom(BITS, D).chunk_bytes, kCodes = 4 * CB, kMeta = D / 32 * 4;   // units of a code and of a meta region
+  constexpr int kLog = (BITS == 2 ? 1 : (BITS == 4 ? 2 : 3)) + (D == 128 ? 2 : 1);           // of CB
+  const int r = u < kCodes + kMeta ? u : u - kCodes - kMeta;   // inside the half of keys or of values
+  int quad, shift;
+  if (r >= kCodes) {          // unit 4 group + quad
+    quad = (r - kCodes) & 3;
+    shift = 4;
+  } else if (u < kCodes) {    // chunk 16 j + slot
+    quad = r >> (kLog - 2) & 3;
+    shift = kLog + 2;
+  } else {                    // chunk 16 quad + c
+    quad = r >> kLog;
+    shift = kLog + 4;
+  }
+  return quad | shift << 2 | (16 * u - (quad << shift)) << 8;
+}
+
+// The pairs of quads i .. end - 1, through the wave's ring like stream_pairs
+template <int RING, class Runner, class Quads>
+__device__ __forceinline__ void quad_pairs(Runner& run, Quads& q, const thinkv_view& v, int cls, int hkv, uint32_t ring) {
+  constexpr int kUnits = Runner::kBlockBytes / 16, kPageOps = (kUnits + 63) / 64, kRest = kUnits % 64, kOps = 2 * kPageOps;
+  constexpr int kPairBytes = 2 * Runner::kBlockBytes;
+  constexpr int kSlots = RING / kPairBytes;
+  static_assert(kSlots >= 1 && (kSlots - 1) * kOps < 64 && Runner::kBlockBytes % 16 == 0, "the ring holds a pair, the waits six bits");
+  const int lane = run.lane;
+  const uint32_t page_bytes = __builtin_amdgcn_readfirstlane(v.cfg.n_kv_heads * Runner::kBlockBytes);
+  const uint8_t* const base = scalar_ptr(v.arena[cls] + (int64_t)hkv * Runner::kBlockBytes);
+  int unit[kPageOps];
+#pragma unroll
+  for (int o = 0; o < kPageOps; ++o) unit[o] = quad_unit<Runner::kD, Runner::kBits>(min(64 * o + lane, kUnits - 1));
+  int f_live = 0, f_first = 0;   // lane s: visible slots and first quad of the pair in slot s
+  // asks for the next pair in slot, moves on; false: there is none
+  auto issue = [&](int slot) -> bool {
+    if (q.i >= q.end) return false;
+    const int first = 8 * q.i;
+    const int own = min(first + (lane >> 2 & 7), q.n - 1);
+    const uint32_t live = (uint32_t)__ballot((q.msk[own] >> (lane & 3) & 1) != 0 && first + (lane >> 2) < q.n && lane < 32);
+#pragma unroll (kPageOps <= 2 ? 2 : 1)
+    for (int page = 0; page < 2; ++page) {
+      int u[kPageOps], from[kPageOps];
+#pragma unroll
+      for (int o = 0; o < kPageOps; ++o) {   // (behind the last quad, that one once more: nothing of it is visible there)
+        u[o] = unit[o];
+        asm volatile("" : "+v"(u[o]));       // (what follows from it is worked out each time: there are no registers to keep it)
+        from[o] = q.pid[min(first + 4 * page + (u[o] & 3), q.n - 1)];
+      }
+#pragma unroll
+      for (int o = 0; o < kPageOps; ++o) {
+        const uint8_t* src = base + (uint64_t)((uint32_t)from[o] >> 2) * page_bytes + (uint32_t)((u[o] >> 8) + ((from[o] & 3) << (u[o] >> 2 & 31)));
+        const uint32_t lds = uniform(ring + slot * kPairBytes + page * Runner::kBlockBytes + 1024 * o);
+        if (kRest != 0 && o == kPageOps - 1)
+          asm volatile("s_mov_b32 m0, %0\n\ts_mov_b64 exec, %2\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %1, off nt\n\ts_mov_b64 exec, -1"
+                       ::"s"(lds), "v"(src), "s"((1ull << kRest) - 1ull) : "m0", "memory");
+        else
+          asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %1, off nt" ::"s"(lds), "v"(src) : "m0", "memory");
+      }
+    }
+    const bool mine = lane == slot;
+    f_live = mine ? (int)live : f_live;
+    if constexpr (Runner::kStat) f_first = mine ? first : f_first;
+    q.i += q.step;
+    return true;
+  };
+  int flying = 0;
+#pragma nounroll
+  while (flying < kSlots && issue(flying)) ++flying;
+  int slot = 0;
+#pragma nounroll
+  while (flying > 0) {
+    if (flying == kSlots) wait_loads<(kSlots - 1) * kOps>();
+    else wait_loads<0>();
+    const LdsPtr blk_a = (LdsPtr)(uintptr_t)(ring + slot * kPairBytes), blk_b = blk_a + Runner::kBlockBytes;
+    typename Runner::Pair r;
+    run.load_k(r, blk_a, blk_b);
+    const uint32_t live = (uint32_t)__builtin_amdgcn_readlane(f_live, slot);
+    QuadIds cur;
+    cur.live_a = live & 0xFFFFu;
+    cur.live_b = live >> 16;
+    if constexpr (Runner::kStat) {
+      const int first = __builtin_amdgcn_readlane(f_first, slot) + (lane >> 2 & 3);
+      auto place = [&](int e) { return e < q.n ? q.idx[e] * kPage + 4 * (q.pid[e] & 3) + (lane & 3) : -1; };
+      cur.at_a = place(first);
+      cur.at_b = place(first + 4);
+    }
+    run.load_v(r, blk_a, blk_b);
+    wait_lds();   // the slot has been read: it can be filled again
+    if (!issue(slot)) --flying;
+    run.scores(r, cur);
+    run.values(r);
+    slot = slot + 1 == kSlots ? 0 : slot + 1;
+  }
+}
 
 // What a lane keeps of the query for the whole item: per column set the eight binary16 values of
 // (its head, its slice's group, channels 8qd .. 8qd+7) and, for the four rows of its quad, the sum of the 32 values
@@ -574,7 +701,8 @@ struct Softmax {
     for (int i = 0; i < NS; ++i) st.m[i] = top[i] == -INFINITY ? -INFINITY : mref[i] + lift;
   }
   // sa, sb: scores of the lane's token in pages a and b (NS heads each), in MFMA units.  Masks them and leaves the pooled scores.
-  __device__ __forceinline__ void mask(float* sa, float* sb, const PairIds& id) {
+  template <class Ids>
+  __device__ __forceinline__ void mask(float* sa, float* sb, const Ids& id) {
     if ((id.live_a & id.live_b) != 0xFFFFu) {
       // dead slots: score -inf, hence p = 0.  Their scales and zero-points are finite (stale, or zero in a slot
       // never written: arenas start zero-filled), so they drop out of every sum.
@@ -588,15 +716,15 @@ struct Softmax {
     }
     if constexpr (STAT) {
       // pooled scores: maximum over the heads of the group, i.e. over the lane's heads and the four lanes of a token
-      auto pooled = [&](const float* sc, int idx) {
+      auto pooled = [&](const float* sc, int at) {
         float u = -INFINITY;
 #pragma unroll
         for (int i = 0; i < NS; ++i) u = head_of<GP>(lane >> 4, i) < G ? fmaxf(u, sc[i] * kappa) : u;
         u = col_max(u);   // the same in the four lanes of a token, which store it to one place
-        if (idx >= 0 && idx < stat_room) stat[(int64_t)idx * kPage + (lane & (kPage - 1))] = u;
+        if (at >= 0 && at < stat_room * kPage) stat[at] = u;
       };
-      pooled(sa, id.idx_a);
-      pooled(sb, id.idx_b);
+      pooled(sa, id.place_a(lane));
+      pooled(sb, id.place_b(lane));
     }
   }
   // Online softmax: the weights are 2^(score - m) with m a reference that is at most `slack` below the maximum seen.  It
@@ -681,7 +809,7 @@ struct Softmax {
 template <int D, int BITS, int GP, bool STAT>
 struct ClassRunner {
   using CL = Cols<D, GP>;
-  static constexpr int kD = D, kBlockBytes = block_geom(BITS, D).block_bytes;
+  static constexpr int kD = D, kBits = BITS, kBlockBytes = block_geom(BITS, D).block_bytes;
   static constexpr bool kStat = STAT, kFp = false;
   static constexpr int NG = D / 32, NM = D / 16, CS = CL::CS, NSET = CL::NSET, NS = GP / 4;
   using F = Fld<BITS>;
@@ -809,7 +937,8 @@ struct ClassRunner {
   }
 
   float sa[NS], sb[NS];   // scores of the pair at hand
-  __device__ __forceinline__ void scores(const Pair& r, const PairIds& id) {
+  template <class Ids>
+  __device__ __forceinline__ void scores(const Pair& r, const Ids& id) {
     page_scores(r.a, sa);
     page_scores(r.b, sb);
     sm.mask(sa, sb, id);
@@ -1155,22 +1284,28 @@ __global__ __launch_bounds__(256 * decode_waves_per_simd(D, FP)) __attribute__((
   }
 }
 
-// Sliding-window layers.  Little is visible (a window of 128 tokens: some twenty pages of a list of a thousand), so the page
+// Sliding-window layers.  Little is visible (a window of 128 tokens: some ten to eighty pages of a list of a thousand), so the page
 // lists are scanned: mask and id, page_pos_max, and where that reaches into the window the
-// sixteen positions, three dependent loads.  A workgroup of eight waves scans for `hg` kv-heads at once, a page of
-// each type per thread with the three chains side by side, leaves the visible pages in LDS in list order, and its waves then
-// attend them, 8 / hg waves to a head; partials are folded in LDS, so a head with one item is finished here.
-// What bounds it is latency: the scan's chains, then the few page pairs a wave has of each type (with one or two visible slots
-// a page), whose loads little else covers.  128 x 4k..32k tokens, window 128, 64 heads, head_dim 64: the kernel takes 27.6 us, 11.3 with
-// the attending left out; vector ALUs busy 18 %, matrix cores 2 %.  (One wave per head and third of the lists, each scanning for
-// itself 64 pages at a time: 52 us a call, 30 now.)
+// sixteen positions, three dependent loads.  A workgroup, all the waves of a compute unit, scans for `hg` kv-heads at once, a page of
+// each type per thread with the three chains side by side, and leaves in LDS, in list order, what is visible: quads of slots (SlotQuads), in the
+// paper's formats pages.  Its waves then attend that, an hg-th of them a head; partials are folded in LDS, so a head with one item is finished here.
+// Blocks of pages are scanned until the lists are complete or full (kWindowList); entries of a block that found no room are there the next time
+// round, when the block is scanned again.
+// What bounds it: the scan's chains (11 us with the launch), then the pairs of a wave.  How many there are follows from the slots: 128 tokens in
+// slots that evictions freed lie in up to eighty pages, 40 pairs a head, most of whose slots are something else; of their quads there are
+// 15 pairs.  us a call, pages attended by eight waves / quads by all: 128 x 4k..32k tokens, 64 heads of 64, window 128 27.4 / 19.6, window 1,024 101 / 60;
+// 64 x 8k, 8 kv-heads of 128, window 500 41.7 / 31.2; 256 x 500..5k, window 128 52.6 / 36.2.  In fresh pages, whose quads are whole pages, 16.9 / 15.9,
+// 33.9 / 32.4, 20.5 / 19.7, 23.3 / 23.6 (an address from every lane instead of a scalar one; a branch to scalar ones for whole pages costs more: 38.7
+// instead of 34.7 for 256 x 500..5k, heads of 64, window 500).  A head's pairs by turns to its waves instead of in runs: no difference in long lists,
+// 12.0 instead of 11.1 for 1 x 4k.
 template <int D, int GP, bool STAT, bool FP>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void decode_window_kernel(thinkv_view v, DecodeArgs a) {
-  constexpr int kRing = window_ring_bytes(D), kRow = D + kRowPad;
+__global__ __launch_bounds__(64 * window_waves(D)) __attribute__((amdgpu_waves_per_eu(window_waves(D) / 4, window_waves(D) / 4))) void decode_window_kernel(thinkv_view v, DecodeArgs a) {
+  static_assert(window_lds_bytes(D, STAT) + window_waves(D) * exchange_bytes(D, GP, FP) <= 163840, "the LDS of a compute unit");
+  constexpr int kWaves = window_waves(D), kRing = window_ring_bytes(D), kRow = D + kRowPad;
   extern __shared__ __attribute__((aligned(16))) uint8_t tkv_lds[];
   const thinkv_config& c = v.cfg;
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-  const int H = c.n_kv_heads, Hq = c.n_q_heads, G = Hq / H, hg = a.waves, wph = kWindowWaves / hg;
+  const int H = c.n_kv_heads, Hq = c.n_q_heads, G = Hq / H, hg = a.waves, wph = whole(kWaves, hg);
   const int groups = quotient(H + hg - 1, hg);
   // item id -> query, group of heads, item j of n (item-major)
   const int per = groups * a.B, j = a.per_head > 1 ? uniform((int)blockIdx.x / per) : 0, rest = (int)blockIdx.x - j * per;
@@ -1184,14 +1319,17 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     n = n < 1 ? 1 : (n > a.per_head ? a.per_head : n);
   }
   if (j >= n) return;
-  const int hw = uniform(wave / wph), hkv = min(h0 + hw, H - 1);   // this wave's head (waves beyond the last head idle)
+  const int hw = whole(wave, wph), hkv = min(h0 + hw, H - 1);   // this wave's head (waves beyond the last head idle)
   if (j == 0 && !a.direct && tid < hg && h0 + tid < H) {
     a.alloc[2 * (b * H + h0 + tid)] = (b * H + h0 + tid) * a.per_head;
     a.alloc[2 * (b * H + h0 + tid) + 1] = n;
   }
-  const uint32_t lds = lds_address(tkv_lds), xch = lds + window_lds_bytes(D) + exchange_bytes(D, GP, FP) * wave;
-  int32_t* const lists = (int32_t*)(tkv_lds + kWindowWaves * kRing);   // [type][id, mask, list position][kWindowBlock]
-  int32_t* const counts = lists + 9 * kWindowBlock;                    // [type][wave]
+  const uint32_t lds = lds_address(tkv_lds), xch = lds + window_lds_bytes(D, STAT) + exchange_bytes(D, GP, FP) * wave;
+  // [type][page id], then [type][list position] with the statistic, [type][mask], [wave] counts
+  int32_t* const ids = (int32_t*)(tkv_lds + kWaves * kRing);
+  int32_t* const listed = ids + 3 * kWindowList;
+  uint16_t* const masks = (uint16_t*)(ids + (STAT ? 6 : 3) * kWindowList);
+  int32_t* const counts = (int32_t*)(masks + 3 * kWindowList);
   Query<D, GP, FP> query;
   query.load(a, ((int64_t)b * Hq + hkv * G) * D, G, lane);
   query.finish(a, G, lane);
@@ -1204,7 +1342,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int s1 = portion(np[1], j, n), e1 = portion(np[1], j + 1, n);
   const int s2 = portion(np[2], j, n), e2 = portion(np[2], j + 1, n);
   const int most = max(e0 - s0, max(e1 - s1, e2 - s2));
-  for (int base = 0; base < most; base += kWindowBlock) {
+  using Source = std::conditional_t<FP, VisiblePages<STAT>, SlotQuads<STAT>>;
+  int have[3] = {0, 0, 0}, skip[3] = {0, 0, 0};   // entries in the lists; entries of this block that have been there before
+  for (int base = 0; base < most;) {
     int pg[3], pid[3];
     uint32_t vis[3];
 #pragma unroll
@@ -1238,52 +1378,78 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         }
         vis[k] &= m;
       }
-    // the visible pages in list order
-    uint64_t seen[3];
+    // what is visible, in list order: an entry for each page (quad of slots) with a visible slot.  Counts of the three types in a word: a
+    // wave has at most 256 of each
+    auto entries = [](uint32_t m) { return FP ? (m != 0 ? 1 : 0) : __popc((m | m >> 1 | m >> 2 | m >> 3) & 0x1111u); };
+    auto add = [](int x, int y) { return x + y; };
+    const int mine = entries(vis[0]) | entries(vis[1]) << 10 | entries(vis[2]) << 20, upto = wave_scan(mine, add);
+    if (lane == 63) counts[wave] = upto;
+    __syncthreads();
+    const int of_wave = lane < kWaves ? counts[lane] : 0;
+    bool all = true;
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-      seen[k] = __ballot(vis[k] != 0);
-      if (lane == 0) counts[k * kWindowWaves + wave] = __popcll(seen[k]);
+      const int waves = wave_scan(of_wave >> (10 * k) & 1023, add), total = last_lane(waves);
+      const int room = kWindowList - have[k];
+      int at = (wave > 0 ? __builtin_amdgcn_readlane(waves, max(wave - 1, 0)) : 0) + ((upto - mine) >> (10 * k) & 1023) - skip[k];
+      auto put = [&](int id, uint32_t m) {
+        if (at >= 0 && at < room) {
+          const int e = k * kWindowList + have[k] + at;
+          ids[e] = id;
+          masks[e] = (uint16_t)m;
+          if (STAT) listed[e] = pg[k];
+        }
+        ++at;
+      };
+      if (FP) {
+        if (vis[k] != 0) put(pid[k], vis[k]);
+      } else {
+#pragma unroll
+        for (int quad = 0; quad < 4; ++quad)
+          if (vis[k] >> (4 * quad) & 15u) put(pid[k] << 2 | quad, vis[k] >> (4 * quad) & 15u);
+      }
+      const int took = min(total - skip[k], room);
+      have[k] += took;
+      skip[k] += took;
+      all = all && skip[k] == total;
     }
     __syncthreads();
-    int total[3];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      int before = 0;
-      total[k] = 0;
-#pragma unroll
-      for (int w = 0; w < kWindowWaves; ++w) {
-        const int x = uniform(counts[k * kWindowWaves + w]);
-        before += w < wave ? x : 0;
-        total[k] += x;
-      }
-      if (vis[k] != 0) {
-        const int at = before + __popcll(seen[k] & ((1ull << lane) - 1ull));
-        lists[(3 * k + 0) * kWindowBlock + at] = pid[k];
-        lists[(3 * k + 1) * kWindowBlock + at] = (int32_t)vis[k];
-        lists[(3 * k + 2) * kWindowBlock + at] = pg[k];
-      }
+    if (all) {
+      base += 64 * kWaves;
+      skip[0] = skip[1] = skip[2] = 0;
+      if (base < most) continue;   // what further blocks have is attended with this one's
     }
-    __syncthreads();
-    if (h0 + hw < H) {
+    if (hw < hg && h0 + hw < H) {
+      // The pairs of the three types one after the other, an equal run of them to each of the head's waves: a wave meets one type or two, and
+      // waits for its first pages once or twice instead of three times.  (The paper's formats: by turns within each type.  A run of 8-bit pages, of
+      // which the ring holds one pair, is slow there: 64 x 4k..8k, 40 heads, window 500 44.0 us by turns, 49.0 in runs.)
+      int pairs[3];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) pairs[k] = (have[k] + Source::kPair - 1) / Source::kPair;
+      const int everything = pairs[0] + pairs[1] + pairs[2];
+      const int from = portion(everything, wave - hw * wph, wph), to = portion(everything, wave - hw * wph + 1, wph);
 #pragma unroll 1
       for (int k = 0; k < 3; ++k) {
-        VisiblePages q;
-        q.n = k == 0 ? total[0] : (k == 1 ? total[1] : total[2]);
-        if (q.n == 0) continue;
-        const uint32_t at = lds + kWindowWaves * kRing + 3 * k * kWindowBlock * 4;
-        q.pid = (VisiblePages::Words)(uintptr_t)at;
-        q.msk = (VisiblePages::Words)(uintptr_t)(at + kWindowBlock * 4);
-        q.idx = (VisiblePages::Words)(uintptr_t)(at + kWindowBlock * 8);
-        q.i = wave - hw * wph;
-        q.step = wph;
+        const int first = k == 0 ? 0 : (k == 1 ? pairs[0] : pairs[0] + pairs[1]);
+        Source q;
+        q.n = k == 0 ? have[0] : (k == 1 ? have[1] : have[2]);
+        q.end = (q.n + Source::kPair - 1) / Source::kPair;
+        q.i = FP ? wave - hw * wph : max(from - first, 0);
+        q.step = FP ? wph : 1;
+        if (!FP) q.end = min(q.end, to - first);
+        if (q.i >= q.end) continue;
+        q.pid = (LdsWords)(uintptr_t)(lds + kWaves * kRing + 4 * k * kWindowList);
+        q.idx = q.pid + 3 * kWindowList;
+        q.msk = (LdsHalves)(uintptr_t)(lds + kWaves * kRing + 4 * (STAT ? 6 : 3) * kWindowList + 2 * k * kWindowList);
         const int bits = c.bits_of_class[k];
         float* stat = nullptr;
         int stat_room = 0;
         if constexpr (STAT) stat = stat_row(c, a, b, hkv, k, np, &stat_room);
-        TKV_BY_WIDTH(bits, stream_pairs<kRing>(cr, q, v, k, hkv, lds + wave * kRing))
+        if constexpr (FP) TKV_BY_WIDTH(bits, stream_pairs<kRing>(cr, q, v, k, hkv, lds + wave * kRing))
+        else TKV_BY_WIDTH(bits, quad_pairs<kRing>(cr, q, v, k, hkv, lds + wave * kRing))
       }
     }
+    have[0] = have[1] = have[2] = 0;
     __syncthreads();   // the lists have been used
   }
   const Partial<D, GP, FP> part(st, lane);
@@ -1298,7 +1464,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     }
   }
   __syncthreads();
-  for (int i = tid; i < hg * G * (D / 4); i += 64 * kWindowWaves) {
+  for (int i = tid; i < hg * G * (D / 4); i += 64 * kWaves) {
     const int hd = i / (G * (D / 4)), g = i / (D / 4) % G, ch = 4 * (i % (D / 4));
     if (h0 + hd < H) fold_rows<D>(a, rows + (hd * wph * G + g) * kRow, G * kRow, wph, b, h0 + hd, g, ch, Hq, G, (b * H + h0 + hd) * a.per_head + j);
   }
@@ -1308,7 +1474,7 @@ template <int D, int GP, bool STAT, bool FP>
 static int launch_one(const thinkv_view& v, const DecodeArgs& a, hipStream_t st) {
   if (a.window > 0) {
     const int groups = (v.cfg.n_kv_heads + a.waves - 1) / a.waves;
-    hipLaunchKernelGGL((decode_window_kernel<D, GP, STAT, FP>), dim3(a.per_head * groups * a.B), dim3(64 * kWindowWaves), window_lds_bytes(D) + kWindowWaves * exchange_bytes(D, GP, FP), st, v, a);
+    hipLaunchKernelGGL((decode_window_kernel<D, GP, STAT, FP>), dim3(a.per_head * groups * a.B), dim3(64 * window_waves(D)), window_lds_bytes(D, STAT) + window_waves(D) * exchange_bytes(D, GP, FP), st, v, a);
   } else {
     hipLaunchKernelGGL((decode_stream_kernel<D, GP, STAT, FP>), dim3(a.grid ? a.grid : a.n_rows), dim3(64 * a.waves), a.waves * (stream_ring_bytes(D, FP) + exchange_bytes(D, GP, FP)) + kTicketBytes, st, v, a);
   }

@@ -153,6 +153,55 @@ def test_window_kernel_against_the_plain_kernel(D, G, H, ctx, fmt, window, dead)
     _close(o, l, ro, rl)
 
 
+@pytest.mark.parametrize("D,G,H,ctx,bits,window,fresh", [
+    (64, 8, 8, [3000] * 40 + [5, 17], (8, 2, 4), 128, 0.0),   # a few tokens to a page, several heads to a workgroup
+    (64, 4, 3, [20000, 33], (2, 4, 8), 30000, 0.0),           # all of it: more quads to a type than a list holds, tails of less than a pair
+    (128, 4, 2, [26000, 1], (4, 8, 2), 30000, 0.0),
+    (128, 8, 2, [9000, 800], (8, 2, 4), 700, 0.0),
+    (128, 2, 1, [2000], (2, 2, 8), 37, 0.5),                  # some of the freed slots taken
+    (64, 1, 16, [400] * 70, (4, 8, 2), 1, 0.0),
+], ids=lambda x: str(x)[:24].replace(" ", ""))
+def test_window_over_reused_slots(D, G, H, ctx, bits, window, fresh):
+    """tokens evicted one by one and their slots taken again: the window's tokens are scattered over the lists.  Against the plain kernel; the
+    statistic against full attention's where everything is visible"""
+    print("window, reused slots:", D, G, H, len(ctx), max(ctx), bits, window, flush=True)
+    c, q = _cache(D, G, H, ctx, 0, bits, 31 + D + G)
+    rng = np.random.default_rng(D + G + window)
+    pick = lambda ok: np.flatnonzero(ok & (rng.random(len(ok)) < 0.3))  # noqa: E731
+    ev_seq, ev_h, cls = [], [], []
+    mask, n_pages = c.slot_mask[:, 0].cpu().numpy(), c.n_pages[:, 0].cpu().numpy()
+    for b in range(len(ctx)):
+        for k in range(3):
+            live = ((mask[b, k, :n_pages[b, k], None] >> np.arange(16)) & 1).astype(bool).reshape(-1)
+            at = pick(live)
+            ev_seq.append(np.full(len(at), b))
+            ev_h.append(k << 28 | at)               # list index << 4 | slot
+            cls.append(np.full(len(at), k))
+    d = lambda x, t: torch.from_numpy(np.ascontiguousarray(x).astype(t)).to("cuda:0")  # noqa: E731
+    seq, h, cls = np.concatenate(ev_seq), np.concatenate(ev_h), np.concatenate(cls)
+    B.thinkv_evict(c, 0, d(seq, np.int32), d(h, np.int32))
+    take = rng.random(len(seq)) >= fresh
+    order = np.lexsort((rng.random(int(take.sum())), seq[take]))
+    seq, cls = seq[take][order], cls[take][order]
+    new = np.bincount(seq, minlength=len(ctx))
+    pos = np.concatenate([x + np.arange(n) for x, n in zip(ctx, new)])
+    if len(seq):
+        kv = [torch.randn((len(seq), H, D), device="cuda:0").to(torch.bfloat16) for _ in range(2)]
+        B.thinkv_append_quantized(c, 0, kv[0], kv[1], d(seq, np.int32), d(pos, np.int32), d(cls, np.uint8))
+    q_pos = [int(x + n - 1) for x, n in zip(ctx, new)]
+    (o, l), (ro, rl) = _both(c, q, D, window=window, q_pos=q_pos)
+    _close(o, l, ro, rl)
+    if window < max(q_pos):
+        return
+    S, pages = q.shape[0], int(c.n_pages[:, 0].sum(-1).max())
+    ids, qp = torch.arange(S, dtype=torch.int32, device="cuda:0"), d(q_pos, np.int32)
+    out, sp = torch.empty((S, G * H, D), dtype=torch.float32, device="cuda:0"), [torch.empty(S, dtype=torch.float32, device="cuda:0") for _ in range(2)]
+    for w, x in zip((0, window), sp):
+        B.thinkv_decode_attention_sparsity(c, 0, q, out, None, x, ids, qp, w, D ** -0.5, pages)
+    # (scores alike up to the order of a few additions: one entry in a thousand may change sides)
+    assert float((sp[0] - sp[1]).abs().max()) <= 1e-3 and float(sp[0].max()) > 0.01
+
+
 @pytest.mark.parametrize("D,G,ctx,fmt,dead,bound", [
     (128, 4, [3000, 17, 1], 0, 0.6, None), (64, 8, [5000, 300], 0, 0.6, 100), (128, 2, [900], 1, 0.6, None), (64, 4, [200, 40], 0, 1.0, None)])
 def test_sparsity_of_pages_with_nothing_live(D, G, ctx, fmt, dead, bound):
