@@ -60,6 +60,7 @@ struct DecodeArgs {
   float* stat;          // [B][n_kv_heads][stat_stride] pooled scores, 16 per page in page-list order (types 0, 1, 2)
   int64_t stat_stride;  // floats per (query, kv-head): 16 * max_ctx_pages
   float* sparsity;      // [B]
+  unsigned long long* stat_sum;   // [B] sum of the kv-heads' fractions, and how many are in it (stat_count_kernel); null: every fraction by itself
   int direct;           // 1: every head has a single item and the attention kernel writes out / lse itself
   int waves;            // fast kernel: waves of a workgroup (full attention), kv-heads of one (sliding window)
   int grid;             // full attention, items dealt by the batch's page counts: workgroups; 0: locate_item

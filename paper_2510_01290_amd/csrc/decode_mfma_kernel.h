@@ -262,16 +262,22 @@ struct PairIds {
   int pid_a, pid_b;
   uint32_t live_a, live_b;
   int idx_a, idx_b;   // positions in the type's page list (idx_b = -1: no second page); used by STAT only
-  // STAT: where the lane's tokens stand in the type's pooled scores (negative: nowhere)
-  __device__ __forceinline__ int place_a(int lane) const { return idx_a * kPage + (lane & (kPage - 1)); }
-  __device__ __forceinline__ int place_b(int lane) const { return idx_b < 0 ? -1 : idx_b * kPage + (lane & (kPage - 1)); }
+  // STAT: the pooled score of the lane's token to its place among the type's, of which there are `room` pages (a scalar branch)
+  __device__ __forceinline__ void keep_a(float* stat, int room, int lane, float u) const { keep(stat, room, lane, u, idx_a); }
+  __device__ __forceinline__ void keep_b(float* stat, int room, int lane, float u) const { keep(stat, room, lane, u, idx_b); }
+  static __device__ __forceinline__ void keep(float* stat, int room, int lane, float u, int idx) {
+    if (idx >= 0 && idx < room) stat[(int64_t)idx * kPage + (lane & (kPage - 1))] = u;
+  }
 };
 // ... of a pair whose "pages" are made of quads of slots (SlotQuads)
 struct QuadIds {
   uint32_t live_a, live_b;
-  int at_a, at_b;
-  __device__ __forceinline__ int place_a(int) const { return at_a; }
-  __device__ __forceinline__ int place_b(int) const { return at_b; }
+  int at_a, at_b;   // STAT: where the lane's tokens stand among the type's pooled scores (negative: nowhere)
+  __device__ __forceinline__ void keep_a(float* stat, int room, int, float u) const { keep(stat, room, u, at_a); }
+  __device__ __forceinline__ void keep_b(float* stat, int room, int, float u) const { keep(stat, room, u, at_b); }
+  static __device__ __forceinline__ void keep(float* stat, int room, float u, int at) {
+    if (at >= 0 && at < room * kPage) stat[at] = u;
+  }
 };
 
 template <int D, int BITS, int NSET>
@@ -716,15 +722,14 @@ struct Softmax {
     }
     if constexpr (STAT) {
       // pooled scores: maximum over the heads of the group, i.e. over the lane's heads and the four lanes of a token
-      auto pooled = [&](const float* sc, int at) {
+      auto pooled = [&](const float* sc) {
         float u = -INFINITY;
 #pragma unroll
         for (int i = 0; i < NS; ++i) u = head_of<GP>(lane >> 4, i) < G ? fmaxf(u, sc[i] * kappa) : u;
-        u = col_max(u);   // the same in the four lanes of a token, which store it to one place
-        if (at >= 0 && at < stat_room * kPage) stat[at] = u;
+        return col_max(u);   // the same in the four lanes of a token, which store it to one place
       };
-      pooled(sa, id.place_a(lane));
-      pooled(sb, id.place_b(lane));
+      id.keep_a(stat, stat_room, lane, pooled(sa));
+      id.keep_b(stat, stat_room, lane, pooled(sb));
     }
   }
   // Online softmax: the weights are 2^(score - m) with m a reference that is at most `slack` below the maximum seen.  It
@@ -1242,6 +1247,8 @@ __global__ __launch_bounds__(256 * decode_waves_per_simd(D, FP)) __attribute__((
   q.cum2 = q.cum1 + q.share(Pairs::pick(q.kind2, np[0], np[1], np[2]), it.j, share_n, q.first2, q.end2);
   if (wave == wave0 && lane == 0) {
     *q.ticket = 0;
+    if constexpr (STAT)
+      if (a.stat_sum && it.n > 0 && it.j == 0 && hkv == 0) a.stat_sum[b] = 0;
     if (it.n > 0 && it.j == 0 && !a.direct) {
       a.alloc[2 * (b * c.n_kv_heads + hkv)] = it.row0;
       a.alloc[2 * (b * c.n_kv_heads + hkv) + 1] = it.n;
@@ -1320,6 +1327,8 @@ __global__ __launch_bounds__(64 * window_waves(D)) __attribute__((amdgpu_waves_p
   }
   if (j >= n) return;
   const int hw = whole(wave, wph), hkv = min(h0 + hw, H - 1);   // this wave's head (waves beyond the last head idle)
+  if constexpr (STAT)
+    if (a.stat_sum && j == 0 && h0 == 0 && tid == 0) a.stat_sum[b] = 0;
   if (j == 0 && !a.direct && tid < hg && h0 + tid < H) {
     a.alloc[2 * (b * H + h0 + tid)] = (b * H + h0 + tid) * a.per_head;
     a.alloc[2 * (b * H + h0 + tid) + 1] = n;

@@ -149,6 +149,43 @@ def test_sparsity_bench_workload_sampled():
     _say(_run(wl, sample=[(2, 0), (13, 0)]))
 
 
+@pytest.mark.parametrize("H,shift", [(1, 0), (2, 0), (3, 0), (3, 4), (16, 0)])
+def test_sparsity_mean_over_the_heads(H, shift):
+    """the heads' fractions added up in one word, or, with one head or a workspace that is not aligned to eight bytes, by a kernel of their own:
+    against each head's own statistic, as caches of one head give it"""
+    import torch
+    from paper_2510_01290_amd import binding as B
+    ctx, D, G = [700, 1, 33], 64, 2
+    S, n = len(ctx), sum(ctx)
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(H)
+    kv = [torch.randn((n, H, D), generator=gen, device="cuda:0").half() for _ in range(2)]
+    q = torch.randn((S, H * G, D), generator=gen, device="cuda:0").half() * 2
+    seq = torch.repeat_interleave(torch.arange(S), torch.tensor(ctx)).int().cuda()
+    pos = torch.cat([torch.arange(c) for c in ctx]).int().cuda()
+    cls = (torch.arange(n) // 40 % 3).to(torch.uint8).cuda()
+
+    def run(heads, shift):
+        h = len(heads)
+        c = B.Cache(1, G * h, h, D, (8, 2, 4), S, 60, [n // 16 + 3 * S + 8] * 3)
+        B.thinkv_append_quantized(c, 0, kv[0][:, heads].contiguous(), kv[1][:, heads].contiguous(), seq, pos, cls)
+        qq = q.view(S, H, G, D)[:, heads].reshape(S, h * G, D).contiguous()
+        pages = int(c.n_pages[:, 0].sum(-1).max())
+        need = B.load().thinkv_decode_sparsity_workspace_bytes(B.C.byref(c.cfg), S, pages)
+        ws = torch.full((need + 64,), 0x5A, dtype=torch.uint8, device="cuda:0")[shift:]
+        out, sp = torch.empty((S, h * G, D), dtype=torch.float32, device="cuda:0"), torch.empty(S, dtype=torch.float32, device="cuda:0")
+        ids, qp = torch.arange(S, dtype=torch.int32, device="cuda:0"), torch.zeros(S, dtype=torch.int32, device="cuda:0")
+        for _ in range(2):   # (the words are cleared by every call)
+            rc = B.load().thinkv_decode_attention_sparsity(B.C.byref(c.view), 0, B._ptr(qq), B._ptr(out), B._ptr(None), B._ptr(sp), B._ptr(ids), B._ptr(qp), S,
+                                                           0, D ** -0.5, B.F16, B.F32, pages, B._ptr(ws), need, B._stream(None))
+            torch.cuda.synchronize()
+            assert rc == 0 and bool((ws[need:] == 0x5A).all())
+        return sp.double().cpu()
+    want = sum(run([h], 0) for h in range(H)) / H
+    assert float((run(list(range(H)), shift) - want).abs().max()) <= 1.2e-7   # (two roundings to binary32)
+    assert float(want[0]) > 0.02
+
+
 def test_sparsity_context_bound_too_small_is_safe():
     _say("a context bound below the true page count: counted over the first pages only, nothing written out of bounds")
     geom = synth.Geometry(1, 8, 2, 64, "f16", (8, 2, 4))
