@@ -26,9 +26,9 @@
 // whole: segments of more tokens (a matrix of up to 132 KB), a workgroup per compute unit that does both; and, alone, all segments of up to 512
 // channels.
 // 314 segments of ~110 tokens, 1,024 channels, us: keys to memory and a workgroup of a whole compute unit per segment (its
-// 139 KB of LDS made that 1.2 rounds of workgroups) 37 + 177; now 67 + 74 (and 6 for whole, which finds nothing).  gram is bound by vector
-// instructions (four a number to unpack and split it) and by 141 MB of rows; kmeans by chains from the lists of members to LDS and
-// back (20 us around the first assignment, 1.5 to 4 for every further one), the parts (10) and the 54 MB of centroids (20).
+// 139 KB of LDS made that 1.2 rounds of workgroups) 37 + 177; now 66 + 58 (and 6 for whole, which finds nothing).  gram is bound by vector
+// instructions (four a number to unpack and split it) and by 141 MB of rows; kmeans by its longest segments' iterations (choose_survivors), the parts
+// (5 to 10), and the 54 MB of centroids (9 to 35, the rows they are made of are 141 MB).
 // The products run on the matrix cores; a dequantised key does not
 // fit binary16 and the binary32 matrix instruction is slow, so every number enters as the sum of
 // two binary16 parts (22 significant bits) and a product is three binary16 MFMAs.  The error of
@@ -475,15 +475,17 @@ constexpr int kKmWaves = 12, kWholeWaves = 16;
 constexpr int kPT = kTbeMaxTokens / 64;                   // tokens per lane of a wave that sorts a list
 constexpr int kWords = kTbeMaxTokens / 32;
 
+// An entry of the list of members: the point, where its row of the triangle begins, that it is one, its cluster, and that the four
+// entries of a step it stands in are the cluster's last
+constexpr uint32_t kIsMember = 1u << 23, kLastStep = 1u << 31;
+__device__ __forceinline__ uint32_t member(int p, int j, bool last) { return (uint32_t)p | (uint32_t)tri(p) << 8 | kIsMember | (uint32_t)j << 24 | (last ? kLastStep : 0u); }
+constexpr uint32_t kUnmoved = ~0u;
+
 template <int W, int POINTS>
 struct KmScratch {
   float gram[POINTS * (POINTS + 1) / 2];                       // products of all pairs of points, lower triangle
   uint32_t basis[kTbeMaxKeep][kWords];                         // the points a cluster's centroid is the mean of
   union {
-    struct {
-      float bd[64 * W];                                        // per group of waves: best distance of every point ...
-      uint8_t bj[64 * W];                                      // ... and the cluster it belongs to
-    };
     uint32_t next[kTbeMaxKeep][kWords];                        // members under the assignment just made
     struct {
       unsigned long long best[kTbeMaxKeep];                    // survivors: nearest member, and the lowest index, of every cluster
@@ -491,169 +493,154 @@ struct KmScratch {
     };
   };
   float own[kTbeMaxTokens];                                    // product of a point with the centroid it belongs to
-  float cc[kTbeMaxKeep];                                       // squared norms of the centroids
-  uint32_t span[kTbeMaxKeep];                                  // members in the list: first | count << 16
-  uint32_t list[kTbeMaxTokens / 4];                            // the points, cluster by cluster, in index order, a byte each
-  unsigned long long moved;                                    // clusters whose centroid has just changed
+  float cc[4][kTbeMaxKeep / 4];                                // squared norms of the centroids: cluster j at [j % 4][j / 4]
+  uint32_t count[kTbeMaxKeep];                                 // members
+  uint32_t start[kTbeMaxKeep];                                 // where those of a cluster whose centroid has just moved begin in the list
+  uint32_t list[kTbeMaxTokens + 3 * kTbeMaxKeep];              // the points of these clusters, cluster by cluster, in index order, each cluster's filled up to fours
+  int steps;                                                   // fours of the list
   int vote[2];                                                 // a point changed its cluster, in iterations of either parity
 };
 static_assert(sizeof(KmScratch<kKmWaves, kFewPoints>) <= 81920, "two workgroups share the LDS of a compute unit");
 
-// f(point) for every point of a cluster's basis, in index order, two at a time (the second -1 where there is none); the
-// points are the same in all lanes
-template <class F>
-__device__ __forceinline__ void for_basis(const uint32_t* mask, F f) {
-  int held = -1;
-  for (int w = 0; w < kWords; ++w) {
-    uint32_t m = __builtin_amdgcn_readfirstlane(mask[w]);
-    while (m) {
-      const int i = 32 * w + __builtin_ctz(m);
-      m &= m - 1;
-      if (held < 0) {
-        held = i;
-      } else {
-        f(held, i);
-        held = -1;
-      }
-    }
-  }
-  if (held >= 0) f(held, -1);
+__device__ __forceinline__ float add_quarters(float x) {   // the sum over the lanes l, l ^ 16, l ^ 32, l ^ 48, the same in the four
+  const uint32_t u = __builtin_bit_cast(uint32_t, x);
+  auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  const uint32_t w = __builtin_bit_cast(uint32_t, __builtin_bit_cast(float, (uint32_t)a[0]) + __builtin_bit_cast(float, (uint32_t)a[1]));
+  auto b = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+  return __builtin_bit_cast(float, (uint32_t)b[0]) + __builtin_bit_cast(float, (uint32_t)b[1]);
 }
 
-// Lloyd's algorithm, the survivors and the centroids of a segment whose matrix is in LDS
+// Lloyd's algorithm, the survivors and the centroids of a segment whose matrix is in LDS.  A wave has sixteen points; lane (r, quarter) shares
+// point r with three others: a quarter adds every fourth member of a cluster and keeps the products with every fourth cluster.  So
+// all waves have the same work whatever the sizes of the clusters are, and the nearest cluster is found inside a wave, without a barrier.  What bounds
+// it: instructions (some twenty for four members of a wave's points) and, where few clusters move, barriers and LDS latency; 161 points and sixteen clusters
+// take 10 us for all products of an iteration, 4 for a few clusters', 1.5 for the assignment.  (A point a lane and clusters dealt to groups of waves: 9, 2 to 8
+// and 2.1, the largest cluster being what everybody waited for.  The sums as a matrix product with the 0/1 matrix of the members, in
+// binary32 on the matrix cores: 5 a tile of sixteen clusters, however few of them moved; 314 segments of 64 to 192 tokens 177 us instead of 145.)
 template <int W, int POINTS>
 __device__ __forceinline__ void choose_survivors(const TbeArgs& a, int seg, int lo, int n, int k, KmScratch<W, POINTS>& sm) {
-  constexpr int kThreads = 64 * W, kMinGroups = W / (POINTS / 64), kClPerThread = (kTbeMaxKeep + kMinGroups - 1) / kMinGroups;
-  static_assert(kClPerThread == 16, "");
-  typedef float f32xk __attribute__((ext_vector_type(kClPerThread)));   // a number for each of a thread's clusters
+  constexpr int kThreads = 64 * W, kPer = kTbeMaxKeep / 4, kAhead = 4, kRows = 8;
+  static_assert(POINTS <= 16 * W && 8 * kTbeMaxKeep <= kThreads, "a wave for sixteen points, eight lanes for a cluster");
+  typedef float f32xk __attribute__((ext_vector_type(kPer)));   // a number for each of a lane's clusters, 4 i + quarter
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), dim = a.dim;
-  // The waves form groups of `pw` that hold all points between them, and a group looks at every `groups`-th cluster (waves that
-  // make no whole group: at none)
-  const int pw = (n + 63) >> 6, groups = W / pw;
-  const int group = wave / pw, p = (wave - group * pw) * 64 + lane;
-  const bool here = p < n;
+  const int quarter = lane >> 4, p = 16 * wave + (lane & 15);
+  const bool here = p < n, first = here && quarter == 0;
   const int pc = here ? p : n - 1, tp = tri(pc);
+  auto product = [&](int m, int tm) { return sm.gram[pc >= m ? tp + m : tm + pc]; };   // with point m, whose row begins at tm
   // initial centroids: evenly spaced points, distinct, since k < n
-  for (int i = tid; i < kTbeMaxKeep * kWords; i += kThreads) (&sm.basis[0][0])[i] = 0u;
-  if (tid < kTbeMaxKeep) sm.span[tid] = 0u;
-  if (tid < kTbeMaxTokens / 4) sm.list[tid] = 0u;   // every byte is a point's at any time
+  for (int i = tid; i < kTbeMaxKeep * kWords; i += kThreads) (&sm.basis[0][0])[i] = (&sm.next[0][0])[i] = 0u;
   if (tid < 2) sm.vote[tid] = 0;
-  __syncthreads();
-  if (tid < k) {
-    const int q = (tid * n) / k;
-    sm.basis[tid][q >> 5] = 1u << (q & 31);
-    ((uint8_t*)sm.list)[tid] = (uint8_t)q;
-    sm.span[tid] = (uint32_t)tid | 1u << 16;
-  }
-  if (tid == 0) sm.moved = k == 64 ? ~0ull : (1ull << k) - 1;
-  const int seed = (pc * k + n - 1) / n;             // the only cluster whose first centroid the point can be
-  int mine = seed < k && (seed * n) / k == pc ? seed : -1;   // the cluster whose basis this point is in
-  int last = -1;                                     // this point's cluster at the last assignment
   __syncthreads();
   f32xk dot;
 #pragma unroll
-  for (int i = 0; i < kClPerThread; ++i) dot[i] = 0.f;
-  // Products of every point with the centroids that moved: a thread leaves those of the clusters group, group + groups, ...
-  // in dot[]; own of the points that are in a basis, and the squared norms of the centroids
+  for (int i = 0; i < kPer; ++i) {
+    const int j = 4 * i + quarter, m = j < k ? j * n / k : 0;
+    dot[i] = 4 * i < k ? product(m, tri(m)) : 0.f;
+  }
+  if (tid < kTbeMaxKeep) {
+    const int q = tid < k ? tid * n / k : 0;
+    if (tid < k) sm.basis[tid][q >> 5] = 1u << (q & 31);
+    sm.cc[tid & 3][tid >> 2] = sm.gram[tri(q) + q];
+    if (tid < k) sm.own[q] = sm.gram[tri(q) + q];
+    sm.count[tid] = tid < k ? 1u : 0u;
+  }
+  int mine = -1;                                     // this point's cluster at the last assignment
+  __syncthreads();
+  // Products of every point with the centroids that moved, in dot[]; own of their members, and the squared norms of the centroids
   auto products = [&]() {
-    const uint32_t list = sm.list[lane], span = sm.span[lane];
-    const uint32_t inv = __builtin_bit_cast(uint32_t, 1.0f / (float)(span >> 16));
-    const uint64_t moved = (uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(sm.moved >> 32)) << 32 | (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)sm.moved);
-    auto place = [&](int q) {   // of the product with the q-th point of the list, the same point in all lanes
-      const int m = (int)((uint32_t)__builtin_amdgcn_readlane(list, q >> 2) >> (8 * (q & 3))) & 255;
-      const int below = tp + m, above = tri(m) + pc;
-      return pc >= m ? below : above;
-    };
-    for (int i = 0, j = group < groups ? group : k; j < k; ++i, j += groups) {
-      if (!(moved >> j & 1)) continue;
-      const uint32_t sp = __builtin_amdgcn_readlane(span, j);
-      int q = (int)(sp & 0xFFFFu);
-      const int end = q + (int)(sp >> 16);
-      float sum = 0.f;
-      // four at a time, then two, then one: the additions stay in order, the loads do not wait for each other (one ahead of the
-      // other an eviction event of 316 segments took 215.2 us, now 212.2)
-      for (; q + 4 <= end; q += 4) {
-        const float a0 = sm.gram[place(q)], a1 = sm.gram[place(q + 1)], a2 = sm.gram[place(q + 2)], a3 = sm.gram[place(q + 3)];
-        sum += a0;
-        sum += a1;
-        sum += a2;
-        sum += a3;
-      }
-      if (q + 2 <= end) {
-        const float a0 = sm.gram[place(q)], a1 = sm.gram[place(q + 1)];
-        sum += a0;
-        sum += a1;
-        q += 2;
-      }
-      if (q < end) sum += sm.gram[place(q)];
-      const float d = sum * __builtin_bit_cast(float, __builtin_amdgcn_readlane(inv, j));
-      dot[i] = d;
-      if (mine == j && here) sm.own[p] = d;
-    }
-    __syncthreads();
-    // |c|^2 = mean over the basis of its points' products with the centroid: eight lanes per cluster, a fixed tree
-    const int j = tid >> 3;
-    if (j < k && (sm.moved >> j & 1)) {
-      const int q0 = (int)(sm.span[j] & 0xFFFFu), cnt = (int)(sm.span[j] >> 16);
-      float sum = 0.f;
-      for (int q = tid & 7; q < cnt; q += 8) sum += sm.own[((const uint8_t*)sm.list)[q0 + q]];
+    const int steps = __builtin_amdgcn_readfirstlane(sm.steps);
+    const uint32_t inv = __builtin_bit_cast(uint32_t, 1.0f / (float)sm.count[lane]);
+    float sum = 0.f;
+    if (16 * wave < n)
+      for (int s0 = 0; s0 < steps; s0 += kAhead) {   // the loads of four steps do not wait for each other
+        uint32_t e[kAhead];
+        float g[kAhead];
 #pragma unroll
-      for (int d = 4; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, 8);
-      if ((tid & 7) == 0) sm.cc[j] = sum * (1.0f / (float)cnt);
+        for (int u = 0; u < kAhead; ++u) e[u] = sm.list[4 * min(s0 + u, steps - 1) + quarter];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) g[u] = product(e[u] & 255, e[u] >> 8 & 0x7FFF);
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+          if (s0 + u >= steps) break;
+          sum += e[u] & kIsMember ? g[u] : 0.f;
+          const uint32_t all = __builtin_amdgcn_readfirstlane(e[u]);   // (the first of a step is a member)
+          if (all & kLastStep) {
+            const int j = all >> 24 & 63;
+            const float d = add_quarters(sum) * __builtin_bit_cast(float, __builtin_amdgcn_readlane(inv, j));
+            dot[j >> 2] = quarter == (j & 3) ? d : dot[j >> 2];
+            if (first && mine == j) sm.own[p] = d;
+            sum = 0.f;
+          }
+        }
+      }
+    __syncthreads();
+    // |c|^2 = mean over the members of their products with the centroid: eight lanes per cluster, a fixed tree
+    const int j = tid >> 3;
+    if (j < k && sm.start[j] != kUnmoved) {
+      const uint32_t q0 = sm.start[j], cnt = sm.count[j];
+      float part = 0.f;
+      for (uint32_t q = tid & 7; q < cnt; q += 8) part += sm.own[sm.list[q0 + q] & 255];
+#pragma unroll
+      for (int d = 4; d >= 1; d >>= 1) part += __shfl_xor(part, d, 8);
+      if ((tid & 7) == 0) sm.cc[j & 3][j >> 2] = part * (1.0f / (float)cnt);
     }
+    // (the members of the assignment before have been used)
+    for (int i = tid; i < kTbeMaxKeep * kWords; i += kThreads) (&sm.next[0][0])[i] = 0u;
     __syncthreads();
   };
   bool converged = false;
   for (int it = 0; it < a.max_iters; ++it) {
     // centroids: the initial ones, later the means under the previous assignment
-    products();
+    if (it > 0) products();
     // nearest cluster of every point: |c|^2 - 2 x.c decides (|x|^2 is common to a point's candidates); ties go to the
     // lowest cluster
-    const uint32_t cc = __builtin_bit_cast(uint32_t, sm.cc[lane]);
     float bd = INFINITY;
     int bj = kTbeMaxKeep;
 #pragma unroll
-    for (int i = 0; i < kClPerThread; ++i) {
-      const int j = group + groups * i;
-      if (j < k) {
-        const float d = fmaf(-2.f, dot[i], __builtin_bit_cast(float, __builtin_amdgcn_readlane(cc, j)));
-        if (d < bd) {
-          bd = d;
-          bj = j;
-        }
+    for (int i = 0; i < kPer; ++i) {
+      if (4 * i >= k) break;
+      const int j = 4 * i + quarter;
+      const float d = fmaf(-2.f, dot[i], sm.cc[quarter][i]);
+      if (j < k && d < bd) {
+        bd = d;
+        bj = j;
       }
     }
-    sm.bd[tid] = bd;
-    sm.bj[tid] = (uint8_t)bj;
-    __syncthreads();
-    bd = sm.bd[p];
-    bj = sm.bj[p];
-    for (int w = 1; w < groups; ++w) {
-      const float od = sm.bd[w * pw * 64 + p];
-      const int oj = sm.bj[w * pw * 64 + p];
-      if (od < bd || (od == bd && oj < bj)) {
-        bd = od;
-        bj = oj;
-      }
+    {
+      auto nearer = [&](auto d, auto c) {   // of the two that a swap brings together
+        const float d0 = __builtin_bit_cast(float, (uint32_t)d[0]), d1 = __builtin_bit_cast(float, (uint32_t)d[1]);
+        const int c0 = (int)c[0], c1 = (int)c[1];
+        const bool second = d1 < d0 || (d1 == d0 && c1 < c0);
+        bd = second ? d1 : d0;
+        bj = second ? c1 : c0;
+      };
+      const uint32_t d16 = __builtin_bit_cast(uint32_t, bd), c16 = (uint32_t)bj;
+      nearer(__builtin_amdgcn_permlane16_swap(d16, d16, false, false), __builtin_amdgcn_permlane16_swap(c16, c16, false, false));
+      const uint32_t d32 = __builtin_bit_cast(uint32_t, bd), c32 = (uint32_t)bj;
+      nearer(__builtin_amdgcn_permlane32_swap(d32, d32, false, false), __builtin_amdgcn_permlane32_swap(c32, c32, false, false));
     }
     if (bj >= k) bj = 0;   // no candidate compares (the distances are not numbers): the first cluster, as a comparison that never holds leaves it
-    if (here && bj != last) sm.vote[it & 1] = 1;
-    last = mine = bj;
+    if (first) {
+      if (bj != mine) sm.vote[it & 1] = 1;
+      atomicOr(&sm.next[bj][p >> 5], 1u << (p & 31));
+    }
+    mine = bj;
     __syncthreads();
     if (!sm.vote[it & 1]) {
       converged = true;   // the products at hand are those with the final centroids
       break;
     }
-    if (tid == 0) sm.vote[~it & 1] = 0;
     // members of every cluster; a cluster without any keeps its basis
-    for (int i = tid; i < kTbeMaxKeep * kWords; i += kThreads) (&sm.next[0][0])[i] = 0u;
-    __syncthreads();
-    if (group == 0 && here) atomicOr(&sm.next[mine][p >> 5], 1u << (p & 31));
-    __syncthreads();
-    if (wave == 0) {
+    int rank = 0;
+    if (first) {
+      for (int w = 0; w < (p >> 5); ++w) rank += __popc(sm.next[mine][w]);
+      rank += __popc(sm.next[mine][p >> 5] & ((1u << (p & 31)) - 1u));
+    }
+    if (wave == W - 1) {
+      if (lane == 0) sm.vote[~it & 1] = 0;
       int m = 0;
       // a cluster that gets back the members it lost has the centroid it had, but their products (own) are with others by now
-      bool differs = sm.span[lane] >> 16 == 0;
+      bool differs = sm.count[lane] == 0;
       uint32_t row[kWords];
 #pragma unroll
       for (int w = 0; w < kWords; ++w) {
@@ -665,23 +652,22 @@ __device__ __forceinline__ void choose_survivors(const TbeArgs& a, int seg, int 
 #pragma unroll
         for (int w = 0; w < kWords; ++w) sm.basis[lane][w] = row[w];
       }
-      int upto = m;
+      const bool moved = m > 0 && differs;
+      const int fours = moved ? (m + 3) >> 2 : 0;
+      int upto = fours;
 #pragma unroll
       for (int d = 1; d < 64; d <<= 1) {
         const int o = __shfl_up(upto, d, 64);
         if (lane >= d) upto += o;
       }
-      sm.span[lane] = (uint32_t)(upto - m) | (uint32_t)m << 16;
-      const unsigned long long moved = __ballot(m > 0 && differs);
-      if (lane == 0) sm.moved = moved;
+      const int from = 4 * (upto - fours);
+      sm.count[lane] = m;
+      sm.start[lane] = moved ? (uint32_t)from : kUnmoved;
+      for (int q = m; q < 4 * fours; ++q) sm.list[from + q] = 0u;
+      if (lane == 63) sm.steps = upto;
     }
     __syncthreads();
-    if (group == 0 && here) {
-      int rank = 0;
-      for (int w = 0; w < (p >> 5); ++w) rank += __popc(sm.next[mine][w]);
-      rank += __popc(sm.next[mine][p >> 5] & ((1u << (p & 31)) - 1u));
-      ((uint8_t*)sm.list)[(sm.span[mine] & 0xFFFFu) + rank] = (uint8_t)p;
-    }
+    if (first && sm.start[mine] != kUnmoved) sm.list[sm.start[mine] + rank] = member(p, mine, rank >> 2 == (int)(sm.count[mine] - 1) >> 2);
     __syncthreads();
   }
   // ---- survivors: nearest member of every cluster under the final centroids
@@ -691,54 +677,80 @@ __device__ __forceinline__ void choose_survivors(const TbeArgs& a, int seg, int 
     sm.best[tid] = ~0ull;
   }
   __syncthreads();
-  if (group == 0 && here) {
-    const float dist = fmaxf(fmaf(-2.f, sm.own[p], sm.gram[tp + p]) + sm.cc[mine], 0.f);
+  if (first) {
+    const float dist = fmaxf(fmaf(-2.f, sm.own[p], sm.gram[tp + p]) + sm.cc[mine & 3][mine >> 2], 0.f);
     atomicMin(&sm.low[mine], p);
     // distances are not negative, so their bit patterns order like the numbers; the index breaks ties
     atomicMin(&sm.best[mine], ((unsigned long long)__builtin_bit_cast(uint32_t, dist) << 32) | (unsigned)p);
   }
   __syncthreads();
-  if (group == 0 && here) {
+  if (first) {
     // two members are equally near their mean whatever the rounding says: the earlier one stays (a cluster with members
     // has them as its basis)
-    const bool keep = (sm.span[mine] >> 16) <= 2 ? p == sm.low[mine] : (int)(sm.best[mine] & 0xFFFFFFFFull) == p;
+    const bool keep = sm.count[mine] <= 2 ? p == sm.low[mine] : (int)(sm.best[mine] & 0xFFFFFFFFull) == p;
     a.ev_handle[lo + p] = keep ? -1 : a.tok_handle[lo + p];
     a.assign[lo + p] = mine;
   }
-  // ---- the centroids, for callers that look at them: a wave per cluster, up to 1,024 channels at a time, two members' rows
-  // (eight loads a lane) in flight, members in index order.  Nothing here reads them again: past the caches, where they made
+  // ---- the centroids, for callers that look at them.  The members of all clusters in a row, cluster by cluster, each in index order (the matrix has
+  // been used: a cluster that has lost its last member shares those it had, so there may be more than n); a wave takes 256 channels and a share of the
+  // row, kRows members' rows in flight whatever the sizes of the clusters.  (A wave per cluster and 1,024 channels with two rows in flight: whoever had a
+  // cluster of sixty members took thirty turns, 12 to 30 us where it is now 5 to 12.)  Nothing here reads them again: past the caches, where they made
   // the next call's gram kernel wait (66 us, now 60)
+  __syncthreads();
+  uint32_t* const row = (uint32_t*)sm.gram;   // point | cluster << 8 | last member << 31
+  static_assert(sizeof(sm.gram) >= 4 * kTbeMaxKeep * POINTS, "all points in all clusters");
+  int size = 0;                               // of cluster `lane`, and where its members begin
+#pragma unroll
+  for (int w = 0; w < kWords; ++w) size += __popc(sm.basis[lane][w]);
+  int begin = size;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int o = __shfl_up(begin, d, 64);
+    if (lane >= d) begin += o;
+  }
+  const int total = __builtin_amdgcn_readlane(begin, 63);
+  begin -= size;
+  for (int j = wave; j < k; j += W) {
+    int at = __builtin_amdgcn_readlane(begin, j);
+    const int end = at + __builtin_amdgcn_readlane(size, j);
+    for (int q = 0; q < n; q += 64) {
+      const uint64_t in = (uint64_t)sm.basis[j][q / 32 + 1] << 32 | sm.basis[j][q / 32];
+      const int to = at + __popcll(in & ((1ull << lane) - 1ull));
+      if (in >> lane & 1ull) row[to] = (uint32_t)(q + lane) | (uint32_t)j << 8 | (to + 1 == end ? 1u << 31 : 0u);
+      at += __popcll(in);
+    }
+  }
+  __syncthreads();
+  const float inv = 1.0f / (float)size;
   const float* x = a.x + (int64_t)lo * dim;
   float* cent = a.cent + (int64_t)seg * kTbeMaxKeep * dim;
-  for (int j = wave; j < k; j += W) {
-    int cnt = 0;
+  const int slices = (dim + 255) >> 8, shares = slices < W ? W / slices : 1;
+  for (int unit = wave; unit < slices * shares; unit += W) {
+    const int share = unit / slices, d0 = 256 * (unit - share * slices) + 4 * lane;
+    // whole clusters: those that begin in the share
+    const int j0 = __popcll(__ballot(lane < k && begin < share * total / shares)), j1 = __popcll(__ballot(lane < k && begin < (share + 1) * total / shares));
+    if (j0 == j1) continue;
+    const int e0 = __builtin_amdgcn_readlane(begin, j0), e1 = j1 < k ? __builtin_amdgcn_readlane(begin, min(j1, 63)) : total;
+    const bool on = d0 < dim;
+    const float* const col = x + (on ? d0 : 0);
+    f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+    for (int e = e0; e < e1; e += kRows) {
+      const uint32_t some = row[min(e + min(lane, kRows - 1), e1 - 1)];
+      f32x4 r[kRows];
 #pragma unroll
-    for (int w = 0; w < kWords; ++w) cnt += __popc(sm.basis[j][w]);
-    const float by = 1.0f / (float)cnt;
-    for (int d0 = 4 * lane; d0 < dim; d0 += 1024) {
-      f32x4 sum[4];
+      for (int u = 0; u < kRows; ++u) r[u] = *(const f32x4*)(col + (int64_t)(__builtin_amdgcn_readlane(some, u) & 255) * dim);
 #pragma unroll
-      for (int u = 0; u < 4; ++u) sum[u] = f32x4{0.f, 0.f, 0.f, 0.f};
-      for_basis(sm.basis[j], [&](int m0, int m1) {
-        f32x4 t[2][4];
-        const float* r0 = x + (int64_t)m0 * dim + d0;
-        const float* r1 = x + (int64_t)(m1 < 0 ? m0 : m1) * dim + d0;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          if (d0 + 256 * u >= dim) continue;
-          t[0][u] = *(const f32x4*)(r0 + 256 * u);
-          if (m1 >= 0) t[1][u] = *(const f32x4*)(r1 + 256 * u);
+      for (int u = 0; u < kRows; ++u) {
+        if (e + u >= e1) break;
+        sum += r[u];
+        const uint32_t m = __builtin_amdgcn_readlane(some, u);
+        if (m >> 31) {
+          const int j = m >> 8 & 63;
+          const f32x4 mean = sum * __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, inv), j));
+          if (on) __builtin_nontemporal_store(mean, (f32x4*)&cent[(int64_t)j * dim + d0]);
+          sum = f32x4{0.f, 0.f, 0.f, 0.f};
         }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          if (d0 + 256 * u >= dim) continue;
-          sum[u] += t[0][u];
-          if (m1 >= 0) sum[u] += t[1][u];
-        }
-      });
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (d0 + 256 * u < dim) __builtin_nontemporal_store(sum[u] * by, (f32x4*)&cent[(int64_t)j * dim + d0 + 256 * u]);
+      }
     }
   }
 }
