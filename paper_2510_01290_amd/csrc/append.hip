@@ -503,13 +503,16 @@ __device__ __forceinline__ GroupCode group_code(float mn, float mx, float qmax, 
   return g;
 }
 // (The middle of three with a NaN is the smaller of the other two.  With a finite scale differences stay below 2^25, but for an
-// infinity whose group's maximum a signalling NaN has swallowed: the first clamp keeps it out of the correction.)
+// infinity whose group's maximum a signalling NaN has swallowed: the first clamp keeps it out of the correction.)  The result is what the
+// conversion to a byte rounds (v_cvt_pk_u8_f32: to nearest, ties to even).
 __device__ __forceinline__ float group_quotient(const GroupCode& g, float x, float qmax) {
   const float d = __builtin_amdgcn_fmed3f(x - g.zf, -0x1p60f, 0x1p60f);
   const float q0 = d * g.r;
   const float q = fmaf(fmaf(-g.sf, q0, d), g.r, q0);
-  return __builtin_amdgcn_fmed3f(rintf(q), 0.0f, qmax);
+  return __builtin_amdgcn_fmed3f(q, 0.0f, qmax);
 }
+// 1 / (2^bits - 1), as a division gives it
+__device__ __forceinline__ float inverse_of_qmax(int bits) { return bits == 2 ? 1.0f / 3.0f : (bits == 4 ? 1.0f / 15.0f : 1.0f / 255.0f); }
 
 template <int CTRL>
 __device__ __forceinline__ float dpp(float x) {
@@ -658,9 +661,8 @@ __global__ __launch_bounds__(256) void append_place_kernel(thinkv_view v, int la
         mn = fminf(mn, __shfl_xor(mn, d, 64));
         mx = fmaxf(mx, __shfl_xor(mx, d, 64));
       }
-      const GroupCode gc = group_code(mn, mx, qmax, 1.0f / qmax);
-      const float code = group_quotient(gc, x, qmax);
-      s_codes[hs][kind][ch] = (uint8_t)(int)code;
+      const GroupCode gc = group_code(mn, mx, qmax, inverse_of_qmax(bits));
+      s_codes[hs][kind][ch] = (uint8_t)__builtin_amdgcn_cvt_pk_u8_f32(group_quotient(gc, x, qmax), 0, 0u);
       if ((ch & 31) == 0)
         s_meta[hs][kind][ch >> 5] = gc.meta;
       }
@@ -723,7 +725,8 @@ __global__ __launch_bounds__(256) void append_place_kernel(thinkv_view v, int la
 // fifteen of its type, and the unit's part of the page (0.3 to 2.3 KB) is put together in LDS and stored in 16-byte words.
 // Tokens that take slots of existing pages are stored field by field.
 // What bounds it: reading the rows, 256 bytes at a time, and next to that the vector instructions of the quantiser (with
-// divisions in it the kernel is a fifth longer).
+// divisions in it the kernel is a fifth longer).  Leaving things out of its 58 us: the rows' loads 45, the pages' stores 54, the quantiser 47, all of
+// these 28, and everything but the places 15.
 // 37,000 tokens of 16 prompts, 8 kv-heads of 128, bf16 (151 MB in, 50 MB out): 96.5 us with a block of sixteen tokens
 // storing 2 to 8 bytes at a time into pages that four blocks shared, 67 with whole pages, 60 with nontemporal loads of
 // neighbouring heads side by side.  Rows requested a unit ahead gained nothing (64 against 60), nor did K and V in one unit (more
@@ -820,7 +823,7 @@ __device__ __forceinline__ void place_unit(const thinkv_view& v, const void* __r
     float x[8];
     widen<IN>(raw[p], x);
     uint32_t meta = 0;
-    const uint2 w = FP ? piece_codes_fp(x, bits, (double)c.fp8_scale[kind], &meta) : piece_codes(x, qmax, 1.0f / qmax, &meta);
+    const uint2 w = FP ? piece_codes_fp(x, bits, (double)c.fp8_scale[kind], &meta) : piece_codes(x, qmax, inverse_of_qmax(bits), &meta);
     if (rows >> r & 1) {
       const BlockGeom g = block_geom(bits, D, c.format);
       uint8_t* const blk = WHOLE ? nullptr : v.arena[row.cls] + ((int64_t)row.pid * H + h) * g.block_bytes;
@@ -879,8 +882,12 @@ __device__ __forceinline__ void place_unit(const thinkv_view& v, const void* __r
   }
 }
 
+// Blocks a compute unit: eight, as many as its LDS holds at head_dim 128, where registers allow (not binary32 rows, nor the binary64 of the paper's formats).  Vector
+// instructions are issued in 68 % of the kernel's time and a block starts with a chain of loads, so another wave shows: 37,000 tokens of 16 prompts,
+// with the reset, 82.0 us with seven and divisions by the head count, now 80.0; 60 prompts of 4k to 8k tokens 540 and 523.
+__host__ __device__ constexpr int bulk_blocks(int in_dtype, bool fp) { return fp ? 6 : (in_dtype == THINKV_F32 ? 6 : 8); }
 template <int D, int IN, bool FP>
-__global__ __launch_bounds__(256) void append_place_bulk_kernel(thinkv_view v, int layer, const void* __restrict__ k_new,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(bulk_blocks(IN, FP)))) void append_place_bulk_kernel(thinkv_view v, int layer, const void* __restrict__ k_new,
                                                                 const void* __restrict__ v_new, const int32_t* __restrict__ tok_seq,
                                                                 const int32_t* __restrict__ tok_pos,
                                                                 const uint8_t* __restrict__ tok_class, int32_t* __restrict__ tok_handle,
@@ -948,8 +955,10 @@ __global__ __launch_bounds__(256) void append_place_bulk_kernel(thinkv_view v, i
     }
   }
   __syncthreads();
-  for (int w = wave; w < 2 * n_new * hn; w += 4) {
-    const int q = w / (2 * hn), kind = w / hn & 1, h = h_lo + w % hn;   // neighbours in memory side by side
+  const int lg = 31 - __builtin_clz(2 * heads_per_block - 1);   // (heads by a power of two: shifts instead of divisions)
+  for (int w = wave; w < n_new << (lg + 1); w += 4) {
+    const int q = w >> (lg + 1), kind = w >> lg & 1, h = h_lo + (w & ((1 << lg) - 1));   // neighbours in memory side by side
+    if (h >= h_hi) continue;
     const int cls = __builtin_amdgcn_readfirstlane(s_new[q].cls), pid = __builtin_amdgcn_readfirstlane(s_new[q].pid);
     const int cnt = __builtin_amdgcn_readfirstlane(s_new[q].cnt);
     place_unit<D, IN, FP, true>(v, kind ? v_new : k_new, kind, h, [&](int r) { return Row{s_tok[q][r], cls, pid, r}; }, (1u << cnt) - 1u, s_unit[wave]);
