@@ -105,9 +105,9 @@ __device__ __forceinline__ Packed3 wave_scan(Packed3 x) {
   return scan_step<0x143, 0xC>(x);
 }
 
-// exclusive scans of N words per thread over a 256-thread block, and the block's totals
-template <int N>
-__device__ inline void block_excl_scan(const Packed3 (&v)[N], Packed3 (&excl)[N], Packed3 (&tot)[N], Packed3 (*lds)[4]) {
+// exclusive scans of N words per thread over a block of W waves, and the block's totals
+template <int W, int N>
+__device__ inline void block_excl_scan(const Packed3 (&v)[N], Packed3 (&excl)[N], Packed3 (&tot)[N], Packed3 (*lds)[W]) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   Packed3 inc[N];
 #pragma unroll
@@ -122,7 +122,7 @@ __device__ inline void block_excl_scan(const Packed3 (&v)[N], Packed3 (&excl)[N]
     Packed3 off = 0;
     tot[i] = 0;
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
+    for (int w = 0; w < W; ++w) {
       const Packed3 t = lds[i][w];
       if (w < wave) off += t;
       tot[i] += t;
@@ -150,8 +150,11 @@ __device__ inline int token_bound(const int32_t* __restrict__ tok_seq, int n_tok
   return lo;
 }
 
-constexpr int kKeep = 4;        // pages of a type a thread keeps the masks of (1,024 pages a list); longer lists are read again
+constexpr int kKeep = 4;        // pages of a type a thread keeps the masks of (1,024 pages a list by 256 threads); longer lists are read again
 constexpr int kWindow = 4096;   // tokens ranked at a time
+// With more tokens than that per sequence of the view the plan takes 512 threads a sequence.  (Fewer: the threads without a token only cost: 256 sequences, five
+// tokens each, with their eviction, 19.9 us by 256 threads and 20.5 by 512.)
+constexpr int kLongPrompts = 256;
 constexpr int kEvAhead = 2;     // evictions of a call a thread holds before it applies the first
 // (The plan is a chain of dependent loads: with handles, page counts, token ranges and last pages asked for one after the other behind
 // the evictions it was eight long, now five.  256 sequences, a token out and a token in: plan 7.7 us, now 6.7, the call 15.7 and 14.5.)
@@ -161,12 +164,15 @@ __device__ __forceinline__ uint32_t page_mask(const uint32_t* msk, const uint32_
   return u == 0 ? kept[0] : (u == 1 ? kept[1] : (u == 2 ? kept[2] : (u == 3 ? kept[3] : msk[pi])));
 }
 
-__global__ __launch_bounds__(256) void append_plan_kernel(thinkv_view v, int layer, const int32_t* __restrict__ tok_seq,
+// T threads: 256, which have a token each up to that many and sixteen beyond, or 512, with one and eight.  (us a call, reset included, 256 / 512: 1 x 600 tokens
+// 22.7 / 20.9, 1 x 8k 48.4 / 42.5, 16 x 1k..4k 80.0 / 77.4, 256 x 1k of 2 heads of 64 108 / 102; 1,024 have no registers for it: 33.9, 55.9, 89.7, 129.)
+template <int T>
+__global__ __launch_bounds__(T) void append_plan_kernel(thinkv_view v, int layer, const int32_t* __restrict__ tok_seq,
                                                           const uint8_t* __restrict__ tok_class, int n_tok, AppendWs ws,
                                                           const int32_t* __restrict__ ev_seq, const int32_t* __restrict__ ev_handle,
                                                           int n_ev) {
   __shared__ int s_rng[2];
-  __shared__ Packed3 s_scan[4][4];
+  __shared__ Packed3 s_scan[4][T / 64];
   __shared__ uint16_t s_tok[kWindow];
   const thinkv_config& c = v.cfg;
   const int s = blockIdx.x, tid = threadIdx.x;
@@ -178,9 +184,9 @@ __global__ __launch_bounds__(256) void append_plan_kernel(thinkv_view v, int lay
   int ev_s[kEvAhead], ev_h[kEvAhead];
 #pragma unroll
   for (int u = 0; u < kEvAhead; ++u) {
-    const bool in = tid + 256 * u < n_ev;
-    ev_s[u] = in ? ev_seq[tid + 256 * u] : s;
-    ev_h[u] = in ? ev_handle[tid + 256 * u] : -1;
+    const bool in = tid + T * u < n_ev;
+    ev_s[u] = in ? ev_seq[tid + T * u] : s;
+    ev_h[u] = in ? ev_handle[tid + T * u] : -1;
   }
   if (s == 0 && tid < 3) ws.avail_old[tid] = v.free_top[tid];   // the pools as the call finds them
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -206,7 +212,7 @@ __global__ __launch_bounds__(256) void append_plan_kernel(thinkv_view v, int lay
     };
 #pragma unroll
     for (int u = 0; u < kEvAhead; ++u) evict(ev_s[u], ev_h[u]);
-    for (int i = tid + 256 * kEvAhead; i < n_ev; i += 256) evict(ev_seq[i], ev_handle[i]);
+    for (int i = tid + T * kEvAhead; i < n_ev; i += T) evict(ev_seq[i], ev_handle[i]);
     __threadfence_block();
   }
   __syncthreads();
@@ -228,7 +234,7 @@ __global__ __launch_bounds__(256) void append_plan_kernel(thinkv_view v, int lay
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
     const int64_t row = table_base(c, s, layer, k);
-    const int np = np_of[k], per = (np + 255) / 256;
+    const int np = np_of[k], per = (np + T - 1) / T;
     q0[k] = min(tid * per, np);
     q1[k] = min(q0[k] + per, np);
 #pragma unroll
@@ -265,7 +271,7 @@ __global__ __launch_bounds__(256) void append_plan_kernel(thinkv_view v, int lay
     // the window's tokens of each type together, the reclaimable slots apart (there may be more than a packed word holds)
     const Packed3 x[4] = {pack3(mine[0], mine[1], mine[2]), (Packed3)have[0], (Packed3)have[1], (Packed3)have[2]};
     Packed3 ex[4], tot[4];
-    block_excl_scan(x, ex, tot, s_scan);
+    block_excl_scan<T / 64>(x, ex, tot, s_scan);
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
       rank[k] = part3(ex[0], k);
@@ -310,9 +316,9 @@ __global__ __launch_bounds__(256) void append_plan_kernel(thinkv_view v, int lay
 #pragma unroll
     for (int k = 0; k < 3; ++k) n[k] += cnt[k];
   };
-  if (hi - lo <= 256) window(std::integral_constant<int, 1>(), lo);
+  if (hi - lo <= T) window(std::integral_constant<int, 1>(), lo);
   else
-    for (int w0 = lo; w0 < hi; w0 += kWindow) window(std::integral_constant<int, kWindow / 256>(), w0);
+    for (int w0 = lo; w0 < hi; w0 += kWindow) window(std::integral_constant<int, kWindow / T>(), w0);
   // ---- what follows for the pages the sequence has: the first n of the reclaimable, then of the never-used slots are live
   int placed = 0;
 #pragma unroll
@@ -978,7 +984,10 @@ int launch_append(const thinkv_view& v, int layer, const void* k_new, const void
                   void* workspace, hipStream_t st, const int32_t* ev_seq, const int32_t* ev_handle, int n_ev) {
   AppendWs ws = carve(v.cfg, n_tok, workspace);
   const int S = v.cfg.max_seqs;
-  hipLaunchKernelGGL(append_plan_kernel, dim3(S), dim3(256), 0, st, v, layer, tok_seq, tok_class, n_tok, ws, ev_seq, ev_handle, n_ev);
+  if ((int64_t)n_tok > (int64_t)kLongPrompts * S)
+    hipLaunchKernelGGL(append_plan_kernel<512>, dim3(S), dim3(512), 0, st, v, layer, tok_seq, tok_class, n_tok, ws, ev_seq, ev_handle, n_ev);
+  else
+    hipLaunchKernelGGL(append_plan_kernel<256>, dim3(S), dim3(256), 0, st, v, layer, tok_seq, tok_class, n_tok, ws, ev_seq, ev_handle, n_ev);
   const bool small = n_tok <= kBulkFrom;
   const bool aligned = (((uintptr_t)k_new | (uintptr_t)v_new) & 15) == 0;
   if (!small && aligned) {

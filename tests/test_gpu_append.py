@@ -48,6 +48,17 @@ def test_bulk_plan_and_new_pages(D, dtype, fmt, calls, classes):
     parity.compare_sequences(ob.cache, gc, [(s, s, 0) for s in range(S)], check_bytes=True)
 
 
+
+@pytest.mark.parametrize("D,dtype,fmt,calls,classes", [
+    (64, torch.bfloat16, "int", [[257], [255], [257], [513]], 3),               # one sequence: a token more than 256, where the plan takes 512 threads, and fewer
+    (128, torch.bfloat16, "int", [[511, 512, 513], [1, 1600, 2]], 3),           # a token a thread, one more, and sequences with hardly any beside long ones
+    (64, torch.float16, "int", [[33500], [9000]], 1),                           # lists of more pages than 512 threads keep the masks of
+    (64, torch.bfloat16, "fp", [[4096, 4097], [4608, 300]], 2),                 # windows
+])
+def test_plan_of_long_prompts(D, dtype, fmt, calls, classes):
+    test_bulk_plan_and_new_pages(D, dtype, fmt, calls, classes)
+
+
 @pytest.mark.parametrize("n_tok", [40, 100])
 def test_groups_out_of_binary16_range(n_tok):
     """zero-points that overflow to -inf and +inf next to a finite scale, ranges whose scale overflows, equal values, tiny ranges: both
