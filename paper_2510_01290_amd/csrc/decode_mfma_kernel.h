@@ -262,10 +262,14 @@ struct PairIds {
   int pid_a, pid_b;
   uint32_t live_a, live_b;
   int idx_a, idx_b;   // positions in the type's page list (idx_b = -1: no second page); used by STAT only
-  // STAT: the pooled score of the lane's token to its place among the type's, of which there are `room` pages (a scalar branch)
-  __device__ __forceinline__ void keep_a(float* stat, int room, int lane, float u) const { keep(stat, room, lane, u, idx_a); }
-  __device__ __forceinline__ void keep_b(float* stat, int room, int lane, float u) const { keep(stat, room, lane, u, idx_b); }
-  static __device__ __forceinline__ void keep(float* stat, int room, int lane, float u, int idx) {
+  // STAT: the pooled scores of the lane's tokens, ua and ub the largest of the lane's heads, to their places among the type's, of which there
+  // are `room` pages (a scalar branch)
+  static constexpr int kStores = 0;
+  __device__ __forceinline__ void keep(float* stat, int room, int lane, float ua, float ub) const {
+    put(stat, room, lane, col_max(ua), idx_a);   // (the same in the four lanes of a token, which store it to one place)
+    put(stat, room, lane, col_max(ub), idx_b);
+  }
+  static __device__ __forceinline__ void put(float* stat, int room, int lane, float u, int idx) {
     if (idx >= 0 && idx < room) stat[(int64_t)idx * kPage + (lane & (kPage - 1))] = u;
   }
 };
@@ -273,9 +277,11 @@ struct PairIds {
 struct QuadIds {
   uint32_t live_a, live_b;
   int at_a, at_b;   // STAT: where the lane's tokens stand among the type's pooled scores (negative: nowhere)
-  __device__ __forceinline__ void keep_a(float* stat, int room, int, float u) const { keep(stat, room, u, at_a); }
-  __device__ __forceinline__ void keep_b(float* stat, int room, int, float u) const { keep(stat, room, u, at_b); }
-  static __device__ __forceinline__ void keep(float* stat, int room, float u, int at) {
+  __device__ __forceinline__ void keep(float* stat, int room, int, float ua, float ub) const {
+    put(stat, room, col_max(ua), at_a);
+    put(stat, room, col_max(ub), at_b);
+  }
+  static __device__ __forceinline__ void put(float* stat, int room, float u, int at) {
     if (at >= 0 && at < room * kPage) stat[at] = u;
   }
 };
@@ -335,6 +341,32 @@ __device__ __forceinline__ void wait_loads() {   // until at most N of the wave'
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 __device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
+// Ids of a pair of pages that stand side by side in the list
+struct ListIds {
+  int pid_a, pid_b;
+  uint32_t live_a, live_b;
+  int idx;   // STAT: twice the first one's position in the type's page list, plus one where there is a second
+  // One store a pair, always, so that the waits of the ring can count it: two, which they did not count, made a wave wait for its next pairs'
+  // loads: 200 x 1k..10k tokens, statistic included, 294 us, now 289, 32 x 2k..20k of 40 heads 140 and 136, 64 x 1k..10k at head_dim 64 70 and 68
+  static constexpr int kStores = 1;
+  __device__ __forceinline__ void keep(float* stat, int room, int lane, float ua, float ub) const {
+    // rows (0, 1, 2, 3) of ua and ub: the larger of a0 and a1, b0 and b1, a2 and a3, b2 and b3, then of the halves: a, b, a, b
+    auto r16 = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, ua), __builtin_bit_cast(uint32_t, ub), false, false);
+    const uint32_t w = __builtin_bit_cast(uint32_t, fmaxf(__builtin_bit_cast(float, (uint32_t)r16[0]), __builtin_bit_cast(float, (uint32_t)r16[1])));
+    auto r32 = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+    const float u = fmaxf(__builtin_bit_cast(float, (uint32_t)r32[0]), __builtin_bit_cast(float, (uint32_t)r32[1]));
+    const int first = idx >> 1, pages = min((idx & 1) + 1, room - first);
+    if (pages > 0) {
+      // (all lanes are on, before and after; wait states as for the direct copies)
+      float* const dst = (float*)scalar_ptr((const uint8_t*)(stat + (int64_t)first * kPage));
+      asm volatile("s_mov_b64 exec, %3\n\ts_nop 4\n\tglobal_store_dword %0, %1, %2\n\ts_mov_b64 exec, -1"
+                   ::"v"(4 * lane), "v"(u), "s"(dst), "s"((1ull << (kPage * pages)) - 1ull) : "memory");
+    } else {
+      wait_loads<0>();   // no room, no store: with nothing outstanding the next waits hold all the same
+    }
+  }
+};
 
 // The page pairs an item works on, as one wave sees them.  The item's share of the three page lists is cut into chunks of
 // 2^shift consecutive pairs, type after type; chunk numbers come from the workgroup's ticket counter.  The ids and
@@ -432,14 +464,14 @@ struct Stream {
   }
   // the pair at hand, if it is one of the x-th type walked (want): its ids and masks are waited for here and not before
   int want;
-  __device__ __forceinline__ bool next(PairIds& id) const {
+  typedef ListIds Ids;
+  __device__ __forceinline__ bool next(ListIds& id) const {
     if (sec != want) return false;
     id.pid_a = arrived(pid_a);
     id.pid_b = arrived(pid_b);
     id.live_a = (uint32_t)arrived(msk_a) & 0xFFFFu;
     id.live_b = (uint32_t)(arrived(msk_b) & (0 - more_pages)) & 0xFFFFu;
-    id.idx_a = pg;
-    id.idx_b = more_pages ? pg + 1 : -1;
+    id.idx = 2 * pg + more_pages;
     return true;
   }
 };
@@ -451,7 +483,9 @@ __device__ __forceinline__ void stream_pairs(Runner& run, Source& q, const think
   using Dma = BlockDma<Runner::kBlockBytes>;
   constexpr int kPairBytes = 2 * Runner::kBlockBytes, kOps = 2 * Dma::kOps;
   constexpr int kSlots = RING / kPairBytes;
-  static_assert(kSlots >= 1 && kSlots <= 32 && (kSlots - 1) * kOps < 64, "the ring holds a pair, the waits six bits");
+  typedef typename Source::Ids Ids;
+  constexpr int kStores = Runner::kStat ? Ids::kStores : 0;
+  static_assert(kSlots >= 1 && kSlots <= 32 && (kSlots - 1) * kOps + kSlots * kStores < 64, "the ring holds a pair, the waits six bits");
   const int lane = run.lane;
   const uint32_t voff = 16 * lane;
   const uint32_t page_bytes = __builtin_amdgcn_readfirstlane(v.cfg.n_kv_heads * Runner::kBlockBytes);
@@ -459,7 +493,7 @@ __device__ __forceinline__ void stream_pairs(Runner& run, Source& q, const think
   int f_live = 0, f_ia = 0, f_ib = 0;   // lane s: what slot s holds (live bits of both pages; STAT: their list positions)
   // asks for the next live pair in slot, moves on; false: there is none
   auto issue = [&](int slot) -> bool {
-    PairIds id;
+    Ids id;
     while (q.next(id)) {
       const bool on = (id.live_a | id.live_b) != 0;
       if (on) {
@@ -468,7 +502,9 @@ __device__ __forceinline__ void stream_pairs(Runner& run, Source& q, const think
         Dma::issue(at + Runner::kBlockBytes, scalar_ptr(base + (uint64_t)(uint32_t)id.pid_b * page_bytes), voff);
         const bool mine = lane == slot;
         f_live = mine ? (int)(id.live_a | id.live_b << 16) : f_live;
-        if constexpr (Runner::kStat) {
+        if constexpr (kStores) {
+          f_ia = mine ? id.idx : f_ia;
+        } else if constexpr (Runner::kStat) {
           f_ia = mine ? id.idx_a : f_ia;
           f_ib = mine ? id.idx_b : f_ib;
         }
@@ -481,21 +517,29 @@ __device__ __forceinline__ void stream_pairs(Runner& run, Source& q, const think
   int flying = 0;
 #pragma nounroll
   while (flying < kSlots && issue(flying)) ++flying;
-  int slot = 0;
+  int slot = 0, first = kSlots;   // (pairs to go until there has been a store for each of the ring's slots)
 #pragma nounroll
   while (flying > 0) {
-    // the oldest pair has landed when only the others' loads are left (with fewer pairs in flight all are waited for: the
-    // end is near)
-    if (flying == kSlots) wait_loads<(kSlots - 1) * kOps>();
-    else wait_loads<0>();
+    // The oldest pair has landed when only the others' loads are left, and what was stored since it was asked for: operations of one
+    // kind or the other are reported done in their order (with fewer pairs in flight all are waited for: the end is near).
+    if (flying != kSlots) {
+      wait_loads<0>();
+    } else if (kStores == 0 || first > 0) {
+      wait_loads<(kSlots - 1) * kOps>();
+      if constexpr (kStores) --first;
+    } else {
+      wait_loads<(kSlots - 1) * kOps + kSlots * kStores>();
+    }
     const LdsPtr blk_a = (LdsPtr)(uintptr_t)(ring + slot * kPairBytes), blk_b = blk_a + Runner::kBlockBytes;
     typename Runner::Pair r;
     run.load_k(r, blk_a, blk_b);
     const uint32_t live = (uint32_t)__builtin_amdgcn_readlane(f_live, slot);
-    PairIds cur;
+    Ids cur;
     cur.live_a = live & 0xFFFFu;
     cur.live_b = live >> 16;
-    if constexpr (Runner::kStat) {
+    if constexpr (kStores) {
+      cur.idx = __builtin_amdgcn_readlane(f_ia, slot);
+    } else if constexpr (Runner::kStat) {
       cur.idx_a = __builtin_amdgcn_readlane(f_ia, slot);
       cur.idx_b = __builtin_amdgcn_readlane(f_ib, slot);
     }
@@ -518,6 +562,7 @@ struct VisiblePages {
   LdsWords pid, idx;
   LdsHalves msk;
   int n, i, end, step;
+  typedef PairIds Ids;
   __device__ __forceinline__ bool next(PairIds& id) const {
     if (i >= end) return false;
     const int a = 2 * i, b = min(a + 1, n - 1);
@@ -721,15 +766,14 @@ struct Softmax {
       }
     }
     if constexpr (STAT) {
-      // pooled scores: maximum over the heads of the group, i.e. over the lane's heads and the four lanes of a token
+      // pooled scores: maximum over the heads of the group, i.e. over the lane's heads here, then the four lanes of a token
       auto pooled = [&](const float* sc) {
         float u = -INFINITY;
 #pragma unroll
         for (int i = 0; i < NS; ++i) u = head_of<GP>(lane >> 4, i) < G ? fmaxf(u, sc[i] * kappa) : u;
-        return col_max(u);   // the same in the four lanes of a token, which store it to one place
+        return u;
       };
-      id.keep_a(stat, stat_room, lane, pooled(sa));
-      id.keep_b(stat, stat_room, lane, pooled(sb));
+      id.keep(stat, stat_room, lane, pooled(sa), pooled(sb));
     }
   }
   // Online softmax: the weights are 2^(score - m) with m a reference that is at most `slack` below the maximum seen.  It

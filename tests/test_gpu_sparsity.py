@@ -186,6 +186,48 @@ def test_sparsity_mean_over_the_heads(H, shift):
     assert float(want[0]) > 0.02
 
 
+@pytest.mark.parametrize("D,G,fmt,bits", [(128, 4, 0, (8, 2, 4)), (128, 8, 0, (2, 2, 2)), (64, 8, 0, (4, 4, 8)), (128, 4, 1, (2, 4, 8)), (64, 2, 1, (8, 8, 2))])
+def test_sparsity_of_many_pairs_a_wave(D, G, fmt, bits):
+    """waves with more page pairs than their ring has slots, lists that end on half a pair: each sequence's statistic as it is alone, where a wave has a
+    few pairs (the scores do not depend on the split, so the counts are the same: two roundings to binary32), and attention's results as without
+    the statistic (another split: sums of at most 6,000 weights in binary32, relative 6,000 * 2^-24 at the very most)"""
+    from paper_2510_01290_amd import binding as B
+    H, S = 8, 48
+    ctx = [600 + 113 * i for i in range(S)]
+    n = sum(ctx)
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(D + G)
+    kv = [torch.randn((n, H, D), generator=gen, device="cuda:0").half() for _ in range(2)]
+    q = (torch.randn((S, H * G, D), generator=gen, device="cuda:0") * 2).half()
+    seq = torch.repeat_interleave(torch.arange(S), torch.tensor(ctx)).int().cuda()
+    pos = torch.cat([torch.arange(c) for c in ctx]).int().cuda()
+    cls = (torch.arange(n) // 1700 % 3).to(torch.uint8).cuda()
+    c = B.Cache(1, G * H, H, D, bits, S, 400, [n // 16 + 3 * S + 8] * 3, fmt=fmt, fp8_scale=(0.05, 0.05))
+    B.thinkv_append_quantized(c, 0, kv[0], kv[1], seq, pos, cls)
+    pages = int(c.n_pages[:, 0].sum(-1).max())
+
+    def run(ids, stat):
+        k = len(ids)
+        out, lse = torch.empty((k, H * G, D), dtype=torch.float32, device="cuda:0"), torch.empty((k, H * G), dtype=torch.float32, device="cuda:0")
+        sp = torch.full((k,), -1.0, dtype=torch.float32, device="cuda:0")
+        sid, qp = torch.tensor(ids, dtype=torch.int32, device="cuda:0"), torch.tensor([ctx[i] for i in ids], dtype=torch.int32, device="cuda:0")
+        if stat:
+            B.thinkv_decode_attention_sparsity(c, 0, q[ids].contiguous(), out, lse, sp, sid, qp, 0, D ** -0.5, pages)
+        else:
+            B.thinkv_decode_attention(c, 0, q[ids].contiguous(), out, lse, sid, qp, 0, D ** -0.5, pages)
+        torch.cuda.synchronize()
+        return out, lse, sp
+    everyone = list(range(S))
+    out, lse, sp = run(everyone, True)
+    plain, plain_lse, _ = run(everyone, False)
+    assert float((out - plain).abs().max()) <= 6000 * 2.0 ** -24 * float(plain.abs().max())
+    assert float((lse - plain_lse).abs().max()) <= 6000 * 2.0 ** -24 + 2.0 ** -22 * float(plain_lse.abs().max())
+    for i in (0, 1, 17, S - 2, S - 1):
+        alone = run([i], True)[2]
+        assert float((alone[0] - sp[i]).abs()) <= 1.2e-7, i
+    assert float(sp.min()) > 0.02
+
+
 def test_sparsity_context_bound_too_small_is_safe():
     _say("a context bound below the true page count: counted over the first pages only, nothing written out of bounds")
     geom = synth.Geometry(1, 8, 2, 64, "f16", (8, 2, 4))
