@@ -21,6 +21,10 @@ __global__ __launch_bounds__(256) void evict_kernel(thinkv_view v, int layer, co
 // multiples of 16 bytes): a page can hold slots that were never written; attention reads them and discards them by their
 // live bit, which is only safe if their scales and zero-points are finite numbers.  (One launch instead of one for the
 // tables and one an arena, each of which starts on an idle chip: 60 MB of arenas in 14 us instead of 26.)
+// Two blocks to a compute unit, four stores of a thread at once: the rate of the stores bounds large arenas, and with eight blocks a unit
+// the start of so many waves, each of which goes round all of these loops, bounds small ones.  With the append of 16 prompts of 1k to 4k tokens, of 4 of
+// 500 to 2,000 at head_dim 64, of 2 of 200 tokens, us: eight blocks and a store at a time 78.7, 24.8, 16.8, now 77.8, 23.9, 15.8 (four blocks 80.9, 24.1,
+// 16.0).  Non-temporal stores take the arenas out of the caches, where an append finds them: 82.9.
 __global__ __launch_bounds__(256) void init_kernel(thinkv_view v) {
   const thinkv_config& c = v.cfg;
   const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -49,7 +53,15 @@ __global__ __launch_bounds__(256) void init_kernel(thinkv_view v) {
   for (int k = 0; k < 3; ++k) {
     const int64_t n16 = v.arena_pages[k] * (int64_t)c.n_kv_heads * block_geom(c.bits_of_class[k], c.head_dim, c.format).block_bytes / 16;
     uint4* const p = (uint4*)v.arena[k];
-    for (int64_t i = tid; i < n16; i += stride) p[i] = uint4{0u, 0u, 0u, 0u};
+    const uint4 zero = {0u, 0u, 0u, 0u};
+    int64_t i = tid;
+    for (; i + 3 * stride < n16; i += 4 * stride) {
+      p[i] = zero;
+      p[i + stride] = zero;
+      p[i + 2 * stride] = zero;
+      p[i + 3 * stride] = zero;
+    }
+    for (; i < n16; i += stride) p[i] = zero;
   }
 }
 
@@ -60,7 +72,7 @@ int launch_evict(const thinkv_view& v, int layer, const int32_t* ev_seq, const i
 }
 
 int launch_init(const thinkv_view& v, hipStream_t st) {
-  hipLaunchKernelGGL(init_kernel, dim3(2048), dim3(256), 0, st, v);
+  hipLaunchKernelGGL(init_kernel, dim3(512), dim3(256), 0, st, v);
   return hipGetLastError() == hipSuccess ? THINKV_OK : THINKV_E_HIP;
 }
 

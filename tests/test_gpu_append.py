@@ -111,3 +111,22 @@ def test_new_pages_of_scattered_and_few_tokens(D, dtype, fmt, S, lens, share):
     assert np.array_equal(hg, ob.append(0, k, v, ts, tp, tc))
     parity.compare_bookkeeping_full(ob.cache, gc)
     parity.compare_sequences(ob.cache, gc, [(s, s, 0) for s in range(S)], check_bytes=True)
+
+
+@pytest.mark.parametrize("pages", [(1, 2, 3), (257, 1030, 4099), (5000, 9001, 0)])
+@pytest.mark.parametrize("D,H", [(64, 1), (128, 8)])
+def test_reset_clears_the_arenas_and_nothing_else(pages, D, H):
+    """stores in fours and the rest one by one: every byte of the pages of the view, none behind them"""
+    from paper_2510_01290_amd import binding as B
+    c = B.Cache(1, 2 * H, H, D, (8, 2, 4), 3, 40, [n + 1 for n in pages])
+    for t in c.arena + c.slot_pos:
+        t.fill_(0x5A)
+    for k, n in enumerate(pages):
+        c.view.arena_pages[k] = n
+    B.thinkv_init_view(c)
+    torch.cuda.synchronize()
+    for k, n in enumerate(pages):
+        used = n * c.page_bytes[k]
+        assert not bool(c.arena[k][:used].any()) and bool((c.arena[k][used:] == 0x5A).all())
+        assert bool((c.slot_pos[k][:n] == -1).all()) and bool((c.slot_pos[k][n:] == 0x5A).all())
+        assert int(c.free_top[k]) == n
