@@ -1279,6 +1279,93 @@ __device__ inline Place place_in_order(const PlanArgs& a, int b) {
   return at;
 }
 
+// A cut's list [lo, lo + n) (at most kTbeMaxTokens: larger segments are never cut) into ascending order of the positions, by one wave.  A segment's
+// positions lie close together: within 2,048 of each other, and no two alike, a bit each in a row of words says by counting how many are before a token.
+// Otherwise a token's rank is the number of smaller keys (position, then place in the list), four keys of the list compared at a time.
+// keys: LDS, kTbeMaxTokens of them.  (By keys alone, which is 640 comparisons of 64 bits a lane for 160 tokens, the fill kernel of the plan below took 24 us, now 13.)
+struct CutList {
+  int lo, n;
+  int pos[kPT], h[kPT];
+  __device__ __forceinline__ void load(const PlanArgs& a, int lo_, int n_) {
+    lo = lo_;
+    n = n_;
+#pragma unroll
+    for (int q = 0; q < kPT; ++q) {
+      const int i = (threadIdx.x & 63) + 64 * q;
+      pos[q] = 0x7FFFFFFF;
+      h[q] = 0;
+      if (i < n) {
+        pos[q] = a.tok_seq[lo + i];
+        h[q] = a.tok_handle[lo + i];
+      }
+    }
+  }
+};
+__device__ __forceinline__ void sort_cut(const PlanArgs& a, const CutList& l, int seq, long long* keys) {
+  const int lane = threadIdx.x & 63, n = l.n;
+  auto settle = [] {   // (a wave's LDS operations happen in order)
+    __builtin_amdgcn_wave_barrier();
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  };
+  uint32_t* const words = (uint32_t*)keys;
+  words[lane] = 0u;
+  int rank[kPT] = {}, first = 0x7FFFFFFF;
+#pragma unroll
+  for (int q = 0; q < kPT; ++q) first = l.pos[q] < first ? l.pos[q] : first;
+  first = 0x7FFFFFFF - last_lane(wave_scan(0x7FFFFFFF - first, [](int x, int y) { return x > y ? x : y; }));   // (of all lanes)
+  settle();
+  bool apart = true;   // close together, and no two alike
+#pragma unroll
+  for (int q = 0; q < kPT; ++q)
+    if (lane + 64 * q < n) {
+      const uint32_t at = (uint32_t)l.pos[q] - (uint32_t)first;
+      if (at >= 2048u) apart = false;
+      else if (atomicOr(&words[at >> 5], 1u << (at & 31u)) >> (at & 31u) & 1u) apart = false;
+    }
+  settle();
+  if (__all(apart)) {
+    const int mine = __popc(words[lane]);
+    words[64 + lane] = (uint32_t)(wave_scan(mine, [](int x, int y) { return x + y; }) - mine);
+    settle();
+#pragma unroll
+    for (int q = 0; q < kPT; ++q)
+      if (lane + 64 * q < n) {
+        const uint32_t at = (uint32_t)l.pos[q] - (uint32_t)first;
+        rank[q] = (int)words[64 + (at >> 5)] + __popc(words[at >> 5] & ((1u << (at & 31u)) - 1u));
+      }
+  } else {
+    long long key[kPT];
+#pragma unroll
+    for (int q = 0; q < kPT; ++q) {
+      const int i = lane + 64 * q;
+      key[q] = i < n ? (long long)l.pos[q] << 8 | i : 0x7FFFFFFFFFFFFFFFll;
+      keys[i] = key[q];
+    }
+    settle();
+    for (int i = 0; i < n; i += 4) {
+      const long long o[4] = {keys[i], keys[i + 1], keys[i + 2], keys[i + 3]};
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int q = 0; q < kPT; ++q) rank[q] += o[e] < key[q];
+    }
+  }
+  settle();
+#pragma unroll
+  for (int q = 0; q < kPT; ++q)
+    if (lane + 64 * q < n) {
+      a.tok_handle[l.lo + rank[q]] = l.h[q];
+      a.tok_seq[l.lo + rank[q]] = seq;
+    }
+}
+
+// Up to this many cuts a sequence, the workgroup that deals out a sequence's tokens sorts its lists as well, four for each of its sixteen waves at
+// most, which takes no longer than a launch of its own with a wave for every cut; beyond it would.  The plan, us, with a launch for the sort (by keys) / so: 32 sequences of
+// 10 cuts of 64 to 192 tokens fill and sort 8.8 + 9.7 / 13.2, 256 of 16 cuts of 128 29.0 / 20.8, 256 of 7 23.2 / 17.6, 1 of 32 cuts of 200 32.2 / 27.2; of 64 cuts, 32 of
+// 128 tokens 34.9 / 34.3, 1 of 200 39.4 / 40.1.
+constexpr int kSortHere = 64;
+
+template <bool SORT>
 __global__ __launch_bounds__(kPlanThreads) void tbe_fill_kernel(thinkv_view v, PlanArgs a) {
   const int b = blockIdx.x, tid = threadIdx.x;
   __shared__ unsigned long long s_sum[4];         // cuts and tokens of all sequences, and of those before this one
@@ -1361,51 +1448,33 @@ __global__ __launch_bounds__(kPlanThreads) void tbe_fill_kernel(thinkv_view v, P
     a.tok_seq[at] = pos;
     a.tok_handle[at] = h;
   });
+  if constexpr (SORT) {
+    __shared__ __attribute__((aligned(16))) long long s_key[kPlanThreads / 64][kTbeMaxTokens];
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    __syncthreads();
+    CutList l, next = {};
+    if (wave < n_cuts) l.load(a, s_off[wave], s_fill[wave]);
+    for (int cu = wave; cu < n_cuts; cu += kPlanThreads / 64) {
+      const int after = cu + kPlanThreads / 64;
+      if (after < n_cuts) next.load(a, s_off[after], s_fill[after]);
+      sort_cut(a, l, seq, s_key[wave]);
+      l = next;
+    }
+  }
 }
 
-// one wave per cut of the dense lists: ascending position inside the list.  A token's rank is the number of smaller keys (position,
-// then place in the list), four keys of the list compared at a time
+// one wave per cut of the dense lists
 __global__ __launch_bounds__(256) void tbe_sort_kernel(PlanArgs a) {
   __shared__ __attribute__((aligned(16))) long long s_key[4][kTbeMaxTokens];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int wave = threadIdx.x >> 6;
   const int cu = blockIdx.x * 4 + wave;
   if (cu >= a.counts[0]) return;   // the waves do not meet
-  const int lo = a.seg_offset[cu], n = a.seg_offset[cu + 1] - lo;   // at most kTbeMaxTokens: larger segments are never cut
-  const int seq = a.st_cut_seq[cu];
-  long long key[kPT];
-  int h[kPT], rank[kPT];
-#pragma unroll
-  for (int q = 0; q < kPT; ++q) {
-    const int i = lane + 64 * q;
-    rank[q] = 0;
-    key[q] = 0x7FFFFFFFFFFFFFFFll;
-    if (i < n) {
-      key[q] = (long long)a.tok_seq[lo + i] << 8 | i;
-      h[q] = a.tok_handle[lo + i];
-    }
-    s_key[wave][i] = key[q];
-  }
-  __builtin_amdgcn_wave_barrier();
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-  auto walk = [&](auto rows) {   // points of so many 64
-    for (int i = 0; i < n; i += 4) {
-      const long long o[4] = {s_key[wave][i], s_key[wave][i + 1], s_key[wave][i + 2], s_key[wave][i + 3]};
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-#pragma unroll
-        for (int q = 0; q < decltype(rows)::value; ++q) rank[q] += o[e] < key[q];
-    }
-  };
-  if (n <= 64) walk(std::integral_constant<int, 1>{});
-  else if (n <= 128) walk(std::integral_constant<int, 2>{});
-  else walk(std::integral_constant<int, kPT>{});
-#pragma unroll
-  for (int q = 0; q < kPT; ++q)
-    if (lane + 64 * q < n) {
-      a.tok_handle[lo + rank[q]] = h[q];
-      a.tok_seq[lo + rank[q]] = seq;
-    }
+  const int lo = a.seg_offset[cu];
+  CutList l;
+  l.load(a, lo, a.seg_offset[cu + 1] - lo);
+  sort_cut(a, l, a.st_cut_seq[cu], s_key[wave]);
 }
+
 
 int launch_tbe_plan(const thinkv_view& v, int layer, const int32_t* seq_ids, const int32_t* seg_start, const uint8_t* seg_type,
                     const int32_t* n_segs, const uint8_t* transition_ended, int32_t* seg_count, int rule, int B, int max_segs, int budget, int max_cuts,
@@ -1439,7 +1508,12 @@ int launch_tbe_plan(const thinkv_view& v, int layer, const int32_t* seq_ids, con
   a.cap_seg = cap_seg;
   a.cap_tok = cap_tok;
   if (B > 0) hipLaunchKernelGGL(tbe_count_plan_kernel, dim3(B), dim3(kPlanThreads), 0, st, v, a);
-  hipLaunchKernelGGL(tbe_fill_kernel, dim3(B > 0 ? B : 1), dim3(kPlanThreads), 0, st, v, a);
+  const dim3 each(B > 0 ? B : 1);
+  if (max_cuts <= kSortHere) {
+    hipLaunchKernelGGL(tbe_fill_kernel<true>, each, dim3(kPlanThreads), 0, st, v, a);
+    return hipGetLastError() == hipSuccess ? THINKV_OK : THINKV_E_HIP;
+  }
+  hipLaunchKernelGGL(tbe_fill_kernel<false>, each, dim3(kPlanThreads), 0, st, v, a);
   const int64_t most = (int64_t)B * max_cuts < cap_seg ? (int64_t)B * max_cuts : cap_seg;
   if (most > 0) hipLaunchKernelGGL(tbe_sort_kernel, dim3((unsigned)((most + 3) / 4)), dim3(256), 0, st, a);
   return hipGetLastError() == hipSuccess ? THINKV_OK : THINKV_E_HIP;

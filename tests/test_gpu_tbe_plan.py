@@ -89,3 +89,38 @@ def test_tbe_plan_of_many_sequences_into_short_lists(share_seg, share_tok, max_c
         assert np.array_equal(got["seg_keep"][:n_seg], w_keep) and np.array_equal(got["seg_offset"][:n_seg + 1], w_off)
         assert np.array_equal(got["tok_handle"][:n_tok], w_h) and np.array_equal(got["tok_seq"][:n_tok], w_seq)
         assert np.array_equal(dev, ora)
+
+
+@pytest.mark.parametrize("max_cuts", [1, 16, 17, 64, 65])
+def test_tbe_plan_sorts_lists_of_long_segments(max_cuts):
+    """lists of up to 250 tokens, sorted by the workgroup of their sequence (a wave has one to four of them) or, from 65 cuts on, by a launch of its own"""
+    test_tbe_plan_over_many_segments(250, None, 0, max_cuts, 2048, 1 << 16)
+    test_tbe_plan_over_many_segments(250, [1, 0, 1], 0, max_cuts, 60, 1 << 16)
+
+
+@pytest.mark.parametrize("num,den", [(40, 1), (9, 1), (1, 2)])
+@pytest.mark.parametrize("max_cuts", [20, 256])
+def test_tbe_plan_of_spread_and_of_equal_positions(num, den, max_cuts):
+    """lists whose positions are further apart than the row of bits reaches, close to that, or (two tokens to a position: in either order) not all different"""
+    from paper_2510_01290_amd import binding as B
+    n, width = 1840, 8
+    c = B.Cache(1, 2, 1, 64, (8, 2, 4), 1, 200, [400] * 3)
+    rng = np.random.default_rng(7)
+    pos = np.arange(n) * num // den
+    kv = torch.randn((n, 1, 64), device="cuda:0").half()
+    ten = lambda x, t: torch.tensor(np.ascontiguousarray(x), dtype=t, device="cuda:0")
+    h = torch.empty(n, dtype=torch.int32, device="cuda:0")
+    B.thinkv_append_quantized(c, 0, kv, kv, torch.zeros(n, dtype=torch.int32, device="cuda:0"), ten(pos, torch.int32), ten(rng.integers(0, 3, n), torch.uint8), h)
+    of = {int(a): int(p) for a, p in zip(h.cpu(), pos)}
+    assert len(of) == n
+    start = np.zeros((1, width), np.int32)
+    start[0] = np.arange(width) * 230 * num // den
+    got = _device_plan(c, 0, [0], start, np.zeros((1, width), np.uint8), np.array([width], np.int32), [1], 10 ** 6, max_cuts, 64, 4096, seg_count=np.zeros((1, width), np.int32))
+    n_seg, n_tok = got["counts"].tolist()
+    assert n_seg == width - 1 and n_tok == 230 * (width - 1)
+    for i in range(n_seg):
+        lo, hi = got["seg_offset"][i:i + 2]
+        listed = [of[int(x)] for x in got["tok_handle"][lo:hi]]
+        assert listed == sorted(pos[(pos >= start[0, i]) & (pos < start[0, i + 1])].tolist())
+        assert len(set(got["tok_handle"][lo:hi].tolist())) == hi - lo
+    assert not np.any(got["tok_seq"][:n_tok])
