@@ -522,7 +522,10 @@ __device__ __forceinline__ void choose_survivors(const TbeArgs& a, int seg, int 
   constexpr int kThreads = 64 * W, kPer = kTbeMaxKeep / 4, kAhead = 4, kRows = 8;
   static_assert(POINTS <= 16 * W && 8 * kTbeMaxKeep <= kThreads, "a wave for sixteen points, eight lanes for a cluster");
   typedef float f32xk __attribute__((ext_vector_type(kPer)));   // a number for each of a lane's clusters, 4 i + quarter
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), dim = a.dim;
+  // (opaque: what follows from it would be worked out before a caller's loop over segments and held in registers that the products need)
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), dim = a.dim;
   const int quarter = lane >> 4, p = 16 * wave + (lane & 15);
   const bool here = p < n, first = here && quarter == 0;
   const int pc = here ? p : n - 1, tp = tri(pc);
