@@ -469,8 +469,8 @@ __global__ __launch_bounds__(kGramThreads, 4) void tbe_gram_kernel(thinkv_view v
 // ---- kmeans
 // W waves; LDS holds the matrix of POINTS points.  Up to kFewPoints: twelve waves, two workgroups a compute unit.  More: sixteen waves, a
 // compute unit to themselves.  (With the products of the points 192..255 in memory instead, 314 segments, us, before the keys went from the pages to the
-// matrix cores / with those in memory / now: 8 heads of 128, 200 to 256 tokens 473 / 534 / 342, 256 tokens 501 / 734 / 353; 8 of 64 337 / 497 / 235; 2 of 128
-// 251 / 384 / 195; 2 of 64 279 / 297 / 185; one segment of 256, 8 of 128, 165 / 268 / 142.)
+// matrix cores / with those in memory / now: 8 heads of 128, 200 to 256 tokens 473 / 534 / 305, 256 tokens 501 / 734 / 323; 8 of 64 337 / 497 / 189; 2 of 128
+// 251 / 384 / 159; 2 of 64 279 / 297 / 156; one segment of 256, 8 of 128, 165 / 268 / 136.)
 constexpr int kKmWaves = 12, kWholeWaves = 16;
 constexpr int kPT = kTbeMaxTokens / 64;                   // tokens per lane of a wave that sorts a list
 constexpr int kWords = kTbeMaxTokens / 32;
@@ -517,6 +517,8 @@ __device__ __forceinline__ float add_quarters(float x) {   // the sum over the l
 // take 10 us for all products of an iteration, 4 for a few clusters', 1.5 for the assignment.  (A point a lane and clusters dealt to groups of waves: 9, 2 to 8
 // and 2.1, the largest cluster being what everybody waited for.  The sums as a matrix product with the 0/1 matrix of the members, in
 // binary32 on the matrix cores: 5 a tile of sixteen clusters, however few of them moved; 314 segments of 64 to 192 tokens 177 us instead of 145.)
+// (With 256 points and 64 clusters, four members each, a step and its sum over the quarters cost more than four additions of a point a lane: one such segment,
+// 2 heads of 64, 87 us instead of 82, 314 of 200 to 256 tokens, 1 of 64, 143 and 139; 314 of 8 of 128 305 and 341.)
 template <int W, int POINTS>
 __device__ __forceinline__ void choose_survivors(const TbeArgs& a, int seg, int lo, int n, int k, KmScratch<W, POINTS>& sm) {
   constexpr int kThreads = 64 * W, kPer = kTbeMaxKeep / 4, kAhead = 4, kRows = 8;
