@@ -910,15 +910,15 @@ int launch_tbe_select(const thinkv_view& v, int layer, const int32_t* tok_seq, c
 // A live token belongs to the segment whose start is the largest one not above its position
 // (the block table's start-index column, Sec. 5.2).
 //
-// Three kernels.  count (one workgroup per examined sequence): live tokens per segment (a thread takes four slots of a page:
+// Two kernels, or three.  count (one workgroup per examined sequence): live tokens per segment (a thread takes four slots of a page:
 // one load of positions, a binary search in the segment starts, held in LDS, where a slot leaves the segment of the one
 // before), then the plan, whose cuts wait in a staging area.  fill (one workgroup per sequence): the sequence's place in
 // the dense output lists from the totals of the sequences before it; where the lists are too short for all, the sequences
 // in order keep the leading cuts that still fit (the rest waits for the next call).  Then the list offsets of its cuts by a
-// prefix sum, and its live tokens are dealt to their lists.  sort (one wave per cut): each list is put in ascending
-// position by a rank sort in LDS, so the output does not depend on the order in which threads
-// got there.  32 sequences of 2k to 4k tokens, 314 cuts, us, with sixteen slots of three pages a thread, one thread for the
-// second case and a kernel for the offsets / now: count 39 / 11, offsets 9 / -, fill 32 / 9, sort 19 / 10.
+// prefix sum, and its live tokens are dealt to their lists.  sort (one wave per cut, in the fill kernel or, where a sequence may
+// have many cuts, by a launch of its own): each list is put in ascending position, so the output does not depend on the order in which threads
+// dealt.  32 sequences of 2k to 4k tokens, 314 cuts, us (sixteen slots of three pages a thread, one thread for the
+// second case and a kernel for the offsets / now): count 39 / 10, offsets 9 / -, fill 32 and sort 19 / 13 together.
 constexpr int kMaxSegs = THINKV_TBE_MAX_SEGS;
 constexpr int kRetention[5] = {64, 32, 16, 8, 4};
 constexpr int kPlanThreads = 1024;
