@@ -258,7 +258,7 @@ static int decode_common(const thinkv_view* view, int32_t layer, const void* q, 
     // 97.7 / 96.7, 64 x 1k..10k 70.3 / 70.0, 256 x 1k 126.8 / 127.6.
     unsigned long long* const sum = (unsigned long long*)(a.stat + (int64_t)B * view->cfg.n_kv_heads * a.stat_stride);
     const int64_t heads = (int64_t)B * view->cfg.n_kv_heads;
-    if (view->cfg.n_kv_heads >= 2 && view->cfg.n_kv_heads < 32768 && heads <= 2 * compute_units() && ((uintptr_t)sum & 7) == 0) a.stat_sum = sum;
+    if (view->cfg.n_kv_heads >= 2 && view->cfg.n_kv_heads <= kStatHeads && heads <= 2 * compute_units() && ((uintptr_t)sum & 7) == 0) a.stat_sum = sum;
     rc = launch_stat_fill(*view, a, st);
     if (rc) return rc;
     rc = launch_decode_mfma_stat(*view, a, st);

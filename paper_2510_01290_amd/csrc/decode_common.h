@@ -38,6 +38,11 @@ __host__ __device__ constexpr int window_lds_bytes(int head_dim, bool stat) {
   return window_waves(head_dim) * window_ring_bytes(head_dim) + 3 * kWindowList * (stat ? 10 : 6) + 64;
 }
 
+// The statistic's sum over the kv-heads in one word (stat_count_kernel): for up to 2^lg heads a count of lg + 1 bits above 63 - lg bits in units
+// of 2^-(62 - 2 lg).  A fraction is a binary32 quotient of counts, 24 bits from 2^-31 on, so a whole number of units for up to sixteen heads whatever the
+// context, for 32 up to 2^29 tokens and for 64 up to 2^27, whose keys and values no card holds: nothing is lost, and the mean is rounded once.
+constexpr int kStatHeads = 64;
+
 // Items dealt over a batch (deal_item): fewest pages a wave is worth.
 constexpr int kDealPages = 8;
 

@@ -13,7 +13,7 @@ import torch
 import parity
 from oracle import attention as oattn
 from oracle import sparsity as osp
-from paper_2510_01290_amd import synth
+from paper_2510_01290_amd import binding as B, synth
 
 pytestmark = pytest.mark.gpu
 
@@ -242,3 +242,25 @@ def test_sparsity_context_bound_too_small_is_safe():
     got, lse, sp = _gpu(gc, wl, 0, max_ctx_pages=true_pages // 2)
     assert np.all((sp >= 0.0) & (sp <= 1.0))
     assert bool((guard[nb:nb + 4096] == 0x5A).all().item()), "wrote past the workspace it asked for"
+
+
+@pytest.mark.parametrize("H", [2, 3, 8, 12, 64, 66])
+def test_mean_of_small_fractions(H):
+    """a token or none a head that is negligible among 20,000: fractions of 5e-5, whose 24 bits the mean over the heads keeps.  Up to 64 heads they are added
+    exactly and the mean is rounded once (half an ulp; the quotient in binary64 before it another sliver: an ulp is allowed), beyond in binary32, one rounding a
+    head and the division's"""
+    _say(f"sparsity statistic, mean of small fractions over {H} heads")
+    n, D = 20000, 64
+    dev = lambda x: torch.from_numpy(np.ascontiguousarray(x)).to("cuda:0")  # noqa: E731
+    gc = B.Cache(1, H, H, D, (8, 2, 4), 1, n // 16 + 4, [n // 16 + 4] * 3)
+    k = torch.ones((n, H, D), dtype=torch.float16, device="cuda:0")
+    odd = [h for h in range(H) if h % 3 != 1]                      # heads with a token far below the others
+    for h in odd:
+        k[(777 * (h + 1)) % n, h] = -60.0
+    cls = (np.arange(n) // 100 % 3).astype(np.uint8)
+    B.thinkv_append_quantized(gc, 0, k, k, dev(np.zeros(n, np.int32)), dev(np.arange(n, dtype=np.int32)), dev(cls))
+    q = torch.ones((1, H, D), dtype=torch.float16, device="cuda:0")
+    out, sp = torch.empty((1, H, D), dtype=torch.float32, device="cuda:0"), torch.empty(1, dtype=torch.float32, device="cuda:0")
+    B.thinkv_decode_attention_sparsity(gc, 0, q, out, None, sp, dev(np.zeros(1, np.int32)), dev(np.array([n - 1], np.int32)), 0, D ** -0.5, n // 16 + 3)
+    want = float(np.float32(1.0) / np.float32(n)) * len(odd) / H
+    assert abs(float(sp.item()) - want) <= want * (2.0 ** -23 if H <= 64 else (H + 1) * 2.0 ** -24), (float(sp.item()), want)
