@@ -59,6 +59,39 @@ def test_plan_of_long_prompts(D, dtype, fmt, calls, classes):
     test_bulk_plan_and_new_pages(D, dtype, fmt, calls, classes)
 
 
+@pytest.mark.parametrize("H,D,fmt,n,heads_per_block", [(3, 64, "int", 22000, 2), (3, 64, "int", 43760, 3), (5, 64, "int", 26300, 4), (5, 128, "fp", 26300, 4),
+                                                       (6, 64, "int", 22000, 4), (9, 64, "fp", 14600, 4), (8, 64, "int", 16400, 4)])
+def test_heads_of_a_block(H, D, fmt, n, heads_per_block):
+    """blocks of two, three and four heads, and a last one of one or two: every head's bytes are those of a cache with that head alone (whose
+    tables, and whose bytes at these sizes, the tests above compare with the oracle's)"""
+    from paper_2510_01290_amd import binding as B
+    print(f"[gpu] append, heads of a block: H={H} D={D} {fmt} {n}", flush=True)
+    per = (H * ((n + 15) // 16) + 4095) // 4096
+    assert min(4 if per > 2 else per, H) == heads_per_block
+    rng = np.random.default_rng(H + D)
+    d = lambda x: torch.from_numpy(np.ascontiguousarray(x)).to("cuda:0")  # noqa: E731
+    cls = np.repeat(np.arange(n), rng.integers(1, 120, n))[:n] % 3
+    gen = torch.Generator(device="cuda:0").manual_seed(H)
+    k, v = (torch.randn((n, H, D), generator=gen, device="cuda:0").to(torch.bfloat16) for _ in range(2))
+    tok = [d(x) for x in (np.arange(n, dtype=np.int32) // (n // 2 + 1), np.arange(n, dtype=np.int32), cls.astype(np.uint8))]
+
+    def filled(heads):
+        c = B.Cache(1, heads.stop - heads.start, heads.stop - heads.start, D, (8, 4, 2), 2, n // 16 + 4, [n // 16 + 8] * 3, fmt=B.FMT_FP if fmt == "fp" else B.FMT_INT,
+                    fp8_scale=(0.05, 0.05))
+        h = torch.empty(n, dtype=torch.int32, device="cuda:0")
+        B.thinkv_append_quantized(c, 0, k[:, heads].contiguous(), v[:, heads].contiguous(), *tok, h)
+        return c, h
+
+    c, h = filled(slice(0, H))
+    assert int(c.dev_status.abs().sum()) == 0 and int(c.n_live.sum()) == n
+    for x in range(H):
+        one, h1 = filled(slice(x, x + 1))
+        assert torch.equal(h, h1) and torch.equal(c.block_table, one.block_table)
+        for t in range(3):
+            size = one.page_bytes[t]
+            assert torch.equal(c.arena[t].view(-1, H, size)[:, x], one.arena[t].view(-1, size)), (x, t)
+
+
 @pytest.mark.parametrize("n_tok", [40, 100])
 def test_groups_out_of_binary16_range(n_tok):
     """zero-points that overflow to -inf and +inf next to a finite scale, ranges whose scale overflows, equal values, tiny ranges: both
