@@ -125,14 +125,20 @@ __device__ inline void store_from_f32(void* p, int64_t i, int dtype, float v) {
   }
 }
 
-// inclusive scan over a wave (x not negative): by 1, 2, 4, 8 lanes inside rows of sixteen, then the rows' results onwards
-template <class T, class Op>
-__device__ __forceinline__ T wave_scan(T x, Op op) {
+// inclusive scan over a wave (x not negative): by 1, 2, 4, 8 lanes inside rows of sixteen (row_scan: no further), then the rows' results onwards
 #define TKV_STEP(CTRL, ROWS) x = op(x, __builtin_bit_cast(T, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, ROWS, 0xF, false)))
-  TKV_STEP(0x111, 0xF); TKV_STEP(0x112, 0xF); TKV_STEP(0x114, 0xF); TKV_STEP(0x118, 0xF); TKV_STEP(0x142, 0xA); TKV_STEP(0x143, 0xC);
-#undef TKV_STEP
+template <class T, class Op>
+__device__ __forceinline__ T row_scan(T x, Op op) {
+  TKV_STEP(0x111, 0xF); TKV_STEP(0x112, 0xF); TKV_STEP(0x114, 0xF); TKV_STEP(0x118, 0xF);
   return x;
 }
+template <class T, class Op>
+__device__ __forceinline__ T wave_scan(T x, Op op) {
+  x = row_scan(x, op);
+  TKV_STEP(0x142, 0xA); TKV_STEP(0x143, 0xC);
+  return x;
+}
+#undef TKV_STEP
 template <class T>
 __device__ __forceinline__ T last_lane(T x) { return __builtin_bit_cast(T, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), 63)); }
 

@@ -31,11 +31,11 @@ __host__ __device__ constexpr int exchange_bytes(int head_dim, int heads, bool f
 // Sliding-window layers: waves of a workgroup (as many as a compute unit holds; a page of each type per thread is scanned at a time), entries
 // of a type's list of what is visible, a wave's ring, and all LDS (rings, the lists' page ids, with the statistic list positions, and their
 // masks, counts per wave).
-constexpr int kWindowList = 1024;
+constexpr int kWindowList = 1024, kCounts = 16;
 __host__ __device__ constexpr int window_waves(int head_dim) { return 4 * decode_waves_per_simd(head_dim, false); }
 __host__ __device__ constexpr int window_ring_bytes(int head_dim) { return head_dim == 128 ? 14336 : 9216; }
 __host__ __device__ constexpr int window_lds_bytes(int head_dim, bool stat) {
-  return window_waves(head_dim) * window_ring_bytes(head_dim) + 3 * kWindowList * (stat ? 10 : 6) + 64;
+  return window_waves(head_dim) * window_ring_bytes(head_dim) + 3 * kWindowList * (stat ? 10 : 6) + 8 * kCounts;
 }
 
 // The statistic's sum over the kv-heads in one word (stat_count_kernel): for up to 2^lg heads a count of lg + 1 bits above 63 - lg bits in units

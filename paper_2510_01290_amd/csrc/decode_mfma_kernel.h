@@ -212,13 +212,29 @@ struct WaveState {
 template <int GP>
 __device__ __forceinline__ int head_of(int qd, int i) { return GP == 4 ? qd : 4 * (qd & 1) + 2 * (qd >> 1) + i; }
 
+// The lane, of which the compiler knows nothing: what follows from it is worked out where it is used, and no register is kept for it over
+// the loops between
+__device__ __forceinline__ int fresh_lane() {
+  int lane;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
+  return lane;
+}
+
+__device__ __forceinline__ int fresh(int scalar) {   // likewise
+  asm volatile("" : "+s"(scalar));
+  return scalar;
+}
+
+// x of lane `from`
+__device__ __forceinline__ float lane_of(float x, int from) { return __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(4 * from, __builtin_bit_cast(int, x))); }
+
 // score layout -> column layout, for values that are the same in all lanes of a row quad
 template <int GP>
 __device__ __forceinline__ float to_column(const float* x, int lane) {
   const int h = lane & (GP - 1);
-  if constexpr (GP == 4) return __shfl(x[0], 16 * h, 64);
+  if constexpr (GP == 4) return lane_of(x[0], 16 * h);
   const int src = 16 * ((h >> 2) + (h & 2));
-  const float a = __shfl(x[0], src, 64), b = __shfl(x[1], src, 64);
+  const float a = lane_of(x[0], src), b = lane_of(x[1], src);
   return (h & 1) ? b : a;
 }
 
@@ -265,7 +281,8 @@ struct PairIds {
   // STAT: the pooled scores of the lane's tokens, ua and ub the largest of the lane's heads, to their places among the type's, of which there
   // are `room` pages (a scalar branch)
   static constexpr int kStores = 0;
-  __device__ __forceinline__ void keep(float* stat, int room, int lane, float ua, float ub) const {
+  __device__ __forceinline__ void keep(float* stat, int room, int, float ua, float ub) const {
+    const int lane = fresh_lane();
     put(stat, room, lane, col_max(ua), idx_a);   // (the same in the four lanes of a token, which store it to one place)
     put(stat, room, lane, col_max(ub), idx_b);
   }
@@ -552,13 +569,12 @@ __device__ __forceinline__ void stream_pairs(Runner& run, Source& q, const think
   }
 }
 
-// Sliding-window layers, the paper's formats: pages of one type with a visible slot, as the workgroup's scan left them in LDS; a wave takes
+// Sliding-window layers: pages of one type with a visible slot, as the workgroup's scan left them in LDS; a wave takes
 // the pairs i, i + step, ... before end.
 typedef __attribute__((address_space(3))) const int32_t* LdsWords;
 typedef __attribute__((address_space(3))) const uint16_t* LdsHalves;
 template <bool STAT>
 struct VisiblePages {
-  static constexpr int kPair = 2;   // entries of a pair
   LdsWords pid, idx;
   LdsHalves msk;
   int n, i, end, step;
@@ -586,15 +602,14 @@ struct VisiblePages {
 // block's regions are made of 16-byte units of one quad each, and a direct load to LDS takes an address from every lane.
 template <bool STAT>
 struct SlotQuads {
-  static constexpr int kPair = 8;
   LdsWords pid, idx;   // page << 2 | quad (a page number has far fewer than thirty bits: pages of 768 bytes and more); list positions
   LdsHalves msk;       // visible slots of the quad
   int n, i, end, step;
 };
 
 // Unit u (16 bytes) of a block, u = 64 op + lane: the quad of the "page" it belongs to, and where it lies in the block of the page that the
-// quad comes from: at + quad there << shift.  In one register: quad | shift << 2 | at << 8.
-template <int D, int BITS>
+// quad comes from: at + quad there << shift.  As quad | shift << 2 | at << AT; at is a multiple of 16, so with AT 2 that is fifteen bits.
+template <int D, int BITS, int AT>
 __device__ __forceinline__ int quad_unit(int u) {
   constexpr int CB = block_geom(BITS, D).chunk_bytes, kCodes = 4 * CB, kMeta = D / 32 * 4;   // units of a code and of a meta region
   constexpr int kLog = (BITS == 2 ? 1 : (BITS == 4 ? 2 : 3)) + (D == 128 ? 2 : 1);           // of CB
@@ -610,7 +625,7 @@ __device__ __forceinline__ int quad_unit(int u) {
     quad = r >> kLog;
     shift = kLog + 4;
   }
-  return quad | shift << 2 | (16 * u - (quad << shift)) << 8;
+  return quad | shift << 2 | (16 * u - (quad << shift)) << AT;
 }
 
 // The pairs of quads i .. end - 1, through the wave's ring like stream_pairs
@@ -623,9 +638,11 @@ __device__ __forceinline__ void quad_pairs(Runner& run, Quads& q, const thinkv_v
   const int lane = run.lane;
   const uint32_t page_bytes = __builtin_amdgcn_readfirstlane(v.cfg.n_kv_heads * Runner::kBlockBytes);
   const uint8_t* const base = scalar_ptr(v.arena[cls] + (int64_t)hkv * Runner::kBlockBytes);
-  int unit[kPageOps];
+  constexpr int kUnitsOf = Runner::kTight ? 2 : 1, kAt = Runner::kTight ? 2 : 8;   // units to a register
+  int unit[(kPageOps + kUnitsOf - 1) / kUnitsOf] = {};
+  const int here = fresh_lane();   // (not for all widths at once before the loops around)
 #pragma unroll
-  for (int o = 0; o < kPageOps; ++o) unit[o] = quad_unit<Runner::kD, Runner::kBits>(min(64 * o + lane, kUnits - 1));
+  for (int o = 0; o < kPageOps; ++o) unit[o / kUnitsOf] |= quad_unit<Runner::kD, Runner::kBits, kAt>(min(64 * o + here, kUnits - 1)) << (o % kUnitsOf * 16);
   int f_live = 0, f_first = 0;   // lane s: visible slots and first quad of the pair in slot s
   // asks for the next pair in slot, moves on; false: there is none
   auto issue = [&](int slot) -> bool {
@@ -633,18 +650,19 @@ __device__ __forceinline__ void quad_pairs(Runner& run, Quads& q, const thinkv_v
     const int first = 8 * q.i;
     const int own = min(first + (lane >> 2 & 7), q.n - 1);
     const uint32_t live = (uint32_t)__ballot((q.msk[own] >> (lane & 3) & 1) != 0 && first + (lane >> 2) < q.n && lane < 32);
-#pragma unroll (kPageOps <= 2 ? 2 : 1)
+#pragma unroll(kPageOps <= 2 ? 2 : 1)
     for (int page = 0; page < 2; ++page) {
       int u[kPageOps], from[kPageOps];
 #pragma unroll
       for (int o = 0; o < kPageOps; ++o) {   // (behind the last quad, that one once more: nothing of it is visible there)
-        u[o] = unit[o];
+        u[o] = unit[o / kUnitsOf];
         asm volatile("" : "+v"(u[o]));       // (what follows from it is worked out each time: there are no registers to keep it)
+        u[o] = kUnitsOf > 1 ? u[o] >> (o % kUnitsOf * 16) & 0x7FFF : u[o];
         from[o] = q.pid[min(first + 4 * page + (u[o] & 3), q.n - 1)];
       }
 #pragma unroll
       for (int o = 0; o < kPageOps; ++o) {
-        const uint8_t* src = base + (uint64_t)((uint32_t)from[o] >> 2) * page_bytes + (uint32_t)((u[o] >> 8) + ((from[o] & 3) << (u[o] >> 2 & 31)));
+        const uint8_t* src = base + (uint64_t)((uint32_t)from[o] >> 2) * page_bytes + (uint32_t)((Runner::kTight ? u[o] >> 6 << 4 : u[o] >> 8) + ((from[o] & 3) << (u[o] >> 2 & 15)));
         const uint32_t lds = uniform(ring + slot * kPairBytes + page * Runner::kBlockBytes + 1024 * o);
         if (kRest != 0 && o == kPageOps - 1)
           asm volatile("s_mov_b32 m0, %0\n\ts_mov_b64 exec, %2\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %1, off nt\n\ts_mov_b64 exec, -1"
@@ -859,7 +877,7 @@ template <int D, int BITS, int GP, bool STAT>
 struct ClassRunner {
   using CL = Cols<D, GP>;
   static constexpr int kD = D, kBits = BITS, kBlockBytes = block_geom(BITS, D).block_bytes;
-  static constexpr bool kStat = STAT, kFp = false;
+  static constexpr bool kStat = STAT, kFp = false, kTight = D == 128 && GP == 8;
   static constexpr int NG = D / 32, NM = D / 16, CS = CL::CS, NSET = CL::NSET, NS = GP / 4;
   using F = Fld<BITS>;
   using Pair = PairRegs<D, BITS, NSET>;
@@ -1135,7 +1153,7 @@ struct Partial {
     for (int i = 0; i < NS; ++i) {
       ls[i] = st.l[i];
 #pragma unroll
-      for (int d = 8; d >= 1; d >>= 1) ls[i] += __shfl_xor(ls[i], d, 64);
+      for (int d = 8; d >= 1; d >>= 1) ls[i] += lane_of(ls[i], lane ^ d);
     }
     l = to_column<GP>(ls, lane);
     m = to_column<GP>(st.m, lane);
@@ -1143,8 +1161,8 @@ struct Partial {
     for (int set = 0; set < NSET; ++set) {
       float z = FP ? 0.f : st.oz[set];   // the paper's formats have no zero-points
       if constexpr (!FP) {
-        z += __shfl_xor(z, 16, 64);
-        z += __shfl_xor(z, 32, 64);
+        z += lane_of(z, lane ^ 16);
+        z += lane_of(z, lane ^ 32);
       }
       zsum[set] = z;
     }
@@ -1338,24 +1356,28 @@ __global__ __launch_bounds__(256 * decode_waves_per_simd(D, FP)) __attribute__((
 // Sliding-window layers.  Little is visible (a window of 128 tokens: some ten to eighty pages of a list of a thousand), so the page
 // lists are scanned: mask and id, page_pos_max, and where that reaches into the window the
 // sixteen positions, three dependent loads.  A workgroup, all the waves of a compute unit, scans for `hg` kv-heads at once, a page of
-// each type per thread with the three chains side by side, and leaves in LDS, in list order, what is visible: quads of slots (SlotQuads), in the
-// paper's formats pages.  Its waves then attend that, an hg-th of them a head; partials are folded in LDS, so a head with one item is finished here.
-// Blocks of pages are scanned until the lists are complete or full (kWindowList); entries of a block that found no room are there the next time
-// round, when the block is scanned again.
-// What bounds it: the scan's chains (11 us with the launch), then the pairs of a wave.  How many there are follows from the slots: 128 tokens in
-// slots that evictions freed lie in up to eighty pages, 40 pairs a head, most of whose slots are something else; of their quads there are
-// 15 pairs.  us a call, pages attended by eight waves / quads by all: 128 x 4k..32k tokens, 64 heads of 64, window 128 27.4 / 19.6, window 1,024 101 / 60;
-// 64 x 8k, 8 kv-heads of 128, window 500 41.7 / 31.2; 256 x 500..5k, window 128 52.6 / 36.2.  In fresh pages, whose quads are whole pages, 16.9 / 15.9,
-// 33.9 / 32.4, 20.5 / 19.7, 23.3 / 23.6 (an address from every lane instead of a scalar one; a branch to scalar ones for whole pages costs more: 38.7
-// instead of 34.7 for 256 x 500..5k, heads of 64, window 500).  A head's pairs by turns to its waves instead of in runs: no difference in long lists,
-// 12.0 instead of 11.1 for 1 x 4k.
+// each type per thread with the three chains side by side, and leaves in LDS, in list order, what is visible: pages, or quads of slots (SlotQuads), as the
+// first block with anything visible says: pages (which have scalar addresses, and a pair of which costs 5 to 8 % less) where a wave has one pair of them at most, or where
+// they are hardly more pairs than the quads would be; the paper's formats have pages only.  Its waves then attend that, an hg-th of them a head; partials are folded in
+// LDS, so a head with one item is finished here.  Blocks of pages are scanned until the lists are complete or full (kWindowList); entries of a block that found no room are
+// there the next time round, when the block is scanned again.
+// What bounds it: the scan's chains and the code that is met for the first time (a wave waits some 65 ns for every 64 bytes of instructions; so comparisons are
+// as short as they can be, and sums over waves are taken inside a row), 10 us with the launch, then the pairs of a wave.  How many there are follows from the
+// slots: 128 tokens in slots that evictions freed lie in up to eighty pages, 40 pairs a head, most of whose slots are something else; of their quads there are
+// 15 pairs.  us a call, pages attended by eight waves / quads by all, always / now:
+//   reused slots: 128 x 4k..32k tokens, 64 heads of 64, window 128 27.4 / 19.2 / 19.1; 64 x 4k..8k, 40 heads of 128, window 500 52.0 / 36.2 / 35.9, 1,024 68.3 / 53.2 / 50.4;
+//     256 x 500..5k, 64 heads of 64, window 500 90.2 / 57.6 / 58.3; 1 x 16k, 32 heads of 128, window 128 13.8 / 14.8 / 13.4
+//   fresh slots, whose quads are whole pages: 256 x 500..5k, 40 heads of 128, window 500 45.6 / 50.5 / 45.5, 64 heads of 64 32.4 / 34.2 / 33.0;
+//     64 x 4k..8k, 40 heads of 128, window 1,024 28.7 / 31.0 / 26.9; 8 x 8k, 40 heads of 128, window 128 11.7 / 12.5 / 10.9
+// Twelve waves at head_dim 64 cost the smallest calls a little (2 x 16k tokens, window 128, fresh slots 9.6 with eight, now 10.7) and give more where slots are
+// reused (1 x 16k, window 500 15.5 with eight, now 14.1).  A head's pairs by turns to its waves instead of in runs: 11.3 instead of 10.5 for 8 x 16k, window 128.
 template <int D, int GP, bool STAT, bool FP>
 __global__ __launch_bounds__(64 * window_waves(D)) __attribute__((amdgpu_waves_per_eu(window_waves(D) / 4, window_waves(D) / 4))) void decode_window_kernel(thinkv_view v, DecodeArgs a) {
   static_assert(window_lds_bytes(D, STAT) + window_waves(D) * exchange_bytes(D, GP, FP) <= 163840, "the LDS of a compute unit");
   constexpr int kWaves = window_waves(D), kRing = window_ring_bytes(D), kRow = D + kRowPad;
   extern __shared__ __attribute__((aligned(16))) uint8_t tkv_lds[];
   const thinkv_config& c = v.cfg;
-  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int H = c.n_kv_heads, Hq = c.n_q_heads, G = Hq / H, hg = a.waves, wph = whole(kWaves, hg);
   const int groups = quotient(H + hg - 1, hg);
   // item id -> query, group of heads, item j of n (item-major)
@@ -1372,8 +1394,8 @@ __global__ __launch_bounds__(64 * window_waves(D)) __attribute__((amdgpu_waves_p
   if (j >= n) return;
   const int hw = whole(wave, wph), hkv = min(h0 + hw, H - 1);   // this wave's head (waves beyond the last head idle)
   if constexpr (STAT)
-    if (a.stat_sum && j == 0 && h0 == 0 && tid == 0) a.stat_sum[b] = 0;
-  if (j == 0 && !a.direct && tid < hg && h0 + tid < H) {
+    if (a.stat_sum && j == 0 && h0 == 0 && threadIdx.x == 0) a.stat_sum[b] = 0;
+  if (const int tid = threadIdx.x; j == 0 && !a.direct && tid < hg && h0 + tid < H) {
     a.alloc[2 * (b * H + h0 + tid)] = (b * H + h0 + tid) * a.per_head;
     a.alloc[2 * (b * H + h0 + tid) + 1] = n;
   }
@@ -1384,8 +1406,8 @@ __global__ __launch_bounds__(64 * window_waves(D)) __attribute__((amdgpu_waves_p
   uint16_t* const masks = (uint16_t*)(ids + (STAT ? 6 : 3) * kWindowList);
   int32_t* const counts = (int32_t*)(masks + 3 * kWindowList);
   Query<D, GP, FP> query;
-  query.load(a, ((int64_t)b * Hq + hkv * G) * D, G, lane);
-  query.finish(a, G, lane);
+  query.load(a, ((int64_t)b * Hq + hkv * G) * D, G, threadIdx.x & 63);
+  query.finish(a, G, threadIdx.x & 63);
   WaveState<D, GP, Query<D, GP, FP>::NSET> st;
   clear(st);
   const int qpos = uniform(a.q_pos[b]);
@@ -1394,10 +1416,11 @@ __global__ __launch_bounds__(64 * window_waves(D)) __attribute__((amdgpu_waves_p
   const int s0 = portion(np[0], j, n), e0 = portion(np[0], j + 1, n);
   const int s1 = portion(np[1], j, n), e1 = portion(np[1], j + 1, n);
   const int s2 = portion(np[2], j, n), e2 = portion(np[2], j + 1, n);
-  const int most = max(e0 - s0, max(e1 - s1, e2 - s2));
-  using Source = std::conditional_t<FP, VisiblePages<STAT>, SlotQuads<STAT>>;
+  const int most = uniform(max(e0 - s0, max(e1 - s1, e2 - s2)));
+  bool by_page = FP;
   int have[3] = {0, 0, 0}, skip[3] = {0, 0, 0};   // entries in the lists; entries of this block that have been there before
   for (int base = 0; base < most;) {
+    const int lane = fresh_lane(), tid = 64 * wave + lane;
     int pg[3], pid[3];
     uint32_t vis[3];
 #pragma unroll
@@ -1420,31 +1443,60 @@ __global__ __launch_bounds__(64 * window_waves(D)) __attribute__((amdgpu_waves_p
       if (vis[k] != 0) {
         const int4* sp = (const int4*)(v.slot_pos[k] + (int64_t)pid[k] * kPage);
         uint32_t m = 0;
+        auto inside = [&](int pos) { m += m + ((uint32_t)(qpos - pos) < (uint32_t)a.window ? 1u : 0u); };   // 0 <= qpos - pos < window
 #pragma unroll
-        for (int t4 = 0; t4 < kPage / 4; ++t4) {
+        for (int t4 = kPage / 4 - 1; t4 >= 0; --t4) {
           const int4 pos = sp[t4];
-          const int d0 = qpos - pos.x, d1 = qpos - pos.y, d2 = qpos - pos.z, d3 = qpos - pos.w;
-          m |= ((d0 >= 0 && d0 < a.window) ? 1u : 0u) << (4 * t4);
-          m |= ((d1 >= 0 && d1 < a.window) ? 2u : 0u) << (4 * t4);
-          m |= ((d2 >= 0 && d2 < a.window) ? 4u : 0u) << (4 * t4);
-          m |= ((d3 >= 0 && d3 < a.window) ? 8u : 0u) << (4 * t4);
+          inside(pos.w), inside(pos.z), inside(pos.y), inside(pos.x);
         }
         vis[k] &= m;
       }
-    // what is visible, in list order: an entry for each page (quad of slots) with a visible slot.  Counts of the three types in a word: a
-    // wave has at most 256 of each
-    auto entries = [](uint32_t m) { return FP ? (m != 0 ? 1 : 0) : __popc((m | m >> 1 | m >> 2 | m >> 3) & 0x1111u); };
+    // what is visible, in list order: an entry for each page or quad of slots with a visible slot.  Counts of the three types in a word: a
+    // wave has at most 64 pages and 256 quads of each
     auto add = [](int x, int y) { return x + y; };
-    const int mine = entries(vis[0]) | entries(vis[1]) << 10 | entries(vis[2]) << 20, upto = wave_scan(mine, add);
-    if (lane == 63) counts[wave] = upto;
+    uint64_t seen[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) seen[k] = __ballot(vis[k] != 0);
+    const int pages_seen = __popcll(seen[0]) | __popcll(seen[1]) << 10 | __popcll(seen[2]) << 20;
+    int mine = 0, upto = 0;
+    if constexpr (!FP) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k) mine |= __popc((vis[k] | vis[k] >> 1 | vis[k] >> 2 | vis[k] >> 3) & 0x1111u) << (10 * k);
+      upto = wave_scan(mine, add);
+      if (lane == 63) counts[kCounts + wave] = upto;
+    }
+    if (lane == 63) counts[wave] = pages_seen;
     __syncthreads();
-    const int of_wave = lane < kWaves ? counts[lane] : 0;
+    // ... summed over the waves before this one, and over all
+    static_assert(kWaves < 16, "a row holds the counts of the waves behind a zero");
+    const bool counted = lane > 0 && lane <= kWaves;
+    const int pages_of_wave = counted ? counts[lane - 1] : 0, quads_of_wave = !FP && counted ? counts[kCounts + lane - 1] : 0;
+    const int upto_wave = row_scan(pages_of_wave, add);   // (at most 768 pages of a type)
+    const int pages_all = __builtin_amdgcn_readlane(upto_wave, 15), pages_before = __builtin_amdgcn_readlane(upto_wave, wave);
+    int total[3], from[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) total[k] = pages_all >> (10 * k) & 1023, from[k] = pages_before >> (10 * k) & 1023;
+    if constexpr (!FP) {
+      if ((have[0] | have[1] | have[2] | skip[0] | skip[1] | skip[2]) == 0) {
+        const int quads = __builtin_amdgcn_readlane(row_scan((quads_of_wave & 1023) + (quads_of_wave >> 10 & 1023) + (quads_of_wave >> 20), add), 15);
+        const int whole_pairs = (total[0] + total[1] + total[2] + 1) >> 1, quad_pairs = (quads + 7) >> 3;
+        by_page = whole_pairs <= max(wph, quad_pairs + (quad_pairs >> 3) + 1);
+      }
+      if (!by_page) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          const int upto_k = row_scan(quads_of_wave >> (10 * k) & 1023, add);
+          total[k] = __builtin_amdgcn_readlane(upto_k, 15);
+          from[k] = __builtin_amdgcn_readlane(upto_k, wave);
+        }
+      }
+    }
     bool all = true;
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-      const int waves = wave_scan(of_wave >> (10 * k) & 1023, add), total = last_lane(waves);
       const int room = kWindowList - have[k];
-      int at = (wave > 0 ? __builtin_amdgcn_readlane(waves, max(wave - 1, 0)) : 0) + ((upto - mine) >> (10 * k) & 1023) - skip[k];
+      const int inside = by_page ? __builtin_amdgcn_mbcnt_hi((uint32_t)(seen[k] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)seen[k], 0)) : (upto - mine) >> (10 * k) & 1023;
+      int at = from[k] + inside - skip[k];
       auto put = [&](int id, uint32_t m) {
         if (at >= 0 && at < room) {
           const int e = k * kWindowList + have[k] + at;
@@ -1454,17 +1506,17 @@ __global__ __launch_bounds__(64 * window_waves(D)) __attribute__((amdgpu_waves_p
         }
         ++at;
       };
-      if (FP) {
+      if (by_page) {
         if (vis[k] != 0) put(pid[k], vis[k]);
       } else {
 #pragma unroll
         for (int quad = 0; quad < 4; ++quad)
           if (vis[k] >> (4 * quad) & 15u) put(pid[k] << 2 | quad, vis[k] >> (4 * quad) & 15u);
       }
-      const int took = min(total - skip[k], room);
+      const int took = min(total[k] - skip[k], room);
       have[k] += took;
       skip[k] += took;
-      all = all && skip[k] == total;
+      all = all && skip[k] == total[k];
     }
     __syncthreads();
     if (all) {
@@ -1474,37 +1526,49 @@ __global__ __launch_bounds__(64 * window_waves(D)) __attribute__((amdgpu_waves_p
     }
     if (hw < hg && h0 + hw < H) {
       // The pairs of the three types one after the other, an equal run of them to each of the head's waves: a wave meets one type or two, and
-      // waits for its first pages once or twice instead of three times.  (The paper's formats: by turns within each type.  A run of 8-bit pages, of
+      // waits for its first pages, and for a type's code, once or twice instead of three times.  (The paper's formats: by turns within each type.  A run of 8-bit pages, of
       // which the ring holds one pair, is slow there: 64 x 4k..8k, 40 heads, window 500 44.0 us by turns, 49.0 in runs.)
       int pairs[3];
 #pragma unroll
-      for (int k = 0; k < 3; ++k) pairs[k] = (have[k] + Source::kPair - 1) / Source::kPair;
+      for (int k = 0; k < 3; ++k) pairs[k] = by_page ? (have[k] + 1) >> 1 : (have[k] + 7) >> 3;
       const int everything = pairs[0] + pairs[1] + pairs[2];
-      const int from = portion(everything, wave - hw * wph, wph), to = portion(everything, wave - hw * wph + 1, wph);
+      // Those that get one more are the head's first waves, on SIMDs side by side, or its last where the head before it has its first on the
+      // same SIMDs (64 x 4k..8k tokens of reused slots, 8 kv-heads of 128, window 128 16.9 us without, 16.2 so)
+      const int waves = fresh(wph), own = wave - hw * waves, turn = (hw * waves & 7) == 4 ? waves - 1 - own : own;
+      const int each = whole(everything, waves), more = everything - waves * each;
+      const int from = turn * each + min(turn, more), to = from + each + (turn < more ? 1 : 0);
 #pragma unroll 1
       for (int k = 0; k < 3; ++k) {
-        const int first = k == 0 ? 0 : (k == 1 ? pairs[0] : pairs[0] + pairs[1]);
-        Source q;
-        q.n = k == 0 ? have[0] : (k == 1 ? have[1] : have[2]);
-        q.end = (q.n + Source::kPair - 1) / Source::kPair;
-        q.i = FP ? wave - hw * wph : max(from - first, 0);
-        q.step = FP ? wph : 1;
-        if (!FP) q.end = min(q.end, to - first);
-        if (q.i >= q.end) continue;
-        q.pid = (LdsWords)(uintptr_t)(lds + kWaves * kRing + 4 * k * kWindowList);
-        q.idx = q.pid + 3 * kWindowList;
-        q.msk = (LdsHalves)(uintptr_t)(lds + kWaves * kRing + 4 * (STAT ? 6 : 3) * kWindowList + 2 * k * kWindowList);
+        const int first = k == 0 ? 0 : (k == 1 ? pairs[0] : pairs[0] + pairs[1]), mine_of = k == 0 ? pairs[0] : (k == 1 ? pairs[1] : pairs[2]);
+        const int begin = FP ? turn : max(from - first, 0), end = FP ? mine_of : min(mine_of, to - first);
+        if (begin >= end) continue;
         const int bits = c.bits_of_class[k];
         float* stat = nullptr;
         int stat_room = 0;
         if constexpr (STAT) stat = stat_row(c, a, b, hkv, k, np, &stat_room);
-        if constexpr (FP) TKV_BY_WIDTH(bits, stream_pairs<kRing>(cr, q, v, k, hkv, lds + wave * kRing))
-        else TKV_BY_WIDTH(bits, quad_pairs<kRing>(cr, q, v, k, hkv, lds + wave * kRing))
+        auto source = [&](auto q) {
+          q.n = k == 0 ? have[0] : (k == 1 ? have[1] : have[2]);
+          q.i = begin;
+          q.end = end;
+          q.step = FP ? wph : 1;
+          q.pid = (LdsWords)(uintptr_t)(lds + kWaves * kRing + 4 * k * kWindowList);
+          q.idx = q.pid + 3 * kWindowList;
+          q.msk = (LdsHalves)(uintptr_t)(lds + kWaves * kRing + 4 * (STAT ? 6 : 3) * kWindowList + 2 * k * kWindowList);
+          return q;
+        };
+        if (by_page) {
+          auto q = source(VisiblePages<STAT>());
+          TKV_BY_WIDTH(bits, stream_pairs<kRing>(cr, q, v, k, hkv, lds + wave * kRing))
+        } else if constexpr (!FP) {
+          auto q = source(SlotQuads<STAT>());
+          TKV_BY_WIDTH(bits, quad_pairs<kRing>(cr, q, v, k, hkv, lds + wave * kRing))
+        }
       }
     }
     have[0] = have[1] = have[2] = 0;
     __syncthreads();   // the lists have been used
   }
+  const int lane = fresh_lane(), tid = 64 * wave + lane;
   const Partial<D, GP, FP> part(st, lane);
   const int head = lane & (GP - 1), qd = lane >> 4;
   float* const rows = (float*)tkv_lds;   // [wave][G][kRow]
