@@ -67,7 +67,7 @@ def _both(c, q, D, bound=None, window=0, q_pos=None, ids=None, items=None):
     return res
 
 
-def _close(o, l, ro, rl):
+def _close(o, l, ro, rl, least=1.2e-6):
     """Every sequence's outputs to 2e-5 of its own largest one: products whose second operand holds 22 bits are 2e-7 off, and with 11
     bits, one term of the pair lost, 2e-4.  Below that stands what the sums themselves lose: codes and zero-points are summed
     apart, about 4 each for values of N(0, 1), with a rounding of 2^-25 of that for each of some hundred additions a wave and item,
@@ -76,7 +76,7 @@ def _close(o, l, ro, rl):
         fin = torch.isfinite(rl[b])
         assert torch.equal(torch.isfinite(l[b]), fin) and (not fin.any() or float((l[b][fin] - rl[b][fin]).abs().max()) <= 2e-5 * max(1.0, float(rl[b][fin].abs().max())))
         far, top = float((o[b] - ro[b]).abs().max()), float(ro[b].abs().max())
-        assert far <= max(2e-5 * top, 1.2e-6), (b, far, top)
+        assert far <= max(2e-5 * top, least), (b, far, top)
 
 
 @pytest.mark.parametrize("D,G,H,ctx,fmt,bits,dead", [
@@ -126,7 +126,7 @@ def test_value_scales_out_of_the_lifted_range(D, G, v_scale):
 
 
 @pytest.mark.parametrize("D,G,H,ctx,fmt,window,dead", [
-    (64, 8, 8, [3000] * 70, 0, 128, 0.3),            # several heads to a workgroup
+    (64, 8, 8, [3000] * 70, 0, 128, 0.3),            # two heads to a workgroup
     (128, 4, 5, [9000, 40, 1, 700], 0, 1024, 0.2),   # one head to a workgroup, several items a head; heads no power of two
     (128, 8, 3, [26000], 0, 30000, 0.0),             # everything visible, many items
     (128, 4, 2, [29000], 0, 400, 0.2),               # lists longer than one scan by one item
@@ -153,9 +153,44 @@ def test_window_kernel_against_the_plain_kernel(D, G, H, ctx, fmt, window, dead)
     _close(o, l, ro, rl)
 
 
+def _put(x, t=np.int32):
+    return torch.from_numpy(np.ascontiguousarray(x).astype(t)).to("cuda:0")
+
+
+def _live(c, b, k):
+    """[pages, 16] of sequence b, type k: which slots are live, and their positions"""
+    n = int(c.n_pages[b, 0, k])
+    mask, ids = c.slot_mask[b, 0, k, :n].cpu().numpy(), c.block_table[b, 0, k, :n].long()
+    return ((mask[:, None] >> np.arange(16)) & 1).astype(bool), c.slot_pos[k][ids].cpu().numpy()
+
+
+def _reuse(c, ctx, rng, share, fresh=0.0):
+    """evicts a share of the tokens, one by one, and puts new ones into all but `fresh` of their slots: the sequences' last positions"""
+    H, D = c.cfg.n_kv_heads, c.cfg.head_dim
+    ev_seq, ev_h, cls = [], [], []
+    for b in range(len(ctx)):
+        for k in range(3):
+            live = _live(c, b, k)[0].reshape(-1)
+            at = np.flatnonzero(live & (rng.random(len(live)) < share))
+            ev_seq.append(np.full(len(at), b))
+            ev_h.append(k << 28 | at)               # list index << 4 | slot
+            cls.append(np.full(len(at), k))
+    seq, h, cls = np.concatenate(ev_seq), np.concatenate(ev_h), np.concatenate(cls)
+    B.thinkv_evict(c, 0, _put(seq), _put(h))
+    take = rng.random(len(seq)) >= fresh
+    order = np.lexsort((rng.random(int(take.sum())), seq[take]))
+    seq, cls = seq[take][order], cls[take][order]
+    new = np.bincount(seq, minlength=len(ctx))
+    pos = np.concatenate([x + np.arange(n) for x, n in zip(ctx, new)])
+    if len(seq):
+        kv = [torch.randn((len(seq), H, D), device="cuda:0").to(torch.bfloat16) for _ in range(2)]
+        B.thinkv_append_quantized(c, 0, kv[0], kv[1], _put(seq), _put(pos), _put(cls, np.uint8))
+    return [int(x + n - 1) for x, n in zip(ctx, new)]
+
+
 @pytest.mark.parametrize("D,G,H,ctx,bits,window,fresh", [
-    (64, 8, 8, [3000] * 40 + [5, 17], (8, 2, 4), 128, 0.0),   # a few tokens to a page, several heads to a workgroup
-    (64, 4, 3, [20000, 33], (2, 4, 8), 30000, 0.0),           # all of it: more quads to a type than a list holds, tails of less than a pair
+    (64, 8, 8, [3000] * 40 + [5, 17], (8, 2, 4), 128, 0.0),   # a few tokens to a page, a head to a workgroup
+    (64, 4, 3, [20000, 33], (2, 4, 8), 30000, 0.0),           # all of it: twenty items a head, tails of less than a pair
     (128, 4, 2, [26000, 1], (4, 8, 2), 30000, 0.0),
     (128, 8, 2, [9000, 800], (8, 2, 4), 700, 0.0),
     (128, 2, 1, [2000], (2, 2, 8), 37, 0.5),                  # some of the freed slots taken
@@ -166,40 +201,101 @@ def test_window_over_reused_slots(D, G, H, ctx, bits, window, fresh):
     statistic against full attention's where everything is visible"""
     print("window, reused slots:", D, G, H, len(ctx), max(ctx), bits, window, flush=True)
     c, q = _cache(D, G, H, ctx, 0, bits, 31 + D + G)
-    rng = np.random.default_rng(D + G + window)
-    pick = lambda ok: np.flatnonzero(ok & (rng.random(len(ok)) < 0.3))  # noqa: E731
-    ev_seq, ev_h, cls = [], [], []
-    mask, n_pages = c.slot_mask[:, 0].cpu().numpy(), c.n_pages[:, 0].cpu().numpy()
-    for b in range(len(ctx)):
-        for k in range(3):
-            live = ((mask[b, k, :n_pages[b, k], None] >> np.arange(16)) & 1).astype(bool).reshape(-1)
-            at = pick(live)
-            ev_seq.append(np.full(len(at), b))
-            ev_h.append(k << 28 | at)               # list index << 4 | slot
-            cls.append(np.full(len(at), k))
-    d = lambda x, t: torch.from_numpy(np.ascontiguousarray(x).astype(t)).to("cuda:0")  # noqa: E731
-    seq, h, cls = np.concatenate(ev_seq), np.concatenate(ev_h), np.concatenate(cls)
-    B.thinkv_evict(c, 0, d(seq, np.int32), d(h, np.int32))
-    take = rng.random(len(seq)) >= fresh
-    order = np.lexsort((rng.random(int(take.sum())), seq[take]))
-    seq, cls = seq[take][order], cls[take][order]
-    new = np.bincount(seq, minlength=len(ctx))
-    pos = np.concatenate([x + np.arange(n) for x, n in zip(ctx, new)])
-    if len(seq):
-        kv = [torch.randn((len(seq), H, D), device="cuda:0").to(torch.bfloat16) for _ in range(2)]
-        B.thinkv_append_quantized(c, 0, kv[0], kv[1], d(seq, np.int32), d(pos, np.int32), d(cls, np.uint8))
-    q_pos = [int(x + n - 1) for x, n in zip(ctx, new)]
+    q_pos = _reuse(c, ctx, np.random.default_rng(D + G + window), 0.3, fresh)
     (o, l), (ro, rl) = _both(c, q, D, window=window, q_pos=q_pos)
     _close(o, l, ro, rl)
     if window < max(q_pos):
         return
     S, pages = q.shape[0], int(c.n_pages[:, 0].sum(-1).max())
-    ids, qp = torch.arange(S, dtype=torch.int32, device="cuda:0"), d(q_pos, np.int32)
+    ids, qp = torch.arange(S, dtype=torch.int32, device="cuda:0"), _put(q_pos)
     out, sp = torch.empty((S, G * H, D), dtype=torch.float32, device="cuda:0"), [torch.empty(S, dtype=torch.float32, device="cuda:0") for _ in range(2)]
     for w, x in zip((0, window), sp):
         B.thinkv_decode_attention_sparsity(c, 0, q, out, None, x, ids, qp, w, D ** -0.5, pages)
     # (scores alike up to the order of a few additions: one entry in a thousand may change sides)
     assert float((sp[0] - sp[1]).abs().max()) <= 1e-3 and float(sp[0].max()) > 0.01
+
+
+LIST = 1024   # entries of a type's list of what is visible
+
+
+def _grouping(c, S):
+    """heads of a workgroup, and waves of it"""
+    cus, H, waves = torch.cuda.get_device_properties(0).multi_processor_count, c.cfg.n_kv_heads, 8 if c.cfg.head_dim == 128 else 12
+    hg = 1
+    while 2 * hg <= min(waves, H) and S * H >= 2 * hg * cus:
+        hg *= 2
+    return hg, waves
+
+
+def _visible(c, b, q_pos, window, waves, hg):
+    """what one item finds for sequence b: entries of each type, whether they are pages, and entries of the first block of the scan"""
+    pages, quads = [], []
+    for k in range(3):
+        live, pos = _live(c, b, k)
+        see = live & (pos <= q_pos) & (pos > q_pos - window)
+        pages.append(see.any(1).astype(int))
+        quads.append(see.reshape(-1, 4, 4).any(2).sum(1))
+    block, at = 64 * waves, 0
+    while at + block < max(map(len, pages)) and not any(x[at:at + block].any() for x in pages):
+        at += block
+    first = lambda lists: sum(int(x[at:at + block].sum()) for x in lists)  # noqa: E731
+    whole, four = (first(pages) + 1) // 2, (first(quads) + 7) // 8
+    by_page = c.cfg.format == B.FMT_FP or whole <= max(waves // hg, four + four // 8 + 1)
+    use = pages if by_page else quads
+    return [int(x.sum()) for x in use], by_page, [int(x[at:at + block].sum()) for x in use]
+
+
+MANY = [5] * 15 + [1]   # with 8 kv-heads: an item a head, whatever the others' lengths
+@pytest.mark.parametrize("D,G,H,ctx,fmt,bits,window,share,hg,by_page,overflow", [
+    (64, 4, 8, [22000] + MANY, 0, (8, 2, 4), -1, 0.3, 1, False, "first"),       # the refilled tokens: the first block of pages has more quads than a list holds
+    (128, 5, 8, [33000] + MANY, 0, (2, 4, 8), -1, 0.15, 1, False, "later"),     # ... the second has
+    (64, 8, 8, [60000] + MANY, 0, (8, 4, 2), 1 << 20, 0.0, 1, True, "later"),   # whole pages, everything visible
+    (128, 8, 8, [54000] + MANY, 0, (8, 2, 4), 1 << 20, 0.05, 1, True, "later"),
+    (64, 8, 8, [60000] + MANY, 1, (2, 4, 8), 1 << 20, 0.1, 1, True, "later"),   # the paper's formats
+    (64, 4, 8, [900, 300] * 36, 0, (8, 2, 4), 128, 0.3, 2, False, None),
+    (128, 8, 8, [700, 90] * 36, 0, (4, 8, 2), 128, 0.3, 2, False, None),
+    (64, 8, 8, [300, 120] * 128, 0, (8, 2, 4), 128, 0.0, 8, True, None),        # a wave a head, four without one
+    (64, 4, 8, [400, 40] * 128, 0, (8, 2, 4), 60, 0.3, 8, False, None),
+    (128, 5, 8, [400, 200] * 128, 0, (2, 4, 8), 60, 0.3, 8, False, None),
+    (64, 8, 12, [300, 70] * 90, 0, (8, 2, 4), 60, 0.3, 8, False, None),         # the last workgroup of a sequence has four of eight heads
+    (128, 4, 12, [300, 70] * 90, 1, (2, 4, 8), 60, 0.3, 8, True, None),
+    (64, 4, 8, [300, 120] * 128, 1, (2, 4, 8), 60, 0.2, 8, True, None),
+], ids=lambda x: str(x)[:24].replace(" ", ""))
+def test_window_lists_and_groups(D, G, H, ctx, fmt, bits, window, share, hg, by_page, overflow):
+    """lists of pages and of quads, longer than they can be, and several heads to a workgroup.  Against the plain kernel, and, for the statistic, against
+    full attention once everything outside the window is evicted"""
+    print("window, lists and groups:", D, G, H, len(ctx), max(ctx), fmt, bits, window, share, flush=True)
+    c, q = _cache(D, G, H, ctx, fmt, bits, 41 + D + G)
+    q_pos = _reuse(c, ctx, np.random.default_rng(D + G + len(ctx)), share) if share else [x - 1 for x in ctx]
+    if window < 0:
+        window = q_pos[0] + 1 - ctx[0]
+    S, pages = q.shape[0], int(c.n_pages[:, 0].sum(-1).max())
+    heads, waves = _grouping(c, S)
+    entries, kind, first = _visible(c, 0, q_pos[0], window, waves, heads)
+    print("entries", entries, "in the first block", first, "pages" if kind else "quads", flush=True)
+    assert heads == hg and kind == by_page
+    assert (max(entries) > LIST) == (overflow is not None) and (max(first) > LIST) == (overflow == "first")
+    assert overflow != "later" or (0 < max(first) < LIST)
+    (o, l), (ro, rl) = _both(c, q, D, window=window, q_pos=q_pos)
+    # (five items of four waves share a head in the plain kernel, which adds token by token; a page more or less moves an output by 4 / tokens, ten times that)
+    _close(o, l, ro, rl, least=1.2e-7 * max(100, min(window, max(ctx)) / 20) ** 0.5)
+    ids, qp = torch.arange(S, dtype=torch.int32, device="cuda:0"), _put(q_pos)
+    got = []
+    for w in (window, 0):
+        out, sp = torch.empty((S, G * H, D), dtype=torch.float32, device="cuda:0"), torch.empty(S, dtype=torch.float32, device="cuda:0")
+        B.thinkv_decode_attention_sparsity(c, 0, q, out, None, sp, ids, qp, w, D ** -0.5, pages)
+        got.append((out, sp))
+        if w:
+            for b in range(S):
+                for k in range(3):
+                    live, pos = _live(c, b, k)
+                    old = np.flatnonzero((live & (pos <= q_pos[b] - window)).reshape(-1))
+                    if len(old):
+                        B.thinkv_evict(c, 0, _put(np.full(len(old), b)), _put(k << 28 | old))
+    # (scores alike up to the order of a few additions: one entry in a thousand, or one of a short context, may change sides)
+    n = torch.tensor([min(x + 1, window) for x in q_pos], device="cuda:0")
+    assert float(((got[0][1] - got[1][1]).abs() - 1.0 / (n * H)).max()) <= 1e-3 and float(got[1][1].max()) > 1e-3
+    assert float((got[0][0] - got[1][0]).abs().max()) <= 1e-4
 
 
 @pytest.mark.parametrize("D,G,ctx,fmt,dead,bound", [
