@@ -1362,14 +1362,14 @@ __global__ __launch_bounds__(256 * decode_waves_per_simd(D, FP)) __attribute__((
 // LDS, so a head with one item is finished here.  Blocks of pages are scanned until the lists are complete or full (kWindowList); entries of a block that found no room are
 // there the next time round, when the block is scanned again.
 // What bounds it: the scan's chains and the code that is met for the first time (a wave waits some 65 ns for every 64 bytes of instructions; so comparisons are
-// as short as they can be, and sums over waves are taken inside a row), 10 us with the launch, then the pairs of a wave.  How many there are follows from the
+// as short as they can be, sums over waves are taken inside a row, and the fold divides by a reciprocal), 10 us with the launch, then the pairs of a wave.  How many there are follows from the
 // slots: 128 tokens in slots that evictions freed lie in up to eighty pages, 40 pairs a head, most of whose slots are something else; of their quads there are
 // 15 pairs.  us a call, pages attended by eight waves / quads by all, always / now:
 //   reused slots: 128 x 4k..32k tokens, 64 heads of 64, window 128 27.4 / 19.2 / 19.1; 64 x 4k..8k, 40 heads of 128, window 500 52.0 / 36.2 / 35.9, 1,024 68.3 / 53.2 / 50.4;
 //     256 x 500..5k, 64 heads of 64, window 500 90.2 / 57.6 / 58.3; 1 x 16k, 32 heads of 128, window 128 13.8 / 14.8 / 13.4
 //   fresh slots, whose quads are whole pages: 256 x 500..5k, 40 heads of 128, window 500 45.6 / 50.5 / 45.5, 64 heads of 64 32.4 / 34.2 / 33.0;
 //     64 x 4k..8k, 40 heads of 128, window 1,024 28.7 / 31.0 / 26.9; 8 x 8k, 40 heads of 128, window 128 11.7 / 12.5 / 10.9
-// Twelve waves at head_dim 64 cost the smallest calls a little (2 x 16k tokens, window 128, fresh slots 9.6 with eight, now 10.7) and give more where slots are
+// Twelve waves at head_dim 64 cost the smallest calls a little (2 x 16k tokens, window 128, fresh slots 9.5 whole pages by eight, now 10.4) and give more where slots are
 // reused (1 x 16k, window 500 15.5 with eight, now 14.1).  A head's pairs by turns to its waves instead of in runs: 11.3 instead of 10.5 for 8 x 16k, window 128.
 template <int D, int GP, bool STAT, bool FP>
 __global__ __launch_bounds__(64 * window_waves(D)) __attribute__((amdgpu_waves_per_eu(window_waves(D) / 4, window_waves(D) / 4))) void decode_window_kernel(thinkv_view v, DecodeArgs a) {
@@ -1581,8 +1581,9 @@ __global__ __launch_bounds__(64 * window_waves(D)) __attribute__((amdgpu_waves_p
     }
   }
   __syncthreads();
+  const float inv_G = __builtin_amdgcn_rcpf((float)G);   // (at most 64 query heads)
   for (int i = tid; i < hg * G * (D / 4); i += 64 * kWaves) {
-    const int hd = i / (G * (D / 4)), g = i / (D / 4) % G, ch = 4 * (i % (D / 4));
+    const int of = i / (D / 4), hd = (int)(((float)of + 0.5f) * inv_G), g = of - hd * G, ch = 4 * (i % (D / 4));
     if (h0 + hd < H) fold_rows<D>(a, rows + (hd * wph * G + g) * kRow, G * kRow, wph, b, h0 + hd, g, ch, Hq, G, (b * H + h0 + hd) * a.per_head + j);
   }
 }
