@@ -477,7 +477,7 @@ constexpr int kWords = kTbeMaxTokens / 32;
 
 // An entry of the list of members: the point, where its row of the triangle begins, that it is one, its cluster, and that the four
 // entries of a step it stands in are the cluster's last
-constexpr uint32_t kIsMember = 1u << 23, kLastStep = 1u << 31;
+constexpr uint32_t kIsMember = 1u << 31, kLastStep = 1u << 23;
 __device__ __forceinline__ uint32_t member(int p, int j, bool last) { return (uint32_t)p | (uint32_t)tri(p) << 8 | kIsMember | (uint32_t)j << 24 | (last ? kLastStep : 0u); }
 constexpr uint32_t kUnmoved = ~0u;
 
@@ -513,12 +513,13 @@ __device__ __forceinline__ float add_quarters(float x) {   // the sum over the l
 // Lloyd's algorithm, the survivors and the centroids of a segment whose matrix is in LDS.  A wave has sixteen points; lane (r, quarter) shares
 // point r with three others: a quarter adds every fourth member of a cluster and keeps the products with every fourth cluster.  So
 // all waves have the same work whatever the sizes of the clusters are, and the nearest cluster is found inside a wave, without a barrier.  What bounds
-// it: instructions (some twenty for four members of a wave's points) and, where few clusters move, barriers and LDS latency; 161 points and sixteen clusters
-// take 10 us for all products of an iteration, 4 for a few clusters', 1.5 for the assignment.  (A point a lane and clusters dealt to groups of waves: 9, 2 to 8
-// and 2.1, the largest cluster being what everybody waited for.  The sums as a matrix product with the 0/1 matrix of the members, in
-// binary32 on the matrix cores: 5 a tile of sixteen clusters, however few of them moved; 314 segments of 64 to 192 tokens 177 us instead of 145.)
-// (With 256 points and 64 clusters, four members each, a step and its sum over the quarters cost more than four additions of a point a lane: one such segment,
-// 2 heads of 64, 87 us instead of 82, 314 of 200 to 256 tokens, 1 of 64, 143 and 139; 314 of 8 of 128 305 and 341.)
+// it: instructions (some fourteen for four members of a wave's points) and, where few clusters move, barriers and LDS latency: so a point's rank among the
+// members and the clusters' places in the list ask LDS once.  (A point a lane and clusters dealt to groups of waves, the largest cluster being what everybody
+// waited for / this way with a step of twenty instructions, and a rank of up to eight dependent loads / now, us, K of 64, 32 and 16 in turn: 314 segments of 64 to 192
+// tokens, 8 kv-heads of 128 140 / 131 / 128, 2 of 64 96 / 85 / 81; 64 of 193 to 256, 1 of 64, 87.5 / 92.9 / 84.3; one of 256 tokens and 64 clusters, where four members a
+// cluster cost a step and a sum over the quarters, 1 of 64, 45.0 / 46.8 / 44.0, 2 of 128 56.6 / 58.0 / 55.1; the one size that still loses, one of 192, 8 of 128, 61.6 / 63.7 / 62.6.
+// The sums as a matrix product with the 0/1 matrix of the members, in binary32 on the matrix cores: 5 a tile of sixteen clusters, however few of them moved; 314 segments of
+// 64 to 192 tokens 177 us where the second way took 145.)
 template <int W, int POINTS>
 __device__ __forceinline__ void choose_survivors(const TbeArgs& a, int seg, int lo, int n, int k, KmScratch<W, POINTS>& sm) {
   constexpr int kThreads = 64 * W, kPer = kTbeMaxKeep / 4, kAhead = 4, kRows = 8;
@@ -531,7 +532,8 @@ __device__ __forceinline__ void choose_survivors(const TbeArgs& a, int seg, int 
   const int quarter = lane >> 4, p = 16 * wave + (lane & 15);
   const bool here = p < n, first = here && quarter == 0;
   const int pc = here ? p : n - 1, tp = tri(pc);
-  auto product = [&](int m, int tm) { return sm.gram[pc >= m ? tp + m : tm + pc]; };   // with point m, whose row begins at tm
+  // with point m, whose row begins at tm: the pair's place is in the row of the larger, the larger of the two sums (alike only where both are the place)
+  auto product = [&](int m, int tm) { return sm.gram[max(tp + m, tm + pc)]; };
   // initial centroids: evenly spaced points, distinct, since k < n
   for (int i = tid; i < kTbeMaxKeep * kWords; i += kThreads) (&sm.basis[0][0])[i] = (&sm.next[0][0])[i] = 0u;
   if (tid < 2) sm.vote[tid] = 0;
@@ -555,7 +557,7 @@ __device__ __forceinline__ void choose_survivors(const TbeArgs& a, int seg, int 
   auto products = [&]() {
     const int steps = __builtin_amdgcn_readfirstlane(sm.steps);
     const uint32_t inv = __builtin_bit_cast(uint32_t, 1.0f / (float)sm.count[lane]);
-    float sum = 0.f;
+    float sum = 0.f, with_own = 0.f;
     if (16 * wave < n)
       for (int s0 = 0; s0 < steps; s0 += kAhead) {   // the loads of four steps do not wait for each other
         uint32_t e[kAhead];
@@ -567,17 +569,18 @@ __device__ __forceinline__ void choose_survivors(const TbeArgs& a, int seg, int 
 #pragma unroll
         for (int u = 0; u < kAhead; ++u) {
           if (s0 + u >= steps) break;
-          sum += e[u] & kIsMember ? g[u] : 0.f;
+          sum += __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, g[u]) & (uint32_t)((int)e[u] >> 31));   // (no member: zero, whatever is there)
           const uint32_t all = __builtin_amdgcn_readfirstlane(e[u]);   // (the first of a step is a member)
           if (all & kLastStep) {
             const int j = all >> 24 & 63;
             const float d = add_quarters(sum) * __builtin_bit_cast(float, __builtin_amdgcn_readlane(inv, j));
             dot[j >> 2] = quarter == (j & 3) ? d : dot[j >> 2];
-            if (first && mine == j) sm.own[p] = d;
+            with_own = mine == j ? d : with_own;
             sum = 0.f;
           }
         }
       }
+    if (first && sm.start[mine] != kUnmoved) sm.own[p] = with_own;
     __syncthreads();
     // |c|^2 = mean over the members of their products with the centroid: eight lanes per cluster, a fixed tree
     const int j = tid >> 3;
@@ -638,8 +641,8 @@ __device__ __forceinline__ void choose_survivors(const TbeArgs& a, int seg, int 
     // members of every cluster; a cluster without any keeps its basis
     int rank = 0;
     if (first) {
-      for (int w = 0; w < (p >> 5); ++w) rank += __popc(sm.next[mine][w]);
-      rank += __popc(sm.next[mine][p >> 5] & ((1u << (p & 31)) - 1u));
+#pragma unroll
+      for (int w = 0; w < kWords; ++w) rank += __popc(sm.next[mine][w] & (w < (p >> 5) ? ~0u : (w == (p >> 5) ? (1u << (p & 31)) - 1u : 0u)));
     }
     if (wave == W - 1) {
       if (lane == 0) sm.vote[~it & 1] = 0;
@@ -659,12 +662,7 @@ __device__ __forceinline__ void choose_survivors(const TbeArgs& a, int seg, int 
       }
       const bool moved = m > 0 && differs;
       const int fours = moved ? (m + 3) >> 2 : 0;
-      int upto = fours;
-#pragma unroll
-      for (int d = 1; d < 64; d <<= 1) {
-        const int o = __shfl_up(upto, d, 64);
-        if (lane >= d) upto += o;
-      }
+      const int upto = wave_scan(fours, [](int x, int y) { return x + y; });
       const int from = 4 * (upto - fours);
       sm.count[lane] = m;
       sm.start[lane] = moved ? (uint32_t)from : kUnmoved;
@@ -707,12 +705,7 @@ __device__ __forceinline__ void choose_survivors(const TbeArgs& a, int seg, int 
   int size = 0;                               // of cluster `lane`, and where its members begin
 #pragma unroll
   for (int w = 0; w < kWords; ++w) size += __popc(sm.basis[lane][w]);
-  int begin = size;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const int o = __shfl_up(begin, d, 64);
-    if (lane >= d) begin += o;
-  }
+  int begin = wave_scan(size, [](int x, int y) { return x + y; });
   const int total = __builtin_amdgcn_readlane(begin, 63);
   begin -= size;
   for (int j = wave; j < k; j += W) {
