@@ -1299,68 +1299,93 @@ struct CutList {
     }
   }
 };
-__device__ __forceinline__ void sort_cut(const PlanArgs& a, const CutList& l, int seq, long long* keys) {
-  const int lane = threadIdx.x & 63, n = l.n;
+// M lists side by side: what a wave waits for is LDS, five times, whatever there is to do.
+template <int M>
+__device__ __forceinline__ void sort_cuts(const PlanArgs& a, const CutList (&l)[M], int seq, long long (*keys)[kTbeMaxTokens]) {
+  const int lane = threadIdx.x & 63;
   auto settle = [] {   // (a wave's LDS operations happen in order)
     __builtin_amdgcn_wave_barrier();
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   };
-  uint32_t* const words = (uint32_t*)keys;
-  words[lane] = 0u;
-  int rank[kPT] = {}, first = 0x7FFFFFFF;
+  int rank[M][kPT] = {};
+  uint32_t at[M][kPT], bit[M][kPT];
+  bool far[M];
 #pragma unroll
-  for (int q = 0; q < kPT; ++q) first = l.pos[q] < first ? l.pos[q] : first;
-  first = 0x7FFFFFFF - last_lane(wave_scan(0x7FFFFFFF - first, [](int x, int y) { return x > y ? x : y; }));   // (of all lanes)
-  settle();
-  bool apart = true;   // close together, and no two alike
+  for (int m = 0; m < M; ++m) {
+    int first = 0x7FFFFFFF;
 #pragma unroll
-  for (int q = 0; q < kPT; ++q)
-    if (lane + 64 * q < n) {
-      const uint32_t at = (uint32_t)l.pos[q] - (uint32_t)first;
-      if (at >= 2048u) apart = false;
-      else if (atomicOr(&words[at >> 5], 1u << (at & 31u)) >> (at & 31u) & 1u) apart = false;
-    }
-  settle();
-  if (__all(apart)) {
-    const int mine = __popc(words[lane]);
-    words[64 + lane] = (uint32_t)(wave_scan(mine, [](int x, int y) { return x + y; }) - mine);
-    settle();
-#pragma unroll
-    for (int q = 0; q < kPT; ++q)
-      if (lane + 64 * q < n) {
-        const uint32_t at = (uint32_t)l.pos[q] - (uint32_t)first;
-        rank[q] = (int)words[64 + (at >> 5)] + __popc(words[at >> 5] & ((1u << (at & 31u)) - 1u));
-      }
-  } else {
-    long long key[kPT];
+    for (int q = 0; q < kPT; ++q) first = l[m].pos[q] < first ? l[m].pos[q] : first;
+    first = 0x7FFFFFFF - last_lane(wave_scan(0x7FFFFFFF - first, [](int x, int y) { return x > y ? x : y; }));   // (of all lanes)
+    far[m] = false;
 #pragma unroll
     for (int q = 0; q < kPT; ++q) {
-      const int i = lane + 64 * q;
-      key[q] = i < n ? (long long)l.pos[q] << 8 | i : 0x7FFFFFFFFFFFFFFFll;
-      keys[i] = key[q];
+      const bool in = lane + 64 * q < l[m].n;
+      at[m][q] = (uint32_t)l[m].pos[q] - (uint32_t)first;
+      far[m] = far[m] || (in && at[m][q] >= 2048u);
+      in && at[m][q] < 2048u ? bit[m][q] = 1u << (at[m][q] & 31u) : (at[m][q] = 32u * lane, bit[m][q] = 0u);   // (who has no token sets nothing, in a word of its own)
     }
-    settle();
-    for (int i = 0; i < n; i += 4) {
-      const long long o[4] = {keys[i], keys[i + 1], keys[i + 2], keys[i + 3]};
+    ((uint32_t*)keys[m])[lane] = 0u;
+  }
+  settle();
+  uint32_t was[M][kPT];
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
+  for (int m = 0; m < M; ++m)
 #pragma unroll
-        for (int q = 0; q < kPT; ++q) rank[q] += o[e] < key[q];
-    }
+    for (int q = 0; q < kPT; ++q) was[m][q] = atomicOr((uint32_t*)keys[m] + (at[m][q] >> 5), bit[m][q]);
+  settle();
+#pragma unroll
+  for (int m = 0; m < M; ++m) {
+    const int mine = __popc(((uint32_t*)keys[m])[lane]);
+    ((uint32_t*)keys[m])[64 + lane] = (uint32_t)(wave_scan(mine, [](int x, int y) { return x + y; }) - mine);
   }
   settle();
 #pragma unroll
-  for (int q = 0; q < kPT; ++q)
-    if (lane + 64 * q < n) {
-      a.tok_handle[l.lo + rank[q]] = l.h[q];
-      a.tok_seq[l.lo + rank[q]] = seq;
+  for (int m = 0; m < M; ++m)
+#pragma unroll
+    for (int q = 0; q < kPT; ++q) {
+      const uint32_t* const words = (const uint32_t*)keys[m] + (at[m][q] >> 5);
+      rank[m][q] = (int)words[64] + __popc(words[0] & (bit[m][q] - 1u));
     }
+#pragma unroll
+  for (int m = 0; m < M; ++m) {
+    uint32_t twice = 0;
+#pragma unroll
+    for (int q = 0; q < kPT; ++q) twice |= was[m][q] & bit[m][q];
+    const int n = l[m].n;
+    if (!__all(!far[m] && twice == 0)) {   // not close together, or two alike
+      settle();
+      long long key[kPT];
+#pragma unroll
+      for (int q = 0; q < kPT; ++q) {
+        const int i = lane + 64 * q;
+        key[q] = i < n ? (long long)l[m].pos[q] << 8 | i : 0x7FFFFFFFFFFFFFFFll;
+        keys[m][i] = key[q];
+        rank[m][q] = 0;
+      }
+      settle();
+      for (int i = 0; i < n; i += 4) {
+        const long long o[4] = {keys[m][i], keys[m][i + 1], keys[m][i + 2], keys[m][i + 3]};
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int q = 0; q < kPT; ++q) rank[m][q] += o[e] < key[q];
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < kPT; ++q)
+      if (lane + 64 * q < n) {
+        a.tok_handle[l[m].lo + rank[m][q]] = l[m].h[q];
+        a.tok_seq[l[m].lo + rank[m][q]] = seq;
+      }
+  }
+  settle();
 }
 
-// Up to this many cuts a sequence, the workgroup that deals out a sequence's tokens sorts its lists as well, four for each of its sixteen waves at
-// most, which takes no longer than a launch of its own with a wave for every cut; beyond it would.  The plan, us, with a launch for the sort (by keys) / so: 32 sequences of
-// 10 cuts of 64 to 192 tokens fill and sort 8.8 + 9.7 / 13.2, 256 of 16 cuts of 128 29.0 / 20.8, 256 of 7 23.2 / 17.6, 1 of 32 cuts of 200 32.2 / 27.2; of 64 cuts, 32 of
-// 128 tokens 34.9 / 34.3, 1 of 200 39.4 / 40.1.
+// Up to this many cuts a sequence, the workgroup that deals out a sequence's tokens sorts its lists as well, two rounds of two for each of its sixteen waves at
+// most.  The bound is the caller's, which is all that the host knows.  Where a sequence has few cuts that saves a launch, where it has the 64 that are allowed a launch with a
+// wave for every cut would be faster; beyond that it is taken.  The plan, us, with lists sorted by keys in a launch / here / with a launch and rows of bits: 256 sequences of
+// 16 cuts of 128 tokens 28 / 20.9 / 25, 32 of 10 cuts of 64 to 192 29.5 / 23.5 / 24.4, 1 of 32 cuts of 200 33.5 / 28.3 / 27.4, 1 of 48 40.4 / 37.6 / 34.2, 1 of 64
+// 45.4 / 43.4 / 39.1, 32 of 64 cuts of 128 35.9 / 35.6 / 33.5.  (One list at a time: 1 of 64 46.0, 32 of 64 36.7; two also where a wave has one: 0.5 more.)
 constexpr int kSortHere = 64;
 
 template <bool SORT>
@@ -1447,30 +1472,45 @@ __global__ __launch_bounds__(kPlanThreads) void tbe_fill_kernel(thinkv_view v, P
     a.tok_handle[at] = h;
   });
   if constexpr (SORT) {
-    __shared__ __attribute__((aligned(16))) long long s_key[kPlanThreads / 64][kTbeMaxTokens];
+    constexpr int kWaves = kPlanThreads / 64;
+    __shared__ __attribute__((aligned(16))) long long s_key[kWaves][2][kTbeMaxTokens];
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     __syncthreads();
-    CutList l, next = {};
-    if (wave < n_cuts) l.load(a, s_off[wave], s_fill[wave]);
-    for (int cu = wave; cu < n_cuts; cu += kPlanThreads / 64) {
-      const int after = cu + kPlanThreads / 64;
-      if (after < n_cuts) next.load(a, s_off[after], s_fill[after]);
-      sort_cut(a, l, seq, s_key[wave]);
-      l = next;
+    if (n_cuts <= kWaves) {   // a list a wave
+      CutList l[1];
+      if (wave < n_cuts) {
+        l[0].load(a, s_off[wave], s_fill[wave]);
+        sort_cuts(a, l, seq, s_key[wave]);
+      }
+      return;
+    }
+    auto load = [&](CutList (&l)[2], int cu) {
+      l[0].load(a, s_off[cu], s_fill[cu]);
+      const bool two = cu + kWaves < n_cuts;
+      l[1].load(a, two ? s_off[cu + kWaves] : 0, two ? s_fill[cu + kWaves] : 0);
+    };
+    CutList l[2], next[2];
+    if (wave < n_cuts) load(l, wave);
+    for (int cu = wave; cu < n_cuts; cu += 2 * kWaves) {
+      const int after = cu + 2 * kWaves;
+      if (after < n_cuts) load(next, after);
+      sort_cuts(a, l, seq, s_key[wave]);
+      l[0] = next[0];
+      l[1] = next[1];
     }
   }
 }
 
 // one wave per cut of the dense lists
 __global__ __launch_bounds__(256) void tbe_sort_kernel(PlanArgs a) {
-  __shared__ __attribute__((aligned(16))) long long s_key[4][kTbeMaxTokens];
+  __shared__ __attribute__((aligned(16))) long long s_key[4][1][kTbeMaxTokens];
   const int wave = threadIdx.x >> 6;
   const int cu = blockIdx.x * 4 + wave;
   if (cu >= a.counts[0]) return;   // the waves do not meet
   const int lo = a.seg_offset[cu];
-  CutList l;
-  l.load(a, lo, a.seg_offset[cu + 1] - lo);
-  sort_cut(a, l, a.st_cut_seq[cu], s_key[wave]);
+  CutList l[1];
+  l[0].load(a, lo, a.seg_offset[cu + 1] - lo);
+  sort_cuts(a, l, a.st_cut_seq[cu], s_key[wave]);
 }
 
 

@@ -93,7 +93,7 @@ def test_tbe_plan_of_many_sequences_into_short_lists(share_seg, share_tok, max_c
 
 @pytest.mark.parametrize("max_cuts", [1, 16, 17, 64, 65])
 def test_tbe_plan_sorts_lists_of_long_segments(max_cuts):
-    """lists of up to 250 tokens, sorted by the workgroup of their sequence (a wave has one to four of them) or, from 65 cuts on, by a launch of its own"""
+    """lists of up to 250 tokens, sorted by the workgroup of their sequence (a wave has one, or one or two pairs of them) or, from 65 cuts on, by a launch of its own"""
     test_tbe_plan_over_many_segments(250, None, 0, max_cuts, 2048, 1 << 16)
     test_tbe_plan_over_many_segments(250, [1, 0, 1], 0, max_cuts, 60, 1 << 16)
 
@@ -102,11 +102,22 @@ def test_tbe_plan_sorts_lists_of_long_segments(max_cuts):
 @pytest.mark.parametrize("max_cuts", [20, 256])
 def test_tbe_plan_of_spread_and_of_equal_positions(num, den, max_cuts):
     """lists whose positions are further apart than the row of bits reaches, close to that, or (two tokens to a position: in either order) not all different"""
+    _lists_of(np.arange(1840) * num // den, 8, max_cuts)
+
+
+@pytest.mark.parametrize("odd,even", [(40, 1), (1, 40), (0.5, 9), (9, 0.5), (9, 9)])
+@pytest.mark.parametrize("cuts", [17, 23, 32, 33, 48])
+def test_tbe_plan_of_lists_sorted_in_pairs(odd, even, cuts):
+    """more cuts than waves, which take two lists at once: either of the two further apart than the row reaches, or with two tokens to a position"""
+    step = np.repeat(np.where(np.arange(cuts + 1) // 16 % 2 == 1, odd, even), 230)
+    _lists_of(np.concatenate([[0], np.cumsum(step)[:-1]]).astype(np.int64), cuts + 1, 64)
+
+
+def _lists_of(pos, width, max_cuts):
     from paper_2510_01290_amd import binding as B
-    n, width = 1840, 8
-    c = B.Cache(1, 2, 1, 64, (8, 2, 4), 1, 200, [400] * 3)
+    n = len(pos)
+    c = B.Cache(1, 2, 1, 64, (8, 2, 4), 1, n // 16 + 4, [n // 16 + 8] * 3)
     rng = np.random.default_rng(7)
-    pos = np.arange(n) * num // den
     kv = torch.randn((n, 1, 64), device="cuda:0").half()
     ten = lambda x, t: torch.tensor(np.ascontiguousarray(x), dtype=t, device="cuda:0")
     h = torch.empty(n, dtype=torch.int32, device="cuda:0")
@@ -114,8 +125,8 @@ def test_tbe_plan_of_spread_and_of_equal_positions(num, den, max_cuts):
     of = {int(a): int(p) for a, p in zip(h.cpu(), pos)}
     assert len(of) == n
     start = np.zeros((1, width), np.int32)
-    start[0] = np.arange(width) * 230 * num // den
-    got = _device_plan(c, 0, [0], start, np.zeros((1, width), np.uint8), np.array([width], np.int32), [1], 10 ** 6, max_cuts, 64, 4096, seg_count=np.zeros((1, width), np.int32))
+    start[0] = pos[np.arange(width) * 230]
+    got = _device_plan(c, 0, [0], start, np.zeros((1, width), np.uint8), np.array([width], np.int32), [1], 10 ** 6, max_cuts, 64, 1 << 14, seg_count=np.zeros((1, width), np.int32))
     n_seg, n_tok = got["counts"].tolist()
     assert n_seg == width - 1 and n_tok == 230 * (width - 1)
     for i in range(n_seg):
