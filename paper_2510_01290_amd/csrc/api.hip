@@ -171,11 +171,12 @@ static ItemSizing size_stream(const thinkv_config& c, int B, int max_ctx_pages, 
 // attends what is visible with an hg-th of its waves a head.  As many heads to a workgroup as leave a workgroup for every compute
 // unit (fewer repeated scans), and, where even one head a workgroup does not, several items to a head.  How many follows from the
 // two things an item spends its time on.  What is visible: the window's tokens lie in as few pages as hold them, or, where they
-// took freed slots, in a page each, so above 512 tokens an item per 128 of them (2 x 8 heads, 16k tokens, window 1,024, a third
-// of the slots reused, when whole pages were attended: 38.5 us with an item per 512 tokens, 27.7 per 256, 21.9 per 128; all in fresh pages 19.4,
-// 19.3, 20.0).
-// And the scan: above 6,144 pages an item per 2,048 of them (8 x 8 heads, window 128: 131k tokens 24.1 us with one item, now 17.8,
-// 262k 35.0 and 22.1; below, the merge launch costs what the shorter scan gains).
+// took freed slots, a few to a page all over the lists, so above 512 tokens an item per 128 of them.  2 x 8 heads of 128, 16k tokens, window 1,024, us with an item per 512
+// tokens / 256 / 128: a third of the slots reused once 27.3 / 22.9 / 20.5, four times 22.6 / 19.1 / 17.7, heads of 64 23.7 / 20.3 / 18.1; all in fresh pages, where the
+// last item has everything, 18.9 / 18.7 / 19.2, and 15.0 with one item a head, which takes 24.7 in reused slots.
+// And the scan: above 6,144 pages an item per 2,048 of them (8 x 8 heads of 128, window 128: 131k tokens 23.9 us with one item, 16.8 so,
+// 262k 36.9 and 21.8; heads of 64 20.0 and 17.3, 28.6 and 20.0).  An item per 1,024 above 3,072 gains at head_dim 128 (8 x 65k 17.4 and 14.9) and loses the merge launch at 64 (8 x 50k
+// 13.4 and 15.8), where a workgroup scans half as many pages again at a time, and with many heads (16 x 56k 16.9 and 18.0).
 static ItemSizing size_window(const thinkv_config& c, int B, int max_ctx_pages, int window, int* heads_per_group) {
   const int64_t heads = (int64_t)B * c.n_kv_heads, cus = compute_units();
   int hg = 1;

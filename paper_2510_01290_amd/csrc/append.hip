@@ -152,8 +152,10 @@ __device__ inline int token_bound(const int32_t* __restrict__ tok_seq, int n_tok
 
 constexpr int kKeep = 4;        // pages of a type a thread keeps the masks of (1,024 pages a list by 256 threads); longer lists are read again
 constexpr int kWindow = 4096;   // tokens ranked at a time
-// With more tokens than that per sequence of the view the plan takes 512 threads a sequence.  (Fewer: the threads without a token only cost: 256 sequences, five
-// tokens each, with their eviction, 19.9 us by 256 threads and 20.5 by 512.)
+// With more tokens than that per sequence slot of the view the plan takes 512 threads a sequence.  Fewer: the threads without a token only cost: 256 sequences, five
+// tokens each, with their eviction, 19.9 us by 256 threads and 20.5 by 512.  The host does not know how many of the sequences bring tokens, so a prompt that comes
+// alone into a view of many slots keeps 256: with the reset, 256 threads / 512, one of 300 tokens in 64 slots 22.2 / 18.3, of 8k 49.1 / 44.2, in 256 slots 50.3 / 45.3; but
+// 64 prompts of 40 tokens in 256 slots 24.4 / 25.1, 4 of 64 in 64 18.0 / 18.7.
 constexpr int kLongPrompts = 256;
 constexpr int kEvAhead = 2;     // evictions of a call a thread holds before it applies the first
 // (The plan is a chain of dependent loads: with handles, page counts, token ranges and last pages asked for one after the other behind

@@ -290,7 +290,8 @@ struct PairIds {
     if (idx >= 0 && idx < room) stat[(int64_t)idx * kPage + (lane & (kPage - 1))] = u;
   }
 };
-// ... of a pair whose "pages" are made of quads of slots (SlotQuads)
+// ... of a pair whose "pages" are made of quads of slots (SlotQuads).  (Two stores, as above, of which the ring's waits know nothing and which they therefore
+// wait for too; one counted store, as full attention has it, has not been tried in windows.)
 struct QuadIds {
   uint32_t live_a, live_b;
   int at_a, at_b;   // STAT: where the lane's tokens stand among the type's pooled scores (negative: nowhere)

@@ -26,7 +26,7 @@
 // whole: segments of more tokens (a matrix of up to 132 KB), a workgroup per compute unit that does both; and, alone, all segments of up to 512
 // channels.
 // 314 segments of ~110 tokens, 1,024 channels, us: keys to memory and a workgroup of a whole compute unit per segment (its
-// 139 KB of LDS made that 1.2 rounds of workgroups) 37 + 177; now 66 + 58 (and 6 for whole, which finds nothing).  gram is bound by vector
+// 139 KB of LDS made that 1.2 rounds of workgroups) 37 + 177; now 67 + 56 (and 5 for whole, which finds nothing).  gram is bound by vector
 // instructions (four a number to unpack and split it) and by 141 MB of rows; kmeans by its longest segments' iterations (choose_survivors), the parts
 // (5 to 10), and the 54 MB of centroids (9 to 35, the rows they are made of are 141 MB).
 // The products run on the matrix cores; a dequantised key does not
@@ -802,7 +802,8 @@ __global__ __launch_bounds__(64 * kKmWaves) __attribute__((amdgpu_waves_per_eu(6
 }
 
 // The segments that kmeans leaves out: a workgroup of sixteen waves, with the LDS of a whole compute unit, makes the matrix and iterates.
-// Where there are none, the launch is 6 us.  (A segment a lane to find them: no less, and five more registers spilled.)  NARROW: it is the only
+// Where there are none, the launch is 5 us.  (A segment a lane to find them: no less, and five more registers spilled.  The narrow form at head_dim 128 spills five,
+// six in the paper's formats: what follows from the thread's number, read back once a tile; the other forms none.)  NARROW: it is the only
 // kernel, for all segments and for the rows of tokens that are not clustered.
 template <int D, bool FP, bool NARROW>
 __global__ __launch_bounds__(64 * kWholeWaves) void tbe_whole_kernel(thinkv_view v, TbeArgs a) {
